@@ -114,6 +114,14 @@ __device__ __forceinline__ long long partner(long long v)
     return ((long long)hi << 32) | (unsigned int)lo;
 }
 
+// LDS written by some lanes of a wavefront is read by others of the same wavefront: LDS operations of a wavefront
+// complete in order, so this only keeps the compiler from moving them across (no instruction)
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 struct OpMin { template <class T> __device__ T operator()(T a, T b) const { return a < b ? a : b; } };
 struct OpMax { template <class T> __device__ T operator()(T a, T b) const { return a > b ? a : b; } };
 struct OpAdd { template <class T> __device__ T operator()(T a, T b) const { return a + b; } };

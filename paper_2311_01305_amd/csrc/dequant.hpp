@@ -1,0 +1,120 @@
+// De-quantisation of packed 4-bit / 3-bit weight codes to binary16, shared by the weight-only kernels:
+// w~_h = RN16((u - Z) RN16(Step)) (Eq. 1 with the weight operand in binary16).
+#pragma once
+#include "common.hpp"
+
+namespace aweq {
+namespace wonly {
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ f16x2 as_h2(uint32_t u) { return __builtin_bit_cast(f16x2, u); }
+__device__ __forceinline__ uint32_t as_u32(f16x2 h) { return __builtin_bit_cast(uint32_t, h); }
+
+// 32 consecutive codes of one row as loaded: 16 (INT4) or 12 (INT3) bytes
+template <int BITS> struct RawCodes { uint32_t w[BITS == 4 ? 4 : 3]; };
+
+template <int BITS>
+__device__ __forceinline__ RawCodes<BITS> load_codes(const uint8_t* p)
+{
+    RawCodes<BITS> rc;
+    if constexpr (BITS == 4) {
+        const v4i w = *reinterpret_cast<const v4i*>(p);
+        rc.w[0] = (uint32_t)w[0]; rc.w[1] = (uint32_t)w[1]; rc.w[2] = (uint32_t)w[2]; rc.w[3] = (uint32_t)w[3];
+    } else {
+        // rows of 3-bit codes start on 4-byte boundaries only
+        const uint32_t* p32 = reinterpret_cast<const uint32_t*>(p);
+        rc.w[0] = p32[0]; rc.w[1] = p32[1]; rc.w[2] = p32[2];
+    }
+    return rc;
+}
+
+// Step and Z of one slice, ready for dequant8.  A code field at bit b of a binary16 significand whose
+// exponent makes that bit worth 1 reads as 2^(10 - b) + u, so subtracting 2^(10 - b) + Z leaves u - Z
+// (exact: both are integers below 2048), and no shift is needed to bring the field to bit 0.
+template <int BITS>
+struct Scale {
+    f16x2 step, z0, z1, z2;   // Step; 2^(10 - b) + Z for the field positions in use (b = 0, 4 / b = 0, 3, 6)
+    float step_f;
+    int z;
+    bool packed;              // |Z| small enough for the packed path
+    __device__ __forceinline__ void set(float s, int zero)
+    {
+        const _Float16 sh = (_Float16)s;
+        step_f = (float)sh;
+        z = zero;
+        packed = zero >= -1024 && zero <= 1024;
+        const _Float16 zh = (_Float16)(float)zero;
+        const f16x2 zz = {zh, zh};
+        step = f16x2{sh, sh};
+        z0 = as_h2(0x64006400u) + zz;                                       // 1024 + Z
+        z1 = as_h2(BITS == 4 ? 0x54005400u : 0x58005800u) + zz;             // 64 + Z / 128 + Z
+        z2 = BITS == 4 ? z1 : as_h2(0x4c004c00u) + zz;                      // 16 + Z
+    }
+};
+
+// The 8 codes k = 8 d .. 8 d + 7 of the 32 as four binary16 pairs (k, k + 4): (0,4) (1,5) (2,6) (3,7),
+// the order the fields come out of the packed formats in (a caller that needs natural order permutes).
+// 13 (INT4) / 16 (INT3) packed operations per 8 codes.
+template <int BITS>
+__device__ __forceinline__ void dequant8_pairs(const RawCodes<BITS>& rc, int d, const Scale<BITS>& s, uint32_t o[4])
+{
+    if constexpr (BITS == 4) {
+        const uint32_t w = rc.w[d], v = w >> 8;
+        o[0] = as_u32((as_h2((w & 0x000f000fu) | 0x64006400u) - s.z0) * s.step);
+        o[1] = as_u32((as_h2((w & 0x00f000f0u) | 0x54005400u) - s.z1) * s.step);
+        o[2] = as_u32((as_h2((v & 0x000f000fu) | 0x64006400u) - s.z0) * s.step);
+        o[3] = as_u32((as_h2((v & 0x00f000f0u) | 0x54005400u) - s.z1) * s.step);
+    } else {
+        // 24 bits of the stream; codes 4 .. 7 (bits 12 .. 23) move up by 4, so that both halves hold
+        // four fields at bits 0, 3, 6, 9
+        const uint32_t f = d == 0 ? rc.w[0] : d == 1 ? __builtin_amdgcn_alignbit(rc.w[1], rc.w[0], 24)
+                         : d == 2 ? __builtin_amdgcn_alignbit(rc.w[2], rc.w[1], 16) : rc.w[2] >> 8;
+        const uint32_t g = (f & 0x0fffu) | ((f << 4) & 0x0fff0000u), h = g >> 9;
+        o[0] = as_u32((as_h2((g & 0x00070007u) | 0x64006400u) - s.z0) * s.step);
+        o[1] = as_u32((as_h2((g & 0x00380038u) | 0x58005800u) - s.z1) * s.step);
+        o[2] = as_u32((as_h2((g & 0x01c001c0u) | 0x4c004c00u) - s.z2) * s.step);
+        o[3] = as_u32((as_h2((h & 0x00070007u) | 0x64006400u) - s.z0) * s.step);
+    }
+}
+
+// the same pairs for any zero point, through binary32
+template <int BITS>
+__device__ __forceinline__ void dequant8_pairs_any(const RawCodes<BITS>& rc, int d, const Scale<BITS>& s, uint32_t o[4])
+{
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        int c[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int k = 8 * d + q + 4 * e;
+            if constexpr (BITS == 4) c[e] = (int)((rc.w[k >> 3] >> (4 * (k & 7))) & 15u);
+            else {
+                const int bit = 3 * k, idx = bit >> 5, sh = bit & 31;
+                const uint32_t lo = rc.w[idx], hi = idx + 1 < 3 ? rc.w[idx + 1] : 0u;
+                c[e] = (int)(__builtin_amdgcn_alignbit(hi, lo, sh) & 7u);
+            }
+        }
+        const f16x2 h = {(_Float16)((float)(c[0] - s.z) * s.step_f), (_Float16)((float)(c[1] - s.z) * s.step_f)};
+        o[q] = as_u32(h);
+    }
+}
+
+// pairs (k, k + 4) -> natural order (and back: the permutation of a 16-byte chunk of 8 halves is its own kind)
+__device__ __forceinline__ v4i natural_order(const uint32_t o[4])
+{
+    return v4i{(int)__builtin_amdgcn_perm(o[1], o[0], 0x05040100u),    // k0 k1
+               (int)__builtin_amdgcn_perm(o[3], o[2], 0x05040100u),    // k2 k3
+               (int)__builtin_amdgcn_perm(o[1], o[0], 0x07060302u),    // k4 k5
+               (int)__builtin_amdgcn_perm(o[3], o[2], 0x07060302u)};   // k6 k7
+}
+__device__ __forceinline__ v4i pair_order(v4i x)   // (k0 k1) (k2 k3) (k4 k5) (k6 k7) -> (0,4) (1,5) (2,6) (3,7)
+{
+    return v4i{(int)__builtin_amdgcn_perm((uint32_t)x[2], (uint32_t)x[0], 0x05040100u),
+               (int)__builtin_amdgcn_perm((uint32_t)x[2], (uint32_t)x[0], 0x07060302u),
+               (int)__builtin_amdgcn_perm((uint32_t)x[3], (uint32_t)x[1], 0x05040100u),
+               (int)__builtin_amdgcn_perm((uint32_t)x[3], (uint32_t)x[1], 0x07060302u)};
+}
+
+}  // namespace wonly
+}  // namespace aweq

@@ -21,13 +21,13 @@
 // wavefront's loads retiring in issue order, "at most the 4 newest outstanding" at the end of a
 // stage means everything the next stage reads has landed.  The MFMA is issued with the weight
 // fragment first so that a lane ends with four consecutive n of one token.
-#include "common.hpp"
+#include "dequant.hpp"
+#include "gemm_wonly_small.hpp"
 #include <type_traits>
 
 namespace aweq {
 namespace wonly {
 
-typedef int v4i __attribute__((ext_vector_type(4)));
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef float v4f __attribute__((ext_vector_type(4)));
@@ -66,61 +66,6 @@ __device__ __forceinline__ void dma16(const char* sbase, uint32_t voff, uint32_t
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(voff), "s"(sbase) : "memory");
 }
 
-__device__ __forceinline__ f16x2 as_h2(uint32_t u) { return __builtin_bit_cast(f16x2, u); }
-__device__ __forceinline__ uint32_t as_u32(f16x2 h) { return __builtin_bit_cast(uint32_t, h); }
-
-// 32 consecutive codes of one row (the lane's half of a stage row), as loaded
-template <int BITS> struct RawCodes { uint32_t w[BITS == 4 ? 4 : 3]; };
-
-// de-quantise the 8 codes k = 8 d .. 8 d + 7 of the lane's 32 into one 16-byte chunk (natural k order)
-template <int BITS>
-__device__ __forceinline__ v4i dequant8(const RawCodes<BITS>& rc, int d, float step_h, int z, bool fast)
-{
-    uint32_t o[4];
-    if (fast) {
-        const f16x2 zs = as_h2(0x64006400u) + f16x2{(_Float16)z, (_Float16)z};       // 1024 + Z, exact
-        const f16x2 sp = {(_Float16)step_h, (_Float16)step_h};
-        if constexpr (BITS == 4) {
-            // (w >> 4 i) & 0x000f000f holds codes i and i + 4 of the dword in its two halves
-            f16x2 h[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) h[i] = (as_h2(((rc.w[d] >> (4 * i)) & 0x000f000fu) | 0x64006400u) - zs) * sp;
-            o[0] = __builtin_amdgcn_perm(as_u32(h[1]), as_u32(h[0]), 0x05040100u);  // k0 k1
-            o[1] = __builtin_amdgcn_perm(as_u32(h[3]), as_u32(h[2]), 0x05040100u);  // k2 k3
-            o[2] = __builtin_amdgcn_perm(as_u32(h[1]), as_u32(h[0]), 0x07060302u);  // k4 k5
-            o[3] = __builtin_amdgcn_perm(as_u32(h[3]), as_u32(h[2]), 0x07060302u);  // k6 k7
-        } else {
-            // codes 2 j, 2 j + 1 are the 6 bits at bit 6 j of the 96-bit stream
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int j = 4 * d + q, bit = 6 * j, idx = bit >> 5, sh = bit & 31;
-                const uint32_t lo = rc.w[idx], hi = idx + 1 < 3 ? rc.w[idx + 1] : 0u;
-                const uint32_t f = __builtin_amdgcn_alignbit(hi, lo, sh);
-                const uint32_t u2 = ((f & 0x38u) << 13) | ((f & 7u) | 0x64006400u);
-                o[q] = as_u32((as_h2(u2) - zs) * sp);
-            }
-        }
-    } else {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            int c[2];
-#pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                const int k = 8 * d + 2 * q + e;
-                if constexpr (BITS == 4) c[e] = (int)((rc.w[k >> 3] >> (4 * (k & 7))) & 15u);
-                else {
-                    const int bit = 3 * k, idx = bit >> 5, sh = bit & 31;
-                    const uint32_t lo = rc.w[idx], hi = idx + 1 < 3 ? rc.w[idx + 1] : 0u;
-                    c[e] = (int)(__builtin_amdgcn_alignbit(hi, lo, sh) & 7u);
-                }
-            }
-            const f16x2 h = {(_Float16)((float)(c[0] - z) * step_h), (_Float16)((float)(c[1] - z) * step_h)};
-            o[q] = as_u32(h);
-        }
-    }
-    return v4i{(int)o[0], (int)o[1], (int)o[2], (int)o[3]};
-}
-
 // one thread per 32 consecutive codes of a row: 16 (INT4) or 12 (INT3) bytes in, 64 bytes out
 template <int BITS>
 __global__ __launch_bounds__(256) void dequant_weight_h_kernel(
@@ -132,21 +77,18 @@ __global__ __launch_bounds__(256) void dequant_weight_h_kernel(
     if (id >= N * per_row) return;
     const int64_t n = id / per_row, kk = id % per_row;
     const uint8_t* p = codes + n * (K * BITS / 8) + kk * (32 * BITS / 8);
-    RawCodes<BITS> rc;
-    if constexpr (BITS == 4) {
-        const v4i w = *reinterpret_cast<const v4i*>(p);
-        rc.w[0] = (uint32_t)w[0]; rc.w[1] = (uint32_t)w[1]; rc.w[2] = (uint32_t)w[2]; rc.w[3] = (uint32_t)w[3];
-    } else {
-        const uint32_t* p32 = reinterpret_cast<const uint32_t*>(p);
-        rc.w[0] = p32[0]; rc.w[1] = p32[1]; rc.w[2] = p32[2];
-    }
+    const RawCodes<BITS> rc = load_codes<BITS>(p);
     const int64_t pi = group < 0 ? 0 : (group == 0 ? n : n * (K / group) + (kk * 32) / group);
-    const float step_h = (float)(_Float16)step[pi];   // Step as binary16
-    const int z = zero[pi];
-    const bool fast = z >= -1024 && z <= 1024;
+    Scale<BITS> s;
+    s.set(step[pi], zero[pi]);
     v4i* dst = reinterpret_cast<v4i*>(W + n * K + kk * 32);
 #pragma unroll
-    for (int d = 0; d < 4; ++d) dst[d] = dequant8<BITS>(rc, d, step_h, z, fast);
+    for (int d = 0; d < 4; ++d) {
+        uint32_t o[4];
+        if (s.packed) dequant8_pairs<BITS>(rc, d, s, o);
+        else dequant8_pairs_any<BITS>(rc, d, s, o);
+        dst[d] = natural_order(o);
+    }
 }
 
 #define SB() __builtin_amdgcn_sched_barrier(0)
@@ -450,6 +392,16 @@ extern "C" int aweq_wonly_gemm(const void* X_hat, int64_t T, int64_t K, int64_t 
     if (tiles_m * tiles_n > (1ll << 30)) return AWEQ_ERR_SHAPE;
     hipStream_t st = as_stream(stream);
 
+    // few tokens: straight from the codes (both forms measured in gemm_wonly_small.hip; at 512 tokens the
+    // de-quantising pass and the tiled GEMM are ahead)
+    if (T <= wonly::kSmallTokens) {
+        wonly::SmallArgs a;
+        a.X = reinterpret_cast<const _Float16*>(X_hat); a.codes = reinterpret_cast<const uint8_t*>(codes);
+        a.step = step_w; a.zero = zero_w; a.bias = bias; a.out = out; a.ldx = ldx; a.ldo = ldo; a.T = T; a.N = N; a.K = K;
+        a.scale_pitch = group < 0 ? 0u : group == 0 ? 1u : (uint32_t)(K / group);
+        a.group_magic = group <= 0 ? 0u : (uint32_t)cdiv(1ll << 31, group / 32);
+        return wonly::launch_small(a, bits, group, out_dt == AWEQ_F16, st);
+    }
     // the binary16 weight, once
     _Float16* W = reinterpret_cast<_Float16*>(ws);
     const int64_t dq_blocks = cdiv(N * (K / 32), 256);

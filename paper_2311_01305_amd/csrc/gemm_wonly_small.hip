@@ -1,0 +1,278 @@
+// Weight-only forward for few tokens (decoding, small batches): y = X_hat W~^T + b straight from the packed codes.
+//
+// The codes are nearly all the traffic, so they are read once and de-quantised in registers; nothing is written to
+// the workspace.  A workgroup of 8 wavefronts owns 16 NT output channels x 16 TT tokens and splits K between its
+// wavefronts (the partial sums meet in LDS, in a fixed order), so that even one token spreads over N / 16
+// workgroups.  A wavefront works on 256 values of K at a time: per 16 output channels two loads of codes in which
+// 8 lanes cover the 128 (INT4) or 96 (INT3) contiguous bytes of a row, and one load of (Step, Z).  The matrix
+// operand has the row in the lowest lane bits instead (lane l: channel l % 16, values 32 (l / 16) .. + 31 of 128),
+// and loading in that order touches four rows per quad of lanes, which the address unit takes one by one: codes
+// and activations therefore pass through a region of LDS private to the wavefront (no barriers).  The product is
+// v_mfma_f32_16x16x32_f16, whose two operands may enumerate K in any common order: both use the order in which the
+// code fields come out of their packed words.
+//
+// Bound by the read of the codes and, for small layers, by the launch and one round trip to memory.  Measured (INT4,
+// groups of 128, us per call on the device; before = de-quantising the whole weight and a 256 x 256-tiled GEMM):
+//   tokens          1            16           32           64           128          256
+//   4096 x 4096     85.7 ->  5.2  85.8 ->  6.4  86.3 ->  8.3  86.8 -> 10.4  88.2 -> 14.4  87.6 -> 26.5
+//   11008 x 4096     100 -> 10.3   101 -> 12.7   101 -> 15.1   102 -> 27.4   103 -> 42.4   103 -> 81.4
+//   22016 x 8192     312 -> 26.3   310 -> 33.5   312 -> 50.4   320 -> 76.1   329 ->  146   331 ->  263
+// (22016 x 8192 at one token: 101 MB of codes and scales, 3.9 TB/s.)  With the operands loaded straight in the matrix
+// operand's order, and no pass through LDS, the same table began 6.2 / 13.9 / 42.5 for one token.
+#include "dequant.hpp"
+#include "gemm_wonly_small.hpp"
+
+namespace aweq {
+namespace wonly {
+
+typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+constexpr int kSmallThreads = 512;
+constexpr int kSmallWaves = kSmallThreads / kWave;
+constexpr int kChunk = 256;   // values of K a wavefront takes at a time
+
+// LDS per wavefront: 128 values of RX tokens (256 for RX = 4), 256 codes of 16 NT channels (16 bytes per 32 codes)
+constexpr int small_wave_lds(int rx, int nt) { return (rx == 4 ? 4 * 512 : rx * 256) + nt * 16 * 128; }
+
+// FINE: groups that are no multiple of 128 (a lane's 32 codes have one (Step, Z), but the four lanes that share
+// 128 values of a channel may differ)
+template <int BITS, int RX, int NT, bool FINE, bool OUT_F16>
+__global__ __launch_bounds__(kSmallThreads) void gemm_small_kernel(SmallArgs g)
+{
+    constexpr int TT = RX < 16 ? 1 : RX / 16;
+    constexpr int XH = RX == 4 ? 1 : 2;             // activation loads per chunk: whole, or 128 values at a time
+    constexpr int XL = RX == 4 ? 2 : 4 * TT;        // 16-byte loads of activations per lane and time
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    const int r = lane & 15, q = lane >> 4;
+    const int64_t n0 = (int64_t)blockIdx.x * (16 * NT), t0 = (int64_t)blockIdx.y * (16 * TT);
+    const int K = (int)g.K;
+    char* const lx = lds + wave * small_wave_lds(RX, NT);
+    char* const lc = lx + (RX == 4 ? 4 * 512 : RX * 256);
+
+    // codes: lane -> row 8 i + lane / 8 of 16, 32 codes lane % 8 of 256.  Rows past the edge re-read the last valid
+    // row; their results are never stored.  (32-bit offsets from the tile's first row: 64 rows of K <= 2^20 at most)
+    const int c_row = lane >> 3, c_piece = lane & 7;
+    const uint32_t code_pitch = (uint32_t)(K >> 3) * BITS;
+    const uint8_t* const cbase = g.codes + n0 * code_pitch;
+    const int rows_left = (int)min(g.N - n0, (int64_t)(16 * NT)) - 1;
+    uint32_t crow[NT][2];
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) crow[j][i] = (uint32_t)min(16 * j + 8 * i + c_row, rows_left) * code_pitch + c_piece * (4 * BITS);
+    // (Step, Z): lane -> row lane / 4 of 16, {Step, Step, Z, Z} of the chunk's first / second 128 values
+    const uint32_t* const sbase = ((lane & 2) ? reinterpret_cast<const uint32_t*>(g.zero) : reinterpret_cast<const uint32_t*>(g.step)) +
+                                  n0 * g.scale_pitch;
+    uint32_t srow[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) srow[j] = (uint32_t)min(16 * j + (FINE ? r : lane >> 2), rows_left) * g.scale_pitch;
+    // activations: lane -> token 4 i + lane / 16, 8 values lane % 16 of 128 (RX = 4: the second load is the second 128)
+    const _Float16* const xbase = g.X + t0 * g.ldx;
+    const int tokens_left = (int)min(g.T - t0, (int64_t)(16 * TT));
+    const uint32_t xoff = (uint32_t)(lane >> 4) * (uint32_t)g.ldx + (lane & 15) * 8, x_pitch4 = 4u * (uint32_t)g.ldx;
+
+    RawCodes<BITS> rc[NT][2];
+    uint32_t sc[NT];
+    v4i xr[XL];
+    auto load_codes_at = [&](int k) {
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+#pragma unroll
+                for (int e = 0; e < (BITS == 4 ? 4 : 3); ++e) rc[j][i].w[e] = 0u;
+                if (k + c_piece * 32 < K) rc[j][i] = load_codes<BITS>(cbase + (crow[j][i] + (uint32_t)(k >> 5) * (4 * BITS)));
+            }
+            sc[j] = 0u;
+            if constexpr (!FINE) {
+                const int ks = k + (lane & 1) * 128;
+                if (ks < K) sc[j] = sbase[srow[j] + __umulhi((uint32_t)ks >> 4, g.group_magic)];
+            }
+        }
+    };
+    auto load_x_at = [&](int k) {
+#pragma unroll
+        for (int i = 0; i < XL; ++i) {
+            const int row = RX == 4 ? 0 : 4 * i, kk = RX == 4 ? k + 128 * i : k;
+            xr[i] = v4i{0, 0, 0, 0};
+            if (row + (lane >> 4) < tokens_left && kk + (lane & 15) * 8 < K)
+                xr[i] = *reinterpret_cast<const v4i*>(xbase + (xoff + (uint32_t)(row / 4) * x_pitch4 + (uint32_t)kk));
+        }
+    };
+
+    const int fr = RX == 4 ? r & 3 : r;   // (RX = 4: tokens past the fourth repeat the first four, their columns are not stored)
+    v4f acc[TT][NT];
+#pragma unroll
+    for (int i = 0; i < TT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+
+    constexpr int kStride = kSmallWaves * kChunk;
+    int kc = wave * kChunk;
+    if (kc < K) { load_codes_at(kc); load_x_at(kc); }
+    for (; kc < K; kc += kStride) {
+        uint32_t scc[NT];
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            scc[j] = sc[j];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int row = 8 * i + c_row;
+                v4i w = {(int)rc[j][i].w[0], (int)rc[j][i].w[1], (int)rc[j][i].w[2], 0};
+                if constexpr (BITS == 4) w[3] = (int)rc[j][i].w[3];
+                *reinterpret_cast<v4i*>(lc + j * 2048 + row * 128 + ((c_piece ^ (row & 7)) * 16)) = w;
+            }
+        }
+        wave_lds_fence();
+        if (kc + kStride < K) load_codes_at(kc + kStride);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            if (kc + h * 128 >= K) break;
+            if (h < XH) {
+#pragma unroll
+                for (int i = 0; i < XL; ++i) {
+                    const int row = (RX == 4 ? 0 : 4 * i) + (lane >> 4);
+                    *reinterpret_cast<v4i*>(lx + (RX == 4 ? i * 1024 : 0) + row * 256 + (((lane & 15) ^ (row & 15)) * 16)) = pair_order(xr[i]);
+                }
+                wave_lds_fence();
+                const int kx = h + 1 < XH ? kc + 128 : kc + kStride;
+                if (kx < K) load_x_at(kx);
+            }
+            // the operand with fewer tiles stays in registers over the loop on the other
+            auto frag_x = [&](int i, int d) {
+                return __builtin_bit_cast(v8h, *reinterpret_cast<const v4i*>(lx + (RX == 4 ? h * 1024 : i * 4096) + fr * 256 + (((4 * q + d) ^ fr) * 16)));
+            };
+            auto frag_w = [&](int j, uint32_t w[4][4]) {
+                const v4i cw = *reinterpret_cast<const v4i*>(lc + j * 2048 + r * 128 + (((4 * h + q) ^ (r & 7)) * 16));
+                RawCodes<BITS> c;
+#pragma unroll
+                for (int e = 0; e < (BITS == 4 ? 4 : 3); ++e) c.w[e] = (uint32_t)cw[e];
+                Scale<BITS> s;
+                if constexpr (FINE) {
+                    const int k = kc + h * 128 + q * 32;
+                    const int64_t gi = n0 * g.scale_pitch + srow[j] + (k < K ? __umulhi((uint32_t)k >> 4, g.group_magic) : 0u);
+                    s.set(g.step[gi], g.zero[gi]);
+                } else {
+                    s.set(__uint_as_float((uint32_t)__builtin_amdgcn_ds_bpermute((4 * r + h) * 4, (int)scc[j])),
+                          __builtin_amdgcn_ds_bpermute((4 * r + 2 + h) * 4, (int)scc[j]));
+                }
+                if (__all(s.packed)) {
+#pragma unroll
+                    for (int d = 0; d < 4; ++d) dequant8_pairs<BITS>(c, d, s, w[d]);
+                } else {
+#pragma unroll
+                    for (int d = 0; d < 4; ++d) dequant8_pairs_any<BITS>(c, d, s, w[d]);
+                }
+            };
+            auto mul = [&](int i, int j, const uint32_t w[4], v8h x) {
+                const v4i a = {(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, a), x, acc[i][j], 0, 0, 0);
+            };
+            if constexpr (TT <= NT) {
+                v8h x[TT][4];
+#pragma unroll
+                for (int i = 0; i < TT; ++i)
+#pragma unroll
+                    for (int d = 0; d < 4; ++d) x[i][d] = frag_x(i, d);
+#pragma unroll
+                for (int j = 0; j < NT; ++j) {
+                    uint32_t w[4][4];
+                    frag_w(j, w);
+#pragma unroll
+                    for (int d = 0; d < 4; ++d)
+#pragma unroll
+                        for (int i = 0; i < TT; ++i) mul(i, j, w[d], x[i][d]);
+                }
+            } else {
+                uint32_t w[NT][4][4];
+#pragma unroll
+                for (int j = 0; j < NT; ++j) frag_w(j, w[j]);
+#pragma unroll
+                for (int i = 0; i < TT; ++i)
+#pragma unroll
+                    for (int d = 0; d < 4; ++d) {
+                        const v8h x = frag_x(i, d);
+#pragma unroll
+                        for (int j = 0; j < NT; ++j) mul(i, j, w[j][d], x);
+                    }
+            }
+            wave_lds_fence();   // this chunk's reads stay ahead of the next one's writes
+        }
+    }
+
+    // register v of lane l is output channel 4 (l / 16) + v of the 16, token l % 16
+    constexpr int kTiles = TT * NT;
+    float* const red = reinterpret_cast<float*>(lds);   // [wave][TT NT][lane][4]
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < TT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) *reinterpret_cast<v4f*>(red + ((wave * kTiles + i * NT + j) * kWave + lane) * 4) = acc[i][j];
+    __syncthreads();
+    for (int e = threadIdx.x; e < kTiles * kWave; e += kSmallThreads) {
+        const int tile = e / kWave, l = e & (kWave - 1);
+        const int64_t t = t0 + 16 * (tile / NT) + (l & 15), n = n0 + 16 * (tile % NT) + 4 * (l >> 4);
+        if (t >= g.T || n >= g.N) continue;     // N % 4 == 0: all four channels or none
+        v4f o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < kSmallWaves; ++w) o += *reinterpret_cast<const v4f*>(red + ((w * kTiles + tile) * kWave + l) * 4);
+        if (g.bias) o += *reinterpret_cast<const v4f*>(g.bias + n);
+        if constexpr (OUT_F16) {
+            typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+            *reinterpret_cast<h4*>(reinterpret_cast<_Float16*>(g.out) + t * g.ldo + n) =
+                h4{(_Float16)o[0], (_Float16)o[1], (_Float16)o[2], (_Float16)o[3]};
+        } else {
+            *reinterpret_cast<v4f*>(reinterpret_cast<float*>(g.out) + t * g.ldo + n) = o;
+        }
+    }
+}
+
+template <int BITS, int RX, int NT>
+static int launch_tile(const SmallArgs& g, bool fine, bool out_f16, hipStream_t st)
+{
+    constexpr int TT = RX < 16 ? 1 : RX / 16;
+    const dim3 grid((unsigned)cdiv(g.N, 16 * NT), (unsigned)cdiv(g.T, RX));
+    constexpr int work = kSmallWaves * small_wave_lds(RX, NT), red = kSmallWaves * TT * NT * kWave * 16;
+    constexpr int lds = work > red ? work : red;
+    const void* fn = fine ? (out_f16 ? reinterpret_cast<const void*>(gemm_small_kernel<BITS, RX, NT, true, true>)
+                                     : reinterpret_cast<const void*>(gemm_small_kernel<BITS, RX, NT, true, false>))
+                          : (out_f16 ? reinterpret_cast<const void*>(gemm_small_kernel<BITS, RX, NT, false, true>)
+                                     : reinterpret_cast<const void*>(gemm_small_kernel<BITS, RX, NT, false, false>));
+    int dev = 0, cus = 0;
+    if (lds > 65536 && (device_cus(dev, cus) != AWEQ_OK || raise_lds_limit(fn, dev, lds) != AWEQ_OK)) return AWEQ_ERR_LAUNCH;
+    void* args[] = {const_cast<SmallArgs*>(&g)};
+    if (hipLaunchKernel(fn, grid, dim3(kSmallThreads), args, lds, st) != hipSuccess) return AWEQ_ERR_LAUNCH;
+    return launch_status();
+}
+
+template <int BITS>
+static int launch_bits(const SmallArgs& g, bool fine, bool out_f16, hipStream_t st)
+{
+    // Up to 16 tokens the pass is a read of the codes: 16 channels per workgroup until those workgroups fill the chip
+    // 1.3 times over, then 32, which read the tokens half as often (8192 x 8192, one token: 11.9 / 12.2 us with 16 / 32;
+    // 22016 x 8192: 28.3 / 26.3; 11008 x 4096: 10.3 / 11.3; 64 channels lose everywhere)
+    const bool wide = g.N > 12288;
+    if (g.T <= 4) return wide ? launch_tile<BITS, 4, 2>(g, fine, out_f16, st) : launch_tile<BITS, 4, 1>(g, fine, out_f16, st);
+    if (g.T <= 16) return wide ? launch_tile<BITS, 16, 2>(g, fine, out_f16, st) : launch_tile<BITS, 16, 1>(g, fine, out_f16, st);
+    // More tokens, 32 per workgroup: as many channels as give the fewest rounds of workgroups, each weighted with what a
+    // round was measured to take (8192 x 8192, 17 tokens, us: 19 for 512 workgroups of 16 channels, two per compute unit,
+    // 14 for 256; 17.5 for 32 channels and 27 for 64, one per compute unit).  64 tokens per workgroup gain nothing
+    // (64 tokens: 10.4 us at 4096 x 4096 in 32s, 14.0 in 64s; 76 / 75 at 22016 x 8192).
+    const int64_t tm = cdiv(g.T, 32), w1 = cdiv(g.N, 16) * tm, w2 = cdiv(g.N, 32) * tm, w4 = cdiv(g.N, 64) * tm;
+    const double c1 = w1 <= 256 ? 14.0 : 19.0 * (double)cdiv(w1, 512), c2 = 17.5 * (double)cdiv(w2, 256), c4 = 27.0 * (double)cdiv(w4, 256);
+    if (c1 <= c2 && c1 <= c4) return launch_tile<BITS, 32, 1>(g, fine, out_f16, st);
+    if (c2 <= c4) return launch_tile<BITS, 32, 2>(g, fine, out_f16, st);
+    return launch_tile<BITS, 32, 4>(g, fine, out_f16, st);
+}
+
+int launch_small(const SmallArgs& g, int bits, int group, bool out_f16, hipStream_t st)
+{
+    const bool fine = group > 0 && group % 128 != 0;
+    return bits == 4 ? launch_bits<4>(g, fine, out_f16, st) : launch_bits<3>(g, fine, out_f16, st);
+}
+
+}  // namespace wonly
+}  // namespace aweq
