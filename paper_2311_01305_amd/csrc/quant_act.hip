@@ -324,6 +324,80 @@ __global__ __launch_bounds__(kQaMergeCols * kQaMergeParts) void quant_act_merge(
     }
 }
 
+// ---- row form: a block owns ROWS whole rows, so their code sums are complete inside it and no partial buffer or merge
+// is needed.  For calls that do not ask for column sums (a forward with a calibrated scale).  Small calls are bound by
+// the launch and one round trip to memory: one launch instead of two (the figures are at the dispatch below).
+constexpr int kQrBlock = 512;
+template <bool F16, int ROWS>
+__global__ __launch_bounds__(kQrBlock) void quant_act_rows(
+    const void* __restrict__ X, int64_t T, int64_t K, int64_t ldx, const float* __restrict__ inv_s,
+    const float* __restrict__ act_step, const int32_t* __restrict__ act_zero, int8_t* __restrict__ xq,
+    int32_t* __restrict__ rowsum_x, uint32_t* status)
+{
+    __shared__ int s_rs[kQrBlock / kWave][ROWS];
+    const int64_t r0 = (int64_t)blockIdx.x * ROWS;
+    const int nrows = (int)min((int64_t)ROWS, T - r0);
+    const ActParams p = act_params(act_step, act_zero, F16);
+    const int64_t units = K / 8, padded = panel_count(K) * (kPanel / 8);
+    uint32_t st = 0;
+    float big = 0.0f;
+    int rs[ROWS];
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) rs[i] = 0;
+    for (int64_t u = threadIdx.x; u < padded; u += kQrBlock) {
+        int8_t* const d = xq + ((u >> 3) * T + r0) * kPanel + (u & 7) * 8;
+        if (u >= units) {                      // zero fill of the last panel
+            for (int i = 0; i < nrows; ++i) *reinterpret_cast<uint2*>(d + i * kPanel) = make_uint2(0u, 0u);
+            break;
+        }
+        RawUnit<F16> raw[ROWS];
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i)
+            if (i < nrows) raw[i].load(X, (r0 + i) * ldx + u * 8);
+        float is[8];
+        bool fast = p.fast;
+        float is_max = 0.0f;
+        const Float4 a = *reinterpret_cast<const Float4*>(inv_s + u * 8), b = *reinterpret_cast<const Float4*>(inv_s + u * 8 + 4);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            is[i] = i < 4 ? a.f[i & 3] : b.f[i & 3];
+            if (!(fabsf(is[i]) < 1.0e12f)) fast = false;
+            is_max = fmaxf(is_max, fabsf(is[i]));
+        }
+        // the same choice of quotient as the tiled form, per wavefront
+        const bool screen = __all(fast && p.screen && 65600.0f * is_max * p.rstep < 16777216.0f);
+        const bool exact = __all(fast);
+        float csf[8];
+        int csi[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) { csf[i] = 0.0f; csi[i] = 0; }
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i) {
+            if (i >= nrows) break;
+            float x[8];
+            raw[i].get(x);
+            if (F16 && screen) act_unit<2>(x, is, p, d + i * kPanel, csf, csi, rs[i], big, st);
+            else if (F16 && exact) act_unit<1>(x, is, p, d + i * kPanel, csf, csi, rs[i], big, st);
+            else act_unit<0>(x, is, p, d + i * kPanel, csf, csi, rs[i], big, st);
+        }
+    }
+    if (big >= 16777216.0f) st |= AWEQ_ST_BIGQUOT;
+    raise_status(status, st);
+    if (!rowsum_x) return;
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) {
+        const int v = wave_allreduce(rs[i], OpAdd());
+        if ((threadIdx.x & (kWave - 1)) == 0) s_rs[threadIdx.x / kWave][i] = v;
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < nrows) {
+        int tot = 0;
+#pragma unroll
+        for (int w = 0; w < kQrBlock / kWave; ++w) tot += s_rs[w][threadIdx.x];
+        rowsum_x[r0 + threadIdx.x] = tot;
+    }
+}
+
 struct QaPlan {
     int chunks;      // column chunks of 8 panels
     int64_t slices;  // row slices
@@ -355,6 +429,17 @@ int launch_quant_act(const void* X, aweq_dtype dt, int64_t T, int64_t K, int64_t
                      const float* act_step, const int32_t* act_zero, int8_t* xq, int32_t* rowsum_x,
                      int64_t* colsum_xq, void* ws, uint32_t* status, hipStream_t st)
 {
+    // whole rows per block where nothing is summed over tokens, up to the size where the panel form streams as fast
+    // (K = 4096 / 11008, us, panel form -> row form: 1 token 7.1 -> 3.1 / 7.9 -> 4.6, 256: 10.1 -> 3.8 / 13.8 -> 6.5,
+    // 2048: 13.0 -> 8.9 / 27.0 -> 18.1, 8192: 30.3 -> 26.7 / 68.2 -> 65.9, but 119 -> 128 at K = 22016); one row per block
+    // up to 256 tokens, two up to 1024 (1024 tokens, 1 / 2 / 4 rows: 6.8 / 5.5 / 6.0)
+    if (!colsum_xq && xq && aligned16(inv_s) && T <= 4096) {
+#define AWEQ_QR(F, R) quant_act_rows<F, R><<<(unsigned)cdiv(T, R), kQrBlock, 0, st>>>(X, T, K, ldx, inv_s, act_step, act_zero, xq, rowsum_x, status)
+        if (dt == AWEQ_F16) { if (T <= 256) AWEQ_QR(true, 1); else if (T <= 1024) AWEQ_QR(true, 2); else AWEQ_QR(true, 4); }
+        else { if (T <= 256) AWEQ_QR(false, 1); else if (T <= 1024) AWEQ_QR(false, 2); else AWEQ_QR(false, 4); }
+#undef AWEQ_QR
+        return launch_status();
+    }
     const QaPlan p = qa_plan(T, K);
     if (p.slices * p.chunks > 0x7ffffff0ll) return AWEQ_ERR_SHAPE;
     const bool multi = p.chunks > 1;
