@@ -24,7 +24,7 @@
 //    slower, used for shapes the fast kernel does not take.
 // Workgroups are numbered so that the ones resident on one XCD (which share an L2) form a
 // compact patch of the output.
-#include "common.hpp"
+#include "gemm_i8.hpp"
 #include <type_traits>
 
 namespace aweq {
@@ -46,40 +46,6 @@ __device__ __forceinline__ int swz(int row, int chunk)
     const int g = (((row >> 2) & 1) << 1) | (((row >> 1) ^ (row >> 3)) & 1);
     return chunk ^ g;
 }
-
-struct GemmArgs {
-    const int8_t* A;   // xq [T x K], K-panel layout
-    const int8_t* B;   // wq [N x K], K-panel layout
-    int64_t T, N, K;
-    int32_t* out_i32;
-    void* out_deq;
-    int out_f16;
-    int64_t ldo;
-    long long* colsum_acc;
-    const float* act_step;
-    const int32_t* act_zero;
-    const float* step_w;
-    const int32_t* zero_w;
-    const int32_t* rowsum_x;
-    const int32_t* rowsum_w;
-    const float* bias;
-    int w_per_tensor;  // step_w / zero_w hold one entry for the whole weight instead of one per output channel
-    int tiles_m, tiles_n, patch_m, patch_n, patches_n, n_patches;
-    int n_ids;  // workgroup ids that may name a tile (whole rounds of patches over the XCDs)
-    // tiled kernel: the tile columns that do not fill a whole patch column form patches of their own shape
-    int main_pn, n_main, tail_cols, tail_pm, per_patch, n_patches_fast;
-    // fused epilogues on the de-quantised binary16 output y (the next layer's calibration input)
-    int act;                    // 0: none, 1: ReLU before y is rounded
-    uint32_t* ykeys;            // [2 N] order-preserving keys of the column minimum / maximum of y
-    long long* yfix;            // [N] column sums of y in units of 2^-24 (exact: y is binary16)
-    const float* next_inv_s;    // [N] the next layer's 1 / s, Step and Z: y is quantised with them
-    const float* next_step;
-    const int32_t* next_zero;
-    int8_t* yq;                 // [T x N] codes of y, K-panel layout (panels of 64 output channels)
-    int32_t* rowsum_y;          // [T]
-    long long* colsum_yq;       // [N]
-    uint32_t* status;
-};
 
 // order-preserving unsigned key of a float (and back): integer atomics then find extremes
 __device__ __forceinline__ uint32_t ykey(float f)
@@ -963,6 +929,8 @@ extern "C" int aweq_w8a8_gemm(const void* X, aweq_dtype x_dt, int64_t T, int64_t
     if (out_deq && (!aligned16(out_deq) || (ldo % 4) != 0 || (w_group == 0 && (!aligned16(step_w) || !aligned16(zero_w))) ||
                     !aligned16(rowsum_w) || (bias && !aligned16(bias))))
         fast_ok = false;
+    const FewPlan few = plan_few(T, N);
+    if (fast_ok && few.cost < kTiledRoundCost * (double)cdiv(cdiv(T, BM) * cdiv(N, BN), 256)) return launch_gemm_i8_few(g, few, st);
     if (fast_ok) {
         const int deq = out_deq ? (out_dt == AWEQ_F16 ? 2 : 1) : 0;
         const void* fn = nullptr;

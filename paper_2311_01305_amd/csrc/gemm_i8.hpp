@@ -1,0 +1,52 @@
+// Arguments of the int8 GEMM kernels, and the few-token form (gemm_i8_few.hip) that aweq_w8a8_gemm chooses.
+#pragma once
+#include "common.hpp"
+
+namespace aweq {
+
+struct GemmArgs {
+    const int8_t* A;   // xq [T x K], K-panel layout
+    const int8_t* B;   // wq [N x K], K-panel layout
+    int64_t T, N, K;
+    int32_t* out_i32;
+    void* out_deq;
+    int out_f16;
+    int64_t ldo;
+    long long* colsum_acc;
+    const float* act_step;
+    const int32_t* act_zero;
+    const float* step_w;
+    const int32_t* zero_w;
+    const int32_t* rowsum_x;
+    const int32_t* rowsum_w;
+    const float* bias;
+    int w_per_tensor;  // step_w / zero_w hold one entry for the whole weight instead of one per output channel
+    int tiles_m, tiles_n, patch_m, patch_n, patches_n, n_patches;
+    int n_ids;  // workgroup ids that may name a tile (whole rounds of patches over the XCDs)
+    // tiled kernel: the tile columns that do not fill a whole patch column form patches of their own shape
+    int main_pn, n_main, tail_cols, tail_pm, per_patch, n_patches_fast;
+    // fused epilogues on the de-quantised binary16 output y (the next layer's calibration input)
+    int act;                    // 0: none, 1: ReLU before y is rounded
+    uint32_t* ykeys;            // [2 N] order-preserving keys of the column minimum / maximum of y
+    long long* yfix;            // [N] column sums of y in units of 2^-24 (exact: y is binary16)
+    const float* next_inv_s;    // [N] the next layer's 1 / s, Step and Z: y is quantised with them
+    const float* next_step;
+    const int32_t* next_zero;
+    int8_t* yq;                 // [T x N] codes of y, K-panel layout (panels of 64 output channels)
+    int32_t* rowsum_y;          // [T]
+    long long* colsum_yq;       // [N]
+    uint32_t* status;
+};
+
+// The few-token kernel's tile for a shape, and what it is modelled to take in the unit of kTiledRoundCost
+struct FewPlan {
+    int tile;      // index of the instantiation
+    double cost;
+};
+FewPlan plan_few(int64_t T, int64_t N);
+int launch_gemm_i8_few(const GemmArgs& g, const FewPlan& p, hipStream_t st);
+
+// Time of one round of workgroups at K = 8192 (us; every kernel's time is proportional to K): 256 tiles of 256 x 256
+constexpr double kTiledRoundCost = 68.0;
+
+}  // namespace aweq

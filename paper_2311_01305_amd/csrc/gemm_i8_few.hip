@@ -1,0 +1,182 @@
+// Stage 4b for few tokens (decoding, small batches): the int8 GEMM when one read of the weight codes is nearly all
+// there is to do.
+//
+// A workgroup of 8 wavefronts owns 16 NT output channels x 16 TT tokens and splits K between its wavefronts, whose
+// int32 partial sums meet in LDS, so that one token spreads over N / 16 workgroups instead of N / 256.  Both
+// operands come straight from their K-panels (16 rows of a panel are 1 KiB contiguous) in the operand order of
+// v_mfma_i32_16x16x64_i8: lane l holds row l % 16, bytes 16 (l / 16) .. + 15 of the panel row.
+//
+// Bound by the read of the weight.  Measured (us per call on the device, binary16 output, before = 256 x 256 tiles):
+//   tokens          1             32            64            128           256
+//   4096 x 4096     37.7 ->  6.0  38.4 ->  7.3  38.9 ->  7.6  40.8 ->  9.5  43.0 -> 12.4
+//   8192 x 8192     68.3 -> 13.3  68.5 -> 13.7  69.3 -> 15.0  71.4 -> 19.4  72.7 -> 36.7
+//   22016 x 8192    71.8 -> 34.5  70.4 -> 39.6  71.3 -> 48.9  73.2 -> 69.4  (tiled: 80)
+// (22016 x 8192 at one token: 180 MB, 5.2 TB/s.)
+#include "gemm_i8.hpp"
+
+namespace aweq {
+namespace few {
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+
+constexpr int kThreads = 512;
+constexpr int kWaves = kThreads / kWave;
+
+template <int TT, int NT, int U>
+__global__ __launch_bounds__(kThreads) void gemm_i8_few(GemmArgs g)
+{
+    extern __shared__ __attribute__((aligned(16))) int red[];   // [wave][TT NT][lane][4]
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    const int r = lane & 15, q = lane >> 4;
+    const int64_t n0 = (int64_t)blockIdx.x * (16 * NT), t0 = (int64_t)blockIdx.y * (16 * TT);
+    const int np = (int)panel_count(g.K);
+    const int rows_left = (int)min(g.N - n0, (int64_t)(16 * NT)) - 1, tokens_left = (int)min(g.T - t0, (int64_t)(16 * TT)) - 1;
+
+    // rows past the edge re-read the last valid row; their results are never stored
+    uint32_t wo[NT], xo[TT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) wo[j] = (uint32_t)min(16 * j + r, rows_left) * kPanel + q * 16;
+#pragma unroll
+    for (int i = 0; i < TT; ++i) xo[i] = (uint32_t)min(16 * i + r, tokens_left) * kPanel + q * 16;
+    const int8_t* const wbase = g.B + n0 * kPanel;
+    const int8_t* const xbase = g.A + t0 * kPanel;
+    const int64_t wp = g.N * kPanel, xp = g.T * kPanel;
+
+    v4i acc[TT][NT];
+#pragma unroll
+    for (int i = 0; i < TT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[i][j] = v4i{0, 0, 0, 0};
+
+    // panels wave, wave + 8, ...: U of them on their way while U are multiplied
+    v4i w[U][NT], x[U][TT];
+    auto load = [&](int p0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int p = p0 + u * kWaves;
+            if (p < np) {
+#pragma unroll
+                for (int j = 0; j < NT; ++j) w[u][j] = *reinterpret_cast<const v4i*>(wbase + p * wp + wo[j]);
+#pragma unroll
+                for (int i = 0; i < TT; ++i) x[u][i] = *reinterpret_cast<const v4i*>(xbase + p * xp + xo[i]);
+            }
+        }
+    };
+    load(wave);
+    for (int p0 = wave; p0 < np; p0 += U * kWaves) {
+        v4i cw[U][NT], cx[U][TT];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+#pragma unroll
+            for (int j = 0; j < NT; ++j) cw[u][j] = w[u][j];
+#pragma unroll
+            for (int i = 0; i < TT; ++i) cx[u][i] = x[u][i];
+        }
+        load(p0 + U * kWaves);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (p0 + u * kWaves < np) {
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+#pragma unroll
+                    for (int i = 0; i < TT; ++i) acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(cw[u][j], cx[u][i], acc[i][j], 0, 0, 0);
+            }
+    }
+
+    // register v of lane l is output channel 4 (l / 16) + v of the 16, token l % 16
+    constexpr int kTiles = TT * NT;
+#pragma unroll
+    for (int i = 0; i < TT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) *reinterpret_cast<v4i*>(red + ((wave * kTiles + i * NT + j) * kWave + lane) * 4) = acc[i][j];
+    __syncthreads();
+    uint32_t est = 0;
+    for (int e = threadIdx.x; e < kTiles * kWave; e += kThreads) {
+        const int tile = e / kWave, l = e & (kWave - 1);
+        const int64_t t = t0 + 16 * (tile / NT) + (l & 15), n = n0 + 16 * (tile % NT) + 4 * (l >> 4);
+        const bool ok = t < g.T && n < g.N;     // N % 4 == 0: all four channels or none
+        v4i o = {0, 0, 0, 0};
+#pragma unroll
+        for (int wv = 0; wv < kWaves; ++wv) o += *reinterpret_cast<const v4i*>(red + ((wv * kTiles + tile) * kWave + l) * 4);
+        if (ok && g.out_i32) *reinterpret_cast<v4i*>(g.out_i32 + t * g.ldo + n) = o;
+        if (ok && g.out_deq) {
+            // the tiled kernel's arithmetic: the integer part in wrap-around 32 bits, scaled and shifted in fp64
+            const int zx = *g.act_zero - 128;
+            const double sx = (double)*g.act_step;
+            if (zx < -128 || zx > 127) est |= AWEQ_ST_ZEROPOINT;
+            const unsigned rs = (unsigned)g.rowsum_x[t];
+            float y[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int64_t pi = g.w_per_tensor ? 0 : n + c;
+                const int zw = g.zero_w[pi] - 128;
+                if (zw < -128 || zw > 127) est |= AWEQ_ST_ZEROPOINT;
+                const double scale = sx * (double)g.step_w[pi], bd = g.bias ? (double)g.bias[n + c] : 0.0;
+                const unsigned cn = (unsigned)g.K * (unsigned)zx * (unsigned)zw - (unsigned)zx * (unsigned)g.rowsum_w[n + c];
+                const double div = (double)(int)((unsigned)o[c] + cn - (unsigned)zw * rs);
+                y[c] = g.out_f16 ? (float)__builtin_fma(div, scale, bd) : (float)(div * scale + bd);
+            }
+            if (g.out_f16) {
+                typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+                *reinterpret_cast<h4*>(reinterpret_cast<_Float16*>(g.out_deq) + t * g.ldo + n) =
+                    h4{(_Float16)y[0], (_Float16)y[1], (_Float16)y[2], (_Float16)y[3]};
+            } else {
+                *reinterpret_cast<Float4*>(reinterpret_cast<float*>(g.out_deq) + t * g.ldo + n) = Float4{{y[0], y[1], y[2], y[3]}};
+            }
+        }
+        if (g.colsum_acc) {   // (uniform; every lane of a wavefront is here: kTiles * 64 is a multiple of it)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const long long s = group_allreduce<4>(ok ? (long long)o[c] : 0ll, OpAdd());
+                if ((l & 15) == 0 && n < g.N) atomicAdd(reinterpret_cast<unsigned long long*>(&g.colsum_acc[n + c]), (unsigned long long)s);
+            }
+        }
+    }
+    raise_status(g.status, est);
+}
+
+template <int TT, int NT, int U>
+static int launch_tile(const GemmArgs& g, hipStream_t st)
+{
+    constexpr int lds = kWaves * TT * NT * kWave * 16;
+    const void* fn = reinterpret_cast<const void*>(gemm_i8_few<TT, NT, U>);
+    int dev = 0, cus = 0;
+    if (lds > 65536 && (device_cus(dev, cus) != AWEQ_OK || raise_lds_limit(fn, dev, lds) != AWEQ_OK)) return AWEQ_ERR_LAUNCH;
+    void* args[] = {const_cast<GemmArgs*>(&g)};
+    if (hipLaunchKernel(fn, dim3((unsigned)cdiv(g.N, 16 * NT), (unsigned)cdiv(g.T, 16 * TT)), dim3(kThreads), args, lds, st) != hipSuccess)
+        return AWEQ_ERR_LAUNCH;
+    return launch_status();
+}
+}  // namespace few
+
+// Tile by token count and channels.  Up to 32 tokens one row of workgroups covers them and the pass is a read of the
+// weight: 16 channels per workgroup while they fill the chip 1.5 times over, then 32 (one token, us: 4096 x 4096 6.0 with
+// 16 channels, 6.3 with 32; 16384 x 4096 14.0 / 12.8; 8192 x 8192 13.9 / 13.3).  Beyond that the tile whose rounds of 256
+// workgroups, each weighted with its measured time at K = 8192, are cheapest (64 tokens, us, 32 x 32 / 32 x 64 / 64 x 64
+// tiles: 4096 x 4096 7.6 / 9.3 / 12.2; 8192 x 8192 22.7 / 15.0 / 19.2; 16384 x 4096 23.3 / 24.2 / 14.8).
+FewPlan plan_few(int64_t T, int64_t N)
+{
+    const bool wide = N > 6144;
+    auto rounds = [&](int tt, int nt) { return (double)cdiv(cdiv(T, 16 * tt) * cdiv(N, 16 * nt), 256); };
+    if (T <= 16) return wide ? FewPlan{1, 13.0 * rounds(1, 2)} : FewPlan{0, 13.0 * rounds(1, 2)};
+    if (T <= 32) return wide ? FewPlan{3, 13.0 * rounds(2, 2)} : FewPlan{2, 13.0 * rounds(2, 2)};
+    const double c22 = 13.0 * rounds(2, 2), c24 = 19.0 * rounds(2, 4), c44 = 22.0 * rounds(4, 4);
+    if (c22 <= c24 && c22 <= c44) return FewPlan{3, c22};
+    if (c24 <= c44) return FewPlan{4, c24};
+    return FewPlan{5, c44};
+}
+
+int launch_gemm_i8_few(const GemmArgs& g, const FewPlan& p, hipStream_t st)
+{
+    switch (p.tile) {
+    case 0: return few::launch_tile<1, 1, 4>(g, st);
+    case 1: return few::launch_tile<1, 2, 4>(g, st);
+    case 2: return few::launch_tile<2, 1, 4>(g, st);
+    case 3: return few::launch_tile<2, 2, 2>(g, st);
+    case 4: return few::launch_tile<2, 4, 2>(g, st);
+    default: return few::launch_tile<4, 4, 1>(g, st);
+    }
+}
+
+}  // namespace aweq
