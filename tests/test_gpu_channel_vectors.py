@@ -1,0 +1,69 @@
+"""K-vector work at the edges of its launches: the statistics' finishing kernel (blocks of 256 channels, block extremes
+every 32 channels) and the equalization scales (one block up to 4096 channels, a block per 1024 and a range launch
+beyond), against the oracle."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def B():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2311_01305_amd import binding
+    binding.load_library()
+    return binding
+
+
+@pytest.mark.parametrize("K", [8, 40, 256, 4088, 4096, 4104, 8200, 12296, 49160])
+def test_ranges_and_scales(B, orc, K):
+    print(f"[channel vectors] K={K}", flush=True)
+    rng = np.random.default_rng(K)
+    T, N = 33, 5
+    X = (rng.standard_normal((T, K)) * np.exp(rng.standard_normal(K))).astype(np.float16)
+    W = (rng.standard_normal((N, K)) * 0.02).astype(np.float16)
+    X[:, K // 2] = 0.25        # a constant channel: guarded scale
+    X[3, K - 1] = 900.0        # the tensor's extremes in the last and the first channel
+    X[7, 0] = -1000.0
+    e = lambda *s, dtype=torch.float32: torch.empty(s, dtype=dtype, device=DEV)
+    d = lambda a: torch.from_numpy(a).to(DEV)
+    st = torch.zeros(1, dtype=torch.int32, device=DEV)
+
+    def stats(M, rows, want_sum):
+        o = dict(cmin=e(K), cmax=e(K), csum=e(K, dtype=torch.float64) if want_sum else None, count=e(1, dtype=torch.int64),
+                 r=e(K), R=e(1), p=e(K))
+        ws = torch.full((B.aweq_workspace_size(B.OP_CALIB_STATS, rows, K),), 0x5A, dtype=torch.uint8, device=DEV)
+        half = rows // 2
+        for r0, r1, acc in ((0, half, 0), (half, rows, 1)):   # merged in two batches, finished with the second
+            B.aweq_calib_stats(M[r0:], B.AWEQ_F16, r1 - r0, K, K, o["cmin"], o["cmax"], o["csum"], o["count"], acc, acc, o["r"],
+                               o["R"], o["p"], ws, st)
+        return o
+
+    gx, gw = stats(d(X), T, True), stats(d(W), N, False)
+    for M, g in ((X, gx), (W, gw)):
+        ref = orc.col_stats(M, want_sum=False)
+        r, R, p = orc.ranges(ref["cmin"], ref["cmax"])
+        assert np.array_equal(g["r"].cpu().numpy(), r) and g["R"].item() == R
+        assert np.array_equal(g["p"].cpu().numpy(), p)
+    s, inv_s, mu, rngx, step, zero = e(K), e(K), e(K), e(2), e(1), e(1, dtype=torch.int32)
+    B.aweq_equalize(gx["cmin"], gx["cmax"], gx["csum"], T, gw["cmin"], gw["cmax"], K, 1, s, inv_s, None, None, B.AWEQ_F16, 0, K, K,
+                    None, rngx, mu, step, zero, st)
+    sx, sw = orc.col_stats(X), orc.col_stats(W, want_sum=False)
+    r_x, _, _ = orc.ranges(sx["cmin"], sx["cmax"])
+    r_w, _, _ = orc.ranges(sw["cmin"], sw["cmax"])
+    s_ref, inv_ref, _ = orc.scales(r_x, r_w)
+    np.testing.assert_allclose(s.cpu().numpy(), s_ref, rtol=1e-6)     # fp64 square root and quotient, rounded once
+    inv = inv_s.cpu().numpy()
+    assert np.array_equal(inv, np.float32(1.0) / s.cpu().numpy())
+    lo, hi = (sx["cmin"] * inv).min(), (sx["cmax"] * inv).max()       # binary32 products, as in the kernel
+    assert rngx.cpu().numpy().tolist() == [lo, hi]
+    assert step.item() == np.float32(hi - lo) / np.float32(255) and zero.item() == -int(np.rint(lo / np.float32(step.item())))
+    # 33 binary16 values summed in binary32 runs of 8: 7 2^-24 of the mean magnitude
+    bound = 1e-6 * np.abs(X.astype(np.float64)).mean(axis=0) * inv + 1e-30
+    assert np.all(np.abs(mu.cpu().numpy() - X.astype(np.float64).mean(axis=0) * inv) <= bound)
+    assert st.item() & B.ST_SCALEGUARD
