@@ -3,46 +3,23 @@
 
 namespace aweq {
 
-// K-vector work, one block: s, inv_s, equalised activation range / mean, the static int8
-// activation quantizer (Eq. 2 on the range of X_hat), optional prev_scale *= inv_s.
-__global__ __launch_bounds__(1024) void equalize_scales(
-    const float* __restrict__ xmin, const float* __restrict__ xmax, const double* __restrict__ xsum,
-    uint64_t count, const float* __restrict__ wmin, const float* __restrict__ wmax, int64_t K,
-    int enable_awe, float* __restrict__ s, float* __restrict__ inv_s, float* __restrict__ prev_scale,
-    float* __restrict__ xhat_range, float* __restrict__ mu_xhat, float* __restrict__ act_step,
-    int32_t* __restrict__ act_zero, uint32_t* status)
+// K-vector work: s, inv_s, equalised activation mean, optional prev_scale *= inv_s; and, if `range` is set (one block
+// only: it is over all channels and the call has no scratch memory), the equalised activation range with the static
+// int8 activation quantizer (Eq. 2 on the range of X_hat).  Bound by the round trips of a block's loads, so a thread
+// requests kScaleBatch channels before it uses the first, and then by its fp64 square roots and divisions: 1 us per 1024
+// channels.  Up to kOneBlockK channels one block does everything; beyond, a block per 1024 channels and a launch of
+// equalize_range (us, one channel at a time in one block -> one block / two launches: K = 4096 7.9 -> 6.2,
+// 8192 14.3 -> 7.7, 11008 16.5 -> 7.8).
+constexpr int kScaleBatch = 4;
+constexpr int kScaleBlock = 1024;
+constexpr int64_t kOneBlockK = 4096;
+
+// extremes of the equalised activation -> its range and quantizer (every thread of the one block calls it)
+__device__ __forceinline__ void finish_range(float lo, float hi, float* slot, float* xhat_range, float* act_step,
+                                             int32_t* act_zero, uint32_t& st)
 {
-    __shared__ float slot[16];
-    uint32_t st = 0;
-    float lo = INFINITY, hi = -INFINITY;
-    for (int64_t k = threadIdx.x; k < K; k += blockDim.x) {
-        // the per-channel quantity the scale balances: the channel range (Eq. 10), or - the definition the
-        // method replaces (Sec. 1, Sec. 3.2) - the channel's largest magnitude
-        const float r_x = enable_awe == AWEQ_SCALE_ABSMAX ? fmaxf(fabsf(xmin[k]), fabsf(xmax[k])) : xmax[k] - xmin[k];
-        const float r_w = enable_awe == AWEQ_SCALE_ABSMAX ? fmaxf(fabsf(wmin[k]), fabsf(wmax[k])) : wmax[k] - wmin[k];
-        float sk = 1.0f;
-        if (enable_awe) {
-            if (!(r_x >= 1e-5f) || !(r_w >= 1e-5f)) {
-                st |= AWEQ_ST_SCALEGUARD;
-            } else {
-                const double rx = (double)r_x, rw = (double)r_w;
-                sk = (float)(sqrt(rx * rw) / rw);
-                if (sk < 1e-4f) { sk = 1e-4f; st |= AWEQ_ST_SCALEGUARD; }
-                if (sk > 1e4f) { sk = 1e4f; st |= AWEQ_ST_SCALEGUARD; }
-            }
-        }
-        const float is = 1.0f / sk;
-        s[k] = sk;
-        inv_s[k] = is;
-        if (prev_scale) prev_scale[k] = prev_scale[k] * is;
-        if (mu_xhat) mu_xhat[k] = (float)((xsum[k] / (double)count) * (double)is);
-        // a correctly rounded multiply by a positive constant is monotone, so the extremes of
-        // the equalised column are the scaled extremes of the column
-        lo = fminf(lo, xmin[k] * is);
-        hi = fmaxf(hi, xmax[k] * is);
-    }
-    lo = block_allreduce<16>(lo, OpMin(), slot);
-    hi = block_allreduce<16>(hi, OpMax(), slot);
+    lo = block_allreduce<kScaleBlock / kWave>(lo, OpMin(), slot);
+    hi = block_allreduce<kScaleBlock / kWave>(hi, OpMax(), slot);
     if (threadIdx.x == 0) {
         if (xhat_range) { xhat_range[0] = lo; xhat_range[1] = hi; }
         if (act_step && act_zero) {
@@ -52,6 +29,83 @@ __global__ __launch_bounds__(1024) void equalize_scales(
             *act_zero = z;
         }
     }
+}
+
+__global__ __launch_bounds__(kScaleBlock) void equalize_scales(
+    const float* __restrict__ xmin, const float* __restrict__ xmax, const double* __restrict__ xsum,
+    uint64_t count, const float* __restrict__ wmin, const float* __restrict__ wmax, int64_t K,
+    int enable_awe, float* __restrict__ s, float* __restrict__ inv_s, float* __restrict__ prev_scale,
+    float* __restrict__ xhat_range, float* __restrict__ mu_xhat, float* __restrict__ act_step,
+    int32_t* __restrict__ act_zero, uint32_t* status, int range)
+{
+    __shared__ float slot[kScaleBlock / kWave];
+    uint32_t st = 0;
+    float lo = INFINITY, hi = -INFINITY;
+    const int64_t stride = (int64_t)kScaleBlock * gridDim.x;
+    for (int64_t k0 = (int64_t)blockIdx.x * kScaleBlock + threadIdx.x; k0 < K; k0 += kScaleBatch * stride) {
+        float x0[kScaleBatch], x1[kScaleBatch], w0[kScaleBatch], w1[kScaleBatch];
+        double xs[kScaleBatch];
+#pragma unroll
+        for (int i = 0; i < kScaleBatch; ++i) {
+            const int64_t k = min(k0 + i * stride, K - 1);   // (past the end: the last channel again, not used)
+            x0[i] = xmin[k]; x1[i] = xmax[k]; w0[i] = wmin[k]; w1[i] = wmax[k];
+            xs[i] = mu_xhat ? xsum[k] : 0.0;
+        }
+#pragma unroll
+        for (int i = 0; i < kScaleBatch; ++i) {
+            const int64_t k = k0 + i * stride;
+            if (k >= K) break;
+            // the per-channel quantity the scale balances: the channel range (Eq. 10), or - the definition the
+            // method replaces (Sec. 1, Sec. 3.2) - the channel's largest magnitude
+            const float r_x = enable_awe == AWEQ_SCALE_ABSMAX ? fmaxf(fabsf(x0[i]), fabsf(x1[i])) : x1[i] - x0[i];
+            const float r_w = enable_awe == AWEQ_SCALE_ABSMAX ? fmaxf(fabsf(w0[i]), fabsf(w1[i])) : w1[i] - w0[i];
+            float sk = 1.0f;
+            if (enable_awe) {
+                if (!(r_x >= 1e-5f) || !(r_w >= 1e-5f)) {
+                    st |= AWEQ_ST_SCALEGUARD;
+                } else {
+                    const double rx = (double)r_x, rw = (double)r_w;
+                    sk = (float)(sqrt(rx * rw) / rw);
+                    if (sk < 1e-4f) { sk = 1e-4f; st |= AWEQ_ST_SCALEGUARD; }
+                    if (sk > 1e4f) { sk = 1e4f; st |= AWEQ_ST_SCALEGUARD; }
+                }
+            }
+            const float is = 1.0f / sk;
+            s[k] = sk;
+            inv_s[k] = is;
+            if (prev_scale) prev_scale[k] = prev_scale[k] * is;
+            if (mu_xhat) mu_xhat[k] = (float)((xs[i] / (double)count) * (double)is);
+            // a correctly rounded multiply by a positive constant is monotone, so the extremes of
+            // the equalised column are the scaled extremes of the column
+            lo = fminf(lo, x0[i] * is);
+            hi = fmaxf(hi, x1[i] * is);
+        }
+    }
+    if (range) finish_range(lo, hi, slot, xhat_range, act_step, act_zero, st);
+    raise_status(status, st);
+}
+
+__global__ __launch_bounds__(kScaleBlock) void equalize_range(
+    const float* __restrict__ xmin, const float* __restrict__ xmax, const float* __restrict__ inv_s, int64_t K,
+    float* __restrict__ xhat_range, float* __restrict__ act_step, int32_t* __restrict__ act_zero, uint32_t* status)
+{
+    __shared__ float slot[kScaleBlock / kWave];
+    uint32_t st = 0;
+    float lo = INFINITY, hi = -INFINITY;
+    for (int64_t k0 = threadIdx.x; k0 < K; k0 += 12 * kScaleBlock) {
+        float x0[12], x1[12], is[12];
+#pragma unroll
+        for (int i = 0; i < 12; ++i) {
+            const int64_t k = min(k0 + i * kScaleBlock, K - 1);   // (past the end: the last channel again)
+            x0[i] = xmin[k]; x1[i] = xmax[k]; is[i] = inv_s[k];
+        }
+#pragma unroll
+        for (int i = 0; i < 12; ++i) {
+            lo = fminf(lo, x0[i] * is[i]);
+            hi = fmaxf(hi, x1[i] * is[i]);
+        }
+    }
+    finish_range(lo, hi, slot, xhat_range, act_step, act_zero, st);
     raise_status(status, st);
 }
 
@@ -122,8 +176,11 @@ extern "C" int aweq_equalize(const float* xmin, const float* xmax, const double*
             return AWEQ_ERR_ALIGN;
     }
     hipStream_t st = as_stream(stream);
-    equalize_scales<<<1, 1024, 0, st>>>(xmin, xmax, xsum, count, wmin, wmax, K, enable_awe, s, inv_s, prev_scale,
-                                        xhat_range, mu_xhat, act_step, act_zero, status);
+    const bool one = K <= kOneBlockK;
+    equalize_scales<<<one ? 1u : (unsigned)cdiv(K, kScaleBlock), kScaleBlock, 0, st>>>(
+        xmin, xmax, xsum, count, wmin, wmax, K, enable_awe, s, inv_s, prev_scale, xhat_range, mu_xhat, act_step, act_zero, status, one);
+    if (!one && (xhat_range || act_step))
+        equalize_range<<<1, kScaleBlock, 0, st>>>(xmin, xmax, inv_s, K, xhat_range, act_step, act_zero, status);
     if (W) {
         const int E = dt == AWEQ_F16 ? 8 : 4;
         const unsigned gx = (unsigned)cdiv(K, 256 * E);
