@@ -19,7 +19,8 @@
 //    The slots are XOR swizzled by choosing which 16-byte chunk each lane fetches; loads, LDS
 //    fragment reads for the next K-step and MFMAs are interleaved by hand.  The MFMA is
 //    issued with the weight fragment as its first operand, so a lane ends up with four
-//    consecutive n of one token: 16-byte output stores.
+//    consecutive n of one token: 16-byte output stores.  A second form has tiles of 128 x 256
+//    (wavefronts of 64 x 64, a ring of five 24 KiB slots) for calls with few tiles.
 //  - gemm_i8_generic (any N, any alignment): 4 wavefronts, half-stages through registers;
 //    slower, used for shapes the fast kernel does not take.
 // Workgroups are numbered so that the ones resident on one XCD (which share an L2) form a
@@ -256,10 +257,19 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_i8_generic(GemmArgs g)
 // ---------------------------------------------------------------------------- fast kernel
 namespace fast {
 constexpr int kThreads = 512;
-constexpr int kHalf = BM * kPanel;   // 16 KiB per operand per slot
-constexpr int kSlot = 2 * kHalf;     // 32 KiB: one panel of the A tile and of the B tile
-constexpr int kSlots = 4;
-constexpr int kLds = kSlots * kSlot + 32768;  // 128 KiB ring + 32 KiB: the epilogue's slabs use the last slot and the tail = 160 KiB
+// Tile of 64 MI tokens (MI = 4: 256, MI = 2: 128) x 256 channels.  One panel of both operands is a slot of the ring; the
+// epilogue's slabs (8 KiB per wavefront) use the last slot and what is behind the ring, 160 KiB with it.
+template <int MI>
+struct Tile {
+    static constexpr int kRows = 64 * MI;
+    static constexpr int kHalfA = kRows * kPanel;                 // activation rows of a slot, then 16 KiB of weight rows
+    static constexpr int kSlot = kHalfA + BN * kPanel;            // 32 KiB / 24 KiB
+    static constexpr int kSlots = MI == 4 ? 4 : 5;
+    static constexpr int kAhead = kSlots - 1;                     // panels requested ahead of the one being multiplied
+    static constexpr int kLoads = MI / 2 + 2;                     // load instructions per wavefront and panel
+    static constexpr int kSlabs = kAhead * kSlot;                 // 96 KiB
+    static constexpr int kLds = kSlabs + 8 * 8192;                // 160 KiB
+};
 
 // chunk swizzle for 64-byte slot rows: the four rows r, r + 4, r + 8, r + 12 share LDS banks,
 // so 16 consecutive rows read at one chunk index land on distinct banks
@@ -290,6 +300,15 @@ __device__ __forceinline__ void wait_vm()
 __host__ __device__ __forceinline__ bool tile_of(const GemmArgs& g, int vb, int& tile_m, int& tile_n)
 {
     const int xcd = vb % kXcds, seq = vb / kXcds;
+    if (g.strip_m) {
+        const int l = ((seq / g.run) * kXcds + xcd) * g.run + seq % g.run;
+        if (l >= g.tiles_m * g.tiles_n) return false;
+        const int strip = l / (g.strip_m * g.tiles_n), in = l % (g.strip_m * g.tiles_n);
+        const int height = min(g.strip_m, g.tiles_m - strip * g.strip_m);
+        tile_m = strip * g.strip_m + in % height;
+        tile_n = in / height;
+        return true;
+    }
     const int patch = (seq / g.per_patch) * kXcds + xcd;
     if (patch >= g.n_patches_fast) return false;
     const int within = seq % g.per_patch;
@@ -311,9 +330,11 @@ __host__ __device__ __forceinline__ bool tile_of(const GemmArgs& g, int vb, int&
 // fly while the results are stored.
 // EPI (with DEQ == 2): bit 0 collects the column statistics of the binary16 output, bit 1 quantises
 // it for the next layer; STORE = false keeps the output itself from being written.
-template <bool I32, int DEQ, bool COLSUM, int EPI = 0, bool STORE = true>
+template <int MI, bool I32, int DEQ, bool COLSUM, int EPI = 0, bool STORE = true>
 __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
 {
+    using TL = Tile<MI>;
+    constexpr int kSlot = TL::kSlot, kHalfA = TL::kHalfA, kAhead = TL::kAhead, kLoads = TL::kLoads;
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 2, wn = wave & 3;
@@ -325,9 +346,9 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
 
     const int64_t panelA = g.T * kPanel, panelB = g.N * kPanel;
     const int nh = (int)panel_count(g.K);
-    const int pre = nh < 3 ? nh : 3;
+    const int pre = nh < kAhead ? nh : kAhead;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
-    const uint32_t wave_off = __builtin_amdgcn_readfirstlane(wave) * 2048;
+    const uint32_t wave_offA = __builtin_amdgcn_readfirstlane(wave) * (512 * MI), wave_offB = kHalfA + __builtin_amdgcn_readfirstlane(wave) * 2048;
 
     // fragment of K-step ks of a panel: lane reads row lane % 32 of a 32-row sub-tile, chunk
     // 2 ks + lane / 32 (sub-tiles start at multiples of 32 rows, so f4(row) = f4(lane % 32))
@@ -335,66 +356,66 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
     int offA[2], offB[2];
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
-        offA[ks] = (wm * 128 + fr_row) * kPanel + ((ks * 2 + fr_half) ^ f4(fr_row)) * 16;
-        offB[ks] = kHalf + (wn * 64 + fr_row) * kPanel + ((ks * 2 + fr_half) ^ f4(fr_row)) * 16;
+        offA[ks] = (wm * (32 * MI) + fr_row) * kPanel + ((ks * 2 + fr_half) ^ f4(fr_row)) * 16;
+        offB[ks] = kHalfA + (wn * 64 + fr_row) * kPanel + ((ks * 2 + fr_half) ^ f4(fr_row)) * 16;
     }
 
-    // global -> LDS: wave w brings tile rows 32 w .. 32 w + 31 of both operands, 16 rows x 64 B
-    // per instruction; lane i sits at row i / 4, chunk slot i % 4 and fetches chunk slot ^ f4(row)
-    uint32_t oa[2], ob[2];  // byte offsets from the tile's first row inside a panel: < 16 KiB
+    // global -> LDS: wave w brings tile rows 32 w .. 32 w + 31 of the weight and 8 MI w .. of the activations, 16 rows
+    // x 64 B per instruction; lane i sits at row i / 4, chunk slot i % 4 and fetches chunk slot ^ f4(row)
+    uint32_t oa[MI / 2], ob[2];  // byte offsets from the tile's first row inside a panel: < 16 KiB
     const int8_t* srcA;     // the tile's rows in the panel being fetched
     const int8_t* srcB;
     int64_t m0, n0;
 
-#define DMA_A(q) dma16(srcA, oa[q], dst_slot + (q) * 1024)
-#define DMA_B(q) dma16(srcB, ob[q], dst_slot + kHalf + (q) * 1024)
+#define DMA_A(q) dma16(srcA, oa[q], dst_slot + wave_offA + (q) * 1024)
+#define DMA_B(q) dma16(srcB, ob[q], dst_slot + wave_offB + (q) * 1024)
     // addresses of tile (tm, tn) and its first `pre` panels on their way into slots 0 ..
     auto start_tile = [&](int tm, int tn) {
         // (wave-uniform by construction; say so, the panel base addresses live in scalar registers)
-        m0 = (int64_t)__builtin_amdgcn_readfirstlane(tm) * BM;
+        m0 = (int64_t)__builtin_amdgcn_readfirstlane(tm) * TL::kRows;
         n0 = (int64_t)__builtin_amdgcn_readfirstlane(tn) * BN;
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-            const int row = wave * 32 + q * 16 + (lane >> 2);
-            const int chunk = (lane & 3) ^ f4(row);
+            const int sub = q * 16 + (lane >> 2), chunk = (lane & 3) ^ f4(sub);   // (wavefronts start at multiples of 16 rows)
             // rows past the edge re-read the last valid row; their results are never stored
-            const int64_t ra = min(m0 + row, g.T - 1) - m0, rb = min(n0 + row, g.N - 1) - n0;
-            oa[q] = (uint32_t)(ra * kPanel + chunk * 16);
-            ob[q] = (uint32_t)(rb * kPanel + chunk * 16);
+            if (q < MI / 2) oa[q] = (uint32_t)((min(m0 + wave * (8 * MI) + sub, g.T - 1) - m0) * kPanel + chunk * 16);
+            ob[q] = (uint32_t)((min(n0 + wave * 32 + sub, g.N - 1) - n0) * kPanel + chunk * 16);
         }
         srcA = g.A + m0 * kPanel;
         srcB = g.B + n0 * kPanel;
         for (int h = 0; h < pre; ++h) {
-            const uint32_t dst_slot = lds0 + h * kSlot + wave_off;
-            DMA_A(0); DMA_B(0); DMA_A(1); DMA_B(1);
+            const uint32_t dst_slot = lds0 + h * kSlot;
+            DMA_A(0); DMA_B(0);
+            if constexpr (MI == 4) DMA_A(1);
+            DMA_B(1);
             srcA += panelA; srcB += panelB;
         }
     };
 
     start_tile(tile_m, tile_n);
-    if (pre >= 3) wait_vm<8>(); else if (pre == 2) wait_vm<4>(); else wait_vm<0>();
+    if (pre == kAhead) wait_vm<(kAhead - 1) * kLoads>(); else wait_vm<0>();
 
     // Vector memory operations of a wave complete in the order issued.  A tile that lies inside
     // the output issues at least kStores stores per wave after requesting the next tile's first
-    // three panels, so "at most kStores operations pending" means those panels have landed
+    // kAhead panels, so "at most kStores operations pending" means those panels have landed
     // while the stores may still be on their way (relaxed: set for the tile that follows).
     static_assert(EPI == 0 || DEQ == 2, "the fused epilogues work on the binary16 output");
-    // 4 sub-tile rows x 8 passes each, per kind of output; the atomics of the fused epilogues come
+    // MI sub-tile rows x 8 passes each, per kind of output; the atomics of the fused epilogues come
     // on top and are not counted: a lower bound is what the relaxed wait needs
-    constexpr int kStoresAll = (I32 ? 32 : 0) + (DEQ != 0 && STORE ? 32 : 0) + ((EPI & 2) != 0 ? 32 : 0);
+    constexpr int kStoresAll = 8 * MI * ((I32 ? 1 : 0) + (DEQ != 0 && STORE ? 1 : 0) + ((EPI & 2) != 0 ? 1 : 0));
     constexpr int kStores = kStoresAll > 63 ? 63 : kStoresAll;
     bool relaxed = false;
 
     for (;;) {
         const int64_t cm0 = m0, cn0 = n0;   // the tile being multiplied
-        v16i acc[4][2];
+        v16i acc[MI][2];
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < MI; ++i)
 #pragma unroll
             for (int j = 0; j < 2; ++j)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[i][j][v] = 0;
-        v4i a0[4], b0[2], a1[4], b1[2];
+        v4i a0[MI], b0[2], a1[MI], b1[2];
 
 #define RDA(dst, ks, i) dst[i] = *reinterpret_cast<const v4i*>(st + offA[ks] + (i) * 32 * kPanel)
 #define RDB(dst, ks, j) dst[j] = *reinterpret_cast<const v4i*>(st + offB[ks] + (j) * 32 * kPanel)
@@ -402,35 +423,51 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
         {
             const char* st = lds;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) RDA(a0, 0, i);
+            for (int i = 0; i < MI; ++i) RDA(a0, 0, i);
             RDB(b0, 0, 0); RDB(b0, 0, 1);
         }
 
-        // one panel (64 bytes of K) = two K-steps of 8 MFMAs per wave.  F0 / F1 are the two
+        // one panel (64 bytes of K) = two K-steps of 2 MI MFMAs per wave.  F0 / F1 are the two
         // fragment register sets; each K-step multiplies one and fetches the other.  ISSUE: panel
-        // h + 3 is fetched into the slot panel h - 1 occupied (every wave finished reading it before
+        // h + kAhead is fetched into the slot panel h - 1 occupied (every wave finished reading it before
         // the barrier of panel h - 1).  WAITN: loads this wave may leave in flight when panel h + 1
-        // has to be complete (4 per panel issued after it).
+        // has to be complete (kLoads per panel issued after it).
+        uint32_t slot = 0;   // byte offset of panel h's slot
         auto half = [&](int h, auto issue_c, auto waitn_c, auto next_c) {
             constexpr bool ISSUE = decltype(issue_c)::value;
             constexpr int WAITN = decltype(waitn_c)::value;
             constexpr bool NEXT = decltype(next_c)::value;
-            const char* st = lds + (h & 3) * kSlot;
-            const uint32_t dst_slot = lds0 + ((h + 3) & 3) * kSlot + wave_off;
+            if constexpr (MI == 4) slot = (h & 3) * kSlot;
+            const uint32_t next_slot = MI == 4 ? ((h + 1) & 3) * kSlot : slot == kAhead * kSlot ? 0 : slot + kSlot;
+            const uint32_t dst_slot = lds0 + (MI == 4 ? ((h + 3) & 3) * kSlot : slot == 0 ? kAhead * kSlot : slot - kSlot);
+            const char* st = lds + slot;
             SB();
-            RDA(a1, 1, 0); RDB(b1, 1, 0); RDB(b1, 1, 1); MF(a0, b0, 0, 0);
-            SB();
-            if constexpr (ISSUE) DMA_A(0);
-            RDA(a1, 1, 1); RDA(a1, 1, 2); MF(a0, b0, 0, 1);
-            SB();
-            if constexpr (ISSUE) DMA_B(0);
-            RDA(a1, 1, 3); MF(a0, b0, 1, 0);
-            SB();
-            if constexpr (ISSUE) DMA_A(1);
-            MF(a0, b0, 1, 1);
-            SB();
-            if constexpr (ISSUE) DMA_B(1);
-            MF(a0, b0, 2, 0); MF(a0, b0, 2, 1); MF(a0, b0, 3, 0); MF(a0, b0, 3, 1);
+            if constexpr (MI == 4) {
+                RDA(a1, 1, 0); RDB(b1, 1, 0); RDB(b1, 1, 1); MF(a0, b0, 0, 0);
+                SB();
+                if constexpr (ISSUE) DMA_A(0);
+                RDA(a1, 1, 1); RDA(a1, 1, 2); MF(a0, b0, 0, 1);
+                SB();
+                if constexpr (ISSUE) DMA_B(0);
+                RDA(a1, 1, 3); MF(a0, b0, 1, 0);
+                SB();
+                if constexpr (ISSUE) DMA_A(1);
+                MF(a0, b0, 1, 1);
+                SB();
+                if constexpr (ISSUE) DMA_B(1);
+                MF(a0, b0, 2, 0); MF(a0, b0, 2, 1); MF(a0, b0, 3, 0); MF(a0, b0, 3, 1);
+            } else {
+                RDA(a1, 1, 0); RDB(b1, 1, 0); MF(a0, b0, 0, 0);
+                SB();
+                if constexpr (ISSUE) DMA_A(0);
+                RDB(b1, 1, 1); RDA(a1, 1, 1); MF(a0, b0, 0, 1);
+                SB();
+                if constexpr (ISSUE) DMA_B(0);
+                MF(a0, b0, 1, 0);
+                SB();
+                if constexpr (ISSUE) DMA_B(1);
+                MF(a0, b0, 1, 1);
+            }
             SB();
             if constexpr (ISSUE) { srcA += panelA; srcB += panelB; }
             if constexpr (NEXT) {
@@ -440,36 +477,42 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                 __builtin_amdgcn_s_barrier();
                 SB();
-                st = lds + ((h + 1) & 3) * kSlot;
+                st = lds + next_slot;
                 RDA(a0, 0, 0); RDB(b0, 0, 0); RDB(b0, 0, 1); MF(a1, b1, 0, 0);
                 SB();
-                RDA(a0, 0, 1); RDA(a0, 0, 2); MF(a1, b1, 0, 1);
-                SB();
-                RDA(a0, 0, 3); MF(a1, b1, 1, 0);
-                SB();
-                MF(a1, b1, 1, 1); MF(a1, b1, 2, 0); MF(a1, b1, 2, 1); MF(a1, b1, 3, 0); MF(a1, b1, 3, 1);
+                if constexpr (MI == 4) {
+                    RDA(a0, 0, 1); RDA(a0, 0, 2); MF(a1, b1, 0, 1);
+                    SB();
+                    RDA(a0, 0, 3); MF(a1, b1, 1, 0);
+                    SB();
+                    MF(a1, b1, 1, 1); MF(a1, b1, 2, 0); MF(a1, b1, 2, 1); MF(a1, b1, 3, 0); MF(a1, b1, 3, 1);
+                } else {
+                    RDA(a0, 0, 1); MF(a1, b1, 0, 1);
+                    SB();
+                    MF(a1, b1, 1, 0); MF(a1, b1, 1, 1);
+                }
                 SB();
             } else {
-                MF(a1, b1, 0, 0); MF(a1, b1, 0, 1); MF(a1, b1, 1, 0); MF(a1, b1, 1, 1);
-                MF(a1, b1, 2, 0); MF(a1, b1, 2, 1); MF(a1, b1, 3, 0); MF(a1, b1, 3, 1);
+#pragma unroll
+                for (int i = 0; i < MI; ++i) { MF(a1, b1, i, 0); MF(a1, b1, i, 1); }
             }
+            if constexpr (MI != 4) slot = next_slot;
         };
-        using I0 = std::integral_constant<int, 0>;
-        using I4 = std::integral_constant<int, 4>;
-        using I8 = std::integral_constant<int, 8>;
-        using I63 = std::integral_constant<int, 63>;
+        using std::integral_constant;
         int h = 0;
         if (relaxed) {
-            // panels 1 and 2 landed together with panel 0: nothing to wait for, and a count of 8
+            // the panels requested before the epilogue landed together with panel 0: nothing to wait for, and a count
             // here would wait for the previous tile's stores
-            half(0, std::true_type{}, I63{}, std::true_type{});
-            half(1, std::true_type{}, I63{}, std::true_type{});
-            h = 2;
+#pragma unroll
+            for (; h < kAhead - 1; ++h) half(h, std::true_type{}, integral_constant<int, 63>{}, std::true_type{});
         }
-        for (; h + 3 < nh; ++h) half(h, std::true_type{}, I8{}, std::true_type{});
-        if (h + 2 < nh) { half(h, std::false_type{}, I4{}, std::true_type{}); ++h; }
-        if (h + 1 < nh) { half(h, std::false_type{}, I0{}, std::true_type{}); ++h; }
-        half(h, std::false_type{}, I0{}, std::false_type{});
+        for (; h + kAhead < nh; ++h) half(h, std::true_type{}, integral_constant<int, (kAhead - 1) * kLoads>{}, std::true_type{});
+        if constexpr (kAhead > 3) {
+            if (h + 3 < nh) { half(h, std::false_type{}, integral_constant<int, 2 * kLoads>{}, std::true_type{}); ++h; }
+        }
+        if (h + 2 < nh) { half(h, std::false_type{}, integral_constant<int, kLoads>{}, std::true_type{}); ++h; }
+        if (h + 1 < nh) { half(h, std::false_type{}, integral_constant<int, 0>{}, std::true_type{}); ++h; }
+        half(h, std::false_type{}, integral_constant<int, 0>{}, std::false_type{});
 #undef RDA
 #undef RDB
 
@@ -482,13 +525,13 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
         // The slabs live in the last ring slot and behind the ring; the next tile's first three
         // panels are already on their way into the other slots.
         const int rd_r = lane >> 4, rd_c = lane & 15;
-        const int64_t t_lane = cm0 + wm * 128 + rd_r;              // + 32 i + 4 p
+        const int64_t t_lane = cm0 + wm * (32 * MI) + rd_r;              // + 32 i + 4 p
         const int64_t n = cn0 + wn * 64 + rd_c * 4;                // this lane's four channels
         const bool n_ok = n < g.N;                                 // N % 4 == 0: all four or none
 
         // everything the epilogue reads from memory is requested before the next tile's panels,
         // so that waiting for it does not wait for them
-        int rsx[2] = {0, 0};   // row sums of this wave's 128 tokens, two per lane: token 64 h + lane
+        int rsx[MI / 2] = {};   // row sums of this wave's 32 MI tokens, one per lane and 64: token 64 h + lane
         Float4 sw = {{0.f, 0.f, 0.f, 0.f}}, bs = {{0.f, 0.f, 0.f, 0.f}};
         int zwv[4] = {0, 0, 0, 0};          // Z'w = Z_w - 128 of this lane's channels
         unsigned cn[4] = {0, 0, 0, 0};      // K Z'x Z'w - Z'x rowsum_w, in wrap-around 32-bit arithmetic
@@ -504,8 +547,8 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
             // [0, 255] guarantee for K <= 32768; anything else is flagged
             if (zx < -128 || zx > 127) est |= AWEQ_ST_ZEROPOINT;
 #pragma unroll
-            for (int hh = 0; hh < 2; ++hh) {
-                const int64_t t = cm0 + wm * 128 + hh * 64 + lane;
+            for (int hh = 0; hh < MI / 2; ++hh) {
+                const int64_t t = cm0 + wm * (32 * MI) + hh * 64 + lane;
                 rsx[hh] = t < g.T ? g.rowsum_x[t] : 0;
             }
             if (n_ok) {
@@ -530,8 +573,8 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
             }
             // pin the values in registers here: the compiler's wait for them then sits before the
             // panel requests below, which it cannot see, instead of behind them
-            asm volatile("" : "+v"(rsx[0]));
-            asm volatile("" : "+v"(rsx[1]));
+#pragma unroll
+            for (int hh = 0; hh < MI / 2; ++hh) asm volatile("" : "+v"(rsx[hh]));
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 asm volatile("" : "+v"(sw.f[c]));
@@ -579,7 +622,7 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
                 bsd[c] = (double)bs.f[c];
             }
         }
-        char* slab = lds + 3 * kSlot + wave * 8192;
+        char* slab = lds + TL::kSlabs + wave * 8192;
         const int wr_t = lane & 31;
         const int wr_sw = wr_t & 15, wr_half = lane >> 5;           // chunk (8 j + 2 q + l / 32) ^ (t & 15)
         // column sums of the accumulator itself (never of the corrected integer, which wraps for zero points far
@@ -592,7 +635,7 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
         const bool yq_pad = (EPI & 2) != 0 && !n_ok && cn0 + wn * 64 < g.N;   // zero fill of the last panel
         int8_t* const yq_lane = (EPI & 2) != 0 ? g.yq + (((cn0 >> 6) + wn) * g.T) * kPanel + rd_c * 4 : nullptr;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < MI; ++i) {
 #pragma unroll
             for (int j = 0; j < 2; ++j)
 #pragma unroll
@@ -749,7 +792,7 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
         if (!more) break;
         vb = nvb;
         // the panels requested before the epilogue have landed
-        relaxed = kStores > 0 && nh >= 6 && cm0 + BM <= g.T && cn0 + BN <= g.N;
+        relaxed = kStores > 0 && nh >= 2 * kAhead && cm0 + TL::kRows <= g.T && cn0 + BN <= g.N;
         if (relaxed) wait_vm<kStores>();
         else wait_vm<0>();
     }
@@ -780,16 +823,19 @@ using namespace aweq;
 
 namespace aweq {
 
-// tile / patch plan of a launch
-static int plan_gemm(GemmArgs& g, int64_t T, int64_t N, int64_t K, int64_t& blocks)
+// rounds of 256 workgroups the planned walk takes
+static int64_t rounds_of(const GemmArgs& g) { return cdiv(g.n_ids, 256); }
+
+// tile / patch plan of a launch on tiles of bm tokens x 256 channels
+static int plan_gemm(GemmArgs& g, int bm, int64_t& blocks)
 {
-    const int64_t tiles_m = cdiv(T, BM), tiles_n = cdiv(N, BN);
+    const int64_t tiles_m = cdiv(g.T, bm), tiles_n = cdiv(g.N, BN);
     if (tiles_m * tiles_n > (1ll << 30)) return AWEQ_ERR_SHAPE;
     g.tiles_m = (int)tiles_m; g.tiles_n = (int)tiles_n;
     // patch of output tiles an XCD works on at a time: 32 tiles (one per compute unit), 8 (t) x 4 (n);
     // 4 x 8 when the contraction is long against N: the activation panels, the operand that does not
     // fit the memory-side cache, are then fetched half as often (1-2 % here, 9 % in the binary16 GEMM)
-    const int want_n = K >= 2 * N ? 8 : 4;
+    const int want_n = g.K >= 2 * g.N ? 8 : 4;
     g.patch_n = (int)(tiles_n < want_n ? tiles_n : want_n);
     g.patch_m = 32 / g.patch_n;
     if (g.patch_m > tiles_m) g.patch_m = (int)tiles_m;
@@ -808,21 +854,46 @@ static int plan_gemm(GemmArgs& g, int64_t T, int64_t N, int64_t K, int64_t& bloc
     g.n_main = (int)(patches_m * g.main_pn);
     g.n_patches_fast = g.n_main + (g.tail_cols ? (int)cdiv(tiles_m, g.tail_pm) : 0);
     g.n_ids = (int)(cdiv(g.n_patches_fast, kXcds) * kXcds * g.per_patch);   // <= blocks
+    // One round of workgroups, or a few where patches leave so many ids without a tile that it costs another: the
+    // tiles in one sequence, up and down strips of strip_m tile rows, an equal run of it for every XCD
+    // (us, patches -> sequence: K = 4096: 1000 tokens x 4096 channels 34.8 -> 28.7, 2304 x 4096 59.7 -> 50.2, 2300 x 7168 88.8 -> 63.2)
+    const int64_t tiles = tiles_m * tiles_n, ideal = cdiv(tiles, 256);
+    g.strip_m = 0;
+    if (ideal == 1 || (ideal <= 4 && rounds_of(g) > ideal)) {
+        g.strip_m = want_n == 8 ? 4 : 8;
+        g.run = ideal == 1 ? (int)cdiv(tiles, kXcds) : 32;
+        g.n_ids = (int)(ideal * g.run * kXcds);
+    }
+    return AWEQ_OK;
+}
+
+// The tiled kernel's plan: tiles of 256 tokens, or of 128 (`half`) where their rounds of workgroups, each kHalfTileCost of
+// a round of the larger ones, take less: a round lasts as long however few of the 256 compute units have a tile.
+// (us, 256 -> 128 tokens per tile, binary16 output: 2048 tokens 4096 x 11008 147 -> 83.9, 4096 x 4096 63.0 -> 36.3; 1000 tokens 4096 x 4096 46.2 -> 34.8.)
+static int plan_tiled(GemmArgs& g, bool& half, double& cost, int64_t& blocks)
+{
+    GemmArgs h = g;
+    int64_t blocks_h = 0;
+    const int rc = plan_gemm(g, BM, blocks);
+    if (rc != AWEQ_OK) return rc;
+    cost = (double)rounds_of(g);
+    half = plan_gemm(h, BM / 2, blocks_h) == AWEQ_OK && kHalfTileCost * (double)rounds_of(h) < cost;
+    if (half) { g = h; cost = kHalfTileCost * (double)rounds_of(h); }
     return AWEQ_OK;
 }
 
 // persistent launch of a fast-kernel instantiation: one workgroup per compute unit (a multiple of
 // 8, so that id % 8 stays the XCD)
-static int launch_fast(const void* fn, GemmArgs& g, hipStream_t st)
+static int launch_fast(const void* fn, int lds, GemmArgs& g, hipStream_t st)
 {
     const int64_t blocks = g.n_ids;
     int dev = 0, cus = 0;
-    if (device_cus(dev, cus) != AWEQ_OK || raise_lds_limit(fn, dev, fast::kLds) != AWEQ_OK) return AWEQ_ERR_LAUNCH;
+    if (device_cus(dev, cus) != AWEQ_OK || raise_lds_limit(fn, dev, lds) != AWEQ_OK) return AWEQ_ERR_LAUNCH;
     void* args[] = {&g};
     int64_t grid = (cus / kXcds) * kXcds;
     if (grid < kXcds) grid = kXcds;
     if (grid > blocks) grid = blocks;
-    if (hipLaunchKernel(fn, dim3((unsigned)grid), dim3(fast::kThreads), args, fast::kLds, st) != hipSuccess) return AWEQ_ERR_LAUNCH;
+    if (hipLaunchKernel(fn, dim3((unsigned)grid), dim3(fast::kThreads), args, lds, st) != hipSuccess) return AWEQ_ERR_LAUNCH;
     return launch_status();
 }
 
@@ -917,29 +988,33 @@ extern "C" int aweq_w8a8_gemm(const void* X, aweq_dtype x_dt, int64_t T, int64_t
     clear_fused(g);
     g.w_per_tensor = w_group == -1;
     g.status = status;
-    int64_t blocks = 0;
-    const int prc = plan_gemm(g, T, N, K, blocks);
-    if (prc != AWEQ_OK) return prc;
-
-    if (colsum_acc) zero_fill_u32_gemm<<<(unsigned)cdiv(2 * N, 256), 256, 0, st>>>(reinterpret_cast<uint32_t*>(colsum_acc), 2 * N);
-
     // the fast kernel stores 16-byte output quads
     bool fast_ok = (N % 4) == 0;
     if (out_i32 && (!aligned16(out_i32) || (ldo % 4) != 0)) fast_ok = false;
     if (out_deq && (!aligned16(out_deq) || (ldo % 4) != 0 || (w_group == 0 && (!aligned16(step_w) || !aligned16(zero_w))) ||
                     !aligned16(rowsum_w) || (bias && !aligned16(bias))))
         fast_ok = false;
+    bool half = false;
+    double tiled_cost = 0.0;
+    int64_t blocks = 0;
+    const int prc = fast_ok ? plan_tiled(g, half, tiled_cost, blocks) : plan_gemm(g, BM, blocks);
+    if (prc != AWEQ_OK) return prc;
+
+    if (colsum_acc) zero_fill_u32_gemm<<<(unsigned)cdiv(2 * N, 256), 256, 0, st>>>(reinterpret_cast<uint32_t*>(colsum_acc), 2 * N);
+
     const FewPlan few = plan_few(T, N);
-    if (fast_ok && few.cost < kTiledRoundCost * (double)cdiv(cdiv(T, BM) * cdiv(N, BN), 256)) return launch_gemm_i8_few(g, few, st);
+    if (fast_ok && few.cost < kTiledRoundCost * tiled_cost) return launch_gemm_i8_few(g, few, st);
     if (fast_ok) {
         const int deq = out_deq ? (out_dt == AWEQ_F16 ? 2 : 1) : 0;
         const void* fn = nullptr;
-#define AWEQ_PICK(I, D, C) if ((out_i32 != nullptr) == I && deq == D && (colsum_acc != nullptr) == C) fn = reinterpret_cast<const void*>(fast::gemm_i8_fast<I, D, C>);
+#define AWEQ_PICK(I, D, C)                                                                                             \
+    if ((out_i32 != nullptr) == I && deq == D && (colsum_acc != nullptr) == C)                                         \
+        fn = half ? reinterpret_cast<const void*>(fast::gemm_i8_fast<2, I, D, C>) : reinterpret_cast<const void*>(fast::gemm_i8_fast<4, I, D, C>);
         AWEQ_PICK(true, 0, true) AWEQ_PICK(true, 0, false) AWEQ_PICK(false, 0, true)
         AWEQ_PICK(true, 1, true) AWEQ_PICK(true, 1, false) AWEQ_PICK(false, 1, true) AWEQ_PICK(false, 1, false)
         AWEQ_PICK(true, 2, true) AWEQ_PICK(true, 2, false) AWEQ_PICK(false, 2, true) AWEQ_PICK(false, 2, false)
 #undef AWEQ_PICK
-        return launch_fast(fn, g, st);
+        return launch_fast(fn, half ? fast::Tile<2>::kLds : fast::Tile<4>::kLds, g, st);
     }
     const size_t lds_bytes = 2 * 2 * kTileBytes;  // 64 KiB
     int dev = 0, cus = 0;
@@ -989,8 +1064,10 @@ extern "C" int aweq_w8a8_gemm_fused(const int8_t* xq, int64_t T, int64_t K, cons
         g.next_inv_s = next_inv_s; g.next_step = next_step; g.next_zero = next_zero;
         g.yq = yq; g.rowsum_y = rowsum_y; g.colsum_yq = reinterpret_cast<long long*>(colsum_yq);
     }
+    bool half = false;
+    double tiled_cost = 0.0;
     int64_t blocks = 0;
-    const int prc = plan_gemm(g, T, N, K, blocks);
+    const int prc = plan_tiled(g, half, tiled_cost, blocks);
     if (prc != AWEQ_OK) return prc;
 
     hipStream_t st = as_stream(stream);
@@ -1001,10 +1078,13 @@ extern "C" int aweq_w8a8_gemm_fused(const int8_t* xq, int64_t T, int64_t K, cons
     const int epi = (want_stats ? 1 : 0) | (want_quant ? 2 : 0);
     const bool store = out_f16 != nullptr;
     const void* fn = nullptr;
-#define AWEQ_PICK(E, S) if (epi == E && store == S) fn = reinterpret_cast<const void*>(fast::gemm_i8_fast<false, 2, true, E, S>);
+#define AWEQ_PICK(E, S)                                                                                                \
+    if (epi == E && store == S)                                                                                        \
+        fn = half ? reinterpret_cast<const void*>(fast::gemm_i8_fast<2, false, 2, true, E, S>)                         \
+                  : reinterpret_cast<const void*>(fast::gemm_i8_fast<4, false, 2, true, E, S>);
     AWEQ_PICK(1, true) AWEQ_PICK(1, false) AWEQ_PICK(2, true) AWEQ_PICK(2, false) AWEQ_PICK(3, true) AWEQ_PICK(3, false)
 #undef AWEQ_PICK
-    const int rc = launch_fast(fn, g, st);
+    const int rc = launch_fast(fn, half ? fast::Tile<2>::kLds : fast::Tile<4>::kLds, g, st);
     if (rc != AWEQ_OK) return rc;
     if (want_stats)
         fused_stats_finish<<<(unsigned)cdiv(N, 256), 256, 0, st>>>(g.ykeys, g.yfix, N, T, ycmin, ycmax, ycsum, ycount, accumulate, status);

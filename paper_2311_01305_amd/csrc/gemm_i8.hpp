@@ -25,6 +25,7 @@ struct GemmArgs {
     int n_ids;  // workgroup ids that may name a tile (whole rounds of patches over the XCDs)
     // tiled kernel: the tile columns that do not fill a whole patch column form patches of their own shape
     int main_pn, n_main, tail_cols, tail_pm, per_patch, n_patches_fast;
+    int strip_m, run;   // or (strip_m > 0) one sequence of tiles, `run` of it per XCD and round
     // fused epilogues on the de-quantised binary16 output y (the next layer's calibration input)
     int act;                    // 0: none, 1: ReLU before y is rounded
     uint32_t* ykeys;            // [2 N] order-preserving keys of the column minimum / maximum of y
@@ -48,5 +49,6 @@ int launch_gemm_i8_few(const GemmArgs& g, const FewPlan& p, hipStream_t st);
 
 // Time of one round of workgroups at K = 8192 (us; every kernel's time is proportional to K): 256 tiles of 256 x 256
 constexpr double kTiledRoundCost = 68.0;
+constexpr double kHalfTileCost = 0.57;   // the same of 128 x 256 tiles, against that
 
 }  // namespace aweq
