@@ -53,51 +53,59 @@ struct Scale {
     }
 };
 
-// The 8 codes k = 8 d .. 8 d + 7 of the 32 as four binary16 pairs (k, k + 4): (0,4) (1,5) (2,6) (3,7),
+// The 24 bits of codes k = 8 d .. 8 d + 7 of the 32 (bits above them are not cleared)
+__device__ __forceinline__ uint32_t fields3(const RawCodes<3>& rc, int d)
+{
+    return d == 0 ? rc.w[0] : d == 1 ? __builtin_amdgcn_alignbit(rc.w[1], rc.w[0], 24)
+         : d == 2 ? __builtin_amdgcn_alignbit(rc.w[2], rc.w[1], 16) : rc.w[2] >> 8;
+}
+
+// Eight codes (32 bits of INT4 / the low 24 bits of INT3) as four binary16 pairs (k, k + 4): (0,4) (1,5) (2,6) (3,7),
 // the order the fields come out of the packed formats in (a caller that needs natural order permutes).
 // 13 (INT4) / 16 (INT3) packed operations per 8 codes.
 template <int BITS>
-__device__ __forceinline__ void dequant8_pairs(const RawCodes<BITS>& rc, int d, const Scale<BITS>& s, uint32_t o[4])
+__device__ __forceinline__ void dequant_word(uint32_t w, const Scale<BITS>& s, uint32_t o[4])
 {
     if constexpr (BITS == 4) {
-        const uint32_t w = rc.w[d], v = w >> 8;
+        const uint32_t v = w >> 8;
         o[0] = as_u32((as_h2((w & 0x000f000fu) | 0x64006400u) - s.z0) * s.step);
         o[1] = as_u32((as_h2((w & 0x00f000f0u) | 0x54005400u) - s.z1) * s.step);
         o[2] = as_u32((as_h2((v & 0x000f000fu) | 0x64006400u) - s.z0) * s.step);
         o[3] = as_u32((as_h2((v & 0x00f000f0u) | 0x54005400u) - s.z1) * s.step);
     } else {
-        // 24 bits of the stream; codes 4 .. 7 (bits 12 .. 23) move up by 4, so that both halves hold
-        // four fields at bits 0, 3, 6, 9
-        const uint32_t f = d == 0 ? rc.w[0] : d == 1 ? __builtin_amdgcn_alignbit(rc.w[1], rc.w[0], 24)
-                         : d == 2 ? __builtin_amdgcn_alignbit(rc.w[2], rc.w[1], 16) : rc.w[2] >> 8;
-        const uint32_t g = (f & 0x0fffu) | ((f << 4) & 0x0fff0000u), h = g >> 9;
+        // codes 4 .. 7 (bits 12 .. 23) move up by 4, so that both halves hold four fields at bits 0, 3, 6, 9
+        const uint32_t g = (w & 0x0fffu) | ((w << 4) & 0x0fff0000u), h = g >> 9;
         o[0] = as_u32((as_h2((g & 0x00070007u) | 0x64006400u) - s.z0) * s.step);
         o[1] = as_u32((as_h2((g & 0x00380038u) | 0x58005800u) - s.z1) * s.step);
         o[2] = as_u32((as_h2((g & 0x01c001c0u) | 0x4c004c00u) - s.z2) * s.step);
         o[3] = as_u32((as_h2((h & 0x00070007u) | 0x64006400u) - s.z0) * s.step);
     }
 }
+template <int BITS>
+__device__ __forceinline__ void dequant8_pairs(const RawCodes<BITS>& rc, int d, const Scale<BITS>& s, uint32_t o[4])
+{
+    if constexpr (BITS == 4) dequant_word<4>(rc.w[d], s, o);
+    else dequant_word<3>(fields3(rc, d), s, o);
+}
 
 // the same pairs for any zero point, through binary32
 template <int BITS>
-__device__ __forceinline__ void dequant8_pairs_any(const RawCodes<BITS>& rc, int d, const Scale<BITS>& s, uint32_t o[4])
+__device__ __forceinline__ void dequant_word_any(uint32_t w, const Scale<BITS>& s, uint32_t o[4])
 {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         int c[2];
 #pragma unroll
-        for (int e = 0; e < 2; ++e) {
-            const int k = 8 * d + q + 4 * e;
-            if constexpr (BITS == 4) c[e] = (int)((rc.w[k >> 3] >> (4 * (k & 7))) & 15u);
-            else {
-                const int bit = 3 * k, idx = bit >> 5, sh = bit & 31;
-                const uint32_t lo = rc.w[idx], hi = idx + 1 < 3 ? rc.w[idx + 1] : 0u;
-                c[e] = (int)(__builtin_amdgcn_alignbit(hi, lo, sh) & 7u);
-            }
-        }
+        for (int e = 0; e < 2; ++e) c[e] = (int)((w >> (BITS * (q + 4 * e))) & ((1u << BITS) - 1u));
         const f16x2 h = {(_Float16)((float)(c[0] - s.z) * s.step_f), (_Float16)((float)(c[1] - s.z) * s.step_f)};
         o[q] = as_u32(h);
     }
+}
+template <int BITS>
+__device__ __forceinline__ void dequant8_pairs_any(const RawCodes<BITS>& rc, int d, const Scale<BITS>& s, uint32_t o[4])
+{
+    if constexpr (BITS == 4) dequant_word_any<4>(rc.w[d], s, o);
+    else dequant_word_any<3>(fields3(rc, d), s, o);
 }
 
 // pairs (k, k + 4) -> natural order (and back: the permutation of a 16-byte chunk of 8 halves is its own kind)

@@ -38,7 +38,6 @@ constexpr int BM = 256, BN = 256, BK = 64;
 constexpr int kChunksPerRow = BK / 16;                       // 16-byte chunks per tile row
 constexpr int kTileBytes = BM * BK;                          // 16 KiB per operand tile
 constexpr int kLoadsPerThread = BM * kChunksPerRow / kGemmThreads;  // 4
-constexpr int kXcds = 8;
 
 // chunk position of (row, chunk) inside a tile row: rows that share LDS banks get distinct
 // positions both for 8 and for 16 consecutive rows read at one chunk index
@@ -71,10 +70,10 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_i8_generic(GemmArgs g)
     // ---- workgroup -> output tile.  Consecutive workgroup ids go round-robin over the XCDs,
     // so id % 8 names the XCD; each XCD walks its own sequence of patch_m x patch_n patches.
     const int b = blockIdx.x;
-    const int xcd = b % kXcds;
-    const int seq = b / kXcds;
+    const int xcd = b % kXcdCount;
+    const int seq = b / kXcdCount;
     const int per_patch = g.patch_m * g.patch_n;
-    const int patch = (seq / per_patch) * kXcds + xcd;
+    const int patch = (seq / per_patch) * kXcdCount + xcd;
     if (patch >= g.n_patches) return;
     const int within = seq % per_patch;
     const int pm = patch / g.patches_n, pn = patch % g.patches_n;
@@ -290,39 +289,6 @@ __device__ __forceinline__ void wait_vm()
 
 #define SB() __builtin_amdgcn_sched_barrier(0)
 #define MF(A_, B_, i, j) acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(B_[j], A_[i], acc[i][j], 0, 0, 0)
-
-// workgroup id -> output tile (false: the id names no tile).  Ids go round-robin over the XCDs,
-// so id % 8 names the XCD; each XCD walks its own sequence of patch_m x patch_n patches.
-// The last tile columns, when they do not fill a patch column, are walked as patches of their own
-// shape (tail_pm x tail_cols, as many tiles as fit 32): a ragged patch would leave part of the XCD's
-// workgroups without a tile, they would run ahead to their next id and the XCD's workgroups would
-// stop walking K together, which is what lets them share operand panels in the L2.
-__host__ __device__ __forceinline__ bool tile_of(const GemmArgs& g, int vb, int& tile_m, int& tile_n)
-{
-    const int xcd = vb % kXcds, seq = vb / kXcds;
-    if (g.strip_m) {
-        const int l = ((seq / g.run) * kXcds + xcd) * g.run + seq % g.run;
-        if (l >= g.tiles_m * g.tiles_n) return false;
-        const int strip = l / (g.strip_m * g.tiles_n), in = l % (g.strip_m * g.tiles_n);
-        const int height = min(g.strip_m, g.tiles_m - strip * g.strip_m);
-        tile_m = strip * g.strip_m + in % height;
-        tile_n = in / height;
-        return true;
-    }
-    const int patch = (seq / g.per_patch) * kXcds + xcd;
-    if (patch >= g.n_patches_fast) return false;
-    const int within = seq % g.per_patch;
-    if (patch < g.n_main) {
-        const int pm = patch / g.main_pn, pn = patch % g.main_pn;
-        tile_m = pm * g.patch_m + within % g.patch_m;
-        tile_n = pn * g.patch_n + within / g.patch_m;
-        return tile_m < g.tiles_m && tile_n < g.tiles_n;
-    }
-    if (within >= g.tail_pm * g.tail_cols) return false;
-    tile_m = (patch - g.n_main) * g.tail_pm + within % g.tail_pm;
-    tile_n = g.main_pn * g.patch_n + within / g.tail_pm;
-    return tile_m < g.tiles_m;
-}
 
 // DEQ: 0 none, 1 fp32, 2 fp16.  Persistent: the grid is one workgroup per compute unit
 // (a multiple of 8), workgroup b takes the ids b, b + grid, b + 2 grid, ...; the first panels
@@ -823,50 +789,6 @@ using namespace aweq;
 
 namespace aweq {
 
-// rounds of 256 workgroups the planned walk takes
-static int64_t rounds_of(const GemmArgs& g) { return cdiv(g.n_ids, 256); }
-
-// tile / patch plan of a launch on tiles of bm tokens x 256 channels
-static int plan_gemm(GemmArgs& g, int bm, int64_t& blocks)
-{
-    const int64_t tiles_m = cdiv(g.T, bm), tiles_n = cdiv(g.N, BN);
-    if (tiles_m * tiles_n > (1ll << 30)) return AWEQ_ERR_SHAPE;
-    g.tiles_m = (int)tiles_m; g.tiles_n = (int)tiles_n;
-    // patch of output tiles an XCD works on at a time: 32 tiles (one per compute unit), 8 (t) x 4 (n);
-    // 4 x 8 when the contraction is long against N: the activation panels, the operand that does not
-    // fit the memory-side cache, are then fetched half as often (1-2 % here, 9 % in the binary16 GEMM)
-    const int want_n = g.K >= 2 * g.N ? 8 : 4;
-    g.patch_n = (int)(tiles_n < want_n ? tiles_n : want_n);
-    g.patch_m = 32 / g.patch_n;
-    if (g.patch_m > tiles_m) g.patch_m = (int)tiles_m;
-    g.patches_n = (int)cdiv(tiles_n, g.patch_n);
-    const int64_t patches_m = cdiv(tiles_m, g.patch_m);
-    g.n_patches = (int)(patches_m * g.patches_n);
-    const int64_t rounds = cdiv(g.n_patches, kXcds);
-    blocks = rounds * kXcds * g.patch_m * g.patch_n;   // grid of the generic kernel
-    if (blocks > 0x7fffffffll) return AWEQ_ERR_SHAPE;
-    // the tiled kernel's walk: whole patch columns first, then the remaining tile columns as patches of their own
-    g.per_patch = g.patch_m * g.patch_n;
-    g.tail_cols = (int)(tiles_n % g.patch_n);
-    g.main_pn = (int)(tiles_n / g.patch_n);
-    g.tail_pm = g.tail_cols ? g.per_patch / g.tail_cols : 0;
-    if (g.tail_cols && g.tail_pm > tiles_m) g.tail_pm = (int)tiles_m;
-    g.n_main = (int)(patches_m * g.main_pn);
-    g.n_patches_fast = g.n_main + (g.tail_cols ? (int)cdiv(tiles_m, g.tail_pm) : 0);
-    g.n_ids = (int)(cdiv(g.n_patches_fast, kXcds) * kXcds * g.per_patch);   // <= blocks
-    // One round of workgroups, or a few where patches leave so many ids without a tile that it costs another: the
-    // tiles in one sequence, up and down strips of strip_m tile rows, an equal run of it for every XCD
-    // (us, patches -> sequence: K = 4096: 1000 tokens x 4096 channels 34.8 -> 28.7, 2304 x 4096 59.7 -> 50.2, 2300 x 7168 88.8 -> 63.2)
-    const int64_t tiles = tiles_m * tiles_n, ideal = cdiv(tiles, 256);
-    g.strip_m = 0;
-    if (ideal == 1 || (ideal <= 4 && rounds_of(g) > ideal)) {
-        g.strip_m = want_n == 8 ? 4 : 8;
-        g.run = ideal == 1 ? (int)cdiv(tiles, kXcds) : 32;
-        g.n_ids = (int)(ideal * g.run * kXcds);
-    }
-    return AWEQ_OK;
-}
-
 // The tiled kernel's plan: tiles of 256 tokens, or of 128 (`half`) where their rounds of workgroups, each kHalfTileCost of
 // a round of the larger ones, take less: a round lasts as long however few of the 256 compute units have a tile.
 // (us, 256 -> 128 tokens per tile, binary16 output: 2048 tokens 4096 x 11008 147 -> 83.9, 4096 x 4096 63.0 -> 36.3; 1000 tokens 4096 x 4096 46.2 -> 34.8.)
@@ -874,27 +796,12 @@ static int plan_tiled(GemmArgs& g, bool& half, double& cost, int64_t& blocks)
 {
     GemmArgs h = g;
     int64_t blocks_h = 0;
-    const int rc = plan_gemm(g, BM, blocks);
+    const int rc = plan_walk(g, g.T, g.N, g.K, BM, blocks);
     if (rc != AWEQ_OK) return rc;
     cost = (double)rounds_of(g);
-    half = plan_gemm(h, BM / 2, blocks_h) == AWEQ_OK && kHalfTileCost * (double)rounds_of(h) < cost;
+    half = plan_walk(h, h.T, h.N, h.K, BM / 2, blocks_h) == AWEQ_OK && kHalfTileCost * (double)rounds_of(h) < cost;
     if (half) { g = h; cost = kHalfTileCost * (double)rounds_of(h); }
     return AWEQ_OK;
-}
-
-// persistent launch of a fast-kernel instantiation: one workgroup per compute unit (a multiple of
-// 8, so that id % 8 stays the XCD)
-static int launch_fast(const void* fn, int lds, GemmArgs& g, hipStream_t st)
-{
-    const int64_t blocks = g.n_ids;
-    int dev = 0, cus = 0;
-    if (device_cus(dev, cus) != AWEQ_OK || raise_lds_limit(fn, dev, lds) != AWEQ_OK) return AWEQ_ERR_LAUNCH;
-    void* args[] = {&g};
-    int64_t grid = (cus / kXcds) * kXcds;
-    if (grid < kXcds) grid = kXcds;
-    if (grid > blocks) grid = blocks;
-    if (hipLaunchKernel(fn, dim3((unsigned)grid), dim3(fast::kThreads), args, lds, st) != hipSuccess) return AWEQ_ERR_LAUNCH;
-    return launch_status();
 }
 
 static void clear_fused(GemmArgs& g)
@@ -997,7 +904,7 @@ extern "C" int aweq_w8a8_gemm(const void* X, aweq_dtype x_dt, int64_t T, int64_t
     bool half = false;
     double tiled_cost = 0.0;
     int64_t blocks = 0;
-    const int prc = fast_ok ? plan_tiled(g, half, tiled_cost, blocks) : plan_gemm(g, BM, blocks);
+    const int prc = fast_ok ? plan_tiled(g, half, tiled_cost, blocks) : plan_walk(g, g.T, g.N, g.K, BM, blocks);
     if (prc != AWEQ_OK) return prc;
 
     if (colsum_acc) zero_fill_u32_gemm<<<(unsigned)cdiv(2 * N, 256), 256, 0, st>>>(reinterpret_cast<uint32_t*>(colsum_acc), 2 * N);
@@ -1014,7 +921,7 @@ extern "C" int aweq_w8a8_gemm(const void* X, aweq_dtype x_dt, int64_t T, int64_t
         AWEQ_PICK(true, 1, true) AWEQ_PICK(true, 1, false) AWEQ_PICK(false, 1, true) AWEQ_PICK(false, 1, false)
         AWEQ_PICK(true, 2, true) AWEQ_PICK(true, 2, false) AWEQ_PICK(false, 2, true) AWEQ_PICK(false, 2, false)
 #undef AWEQ_PICK
-        return launch_fast(fn, half ? fast::Tile<2>::kLds : fast::Tile<4>::kLds, g, st);
+        return launch_persistent(fn, fast::kThreads, half ? fast::Tile<2>::kLds : fast::Tile<4>::kLds, &g, g.n_ids, st);
     }
     const size_t lds_bytes = 2 * 2 * kTileBytes;  // 64 KiB
     int dev = 0, cus = 0;
@@ -1084,7 +991,7 @@ extern "C" int aweq_w8a8_gemm_fused(const int8_t* xq, int64_t T, int64_t K, cons
                   : reinterpret_cast<const void*>(fast::gemm_i8_fast<4, false, 2, true, E, S>);
     AWEQ_PICK(1, true) AWEQ_PICK(1, false) AWEQ_PICK(2, true) AWEQ_PICK(2, false) AWEQ_PICK(3, true) AWEQ_PICK(3, false)
 #undef AWEQ_PICK
-    const int rc = launch_fast(fn, half ? fast::Tile<2>::kLds : fast::Tile<4>::kLds, g, st);
+    const int rc = launch_persistent(fn, fast::kThreads, half ? fast::Tile<2>::kLds : fast::Tile<4>::kLds, &g, g.n_ids, st);
     if (rc != AWEQ_OK) return rc;
     if (want_stats)
         fused_stats_finish<<<(unsigned)cdiv(N, 256), 256, 0, st>>>(g.ykeys, g.yfix, N, T, ycmin, ycmax, ycsum, ycount, accumulate, status);

@@ -1,10 +1,10 @@
 // Arguments of the int8 GEMM kernels, and the few-token form (gemm_i8_few.hip) that aweq_w8a8_gemm chooses.
 #pragma once
-#include "common.hpp"
+#include "tile_walk.hpp"
 
 namespace aweq {
 
-struct GemmArgs {
+struct GemmArgs : TileWalk {
     const int8_t* A;   // xq [T x K], K-panel layout
     const int8_t* B;   // wq [N x K], K-panel layout
     int64_t T, N, K;
@@ -21,11 +21,6 @@ struct GemmArgs {
     const int32_t* rowsum_w;
     const float* bias;
     int w_per_tensor;  // step_w / zero_w hold one entry for the whole weight instead of one per output channel
-    int tiles_m, tiles_n, patch_m, patch_n, patches_n, n_patches;
-    int n_ids;  // workgroup ids that may name a tile (whole rounds of patches over the XCDs)
-    // tiled kernel: the tile columns that do not fill a whole patch column form patches of their own shape
-    int main_pn, n_main, tail_cols, tail_pm, per_patch, n_patches_fast;
-    int strip_m, run;   // or (strip_m > 0) one sequence of tiles, `run` of it per XCD and round
     // fused epilogues on the de-quantised binary16 output y (the next layer's calibration input)
     int act;                    // 0: none, 1: ReLU before y is rounded
     uint32_t* ykeys;            // [2 N] order-preserving keys of the column minimum / maximum of y
