@@ -187,26 +187,25 @@ __device__ __forceinline__ int quant_div(float x, float step, int zero, int qmax
     return min(max(u, 0), qmax);
 }
 
-// Constants of the static int8 activation quantizer (Eq. 1 with b = 8) for the division-free
-// paths: `fast` = the exact two-correction quotient is valid for binary16 inputs, `screen` = the
-// one-FMA quotient with its distance-to-tie test is (both are explained where they are used, in
-// the activation quantizer).
+// Constants of a quantizer (Eq. 1) for the division-free paths: `fast` = the exact two-correction quotient is valid,
+// `screen` = the one-FMA quotient with its distance-to-tie test (both are explained in the activation quantizer, whose
+// clamp range [0, 255] contains every other one).
 struct ActParams {
     float step, rstep, lo_f, hi_f, thr;
     int zero, zoff;
     bool fast, screen;
 };
 
-__device__ __forceinline__ ActParams act_params(const float* act_step, const int32_t* act_zero, bool f16)
+__device__ __forceinline__ ActParams quot_params(float step, int zero)
 {
     ActParams p;
-    p.step = *act_step;
-    p.zero = *act_zero;
+    p.step = step;
+    p.zero = zero;
     p.rstep = 1.0f / p.step;
     const uint32_t b = __float_as_uint(p.step);
     const int e = (int)((b >> 23) & 0xff) - 127;
     const uint32_t m = b & 0x7fffffu;
-    p.fast = f16 && (b >> 31) == 0 && e >= -60 && e <= 60 && m < 0x7ffff0u && p.zero > -(1 << 23) && p.zero < (1 << 23);
+    p.fast = (b >> 31) == 0 && e >= -60 && e <= 60 && m < 0x7ffff0u && p.zero > -(1 << 23) && p.zero < (1 << 23);
     // screened quotient: |Z| small enough for delta to stay far below 1/2
     const int az = p.zero < 0 ? -p.zero : p.zero;
     p.screen = p.fast && az <= 4096;
@@ -214,6 +213,15 @@ __device__ __forceinline__ ActParams act_params(const float* act_step, const int
     p.lo_f = (float)(-p.zero);
     p.hi_f = (float)(255 - p.zero);
     p.zoff = p.zero - 128;
+    return p;
+}
+
+// the activation quantizer's: binary16 input only (no quotient or product leaves the exponent range)
+__device__ __forceinline__ ActParams act_params(const float* act_step, const int32_t* act_zero, bool f16)
+{
+    ActParams p = quot_params(*act_step, *act_zero);
+    p.fast = p.fast && f16;
+    p.screen = p.screen && f16;
     return p;
 }
 

@@ -5,6 +5,11 @@
 // 8 consecutive k (16 bytes of binary16, 32 bytes of binary32).  Per-row slices keep the
 // whole row in registers between the min/max reduction and the quantization; per-group
 // slices are 2^m lanes wide and reduce with DPP butterflies only.
+//
+// Eq. 1's quotient without a division: the screened and the exact quotient of the activation quantizer, per slice where
+// their conditions hold (Step's exponent and significand, |Z| <= 4096) and no element of the wavefront is NaN or reaches a
+// quotient of 2^23 (nothing overflows then and BIGQUOT cannot occur; a binary32 element so small that a product underflows
+// has the code Z either way).  With the division (about 45 operations an element) these kernels were bound by the vector unit.
 #include "common.hpp"
 
 namespace aweq {
@@ -76,45 +81,126 @@ __device__ __forceinline__ void minmax8(const float x[8], float& lo, float& hi)
     for (int i = 0; i < 8; ++i) { lo = fminf(lo, x[i]); hi = fmaxf(hi, x[i]); }
 }
 
+// Extremes of the elements seen so far (binary16: in pairs), and whether one of them was NaN or infinite
+template <bool F16> struct Extremes;
+template <>
+struct Extremes<true> {
+    f16x2 lo = {(_Float16)INFINITY, (_Float16)INFINITY}, hi = {(_Float16)-INFINITY, (_Float16)-INFINITY}, bad = {(_Float16)0.0f, (_Float16)0.0f};
+    __device__ __forceinline__ void add(const Unit<true>& u)
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            lo = hmin2(lo, u.raw.h[i]);
+            hi = hmax2(hi, u.raw.h[i]);
+            bad = __builtin_elementwise_fma(u.raw.h[i], f16x2{(_Float16)0.0f, (_Float16)0.0f}, bad);   // 0, or NaN from then on
+        }
+    }
+    __device__ __forceinline__ float min() const { return fminf((float)lo.x, (float)lo.y); }
+    __device__ __forceinline__ float max() const { return fmaxf((float)hi.x, (float)hi.y); }
+    __device__ __forceinline__ bool finite() const { return bad.x == (_Float16)0.0f && bad.y == (_Float16)0.0f; }
+};
+template <>
+struct Extremes<false> {
+    float lo = INFINITY, hi = -INFINITY, bad = 0.0f;
+    __device__ __forceinline__ void add(const Unit<false>& u)
+    {
+        float x[8];
+        u.get(x);
+        minmax8(x, lo, hi);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) bad = __builtin_fmaf(x[i], 0.0f, bad);
+    }
+    __device__ __forceinline__ float min() const { return lo; }
+    __device__ __forceinline__ float max() const { return hi; }
+    __device__ __forceinline__ bool finite() const { return bad == 0.0f; }
+};
+
+// this thread's elements may take the screened quotient (a thread without elements agrees)
+template <bool F16>
+__device__ __forceinline__ bool may_screen(const Extremes<F16>& ex, const ActParams& p)
+{
+    const float lo = ex.min(), hi = ex.max();
+    return p.screen && ex.finite() && (lo > hi || fmaxf(fabsf(lo), fabsf(hi)) * p.rstep < 8388608.0f);
+}
+
+// the codes of one unit as integral floats, for elements that may_screen accepts
+template <int BITS>
+__device__ __forceinline__ void unit_codes(const float x[8], const ActParams& p, float u[8])
+{
+    constexpr float qmax = (float)((1 << BITS) - 1);
+    const float zf = (float)p.zero;
+    float dmax = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const float q = __builtin_fmaf(x[i], p.rstep, zf);
+        u[i] = rintf(q);
+        dmax = fmaxf(dmax, fabsf(q - u[i]));
+    }
+    if (dmax > p.thr) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            float q = x[i] * p.rstep;
+            float r = __builtin_fmaf(-p.step, q, x[i]);
+            q = __builtin_fmaf(r, p.rstep, q);
+            r = __builtin_fmaf(-p.step, q, x[i]);
+            q = __builtin_fmaf(r, p.rstep, q);
+            u[i] = rintf(q) + zf;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) u[i] = __builtin_amdgcn_fmed3f(u[i], 0.0f, qmax);
+}
+
 // Quantise one unit and store its codes in the format of `bits`.  `row_codes` points at the
 // start of the row's code bytes, u is the unit index inside the row (bits == 8: the unit sits
 // at row_codes + unit_off, which lets the caller pick the layout).  Returns sum (u - 128)
 // (meaningful for bits == 8).  For bits == 3 all four lanes of a quad must call this with
-// consecutive units (u % 4 == lane % 4).
+// consecutive units (u % 4 == lane % 4).  screened: may_screen holds.
 template <int BITS>
-__device__ __forceinline__ int quant_store_unit(const float x[8], float step, int zero, uint8_t* row_codes,
+__device__ __forceinline__ int quant_store_unit(const float x[8], const ActParams& p, bool screened, uint8_t* row_codes,
                                                 int64_t u, uint32_t& st, int64_t unit_off = -1)
 {
     constexpr int qmax = (1 << BITS) - 1;
-    int c[8];
+    uint32_t w0 = 0, w1 = 0;   // the unit's codes, packed (8 bits: minus 128)
+    if (screened) {
+        float c[8];
+        unit_codes<BITS>(x, p, c);
+        if constexpr (BITS == 8) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) c[i] = quant_div(x[i], step, zero, qmax, st);
-    if constexpr (BITS == 8) {
-        int rs = 0;
-        uint32_t w0 = 0, w1 = 0;
+            for (int i = 0; i < 4; ++i) {
+                w0 = __builtin_amdgcn_cvt_pk_u8_f32(c[i], i, w0);
+                w1 = __builtin_amdgcn_cvt_pk_u8_f32(c[4 + i], i, w1);
+            }
+            w0 ^= 0x80808080u;
+            w1 ^= 0x80808080u;
+        } else {   // Horner's rule in binary32: 4 codes of 4 bits, 8 of 3 bits are below 2^24
+            constexpr float base = (float)(1 << BITS);
+            float a = c[3], b = c[7];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            w0 |= (uint32_t)((c[i] - 128) & 0xff) << (8 * i);
-            w1 |= (uint32_t)((c[4 + i] - 128) & 0xff) << (8 * i);
-            rs += c[i] + c[4 + i] - 256;
+            for (int i = 2; i >= 0; --i) { a = __builtin_fmaf(a, base, c[i]); b = __builtin_fmaf(b, base, c[4 + i]); }
+            if constexpr (BITS == 4) w0 = (uint32_t)a | ((uint32_t)b << 16);
+            else w0 = (uint32_t)__builtin_fmaf(b, 4096.0f, a);
         }
-        *reinterpret_cast<uint2*>(row_codes + (unit_off >= 0 ? unit_off : u * 8)) = make_uint2(w0, w1);
-        return rs;
-    } else if constexpr (BITS == 4) {
-        uint32_t w = 0;
+    } else {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) w |= (uint32_t)c[i] << (4 * i);
-        *reinterpret_cast<uint32_t*>(row_codes + u * 4) = w;
+        for (int i = 0; i < 8; ++i) {
+            const int c = quant_div(x[i], p.step, p.zero, qmax, st);
+            if constexpr (BITS == 8) (i < 4 ? w0 : w1) |= (uint32_t)((c - 128) & 0xff) << (8 * (i & 3));
+            else w0 |= (uint32_t)c << (BITS * i);
+        }
+    }
+    if constexpr (BITS == 8) {
+        *reinterpret_cast<uint2*>(row_codes + (unit_off >= 0 ? unit_off : u * 8)) = make_uint2(w0, w1);
+        return __builtin_amdgcn_sdot4((int)w1, 0x01010101, __builtin_amdgcn_sdot4((int)w0, 0x01010101, 0, false), false);
+    } else if constexpr (BITS == 4) {
+        *reinterpret_cast<uint32_t*>(row_codes + u * 4) = w0;
         return 0;
     } else {
         // 8 codes = 24 bits; four neighbouring lanes hold 96 bits = three dwords
-        uint32_t v = 0;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) v |= (uint32_t)c[i] << (3 * i);
-        const uint32_t v0 = (uint32_t)dpp_mov<0x00>((int)v);  // quad_perm [0,0,0,0]
-        const uint32_t v1 = (uint32_t)dpp_mov<0x55>((int)v);  // [1,1,1,1]
-        const uint32_t v2 = (uint32_t)dpp_mov<0xAA>((int)v);  // [2,2,2,2]
-        const uint32_t v3 = (uint32_t)dpp_mov<0xFF>((int)v);  // [3,3,3,3]
+        const uint32_t v0 = (uint32_t)dpp_mov<0x00>((int)w0);  // quad_perm [0,0,0,0]
+        const uint32_t v1 = (uint32_t)dpp_mov<0x55>((int)w0);  // [1,1,1,1]
+        const uint32_t v2 = (uint32_t)dpp_mov<0xAA>((int)w0);  // [2,2,2,2]
+        const uint32_t v3 = (uint32_t)dpp_mov<0xFF>((int)w0);  // [3,3,3,3]
         const int q = threadIdx.x & 3;
         const uint32_t d = q == 0 ? (v0 | (v1 << 24)) : (q == 1 ? ((v1 >> 8) | (v2 << 16)) : ((v2 >> 16) | (v3 << 8)));
         if (q < 3) *reinterpret_cast<uint32_t*>(row_codes + (u >> 2) * 12 + q * 4) = d;
@@ -126,28 +212,42 @@ __device__ __forceinline__ int quant_store_unit(const float x[8], float step, in
 // 8-bit codes are the GEMM's weight operand and go out in its K-panel layout.
 // FOLD: the row read is the un-equalised W; it is multiplied by s[k] (one fp32 multiply, rounded to
 // the weight's type: Eq. 3), written to W_hat and quantised from registers, so W is read once.
-template <bool F16, int BITS, bool PER_TENSOR, bool FOLD = false>
+// TPR threads hold a whole row in UPT units per thread, all requested before the first is used.  Bound by memory (fold and
+// quantise, binary16, us, with the division and the units one after the other -> now: 4096 x 4096 26.6 -> 23.0, 4096 x 11008
+// 58.1 -> 47.5, 225 MB; several rows per block, or neighbouring rows on one XCD, gain nothing).
+template <bool F16, int BITS, bool PER_TENSOR, bool FOLD, int TPR, int UPT>
 __global__ __launch_bounds__(kQwBlock) void quant_weight_row(
-    const void* __restrict__ W, int64_t K, int64_t ldw, uint8_t* __restrict__ codes,
+    const void* __restrict__ W, int64_t N, int64_t K, int64_t ldw, uint8_t* __restrict__ codes,
     float* __restrict__ step, int32_t* __restrict__ zero, int32_t* __restrict__ rowsum_w, uint32_t* status,
-    const float* __restrict__ s = nullptr, void* __restrict__ W_hat = nullptr, int64_t ldwh = 0)
+    const float* __restrict__ s, void* __restrict__ W_hat, int64_t ldwh)
 {
+    constexpr int kRows = kQwBlock / TPR;        // rows per block: one, or one per wavefront
     __shared__ float slot_f[kQwBlock / kWave];
     __shared__ int slot_i[kQwBlock / kWave];
-    const int64_t n = blockIdx.x;
-    const int64_t N = gridDim.x;
+    const int tid = threadIdx.x % TPR;
+    const int64_t n = (int64_t)blockIdx.x * kRows + threadIdx.x / TPR;
+    if (kRows > 1 && n >= N) return;             // (no barriers when rows sit in wavefronts)
     const int64_t units = K / 8;
-    const char* row = reinterpret_cast<const char*>(W) + (size_t)n * ldw * (F16 ? 2 : 4);
-    uint8_t* row_codes = BITS == 8 ? codes + (size_t)n * kPanel : codes + (size_t)n * (K * BITS / 8);
+    const char* const row = reinterpret_cast<const char*>(W) + (size_t)n * ldw * (F16 ? 2 : 4);
+    char* const row_hat = reinterpret_cast<char*>(W_hat) + (size_t)n * ldwh * (F16 ? 2 : 4);
+    uint8_t* const row_codes = BITS == 8 ? codes + (size_t)n * kPanel : codes + (size_t)n * (K * BITS / 8);
+    auto reduce = [](auto v, auto op, auto* slot) {
+        if constexpr (TPR == kWave) return wave_allreduce(v, op);
+        else return block_allreduce<kQwBlock / kWave>(v, op, slot);
+    };
     uint32_t st = 0;
 
-    Unit<F16> reg[kQwMaxUnits];
-    float lo = INFINITY, hi = -INFINITY;
+    Unit<F16> reg[UPT];
 #pragma unroll
-    for (int j = 0; j < kQwMaxUnits; ++j) {
-        const int64_t u = threadIdx.x + (int64_t)j * kQwBlock;
+    for (int j = 0; j < UPT; ++j) {
+        const int64_t u = tid + (int64_t)j * TPR;
+        if (u < units) reg[j].load(row, u);
+    }
+    Extremes<F16> ex;
+#pragma unroll
+    for (int j = 0; j < UPT; ++j) {
+        const int64_t u = tid + (int64_t)j * TPR;
         if (u < units) {
-            reg[j].load(row, u);
             if constexpr (FOLD) {
                 float x[8];
                 reg[j].get(x);
@@ -155,13 +255,9 @@ __global__ __launch_bounds__(kQwBlock) void quant_weight_row(
 #pragma unroll
                 for (int i = 0; i < 4; ++i) { x[i] = rounded_f32(x[i] * s0.f[i]); x[4 + i] = rounded_f32(x[4 + i] * s1.f[i]); }
                 reg[j].set(x);
-                reg[j].store(reinterpret_cast<char*>(W_hat) + (size_t)n * ldwh * (F16 ? 2 : 4), u);
+                reg[j].store(row_hat, u);
             }
-            if constexpr (!PER_TENSOR) {
-                float x[8];
-                reg[j].get(x);
-                minmax8(x, lo, hi);
-            }
+            ex.add(reg[j]);
         }
     }
     float sp;
@@ -170,64 +266,84 @@ __global__ __launch_bounds__(kQwBlock) void quant_weight_row(
         sp = step[0];
         z = zero[0];
     } else {
-        lo = block_allreduce<kQwBlock / kWave>(lo, OpMin(), slot_f);
-        hi = block_allreduce<kQwBlock / kWave>(hi, OpMax(), slot_f);
+        const float lo = reduce(ex.min(), OpMin(), slot_f);
+        const float hi = reduce(ex.max(), OpMax(), slot_f);
         qparams(lo, hi, BITS, sp, z, st);
-        if (threadIdx.x == 0) { step[n] = sp; zero[n] = z; }
+        if (tid == 0) { step[n] = sp; zero[n] = z; }
     }
+    const ActParams p = quot_params(sp, z);
+    const bool screened = __all(may_screen(ex, p));
     int rs = 0;
 #pragma unroll
-    for (int j = 0; j < kQwMaxUnits; ++j) {
-        const int64_t u = threadIdx.x + (int64_t)j * kQwBlock;
+    for (int j = 0; j < UPT; ++j) {
+        const int64_t u = tid + (int64_t)j * TPR;
         if (u < units) {
             float x[8];
             reg[j].get(x);
             // unit u of row n in the panel layout: panel u / 8, bytes 8 (u % 8) ..
-            rs += quant_store_unit<BITS>(x, sp, z, row_codes, u, st, BITS == 8 ? (u >> 3) * N * kPanel + (u & 7) * 8 : -1);
+            rs += quant_store_unit<BITS>(x, p, screened, row_codes, u, st, BITS == 8 ? (u >> 3) * N * kPanel + (u & 7) * 8 : -1);
         }
     }
     if constexpr (BITS == 8) {
         // columns past K in the last panel are zero
-        const int64_t u = units + threadIdx.x;
+        const int64_t u = units + tid;
         if (u < panel_count(K) * 8) *reinterpret_cast<uint2*>(row_codes + (u >> 3) * N * kPanel + (u & 7) * 8) = make_uint2(0u, 0u);
     }
     if (BITS == 8 && rowsum_w) {
-        rs = block_allreduce<kQwBlock / kWave>(rs, OpAdd(), slot_i);
-        if (threadIdx.x == 0) rowsum_w[n] = rs;
+        rs = reduce(rs, OpAdd(), slot_i);
+        if (tid == 0) rowsum_w[n] = rs;
     }
     raise_status(status, st);
 }
 
-// ---- one (Step, Z) per group of 8 * 2^LEVELS consecutive k inside a row
+// ---- one (Step, Z) per group of 8 * 2^LEVELS consecutive k inside a row.  Bound by the vector unit: the slice's three
+// divisions and its reductions cost as much as quantising a unit, so a lane takes two units of a group (from 64 values on).
+// A thread takes the same units of kQgRows rows.
+constexpr int kQgRows = 2;
 template <bool F16, int BITS, int LEVELS>
 __global__ __launch_bounds__(kQwBlock) void quant_weight_group(
-    const void* __restrict__ W, int64_t K, int64_t ldw, uint8_t* __restrict__ codes,
+    const void* __restrict__ W, int64_t N, int64_t K, int64_t ldw, uint8_t* __restrict__ codes,
     float* __restrict__ step, int32_t* __restrict__ zero, uint32_t* status)
 {
-    const int64_t n = blockIdx.y;
+    constexpr int kUnits = LEVELS >= 3 ? 2 : 1, kLanes = LEVELS - (kUnits - 1);   // units per lane; 2^kLanes lanes per group
+    const int64_t n0 = (int64_t)blockIdx.y * kQgRows;
     const int64_t units = K / 8;
-    const int64_t u = (int64_t)blockIdx.x * kQwBlock + threadIdx.x;
+    const int64_t id = (int64_t)blockIdx.x * kQwBlock + threadIdx.x, g = id >> kLanes;
+    const int64_t u0 = (g << LEVELS) + (id & ((1 << kLanes) - 1));
     // K % group == 0 and groups are lane-aligned, so a group is entirely in or out of range
-    if (u >= units) return;
-    const char* row = reinterpret_cast<const char*>(W) + (size_t)n * ldw * (F16 ? 2 : 4);
-    uint8_t* row_codes = codes + (size_t)n * (K * BITS / 8);
+    if (u0 >= units) return;
     uint32_t st = 0;
-    Unit<F16> reg;
-    reg.load(row, u);
-    float x[8];
-    reg.get(x);
-    float lo = INFINITY, hi = -INFINITY;
-    minmax8(x, lo, hi);
-    lo = group_allreduce<LEVELS>(lo, OpMin());
-    hi = group_allreduce<LEVELS>(hi, OpMax());
-    float sp;
-    int z;
-    qparams(lo, hi, BITS, sp, z, st);
-    quant_store_unit<BITS>(x, sp, z, row_codes, u, st);
-    if ((u & ((1 << LEVELS) - 1)) == 0) {
-        const int64_t gi = n * (units >> LEVELS) + (u >> LEVELS);
-        step[gi] = sp;
-        zero[gi] = z;
+    Unit<F16> reg[kQgRows][kUnits];
+#pragma unroll
+    for (int i = 0; i < kQgRows; ++i)   // (past the edge: the last row again, not stored)
+#pragma unroll
+        for (int j = 0; j < kUnits; ++j)
+            reg[i][j].load(reinterpret_cast<const char*>(W) + (size_t)min(n0 + i, N - 1) * ldw * (F16 ? 2 : 4), u0 + (j << kLanes));
+#pragma unroll
+    for (int i = 0; i < kQgRows; ++i) {
+        const int64_t n = n0 + i;
+        if (n >= N) break;
+        Extremes<F16> ex;
+#pragma unroll
+        for (int j = 0; j < kUnits; ++j) ex.add(reg[i][j]);
+        const float lo = group_allreduce<kLanes>(ex.min(), OpMin());
+        const float hi = group_allreduce<kLanes>(ex.max(), OpMax());
+        float sp;
+        int z;
+        qparams(lo, hi, BITS, sp, z, st);
+        const ActParams p = quot_params(sp, z);
+        const bool screened = __all(may_screen(ex, p));
+#pragma unroll
+        for (int j = 0; j < kUnits; ++j) {
+            float x[8];
+            reg[i][j].get(x);
+            quant_store_unit<BITS>(x, p, screened, codes + (size_t)n * (K * BITS / 8), u0 + (j << kLanes), st);
+        }
+        if ((id & ((1 << kLanes) - 1)) == 0) {
+            const int64_t gi = n * (units >> LEVELS) + g;
+            step[gi] = sp;
+            zero[gi] = z;
+        }
     }
     raise_status(status, st);
 }
@@ -285,22 +401,27 @@ __global__ void tensor_qparams(const uint32_t* keys, int bits, float* step, int3
     raise_status(status, st);
 }
 
-template <bool F16, int BITS>
-static void launch_row(bool per_tensor, const void* W, int64_t N, int64_t K, int64_t ldw, uint8_t* codes,
-                       float* step, int32_t* zero, int32_t* rowsum_w, uint32_t* status, hipStream_t st)
+// Rows of up to 1024 values sit in a wavefront each (512 x 512 binary32: 4.0 -> 3.4 us), up to 4096 in two units per thread
+// (4096 x 4096 binary16: 24.7 us with the registers of twelve, 23.0 with two)
+template <bool F16, int BITS, bool PER_TENSOR, bool FOLD>
+static void launch_row(const void* W, int64_t N, int64_t K, int64_t ldw, uint8_t* codes, float* step, int32_t* zero, int32_t* rowsum_w,
+                       uint32_t* status, hipStream_t st, const float* s = nullptr, void* W_hat = nullptr, int64_t ldwh = 0)
 {
-    if (per_tensor)
-        quant_weight_row<F16, BITS, true><<<(unsigned)N, kQwBlock, 0, st>>>(W, K, ldw, codes, step, zero, rowsum_w, status);
-    else
-        quant_weight_row<F16, BITS, false><<<(unsigned)N, kQwBlock, 0, st>>>(W, K, ldw, codes, step, zero, rowsum_w, status);
+#define AWEQ_QR(TPR, UPT)                                                                                              \
+    quant_weight_row<F16, BITS, PER_TENSOR, FOLD, TPR, UPT><<<(unsigned)cdiv(N, kQwBlock / TPR), kQwBlock, 0, st>>>(   \
+        W, N, K, ldw, codes, step, zero, rowsum_w, status, s, W_hat, ldwh)
+    if (K <= 1024) AWEQ_QR(64, 2);
+    else if (K <= 4096) AWEQ_QR(256, 2);
+    else AWEQ_QR(256, kQwMaxUnits);
+#undef AWEQ_QR
 }
 
 template <bool F16, int BITS>
 static void launch_group(int levels, const void* W, int64_t N, int64_t K, int64_t ldw, uint8_t* codes,
                          float* step, int32_t* zero, uint32_t* status, hipStream_t st)
 {
-    dim3 grid((unsigned)cdiv(K / 8, kQwBlock), (unsigned)N);
-#define AWEQ_LG(L) case L: quant_weight_group<F16, BITS, L><<<grid, kQwBlock, 0, st>>>(W, K, ldw, codes, step, zero, status); break;
+    dim3 grid((unsigned)cdiv(levels >= 3 ? K / 16 : K / 8, kQwBlock), (unsigned)cdiv(N, kQgRows));
+#define AWEQ_LG(L) case L: quant_weight_group<F16, BITS, L><<<grid, kQwBlock, 0, st>>>(W, N, K, ldw, codes, step, zero, status); break;
     switch (levels) { AWEQ_LG(0) AWEQ_LG(1) AWEQ_LG(2) AWEQ_LG(3) AWEQ_LG(4) AWEQ_LG(5) AWEQ_LG(6) }
 #undef AWEQ_LG
 }
@@ -348,7 +469,8 @@ extern "C" int aweq_quant_weight(const void* W_hat, aweq_dtype dt, int64_t N, in
     }
 #define AWEQ_DISPATCH(F, B)                                                                            \
     if (group > 0) launch_group<F, B>(levels, W_hat, N, K, ldw, cb, step, zero, status, st);           \
-    else launch_row<F, B>(group == -1, W_hat, N, K, ldw, cb, step, zero, rowsum_w, status, st);
+    else if (group == -1) launch_row<F, B, true, false>(W_hat, N, K, ldw, cb, step, zero, rowsum_w, status, st);      \
+    else launch_row<F, B, false, false>(W_hat, N, K, ldw, cb, step, zero, rowsum_w, status, st);
     if (f16) {
         if (bits == 8) { AWEQ_DISPATCH(true, 8) } else if (bits == 4) { AWEQ_DISPATCH(true, 4) } else { AWEQ_DISPATCH(true, 3) }
     } else {
@@ -376,7 +498,7 @@ extern "C" int aweq_fold_quant_weight(const void* W, aweq_dtype dt, int64_t N, i
         return AWEQ_ERR_ALIGN;
     hipStream_t st = as_stream(stream);
     uint8_t* cb = reinterpret_cast<uint8_t*>(codes);
-#define AWEQ_FQ(F, B) quant_weight_row<F, B, false, true><<<(unsigned)N, kQwBlock, 0, st>>>(W, K, ldw, cb, step, zero, rowsum_w, status, s, W_hat, ldwh)
+#define AWEQ_FQ(F, B) launch_row<F, B, false, true>(W, N, K, ldw, cb, step, zero, rowsum_w, status, st, s, W_hat, ldwh)
     if (dt == AWEQ_F16) { if (bits == 8) AWEQ_FQ(true, 8); else if (bits == 4) AWEQ_FQ(true, 4); else AWEQ_FQ(true, 3); }
     else { if (bits == 8) AWEQ_FQ(false, 8); else if (bits == 4) AWEQ_FQ(false, 4); else AWEQ_FQ(false, 3); }
 #undef AWEQ_FQ
