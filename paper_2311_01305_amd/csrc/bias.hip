@@ -7,8 +7,6 @@
 
 namespace aweq {
 
-constexpr int kBiasBlock = 256;
-
 template <bool F16>
 __device__ __forceinline__ void load_w8(const void* row, int64_t u, float x[8])
 {
@@ -34,11 +32,14 @@ __device__ __forceinline__ void load_w8(const void* row, int64_t u, float x[8])
 // colsum_acc[n] = sum_t acc[t,n] comes from the GEMM, or - by the same linearity, as exact integers -
 // from the weight codes: sum_t sum_k xq[t,k] wq[n,k] = sum_k wq[n,k] colsum_xq[k] (wq given, colsum_acc NULL),
 // so that calibration does not have to run the forward.
-// A block takes kBiasRows output channels at once: mu_xhat and colsum_xq (and their sum over k, which every
+// A block of BLOCK threads takes ROWS output channels at once: mu_xhat and colsum_xq (and their sum over k, which every
 // channel needs) are read once per block instead of once per channel.
-constexpr int kBiasRows = 8;
-template <bool F16>
-__global__ __launch_bounds__(kBiasBlock) void bias_w8a8_kernel(
+// The codes meet colsum_xq in 8-bit pieces: a column sum below 2^30 is four signed digits of base 256, and a dot product
+// instruction multiplies four codes with four digits of equal weight (one instruction per code; 64-bit products took
+// about 15 and bound the kernel).  The four int32 sums of a row grow by at most 2^17 per unit: exact for K < 2^24 with blocks
+// of 64 threads.  Larger column sums and longer rows take the 64-bit products.
+template <bool F16, int BLOCK, int ROWS>
+__global__ __launch_bounds__(BLOCK) void bias_w8a8_kernel(
     const void* __restrict__ W_hat, int64_t N, int64_t K, int64_t ldw, const float* __restrict__ mu_xhat, uint64_t count,
     const long long* __restrict__ colsum_acc, const long long* __restrict__ colsum_xq,
     const int32_t* __restrict__ rowsum_w, const float* __restrict__ act_step, const int32_t* __restrict__ act_zero,
@@ -46,123 +47,192 @@ __global__ __launch_bounds__(kBiasBlock) void bias_w8a8_kernel(
     float* __restrict__ delta, float* __restrict__ bias_out, int enable_bc, const int8_t* __restrict__ wq,
     int w_per_tensor)
 {
-    __shared__ double slot_d[kBiasBlock / kWave];
-    __shared__ long long slot_l[kBiasBlock / kWave];
-    const int64_t n0 = (int64_t)blockIdx.x * kBiasRows;
-    const int rows = (int)min((int64_t)kBiasRows, N - n0);
-    double acc[kBiasRows];
-    long long ca[kBiasRows];
+    constexpr int kWaves = BLOCK / kWave;
+    __shared__ double slot_d[kWaves][ROWS];
+    __shared__ long long slot_l[kWaves][ROWS + 1];
+    const int64_t n0 = (int64_t)blockIdx.x * ROWS;
+    const int rows = (int)min((int64_t)ROWS, N - n0);
+    double acc[ROWS];
+    long long ca[ROWS];
+    int cd[ROWS][4];
 #pragma unroll
-    for (int r = 0; r < kBiasRows; ++r) { acc[r] = 0.0; ca[r] = 0; }
+    for (int r = 0; r < ROWS; ++r) {
+        acc[r] = 0.0;
+        ca[r] = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) cd[r][j] = 0;
+    }
     long long tot = 0;
-    for (int64_t u = threadIdx.x; u < K / 8; u += kBiasBlock) {
+    for (int64_t u = threadIdx.x; u < K / 8; u += BLOCK) {
+        float w[ROWS][8];
+        uint2 v[ROWS];
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {   // (past the edge: the last row again, its results are not stored)
+            const int64_t n = n0 + min(r, rows - 1);
+            load_w8<F16>(reinterpret_cast<const char*>(W_hat) + (size_t)n * ldw * (F16 ? 2 : 4), u, w[r]);
+            // unit u of row n in the K-panel layout: panel u / 8, bytes 8 (u % 8) ..
+            if (wq) v[r] = *reinterpret_cast<const uint2*>(wq + ((u >> 3) * N + n) * kPanel + (u & 7) * 8);
+        }
         const Float4 m0 = *reinterpret_cast<const Float4*>(mu_xhat + u * 8);
         const Float4 m1 = *reinterpret_cast<const Float4*>(mu_xhat + u * 8 + 4);
         long long cx[8];
+        bool small = K < (1 << 24);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) { cx[i] = colsum_xq[u * 8 + i]; tot += cx[i]; }
+        for (int i = 0; i < 8; ++i) {
+            cx[i] = colsum_xq[u * 8 + i];
+            tot += cx[i];
+            small = small && cx[i] < (1ll << 30) && cx[i] > -(1ll << 30);
+        }
 #pragma unroll
-        for (int r = 0; r < kBiasRows; ++r) {
-            if (r >= rows) break;
-            const char* row = reinterpret_cast<const char*>(W_hat) + (size_t)(n0 + r) * ldw * (F16 ? 2 : 4);
-            float w[8];
-            load_w8<F16>(row, u, w);
+        for (int r = 0; r < ROWS; ++r)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                acc[r] += (double)w[i] * (double)m0.f[i];
-                acc[r] += (double)w[4 + i] * (double)m1.f[i];
+                acc[r] = __builtin_fma((double)w[r][i], (double)m0.f[i], acc[r]);
+                acc[r] = __builtin_fma((double)w[r][4 + i], (double)m1.f[i], acc[r]);
             }
-            if (wq) {
-                // unit u of row n in the K-panel layout: panel u / 8, bytes 8 (u % 8) ..
-                const uint2 v = *reinterpret_cast<const uint2*>(wq + ((u >> 3) * N + n0 + r) * kPanel + (u & 7) * 8);
+        if (wq && small) {
+            // digit j of cx[0 .. 3] and of cx[4 .. 7], packed: adding 0x808080 carries into the digit above, and flipping the
+            // lower digits' top bits takes it back out
+            uint32_t d[2][4];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                uint32_t b[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) b[i] = ((uint32_t)(int)cx[4 * h + i] + 0x00808080u) ^ 0x00808080u;
+                const uint32_t l01 = __builtin_amdgcn_perm(b[1], b[0], 0x05010400u), l23 = __builtin_amdgcn_perm(b[3], b[2], 0x05010400u);
+                const uint32_t h01 = __builtin_amdgcn_perm(b[1], b[0], 0x07030602u), h23 = __builtin_amdgcn_perm(b[3], b[2], 0x07030602u);
+                d[h][0] = __builtin_amdgcn_perm(l23, l01, 0x05040100u);
+                d[h][1] = __builtin_amdgcn_perm(l23, l01, 0x07060302u);
+                d[h][2] = __builtin_amdgcn_perm(h23, h01, 0x05040100u);
+                d[h][3] = __builtin_amdgcn_perm(h23, h01, 0x07060302u);
+            }
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    cd[r][j] = __builtin_amdgcn_sdot4((int)v[r].x, (int)d[0][j], cd[r][j], false);
+                    cd[r][j] = __builtin_amdgcn_sdot4((int)v[r].y, (int)d[1][j], cd[r][j], false);
+                }
+        } else if (wq) {
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    ca[r] += (long long)(int8_t)((v.x >> (8 * i)) & 0xff) * cx[i];
-                    ca[r] += (long long)(int8_t)((v.y >> (8 * i)) & 0xff) * cx[4 + i];
+                    ca[r] += (long long)(int8_t)((v[r].x >> (8 * i)) & 0xff) * cx[i];
+                    ca[r] += (long long)(int8_t)((v[r].y >> (8 * i)) & 0xff) * cx[4 + i];
                 }
-            }
         }
     }
-    tot = block_allreduce<kBiasBlock / kWave>(tot, OpAdd(), slot_l);
+    const int wave = threadIdx.x / kWave;
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+        const double a = wave_allreduce(acc[r], OpAdd());
+        if (threadIdx.x % kWave == 0) slot_d[wave][r] = a;
+        if (wq) {
+            const long long c = wave_allreduce(ca[r] + cd[r][0] + ((long long)cd[r][1] << 8) + ((long long)cd[r][2] << 16) +
+                                                   ((long long)cd[r][3] << 24), OpAdd());
+            if (threadIdx.x % kWave == 0) slot_l[wave][r] = c;
+        }
+    }
+    tot = wave_allreduce(tot, OpAdd());
+    if (threadIdx.x % kWave == 0) slot_l[wave][ROWS] = tot;
+    __syncthreads();
+    if ((int)threadIdx.x >= rows) return;
+    const int r = threadIdx.x;
+    const int64_t n = n0 + r;
+    double a_r = 0.0;
+    long long c_r = 0;
+    tot = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        a_r += slot_d[w][r];
+        if (wq) c_r += slot_l[w][r];
+        tot += slot_l[w][ROWS];
+    }
     const long long T = (long long)count;
     const long long zx = (long long)*act_zero - 128;
     const double sx = (double)*act_step;
-#pragma unroll
-    for (int r = 0; r < kBiasRows; ++r) {
-        if (r >= rows) break;    // (block-uniform)
-        const double a_r = block_allreduce<kBiasBlock / kWave>(acc[r], OpAdd(), slot_d);
-        long long c_r = 0;
-        if (wq) c_r = block_allreduce<kBiasBlock / kWave>(ca[r], OpAdd(), slot_l);
-        if (threadIdx.x == 0) {
-            const int64_t n = n0 + r;
-            const int64_t pi = w_per_tensor ? 0 : n;   // one (Step, Z) for the tensor, or one per output channel
-            const long long zw = (long long)zero_w[pi] - 128;
-            const long long a = (wq ? c_r : colsum_acc[n]) - T * zx * (long long)rowsum_w[n] - zw * tot + T * K * zx * zw;
-            const double yq = sx * (double)step_w[pi] * (double)a / (double)T;
-            const double d = a_r - yq;
-            delta[n] = (float)d;
-            bias_out[n] = (float)((bias_in ? (double)bias_in[n] : 0.0) + (enable_bc ? d : 0.0));
-        }
-    }
+    const int64_t pi = w_per_tensor ? 0 : n;   // one (Step, Z) for the tensor, or one per output channel
+    const long long zw = (long long)zero_w[pi] - 128;
+    const long long a = (wq ? c_r : colsum_acc[n]) - T * zx * (long long)rowsum_w[n] - zw * tot + T * K * zx * zw;
+    const double yq = sx * (double)step_w[pi] * (double)a / (double)T;
+    const double d = a_r - yq;
+    delta[n] = (float)d;
+    bias_out[n] = (float)((bias_in ? (double)bias_in[n] : 0.0) + (enable_bc ? d : 0.0));
 }
 
 // Weight-only (Eq. 12-15): E[y~ - y] = eps E[x], eps = W~ - W_hat; delta = -eps mu_xhat.
-template <bool F16, int BITS>
-__global__ __launch_bounds__(kBiasBlock) void bias_wonly_kernel(
-    const void* __restrict__ W_hat, int64_t K, int64_t ldw, const float* __restrict__ mu_xhat,
+// As above a block takes ROWS output channels, so that mu_xhat and the group of a unit are found once for all of them.
+template <bool F16, int BITS, int BLOCK, int ROWS>
+__global__ __launch_bounds__(BLOCK) void bias_wonly_kernel(
+    const void* __restrict__ W_hat, int64_t N, int64_t K, int64_t ldw, const float* __restrict__ mu_xhat,
     const uint8_t* __restrict__ codes, int64_t group, const float* __restrict__ step_w,
     const int32_t* __restrict__ zero_w, const float* __restrict__ bias_in, float* __restrict__ delta,
     float* __restrict__ bias_out, int enable_bc)
 {
-    __shared__ double slot_d[kBiasBlock / kWave];
-    const int64_t n = blockIdx.x;
-    const char* row = reinterpret_cast<const char*>(W_hat) + (size_t)n * ldw * (F16 ? 2 : 4);
-    const uint8_t* crow = codes + (size_t)n * (K * BITS / 8);
+    constexpr int kWaves = BLOCK / kWave;
+    __shared__ double slot_d[kWaves][ROWS];
+    const int64_t n0 = (int64_t)blockIdx.x * ROWS;
+    const int rows = (int)min((int64_t)ROWS, N - n0);
     const int64_t g = group > 0 ? group : K;
     const int64_t ng = K / g;
-    double acc = 0.0;
-    for (int64_t u = threadIdx.x; u < K / 8; u += kBiasBlock) {
-        float w[8];
-        load_w8<F16>(row, u, w);
-        int c[8];
-        if constexpr (BITS == 8) {
-            // per-row / per-tensor 8-bit codes are stored in the GEMM's K-panel layout
-            const uint2 v = group > 0 ? *reinterpret_cast<const uint2*>(crow + u * 8)
-                                      : *reinterpret_cast<const uint2*>(codes + ((u >> 3) * (int64_t)gridDim.x + n) * kPanel + (u & 7) * 8);
+    double acc[ROWS];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                c[i] = (int)(int8_t)((v.x >> (8 * i)) & 0xff) + 128;
-                c[4 + i] = (int)(int8_t)((v.y >> (8 * i)) & 0xff) + 128;
-            }
-        } else if constexpr (BITS == 4) {
-            const uint32_t v = *reinterpret_cast<const uint32_t*>(crow + u * 4);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) c[i] = (int)((v >> (4 * i)) & 15u);
-        } else {
-            const uint8_t* p = crow + u * 3;
-            const uint32_t v = (uint32_t)p[0] | ((uint32_t)p[1] << 8) | ((uint32_t)p[2] << 16);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) c[i] = (int)((v >> (3 * i)) & 7u);
-        }
+    for (int r = 0; r < ROWS; ++r) acc[r] = 0.0;
+    for (int64_t u = threadIdx.x; u < K / 8; u += BLOCK) {
         // the 8 values of a unit share one group (group sizes are multiples of 8)
-        const int64_t pi = group < 0 ? 0 : n * ng + (u * 8) / g;
-        const float sp = step_w[pi];
-        const int z = zero_w[pi];
+        const int64_t gi = K < (1ll << 31) ? (int64_t)((uint32_t)(u * 8) / (uint32_t)g) : (u * 8) / g;
+        float w[ROWS][8], sp[ROWS];
+        int z[ROWS];
+        uint2 v[ROWS];   // the unit's codes as stored: 8, 4 or 3 bytes
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {   // (past the edge: the last row again, its result is not stored)
+            const int64_t n = n0 + min(r, rows - 1);
+            load_w8<F16>(reinterpret_cast<const char*>(W_hat) + (size_t)n * ldw * (F16 ? 2 : 4), u, w[r]);
+            const uint8_t* const crow = codes + (size_t)n * (K * BITS / 8);
+            if constexpr (BITS == 8) {
+                // per-row / per-tensor 8-bit codes are stored in the GEMM's K-panel layout
+                v[r] = group > 0 ? *reinterpret_cast<const uint2*>(crow + u * 8)
+                                 : *reinterpret_cast<const uint2*>(codes + ((u >> 3) * N + n) * kPanel + (u & 7) * 8);
+            } else if constexpr (BITS == 4) {
+                v[r].x = *reinterpret_cast<const uint32_t*>(crow + u * 4);
+            } else {
+                // 24 bits of the 12 bytes four units share (K % 32 == 0: they start on 4-byte boundaries)
+                const uint32_t* const q = reinterpret_cast<const uint32_t*>(crow + (u >> 2) * 12);
+                const int d = (int)(u & 3);
+                v[r].x = __builtin_amdgcn_alignbit(q[min(d, 2)], q[max(d - 1, 0)], (32 - 8 * d) & 31);
+            }
+            const int64_t pi = group < 0 ? 0 : n * ng + gi;
+            sp[r] = step_w[pi];
+            z[r] = zero_w[pi];
+        }
         const Float4 m0 = *reinterpret_cast<const Float4*>(mu_xhat + u * 8);
         const Float4 m1 = *reinterpret_cast<const Float4*>(mu_xhat + u * 8 + 4);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const float wt = (float)(c[i] - z) * sp;
-            const double eps = (double)wt - (double)w[i];
-            acc += eps * (double)(i < 4 ? m0.f[i] : m1.f[i - 4]);
-        }
+        for (int r = 0; r < ROWS; ++r)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int c = BITS == 8 ? (int)(int8_t)(((i < 4 ? v[r].x : v[r].y) >> (8 * (i & 3))) & 0xff) + 128
+                                        : (int)((v[r].x >> (BITS * i)) & ((1u << BITS) - 1u));
+                const float wt = (float)(c - z[r]) * sp[r];
+                const double eps = (double)wt - (double)w[r][i];
+                acc[r] = __builtin_fma(eps, (double)(i < 4 ? m0.f[i] : m1.f[i - 4]), acc[r]);
+            }
     }
-    acc = block_allreduce<kBiasBlock / kWave>(acc, OpAdd(), slot_d);
-    if (threadIdx.x == 0) {
-        const double d = -acc;
-        delta[n] = (float)d;
-        bias_out[n] = (float)((bias_in ? (double)bias_in[n] : 0.0) + (enable_bc ? d : 0.0));
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+        const double a = wave_allreduce(acc[r], OpAdd());
+        if (threadIdx.x % kWave == 0) slot_d[threadIdx.x / kWave][r] = a;
     }
+    __syncthreads();
+    if ((int)threadIdx.x >= rows) return;
+    const int64_t n = n0 + threadIdx.x;
+    double a = 0.0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) a += slot_d[w][threadIdx.x];
+    const double d = -a;
+    delta[n] = (float)d;
+    bias_out[n] = (float)((bias_in ? (double)bias_in[n] : 0.0) + (enable_bc ? d : 0.0));
 }
 
 }  // namespace aweq
@@ -197,12 +267,15 @@ extern "C" int aweq_bias_correct(int mode, const void* W_hat, aweq_dtype dt, int
         if (wq && !aligned16(wq)) return AWEQ_ERR_ALIGN;
         const long long* ca = reinterpret_cast<const long long*>(colsum_acc);
         const long long* cx = reinterpret_cast<const long long*>(colsum_xq);
-        if (f16)
-            bias_w8a8_kernel<true><<<(unsigned)cdiv(N, kBiasRows), kBiasBlock, 0, st>>>(W_hat, N, K, ldw, mu_xhat, count, ca, cx, rowsum_w, act_step,
-                                                                     act_zero, step_w, zero_w, bias_in, delta, bias_out, enable_bc, wq, pt);
-        else
-            bias_w8a8_kernel<false><<<(unsigned)cdiv(N, kBiasRows), kBiasBlock, 0, st>>>(W_hat, N, K, ldw, mu_xhat, count, ca, cx, rowsum_w, act_step,
-                                                                      act_zero, step_w, zero_w, bias_in, delta, bias_out, enable_bc, wq, pt);
+#define AWEQ_B8(F, BLOCK, ROWS)                                                                                        \
+    bias_w8a8_kernel<F, BLOCK, ROWS><<<(unsigned)cdiv(N, ROWS), BLOCK, 0, st>>>(                                       \
+        W_hat, N, K, ldw, mu_xhat, count, ca, cx, rowsum_w, act_step, act_zero, step_w, zero_w, bias_in, delta, bias_out, enable_bc, wq, pt)
+        // small blocks: more of them in flight while others reduce.  us, from the codes 4096 x 11008 / with the GEMM's sums
+        // 4096 x 4096, binary16: 128 threads x 4 channels 24.2 / 11.0, 256 x 8 27.6 / 10.9, 256 x 4 26.6 / 11.9, 512 x 8 32.6 / 15.6,
+        // 64 x 4 33.4 / 13.0 (256 x 8 with 64-bit products and a barrier pair per channel: 40.8 / 13.6); 512 x 512 binary32 7.1 -> 3.6
+        if (f16) { if (K <= 1024) AWEQ_B8(true, 64, 2); else AWEQ_B8(true, 128, 4); }
+        else { if (K <= 1024) AWEQ_B8(false, 64, 2); else AWEQ_B8(false, 128, 4); }
+#undef AWEQ_B8
     } else if (mode == AWEQ_BIAS_WEIGHT_ONLY) {
         if (!codes) return AWEQ_ERR_NULL;
         if (bits != 8 && bits != 4 && bits != 3) return AWEQ_ERR_BITS;
@@ -210,10 +283,14 @@ extern "C" int aweq_bias_correct(int mode, const void* W_hat, aweq_dtype dt, int
         if (!aligned16(codes)) return AWEQ_ERR_ALIGN;
         if (bits == 3 && (K % 32) != 0) return AWEQ_ERR_ALIGN;
         const uint8_t* cb = reinterpret_cast<const uint8_t*>(codes);
-#define AWEQ_BW(F, B) bias_wonly_kernel<F, B><<<(unsigned)N, kBiasBlock, 0, st>>>(W_hat, K, ldw, mu_xhat, cb, group, step_w, zero_w, bias_in, delta, bias_out, enable_bc)
+#define AWEQ_BWS(F, B, BLOCK, ROWS)                                                                                    \
+    bias_wonly_kernel<F, B, BLOCK, ROWS><<<(unsigned)cdiv(N, ROWS), BLOCK, 0, st>>>(                                    \
+        W_hat, N, K, ldw, mu_xhat, cb, group, step_w, zero_w, bias_in, delta, bias_out, enable_bc)
+#define AWEQ_BW(F, B) do { if (K <= 1024) AWEQ_BWS(F, B, 64, 2); else AWEQ_BWS(F, B, 256, 4); } while (0)
         if (f16) { if (bits == 8) AWEQ_BW(true, 8); else if (bits == 4) AWEQ_BW(true, 4); else AWEQ_BW(true, 3); }
         else { if (bits == 8) AWEQ_BW(false, 8); else if (bits == 4) AWEQ_BW(false, 4); else AWEQ_BW(false, 3); }
 #undef AWEQ_BW
+#undef AWEQ_BWS
     } else {
         return AWEQ_ERR_SHAPE;
     }
