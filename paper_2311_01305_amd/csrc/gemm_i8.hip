@@ -909,8 +909,11 @@ extern "C" int aweq_w8a8_gemm(const void* X, aweq_dtype x_dt, int64_t T, int64_t
 
     if (colsum_acc) zero_fill_u32_gemm<<<(unsigned)cdiv(2 * N, 256), 256, 0, st>>>(reinterpret_cast<uint32_t*>(colsum_acc), 2 * N);
 
+    // the form whose rounds of workgroups are modelled to take least
     const FewPlan few = plan_few(T, N);
-    if (fast_ok && few.cost < kTiledRoundCost * tiled_cost) return launch_gemm_i8_few(g, few, st);
+    const MidPlan mid = plan_mid(T, N);
+    if (fast_ok && few.cost <= mid.cost && few.cost < kTiledRoundCost * tiled_cost) return launch_gemm_i8_few(g, few, st);
+    if (fast_ok && mid.cost < kTiledRoundCost * tiled_cost) return launch_gemm_i8_mid(g, mid, st);
     if (fast_ok) {
         const int deq = out_deq ? (out_dt == AWEQ_F16 ? 2 : 1) : 0;
         const void* fn = nullptr;

@@ -1,4 +1,5 @@
-// Arguments of the int8 GEMM kernels, and the few-token form (gemm_i8_few.hip) that aweq_w8a8_gemm chooses.
+// Arguments of the int8 GEMM kernels, and the forms for fewer tokens (gemm_i8_few.hip, gemm_i8_mid.hip) that
+// aweq_w8a8_gemm chooses from.
 #pragma once
 #include "tile_walk.hpp"
 
@@ -42,8 +43,16 @@ struct FewPlan {
 FewPlan plan_few(int64_t T, int64_t N);
 int launch_gemm_i8_few(const GemmArgs& g, const FewPlan& p, hipStream_t st);
 
-// Time of one round of workgroups at K = 8192 (us; every kernel's time is proportional to K): 256 tiles of 256 x 256
-constexpr double kTiledRoundCost = 68.0;
-constexpr double kHalfTileCost = 0.57;   // the same of 128 x 256 tiles, against that
+// The same of the kernel for some hundred tokens (gemm_i8_mid.hip)
+struct MidPlan {
+    bool square;   // 128 x 128 tiles instead of 64 x 128
+    double cost;
+};
+MidPlan plan_mid(int64_t T, int64_t N);
+int launch_gemm_i8_mid(const GemmArgs& g, const MidPlan& p, hipStream_t st);
+
+// Time of one round of workgroups at K = 8192 (us; every kernel's time is close to proportional to K): 256 tiles of 256 x 256
+constexpr double kTiledRoundCost = 100.0;
+constexpr double kHalfTileCost = 0.57;   // the same of 128 x 256 tiles, against that (0.55 - 0.58 from K = 256 to 16384)
 
 }  // namespace aweq

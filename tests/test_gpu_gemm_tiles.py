@@ -1,4 +1,4 @@
-"""The tiled int8 GEMM where its plan changes: tiles of 128 and of 256 tokens, one round of workgroups and several, the
+"""The tiled int8 GEMM where its plan changes: tiles of 64, 128 and 256 tokens, one round of workgroups and several, the
 sequence walk and the patches, and numbers of K-panels around the depth of the load ring.  The int32 accumulator and its
 column sums are exact against the oracle; the binary16 / binary32 output is the fp64 value of the exact integer, rounded
 once (binary32) or within one unit in the last place (binary16: one fused fp64 operation)."""
@@ -27,11 +27,15 @@ def dev(a):
 
 
 @pytest.mark.parametrize("T,N,Ks", [
-    (513, 2304, (8, 64, 192, 256, 264, 320, 504, 512, 584)),   # 128 tokens a tile, one round; 1 .. 10 panels
-    (640, 2060, (200, 1000)),                                  # whole tiles of tokens, a ragged last column
+    (1153, 4352, (8, 64, 192, 256, 264, 320, 504, 512, 584)),  # 128 tokens a tile, one round; 1 .. 10 panels
+    (1280, 4108, (200, 1000)),                                 # whole tiles of tokens, a ragged last column
     (2300, 4100, (40, 192, 256, 328, 456)),                    # 256 tokens a tile, one round
     (2100, 11008, (136, 584)),                                 # 128 tokens a tile, three rounds
-    (4700, 4100, (136, 520)),                                  # 256 tokens a tile, two rounds
+    (6100, 4100, (136, 520)),                                  # 256 tokens a tile, two rounds
+    (385, 4100, (8, 64, 200, 320, 512, 776, 1096)),            # 64 x 128 tiles; 1 .. 5 stages of four panels, three in the ring
+    (512, 4096, (256,)),                                       # whole 64 x 128 tiles
+    (900, 4060, (8, 128, 200, 320, 456, 584)),                 # 128 x 128 tiles; 1 .. 5 stages of two panels, four in the ring
+    (65, 22020, (136, 328)),                                   # few tokens, 64 x 128 tiles
 ])
 def test_tiled_gemm(B, orc, T, N, Ks):
     rng = np.random.default_rng(T + N)
