@@ -216,15 +216,6 @@ __device__ __forceinline__ ActParams quot_params(float step, int zero)
     return p;
 }
 
-// the activation quantizer's: binary16 input only (no quotient or product leaves the exponent range)
-__device__ __forceinline__ ActParams act_params(const float* act_step, const int32_t* act_zero, bool f16)
-{
-    ActParams p = quot_params(*act_step, *act_zero);
-    p.fast = p.fast && f16;
-    p.screen = p.screen && f16;
-    return p;
-}
-
 __device__ __forceinline__ void raise_status(uint32_t* status, uint32_t st)
 {
     if (status && st) atomicOr(status, st);

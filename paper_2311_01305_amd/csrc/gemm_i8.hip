@@ -555,7 +555,7 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
         bool nscreen = false;
         if constexpr ((EPI & 2) != 0) {
             if (n_ok) nis = *reinterpret_cast<const Float4*>(g.next_inv_s + n);
-            const ActParams np_ = act_params(g.next_step, g.next_zero, true);
+            const ActParams np_ = quot_params(*g.next_step, *g.next_zero);
             nstep = np_.step; nzero = np_.zero; nrstep = np_.rstep; nthr = np_.thr;
             // the one-FMA quotient with its distance-to-tie test (see the activation quantizer): valid
             // for this lane if no binary16 value times its 1 / s can reach a quotient of 2^24

@@ -11,7 +11,7 @@
 // 2^-25 / beta ulp away from a rounding boundary (beta = significand(Step) / 2^24 < 1),
 // while the second correction's error is below (1/2 + 2^-22) beta 2^-24 ulp, which is
 // smaller whenever beta <= 1 - 2^-20.  Steps with a significand above that, exponents
-// outside [-60, 60], zero points beyond 2^23 and binary32 inputs take the true division.
+// outside [-60, 60] and zero points beyond 2^23 take the true division.
 //
 // That sequence is still 6 of the 13 operations an element costs, and it only matters next to a
 // rounding tie.  So the common case is screened: q' = RN(a y + Z) in one FMA, n' = rint(q').
@@ -20,7 +20,9 @@
 // so if q' is farther than delta = (258 + |Z|) 2^-23 + 2^-15 from every half-integer, v lies in
 // the same unit interval and rint(RN(Q)) + Z = n' (outside [-1, 256] the relative error 2^-22
 // keeps both on the same side of the clamp).  Units of 8 values with an element inside delta
-// (about 1.5e-4 of all elements for |Z| <= 255) are redone with the exact sequence.
+// (about 1.5e-4 of all elements for |Z| <= 255) are redone with the exact sequence.  Binary32 input takes the screened
+// quotient too, where |Z| allows it, and divides the units with a quotient beyond 2^22 (7419 x 4096 tokens x channels:
+// 47.4 us with the division everywhere, 40.1 now; a quotient that underflows on the way rounds to 0 either way).
 #include "common.hpp"
 #include <type_traits>
 
@@ -40,16 +42,18 @@ constexpr unsigned kQaXcds = 8;                         // workgroup id % 8 name
 // with v_cvt_pk_u8_f32 and turned into the stored signed code by flipping the top bit
 // (u - 128 = u ^ 0x80 as a byte).  Column sums accumulate u in fp32 (exact: at most 512 rows
 // of values <= 255 per block); the caller subtracts 128 per row afterwards.
-// MODE 0: true division; 1: the exact division-free quotient; 2: screened (see the header).
-template <int MODE>
+// MODE 0: true division; 1: the exact division-free quotient; 2: screened (see the header); 3: screened for binary32
+// input, whose quotients have no bound known beforehand: a unit with one beyond 2^22, infinite or NaN is divided.
+// SUMS: only the column sums are wanted (no code buffer, no row sums).
+template <int MODE, bool SUMS = false>
 __device__ __forceinline__ void act_unit(const float x[8], const float is[8], const ActParams& p, int8_t* dst,
                                          float csf[8], int csi[8], int& rs, float& big, uint32_t& st)
 {
     uint32_t w[2] = {0u, 0u};
-    if constexpr (MODE == 2) {
+    if constexpr (MODE == 2 || MODE == 3) {
         const float zf = (float)p.zero;
         float n[8];
-        float dmax = 0.0f;
+        float dmax = 0.0f, largest = 0.0f, bad = 0.0f;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             // x is a widened binary16 value: a = RN(x inv_s) as one mixed-precision FMA (+0 changes
@@ -57,9 +61,17 @@ __device__ __forceinline__ void act_unit(const float x[8], const float is[8], co
             const float a = __builtin_fmaf(x[i], is[i], 0.0f);
             const float q = __builtin_fmaf(a, p.rstep, zf);
             n[i] = rintf(q);
-            dmax = fmaxf(dmax, fabsf(q - n[i]));
+            const float d = fabsf(q - n[i]);
+            dmax = fmaxf(dmax, d);
+            if constexpr (MODE == 3) {
+                largest = fmaxf(largest, fabsf(q));
+                bad += d;   // NaN from an infinite or NaN quotient on
+            }
         }
-        if (dmax > p.thr) {
+        if (MODE == 3 && !(largest < 4194304.0f && bad < 8.0f)) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) n[i] = (float)quant_div(x[i] * is[i], p.step, p.zero, 255, st);
+        } else if (dmax > p.thr) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 const float a = x[i] * is[i];
@@ -75,7 +87,7 @@ __device__ __forceinline__ void act_unit(const float x[8], const float is[8], co
         for (int i = 0; i < 8; ++i) {
             const float u = __builtin_amdgcn_fmed3f(n[i], 0.0f, 255.0f);
             csf[i] += u;
-            w[i >> 2] = __builtin_amdgcn_cvt_pk_u8_f32(u, i & 3, w[i >> 2]);
+            if constexpr (!SUMS) w[i >> 2] = __builtin_amdgcn_cvt_pk_u8_f32(u, i & 3, w[i >> 2]);
         }
         w[0] ^= 0x80808080u;
         w[1] ^= 0x80808080u;
@@ -107,6 +119,7 @@ __device__ __forceinline__ void act_unit(const float x[8], const float is[8], co
             w[i >> 2] |= (uint32_t)(c & 0xff) << (8 * (i & 3));
         }
     }
+    if constexpr (SUMS) return;
     rs = __builtin_amdgcn_sdot4((int)w[0], 0x01010101, rs, false);
     rs = __builtin_amdgcn_sdot4((int)w[1], 0x01010101, rs, false);
     typedef unsigned v2u_ __attribute__((ext_vector_type(2)));
@@ -159,7 +172,9 @@ template <> struct RawUnit<false> {
 // per instruction: lane = 8 (row % 8) + unit; its load covers 8 whole 128-byte lines of
 // binary16 input and its store 512 contiguous bytes of codes.  Each wavefront owns two
 // panels, so a lane keeps the column sums of its 16 columns over the rows it visits.
-template <bool F16>
+// SUMS: neither codes nor row sums are asked for (a calibration without the forward): 14331 x 11008 binary16 72.3 -> 66.3 us
+// without packing the codes, 7419 x 4096 binary32 29.5.
+template <bool F16, bool SUMS>
 __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
     const void* __restrict__ X, int64_t T, int64_t K, int64_t ldx, const float* __restrict__ inv_s,
     const float* __restrict__ act_step, const int32_t* __restrict__ act_zero, int8_t* __restrict__ xq,
@@ -177,7 +192,7 @@ __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
     const int64_t r0 = slice * rows_per_block;
     const int nrows = (int)min((int64_t)rows_per_block, T - r0);
     const int64_t np = panel_count(K);
-    const ActParams p = act_params(act_step, act_zero, F16);
+    const ActParams p = quot_params(*act_step, *act_zero);
 
     const int64_t panel0 = (int64_t)chunk * kQaPanels + wave * kQaVpt;
     const int col0 = (int)(panel0 * kPanel) + c8 * 8;                      // K <= 2^31 - 1 columns
@@ -204,8 +219,8 @@ __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
     // for every binary16 x up front (65504 max|inv_s| / Step with a margin for the roundings)
     const bool screen_thread = fast_thread && p.screen && 65600.0f * is_max * p.rstep < 16777216.0f;
     // one path for the whole block (the choice is uniform unless an inv_s is absurd)
-    const bool fast = __syncthreads_and(fast_thread ? 1 : 0) != 0;
-    const bool screen = __syncthreads_and(screen_thread ? 1 : 0) != 0;
+    const bool fast = F16 ? __syncthreads_and(fast_thread ? 1 : 0) != 0 : p.screen;
+    const bool screen = F16 ? __syncthreads_and(screen_thread ? 1 : 0) != 0 : p.screen;
     uint32_t st = 0;
     float big = 0.0f;
     float csf[kQaVpt][8];
@@ -240,14 +255,16 @@ __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
                         if (valid[j]) {
                             float x[8];
                             raw[b][j].get(x);
-                            act_unit<MODE>(x, is[j], p, d, csf[j], csi[j], rs, big, st);
+                            act_unit<MODE, SUMS>(x, is[j], p, d, csf[j], csi[j], rs, big, st);
                         } else if (pad[j] && d) {
                             *reinterpret_cast<uint2*>(d) = make_uint2(0u, 0u);
                         }
                     }
                 }
-                rs = group_allreduce<3>(rs, OpAdd());  // the 8 lanes of one row
-                if (row_ok && c8 == 0) lds_rs[row][wave] = rs;
+                if constexpr (!SUMS) {
+                    rs = group_allreduce<3>(rs, OpAdd());  // the 8 lanes of one row
+                    if (row_ok && c8 == 0) lds_rs[row][wave] = rs;
+                }
             }
         }
     };
@@ -256,7 +273,8 @@ __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
         else if (fast) rows_loop(std::integral_constant<int, 1>{});
         else rows_loop(std::integral_constant<int, 0>{});
     } else {
-        rows_loop(std::integral_constant<int, 0>{});   // binary32 input: the true division
+        if (screen) rows_loop(std::integral_constant<int, 3>{});
+        else rows_loop(std::integral_constant<int, 0>{});
     }
     if (big >= 16777216.0f) st |= AWEQ_ST_BIGQUOT;
     raise_status(status, st);
@@ -283,6 +301,7 @@ __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
             }
         }
     }
+    if constexpr (SUMS) return;
     __syncthreads();
     // with several column chunks `rowsum_x` is the partial buffer [chunks][T], folded by the merge kernel
     if (rowsum_x)
@@ -337,7 +356,7 @@ __global__ __launch_bounds__(kQrBlock) void quant_act_rows(
     __shared__ int s_rs[kQrBlock / kWave][ROWS];
     const int64_t r0 = (int64_t)blockIdx.x * ROWS;
     const int nrows = (int)min((int64_t)ROWS, T - r0);
-    const ActParams p = act_params(act_step, act_zero, F16);
+    const ActParams p = quot_params(*act_step, *act_zero);
     const int64_t units = K / 8, padded = panel_count(K) * (kPanel / 8);
     uint32_t st = 0;
     float big = 0.0f;
@@ -376,7 +395,8 @@ __global__ __launch_bounds__(kQrBlock) void quant_act_rows(
             if (i >= nrows) break;
             float x[8];
             raw[i].get(x);
-            if (F16 && screen) act_unit<2>(x, is, p, d + i * kPanel, csf, csi, rs[i], big, st);
+            if (!F16 && p.screen) act_unit<3>(x, is, p, d + i * kPanel, csf, csi, rs[i], big, st);
+            else if (F16 && screen) act_unit<2>(x, is, p, d + i * kPanel, csf, csi, rs[i], big, st);
             else if (F16 && exact) act_unit<1>(x, is, p, d + i * kPanel, csf, csi, rs[i], big, st);
             else act_unit<0>(x, is, p, d + i * kPanel, csf, csi, rs[i], big, st);
         }
@@ -448,12 +468,11 @@ int launch_quant_act(const void* X, aweq_dtype dt, int64_t T, int64_t K, int64_t
     int32_t* const rs_out = !rowsum_x ? nullptr : (multi ? rowsum_part : rowsum_x);
     const unsigned pairs = (unsigned)(p.slices * p.chunks);
     const unsigned grid = (unsigned)(cdiv(pairs, kQaXcds) * kQaXcds);
-    if (dt == AWEQ_F16)
-        quant_act_kernel<true><<<grid, kQaBlock, 0, st>>>(X, T, K, ldx, inv_s, act_step, act_zero, xq, rs_out, colsum_part,
-                                                          (int)p.rpb, p.chunks, pairs, status);
-    else
-        quant_act_kernel<false><<<grid, kQaBlock, 0, st>>>(X, T, K, ldx, inv_s, act_step, act_zero, xq, rs_out, colsum_part,
-                                                           (int)p.rpb, p.chunks, pairs, status);
+    const bool sums = !xq && !rowsum_x;
+#define AWEQ_QA(F, S) quant_act_kernel<F, S><<<grid, kQaBlock, 0, st>>>(X, T, K, ldx, inv_s, act_step, act_zero, xq, rs_out, colsum_part, (int)p.rpb, p.chunks, pairs, status)
+    if (dt == AWEQ_F16) { if (sums) AWEQ_QA(true, true); else AWEQ_QA(true, false); }
+    else { if (sums) AWEQ_QA(false, true); else AWEQ_QA(false, false); }
+#undef AWEQ_QA
     const int col_blocks = colsum_xq ? (int)cdiv(K, kQaMergeCols) : 0;
     const int64_t row_blocks = (rowsum_x && multi) ? cdiv(T, kQaMergeCols * kQaMergeParts) : 0;
     if (col_blocks + row_blocks > 0)
