@@ -60,25 +60,54 @@ __device__ __forceinline__ uint32_t fields3(const RawCodes<3>& rc, int d)
          : d == 2 ? __builtin_amdgcn_alignbit(rc.w[2], rc.w[1], 16) : rc.w[2] >> 8;
 }
 
+// (w & mask) | magic in one operation: the compiler spends two on literals, so they sit in registers it cannot see into
+__device__ __forceinline__ uint32_t field(uint32_t w, uint32_t mask, uint32_t magic)
+{
+    asm("" : "+v"(mask));
+    asm("" : "+s"(magic));
+    return (w & mask) | magic;
+}
+
 // Eight codes (32 bits of INT4 / the low 24 bits of INT3) as four binary16 pairs (k, k + 4): (0,4) (1,5) (2,6) (3,7),
 // the order the fields come out of the packed formats in (a caller that needs natural order permutes).
-// 13 (INT4) / 16 (INT3) packed operations per 8 codes.
+// 13 (INT4) / 16 (INT3) operations per 8 codes.
 template <int BITS>
 __device__ __forceinline__ void dequant_word(uint32_t w, const Scale<BITS>& s, uint32_t o[4])
 {
     if constexpr (BITS == 4) {
         const uint32_t v = w >> 8;
-        o[0] = as_u32((as_h2((w & 0x000f000fu) | 0x64006400u) - s.z0) * s.step);
-        o[1] = as_u32((as_h2((w & 0x00f000f0u) | 0x54005400u) - s.z1) * s.step);
-        o[2] = as_u32((as_h2((v & 0x000f000fu) | 0x64006400u) - s.z0) * s.step);
-        o[3] = as_u32((as_h2((v & 0x00f000f0u) | 0x54005400u) - s.z1) * s.step);
+        o[0] = as_u32((as_h2(field(w, 0x000f000fu, 0x64006400u)) - s.z0) * s.step);
+        o[1] = as_u32((as_h2(field(w, 0x00f000f0u, 0x54005400u)) - s.z1) * s.step);
+        o[2] = as_u32((as_h2(field(v, 0x000f000fu, 0x64006400u)) - s.z0) * s.step);
+        o[3] = as_u32((as_h2(field(v, 0x00f000f0u, 0x54005400u)) - s.z1) * s.step);
     } else {
         // codes 4 .. 7 (bits 12 .. 23) move up by 4, so that both halves hold four fields at bits 0, 3, 6, 9
         const uint32_t g = (w & 0x0fffu) | ((w << 4) & 0x0fff0000u), h = g >> 9;
-        o[0] = as_u32((as_h2((g & 0x00070007u) | 0x64006400u) - s.z0) * s.step);
-        o[1] = as_u32((as_h2((g & 0x00380038u) | 0x58005800u) - s.z1) * s.step);
-        o[2] = as_u32((as_h2((g & 0x01c001c0u) | 0x4c004c00u) - s.z2) * s.step);
-        o[3] = as_u32((as_h2((h & 0x00070007u) | 0x64006400u) - s.z0) * s.step);
+        o[0] = as_u32((as_h2(field(g, 0x00070007u, 0x64006400u)) - s.z0) * s.step);
+        o[1] = as_u32((as_h2(field(g, 0x00380038u, 0x58005800u)) - s.z1) * s.step);
+        o[2] = as_u32((as_h2(field(g, 0x01c001c0u, 0x4c004c00u)) - s.z2) * s.step);
+        o[3] = as_u32((as_h2(field(h, 0x00070007u, 0x64006400u)) - s.z0) * s.step);
+    }
+}
+// The same in natural order, (k, k + 1) (k + 2, k + 3) ...: INT4 brings each byte to both halves of a register, whose two
+// fields then sit at bits 0 and 4 (16 operations per 8 codes)
+__device__ __forceinline__ v4i natural_order(const uint32_t o[4]);
+template <int BITS>
+__device__ __forceinline__ v4i dequant_word_natural(uint32_t w, const Scale<BITS>& s)
+{
+    if constexpr (BITS == 4) {
+        const f16x2 z01 = {s.z0.x, s.z1.x};
+        v4i o;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t b = __builtin_amdgcn_perm(w, w, 0x00010001u * (uint32_t)i);
+            o[i] = (int)as_u32((as_h2(field(b, 0x00f0000fu, 0x54006400u)) - z01) * s.step);
+        }
+        return o;
+    } else {
+        uint32_t o[4];
+        dequant_word<3>(w, s, o);
+        return natural_order(o);
     }
 }
 template <int BITS>

@@ -52,7 +52,8 @@ struct Tile {
     static constexpr int kLds = 160 * 1024;
 };
 
-constexpr double kHalfTileCost = 0.57;   // time of a round of 128-token tiles, against one of 256-token tiles
+// Costs, us at K = 8192: a round of 256-token tiles; one of 128-token tiles against that; the de-quantising pass per channel
+constexpr double kTiledRoundCost = 160.0, kHalfTileCost = 0.57, kDequantCost = 0.00445;
 
 struct Args : TileWalk {
     const _Float16* X;     // x_hat [T x K], row-major
@@ -445,16 +446,31 @@ extern "C" int aweq_wonly_gemm(const void* X_hat, int64_t T, int64_t K, int64_t 
 
     const uint32_t scale_pitch = group < 0 ? 0u : group == 0 ? 1u : (uint32_t)(K / group);
     const uint32_t group_magic = group <= 0 ? 0u : (uint32_t)cdiv(1ll << 31, group / 32);
-    // few tokens: straight from the codes (both forms measured in gemm_wonly_small.hip; at 512 tokens the
-    // de-quantising pass and the tiled GEMM are ahead)
-    if (T <= wonly::kSmallTokens) {
-        wonly::SmallArgs a;
-        a.X = reinterpret_cast<const _Float16*>(X_hat); a.codes = reinterpret_cast<const uint8_t*>(codes);
-        a.step = step_w; a.zero = zero_w; a.bias = bias; a.out = out; a.ldx = ldx; a.ldo = ldo; a.T = T; a.N = N; a.K = K;
-        a.scale_pitch = scale_pitch;
-        a.group_magic = group_magic;
-        return wonly::launch_small(a, bits, group, out_dt == AWEQ_F16, st);
-    }
+    const bool f16 = out_dt == AWEQ_F16;
+    // tiles of 256 tokens, or of 128 where their rounds of workgroups take less: a round lasts as long however few of the 256
+    // compute units have a tile (GEMM alone, us, 256 -> 128 tokens a tile: 1531 tokens 4096 x 4096 78 -> 51, 4096 x 11008 226 -> 126,
+    // 768 tokens 8192 x 8192 164 -> 90)
+    wonly::Args g, h;
+    int64_t blocks = 0;
+    int rc = plan_walk(g, T, N, K, 256, blocks);
+    if (rc != AWEQ_OK) return rc;
+    const bool half = plan_walk(h, T, N, K, 128, blocks) == AWEQ_OK && wonly::kHalfTileCost * (double)rounds_of(h) < (double)rounds_of(g);
+    const double tiled_cost = (half ? wonly::kHalfTileCost * (double)rounds_of(h) : (double)rounds_of(g)) * wonly::kTiledRoundCost + wonly::kDequantCost * (double)N;
+    if (half) g = h;
+
+    // Straight from the codes where one of the two kernels that do so is modelled to take less (both sides measured in
+    // gemm_wonly_small.hip and gemm_wonly_mid.hip)
+    wonly::SmallArgs a;
+    a.X = reinterpret_cast<const _Float16*>(X_hat); a.codes = reinterpret_cast<const uint8_t*>(codes);
+    a.step = step_w; a.zero = zero_w; a.bias = bias; a.out = out; a.ldx = ldx; a.ldo = ldo; a.T = T; a.N = N; a.K = K;
+    a.scale_pitch = scale_pitch;
+    a.group_magic = group_magic;
+    const wonly::SmallPlan small = wonly::plan_small(T, N);
+    const wonly::MidPlan mid = wonly::plan_mid(T, N);
+    const bool mid_ok = (group <= 0 || group % 128 == 0) && ldx < (1 << 24);
+    if (small.cost <= tiled_cost && (!mid_ok || small.cost <= mid.cost)) return wonly::launch_small(a, bits, group, small, f16, st);
+    if (mid_ok && mid.cost <= tiled_cost) return wonly::launch_mid(a, bits, mid, f16, st);
+
     // the binary16 weight, once
     _Float16* W = reinterpret_cast<_Float16*>(ws);
     const uint32_t chunks = (uint32_t)cdiv(K, 8 * kWave);
@@ -464,20 +480,9 @@ extern "C" int aweq_wonly_gemm(const void* X_hat, int64_t T, int64_t K, int64_t 
     if (bits == 4) wonly::dequant_weight_h_kernel<4><<<(unsigned)dq_blocks, 256, 0, st>>>(cb, N, K, chunks, scale_pitch, group_magic, step_w, zero_w, W);
     else wonly::dequant_weight_h_kernel<3><<<(unsigned)dq_blocks, 256, 0, st>>>(cb, N, K, chunks, scale_pitch, group_magic, step_w, zero_w, W);
 
-    wonly::Args g;
     g.X = reinterpret_cast<const _Float16*>(X_hat); g.ldx = ldx;
     g.W = W; g.bias = bias;
     g.out = out; g.ldo = ldo; g.T = T; g.N = N; g.K = K;
-    // tiles of 256 tokens, or of 128 where their rounds of workgroups take less: a round lasts as long however few of the 256
-    // compute units have a tile (GEMM alone, us, 256 -> 128 tokens a tile: 1531 tokens 4096 x 4096 78 -> 51, 4096 x 11008 226 -> 126,
-    // 768 tokens 8192 x 8192 164 -> 90)
-    wonly::Args h = g;
-    int64_t blocks = 0;
-    int rc = plan_walk(g, T, N, K, 256, blocks);
-    if (rc != AWEQ_OK) return rc;
-    const bool half = plan_walk(h, T, N, K, 128, blocks) == AWEQ_OK && wonly::kHalfTileCost * (double)rounds_of(h) < (double)rounds_of(g);
-    if (half) g = h;
-    const bool f16 = out_dt == AWEQ_F16;
     const void* fn = half ? (f16 ? reinterpret_cast<const void*>(wonly::gemm_f16_kernel<2, true>) : reinterpret_cast<const void*>(wonly::gemm_f16_kernel<2, false>))
                           : (f16 ? reinterpret_cast<const void*>(wonly::gemm_f16_kernel<4, true>) : reinterpret_cast<const void*>(wonly::gemm_f16_kernel<4, false>));
     return launch_persistent(fn, wonly::kThreads, wonly::Tile<4>::kLds, &g, g.n_ids, st);

@@ -248,30 +248,35 @@ static int launch_tile(const SmallArgs& g, bool fine, bool out_f16, hipStream_t 
     return launch_status();
 }
 
-template <int BITS>
-static int launch_bits(const SmallArgs& g, bool fine, bool out_f16, hipStream_t st)
+SmallPlan plan_small(int64_t T, int64_t N)
 {
     // Up to 16 tokens the pass is a read of the codes: 16 channels per workgroup until those workgroups fill the chip
     // 1.3 times over, then 32, which read the tokens half as often (8192 x 8192, one token: 11.9 / 12.2 us with 16 / 32;
-    // 22016 x 8192: 28.3 / 26.3; 11008 x 4096: 10.3 / 11.3; 64 channels lose everywhere)
-    const bool wide = g.N > 12288;
-    if (g.T <= 4) return wide ? launch_tile<BITS, 4, 2>(g, fine, out_f16, st) : launch_tile<BITS, 4, 1>(g, fine, out_f16, st);
-    if (g.T <= 16) return wide ? launch_tile<BITS, 16, 2>(g, fine, out_f16, st) : launch_tile<BITS, 16, 1>(g, fine, out_f16, st);
+    // 22016 x 8192: 28.3 / 26.3; 11008 x 4096: 10.3 / 11.3; 64 channels lose everywhere).  Nothing else comes near.
+    if (T <= 16) return {N > 12288 ? 2 : 1, 0.0};
     // More tokens, 32 per workgroup: as many channels as give the fewest rounds of workgroups, each weighted with what a
     // round was measured to take (8192 x 8192, 17 tokens, us: 19 for 512 workgroups of 16 channels, two per compute unit,
     // 14 for 256; 17.5 for 32 channels and 27 for 64, one per compute unit).  64 tokens per workgroup gain nothing
     // (64 tokens: 10.4 us at 4096 x 4096 in 32s, 14.0 in 64s; 76 / 75 at 22016 x 8192).
-    const int64_t tm = cdiv(g.T, 32), w1 = cdiv(g.N, 16) * tm, w2 = cdiv(g.N, 32) * tm, w4 = cdiv(g.N, 64) * tm;
+    const int64_t tm = cdiv(T, 32), w1 = cdiv(N, 16) * tm, w2 = cdiv(N, 32) * tm, w4 = cdiv(N, 64) * tm;
     const double c1 = w1 <= 256 ? 14.0 : 19.0 * (double)cdiv(w1, 512), c2 = 17.5 * (double)cdiv(w2, 256), c4 = 27.0 * (double)cdiv(w4, 256);
-    if (c1 <= c2 && c1 <= c4) return launch_tile<BITS, 32, 1>(g, fine, out_f16, st);
-    if (c2 <= c4) return launch_tile<BITS, 32, 2>(g, fine, out_f16, st);
-    return launch_tile<BITS, 32, 4>(g, fine, out_f16, st);
+    if (c1 <= c2 && c1 <= c4) return {1, c1};
+    return c2 <= c4 ? SmallPlan{2, c2} : SmallPlan{4, c4};
 }
 
-int launch_small(const SmallArgs& g, int bits, int group, bool out_f16, hipStream_t st)
+template <int BITS>
+static int launch_bits(const SmallArgs& g, bool fine, int nt, bool out_f16, hipStream_t st)
+{
+    if (g.T <= 4) return nt == 2 ? launch_tile<BITS, 4, 2>(g, fine, out_f16, st) : launch_tile<BITS, 4, 1>(g, fine, out_f16, st);
+    if (g.T <= 16) return nt == 2 ? launch_tile<BITS, 16, 2>(g, fine, out_f16, st) : launch_tile<BITS, 16, 1>(g, fine, out_f16, st);
+    return nt == 1 ? launch_tile<BITS, 32, 1>(g, fine, out_f16, st) : nt == 2 ? launch_tile<BITS, 32, 2>(g, fine, out_f16, st)
+                                                                              : launch_tile<BITS, 32, 4>(g, fine, out_f16, st);
+}
+
+int launch_small(const SmallArgs& g, int bits, int group, const SmallPlan& p, bool out_f16, hipStream_t st)
 {
     const bool fine = group > 0 && group % 128 != 0;
-    return bits == 4 ? launch_bits<4>(g, fine, out_f16, st) : launch_bits<3>(g, fine, out_f16, st);
+    return bits == 4 ? launch_bits<4>(g, fine, p.nt, out_f16, st) : launch_bits<3>(g, fine, p.nt, out_f16, st);
 }
 
 }  // namespace wonly

@@ -1,7 +1,8 @@
-"""The tiled weight-only GEMM and the pass that de-quantises the weight for it, where their plans change: tiles of 128 and of
-256 tokens, one round of workgroups and several, 1 .. 5 stages of K (the load ring holds three), columns that end inside a
-wavefront's 512 codes and rows that end inside its four.  Against the oracle's fp64 product within the bound of fp32
-accumulation in any order, |y - ref| <= K 2^-24 sum_k |x w| plus one rounding of the output."""
+"""The weight-only forward from some hundred tokens on, where its plans change: 64 x 128 and 128 x 128 tiles straight from the
+codes, the pass that de-quantises the weight with tiles of 128 and of 256 tokens behind it, one round of workgroups and
+several, 1 .. 5 stages of K (every load ring holds three), columns that end inside a stage, a panel of 512 codes or a tile,
+zero points outside the packed path.  Against the oracle's fp64 product within the bound of fp32 accumulation in any order,
+|y - ref| <= K 2^-24 sum_k |x w| plus one rounding of the output."""
 import numpy as np
 import pytest
 
@@ -21,8 +22,11 @@ def B():
 
 
 @pytest.mark.parametrize("bits,T,N,K,group", [
-    (4, 257, 260, 64, 64), (3, 385, 516, 192, 96), (4, 513, 2304, 320, 64), (3, 640, 772, 576, -1),   # 128 tokens a tile, one round
-    (4, 900, 12292, 128, 128),                                                                        # the same, two rounds
+    (4, 200, 4100, 64, 0), (3, 200, 4100, 256, 128), (4, 200, 4100, 512, 256), (3, 200, 4100, 832, -1), (4, 193, 4228, 1280, 128),   # 64 x 128
+    (3, 256, 4096, 576, 0),                                                                           # the same, zero points far outside
+    (4, 240, 11012, 64, -1), (3, 240, 11012, 128, 128), (3, 250, 10884, 320, 0), (4, 256, 11008, 384, 128), (4, 129, 22020, 640, 128),   # 128 x 128
+    (4, 900, 7172, 64, 64), (3, 1000, 7936, 192, 96), (4, 1024, 8192, 320, 64), (3, 900, 7172, 576, -1),   # 128 tokens a tile, one round
+    (4, 2500, 7684, 128, 128),                                                                        # the same, three rounds
     (4, 2100, 4100, 64, 0), (3, 2100, 4100, 192, 64), (4, 2304, 4352, 320, 32),                       # 256 tokens a tile, one round
     (3, 4000, 8100, 128, 128),                                                                        # the same, two rounds
 ])
