@@ -600,6 +600,7 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
         int rows_in = 0;   // rows of this lane inside T (the fused code epilogue turns unsigned sums into signed ones)
         float ymn[4] = {INFINITY, INFINITY, INFINITY, INFINITY}, ymx[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
         double ysum[4] = {0.0, 0.0, 0.0, 0.0};   // exact: at most 128 binary16 values each
+        int rsy_kept[MI / 2] = {};               // row sums of the next layer's codes: one per lane and 64 tokens
         float cqf[4] = {0.f, 0.f, 0.f, 0.f};     // column sums of the next layer's unsigned codes over this tile (exact: 32 rows)
         const bool yq_pad = (EPI & 2) != 0 && !n_ok && cn0 + wn * 64 < g.N;   // zero fill of the last panel
         int8_t* const yq_lane = (EPI & 2) != 0 ? g.yq + (((cn0 >> 6) + wn) * g.T) * kPanel + rd_c * 4 : nullptr;
@@ -702,9 +703,9 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
                     *reinterpret_cast<uint32_t*>(yq_lane + t * kPanel) = 0u;
                 }
                 if constexpr ((EPI & 2) != 0) {
-                    // the 16 lanes of one output row (every lane active here)
+                    // the 16 lanes of one output row (every lane active here); lane 16 r + c keeps the sums of passes c and c + 16
                     rsy = group_allreduce<4>(rsy, OpAdd());
-                    if (rd_c == 0 && t < g.T && g.rowsum_y) atomicAdd(&g.rowsum_y[t], rsy);
+                    rsy_kept[(i * 8 + p) >> 4] = ((i * 8 + p) & 15) == rd_c ? rsy : rsy_kept[(i * 8 + p) >> 4];
                 }
             }
         }
@@ -731,6 +732,15 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
             }
         }
         if constexpr ((EPI & 2) != 0) {
+            // (one atomic instruction per 64 neighbouring tokens; four tokens at a time, the two layers 4096 -> 16384 -> 4096 took
+            // 172 instead of 157 us at 1024 tokens, 110 instead of 100 at 512)
+            if (g.rowsum_y) {
+#pragma unroll
+                for (int h = 0; h < MI / 2; ++h) {
+                    const int64_t t = t_lane + h * 64 + rd_c * 4;   // pass c of 16: token 32 (c / 8) + 4 (c % 8) + r = 4 c + r
+                    if (t < g.T) atomicAdd(&g.rowsum_y[t], rsy_kept[h]);
+                }
+            }
             int cq[4];
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
@@ -808,11 +818,12 @@ static void clear_fused(GemmArgs& g)
     g.yq = nullptr; g.rowsum_y = nullptr; g.colsum_yq = nullptr; g.status = nullptr;
 }
 
-// accumulators of the fused epilogues start from their identities (fill kernels: graph-capturable)
-__global__ void fused_init(uint32_t* ykeys, long long* yfix, int64_t N, long long* colsum_yq, int32_t* rowsum_y, int64_t T)
+// accumulators of the fused epilogues start from their identities (a fill kernel: graph-capturable)
+__global__ void fused_init(long long* colsum_acc, uint32_t* ykeys, long long* yfix, int64_t N, long long* colsum_yq, int32_t* rowsum_y, int64_t T)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < N) {
+        colsum_acc[i] = 0;
         if (ykeys) { ykeys[i] = 0xffffffffu; ykeys[N + i] = 0u; yfix[i] = 0; }
         if (colsum_yq) colsum_yq[i] = 0;
     }
@@ -978,10 +989,13 @@ extern "C" int aweq_w8a8_gemm_fused(const int8_t* xq, int64_t T, int64_t K, cons
     if (prc != AWEQ_OK) return prc;
 
     hipStream_t st = as_stream(stream);
-    zero_fill_u32_gemm<<<(unsigned)cdiv(2 * N, 256), 256, 0, st>>>(reinterpret_cast<uint32_t*>(colsum_acc), 2 * N);
     const int64_t init_n = (want_quant && rowsum_y && T > N) ? T : N;
-    fused_init<<<(unsigned)cdiv(init_n, 256), 256, 0, st>>>(g.ykeys, g.yfix, N, want_quant ? g.colsum_yq : nullptr,
+    fused_init<<<(unsigned)cdiv(init_n, 256), 256, 0, st>>>(g.colsum_acc, g.ykeys, g.yfix, N, want_quant ? g.colsum_yq : nullptr,
                                                             want_quant ? rowsum_y : nullptr, T);
+    // fewer tokens: 64 x 128 or 128 x 128 tiles, which have the quantising epilogue but not the statistics one (two layers
+    // 4096 -> 16384 -> 4096, us, 128 tokens a tile -> these: 16 tokens 55.9 -> 47.3, 64 tokens 73.6 -> 62.3, 256 tokens 93.0 -> 83.7)
+    const MidPlan mid = plan_mid(T, N);
+    if (!want_stats && mid.cost < kTiledRoundCost * tiled_cost) return launch_gemm_i8_mid(g, mid, st);
     const int epi = (want_stats ? 1 : 0) | (want_quant ? 2 : 0);
     const bool store = out_f16 != nullptr;
     const void* fn = nullptr;

@@ -49,7 +49,8 @@ __device__ __forceinline__ void wait_vm()
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
-template <int WM, int WN, int WK>
+// QUANT: the epilogue also quantises the binary16 output for the next layer (aweq_w8a8_gemm_fused without statistics)
+template <int WM, int WN, int WK, bool QUANT>
 __global__ __launch_bounds__(kThreads) void gemm_i8_mid(GemmArgs g)
 {
     using TL = Tile<WM, WN, WK>;
@@ -75,7 +76,8 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_mid(GemmArgs g)
     const bool n_ok = n < g.N;     // N % 4 == 0: all four channels or none
     int zx = 0, zw[4] = {0, 0, 0, 0}, rw[4] = {0, 0, 0, 0}, rsx[kRows];
     float sxf = 0.f, sw[4] = {0.f, 0.f, 0.f, 0.f}, bs[4] = {0.f, 0.f, 0.f, 0.f};
-    if (g.out_deq) {
+    const bool deq = QUANT || g.out_deq;
+    if (deq) {
         zx = *g.act_zero - 128;
         sxf = *g.act_step;
 #pragma unroll
@@ -183,7 +185,7 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_mid(GemmArgs g)
     uint32_t est = 0;
     unsigned cn[4] = {0, 0, 0, 0};
     double scale[4] = {0, 0, 0, 0};
-    if (g.out_deq) {
+    if (deq) {
         // the tiled kernel's arithmetic: the integer part in wrap-around 32 bits, scaled and shifted in fp64
         if (zx < -128 || zx > 127) est |= AWEQ_ST_ZEROPOINT;
 #pragma unroll
@@ -193,66 +195,120 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_mid(GemmArgs g)
             scale[c] = (double)sxf * (double)sw[c];
         }
     }
-    long long csum[4] = {0, 0, 0, 0};
+    // the next layer's quantizer, as in the tiled kernel's fused epilogue
+    float nis[4] = {1.f, 1.f, 1.f, 1.f};
+    ActParams np_ = {};
+    bool nscreen = false;
+    if constexpr (QUANT) {
+        np_ = quot_params(*g.next_step, *g.next_zero);
+        nscreen = np_.screen;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            if (n_ok) nis[c] = g.next_inv_s[n + c];
+            nscreen = nscreen && 65600.0f * fabsf(nis[c]) * np_.rstep < 16777216.0f;
+        }
+    }
+    long long csum[4] = {0, 0, 0, 0}, qsum[4] = {0, 0, 0, 0};
+    int rs_kept = 0;   // row sum of the codes of this thread's ec-th token
 #pragma unroll
     for (int i = 0; i < kRows; ++i) {
         const int r = er + i * kRowStep;
         const int64_t t = m0 + r;
-        if (t >= g.T || !n_ok) continue;
+        const bool ok = t < g.T && n_ok;
         v4i o = {0, 0, 0, 0};
+        if (ok) {
 #pragma unroll
-        for (int k = 0; k < WK; ++k) {
-            const char* const part = lds + ((k * WM + r / 64) * WN + ec / 16) * 16384;
-            o += *reinterpret_cast<const v4i*>(part + (r & 63) * 256 + (((ec & 15) ^ (r & 15)) * 16));
+            for (int k = 0; k < WK; ++k) {
+                const char* const part = lds + ((k * WM + r / 64) * WN + ec / 16) * 16384;
+                o += *reinterpret_cast<const v4i*>(part + (r & 63) * 256 + (((ec & 15) ^ (r & 15)) * 16));
+            }
         }
-        if (g.out_i32) *reinterpret_cast<v4i*>(g.out_i32 + t * g.ldo + n) = o;
-        if (g.out_deq) {
+        int rs = 0;
+        if (!QUANT && ok && g.out_i32) *reinterpret_cast<v4i*>(g.out_i32 + t * g.ldo + n) = o;
+        if (ok && deq) {
+            typedef _Float16 h4 __attribute__((ext_vector_type(4)));
             float y[4];
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 const double div = (double)(int)((unsigned)o[c] + cn[c] - (unsigned)zw[c] * (unsigned)rsx[i]);
-                y[c] = g.out_f16 ? (float)__builtin_fma(div, scale[c], (double)bs[c]) : (float)(div * scale[c] + (double)bs[c]);
+                y[c] = QUANT || g.out_f16 ? (float)__builtin_fma(div, scale[c], (double)bs[c]) : (float)(div * scale[c] + (double)bs[c]);
+                if (QUANT && g.act == 1) y[c] = fmaxf(y[c], 0.0f);
             }
-            if (g.out_f16) {
-                typedef _Float16 h4 __attribute__((ext_vector_type(4)));
-                *reinterpret_cast<h4*>(reinterpret_cast<_Float16*>(g.out_deq) + t * g.ldo + n) =
-                    h4{(_Float16)y[0], (_Float16)y[1], (_Float16)y[2], (_Float16)y[3]};
+            const h4 oh = {(_Float16)y[0], (_Float16)y[1], (_Float16)y[2], (_Float16)y[3]};
+            if (QUANT || g.out_f16) {
+                if (g.out_deq) *reinterpret_cast<h4*>(reinterpret_cast<_Float16*>(g.out_deq) + t * g.ldo + n) = oh;
             } else {
                 *reinterpret_cast<Float4*>(reinterpret_cast<float*>(g.out_deq) + t * g.ldo + n) = Float4{{y[0], y[1], y[2], y[3]}};
             }
+            if constexpr (QUANT) {
+                uint32_t w = 0;
+                float u[4], dmax = 0.0f;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const float a = __builtin_fmaf((float)oh[c], nis[c], 0.0f);
+                    const float q = __builtin_fmaf(a, np_.rstep, (float)np_.zero);
+                    u[c] = rintf(q);
+                    dmax = fmaxf(dmax, fabsf(q - u[c]));
+                }
+                if (!nscreen || dmax > np_.thr) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) u[c] = (float)quant_div((float)oh[c] * nis[c], np_.step, np_.zero, 255, est);
+                }
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    u[c] = __builtin_amdgcn_fmed3f(u[c], 0.0f, 255.0f);
+                    qsum[c] += (int)u[c] - 128;
+                    w = __builtin_amdgcn_cvt_pk_u8_f32(u[c], c, w);
+                }
+                w ^= 0x80808080u;
+                rs = __builtin_amdgcn_sdot4((int)w, 0x01010101, 0, false);
+                *reinterpret_cast<uint32_t*>(g.yq + panel_offset(g.T, t, n)) = w;
+            }
+        } else if (QUANT && t < g.T && (n & ~(int64_t)(kPanel - 1)) < g.N) {
+            *reinterpret_cast<uint32_t*>(g.yq + panel_offset(g.T, t, n)) = 0u;   // zero fill of the last panel
+        }
+        if constexpr (QUANT) {
+            static_assert(kRowThreads == 32 && kRows <= 32, "a token's channels sit in half a wavefront");
+            rs = group_allreduce<5>(rs, OpAdd());
+            rs_kept = ec == i ? rs : rs_kept;
         }
 #pragma unroll
         for (int c = 0; c < 4; ++c) csum[c] += o[c];
     }
-    if (g.colsum_acc) {
-        // threads with the same channels: lanes 16 (32) apart, then the wavefronts
+    if (QUANT && g.rowsum_y && ec < kRows) {
+        const int64_t t = m0 + er + ec * kRowStep;
+        if (t < g.T) atomicAdd(&g.rowsum_y[t], rs_kept);
+    }
+    // sums over the tokens: threads with the same channels are lanes 32 apart, then the wavefronts
+    auto add_columns = [&](long long v[4], long long* dst) {
         __syncthreads();
         long long* const red = reinterpret_cast<long long*>(lds);   // [wavefront][channel]
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            if constexpr (kRowThreads <= 16) csum[c] += partner<4>(csum[c]);
-            if constexpr (kRowThreads <= 32) csum[c] += partner<5>(csum[c]);
-            if (lane < kRowThreads) red[wave * TL::kN + lane * 4 + c] = csum[c];
+            v[c] += partner<5>(v[c]);
+            if (lane < kRowThreads) red[wave * TL::kN + lane * 4 + c] = v[c];
         }
         __syncthreads();
         for (int ch = tid; ch < TL::kN; ch += kThreads) {
             long long sum = 0;
 #pragma unroll
             for (int w = 0; w < 8; ++w) sum += red[w * TL::kN + ch];
-            if (n0 + ch < g.N) atomicAdd(reinterpret_cast<unsigned long long*>(&g.colsum_acc[n0 + ch]), (unsigned long long)sum);
+            if (n0 + ch < g.N) atomicAdd(reinterpret_cast<unsigned long long*>(&dst[n0 + ch]), (unsigned long long)sum);
         }
-    }
+    };
+    if (g.colsum_acc) add_columns(csum, g.colsum_acc);
+    if (QUANT && g.colsum_yq) add_columns(qsum, g.colsum_yq);
     raise_status(g.status, est);
 }
 
-template <int WM, int WN, int WK>
+template <int WM, int WN, int WK, bool QUANT>
 static int launch_tile(GemmArgs g, hipStream_t st)
 {
     using TL = Tile<WM, WN, WK>;
     g.tiles_m = (int)cdiv(g.T, TL::kM);
     g.tiles_n = (int)cdiv(g.N, TL::kN);
     g.run = (int)cdiv((int64_t)g.tiles_m * g.tiles_n, kXcdCount);
-    const void* fn = reinterpret_cast<const void*>(gemm_i8_mid<WM, WN, WK>);
+    const void* fn = reinterpret_cast<const void*>(gemm_i8_mid<WM, WN, WK, QUANT>);
     int dev = 0, cus = 0;
     if (device_cus(dev, cus) != AWEQ_OK || raise_lds_limit(fn, dev, TL::kLds) != AWEQ_OK) return AWEQ_ERR_LAUNCH;
     void* args[] = {&g};
@@ -273,7 +329,8 @@ MidPlan plan_mid(int64_t T, int64_t N)
 
 int launch_gemm_i8_mid(const GemmArgs& g, const MidPlan& p, hipStream_t st)
 {
-    return p.square ? mid::launch_tile<2, 2, 2>(g, st) : mid::launch_tile<1, 2, 4>(g, st);
+    if (g.yq) return p.square ? mid::launch_tile<2, 2, 2, true>(g, st) : mid::launch_tile<1, 2, 4, true>(g, st);
+    return p.square ? mid::launch_tile<2, 2, 2, false>(g, st) : mid::launch_tile<1, 2, 4, false>(g, st);
 }
 
 }  // namespace aweq
