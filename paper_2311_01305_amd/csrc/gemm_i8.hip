@@ -888,11 +888,13 @@ extern "C" int aweq_w8a8_gemm(const void* X, aweq_dtype x_dt, int64_t T, int64_t
         if (!act_step || !act_zero || !step_w || !zero_w || !rowsum_x || !rowsum_w) return AWEQ_ERR_NULL;
     }
     hipStream_t st = as_stream(stream);
-    if (x_dt != AWEQ_I8) {
-        const int rc = launch_quant_act(X, x_dt, T, K, ldx, inv_s, act_step, act_zero, xq, rowsum_x, colsum_xq, ws, status, st);
-        if (rc != AWEQ_OK) return rc;
+    auto quantise = [&]() {
+        return x_dt == AWEQ_I8 ? (int)AWEQ_OK : launch_quant_act(X, x_dt, T, K, ldx, inv_s, act_step, act_zero, xq, rowsum_x, colsum_xq, ws, status, st);
+    };
+    if (!out_i32 && !out_deq && !colsum_acc) {
+        const int rc = quantise();
+        return rc != AWEQ_OK ? rc : launch_status();
     }
-    if (!out_i32 && !out_deq && !colsum_acc) return launch_status();
 
     GemmArgs g;
     g.A = a; g.B = wq; g.T = T; g.N = N; g.K = K;
@@ -915,11 +917,20 @@ extern "C" int aweq_w8a8_gemm(const void* X, aweq_dtype x_dt, int64_t T, int64_t
     const int prc = fast_ok ? plan_tiled(g, half, tiled_cost, blocks) : plan_walk(g, g.T, g.N, g.K, BM, blocks);
     if (prc != AWEQ_OK) return prc;
 
-    if (colsum_acc) zero_fill_u32_gemm<<<(unsigned)cdiv(2 * N, 256), 256, 0, st>>>(reinterpret_cast<uint32_t*>(colsum_acc), 2 * N);
-
     // the form whose rounds of workgroups are modelled to take least
     const FewPlan few = plan_few(T, N);
     const MidPlan mid = plan_mid(T, N);
+    // one to four tokens: the few-token form quantises them itself, one launch instead of two (us per call, one / four tokens:
+    // 4096 x 4096 9.2 -> 7.9 / 9.4 -> 9.3, 11008 x 4096 14.8 -> 12.5 / 15.2 -> 14.2, 1536 x 2048 8.5 -> 6.0 / 8.5 -> 7.0; no more than
+    // 16 KiB of codes: every workgroup repeats the work)
+    const bool own_quant = fast_ok && x_dt != AWEQ_I8 && !colsum_xq && T <= kQuantTokens && T * panel_count(K) * kPanel <= kQuantFewBytes && aligned16(inv_s) &&
+                           few.cost <= mid.cost && few.cost < kTiledRoundCost * tiled_cost;
+    if (!own_quant) {
+        const int rc = quantise();
+        if (rc != AWEQ_OK) return rc;
+    }
+    if (colsum_acc) zero_fill_u32_gemm<<<(unsigned)cdiv(2 * N, 256), 256, 0, st>>>(reinterpret_cast<uint32_t*>(colsum_acc), 2 * N);
+    if (own_quant) return launch_gemm_i8_few_quant(g, few, QuantIn{X, ldx, inv_s, xq, rowsum_x}, x_dt == AWEQ_F16, st);
     if (fast_ok && few.cost <= mid.cost && few.cost < kTiledRoundCost * tiled_cost) return launch_gemm_i8_few(g, few, st);
     if (fast_ok && mid.cost < kTiledRoundCost * tiled_cost) return launch_gemm_i8_mid(g, mid, st);
     if (fast_ok) {

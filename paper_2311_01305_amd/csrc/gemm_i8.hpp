@@ -43,6 +43,19 @@ struct FewPlan {
 FewPlan plan_few(int64_t T, int64_t N);
 int launch_gemm_i8_few(const GemmArgs& g, const FewPlan& p, hipStream_t st);
 
+// The same for at most kQuantTokens binary16 / binary32 tokens that the launch quantises itself (what the activation quantizer would
+// write goes to xq and rowsum_x; g.A and g.rowsum_x are not read)
+struct QuantIn {
+    const void* X;
+    int64_t ldx;
+    const float* inv_s;
+    int8_t* xq;
+    int32_t* rowsum_x;
+};
+int launch_gemm_i8_few_quant(const GemmArgs& g, const FewPlan& p, const QuantIn& in, bool f16, hipStream_t st);
+constexpr int kQuantTokens = 4;
+constexpr int64_t kQuantFewBytes = 16384;   // codes such a launch may hold
+
 // The same of the kernel for some hundred tokens (gemm_i8_mid.hip)
 struct MidPlan {
     bool square;   // 128 x 128 tiles instead of 64 x 128

@@ -12,6 +12,7 @@
 //   8192 x 8192     68.3 -> 13.3  68.5 -> 13.7  69.3 -> 15.0  71.4 -> 19.4  72.7 -> 36.7
 //   22016 x 8192    71.8 -> 34.5  70.4 -> 39.6  71.3 -> 48.9  73.2 -> 69.4  (tiled: 80)
 // (22016 x 8192 at one token: 180 MB, 5.2 TB/s.)
+#include "act_unit.hpp"
 #include "gemm_i8.hpp"
 
 namespace aweq {
@@ -21,11 +22,16 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 512;
 constexpr int kWaves = kThreads / kWave;
+constexpr int kMaxQuantLds = 64 * 1024;   // partial sums (at most 16 KiB) and the codes of a quantising launch
 
-template <int TT, int NT, int U>
-__global__ __launch_bounds__(kThreads) void gemm_i8_few(GemmArgs g)
+// QX: 0: the tokens' codes are in memory (g.A).  1 / 2: every workgroup quantises the few binary16 / binary32 tokens (QuantIn) for
+// itself while its first weights are on their way, the first workgroup also for the caller: a second launch costs more
+// than the repeated work.
+template <int TT, int NT, int U, int QX>
+__global__ __launch_bounds__(kThreads) void gemm_i8_few(GemmArgs g, QuantIn in)
 {
-    extern __shared__ __attribute__((aligned(16))) int red[];   // [wave][TT NT][lane][4]
+    extern __shared__ __attribute__((aligned(16))) int red[];   // [wave][TT NT][lane][4], then (QX) the tokens' codes, K padded to panels
+    __shared__ int s_rs[kQuantTokens];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     const int r = lane & 15, q = lane >> 4;
@@ -59,11 +65,61 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_few(GemmArgs g)
 #pragma unroll
                 for (int j = 0; j < NT; ++j) w[u][j] = *reinterpret_cast<const v4i*>(wbase + p * wp + wo[j]);
 #pragma unroll
-                for (int i = 0; i < TT; ++i) x[u][i] = *reinterpret_cast<const v4i*>(xbase + p * xp + xo[i]);
+                for (int i = 0; i < TT; ++i)
+                    if constexpr (QX == 0) x[u][i] = *reinterpret_cast<const v4i*>(xbase + p * xp + xo[i]);
             }
         }
     };
     load(wave);
+    int8_t* const codes = reinterpret_cast<int8_t*>(red + kWaves * TT * NT * kWave * 4);
+    if constexpr (QX != 0) {
+        const ActParams ap = quot_params(*g.act_step, *g.act_zero);
+        uint32_t st = 0;
+        float big = 0.0f;
+        const int units = (int)(g.K / 8), padded = np * (kPanel / 8);
+        const int T = (int)g.T;
+        int rs[kQuantTokens];
+#pragma unroll
+        for (int t = 0; t < kQuantTokens; ++t) rs[t] = 0;
+        if (threadIdx.x < kQuantTokens) s_rs[threadIdx.x] = 0;
+        __syncthreads();
+        for (int u = threadIdx.x; u < padded; u += kThreads) {
+            const bool real = u < units;   // (past K: the zero fill of the last panel)
+            RawUnit<QX == 1> raw[kQuantTokens];
+            float is[8];
+            if (real) {
+#pragma unroll
+                for (int t = 0; t < kQuantTokens; ++t)
+                    if (t < T) raw[t].load(in.X, t * in.ldx + u * 8);
+                const Float4 a = *reinterpret_cast<const Float4*>(in.inv_s + u * 8), b = *reinterpret_cast<const Float4*>(in.inv_s + u * 8 + 4);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) { is[i] = a.f[i]; is[4 + i] = b.f[i]; }
+            }
+#pragma unroll
+            for (int t = 0; t < kQuantTokens; ++t) {
+                if (t >= T) break;
+                uint2 c = make_uint2(0u, 0u);
+                if (real) {
+                    float xf[8];
+                    raw[t].get(xf);
+                    c = act_unit_any<QX == 1>(xf, is, ap, rs[t], big, st);
+                }
+                *reinterpret_cast<uint2*>(codes + (t * padded + u) * 8) = c;
+                if (blockIdx.x == 0) *reinterpret_cast<uint2*>(in.xq + ((int64_t)(u >> 3) * g.T + t) * kPanel + (u & 7) * 8) = c;
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < kQuantTokens; ++t) {
+            if (t >= T) break;
+            rs[t] = wave_allreduce(rs[t], OpAdd());
+            if (lane == 0) atomicAdd(&s_rs[t], rs[t]);
+        }
+        if (big >= 16777216.0f) st |= AWEQ_ST_BIGQUOT;
+        if (blockIdx.x == 0) raise_status(g.status, st);
+        __syncthreads();
+        if (blockIdx.x == 0 && in.rowsum_x && (int)threadIdx.x < (int)g.T) in.rowsum_x[threadIdx.x] = s_rs[threadIdx.x];
+    }
+    const int8_t* const own = codes + min(r, (int)g.T - 1) * np * kPanel + q * 16;   // (QX: one row of 16 tokens)
     for (int p0 = wave; p0 < np; p0 += U * kWaves) {
         v4i cw[U][NT], cx[U][TT];
 #pragma unroll
@@ -71,7 +127,9 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_few(GemmArgs g)
 #pragma unroll
             for (int j = 0; j < NT; ++j) cw[u][j] = w[u][j];
 #pragma unroll
-            for (int i = 0; i < TT; ++i) cx[u][i] = x[u][i];
+            for (int i = 0; i < TT; ++i)
+                if constexpr (QX == 0) cx[u][i] = x[u][i];
+                else cx[u][i] = *reinterpret_cast<const v4i*>(own + min(p0 + u * kWaves, np - 1) * kPanel);
         }
         load(p0 + U * kWaves);
 #pragma unroll
@@ -106,7 +164,7 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_few(GemmArgs g)
             const int zx = *g.act_zero - 128;
             const double sx = (double)*g.act_step;
             if (zx < -128 || zx > 127) est |= AWEQ_ST_ZEROPOINT;
-            const unsigned rs = (unsigned)g.rowsum_x[t];
+            const unsigned rs = QX != 0 ? (unsigned)s_rs[t] : (unsigned)g.rowsum_x[t];
             float y[4];
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
@@ -148,14 +206,14 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_few(GemmArgs g)
     raise_status(g.status, est);
 }
 
-template <int TT, int NT, int U>
-static int launch_tile(const GemmArgs& g, hipStream_t st)
+template <int TT, int NT, int U, int QX = 0>
+static int launch_tile(const GemmArgs& g, hipStream_t st, QuantIn in = {})
 {
-    constexpr int lds = kWaves * TT * NT * kWave * 16;
-    const void* fn = reinterpret_cast<const void*>(gemm_i8_few<TT, NT, U>);
+    const int lds = kWaves * TT * NT * kWave * 16 + (QX != 0 ? (int)(g.T * panel_count(g.K) * kPanel) : 0);
+    const void* fn = reinterpret_cast<const void*>(gemm_i8_few<TT, NT, U, QX>);
     int dev = 0, cus = 0;
-    if (lds > 32768 && (device_cus(dev, cus) != AWEQ_OK || raise_lds_limit(fn, dev, lds) != AWEQ_OK)) return AWEQ_ERR_LAUNCH;
-    void* args[] = {const_cast<GemmArgs*>(&g)};
+    if (lds > 32768 && (device_cus(dev, cus) != AWEQ_OK || raise_lds_limit(fn, dev, QX != 0 ? kMaxQuantLds : lds) != AWEQ_OK)) return AWEQ_ERR_LAUNCH;
+    void* args[] = {const_cast<GemmArgs*>(&g), &in};
     if (hipLaunchKernel(fn, dim3((unsigned)cdiv(g.N, 16 * NT), (unsigned)cdiv(g.T, 16 * TT)), dim3(kThreads), args, lds, st) != hipSuccess)
         return AWEQ_ERR_LAUNCH;
     return launch_status();
@@ -177,6 +235,12 @@ FewPlan plan_few(int64_t T, int64_t N)
     if (c22 <= c24 && c22 <= c44) return FewPlan{3, c22};
     if (c24 <= c44) return FewPlan{4, c24};
     return FewPlan{5, c44};
+}
+
+int launch_gemm_i8_few_quant(const GemmArgs& g, const FewPlan& p, const QuantIn& in, bool f16, hipStream_t st)
+{
+    if (p.tile == 0) return f16 ? few::launch_tile<1, 1, 4, 1>(g, st, in) : few::launch_tile<1, 1, 4, 2>(g, st, in);
+    return f16 ? few::launch_tile<1, 2, 4, 1>(g, st, in) : few::launch_tile<1, 2, 4, 2>(g, st, in);
 }
 
 int launch_gemm_i8_few(const GemmArgs& g, const FewPlan& p, hipStream_t st)

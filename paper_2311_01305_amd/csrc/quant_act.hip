@@ -23,10 +23,12 @@
 // (about 1.5e-4 of all elements for |Z| <= 255) are redone with the exact sequence.  Binary32 input takes the screened
 // quotient too, where |Z| allows it, and divides the units with a quotient beyond 2^22 (7419 x 4096 tokens x channels:
 // 47.4 us with the division everywhere, 40.1 now; a quotient that underflows on the way rounds to 0 either way).
-#include "common.hpp"
+#include "act_unit.hpp"
 #include <type_traits>
 
 namespace aweq {
+
+typedef unsigned v2u __attribute__((ext_vector_type(2)));
 
 constexpr int kQaBlock = 256;
 constexpr int kQaWaves = kQaBlock / kWave;
@@ -36,131 +38,6 @@ constexpr int kQaMaxRows = 512;                         // rows per block (LDS r
 constexpr int kQaRowBatch = 4;                          // groups of 8 rows in flight per thread
 constexpr int kQaRowsPerIter = 8 * kQaRowBatch;
 constexpr unsigned kQaXcds = 8;                         // workgroup id % 8 names the XCD a workgroup runs on
-
-// One unit (8 consecutive columns of one row): codes, packed store, column / row sums.
-// FAST: the division-free quotient; the unsigned code is kept as an (integral) float, packed
-// with v_cvt_pk_u8_f32 and turned into the stored signed code by flipping the top bit
-// (u - 128 = u ^ 0x80 as a byte).  Column sums accumulate u in fp32 (exact: at most 512 rows
-// of values <= 255 per block); the caller subtracts 128 per row afterwards.
-// MODE 0: true division; 1: the exact division-free quotient; 2: screened (see the header); 3: screened for binary32
-// input, whose quotients have no bound known beforehand: a unit with one beyond 2^22, infinite or NaN is divided.
-// SUMS: only the column sums are wanted (no code buffer, no row sums).
-template <int MODE, bool SUMS = false>
-__device__ __forceinline__ void act_unit(const float x[8], const float is[8], const ActParams& p, int8_t* dst,
-                                         float csf[8], int csi[8], int& rs, float& big, uint32_t& st)
-{
-    uint32_t w[2] = {0u, 0u};
-    if constexpr (MODE == 2 || MODE == 3) {
-        const float zf = (float)p.zero;
-        float n[8];
-        float dmax = 0.0f, largest = 0.0f, bad = 0.0f;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            // x is a widened binary16 value: a = RN(x inv_s) as one mixed-precision FMA (+0 changes
-            // nothing but the sign of a zero, which the quotient's rounding forgets)
-            const float a = __builtin_fmaf(x[i], is[i], 0.0f);
-            const float q = __builtin_fmaf(a, p.rstep, zf);
-            n[i] = rintf(q);
-            const float d = fabsf(q - n[i]);
-            dmax = fmaxf(dmax, d);
-            if constexpr (MODE == 3) {
-                largest = fmaxf(largest, fabsf(q));
-                bad += d;   // NaN from an infinite or NaN quotient on
-            }
-        }
-        if (MODE == 3 && !(largest < 4194304.0f && bad < 8.0f)) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) n[i] = (float)quant_div(x[i] * is[i], p.step, p.zero, 255, st);
-        } else if (dmax > p.thr) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const float a = x[i] * is[i];
-                float q = a * p.rstep;
-                float r = __builtin_fmaf(-p.step, q, a);
-                q = __builtin_fmaf(r, p.rstep, q);
-                r = __builtin_fmaf(-p.step, q, a);
-                q = __builtin_fmaf(r, p.rstep, q);
-                n[i] = rintf(q) + zf;   // |rint| < 2^24 here (checked per thread), |Z| <= 4096
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const float u = __builtin_amdgcn_fmed3f(n[i], 0.0f, 255.0f);
-            csf[i] += u;
-            if constexpr (!SUMS) w[i >> 2] = __builtin_amdgcn_cvt_pk_u8_f32(u, i & 3, w[i >> 2]);
-        }
-        w[0] ^= 0x80808080u;
-        w[1] ^= 0x80808080u;
-    } else if constexpr (MODE == 1) {
-        const float zf = (float)p.zero;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const float a = x[i] * is[i];
-            float q = a * p.rstep;
-            float r = __builtin_fmaf(-p.step, q, a);
-            q = __builtin_fmaf(r, p.rstep, q);
-            r = __builtin_fmaf(-p.step, q, a);
-            q = __builtin_fmaf(r, p.rstep, q);
-            const float n = rintf(q);
-            big = fmaxf(big, fabsf(n));
-            // |Z| < 2^23: n + Z is exact wherever it can land inside [0, 255]
-            const float u = __builtin_amdgcn_fmed3f(n + zf, 0.0f, 255.0f);
-            csf[i] += u;
-            w[i >> 2] = __builtin_amdgcn_cvt_pk_u8_f32(u, i & 3, w[i >> 2]);
-        }
-        w[0] ^= 0x80808080u;
-        w[1] ^= 0x80808080u;
-    } else {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const float a = x[i] * is[i];
-            const int c = quant_div(a, p.step, p.zero, 255, st) - 128;
-            csi[i] += c;
-            w[i >> 2] |= (uint32_t)(c & 0xff) << (8 * (i & 3));
-        }
-    }
-    if constexpr (SUMS) return;
-    rs = __builtin_amdgcn_sdot4((int)w[0], 0x01010101, rs, false);
-    rs = __builtin_amdgcn_sdot4((int)w[1], 0x01010101, rs, false);
-    typedef unsigned v2u_ __attribute__((ext_vector_type(2)));
-    if (dst) __builtin_nontemporal_store(v2u_{w[0], w[1]}, reinterpret_cast<v2u_*>(dst));   // (sums only: no code buffer)
-}
-
-// 8 consecutive input values of one row as loaded (binary16: one 16-byte quad), converted to
-// fp32 only when they are consumed so that the loads in flight stay cheap in registers
-template <bool F16> struct RawUnit;
-template <> struct RawUnit<true> {
-    Half8 v;
-    __device__ __forceinline__ void load(const void* X, int64_t elt)
-    {
-        typedef int v4i_ __attribute__((ext_vector_type(4)));
-        const v4i_ r = __builtin_nontemporal_load(reinterpret_cast<const v4i_*>(reinterpret_cast<const _Float16*>(X) + elt));
-        v = __builtin_bit_cast(Half8, r);
-    }
-    __device__ __forceinline__ void get(float x[8]) const
-    {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            float2 f = h2f2(v.h[i]);
-            x[2 * i] = f.x;
-            x[2 * i + 1] = f.y;
-        }
-    }
-};
-template <> struct RawUnit<false> {
-    Float4 a, b;
-    __device__ __forceinline__ void load(const void* X, int64_t elt)
-    {
-        const float* p = reinterpret_cast<const float*>(X) + elt;
-        a = *reinterpret_cast<const Float4*>(p);
-        b = *reinterpret_cast<const Float4*>(p + 4);
-    }
-    __device__ __forceinline__ void get(float x[8]) const
-    {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) { x[i] = a.f[i]; x[4 + i] = b.f[i]; }
-    }
-};
 
 // One-dimensional grid over the (row slice, column chunk) pairs, column chunks of 8 panels varying fastest.
 // Workgroup ids are dealt round-robin to the 8 XCDs, and the pass runs 12 - 23 % faster (K = 8192 / 4096;
@@ -255,7 +132,8 @@ __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
                         if (valid[j]) {
                             float x[8];
                             raw[b][j].get(x);
-                            act_unit<MODE, SUMS>(x, is[j], p, d, csf[j], csi[j], rs, big, st);
+                            const uint2 w = act_unit<MODE, SUMS>(x, is[j], p, csf[j], csi[j], rs, big, st);
+                            if (!SUMS && d) __builtin_nontemporal_store(v2u{w.x, w.y}, reinterpret_cast<v2u*>(d));   // (sums only: no code buffer)
                         } else if (pad[j] && d) {
                             *reinterpret_cast<uint2*>(d) = make_uint2(0u, 0u);
                         }
@@ -374,31 +252,16 @@ __global__ __launch_bounds__(kQrBlock) void quant_act_rows(
         for (int i = 0; i < ROWS; ++i)
             if (i < nrows) raw[i].load(X, (r0 + i) * ldx + u * 8);
         float is[8];
-        bool fast = p.fast;
-        float is_max = 0.0f;
         const Float4 a = *reinterpret_cast<const Float4*>(inv_s + u * 8), b = *reinterpret_cast<const Float4*>(inv_s + u * 8 + 4);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            is[i] = i < 4 ? a.f[i & 3] : b.f[i & 3];
-            if (!(fabsf(is[i]) < 1.0e12f)) fast = false;
-            is_max = fmaxf(is_max, fabsf(is[i]));
-        }
-        // the same choice of quotient as the tiled form, per wavefront
-        const bool screen = __all(fast && p.screen && 65600.0f * is_max * p.rstep < 16777216.0f);
-        const bool exact = __all(fast);
-        float csf[8];
-        int csi[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) { csf[i] = 0.0f; csi[i] = 0; }
+        for (int i = 0; i < 4; ++i) { is[i] = a.f[i]; is[4 + i] = b.f[i]; }
 #pragma unroll
         for (int i = 0; i < ROWS; ++i) {
             if (i >= nrows) break;
             float x[8];
             raw[i].get(x);
-            if (!F16 && p.screen) act_unit<3>(x, is, p, d + i * kPanel, csf, csi, rs[i], big, st);
-            else if (F16 && screen) act_unit<2>(x, is, p, d + i * kPanel, csf, csi, rs[i], big, st);
-            else if (F16 && exact) act_unit<1>(x, is, p, d + i * kPanel, csf, csi, rs[i], big, st);
-            else act_unit<0>(x, is, p, d + i * kPanel, csf, csi, rs[i], big, st);
+            const uint2 w = act_unit_any<F16>(x, is, p, rs[i], big, st);
+            __builtin_nontemporal_store(v2u{w.x, w.y}, reinterpret_cast<v2u*>(d + i * kPanel));
         }
     }
     if (big >= 16777216.0f) st |= AWEQ_ST_BIGQUOT;
