@@ -35,8 +35,8 @@ constexpr int kQaWaves = kQaBlock / kWave;
 constexpr int kQaVpt = 2;                               // panels (units per thread per row) per wavefront
 constexpr int kQaPanels = kQaWaves * kQaVpt;            // 8 panels = 512 columns per block
 constexpr int kQaMaxRows = 512;                         // rows per block (LDS row-sum slots)
-constexpr int kQaRowBatch = 4;                          // groups of 8 rows in flight per thread
-constexpr int kQaRowsPerIter = 8 * kQaRowBatch;
+constexpr int kQaSliceRows = 32;                        // slices are whole multiples of this
+constexpr int64_t kCacheBytes = 256ll << 20;             // memory-side cache
 constexpr unsigned kQaXcds = 8;                         // workgroup id % 8 names the XCD a workgroup runs on
 
 // One-dimensional grid over the (row slice, column chunk) pairs, column chunks of 8 panels varying fastest.
@@ -51,7 +51,11 @@ constexpr unsigned kQaXcds = 8;                         // workgroup id % 8 name
 // panels, so a lane keeps the column sums of its 16 columns over the rows it visits.
 // SUMS: neither codes nor row sums are asked for (a calibration without the forward): 14331 x 11008 binary16 72.3 -> 66.3 us
 // without packing the codes, 7419 x 4096 binary32 29.5.
-template <bool F16, bool SUMS>
+// KEEP: the codes are stored through the caches for the GEMM that reads them next (rule and figures at the launch).
+// A thread has kBatch groups of 8 rows in flight; the first are requested ahead of Step, Z and the scales, the next after the
+// last of a group has been consumed (8192 x 4096 36.6 -> 35.4 us, 262144 x 8192 1209 -> 1199; two groups ahead of four costs
+// binary32 1 % of a whole 2048 x 512 calibration, so it keeps four).
+template <bool F16, bool SUMS, bool KEEP>
 __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
     const void* __restrict__ X, int64_t T, int64_t K, int64_t ldx, const float* __restrict__ inv_s,
     const float* __restrict__ act_step, const int32_t* __restrict__ act_zero, int8_t* __restrict__ xq,
@@ -69,7 +73,6 @@ __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
     const int64_t r0 = slice * rows_per_block;
     const int nrows = (int)min((int64_t)rows_per_block, T - r0);
     const int64_t np = panel_count(K);
-    const ActParams p = quot_params(*act_step, *act_zero);
 
     const int64_t panel0 = (int64_t)chunk * kQaPanels + wave * kQaVpt;
     const int col0 = (int)(panel0 * kPanel) + c8 * 8;                      // K <= 2^31 - 1 columns
@@ -77,13 +80,27 @@ __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
     const int64_t dst_step = T * kPanel;                                   // to the next panel
     const char* const src0 = reinterpret_cast<const char*>(X) + (r0 * ldx + col0) * (F16 ? 2 : 4);
     bool valid[kQaVpt], pad[kQaVpt];
+#pragma unroll
+    for (int j = 0; j < kQaVpt; ++j) {
+        valid[j] = col0 + j * kPanel < K;
+        pad[j] = !valid[j] && panel0 + j < np;  // zero fill of the last panel
+    }
+    constexpr int kBatch = F16 ? 2 : 4, kRowsPerIter = 8 * kBatch;
+    RawUnit<F16> raw[kBatch][kQaVpt];
+    auto request = [&](int b, int j, int row) {
+        if (row < nrows && valid[j]) raw[b][j].load(src0, (int64_t)row * ldx + j * kPanel);
+    };
+#pragma unroll
+    for (int b = 0; b < kBatch; ++b)
+#pragma unroll
+        for (int j = 0; j < kQaVpt; ++j) request(b, j, 8 * b + rsub);
+
+    const ActParams p = quot_params(*act_step, *act_zero);
     float is[kQaVpt][8];
     bool fast_thread = p.fast;
     float is_max = 0.0f;
 #pragma unroll
     for (int j = 0; j < kQaVpt; ++j) {
-        valid[j] = col0 + j * kPanel < K;
-        pad[j] = !valid[j] && panel0 + j < np;  // zero fill of the last panel
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             is[j][i] = valid[j] ? inv_s[col0 + j * kPanel + i] : 1.0f;
@@ -110,17 +127,9 @@ __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
 
     auto rows_loop = [&](auto mode_c) {
         constexpr int MODE = decltype(mode_c)::value;
-        for (int rb = 0; rb < nrows; rb += kQaRowsPerIter) {
-            RawUnit<F16> raw[kQaRowBatch][kQaVpt];
+        for (int rb = 0; rb < nrows; rb += kRowsPerIter) {
 #pragma unroll
-            for (int b = 0; b < kQaRowBatch; ++b)
-#pragma unroll
-                for (int j = 0; j < kQaVpt; ++j) {
-                    const int row = rb + 8 * b + rsub;
-                    if (row < nrows && valid[j]) raw[b][j].load(src0, (int64_t)row * ldx + j * kPanel);
-                }
-#pragma unroll
-            for (int b = 0; b < kQaRowBatch; ++b) {
+            for (int b = 0; b < kBatch; ++b) {
                 const int row = rb + 8 * b + rsub;
                 const bool row_ok = row < nrows;
                 int rs = 0;
@@ -133,7 +142,10 @@ __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
                             float x[8];
                             raw[b][j].get(x);
                             const uint2 w = act_unit<MODE, SUMS>(x, is[j], p, csf[j], csi[j], rs, big, st);
-                            if (!SUMS && d) __builtin_nontemporal_store(v2u{w.x, w.y}, reinterpret_cast<v2u*>(d));   // (sums only: no code buffer)
+                            if (!SUMS && d) {   // (sums only: no code buffer)
+                                if constexpr (KEEP) *reinterpret_cast<v2u*>(d) = v2u{w.x, w.y};
+                                else __builtin_nontemporal_store(v2u{w.x, w.y}, reinterpret_cast<v2u*>(d));
+                            }
                         } else if (pad[j] && d) {
                             *reinterpret_cast<uint2*>(d) = make_uint2(0u, 0u);
                         }
@@ -144,6 +156,10 @@ __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
                     if (row_ok && c8 == 0) lds_rs[row][wave] = rs;
                 }
             }
+#pragma unroll
+            for (int b = 0; b < kBatch; ++b)
+#pragma unroll
+                for (int j = 0; j < kQaVpt; ++j) request(b, j, rb + kRowsPerIter + 8 * b + rsub);
         }
     };
     if constexpr (F16) {
@@ -223,7 +239,9 @@ __global__ __launch_bounds__(kQaMergeCols * kQaMergeParts) void quant_act_merge(
 
 // ---- row form: a block owns ROWS whole rows, so their code sums are complete inside it and no partial buffer or merge
 // is needed.  For calls that do not ask for column sums (a forward with a calibrated scale).  Small calls are bound by
-// the launch and one round trip to memory: one launch instead of two (the figures are at the dispatch below).
+// the launch and the round trips to memory: one launch instead of two (the figures are at the dispatch below), and a row's
+// next unit is requested while this one is quantised (with the stores that stay in the caches, whole int8 forward, us:
+// 300 tokens 4096 x 11008 46.4 -> 40.5, 2048 tokens 99.2 -> 95.6, 4096 tokens 11008 x 4096 182.6 -> 178.6).
 constexpr int kQrBlock = 512;
 template <bool F16, int ROWS>
 __global__ __launch_bounds__(kQrBlock) void quant_act_rows(
@@ -234,8 +252,23 @@ __global__ __launch_bounds__(kQrBlock) void quant_act_rows(
     __shared__ int s_rs[kQrBlock / kWave][ROWS];
     const int64_t r0 = (int64_t)blockIdx.x * ROWS;
     const int nrows = (int)min((int64_t)ROWS, T - r0);
-    const ActParams p = quot_params(*act_step, *act_zero);
     const int64_t units = K / 8, padded = panel_count(K) * (kPanel / 8);
+    // the first unit of every row is requested ahead of Step and Z, the next one as soon as a unit has been consumed
+    RawUnit<F16> raw[ROWS];
+    Float4 isa = {}, isb = {};
+    auto request = [&](int i, int64_t u) {
+        if (u < units && i < nrows) raw[i].load(X, (r0 + i) * ldx + u * 8);
+    };
+    auto request_is = [&](int64_t u) {
+        if (u < units) {
+            isa = *reinterpret_cast<const Float4*>(inv_s + u * 8);
+            isb = *reinterpret_cast<const Float4*>(inv_s + u * 8 + 4);
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) request(i, threadIdx.x);
+    request_is(threadIdx.x);
+    const ActParams p = quot_params(*act_step, *act_zero);
     uint32_t st = 0;
     float big = 0.0f;
     int rs[ROWS];
@@ -247,21 +280,18 @@ __global__ __launch_bounds__(kQrBlock) void quant_act_rows(
             for (int i = 0; i < nrows; ++i) *reinterpret_cast<uint2*>(d + i * kPanel) = make_uint2(0u, 0u);
             break;
         }
-        RawUnit<F16> raw[ROWS];
-#pragma unroll
-        for (int i = 0; i < ROWS; ++i)
-            if (i < nrows) raw[i].load(X, (r0 + i) * ldx + u * 8);
         float is[8];
-        const Float4 a = *reinterpret_cast<const Float4*>(inv_s + u * 8), b = *reinterpret_cast<const Float4*>(inv_s + u * 8 + 4);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) { is[i] = a.f[i]; is[4 + i] = b.f[i]; }
+        for (int i = 0; i < 4; ++i) { is[i] = isa.f[i]; is[4 + i] = isb.f[i]; }
+        request_is(u + kQrBlock);
 #pragma unroll
         for (int i = 0; i < ROWS; ++i) {
             if (i >= nrows) break;
             float x[8];
             raw[i].get(x);
+            request(i, u + kQrBlock);
             const uint2 w = act_unit_any<F16>(x, is, p, rs[i], big, st);
-            __builtin_nontemporal_store(v2u{w.x, w.y}, reinterpret_cast<v2u*>(d + i * kPanel));
+            *reinterpret_cast<v2u*>(d + i * kPanel) = v2u{w.x, w.y};
         }
     }
     if (big >= 16777216.0f) st |= AWEQ_ST_BIGQUOT;
@@ -293,7 +323,7 @@ static QaPlan qa_plan(int64_t T, int64_t K)
     p.chunks = (int)cdiv(panel_count(K), kQaPanels);
     int64_t slices = cdiv(8192, p.chunks);
     int64_t rpb = cdiv(T, slices);
-    rpb = cdiv(rpb, kQaRowsPerIter) * kQaRowsPerIter;
+    rpb = cdiv(rpb, kQaSliceRows) * kQaSliceRows;
     if (rpb > kQaMaxRows) rpb = kQaMaxRows;
     p.rpb = rpb;
     p.slices = cdiv(T, rpb);
@@ -332,9 +362,13 @@ int launch_quant_act(const void* X, aweq_dtype dt, int64_t T, int64_t K, int64_t
     const unsigned pairs = (unsigned)(p.slices * p.chunks);
     const unsigned grid = (unsigned)(cdiv(pairs, kQaXcds) * kQaXcds);
     const bool sums = !xq && !rowsum_x;
-#define AWEQ_QA(F, S) quant_act_kernel<F, S><<<grid, kQaBlock, 0, st>>>(X, T, K, ldx, inv_s, act_step, act_zero, xq, rs_out, colsum_part, (int)p.rpb, p.chunks, pairs, status)
-    if (dt == AWEQ_F16) { if (sums) AWEQ_QA(true, true); else AWEQ_QA(true, false); }
-    else { if (sums) AWEQ_QA(false, true); else AWEQ_QA(false, false); }
+    // codes that fit the memory-side cache are stored through the caches, where the GEMM finds them; more would only evict each
+    // other (int8 forward, us, non-temporal -> cached: 16384 tokens 4096 x 11008 (180 MB) 663 -> 650, 4096 x 16384 (268 MB)
+    // 979 -> 967, 12000 tokens 8192 x 16384 1306 -> 1307; the pass alone at 262144 x 8192 (2.1 GB) 1188 -> 1268)
+    const bool keep = xq && (int64_t)panel_count(K) * kPanel * T <= kCacheBytes;
+#define AWEQ_QA(F, S, P) quant_act_kernel<F, S, P><<<grid, kQaBlock, 0, st>>>(X, T, K, ldx, inv_s, act_step, act_zero, xq, rs_out, colsum_part, (int)p.rpb, p.chunks, pairs, status)
+    if (dt == AWEQ_F16) { if (sums) AWEQ_QA(true, true, false); else if (keep) AWEQ_QA(true, false, true); else AWEQ_QA(true, false, false); }
+    else { if (sums) AWEQ_QA(false, true, false); else if (keep) AWEQ_QA(false, false, true); else AWEQ_QA(false, false, false); }
 #undef AWEQ_QA
     const int col_blocks = colsum_xq ? (int)cdiv(K, kQaMergeCols) : 0;
     const int64_t row_blocks = (rowsum_x && multi) ? cdiv(T, kQaMergeCols * kQaMergeParts) : 0;
