@@ -22,6 +22,7 @@ inline int launch_status() { return hipGetLastError() == hipSuccess ? AWEQ_OK : 
 inline size_t dtype_size(aweq_dtype dt) { return dt == AWEQ_F32 ? 4 : (dt == AWEQ_F16 ? 2 : 1); }
 
 constexpr int kXcdCount = 8;   // workgroup ids are dealt round-robin to the XCDs: id % 8 names the XCD
+constexpr int64_t kCacheBytes = 256ll << 20;   // memory-side cache
 
 // ---------------------------------------------------------------- launch helpers (host)
 // compute units of the current device, asked once per device

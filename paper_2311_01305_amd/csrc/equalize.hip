@@ -128,7 +128,9 @@ __global__ __launch_bounds__(256) void fold_weight(const void* __restrict__ Wv, 
         if constexpr (F16) {
             const _Float16* W = reinterpret_cast<const _Float16*>(Wv);
             _Float16* O = reinterpret_cast<_Float16*>(Ov);
-            Half8 v = *reinterpret_cast<const Half8*>(W + n * ldw + col);
+            // (last read of W: non-temporal, the folded weight and its codes are read next)
+            typedef int v4i_ __attribute__((ext_vector_type(4)));
+            const Half8 v = __builtin_bit_cast(Half8, __builtin_nontemporal_load(reinterpret_cast<const v4i_*>(W + n * ldw + col)));
             Half8 o;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {

@@ -36,7 +36,6 @@ constexpr int kQaVpt = 2;                               // panels (units per thr
 constexpr int kQaPanels = kQaWaves * kQaVpt;            // 8 panels = 512 columns per block
 constexpr int kQaMaxRows = 512;                         // rows per block (LDS row-sum slots)
 constexpr int kQaSliceRows = 32;                        // slices are whole multiples of this
-constexpr int64_t kCacheBytes = 256ll << 20;             // memory-side cache
 constexpr unsigned kQaXcds = 8;                         // workgroup id % 8 names the XCD a workgroup runs on
 
 // One-dimensional grid over the (row slice, column chunk) pairs, column chunks of 8 panels varying fastest.

@@ -44,19 +44,27 @@ inline size_t stats_ws_bytes(int64_t rows, int64_t K)
     return (size_t)s * (size_t)K * (sizeof(float) * 2 + sizeof(double)) + 16;   // (16: part of the size callers were always asked for)
 }
 
-// every byte of the matrix is read exactly once: non-temporal loads (7 - 10 % over plain ones here)
+constexpr int64_t kKeepBytes = kCacheBytes * 3 / 8;
+
+// Every byte of the matrix is read exactly once by this pass.  KEEP: through the caches, for the pass that reads the same matrix next
+// (rule and figures at the launch); otherwise non-temporal.
+template <bool KEEP>
 __device__ __forceinline__ Half8 load_once(const _Float16* p)
 {
     typedef int v4i_ __attribute__((ext_vector_type(4)));
-    return __builtin_bit_cast(Half8, __builtin_nontemporal_load(reinterpret_cast<const v4i_*>(p)));
+    const v4i_* const q = reinterpret_cast<const v4i_*>(p);
+    return __builtin_bit_cast(Half8, KEEP ? *q : __builtin_nontemporal_load(q));
 }
+template <bool KEEP>
 __device__ __forceinline__ Float4 load_once(const float* p)
 {
     typedef float v4f_ __attribute__((ext_vector_type(4)));
-    return __builtin_bit_cast(Float4, __builtin_nontemporal_load(reinterpret_cast<const v4f_*>(p)));
+    const v4f_* const q = reinterpret_cast<const v4f_*>(p);
+    return __builtin_bit_cast(Float4, KEEP ? *q : __builtin_nontemporal_load(q));
 }
 
 // ---- binary16: 8 columns per lane
+template <bool KEEP>
 __global__ __launch_bounds__(kStatsBlock) void col_stats_partial_f16(
     const _Float16* __restrict__ M, int64_t rows, int64_t K, int64_t ld, int64_t rows_per_slice,
     float* __restrict__ pmin, float* __restrict__ pmax, double* __restrict__ psum)
@@ -82,7 +90,7 @@ __global__ __launch_bounds__(kStatsBlock) void col_stats_partial_f16(
             Half8 v[kRowBatch];
 #pragma unroll
             for (int j = 0; j < kRowBatch; ++j)
-                v[j] = load_once(base + (r + (int64_t)j * kStatsWaves) * ld);
+                v[j] = load_once<KEEP>(base + (r + (int64_t)j * kStatsWaves) * ld);
             float part[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
             for (int j = 0; j < kRowBatch; ++j)
@@ -98,7 +106,7 @@ __global__ __launch_bounds__(kStatsBlock) void col_stats_partial_f16(
             for (int i = 0; i < 8; ++i) sum[i] += (double)part[i];
         }
         for (; r < r_end; r += kStatsWaves) {
-            Half8 v = load_once(base + r * ld);
+            Half8 v = load_once<KEEP>(base + r * ld);
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 mn[i] = hmin2(mn[i], v.h[i]);
@@ -143,6 +151,7 @@ __global__ __launch_bounds__(kStatsBlock) void col_stats_partial_f16(
 }
 
 // ---- binary32: 4 columns per lane, every element added in fp64
+template <bool KEEP>
 __global__ __launch_bounds__(kStatsBlock) void col_stats_partial_f32(
     const float* __restrict__ M, int64_t rows, int64_t K, int64_t ld, int64_t rows_per_slice,
     float* __restrict__ pmin, float* __restrict__ pmax, double* __restrict__ psum)
@@ -163,7 +172,7 @@ __global__ __launch_bounds__(kStatsBlock) void col_stats_partial_f32(
             Float4 v[kRowBatch];
 #pragma unroll
             for (int j = 0; j < kRowBatch; ++j)
-                v[j] = load_once(base + (r + (int64_t)j * kStatsWaves) * ld);
+                v[j] = load_once<KEEP>(base + (r + (int64_t)j * kStatsWaves) * ld);
 #pragma unroll
             for (int j = 0; j < kRowBatch; ++j)
 #pragma unroll
@@ -174,7 +183,7 @@ __global__ __launch_bounds__(kStatsBlock) void col_stats_partial_f32(
                 }
         }
         for (; r < r_end; r += kStatsWaves) {
-            Float4 v = load_once(base + r * ld);
+            Float4 v = load_once<KEEP>(base + r * ld);
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 mn[i] = fminf(mn[i], v.f[i]);
@@ -306,12 +315,16 @@ static int run_calib_stats(const void* M, aweq_dtype dt, int64_t rows, int64_t K
     float* pmin = reinterpret_cast<float*>(psum + (size_t)plan.slices * K);
     float* pmax = pmin + (size_t)plan.slices * K;
     dim3 grid(plan.col_chunks, plan.slices);
-    if (dt == AWEQ_F16)
-        col_stats_partial_f16<<<grid, kStatsBlock, 0, st>>>(reinterpret_cast<const _Float16*>(M), rows, K, ld,
-                                                             plan.rows_per_slice, pmin, pmax, psum);
-    else
-        col_stats_partial_f32<<<grid, kStatsBlock, 0, st>>>(reinterpret_cast<const float*>(M), rows, K, ld,
-                                                             plan.rows_per_slice, pmin, pmax, psum);
+    // A matrix that fits the memory-side cache together with what the next pass over it writes (the folded weight and its codes: 2.5
+    // times its size) is read through the caches, where that pass finds it: fold + quantise 4096 x 11008 (90 MB) 51.0 -> 42.9 us,
+    // the fold alone 29.9 -> 27.7, this pass 17.2 -> 16.0 there; seven sequences through the calibration 249.9 -> 239.8.  On matrices in
+    // neither cache the two kinds of loads take the same up to 90 MB (25.9 / 26.1 us with the merge), beyond it plain ones
+    // are slower (134 MB 35.0 -> 36.1, 262 MB 53.1 -> 55.7).
+    const bool keep = rows * K * (int64_t)dtype_size(dt) <= kKeepBytes;
+#define AWEQ_CS(F, E, P) col_stats_partial_##F<P><<<grid, kStatsBlock, 0, st>>>(reinterpret_cast<const E*>(M), rows, K, ld, plan.rows_per_slice, pmin, pmax, psum)
+    if (dt == AWEQ_F16) { if (keep) AWEQ_CS(f16, _Float16, true); else AWEQ_CS(f16, _Float16, false); }
+    else { if (keep) AWEQ_CS(f32, float, true); else AWEQ_CS(f32, float, false); }
+#undef AWEQ_CS
     col_stats_merge<<<(unsigned)cdiv(K, kMergeCols), kMergeCols * kMergeParts, 0, st>>>(
         pmin, pmax, psum, plan.slices, K, rows, cmin, cmax, csum, count, accumulate, status, finalize, r);
     if (finalize) col_stats_finish<<<(unsigned)cdiv(p ? K : 1, kFinishBlock), kFinishBlock, 0, st>>>(pmin, pmax, K, r, R, p);
