@@ -20,6 +20,7 @@
  *     anything is launched (bad pointer, shape, dtype, alignment, workspace);
  *   - numeric conditions met on the device are OR-ed into the optional device word
  *     `status` (AWEQ_ST_* bits); inputs are expected to be finite;
+ *   - an output must not overlap an input, another output or the workspace, except where an entry point says so;
  *   - calls on different streams must not share output or workspace buffers.
  */
 #ifndef AWEQ_H
@@ -207,6 +208,8 @@ int aweq_quant_act(const void* X, aweq_dtype dt, int64_t T, int64_t K, int64_t l
  * w_group = 0: step_w[N] / zero_w[N] hold one entry per output channel (stage 3 with group = 0);
  * w_group = -1: step_w[1] / zero_w[1], one for the tensor (stage 3 with group = -1, the paper's
  * per-tensor setting, Sec. 3); rowsum_w[N] is per output channel in both cases.
+ * With X F16 / F32, out_i32, out_deq and colsum_acc may overlap X and inv_s: the quantizer has read them before the GEMM
+ * stores anything.
  * ws: the workspace of stage 4a when X is F16 / F32 (aweq_workspace_size(AWEQ_OP_W8A8_GEMM, T, K, N));
  * not needed (NULL) for x_dt = I8. */
 int aweq_w8a8_gemm(const void* X, aweq_dtype x_dt, int64_t T, int64_t K, int64_t ldx,

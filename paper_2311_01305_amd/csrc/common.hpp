@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include <atomic>
+#include <initializer_list>
 #include <mutex>
 #include <set>
 #include <utility>
@@ -20,6 +21,26 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline int launch_status() { return hipGetLastError() == hipSuccess ? AWEQ_OK : AWEQ_ERR_LAUNCH; }
 inline size_t dtype_size(aweq_dtype dt) { return dt == AWEQ_F32 ? 4 : (dt == AWEQ_F16 ? 2 : 1); }
+
+// bytes a buffer of a call occupies (from nullptr: none)
+struct Span {
+    const void* p;
+    int64_t bytes;
+};
+inline Span matrix_span(const void* p, int64_t rows, int64_t cols, int64_t pitch, size_t elt)
+{
+    return {p, ((rows - 1) * pitch + cols) * (int64_t)elt};
+}
+// some buffer of `a` shares a byte with one of `b`
+inline bool overlap(std::initializer_list<Span> a, std::initializer_list<Span> b)
+{
+    for (const Span& x : a)
+        for (const Span& y : b) {
+            const uintptr_t px = reinterpret_cast<uintptr_t>(x.p), py = reinterpret_cast<uintptr_t>(y.p);
+            if (px && py && px < py + (uintptr_t)y.bytes && py < px + (uintptr_t)x.bytes) return true;
+        }
+    return false;
+}
 
 constexpr int kXcdCount = 8;   // workgroup ids are dealt round-robin to the XCDs: id % 8 names the XCD
 constexpr int64_t kCacheBytes = 256ll << 20;   // memory-side cache

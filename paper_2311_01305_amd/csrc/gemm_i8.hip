@@ -922,9 +922,12 @@ extern "C" int aweq_w8a8_gemm(const void* X, aweq_dtype x_dt, int64_t T, int64_t
     const MidPlan mid = plan_mid(T, N);
     // one to four tokens: the few-token form quantises them itself, one launch instead of two (us per call, one / four tokens:
     // 4096 x 4096 9.2 -> 7.9 / 9.4 -> 9.3, 11008 x 4096 14.8 -> 12.5 / 15.2 -> 14.2, 1536 x 2048 8.5 -> 6.0 / 8.5 -> 7.0; no more than
-    // 16 KiB of codes: every workgroup repeats the work)
+    // 16 KiB of codes: every workgroup repeats the work).  Not where an output lies over what the quantizer reads: a workgroup would
+    // store it while another still reads; the quantizer's own launch is over before the GEMM stores anything.
     const bool own_quant = fast_ok && x_dt != AWEQ_I8 && !colsum_xq && T <= kQuantTokens && T * panel_count(K) * kPanel <= kQuantFewBytes && aligned16(inv_s) &&
-                           few.cost <= mid.cost && few.cost < kTiledRoundCost * tiled_cost;
+                           few.cost <= mid.cost && few.cost < kTiledRoundCost * tiled_cost &&
+                           !overlap({matrix_span(out_i32, T, N, ldo, 4), matrix_span(out_deq, T, N, ldo, dtype_size(out_dt)), {colsum_acc, N * 8}, {rowsum_x, T * 4}},
+                                    {matrix_span(X, T, K, ldx, dtype_size(x_dt)), {inv_s, K * 4}, {act_step, 4}, {act_zero, 4}});
     if (!own_quant) {
         const int rc = quantise();
         if (rc != AWEQ_OK) return rc;

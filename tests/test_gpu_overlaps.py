@@ -1,0 +1,63 @@
+"""Entry points whose outputs lie over their inputs, as the header allows: the results equal those of the same call on buffers
+of their own, bit for bit."""
+import numpy as np
+import pytest
+
+from conftest import to_panels
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def B():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2311_01305_amd import binding
+    binding.load_library()
+    return binding
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+
+
+@pytest.mark.parametrize("dtype", [np.float16, np.float32])
+@pytest.mark.parametrize("N,K", [(64, 64), (4096, 4096), (16384, 1024), (260, 2112)])
+def test_forward_stores_over_its_input(B, dtype, N, K):
+    """aweq_w8a8_gemm with its output over X or inv_s, on both sides of the four tokens whose launch may quantise them itself."""
+    rng = np.random.default_rng(N + K)
+    dt = B.AWEQ_F16 if dtype == np.float16 else B.AWEQ_F32
+    wq = rng.integers(-128, 128, (N, K), dtype=np.int8)
+    dw, rw = dev(to_panels(wq)), dev(wq.astype(np.int64).sum(1).astype(np.int32))
+    sw, zw, bias = dev(rng.uniform(1e-3, 2e-2, N).astype(np.float32)), dev(rng.integers(0, 256, N).astype(np.int32)), dev(rng.standard_normal(N).astype(np.float32))
+    ds, dz = dev(np.float32([0.0371])), dev(np.int32([117]))
+    for T in (1, 3, 4, 5):
+        X = (rng.standard_normal((T, K)) * 3).astype(dtype)
+        inv_s = rng.uniform(0.2, 2.0, K).astype(np.float32)
+        size = X.itemsize
+        for kind in ("deq", "i32", "deq over inv_s"):
+            print(f"[gpu-overlap] forward {dtype.__name__} T={T} N={N} K={K} {kind}", flush=True)
+            osize = 4 if kind == "i32" else size
+            odt = torch.int32 if kind == "i32" else torch.float16 if size == 2 else torch.float32
+            ws = torch.empty(max(16, B.aweq_workspace_size(B.OP_W8A8_GEMM, T, K, N)), dtype=torch.uint8, device=DEV)
+
+            def run(apart):
+                xs, iss = torch.empty(max(T * K * size, T * N * osize), dtype=torch.uint8, device=DEV), torch.empty(max(K * 4, T * N * osize), dtype=torch.uint8, device=DEV)
+                dX, di = xs[:T * K * size].view(torch.float16 if size == 2 else torch.float32), iss[:K * 4].view(torch.float32)
+                dX.copy_(dev(X.reshape(-1)))
+                di.copy_(dev(inv_s))
+                home = torch.empty(T * N * osize, dtype=torch.uint8, device=DEV) if apart else (iss if kind == "deq over inv_s" else xs)
+                out = home[:T * N * osize].view(odt)
+                xq, rs = torch.zeros(B.aweq_panel_bytes(T, K), dtype=torch.int8, device=DEV), torch.zeros(T, dtype=torch.int32, device=DEV)
+                cs, st = torch.zeros(N, dtype=torch.int64, device=DEV), torch.zeros(1, dtype=torch.int32, device=DEV)
+                B.aweq_w8a8_gemm(dX, dt, T, K, K, di, ds, dz, xq, rs, None, dw, N, sw, zw, 0, rw, bias, out if kind == "i32" else None,
+                                 None if kind == "i32" else out, dt, N, cs, ws, st)
+                return out.clone(), xq, rs, cs, st
+
+            want = run(True)
+            for _ in range(5):
+                for a, b in zip(want, run(False)):
+                    assert torch.equal(a, b), (T, kind)
