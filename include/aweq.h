@@ -185,7 +185,7 @@ int aweq_fold_quant_weight(const void* W, aweq_dtype dt, int64_t N, int64_t K, i
  * (aweq_workspace_size(AWEQ_OP_QUANT_ACT, T, K, 0) bytes; needed when colsum_xq is asked for, or
  * rowsum_x with K > 512) and a merge kernel.  AWEQ_ST_BIGQUOT: some |X_hat / Step| reached 2^24
  * (Step and Z not from this data); the quotient is then rounded, saturated at +-2^30, and clamped
- * as Eq. 1 says. */
+ * as Eq. 1 says.  colsum_xq, and with K > 512 rowsum_x, may overlap X and inv_s: the merge kernel writes them. */
 int aweq_quant_act(const void* X, aweq_dtype dt, int64_t T, int64_t K, int64_t ldx,
                    const float* inv_s, const float* act_step, const int32_t* act_zero,
                    int8_t* xq, int32_t* rowsum_x, int64_t* colsum_xq,
@@ -209,7 +209,7 @@ int aweq_quant_act(const void* X, aweq_dtype dt, int64_t T, int64_t K, int64_t l
  * w_group = -1: step_w[1] / zero_w[1], one for the tensor (stage 3 with group = -1, the paper's
  * per-tensor setting, Sec. 3); rowsum_w[N] is per output channel in both cases.
  * With X F16 / F32, out_i32, out_deq and colsum_acc may overlap X and inv_s: the quantizer has read them before the GEMM
- * stores anything.
+ * stores anything; colsum_xq and rowsum_x as in aweq_quant_act.
  * ws: the workspace of stage 4a when X is F16 / F32 (aweq_workspace_size(AWEQ_OP_W8A8_GEMM, T, K, N));
  * not needed (NULL) for x_dt = I8. */
 int aweq_w8a8_gemm(const void* X, aweq_dtype x_dt, int64_t T, int64_t K, int64_t ldx,

@@ -3,7 +3,7 @@ of their own, bit for bit."""
 import numpy as np
 import pytest
 
-from conftest import to_panels
+from conftest import from_panels, to_panels
 
 torch = pytest.importorskip("torch")
 
@@ -61,3 +61,42 @@ def test_forward_stores_over_its_input(B, dtype, N, K):
             for _ in range(5):
                 for a, b in zip(want, run(False)):
                     assert torch.equal(a, b), (T, kind)
+
+
+@pytest.mark.parametrize("dtype", [np.float16, np.float32])
+@pytest.mark.parametrize("T", [1, 4, 300, 4097])
+def test_row_sums_over_the_activation(B, orc, dtype, T):
+    """aweq_quant_act and aweq_w8a8_gemm with rowsum_x, and colsum_xq, over X or inv_s (several column chunks: the merge writes them)."""
+    rng = np.random.default_rng(T)
+    K, N = 1096, 64
+    dt, tdt = (B.AWEQ_F16, torch.float16) if dtype == np.float16 else (B.AWEQ_F32, torch.float32)
+    X, inv_s = (rng.standard_normal((T, K)) * 3).astype(dtype), rng.uniform(0.2, 2.0, K).astype(np.float32)
+    ref = orc.quant_act(X, inv_s, np.float32(0.0371), 117)
+    ds, dz = dev(np.float32([0.0371])), dev(np.int32([117]))
+    wq = rng.integers(-128, 128, (N, K), dtype=np.int8)
+    ws = torch.empty(B.aweq_workspace_size(B.OP_W8A8_GEMM, T, K, N), dtype=torch.uint8, device=DEV)
+    for over in ("X", "inv_s"):
+        for sums in (False, True):
+            for gemm in (False, True):
+                print(f"[gpu-overlap] row sums {dtype.__name__} T={T} over {over} sums={sums} gemm={gemm}", flush=True)
+                bx, bs = torch.empty(X.nbytes + 8 * K, dtype=torch.uint8, device=DEV), torch.empty(8 * max(T, K), dtype=torch.uint8, device=DEV)
+                dX, di = bx[:X.nbytes].view(tdt), bs[:4 * K].view(torch.float32)
+                dX.copy_(dev(X.reshape(-1)))
+                di.copy_(dev(inv_s))
+                home = bx if over == "X" else bs
+                rs = home[:4 * T].view(torch.int32)
+                cs = torch.zeros(K, dtype=torch.int64, device=DEV) if sums else None
+                if sums and over == "X":
+                    cs, rs = home[:8 * K].view(torch.int64), torch.zeros(T, dtype=torch.int32, device=DEV)
+                xq = torch.zeros(B.aweq_panel_bytes(T, K), dtype=torch.int8, device=DEV)
+                if gemm:
+                    oi = torch.zeros((T, N), dtype=torch.int32, device=DEV)
+                    B.aweq_w8a8_gemm(dX, dt, T, K, K, di, ds, dz, xq, rs, cs, dev(to_panels(wq)), N, None, None, 0, None, None, oi, None, B.AWEQ_F16, N,
+                                     None, ws)
+                    assert np.array_equal(oi.cpu().numpy(), orc.gemm_i8(ref["xq"], wq))
+                else:
+                    B.aweq_quant_act(dX, dt, T, K, K, di, ds, dz, xq, rs, cs, ws)
+                torch.cuda.synchronize()
+                assert np.array_equal(from_panels(xq.cpu().numpy(), T, K), ref["xq"]) and np.array_equal(rs.cpu().numpy(), ref["rowsum_x"])
+                if sums:
+                    assert np.array_equal(cs.cpu().numpy(), ref["colsum_xq"])
