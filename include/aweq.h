@@ -140,7 +140,8 @@ int aweq_calib_stats_static(const void* M, aweq_dtype dt, int64_t rows, int64_t 
  * xhat_range[2] = {min, max}, its mean mu_xhat[K] = (xsum / count) * inv_s and the static
  * int8 activation quantizer derived from that range by Eq. 2 (act_step[1], act_zero[1])
  * are written instead.  prev_scale[K] (nullable) is multiplied by inv_s so the caller can
- * fuse diag(s)^-1 into the preceding block.  mu_xhat / xsum nullable together. */
+ * fuse diag(s)^-1 into the preceding block.  mu_xhat / xsum nullable together.  s, inv_s, mu_xhat and prev_scale may
+ * each replace xmin, xmax, wmin or wmax (the same address: channel k over channel k). */
 int aweq_equalize(const float* xmin, const float* xmax, const double* xsum, uint64_t count,
                   const float* wmin, const float* wmax, int64_t K, int enable_awe,
                   float* s, float* inv_s,

@@ -5,11 +5,12 @@ namespace aweq {
 
 // K-vector work: s, inv_s, equalised activation mean, optional prev_scale *= inv_s; and, if `range` is set (one block
 // only: it is over all channels and the call has no scratch memory), the equalised activation range with the static
-// int8 activation quantizer (Eq. 2 on the range of X_hat).  Bound by the round trips of a block's loads, so a thread
-// requests kScaleBatch channels before it uses the first, and then by its fp64 square roots and divisions: 1 us per 1024
-// channels.  Up to kOneBlockK channels one block does everything; beyond, a block per 1024 channels and a launch of
-// equalize_range (us, one channel at a time in one block -> one block / two launches: K = 4096 7.9 -> 6.2,
-// 8192 14.3 -> 7.7, 11008 16.5 -> 7.8).
+// int8 activation quantizer (Eq. 2 on the range of X_hat).  Bound by the round trips of a block's loads, so a thread of
+// the one block requests kScaleBatch channels before it uses the first, and then by its fp64 square roots and divisions: 1 us
+// per 1024 channels.  Up to kOneBlockK channels one block does everything; beyond, a block per 1024 channels (a thread
+// has one channel then) and a launch of equalize_range (us, one channel at a time in one block -> one block / two
+// launches: K = 4096 7.9 -> 6.2, 8192 14.3 -> 7.7, 11008 16.5 -> 7.8).  equalize_range reads xmin and xmax again, so a
+// call whose vectors replace them stays with one block, which has read a channel's statistics before it writes the channel.
 constexpr int kScaleBatch = 4;
 constexpr int kScaleBlock = 1024;
 constexpr int64_t kOneBlockK = 4096;
@@ -178,7 +179,7 @@ extern "C" int aweq_equalize(const float* xmin, const float* xmax, const double*
             return AWEQ_ERR_ALIGN;
     }
     hipStream_t st = as_stream(stream);
-    const bool one = K <= kOneBlockK;
+    const bool one = K <= kOneBlockK || overlap({{s, K * 4}, {inv_s, K * 4}, {mu_xhat, K * 4}, {prev_scale, K * 4}}, {{xmin, K * 4}, {xmax, K * 4}});
     equalize_scales<<<one ? 1u : (unsigned)cdiv(K, kScaleBlock), kScaleBlock, 0, st>>>(
         xmin, xmax, xsum, count, wmin, wmax, K, enable_awe, s, inv_s, prev_scale, xhat_range, mu_xhat, act_step, act_zero, status, one);
     if (!one && (xhat_range || act_step))

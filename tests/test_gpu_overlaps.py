@@ -100,3 +100,27 @@ def test_row_sums_over_the_activation(B, orc, dtype, T):
                 assert np.array_equal(from_panels(xq.cpu().numpy(), T, K), ref["xq"]) and np.array_equal(rs.cpu().numpy(), ref["rowsum_x"])
                 if sums:
                     assert np.array_equal(cs.cpu().numpy(), ref["colsum_xq"])
+
+
+@pytest.mark.parametrize("K", [1000, 4096, 4104, 11008])   # one block of channels, and several with a range launch
+def test_equalize_vectors_replace_the_statistics(B, K):
+    rng = np.random.default_rng(K)
+    lo = -np.exp(rng.standard_normal((2, K))).astype(np.float32)
+    hi = np.exp(rng.standard_normal((2, K))).astype(np.float32)
+    xsum = rng.standard_normal(K) * 100
+
+    def run(over, under, apart):
+        t = dict(xmin=dev(lo[0]), xmax=dev(hi[0]), xsum=dev(xsum), wmin=dev(lo[1]), wmax=dev(hi[1]))
+        o = {k: torch.full((K,), 2.0, device=DEV) for k in ("s", "inv_s", "mu", "prev")}
+        o.update(range=torch.zeros(2, device=DEV), step=torch.zeros(1, device=DEV), zero=torch.zeros(1, dtype=torch.int32, device=DEV))
+        o[over] = t[under].clone() if apart else t[under]   # (prev is read before it is written)
+        B.aweq_equalize(t["xmin"], t["xmax"], t["xsum"], 777, t["wmin"], t["wmax"], K, 1, o["s"], o["inv_s"], None, None, B.AWEQ_F16, 0, K, K,
+                        o["prev"], o["range"], o["mu"], o["step"], o["zero"])
+        return o
+
+    for over in ("s", "inv_s", "mu", "prev"):
+        for under in ("xmin", "xmax", "wmin", "wmax"):
+            print(f"[gpu-overlap] equalize K={K} {over} over {under}", flush=True)
+            want, got = run(over, under, True), run(over, under, False)
+            for k in want:
+                assert torch.equal(want[k], got[k]), (over, under, k)
