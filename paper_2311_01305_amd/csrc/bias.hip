@@ -36,8 +36,9 @@ __device__ __forceinline__ void load_w8(const void* row, int64_t u, float x[8])
 // channel needs) are read once per block instead of once per channel.
 // The codes meet colsum_xq in 8-bit pieces: a column sum below 2^30 is four signed digits of base 256, and a dot product
 // instruction multiplies four codes with four digits of equal weight (one instruction per code; 64-bit products took
-// about 15 and bound the kernel).  The four int32 sums of a row grow by at most 2^17 per unit: exact for K < 2^24 with blocks
-// of 64 threads.  Larger column sums and longer rows take the 64-bit products.
+// about 15 and bound the kernel).  The four int32 sums of a row grow by at most 2^17 per unit (8 products of at most 2^14), so
+// a thread's 2^14 - 1 units are the most that cannot overflow.  Larger column sums and longer rows take the 64-bit products.
+constexpr int64_t kDigitUnits = (1 << 14) - 1;   // units per thread
 template <bool F16, int BLOCK, int ROWS>
 __global__ __launch_bounds__(BLOCK) void bias_w8a8_kernel(
     const void* __restrict__ W_hat, int64_t N, int64_t K, int64_t ldw, const float* __restrict__ mu_xhat, uint64_t count,
@@ -63,6 +64,7 @@ __global__ __launch_bounds__(BLOCK) void bias_w8a8_kernel(
         for (int j = 0; j < 4; ++j) cd[r][j] = 0;
     }
     long long tot = 0;
+    const bool digits = K / 8 <= kDigitUnits * BLOCK;
     for (int64_t u = threadIdx.x; u < K / 8; u += BLOCK) {
         float w[ROWS][8];
         uint2 v[ROWS];
@@ -76,7 +78,7 @@ __global__ __launch_bounds__(BLOCK) void bias_w8a8_kernel(
         const Float4 m0 = *reinterpret_cast<const Float4*>(mu_xhat + u * 8);
         const Float4 m1 = *reinterpret_cast<const Float4*>(mu_xhat + u * 8 + 4);
         long long cx[8];
-        bool small = K < (1 << 24);
+        bool small = digits;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             cx[i] = colsum_xq[u * 8 + i];
