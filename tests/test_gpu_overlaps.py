@@ -27,13 +27,17 @@ def dev(a):
 @pytest.mark.parametrize("dtype", [np.float16, np.float32])
 @pytest.mark.parametrize("N,K", [(64, 64), (4096, 4096), (16384, 1024), (260, 2112)])
 def test_forward_stores_over_its_input(B, dtype, N, K):
-    """aweq_w8a8_gemm with its output over X or inv_s, on both sides of the four tokens whose launch may quantise them itself."""
+    """aweq_w8a8_gemm with its output over X or inv_s, on both sides of the four tokens whose launch may quantise them itself.  A large
+    product on another stream holds every compute unit when the call comes, so that its workgroups start one after the other."""
     rng = np.random.default_rng(N + K)
     dt = B.AWEQ_F16 if dtype == np.float16 else B.AWEQ_F32
     wq = rng.integers(-128, 128, (N, K), dtype=np.int8)
     dw, rw = dev(to_panels(wq)), dev(wq.astype(np.int64).sum(1).astype(np.int32))
     sw, zw, bias = dev(rng.uniform(1e-3, 2e-2, N).astype(np.float32)), dev(rng.integers(0, 256, N).astype(np.int32)), dev(rng.standard_normal(N).astype(np.float32))
     ds, dz = dev(np.float32([0.0371])), dev(np.int32([117]))
+    side = torch.cuda.Stream()
+    big = [torch.zeros(B.aweq_panel_bytes(4096, 4096), dtype=torch.int8, device=DEV) for _ in range(2)] + [torch.zeros((4096, 4096), dtype=torch.int32, device=DEV)]
+    torch.cuda.synchronize()
     for T in (1, 3, 4, 5):
         X = (rng.standard_normal((T, K)) * 3).astype(dtype)
         inv_s = rng.uniform(0.2, 2.0, K).astype(np.float32)
@@ -53,8 +57,13 @@ def test_forward_stores_over_its_input(B, dtype, N, K):
                 out = home[:T * N * osize].view(odt)
                 xq, rs = torch.zeros(B.aweq_panel_bytes(T, K), dtype=torch.int8, device=DEV), torch.zeros(T, dtype=torch.int32, device=DEV)
                 cs, st = torch.zeros(N, dtype=torch.int64, device=DEV), torch.zeros(1, dtype=torch.int32, device=DEV)
+                torch.cuda.synchronize()
+                if not apart:
+                    B.aweq_w8a8_gemm(big[0], B.AWEQ_I8, 4096, 4096, 4096, None, None, None, None, None, None, big[1], 4096, None, None, 0, None, None,
+                                     big[2], None, B.AWEQ_F16, 4096, None, stream=side)
                 B.aweq_w8a8_gemm(dX, dt, T, K, K, di, ds, dz, xq, rs, None, dw, N, sw, zw, 0, rw, bias, out if kind == "i32" else None,
                                  None if kind == "i32" else out, dt, N, cs, ws, st)
+                torch.cuda.synchronize()
                 return out.clone(), xq, rs, cs, st
 
             want = run(True)
