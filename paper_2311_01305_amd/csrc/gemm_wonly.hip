@@ -468,7 +468,17 @@ extern "C" int aweq_wonly_gemm(const void* X_hat, int64_t T, int64_t K, int64_t 
     const wonly::SmallPlan small = wonly::plan_small(T, N);
     const wonly::MidPlan mid = wonly::plan_mid(T, N);
     const bool mid_ok = (group <= 0 || group % 128 == 0) && ldx < (1 << 24);
-    if (small.cost <= tiled_cost && (!mid_ok || small.cost <= mid.cost)) return wonly::launch_small(a, bits, group, small, f16, st);
+    if (small.cost <= tiled_cost && (!mid_ok || small.cost <= mid.cost)) {
+        // its token tiles ride on the grid's y dimension: 65535 of 32 tokens to a launch
+        for (int64_t t = 0; t < T; t += 65535 * 32) {
+            a.T = T - t < 65535 * 32 ? T - t : 65535 * 32;
+            a.X = reinterpret_cast<const _Float16*>(X_hat) + t * ldx;
+            a.out = reinterpret_cast<char*>(out) + t * ldo * (int64_t)dtype_size(out_dt);
+            rc = wonly::launch_small(a, bits, group, small, f16, st);
+            if (rc != AWEQ_OK) return rc;
+        }
+        return AWEQ_OK;
+    }
     if (mid_ok && mid.cost <= tiled_cost) return wonly::launch_mid(a, bits, mid, f16, st);
 
     // the binary16 weight, once
