@@ -454,7 +454,9 @@ extern "C" int aweq_wonly_gemm(const void* X_hat, int64_t T, int64_t K, int64_t 
     int64_t blocks = 0;
     int rc = plan_walk(g, T, N, K, 256, blocks);
     if (rc != AWEQ_OK) return rc;
-    const bool half = plan_walk(h, T, N, K, 128, blocks) == AWEQ_OK && wonly::kHalfTileCost * (double)rounds_of(h) < (double)rounds_of(g);
+    // Byte offsets inside a tile of rows are 32-bit: whether they reach the last of `rows` tokens (512: a stage's bytes of a row)
+    auto reach = [&](int64_t rows) { return (T < rows ? T : rows) - 1 <= (((1ll << 32) - 512) / 2) / ldx; };
+    const bool half = plan_walk(h, T, N, K, 128, blocks) == AWEQ_OK && (wonly::kHalfTileCost * (double)rounds_of(h) < (double)rounds_of(g) || !reach(256));
     const double tiled_cost = (half ? wonly::kHalfTileCost * (double)rounds_of(h) : (double)rounds_of(g)) * wonly::kTiledRoundCost + wonly::kDequantCost * (double)N;
     if (half) g = h;
 
@@ -467,11 +469,13 @@ extern "C" int aweq_wonly_gemm(const void* X_hat, int64_t T, int64_t K, int64_t 
     a.group_magic = group_magic;
     const wonly::SmallPlan small = wonly::plan_small(T, N);
     const wonly::MidPlan mid = wonly::plan_mid(T, N);
-    const bool mid_ok = (group <= 0 || group % 128 == 0) && ldx < (1 << 24);
-    if (small.cost <= tiled_cost && (!mid_ok || small.cost <= mid.cost)) {
-        // its token tiles ride on the grid's y dimension: 65535 of 32 tokens to a launch
-        for (int64_t t = 0; t < T; t += 65535 * 32) {
-            a.T = T - t < 65535 * 32 ? T - t : 65535 * 32;
+    const bool tiled_ok = reach(half ? 128 : 256), mid_ok = (group <= 0 || group % 128 == 0) && reach(128);
+    if (!tiled_ok || (small.cost <= tiled_cost && (!mid_ok || small.cost <= mid.cost))) {
+        // Its token tiles ride on the grid's y dimension, 65535 of 32 tokens to a launch, and its 32-bit offsets count elements: of
+        // pitches beyond their reach (2^27 for a tile of 32 tokens) a launch takes the tokens that they reach.
+        const int64_t last = ((1ll << 32) - 1 - K) / ldx, step = last >= 31 ? 65535 * 32 : last + 1;
+        for (int64_t t = 0; t < T; t += step) {
+            a.T = T - t < step ? T - t : step;
             a.X = reinterpret_cast<const _Float16*>(X_hat) + t * ldx;
             a.out = reinterpret_cast<char*>(out) + t * ldo * (int64_t)dtype_size(out_dt);
             rc = wonly::launch_small(a, bits, group, small, f16, st);

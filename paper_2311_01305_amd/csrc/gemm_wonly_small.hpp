@@ -27,7 +27,7 @@ SmallPlan plan_small(int64_t T, int64_t N);
 int launch_small(const SmallArgs& g, int bits, int group, const SmallPlan& p, bool out_f16, hipStream_t st);
 
 // The same of the kernel for some hundred tokens (gemm_wonly_mid.hip), which takes groups that are multiples of 128, one (Step, Z)
-// per row or one per tensor, and pitches below 2^24 (32-bit byte offsets inside a tile of rows)
+// per row or one per tensor, and pitches whose 128 rows lie within 2^32 bytes (32-bit byte offsets inside a tile of rows)
 struct MidPlan {
     bool square;   // 128 x 128 tiles instead of 64 x 128
     double cost;
