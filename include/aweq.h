@@ -278,9 +278,10 @@ int aweq_bias_correct(int mode, const void* W_hat, aweq_dtype dt, int64_t N, int
  * for bits in {4, 3} and the same group (group > 0: a multiple of 32 dividing K; 0: per row; -1: per
  * tensor); bias[N] fp32 nullable; out[T x N] F16 or F32, pitch ldo.  K % 64 == 0, N % 4 == 0,
  * ldo % 4 == 0, 16-byte aligned pointers.  Arithmetic: the weight operand is binary16,
- * w~_h = RN16((u - Z) * RN16(Step)), written once per call into the workspace (N * K * 2 bytes:
- * aweq_workspace_size(AWEQ_OP_WONLY_GEMM, T, K, N)); products are exact in fp32 and accumulated in
- * fp32 on the matrix cores (summation order unspecified). */
+ * w~_h = RN16((u - Z) * RN16(Step)), formed in registers, or written once per call into the workspace (N * K * 2 bytes:
+ * aweq_workspace_size(AWEQ_OP_WONLY_GEMM, T, K, N); asked for in any case) where there are many tokens; products are exact in
+ * fp32 and accumulated in fp32 on the matrix cores (summation order unspecified).  out may overlap codes, step_w and zero_w (not
+ * X_hat or bias): the weight is written to the workspace first then. */
 int aweq_wonly_gemm(const void* X_hat, int64_t T, int64_t K, int64_t ldx,
                     const void* codes, int bits, int group,
                     const float* step_w, const int32_t* zero_w, int64_t N,

@@ -461,7 +461,8 @@ extern "C" int aweq_wonly_gemm(const void* X_hat, int64_t T, int64_t K, int64_t 
     if (half) g = h;
 
     // Straight from the codes where one of the two kernels that do so is modelled to take less (both sides measured in
-    // gemm_wonly_small.hip and gemm_wonly_mid.hip)
+    // gemm_wonly_small.hip and gemm_wonly_mid.hip).  Not where the output lies over the codes or their (Step, Z): a workgroup would
+    // store over what another still reads; the de-quantising pass is over before the GEMM stores anything.
     wonly::SmallArgs a;
     a.X = reinterpret_cast<const _Float16*>(X_hat); a.codes = reinterpret_cast<const uint8_t*>(codes);
     a.step = step_w; a.zero = zero_w; a.bias = bias; a.out = out; a.ldx = ldx; a.ldo = ldo; a.T = T; a.N = N; a.K = K;
@@ -469,8 +470,10 @@ extern "C" int aweq_wonly_gemm(const void* X_hat, int64_t T, int64_t K, int64_t 
     a.group_magic = group_magic;
     const wonly::SmallPlan small = wonly::plan_small(T, N);
     const wonly::MidPlan mid = wonly::plan_mid(T, N);
-    const bool tiled_ok = reach(half ? 128 : 256), mid_ok = (group <= 0 || group % 128 == 0) && reach(128);
-    if (!tiled_ok || (small.cost <= tiled_cost && (!mid_ok || small.cost <= mid.cost))) {
+    const int64_t scales = group < 0 ? 4 : group == 0 ? N * 4 : N * (K / group) * 4;
+    const bool apart = !overlap({matrix_span(out, T, N, ldo, dtype_size(out_dt))}, {{codes, N * (K / 8 * bits)}, {step_w, scales}, {zero_w, scales}});
+    const bool tiled_ok = reach(half ? 128 : 256), mid_ok = apart && (group <= 0 || group % 128 == 0) && reach(128);
+    if (!tiled_ok || (apart && small.cost <= tiled_cost && (!mid_ok || small.cost <= mid.cost))) {
         // Its token tiles ride on the grid's y dimension, 65535 of 32 tokens to a launch, and its 32-bit offsets count elements: of
         // pitches beyond their reach (2^27 for a tile of 32 tokens) a launch takes the tokens that they reach.
         const int64_t last = ((1ll << 32) - 1 - K) / ldx, step = last >= 31 ? 65535 * 32 : last + 1;

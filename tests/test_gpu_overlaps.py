@@ -1,5 +1,6 @@
 """Entry points whose outputs lie over their inputs, as the header allows: the results equal those of the same call on buffers
-of their own, bit for bit."""
+of their own, bit for bit (the weight-only forward, which sums in another order then: the oracle's, within the bound of fp32
+accumulation in any order, |y - ref| <= K 2^-24 sum_k |x w| plus one rounding of the output)."""
 import numpy as np
 import pytest
 
@@ -24,20 +25,26 @@ def dev(a):
     return torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
 
 
+@pytest.fixture(scope="module")
+def occupy(B):
+    """A call that holds every compute unit with a large product on another stream: the workgroups of the next launch start one after the other."""
+    side = torch.cuda.Stream()
+    big = [torch.zeros(B.aweq_panel_bytes(4096, 4096), dtype=torch.int8, device=DEV) for _ in range(2)] + [torch.zeros((4096, 4096), dtype=torch.int32, device=DEV)]
+    torch.cuda.synchronize()
+    return lambda: B.aweq_w8a8_gemm(big[0], B.AWEQ_I8, 4096, 4096, 4096, None, None, None, None, None, None, big[1], 4096, None, None, 0, None, None,
+                                    big[2], None, B.AWEQ_F16, 4096, None, stream=side)
+
+
 @pytest.mark.parametrize("dtype", [np.float16, np.float32])
 @pytest.mark.parametrize("N,K", [(64, 64), (4096, 4096), (16384, 1024), (260, 2112)])
-def test_forward_stores_over_its_input(B, dtype, N, K):
-    """aweq_w8a8_gemm with its output over X or inv_s, on both sides of the four tokens whose launch may quantise them itself.  A large
-    product on another stream holds every compute unit when the call comes, so that its workgroups start one after the other."""
+def test_forward_stores_over_its_input(B, occupy, dtype, N, K):
+    """aweq_w8a8_gemm with its output over X or inv_s, on both sides of the four tokens whose launch may quantise them itself."""
     rng = np.random.default_rng(N + K)
     dt = B.AWEQ_F16 if dtype == np.float16 else B.AWEQ_F32
     wq = rng.integers(-128, 128, (N, K), dtype=np.int8)
     dw, rw = dev(to_panels(wq)), dev(wq.astype(np.int64).sum(1).astype(np.int32))
     sw, zw, bias = dev(rng.uniform(1e-3, 2e-2, N).astype(np.float32)), dev(rng.integers(0, 256, N).astype(np.int32)), dev(rng.standard_normal(N).astype(np.float32))
     ds, dz = dev(np.float32([0.0371])), dev(np.int32([117]))
-    side = torch.cuda.Stream()
-    big = [torch.zeros(B.aweq_panel_bytes(4096, 4096), dtype=torch.int8, device=DEV) for _ in range(2)] + [torch.zeros((4096, 4096), dtype=torch.int32, device=DEV)]
-    torch.cuda.synchronize()
     for T in (1, 3, 4, 5):
         X = (rng.standard_normal((T, K)) * 3).astype(dtype)
         inv_s = rng.uniform(0.2, 2.0, K).astype(np.float32)
@@ -59,8 +66,7 @@ def test_forward_stores_over_its_input(B, dtype, N, K):
                 cs, st = torch.zeros(N, dtype=torch.int64, device=DEV), torch.zeros(1, dtype=torch.int32, device=DEV)
                 torch.cuda.synchronize()
                 if not apart:
-                    B.aweq_w8a8_gemm(big[0], B.AWEQ_I8, 4096, 4096, 4096, None, None, None, None, None, None, big[1], 4096, None, None, 0, None, None,
-                                     big[2], None, B.AWEQ_F16, 4096, None, stream=side)
+                    occupy()
                 B.aweq_w8a8_gemm(dX, dt, T, K, K, di, ds, dz, xq, rs, None, dw, N, sw, zw, 0, rw, bias, out if kind == "i32" else None,
                                  None if kind == "i32" else out, dt, N, cs, ws, st)
                 torch.cuda.synchronize()
@@ -133,3 +139,33 @@ def test_equalize_vectors_replace_the_statistics(B, K):
             want, got = run(over, under, True), run(over, under, False)
             for k in want:
                 assert torch.equal(want[k], got[k]), (over, under, k)
+
+
+@pytest.mark.parametrize("bits,group", [(4, 128), (3, 128), (4, -1), (3, 0)])
+@pytest.mark.parametrize("T", [1, 17, 256])   # the few-token kernel and, at 256 tokens, the one for some hundred
+def test_weight_only_output_over_the_weight(B, orc, occupy, T, bits, group):
+    """aweq_wonly_gemm with its output over the codes or their scales, which the kernels for fewer tokens read throughout."""
+    rng = np.random.default_rng(T + bits)
+    N, K = 4096, 1024
+    q = orc.quant_weight((rng.standard_normal((N, K)) * 0.02).astype(np.float16), bits, group)
+    Wh = orc.dequant_weight_h(q["codes_u"], group, q["step"], q["zero"])
+    X, bias = rng.standard_normal((T, K)).astype(np.float16), rng.standard_normal(N).astype(np.float32)
+    ref, mag = orc.wonly_forward(X, Wh, bias)
+    parts = {"codes": dev(orc.pack_codes(q["codes_u"], bits).view(np.uint8).reshape(-1)), "step": dev(q["step"].reshape(-1)), "zero": dev(q["zero"].reshape(-1))}
+    dX, db = dev(X), dev(bias)
+    ws = torch.empty(B.aweq_workspace_size(B.OP_WONLY_GEMM, T, K, N), dtype=torch.uint8, device=DEV)
+    for over in parts:
+        for _ in range(5):
+            print(f"[gpu-overlap] weight-only W{bits} g={group} T={T} over {over}", flush=True)
+            src = dict(parts)
+            raw = parts[over].view(torch.uint8)
+            home = torch.zeros(max(T * N * 2, raw.numel()), dtype=torch.uint8, device=DEV)
+            home[:raw.numel()] = raw
+            src[over] = home[:raw.numel()].view(parts[over].dtype)
+            out = home[:T * N * 2].view(torch.float16)
+            torch.cuda.synchronize()
+            occupy()
+            B.aweq_wonly_gemm(dX, T, K, K, src["codes"], bits, group, src["step"], src["zero"], N, db, out, B.AWEQ_F16, N, ws)
+            torch.cuda.synchronize()
+            got = out.cpu().numpy().astype(np.float64).reshape(T, N)
+            assert np.all(np.abs(got - ref) <= K * 2.0 ** -24 * mag + 2.0 ** -11 * np.abs(ref) + 2.0 ** -24), over
