@@ -38,16 +38,18 @@ __device__ __forceinline__ void load_w8(const void* row, int64_t u, float x[8])
 // instruction multiplies four codes with four digits of equal weight (one instruction per code; 64-bit products took
 // about 15 and bound the kernel).  The four int32 sums of a row grow by at most 2^17 per unit (8 products of at most 2^14), so
 // a thread's 2^14 - 1 units are the most that cannot overflow.  Larger column sums and longer rows take the 64-bit products.
+// SUMS: compiled for calls that bring colsum_acc, without the registers of the digits.
 constexpr int64_t kDigitUnits = (1 << 14) - 1;   // units per thread
-template <bool F16, int BLOCK, int ROWS>
+template <bool F16, bool SUMS, int BLOCK, int ROWS>
 __global__ __launch_bounds__(BLOCK) void bias_w8a8_kernel(
     const void* __restrict__ W_hat, int64_t N, int64_t K, int64_t ldw, const float* __restrict__ mu_xhat, uint64_t count,
     const long long* __restrict__ colsum_acc, const long long* __restrict__ colsum_xq,
     const int32_t* __restrict__ rowsum_w, const float* __restrict__ act_step, const int32_t* __restrict__ act_zero,
     const float* __restrict__ step_w, const int32_t* __restrict__ zero_w, const float* __restrict__ bias_in,
-    float* __restrict__ delta, float* __restrict__ bias_out, int enable_bc, const int8_t* __restrict__ wq,
+    float* __restrict__ delta, float* __restrict__ bias_out, int enable_bc, const int8_t* __restrict__ codes,
     int w_per_tensor)
 {
+    const int8_t* const __restrict__ wq = SUMS ? nullptr : codes;
     constexpr int kWaves = BLOCK / kWave;
     __shared__ double slot_d[kWaves][ROWS];
     __shared__ long long slot_l[kWaves][ROWS + 1];
@@ -198,7 +200,14 @@ __global__ __launch_bounds__(BLOCK) void bias_wonly_kernel(
                                  : *reinterpret_cast<const uint2*>(codes + ((u >> 3) * N + n) * kPanel + (u & 7) * 8);
             } else if constexpr (BITS == 4) {
                 v[r].x = *reinterpret_cast<const uint32_t*>(crow + u * 4);
+            } else if constexpr (ROWS < 4) {
+                // the unit's 24 bits in one load of 4 bytes, of which a quad's last unit has the upper three
+                const int last = (u & 3) == 3;
+                uint32_t x;
+                __builtin_memcpy(&x, crow + u * 3 - last, 4);
+                v[r].x = x >> (8 * last);
             } else {
+                // (two aligned loads where four channels make up for them: binary16 8192 x 22016 103 -> 85 us)
                 // 24 bits of the 12 bytes four units share (K % 32 == 0: they start on 4-byte boundaries)
                 const uint32_t* const q = reinterpret_cast<const uint32_t*>(crow + (u >> 2) * 12);
                 const int d = (int)(u & 3);
@@ -269,14 +278,28 @@ extern "C" int aweq_bias_correct(int mode, const void* W_hat, aweq_dtype dt, int
         if (wq && !aligned16(wq)) return AWEQ_ERR_ALIGN;
         const long long* ca = reinterpret_cast<const long long*>(colsum_acc);
         const long long* cx = reinterpret_cast<const long long*>(colsum_xq);
-#define AWEQ_B8(F, BLOCK, ROWS)                                                                                        \
-    bias_w8a8_kernel<F, BLOCK, ROWS><<<(unsigned)cdiv(N, ROWS), BLOCK, 0, st>>>(                                       \
+#define AWEQ_B8(F, S, BLOCK, ROWS)                                                                                     \
+    bias_w8a8_kernel<F, S, BLOCK, ROWS><<<(unsigned)cdiv(N, ROWS), BLOCK, 0, st>>>(                                    \
         W_hat, N, K, ldw, mu_xhat, count, ca, cx, rowsum_w, act_step, act_zero, step_w, zero_w, bias_in, delta, bias_out, enable_bc, wq, pt)
-        // small blocks: more of them in flight while others reduce.  us, from the codes 4096 x 11008 / with the GEMM's sums
-        // 4096 x 4096, binary16: 128 threads x 4 channels 24.2 / 11.0, 256 x 8 27.6 / 10.9, 256 x 4 26.6 / 11.9, 512 x 8 32.6 / 15.6,
-        // 64 x 4 33.4 / 13.0 (256 x 8 with 64-bit products and a barrier pair per channel: 40.8 / 13.6); 512 x 512 binary32 7.1 -> 3.6
-        if (f16) { if (K <= 1024) AWEQ_B8(true, 64, 2); else AWEQ_B8(true, 128, 4); }
-        else { if (K <= 1024) AWEQ_B8(false, 64, 2); else AWEQ_B8(false, 128, 4); }
+        // us, threads x channels of a block: small blocks, more of them in flight while others reduce (binary16 from the codes
+        // 4096 x 11008: 128 x 4 24.2, 256 x 8 27.6, 256 x 4 26.6, 512 x 8 32.6, 64 x 4 33.4; with 64-bit products and a barrier pair per
+        // channel 40.8), but a weight that does not fit the memory-side cache wants more of its long rows on their way (128 x 4 ->
+        // 256 x 8: from the codes binary16 22016 x 8192 113 -> 100, 8192 x 22016 130 -> 103; with the GEMM's sums binary16 22016 x 8192
+        // 79 -> 70, 8192 x 22016 92 -> 74, 12288 x 12288 65 -> 56, binary32 8192 x 22016 145 -> 128), and binary16 with sums, a read of
+        // the weight alone, eight channels of its short ones (40000 x 4096 71 -> 65).  The threads of a block decide the order of
+        // the sums: they are the same for both sources of the integers, so that delta is.
+        const bool beyond = N * K * (int64_t)dtype_size(dt) >= kCacheBytes, large = beyond && K >= 8192;
+        if (f16) {
+            if (K <= 1024) AWEQ_B8(true, false, 64, 2);
+            else if (large && !wq) AWEQ_B8(true, true, 256, 8);
+            else if (large) AWEQ_B8(true, false, 256, 8);
+            else if (beyond && !wq) AWEQ_B8(true, true, 128, 8);
+            else AWEQ_B8(true, false, 128, 4);
+        } else {   // (without the digits' registers binary32 is no faster: 8192 x 22016 128 -> 139)
+            if (K <= 1024) AWEQ_B8(false, false, 64, 2);
+            else if (large) AWEQ_B8(false, false, 256, 8);
+            else AWEQ_B8(false, false, 128, 4);
+        }
 #undef AWEQ_B8
     } else if (mode == AWEQ_BIAS_WEIGHT_ONLY) {
         if (!codes) return AWEQ_ERR_NULL;
@@ -288,7 +311,11 @@ extern "C" int aweq_bias_correct(int mode, const void* W_hat, aweq_dtype dt, int
 #define AWEQ_BWS(F, B, BLOCK, ROWS)                                                                                    \
     bias_wonly_kernel<F, B, BLOCK, ROWS><<<(unsigned)cdiv(N, ROWS), BLOCK, 0, st>>>(                                    \
         W_hat, N, K, ldw, mu_xhat, cb, group, step_w, zero_w, bias_in, delta, bias_out, enable_bc)
-#define AWEQ_BW(F, B) do { if (K <= 1024) AWEQ_BWS(F, B, 64, 2); else AWEQ_BWS(F, B, 256, 4); } while (0)
+        // Four channels a block where that leaves enough blocks and their values fit the registers, two otherwise (us, 4 -> 2: binary32,
+        // whose channel takes eight registers, INT3 4096 x 11008 49.4 -> 30.0, INT4 8192 x 8192 55.7 -> 45.5; binary16 8-bit groups
+        // 4096 x 11008 24.1 -> 22.7, INT3 4096 x 11008 21.1 -> 20.4, INT4 1000 x 16384 14.0 -> 9.9; but 8-bit rows 8192 x 22016 105 -> 114)
+        const bool four = f16 && N >= 8192 && !(bits == 8 && group > 0);
+#define AWEQ_BW(F, B) do { if (K <= 1024) AWEQ_BWS(F, B, 64, 2); else if (F && four) AWEQ_BWS(F, B, 256, F ? 4 : 2); else AWEQ_BWS(F, B, 256, 2); } while (0)
         if (f16) { if (bits == 8) AWEQ_BW(true, 8); else if (bits == 4) AWEQ_BW(true, 4); else AWEQ_BW(true, 3); }
         else { if (bits == 8) AWEQ_BW(false, 8); else if (bits == 4) AWEQ_BW(false, 4); else AWEQ_BW(false, 3); }
 #undef AWEQ_BW

@@ -83,3 +83,35 @@ def test_longest_rows(B, orc, K):
     step_w, zero_w = np.float32([0.01]), np.int32([128])
     a, b = both_forms(B, Wh, mu, 1, colsum, csa, rowsum, 0.01, 128, codes, 0, step_w, zero_w, np.zeros(1, np.float32))
     assert np.array_equal(a[0], b[0]) and a[0][0] == np.float32(-float(np.float32(0.01)) * float(step_w[0]) * float(csa[0]))
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.float32])
+@pytest.mark.parametrize("N,K", [(4099, 8200), (16390, 8192), (32774, 4104), (8200, 16384)])   # both sides of 256 MiB, short rows and long
+def test_both_sources_of_the_sums_agree(B, dtype, N, K):
+    """The launch shapes of large weights: delta from the codes and from the same integers given as colsum_acc is the same, bit for
+    bit, and within the rounding of its mean in another order of the 64-bit one."""
+    print(f"[gpu-bias-codes] large {dtype} N={N} K={K}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(N + K)
+    dt, T = (B.AWEQ_F16 if dtype == torch.float16 else B.AWEQ_F32), 4096
+    Wh = (torch.randn(N, K, generator=g, device=DEV) * 0.02).to(dtype)
+    mu, b_in = torch.randn(K, generator=g, device=DEV), torch.randn(N, generator=g, device=DEV)
+    codes = torch.randint(-128, 128, (N, K), generator=g, device=DEV, dtype=torch.int8)
+    col = torch.randint(-(1 << 19), 1 << 19, (K,), generator=g, device=DEV)
+    panels = torch.empty(B.aweq_panel_bytes(N, K), dtype=torch.int8, device=DEV)
+    B.aweq_pack_panels_i8(codes, N, K, K, panels)
+    # (exact: every partial sum is an integer below 2^53)
+    csa = torch.cat([(c.double() * col.double()).sum(1) for c in codes.split(1024)]).long()
+    rowsum = codes.sum(1, dtype=torch.int32)
+    sx, zx = torch.tensor([0.0371], device=DEV), torch.tensor([117], dtype=torch.int32, device=DEV)
+    sw = torch.rand(N, generator=g, device=DEV) * 0.02 + 1e-3
+    zw = torch.randint(0, 256, (N,), generator=g, device=DEV, dtype=torch.int32)
+    res = []
+    for ca, wq in ((None, panels), (csa, None)):
+        delta, out = torch.zeros(N, device=DEV), torch.zeros(N, device=DEV)
+        B.aweq_bias_correct(B.BIAS_W8A8, Wh, dt, N, K, K, mu, T, ca, col, rowsum, sx, zx, wq, 8, 0, sw, zw, b_in, delta, out, 1)
+        res.append((delta, out))
+    assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
+    mean = torch.cat([(w.double() * mu.double()).sum(1) for w in Wh.split(1024)])
+    a = csa - T * (117 - 128) * rowsum.long() - (zw.long() - 128) * col.sum() + T * K * (117 - 128) * (zw.long() - 128)
+    ref = mean - sx.double() * sw.double() * a.double() / T
+    assert torch.max(torch.abs(res[0][0].double() - ref)) <= 1e-6 * torch.max(torch.abs(ref))
