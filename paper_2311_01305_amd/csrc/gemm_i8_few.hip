@@ -35,7 +35,7 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_few(GemmArgs g, QuantIn in)
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     const int r = lane & 15, q = lane >> 4;
-    const int64_t n0 = (int64_t)blockIdx.x * (16 * NT), t0 = (int64_t)blockIdx.y * (16 * TT);
+    const int64_t n0 = (int64_t)blockIdx.x * (16 * NT), t0 = (int64_t)(g.run + (int)blockIdx.y) * (16 * TT);   // (run: the launch's first token tile)
     const int np = (int)panel_count(g.K);
     const int rows_left = (int)min(g.N - n0, (int64_t)(16 * NT)) - 1, tokens_left = (int)min(g.T - t0, (int64_t)(16 * TT)) - 1;
 
@@ -206,16 +206,22 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_few(GemmArgs g, QuantIn in)
     raise_status(g.status, est);
 }
 
+// Token tiles ride on the grid's y dimension, at most 65535 to a launch: layers of up to 64 channels come here at any number of tokens
+constexpr int kMaxGridY = 65535;
 template <int TT, int NT, int U, int QX = 0>
-static int launch_tile(const GemmArgs& g, hipStream_t st, QuantIn in = {})
+static int launch_tile(GemmArgs g, hipStream_t st, QuantIn in = {})
 {
     const int lds = kWaves * TT * NT * kWave * 16 + (QX != 0 ? (int)(g.T * panel_count(g.K) * kPanel) : 0);
     const void* fn = reinterpret_cast<const void*>(gemm_i8_few<TT, NT, U, QX>);
     int dev = 0, cus = 0;
     if (lds > 32768 && (device_cus(dev, cus) != AWEQ_OK || raise_lds_limit(fn, dev, QX != 0 ? kMaxQuantLds : lds) != AWEQ_OK)) return AWEQ_ERR_LAUNCH;
-    void* args[] = {const_cast<GemmArgs*>(&g), &in};
-    if (hipLaunchKernel(fn, dim3((unsigned)cdiv(g.N, 16 * NT), (unsigned)cdiv(g.T, 16 * TT)), dim3(kThreads), args, lds, st) != hipSuccess)
-        return AWEQ_ERR_LAUNCH;
+    void* args[] = {&g, &in};
+    const int64_t tiles = cdiv(g.T, 16 * TT);
+    for (int64_t first = 0; first < tiles; first += kMaxGridY) {
+        g.run = (int)first;
+        const unsigned gy = (unsigned)(tiles - first < kMaxGridY ? tiles - first : kMaxGridY);
+        if (hipLaunchKernel(fn, dim3((unsigned)cdiv(g.N, 16 * NT), gy), dim3(kThreads), args, lds, st) != hipSuccess) return AWEQ_ERR_LAUNCH;
+    }
     return launch_status();
 }
 }  // namespace few
