@@ -280,8 +280,8 @@ int aweq_bias_correct(int mode, const void* W_hat, aweq_dtype dt, int64_t N, int
  * ldo % 4 == 0, 16-byte aligned pointers.  Arithmetic: the weight operand is binary16,
  * w~_h = RN16((u - Z) * RN16(Step)), formed in registers, or written once per call into the workspace (N * K * 2 bytes:
  * aweq_workspace_size(AWEQ_OP_WONLY_GEMM, T, K, N); asked for in any case) where there are many tokens; products are exact in
- * fp32 and accumulated in fp32 on the matrix cores (summation order unspecified).  out may overlap codes, step_w and zero_w (not
- * X_hat or bias): the weight is written to the workspace first then. */
+ * fp32 and accumulated in fp32 on the matrix cores (summation order unspecified).  out may overlap codes, step_w and zero_w: the
+ * weight is written to the workspace first then.  With N <= 256 a row of out may also lie over the same row of X_hat. */
 int aweq_wonly_gemm(const void* X_hat, int64_t T, int64_t K, int64_t ldx,
                     const void* codes, int bits, int group,
                     const float* step_w, const int32_t* zero_w, int64_t N,

@@ -911,10 +911,16 @@ extern "C" int aweq_w8a8_gemm(const void* X, aweq_dtype x_dt, int64_t T, int64_t
     if (out_deq && (!aligned16(out_deq) || (ldo % 4) != 0 || (w_group == 0 && (!aligned16(step_w) || !aligned16(zero_w))) ||
                     !aligned16(rowsum_w) || (bias && !aligned16(bias))))
         fast_ok = false;
+    // Up to 256 tokens and 256 channels are one 256 x 256 tile, whose workgroup has read everything before it stores: an output over an
+    // input stays there (tiled_cost 0: no other form is cheaper).  The other forms would have several workgroups, one storing while another reads.
+    const int64_t scales = g.w_per_tensor ? 4 : N * 4;
+    const bool apart = !overlap({matrix_span(out_i32, T, N, ldo, 4), matrix_span(out_deq, T, N, ldo, dtype_size(out_dt))},
+                                {{a, T * panel_count(K) * kPanel}, {wq, N * panel_count(K) * kPanel}, {rowsum_x, T * 4}, {rowsum_w, N * 4},
+                                 {act_step, 4}, {act_zero, 4}, {step_w, scales}, {zero_w, scales}, {bias, N * 4}});
     bool half = false;
     double tiled_cost = 0.0;
     int64_t blocks = 0;
-    const int prc = fast_ok ? plan_tiled(g, half, tiled_cost, blocks) : plan_walk(g, g.T, g.N, g.K, BM, blocks);
+    const int prc = fast_ok && apart ? plan_tiled(g, half, tiled_cost, blocks) : plan_walk(g, g.T, g.N, g.K, BM, blocks);
     if (prc != AWEQ_OK) return prc;
 
     // the form whose rounds of workgroups are modelled to take least
@@ -926,7 +932,7 @@ extern "C" int aweq_w8a8_gemm(const void* X, aweq_dtype x_dt, int64_t T, int64_t
     // store it while another still reads; the quantizer's own launch is over before the GEMM stores anything.
     const bool own_quant = fast_ok && x_dt != AWEQ_I8 && !colsum_xq && T <= kQuantTokens && T * panel_count(K) * kPanel <= kQuantFewBytes && aligned16(inv_s) &&
                            few.cost <= mid.cost && few.cost < kTiledRoundCost * tiled_cost &&
-                           !overlap({matrix_span(out_i32, T, N, ldo, 4), matrix_span(out_deq, T, N, ldo, dtype_size(out_dt)), {colsum_acc, N * 8}, {rowsum_x, T * 4}},
+                           !overlap({matrix_span(out_i32, T, N, ldo, 4), matrix_span(out_deq, T, N, ldo, dtype_size(out_dt)), {colsum_acc, N * 8}, {rowsum_x, T * 4}, {xq, T * panel_count(K) * kPanel}},
                                     {matrix_span(X, T, K, ldx, dtype_size(x_dt)), {inv_s, K * 4}, {act_step, 4}, {act_zero, 4}});
     if (!own_quant) {
         const int rc = quantise();
@@ -996,10 +1002,14 @@ extern "C" int aweq_w8a8_gemm_fused(const int8_t* xq, int64_t T, int64_t K, cons
         g.next_inv_s = next_inv_s; g.next_step = next_step; g.next_zero = next_zero;
         g.yq = yq; g.rowsum_y = rowsum_y; g.colsum_yq = reinterpret_cast<long long*>(colsum_yq);
     }
+    const bool apart = !overlap({matrix_span(out_f16, T, N, ldo, 2), {yq, T * panel_count(N) * kPanel}},
+                                {{xq, T * panel_count(K) * kPanel}, {wq, N * panel_count(K) * kPanel}, {rowsum_x, T * 4}, {rowsum_w, N * 4},
+                                 {act_step, 4}, {act_zero, 4}, {step_w, N * 4}, {zero_w, N * 4}, {bias, N * 4},
+                                 {next_inv_s, N * 4}, {next_step, 4}, {next_zero, 4}});   // (as in aweq_w8a8_gemm)
     bool half = false;
     double tiled_cost = 0.0;
     int64_t blocks = 0;
-    const int prc = plan_tiled(g, half, tiled_cost, blocks);
+    const int prc = apart ? plan_tiled(g, half, tiled_cost, blocks) : plan_walk(g, g.T, g.N, g.K, BM, blocks);
     if (prc != AWEQ_OK) return prc;
 
     hipStream_t st = as_stream(stream);

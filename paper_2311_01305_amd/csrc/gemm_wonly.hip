@@ -447,6 +447,13 @@ extern "C" int aweq_wonly_gemm(const void* X_hat, int64_t T, int64_t K, int64_t 
     const uint32_t scale_pitch = group < 0 ? 0u : group == 0 ? 1u : (uint32_t)(K / group);
     const uint32_t group_magic = group <= 0 ? 0u : (uint32_t)cdiv(1ll << 31, group / 32);
     const bool f16 = out_dt == AWEQ_F16;
+    // An output over an input: the codes and their (Step, Z) are read by the de-quantising pass, before the GEMM stores anything, and
+    // with up to 256 channels a row of X_hat by the workgroup that stores that row (one tile of 256 tokens: everything).  Straight from
+    // the codes a workgroup would store over what another still reads.
+    const int64_t scales = group < 0 ? 4 : group == 0 ? N * 4 : N * (K / group) * 4;
+    const Span o = matrix_span(out, T, N, ldo, dtype_size(out_dt));
+    const bool apart = !overlap({o}, {{codes, N * (K / 8 * bits)}, {step_w, scales}, {zero_w, scales}}) &&
+                       (N > 256 || !overlap({o}, {matrix_span(X_hat, T, K, ldx, 2), {bias, N * 4}}));
     // tiles of 256 tokens, or of 128 where their rounds of workgroups take less: a round lasts as long however few of the 256
     // compute units have a tile (GEMM alone, us, 256 -> 128 tokens a tile: 1531 tokens 4096 x 4096 78 -> 51, 4096 x 11008 226 -> 126,
     // 768 tokens 8192 x 8192 164 -> 90)
@@ -456,13 +463,12 @@ extern "C" int aweq_wonly_gemm(const void* X_hat, int64_t T, int64_t K, int64_t 
     if (rc != AWEQ_OK) return rc;
     // Byte offsets inside a tile of rows are 32-bit: whether they reach the last of `rows` tokens (512: a stage's bytes of a row)
     auto reach = [&](int64_t rows) { return (T < rows ? T : rows) - 1 <= (((1ll << 32) - 512) / 2) / ldx; };
-    const bool half = plan_walk(h, T, N, K, 128, blocks) == AWEQ_OK && (wonly::kHalfTileCost * (double)rounds_of(h) < (double)rounds_of(g) || !reach(256));
+    const bool half = plan_walk(h, T, N, K, 128, blocks) == AWEQ_OK && ((apart && wonly::kHalfTileCost * (double)rounds_of(h) < (double)rounds_of(g)) || !reach(256));
     const double tiled_cost = (half ? wonly::kHalfTileCost * (double)rounds_of(h) : (double)rounds_of(g)) * wonly::kTiledRoundCost + wonly::kDequantCost * (double)N;
     if (half) g = h;
 
     // Straight from the codes where one of the two kernels that do so is modelled to take less (both sides measured in
-    // gemm_wonly_small.hip and gemm_wonly_mid.hip).  Not where the output lies over the codes or their (Step, Z): a workgroup would
-    // store over what another still reads; the de-quantising pass is over before the GEMM stores anything.
+    // gemm_wonly_small.hip and gemm_wonly_mid.hip).
     wonly::SmallArgs a;
     a.X = reinterpret_cast<const _Float16*>(X_hat); a.codes = reinterpret_cast<const uint8_t*>(codes);
     a.step = step_w; a.zero = zero_w; a.bias = bias; a.out = out; a.ldx = ldx; a.ldo = ldo; a.T = T; a.N = N; a.K = K;
@@ -470,8 +476,6 @@ extern "C" int aweq_wonly_gemm(const void* X_hat, int64_t T, int64_t K, int64_t 
     a.group_magic = group_magic;
     const wonly::SmallPlan small = wonly::plan_small(T, N);
     const wonly::MidPlan mid = wonly::plan_mid(T, N);
-    const int64_t scales = group < 0 ? 4 : group == 0 ? N * 4 : N * (K / group) * 4;
-    const bool apart = !overlap({matrix_span(out, T, N, ldo, dtype_size(out_dt))}, {{codes, N * (K / 8 * bits)}, {step_w, scales}, {zero_w, scales}});
     const bool tiled_ok = reach(half ? 128 : 256), mid_ok = apart && (group <= 0 || group % 128 == 0) && reach(128);
     if (!tiled_ok || (apart && small.cost <= tiled_cost && (!mid_ok || small.cost <= mid.cost))) {
         // Its token tiles ride on the grid's y dimension, 65535 of 32 tokens to a launch, and its 32-bit offsets count elements: of

@@ -169,3 +169,98 @@ def test_weight_only_output_over_the_weight(B, orc, occupy, T, bits, group):
             torch.cuda.synchronize()
             got = out.cpu().numpy().astype(np.float64).reshape(T, N)
             assert np.all(np.abs(got - ref) <= K * 2.0 ** -24 * mag + 2.0 ** -11 * np.abs(ref) + 2.0 ** -24), over
+
+
+@pytest.mark.parametrize("T", [17, 200])
+@pytest.mark.parametrize("over", ["codes of X", "weight codes", "bias"])
+def test_one_tile_stores_over_what_it_read(B, occupy, T, over):
+    """The int8 GEMMs on up to 256 tokens x 256 channels with their output over an input: one workgroup, which reads first."""
+    rng = np.random.default_rng(T)
+    N = K = 256
+    xq, wq = rng.integers(-128, 128, (T, K), dtype=np.int8), rng.integers(-128, 128, (N, K), dtype=np.int8)
+    src = {"codes of X": dev(to_panels(xq)), "weight codes": dev(to_panels(wq)), "bias": dev(rng.standard_normal(N).astype(np.float32))}
+    sw, zw = dev(rng.uniform(1e-3, 2e-2, N).astype(np.float32)), dev(rng.integers(0, 256, N).astype(np.int32))
+    rx, rw = dev(xq.astype(np.int64).sum(1).astype(np.int32)), dev(wq.astype(np.int64).sum(1).astype(np.int32))
+    ds, dz, nis, ns = dev(np.float32([0.0371])), dev(np.int32([117])), dev(rng.uniform(0.2, 2.0, N).astype(np.float32)), dev(np.float32([0.9]))
+    sizes = {"i32": 4 * T * N, "f16": 2 * T * N, "fused codes": B.aweq_panel_bytes(T, N), "fused f16": 2 * T * N}
+    for kind, size in sizes.items():
+        print(f"[gpu-overlap] one tile T={T} {kind} over {over}", flush=True)
+
+        def run(apart):
+            t = dict(src)
+            raw = src[over].view(torch.uint8).reshape(-1)
+            home = torch.zeros(max(size, raw.numel()), dtype=torch.uint8, device=DEV)
+            home[:raw.numel()] = raw
+            t[over] = home[:raw.numel()].view(src[over].dtype)
+            out = (torch.zeros(size, dtype=torch.uint8, device=DEV) if apart else home)[:size]
+            cs, st = torch.zeros(N, dtype=torch.int64, device=DEV), torch.zeros(1, dtype=torch.int32, device=DEV)
+            yq, ry = torch.zeros(B.aweq_panel_bytes(T, N), dtype=torch.int8, device=DEV), torch.zeros(T, dtype=torch.int32, device=DEV)
+            torch.cuda.synchronize()
+            if not apart:
+                occupy()
+            if kind.startswith("fused"):
+                codes = kind == "fused codes"
+                B.aweq_w8a8_gemm_fused(t["codes of X"], T, K, t["weight codes"], N, ds, dz, sw, zw, rx, rw, t["bias"], 0, None if codes else out, N, cs,
+                                       next_inv_s=nis, next_step=ns, next_zero=dz, yq=out if codes else yq, rowsum_y=ry, status=st)
+            else:
+                B.aweq_w8a8_gemm(t["codes of X"], B.AWEQ_I8, T, K, K, None, ds, dz, None, rx, None, t["weight codes"], N, sw, zw, 0, rw, t["bias"],
+                                 out if kind == "i32" else None, out if kind == "f16" else None, B.AWEQ_F16, N, cs, None, st)
+            torch.cuda.synchronize()
+            return out.clone(), cs, yq, ry, st
+
+        want = run(True)
+        for _ in range(5):
+            for a, b in zip(want, run(False)):
+                assert torch.equal(a, b), (T, kind)
+
+
+@pytest.mark.parametrize("T", [1, 17, 200, 700])
+@pytest.mark.parametrize("bits", [4, 3])
+def test_weight_only_in_place(B, orc, occupy, T, bits):
+    """aweq_wonly_gemm with up to 256 channels, each row of the output over the row of X_hat that it comes from."""
+    rng = np.random.default_rng(T + bits)
+    N = K = 256
+    q = orc.quant_weight((rng.standard_normal((N, K)) * 0.02).astype(np.float16), bits, 128)
+    Wh = orc.dequant_weight_h(q["codes_u"], 128, q["step"], q["zero"])
+    codes, step, zero = dev(orc.pack_codes(q["codes_u"], bits).view(np.uint8).reshape(-1)), dev(q["step"].reshape(-1)), dev(q["zero"].reshape(-1))
+    X = rng.standard_normal((T, K)).astype(np.float16)
+    ref, mag = orc.wonly_forward(X, Wh, None)
+    ws = torch.empty(B.aweq_workspace_size(B.OP_WONLY_GEMM, T, K, N), dtype=torch.uint8, device=DEV)
+    for _ in range(5):
+        print(f"[gpu-overlap] weight-only W{bits} in place T={T}", flush=True)
+        buf = dev(X)
+        torch.cuda.synchronize()
+        occupy()
+        B.aweq_wonly_gemm(buf, T, K, K, codes, bits, 128, step, zero, N, None, buf, B.AWEQ_F16, N, ws)
+        torch.cuda.synchronize()
+        got = buf.cpu().numpy().astype(np.float64)
+        assert np.all(np.abs(got - ref) <= K * 2.0 ** -24 * mag + 2.0 ** -11 * np.abs(ref) + 2.0 ** -24)
+
+
+@pytest.mark.parametrize("dtype", [np.float16, np.float32])
+@pytest.mark.parametrize("T,N", [(30, 0), (3, 4096)])   # the quantizer, and the GEMM that could quantise three tokens itself
+def test_codes_replace_the_activation(B, orc, occupy, dtype, T, N):
+    """xq over X with one panel of columns and up to 32 tokens: the rows of one block."""
+    rng = np.random.default_rng(T)
+    K = 64
+    dt, tdt = (B.AWEQ_F16, torch.float16) if dtype == np.float16 else (B.AWEQ_F32, torch.float32)
+    X, inv_s = (rng.standard_normal((T, K)) * 3).astype(dtype), rng.uniform(0.2, 2.0, K).astype(np.float32)
+    ref = orc.quant_act(X, inv_s, np.float32(0.0371), 117)
+    ds, dz, di = dev(np.float32([0.0371])), dev(np.int32([117])), dev(inv_s)
+    wq = rng.integers(-128, 128, (max(N, 4), K), dtype=np.int8)
+    dw = dev(to_panels(wq))
+    for _ in range(5):
+        print(f"[gpu-overlap] codes over X T={T} N={N} {dtype.__name__}", flush=True)
+        buf = dev(X).view(torch.uint8).reshape(-1)
+        dX, xq = buf.view(tdt), buf[:B.aweq_panel_bytes(T, K)].view(torch.int8)
+        rs, out = torch.zeros(T, dtype=torch.int32, device=DEV), torch.zeros((T, max(N, 4)), dtype=torch.int32, device=DEV)
+        torch.cuda.synchronize()
+        occupy()
+        if N:
+            B.aweq_w8a8_gemm(dX, dt, T, K, K, di, ds, dz, xq, rs, None, dw, N, None, None, 0, None, None, out, None, B.AWEQ_F16, N, None)
+        else:
+            B.aweq_quant_act(dX, dt, T, K, K, di, ds, dz, xq, rs, None)
+        torch.cuda.synchronize()
+        assert np.array_equal(from_panels(xq.cpu().numpy(), T, K), ref["xq"]) and np.array_equal(rs.cpu().numpy(), ref["rowsum_x"])
+        if N:
+            assert np.array_equal(out.cpu().numpy(), orc.gemm_i8(ref["xq"], wq))
