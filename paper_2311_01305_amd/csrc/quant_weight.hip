@@ -296,31 +296,31 @@ __global__ __launch_bounds__(kQwBlock) void quant_weight_row(
     raise_status(status, st);
 }
 
-// ---- one (Step, Z) per group of 8 * 2^LEVELS consecutive k inside a row.  Bound by the vector unit: the slice's three
-// divisions and its reductions cost as much as quantising a unit, so a lane takes two units of a group (from 64 values on).
-// A thread takes the same units of kQgRows rows.
-constexpr int kQgRows = 2;
-template <bool F16, int BITS, int LEVELS>
+// ---- one (Step, Z) per group of 8 * 2^LEVELS consecutive k inside a row.  Large binary16 calls are bound by the vector unit: the
+// slice's three divisions and its reductions cost as much as quantising a unit, so a lane takes UNITS = 2 units of a group (from 64
+// values on) and a thread the same units of ROWS = 2 rows.  Small calls are one chain of dependent steps, which must not be longer than
+// one unit needs, and binary32 is bound by its loads, which want more and simpler threads (rule and figures at the launch).
+template <bool F16, int BITS, int LEVELS, int ROWS, int UNITS>
 __global__ __launch_bounds__(kQwBlock) void quant_weight_group(
     const void* __restrict__ W, int64_t N, int64_t K, int64_t ldw, uint8_t* __restrict__ codes,
     float* __restrict__ step, int32_t* __restrict__ zero, uint32_t* status)
 {
-    constexpr int kUnits = LEVELS >= 3 ? 2 : 1, kLanes = LEVELS - (kUnits - 1);   // units per lane; 2^kLanes lanes per group
-    const int64_t n0 = (int64_t)blockIdx.y * kQgRows;
+    constexpr int kUnits = LEVELS >= 3 ? UNITS : 1, kLanes = LEVELS - (kUnits - 1);   // units per lane; 2^kLanes lanes per group
+    const int64_t n0 = (int64_t)blockIdx.y * ROWS;
     const int64_t units = K / 8;
     const int64_t id = (int64_t)blockIdx.x * kQwBlock + threadIdx.x, g = id >> kLanes;
     const int64_t u0 = (g << LEVELS) + (id & ((1 << kLanes) - 1));
     // K % group == 0 and groups are lane-aligned, so a group is entirely in or out of range
     if (u0 >= units) return;
     uint32_t st = 0;
-    Unit<F16> reg[kQgRows][kUnits];
+    Unit<F16> reg[ROWS][kUnits];
 #pragma unroll
-    for (int i = 0; i < kQgRows; ++i)   // (past the edge: the last row again, not stored)
+    for (int i = 0; i < ROWS; ++i)   // (past the edge: the last row again, not stored)
 #pragma unroll
         for (int j = 0; j < kUnits; ++j)
             reg[i][j].load(reinterpret_cast<const char*>(W) + (size_t)min(n0 + i, N - 1) * ldw * (F16 ? 2 : 4), u0 + (j << kLanes));
 #pragma unroll
-    for (int i = 0; i < kQgRows; ++i) {
+    for (int i = 0; i < ROWS; ++i) {
         const int64_t n = n0 + i;
         if (n >= N) break;
         Extremes<F16> ex;
@@ -416,14 +416,27 @@ static void launch_row(const void* W, int64_t N, int64_t K, int64_t ldw, uint8_t
 #undef AWEQ_QR
 }
 
+template <bool F16, int BITS, int ROWS, int UNITS>
+static void launch_group_as(int levels, const void* W, int64_t N, int64_t K, int64_t ldw, uint8_t* codes,
+                            float* step, int32_t* zero, uint32_t* status, hipStream_t st)
+{
+    dim3 grid((unsigned)cdiv(levels >= 3 ? K / (8 * UNITS) : K / 8, kQwBlock), (unsigned)cdiv(N, ROWS));
+#define AWEQ_LG(L) case L: quant_weight_group<F16, BITS, L, ROWS, UNITS><<<grid, kQwBlock, 0, st>>>(W, N, K, ldw, codes, step, zero, status); break;
+    switch (levels) { AWEQ_LG(0) AWEQ_LG(1) AWEQ_LG(2) AWEQ_LG(3) AWEQ_LG(4) AWEQ_LG(5) AWEQ_LG(6) }
+#undef AWEQ_LG
+}
+
+// Rows x units of a thread (us, groups of 128, 4 bits, 1 x 1 / 2 x 1 / 2 x 2): binary16 from 2^22 values on two by two (4096 x 11008 34.7 / 33.0 /
+// 24.2, 11008 x 11008 89.8 / 82.6 / 56.4), fewer one by one (512 x 512 3.4 / 3.7 / 4.4, 64 x 4096 3.3 / 3.8 / 4.1).  Binary32 one by one
+// (11008 x 5120 46.8 / 48.6 / 55.2, 4096 x 22016 74.2 / 75.9 / 84.5).  Rows of up to 512 values leave most of a block without
+// work: from 8192 rows on two rows a thread (11008 x 256 in groups of 8 7.6 / 6.0 / 6.0, 11008 x 512 8.2 / 8.0 / 9.3; but 4096 x 512 4.8 / 5.1 / 5.5).
 template <bool F16, int BITS>
 static void launch_group(int levels, const void* W, int64_t N, int64_t K, int64_t ldw, uint8_t* codes,
                          float* step, int32_t* zero, uint32_t* status, hipStream_t st)
 {
-    dim3 grid((unsigned)cdiv(levels >= 3 ? K / 16 : K / 8, kQwBlock), (unsigned)cdiv(N, kQgRows));
-#define AWEQ_LG(L) case L: quant_weight_group<F16, BITS, L><<<grid, kQwBlock, 0, st>>>(W, N, K, ldw, codes, step, zero, status); break;
-    switch (levels) { AWEQ_LG(0) AWEQ_LG(1) AWEQ_LG(2) AWEQ_LG(3) AWEQ_LG(4) AWEQ_LG(5) AWEQ_LG(6) }
-#undef AWEQ_LG
+    if (K <= 512 && N >= 8192) launch_group_as<F16, BITS, 2, 1>(levels, W, N, K, ldw, codes, step, zero, status, st);
+    else if (F16 && K > 512 && N * K >= (1ll << 22)) launch_group_as<F16, BITS, 2, F16 ? 2 : 1>(levels, W, N, K, ldw, codes, step, zero, status, st);
+    else launch_group_as<F16, BITS, 1, 1>(levels, W, N, K, ldw, codes, step, zero, status, st);
 }
 
 }  // namespace aweq
