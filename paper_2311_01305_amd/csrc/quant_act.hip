@@ -52,8 +52,9 @@ constexpr unsigned kQaXcds = 8;                         // workgroup id % 8 name
 // without packing the codes, 7419 x 4096 binary32 29.5.
 // KEEP: the codes are stored through the caches for the GEMM that reads them next (rule and figures at the launch).
 // A thread has kBatch groups of 8 rows in flight; the first are requested ahead of Step, Z and the scales, the next after the
-// last of a group has been consumed (8192 x 4096 36.6 -> 35.4 us, 262144 x 8192 1209 -> 1199; two groups ahead of four costs
-// binary32 1 % of a whole 2048 x 512 calibration, so it keeps four).
+// last of a group has been consumed (8192 x 4096 36.6 -> 35.4 us, 262144 x 8192 1209 -> 1199).  Two groups: four take
+// binary32 210 registers, two wavefronts to a SIMD instead of three (us, 4 -> 2 groups, codes and sums: 4096 x 11008 63.8 -> 51.2,
+// 8192 x 22016 247 -> 222; sums alone 16000 x 4096 59.3 -> 50.2).
 template <bool F16, bool SUMS, bool KEEP>
 __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
     const void* __restrict__ X, int64_t T, int64_t K, int64_t ldx, const float* __restrict__ inv_s,
@@ -84,7 +85,7 @@ __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
         valid[j] = col0 + j * kPanel < K;
         pad[j] = !valid[j] && panel0 + j < np;  // zero fill of the last panel
     }
-    constexpr int kBatch = F16 ? 2 : 4, kRowsPerIter = 8 * kBatch;
+    constexpr int kBatch = 2, kRowsPerIter = 8 * kBatch;
     RawUnit<F16> raw[kBatch][kQaVpt];
     auto request = [&](int b, int j, int row) {
         if (row < nrows && valid[j]) raw[b][j].load(src0, (int64_t)row * ldx + j * kPanel);
