@@ -474,7 +474,11 @@ extern "C" int aweq_wonly_gemm(const void* X_hat, int64_t T, int64_t K, int64_t 
     a.step = step_w; a.zero = zero_w; a.bias = bias; a.out = out; a.ldx = ldx; a.ldo = ldo; a.T = T; a.N = N; a.K = K;
     a.scale_pitch = scale_pitch;
     a.group_magic = group_magic;
-    const wonly::SmallPlan small = wonly::plan_small(T, N);
+    wonly::SmallPlan small = wonly::plan_small(T, N);
+    // The few-token kernel's time falls more slowly with K than the others' (its wavefronts take 256 values each, and however few have some,
+    // eight partial sums are added; us, groups of 64, it / the tiled form: 100 tokens 32000 x 4096 126 / 137, x 1024 56 / 35, x 256
+    // 43 / 21; 512 tokens 4096 x 768 23.7 / 17.7, x 256 22.8 / 11.7)
+    small.cost *= (double)(K + 1024) / (double)(K + 384) * (8192.0 + 384.0) / (8192.0 + 1024.0);
     const wonly::MidPlan mid = wonly::plan_mid(T, N);
     const bool tiled_ok = reach(half ? 128 : 256), mid_ok = apart && (group <= 0 || group % 128 == 0) && reach(128);
     if (!tiled_ok || (apart && small.cost <= tiled_cost && (!mid_ok || small.cost <= mid.cost))) {
