@@ -22,7 +22,6 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 512;
 constexpr int kWaves = kThreads / kWave;
-constexpr int kMaxQuantLds = 64 * 1024;   // partial sums (at most 16 KiB) and the codes of a quantising launch
 
 // QX: 0: the tokens' codes are in memory (g.A).  1 / 2: every workgroup quantises the few binary16 / binary32 tokens (QuantIn) for
 // itself while its first weights are on their way, the first workgroup also for the caller: a second launch costs more
@@ -211,10 +210,12 @@ constexpr int kMaxGridY = 65535;
 template <int TT, int NT, int U, int QX = 0>
 static int launch_tile(GemmArgs g, hipStream_t st, QuantIn in = {})
 {
-    const int lds = kWaves * TT * NT * kWave * 16 + (QX != 0 ? (int)(g.T * panel_count(g.K) * kPanel) : 0);
+    constexpr int kSums = kWaves * TT * NT * kWave * 16;   // partial sums; a launch that quantises has the tokens' codes behind them
+    static_assert(QX == 0 || kSums + kQuantFewBytes <= 32768, "a launch that quantises stays below the LDS limit that has to be raised");
+    const int lds = kSums + (QX != 0 ? (int)(g.T * panel_count(g.K) * kPanel) : 0);
     const void* fn = reinterpret_cast<const void*>(gemm_i8_few<TT, NT, U, QX>);
     int dev = 0, cus = 0;
-    if (lds > 32768 && (device_cus(dev, cus) != AWEQ_OK || raise_lds_limit(fn, dev, QX != 0 ? kMaxQuantLds : lds) != AWEQ_OK)) return AWEQ_ERR_LAUNCH;
+    if (lds > 32768 && (device_cus(dev, cus) != AWEQ_OK || raise_lds_limit(fn, dev, lds) != AWEQ_OK)) return AWEQ_ERR_LAUNCH;
     void* args[] = {&g, &in};
     const int64_t tiles = cdiv(g.T, 16 * TT);
     for (int64_t first = 0; first < tiles; first += kMaxGridY) {
