@@ -318,12 +318,11 @@ static int launch_tile(GemmArgs g, hipStream_t st)
 
 }  // namespace mid
 
-// the tile whose rounds of 256 workgroups are cheaper (us at K = 8192, as in the plans of the other forms: rounds of 64 x 128
-// tiles were measured at 32.5, of 128 x 128 tiles at 42.5)
+// the tile whose rounds of 256 workgroups are cheaper (us at K = 8192 as measured, as in the plans of the other forms)
 MidPlan plan_mid(int64_t T, int64_t N)
 {
     auto rounds = [&](int bm, int bn) { return (double)cdiv(cdiv(T, bm) * cdiv(N, bn), 256); };
-    const double c12 = 32.0 * rounds(64, 128), c22 = 43.0 * rounds(128, 128);
+    const double c12 = 32.5 * rounds(64, 128), c22 = 42.5 * rounds(128, 128);
     return c12 <= c22 ? MidPlan{false, c12} : MidPlan{true, c22};
 }
 
