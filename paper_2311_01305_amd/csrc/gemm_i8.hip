@@ -483,12 +483,12 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
 #undef RDB
 
         // ---- epilogue.  With the weight fragment as first MFMA operand, register v of lane l in
-        // sub-tile (i, j) is token t = m0 + 128 wm + 32 i + l % 32 and output channel
+        // sub-tile (i, j) is token t = m0 + 32 MI wm + 32 i + l % 32 and output channel
         // n = n0 + 64 wn + 32 j + 8 (v / 4) + 4 (l / 32) + v % 4: four consecutive n per register quad.
         // Each wave turns its 32 (t) x 64 (n) slab of sub-tile row i around in a private 8 KiB LDS
         // region (rows of 256 bytes, 16-byte chunks XOR swizzled: conflict-free both ways) so that a
         // lane then holds 16 bytes of one output row and 16 lanes cover 256 contiguous bytes per store.
-        // The slabs live in the last ring slot and behind the ring; the next tile's first three
+        // The slabs live in the last ring slot and behind the ring; the next tile's first kAhead
         // panels are already on their way into the other slots.
         const int rd_r = lane >> 4, rd_c = lane & 15;
         const int64_t t_lane = cm0 + wm * (32 * MI) + rd_r;              // + 32 i + 4 p

@@ -205,7 +205,6 @@ __global__ __launch_bounds__(kThreads) void gemm_f16_kernel(Args g)
     if (ns > 1) wait_vm<TL::kNewest>(); else wait_vm<0>();
 
     // Vector memory operations of a wave complete in the order issued.  A tile that lies inside the
-    // Vector memory operations of a wave complete in the order issued.  A tile that lies inside the
     // output issues 8 MI stores per wave after requesting the next tile's first stages, so "at most
     // that many + kNewest operations pending" means stage 0 has landed while the stores (and the loads
     // of stage 1) may still be on their way.
@@ -352,7 +351,7 @@ __global__ __launch_bounds__(kThreads) void gemm_f16_kernel(Args g)
         stage(s, std::false_type{}, std::false_type{});
 
         // ---- epilogue.  With the weight fragment as first MFMA operand, register v of lane l in
-        // sub-tile (i, j) is token t = m0 + 128 wm + 32 i + l % 32 and output channel
+        // sub-tile (i, j) is token t = m0 + 32 MI wm + 32 i + l % 32 and output channel
         // n = n0 + 64 wn + 32 j + 8 (v / 4) + 4 (l / 32) + v % 4.  Each wave turns its 32 (t) x 64 (n)
         // slab of sub-tile row i around in a private 8 KiB LDS region (256-byte rows, XOR-swizzled
         // 16-byte chunks) so that 16 lanes cover one output row of the slab per store.  The slabs live
