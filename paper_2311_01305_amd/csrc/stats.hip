@@ -41,7 +41,7 @@ inline size_t stats_ws_bytes(int64_t rows, int64_t K)
     // sized for the narrower lane width (more chunks never increases the slice count)
     StatsPlan a = stats_plan(rows, K, 8), b = stats_plan(rows, K, 4);
     int s = a.slices > b.slices ? a.slices : b.slices;
-    return (size_t)s * (size_t)K * (sizeof(float) * 2 + sizeof(double)) + 16;   // (16: part of the size callers were always asked for)
+    return (size_t)s * (size_t)K * (sizeof(float) * 2 + sizeof(double)) + 16;   // partial rows, then the merge kernel's ticket
 }
 
 constexpr int64_t kKeepBytes = kCacheBytes * 3 / 8;
@@ -67,10 +67,11 @@ __device__ __forceinline__ Float4 load_once(const float* p)
 template <bool KEEP>
 __global__ __launch_bounds__(kStatsBlock) void col_stats_partial_f16(
     const _Float16* __restrict__ M, int64_t rows, int64_t K, int64_t ld, int64_t rows_per_slice,
-    float* __restrict__ pmin, float* __restrict__ pmax, double* __restrict__ psum)
+    float* __restrict__ pmin, float* __restrict__ pmax, double* __restrict__ psum, uint32_t* __restrict__ ticket)
 {
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *ticket = 0u;   // (for the merge kernel that follows on the stream)
     const int64_t col = ((int64_t)blockIdx.x * kWave + lane) * 8;
     const bool active = col < K;
     const int64_t r_begin = (int64_t)blockIdx.y * rows_per_slice;
@@ -154,10 +155,11 @@ __global__ __launch_bounds__(kStatsBlock) void col_stats_partial_f16(
 template <bool KEEP>
 __global__ __launch_bounds__(kStatsBlock) void col_stats_partial_f32(
     const float* __restrict__ M, int64_t rows, int64_t K, int64_t ld, int64_t rows_per_slice,
-    float* __restrict__ pmin, float* __restrict__ pmax, double* __restrict__ psum)
+    float* __restrict__ pmin, float* __restrict__ pmax, double* __restrict__ psum, uint32_t* __restrict__ ticket)
 {
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *ticket = 0u;   // (for the merge kernel that follows on the stream)
     const int64_t col = ((int64_t)blockIdx.x * kWave + lane) * 4;
     const bool active = col < K;
     const int64_t r_begin = (int64_t)blockIdx.y * rows_per_slice;
@@ -227,16 +229,21 @@ __global__ __launch_bounds__(kStatsBlock) void col_stats_partial_f32(
 // the fp64 sums are reproducible.
 // finalize: r = max - min per channel is written with the columns; R = tensor max - tensor min and
 // p = r / R (Eq. 4) need every block's columns.  Each block leaves its extremes in its own (already read)
-// columns of the first partial row, and a second small kernel finds R and writes p.  (One launch whose last
-// block, found by a ticket, writes r, R and p took 8.0 / 12.6 / 23 us at K = 512 / 4096 / 11008: every
-// block's device-wide fence and three atomics on one cache line, 37 ns each; two launches take 5.9 / 6.5 / 7.4.)
+// columns of the first partial row, and a second small kernel finds R and writes p.  ONE: the last block, found by
+// a ticket, does that in the same launch.  Every block's device-wide fence and atomic stands in a row with the others', so
+// only few blocks do so (whole binary16 call, us, one launch / two: 64 tokens x 128 channels 10.2 / 11.4, 1 x 512 10.3 / 11.2,
+// 1 x 1024 10.9 / 11.5; 4096 x 1280 14.2 / 11.4, 4096 x 2048 16.4 / 11.7).
 constexpr int kMergeCols = 32, kMergeParts = 32;
+constexpr int64_t kOneMergeK = 1024;
+static_assert(kOneMergeK <= kMergeCols * kMergeCols && kOneMergeK <= kMergeCols * kMergeParts, "the last block reads an extreme a lane, a column a thread");
+template <bool ONE>
 __global__ __launch_bounds__(kMergeCols * kMergeParts) void col_stats_merge(
     float* pmin, float* pmax, const double* __restrict__ psum,
     int slices, int64_t K, int64_t rows, float* cmin, float* cmax,
     double* __restrict__ csum, uint64_t* __restrict__ count, int accumulate, uint32_t* status,
-    int finalize, float* __restrict__ r)
+    int finalize, float* __restrict__ r, float* __restrict__ R, float* __restrict__ p, uint32_t* ticket)
 {
+    __shared__ int s_last;
     __shared__ float s_a[kMergeParts][kMergeCols], s_b[kMergeParts][kMergeCols];
     __shared__ double s_s[kMergeParts][kMergeCols];
     const int c = threadIdx.x & (kMergeCols - 1), part = threadIdx.x / kMergeCols;
@@ -275,7 +282,29 @@ __global__ __launch_bounds__(kMergeCols * kMergeParts) void col_stats_merge(
         // this block's extremes (lanes past K hold the identities)
         a = group_allreduce<5>(k < K ? a : INFINITY, OpMin());
         b = group_allreduce<5>(k < K ? b : -INFINITY, OpMax());
-        if (c == 0) { pmin[k] = a; pmax[k] = b; }
+        if (c == 0) {
+            pmin[k] = a;
+            pmax[k] = b;
+            if constexpr (ONE) {
+                __threadfence();   // the extremes and this wavefront's r are visible device-wide before the ticket is
+                s_last = atomicAdd(ticket, 1u) == gridDim.x - 1;
+            }
+        }
+    }
+    if constexpr (ONE) {
+        if (!finalize) return;
+        __syncthreads();
+        if (!s_last) return;
+        __threadfence();           // every other block's extremes and r are visible to this one
+        auto seen = [](const float* q) { return __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+        const bool ratio = p && (int64_t)threadIdx.x < K;
+        const float rk = ratio ? seen(&r[threadIdx.x]) : 0.0f;
+        const bool some = c < (int)gridDim.x;
+        a = group_allreduce<5>(some ? seen(&pmin[c * kMergeCols]) : INFINITY, OpMin());
+        b = group_allreduce<5>(some ? seen(&pmax[c * kMergeCols]) : -INFINITY, OpMax());
+        const float RR = (b - a) + 0.0f;
+        if (threadIdx.x == 0) *R = RR;
+        if (ratio) p[threadIdx.x] = rk / RR;
     }
 }
 
@@ -314,6 +343,7 @@ static int run_calib_stats(const void* M, aweq_dtype dt, int64_t rows, int64_t K
     double* psum = reinterpret_cast<double*>(ws);
     float* pmin = reinterpret_cast<float*>(psum + (size_t)plan.slices * K);
     float* pmax = pmin + (size_t)plan.slices * K;
+    uint32_t* ticket = reinterpret_cast<uint32_t*>(pmax + (size_t)plan.slices * K);
     dim3 grid(plan.col_chunks, plan.slices);
     // A matrix that fits the memory-side cache together with what the next pass over it writes (the folded weight and its codes: 2.5
     // times its size) is read through the caches, where that pass finds it: fold + quantise 4096 x 11008 (90 MB) 51.0 -> 42.9 us,
@@ -321,13 +351,16 @@ static int run_calib_stats(const void* M, aweq_dtype dt, int64_t rows, int64_t K
     // neither cache the two kinds of loads take the same up to 90 MB (25.9 / 26.1 us with the merge), beyond it plain ones
     // are slower (134 MB 35.0 -> 36.1, 262 MB 53.1 -> 55.7).
     const bool keep = rows * K * (int64_t)dtype_size(dt) <= kKeepBytes;
-#define AWEQ_CS(F, E, P) col_stats_partial_##F<P><<<grid, kStatsBlock, 0, st>>>(reinterpret_cast<const E*>(M), rows, K, ld, plan.rows_per_slice, pmin, pmax, psum)
+#define AWEQ_CS(F, E, P) col_stats_partial_##F<P><<<grid, kStatsBlock, 0, st>>>(reinterpret_cast<const E*>(M), rows, K, ld, plan.rows_per_slice, pmin, pmax, psum, ticket)
     if (dt == AWEQ_F16) { if (keep) AWEQ_CS(f16, _Float16, true); else AWEQ_CS(f16, _Float16, false); }
     else { if (keep) AWEQ_CS(f32, float, true); else AWEQ_CS(f32, float, false); }
 #undef AWEQ_CS
-    col_stats_merge<<<(unsigned)cdiv(K, kMergeCols), kMergeCols * kMergeParts, 0, st>>>(
-        pmin, pmax, psum, plan.slices, K, rows, cmin, cmax, csum, count, accumulate, status, finalize, r);
-    if (finalize) col_stats_finish<<<(unsigned)cdiv(p ? K : 1, kFinishBlock), kFinishBlock, 0, st>>>(pmin, pmax, K, r, R, p);
+    const bool one = finalize && K <= kOneMergeK;
+    const unsigned blocks = (unsigned)cdiv(K, kMergeCols);
+#define AWEQ_CM(ONE) col_stats_merge<ONE><<<blocks, kMergeCols * kMergeParts, 0, st>>>(pmin, pmax, psum, plan.slices, K, rows, cmin, cmax, csum, count, accumulate, status, finalize, r, R, p, ticket)
+    if (one) AWEQ_CM(true); else AWEQ_CM(false);
+#undef AWEQ_CM
+    if (finalize && !one) col_stats_finish<<<(unsigned)cdiv(p ? K : 1, kFinishBlock), kFinishBlock, 0, st>>>(pmin, pmax, K, r, R, p);
     return launch_status();
 }
 
@@ -394,7 +427,7 @@ extern "C" int aweq_calib_stats_static(const void* M, aweq_dtype dt, int64_t row
     void* ptr = nullptr;
     const int src = static_scratch(&ptr);
     if (src != AWEQ_OK) return src;
-    // every partial row the merge reads is written by this call's first
+    // every partial row the merge reads and its ticket are written by this call's first
     // kernel: the array's contents from earlier calls never matter and nothing has to be cleared
     return run_calib_stats(M, dt, rows, K, ld, cmin, cmax, csum, count, accumulate, finalize, r, R, p, ptr, status,
                            as_stream(stream));
