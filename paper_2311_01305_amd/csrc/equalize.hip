@@ -7,13 +7,14 @@ namespace aweq {
 // only: it is over all channels and the call has no scratch memory), the equalised activation range with the static
 // int8 activation quantizer (Eq. 2 on the range of X_hat).  Bound by the round trips of a block's loads, so a thread of
 // the one block requests kScaleBatch channels before it uses the first, and then by its fp64 square roots and divisions: 1 us
-// per 1024 channels.  Up to kOneBlockK channels one block does everything; beyond, a block per 1024 channels (a thread
-// has one channel then) and a launch of equalize_range (us, one channel at a time in one block -> one block / two
-// launches: K = 4096 7.9 -> 6.2, 8192 14.3 -> 7.7, 11008 16.5 -> 7.8).  equalize_range reads xmin and xmax again, so a
+// per 1024 channels.  Up to kOneBlockK channels one block does everything, and up to kOneBlockRangeK where the range is asked
+// for, which costs several blocks a second launch; beyond, a block per 1024 channels (a thread has one channel then) and
+// a launch of equalize_range (us, back to back, one block / two launches: K = 4104 6.4 / 9.0, 5120 7.3 / 9.0, 6144 8.1 / 9.3,
+// 7168 8.7 / 9.3, 8192 9.4 / 9.2, 11008 11.9 / 9.0; without the range 4608 6.4 / 6.0, 8192 9.3 / 5.9).  equalize_range reads xmin and xmax again, so a
 // call whose vectors replace them stays with one block, which has read a channel's statistics before it writes the channel.
 constexpr int kScaleBatch = 4;
 constexpr int kScaleBlock = 1024;
-constexpr int64_t kOneBlockK = 4096;
+constexpr int64_t kOneBlockK = 4096, kOneBlockRangeK = 7168;
 
 // extremes of the equalised activation -> its range and quantizer (every thread of the one block calls it)
 __device__ __forceinline__ void finish_range(float lo, float hi, float* slot, float* xhat_range, float* act_step,
@@ -179,10 +180,12 @@ extern "C" int aweq_equalize(const float* xmin, const float* xmax, const double*
             return AWEQ_ERR_ALIGN;
     }
     hipStream_t st = as_stream(stream);
-    const bool one = K <= kOneBlockK || overlap({{s, K * 4}, {inv_s, K * 4}, {mu_xhat, K * 4}, {prev_scale, K * 4}}, {{xmin, K * 4}, {xmax, K * 4}});
+    const bool range = xhat_range || act_step;
+    const bool one = K <= (range ? kOneBlockRangeK : kOneBlockK) ||
+                     overlap({{s, K * 4}, {inv_s, K * 4}, {mu_xhat, K * 4}, {prev_scale, K * 4}}, {{xmin, K * 4}, {xmax, K * 4}});
     equalize_scales<<<one ? 1u : (unsigned)cdiv(K, kScaleBlock), kScaleBlock, 0, st>>>(
         xmin, xmax, xsum, count, wmin, wmax, K, enable_awe, s, inv_s, prev_scale, xhat_range, mu_xhat, act_step, act_zero, status, one);
-    if (!one && (xhat_range || act_step))
+    if (!one && range)
         equalize_range<<<1, kScaleBlock, 0, st>>>(xmin, xmax, inv_s, K, xhat_range, act_step, act_zero, status);
     if (W) {
         const int E = dt == AWEQ_F16 ? 8 : 4;

@@ -67,3 +67,21 @@ def test_ranges_and_scales(B, orc, K):
     bound = 1e-6 * np.abs(X.astype(np.float64)).mean(axis=0) * inv + 1e-30
     assert np.all(np.abs(mu.cpu().numpy() - X.astype(np.float64).mean(axis=0) * inv) <= bound)
     assert st.item() & B.ST_SCALEGUARD
+
+
+@pytest.mark.parametrize("K", [5120, 7168, 7176])
+def test_both_sides_of_one_block_with_a_range(B, orc, K):
+    """With the range asked for, one block serves up to 7168 channels; without it, several from 4104 on: the same scales."""
+    test_ranges_and_scales(B, orc, K)
+    g = torch.Generator(device=DEV).manual_seed(K)
+    lo, hi = -torch.rand(2, K, generator=g, device=DEV) - 0.1, torch.rand(2, K, generator=g, device=DEV)
+    xsum = torch.randn(K, generator=g, device=DEV, dtype=torch.float64)
+    outs = []
+    for want in (True, False):
+        s, inv_s, mu = (torch.zeros(K, device=DEV) for _ in range(3))
+        rng, step, zero = torch.zeros(2, device=DEV), torch.zeros(1, device=DEV), torch.zeros(1, dtype=torch.int32, device=DEV)
+        B.aweq_equalize(lo[0], hi[0], xsum, 100, lo[1], hi[1], K, 1, s, inv_s, None, None, B.AWEQ_F16, 0, K, K, None, rng if want else None, mu,
+                        step if want else None, zero if want else None)
+        outs.append((s, inv_s, mu))
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
