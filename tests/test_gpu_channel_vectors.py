@@ -85,3 +85,15 @@ def test_both_sides_of_one_block_with_a_range(B, orc, K):
         outs.append((s, inv_s, mu))
     for a, b in zip(*outs):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("K,ld,offset", [(192, 192, 0), (200, 200, 0), (192, 200, 0), (192, 256, 8), (2048, 2048, 0), (2056, 2112, 0)])
+def test_folded_rows_of_whole_lines_and_others(B, K, ld, offset):
+    """The binary16 fold reads rows of whole 128-byte lines non-temporally and others through the caches: RN16(RN32(w s)) either way."""
+    N = 37
+    g = torch.Generator(device=DEV).manual_seed(K + ld)
+    W = torch.randn(N * ld + offset, generator=g, device=DEV).half()[offset:].view(N, ld)
+    lo, hi = -torch.rand(2, K, generator=g, device=DEV) - 0.1, torch.rand(2, K, generator=g, device=DEV)
+    s, inv_s, out = torch.zeros(K, device=DEV), torch.zeros(K, device=DEV), torch.full((N, K), 9.0, dtype=torch.float16, device=DEV)
+    B.aweq_equalize(lo[0], hi[0], None, 0, lo[1], hi[1], K, 1, s, inv_s, W, out, B.AWEQ_F16, N, ld, K, None, None, None, None, None)
+    assert torch.equal(out, (W[:, :K].float() * s).half())
