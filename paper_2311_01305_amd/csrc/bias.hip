@@ -315,7 +315,12 @@ extern "C" int aweq_bias_correct(int mode, const void* W_hat, aweq_dtype dt, int
         // whose channel takes eight registers, INT3 4096 x 11008 49.4 -> 30.0, INT4 8192 x 8192 55.7 -> 45.5; binary16 8-bit groups
         // 4096 x 11008 24.1 -> 22.7, INT3 4096 x 11008 21.1 -> 20.4, INT4 1000 x 16384 14.0 -> 9.9; but 8-bit rows 8192 x 22016 105 -> 114)
         const bool four = f16 && N >= 8192 && !(bits == 8 && group > 0);
-#define AWEQ_BW(F, B) do { if (K <= 1024) AWEQ_BWS(F, B, 64, 2); else if (F && four) AWEQ_BWS(F, B, 256, F ? 4 : 2); else AWEQ_BWS(F, B, 256, 2); } while (0)
+        // Few channels of long rows are bound by the passes over a row: 512 threads on one channel (us, 256 x 2 -> 512 x 1: binary32
+        // INT4 64 x 21632 7.8 -> 5.5, 3664 x 8576 23.5 -> 21.9; binary16 INT3 256 x 17216 6.8 -> 5.6, 1280 x 11008 9.3 -> 8.8, but 2048 x
+        // 11008 11.8 -> 12.2; 8-bit rows, whose panels neighbouring channels share, 512 x 13248 7.1 -> 5.8, 1000 x 16384 11.4 -> 12.7;
+        // up to K = 8192 the two take the same)
+        const bool longrows = K > 8192 && N <= (bits == 8 && group <= 0 ? 512 : f16 ? 1280 : 4096);
+#define AWEQ_BW(F, B) do { if (K <= 1024) AWEQ_BWS(F, B, 64, 2); else if (longrows) AWEQ_BWS(F, B, 512, 1); else if (F && four) AWEQ_BWS(F, B, 256, F ? 4 : 2); else AWEQ_BWS(F, B, 256, 2); } while (0)
         if (f16) { if (bits == 8) AWEQ_BW(true, 8); else if (bits == 4) AWEQ_BW(true, 4); else AWEQ_BW(true, 3); }
         else { if (bits == 8) AWEQ_BW(false, 8); else if (bits == 4) AWEQ_BW(false, 4); else AWEQ_BW(false, 3); }
 #undef AWEQ_BW

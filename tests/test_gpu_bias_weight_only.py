@@ -35,3 +35,10 @@ def test_bias_weight_only(orc, dtype, N, K, bits, group):
     scale = np.max(np.abs(d_ref))
     assert np.max(np.abs(delta.cpu().numpy() - d_ref)) <= 1e-6 * scale
     assert np.max(np.abs(out.cpu().numpy() - b_ref)) <= 1e-6 * max(scale, np.max(np.abs(b_ref)))
+
+
+@pytest.mark.parametrize("bits,group", [(8, 0), (8, 64), (4, -1), (4, 64), (3, 0), (3, 64)])
+@pytest.mark.parametrize("dtype,N,K", [(np.float16, 1, 8256), (np.float32, 3, 8192), (np.float32, 3, 8256), (np.float32, 5, 22016), (np.float16, 1281, 8256), (np.float16, 513, 8256)])
+def test_few_channels_of_long_rows(orc, dtype, N, K, bits, group):
+    """512 threads on one channel (more than 8192 values, few channels), and both sides of the limits of K and N."""
+    test_bias_weight_only(orc, dtype, N, K, bits, group)
