@@ -806,7 +806,10 @@ static int plan_tiled(GemmArgs& g, bool& half, double& cost, int64_t& blocks)
     const int rc = plan_walk(g, g.T, g.N, g.K, BM, blocks);
     if (rc != AWEQ_OK) return rc;
     cost = (double)rounds_of(g);
-    half = plan_walk(h, h.T, h.N, h.K, BM / 2, blocks_h) == AWEQ_OK && kHalfTileCost * (double)rounds_of(h) < cost;
+    // (from seven rounds on a workgroup's idle ids in some rounds make up for each other, which the count of rounds does not see: 8230 tokens
+    // 14720 x 1024 / 14720 x 4096 169 / 487 with 256 tokens per tile, 176 / 501 with 128, modelled 9 and 8.55 rounds)
+    half = plan_walk(h, h.T, h.N, h.K, BM / 2, blocks_h) == AWEQ_OK && kHalfTileCost * (double)rounds_of(h) < cost &&
+           cdiv(g.T, BM) * cdiv(g.N, BM) <= 6 * 256;
     if (half) { g = h; cost = kHalfTileCost * (double)rounds_of(h); }
     return AWEQ_OK;
 }
