@@ -928,7 +928,10 @@ extern "C" int aweq_w8a8_gemm(const void* X, aweq_dtype x_dt, int64_t T, int64_t
 
     // the form whose rounds of workgroups are modelled to take least
     const FewPlan few = plan_few(T, N);
-    const MidPlan mid = plan_mid(T, N);
+    MidPlan mid = plan_mid(T, N);
+    // Short rows in several rounds are mostly epilogue, which the persistent tiled form overlaps with the next tile (us, 128 x 128 tiles / tiled:
+    // 8583 tokens 1920 x 360 34.6 / 24.9, the GEMM of 2987 tokens 2688 x 160 18.2 / 17.0)
+    if (K <= 512 && mid.cost > 43.0) mid.cost *= 1.2;
     // one to four tokens: the few-token form quantises them itself, one launch instead of two (us per call, one / four tokens:
     // 4096 x 4096 9.2 -> 7.9 / 9.4 -> 9.3, 11008 x 4096 14.8 -> 12.5 / 15.2 -> 14.2, 1536 x 2048 8.5 -> 6.0 / 8.5 -> 7.0; no more than
     // 16 KiB of codes: every workgroup repeats the work).  Not where an output lies over what the quantizer reads: a workgroup would

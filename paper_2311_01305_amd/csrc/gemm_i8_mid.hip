@@ -318,11 +318,14 @@ static int launch_tile(GemmArgs g, hipStream_t st)
 
 }  // namespace mid
 
-// the tile whose rounds of 256 workgroups are cheaper (us at K = 8192 as measured, as in the plans of the other forms)
+// the tile whose rounds of 256 workgroups are cheaper (us at K = 8192, as in the plans of the other forms: one round of 64 x 128
+// tiles was measured at 32.5, of 128 x 128 tiles at 42.5).  Rounds after the first come dearer, their workgroups do not overlap
+// the end of one tile with the start of the next as the persistent form's do: four of 128 x 128 tiles against three of the persistent
+// 128 x 256 ones 195 / 169 us (6581 tokens 2432 x 7616), 68.7 / 54.4 (7173 tokens 2104 x 1600)
 MidPlan plan_mid(int64_t T, int64_t N)
 {
     auto rounds = [&](int bm, int bn) { return (double)cdiv(cdiv(T, bm) * cdiv(N, bn), 256); };
-    const double c12 = 32.5 * rounds(64, 128), c22 = 42.5 * rounds(128, 128);
+    const double r22 = rounds(128, 128), c12 = 32.0 * rounds(64, 128), c22 = (r22 >= 4.0 ? 48.0 : 43.0) * r22;
     return c12 <= c22 ? MidPlan{false, c12} : MidPlan{true, c22};
 }
 
