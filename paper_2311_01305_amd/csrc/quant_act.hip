@@ -346,10 +346,11 @@ int launch_quant_act(const void* X, aweq_dtype dt, int64_t T, int64_t K, int64_t
     // (K = 4096 / 11008, us, panel form -> row form: 1 token 7.1 -> 3.1 / 7.9 -> 4.6, 256: 10.1 -> 3.8 / 13.8 -> 6.5,
     // 2048: 13.0 -> 8.9 / 27.0 -> 18.1, 8192: 30.3 -> 26.7 / 68.2 -> 65.9, but 119 -> 128 at K = 22016); one row per block
     // up to 256 tokens, two up to 1024 (1024 tokens, 1 / 2 / 4 rows: 6.8 / 5.5 / 6.0).  Rows of up to 512 columns, one chunk of the panel
-    // form, which then needs no merge, leave most of a block idle: up to 2048 tokens (K = 64 / 512, 2048 tokens 5.5 -> 4.8 / 7.3 -> 4.9,
-    // 2500 tokens 5.6 -> 7.0 / 7.3 -> 7.1, binary32 4096 tokens 5.3 -> 7.6 / 8.4 -> 9.9).  Not where an output lies over what other
+    // form, which then needs no merge, leave most of a block idle: up to 2048 tokens where a row's sum is asked for (K = 64 / 512, 2048 tokens 5.5 -> 4.8 / 7.3 -> 4.9,
+    // 2500 tokens 5.6 -> 7.0 / 7.3 -> 7.1, binary32 4096 tokens 5.3 -> 7.6 / 8.4 -> 9.9;
+    // without the sums 2758 tokens K = 448 6.3 -> 4.8, 4051 tokens K = 120 5.9 -> 5.2).  Not where an output lies over what other
     // blocks still read: the panel form's merge writes the row sums in a launch of its own, and its blocks have 32 rows or more.
-    if (!colsum_xq && xq && aligned16(inv_s) && T <= (K <= kQaPanels * kPanel ? 2048 : 4096) &&
+    if (!colsum_xq && xq && aligned16(inv_s) && T <= (rowsum_x && K <= kQaPanels * kPanel ? 2048 : 4096) &&
         !overlap({{rowsum_x, T * 4}, {xq, T * panel_count(K) * kPanel}}, {matrix_span(X, T, K, ldx, dtype_size(dt)), {inv_s, K * 4}, {act_step, 4}, {act_zero, 4}})) {
 #define AWEQ_QR(F, R) quant_act_rows<F, R><<<(unsigned)cdiv(T, R), kQrBlock, 0, st>>>(X, T, K, ldx, inv_s, act_step, act_zero, xq, rowsum_x, status)
         if (dt == AWEQ_F16) { if (T <= 256) AWEQ_QR(true, 1); else if (T <= 1024) AWEQ_QR(true, 2); else AWEQ_QR(true, 4); }
