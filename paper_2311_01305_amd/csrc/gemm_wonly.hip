@@ -477,10 +477,12 @@ extern "C" int aweq_wonly_gemm(const void* X_hat, int64_t T, int64_t K, int64_t 
     // The few-token kernel's time falls more slowly with K than the others' (its wavefronts take 256 values each, and however few have some,
     // eight partial sums are added; us, groups of 64, it / the tiled form: 100 tokens 32000 x 4096 126 / 137, x 1024 56 / 35, x 256
     // 43 / 21; 512 tokens 4096 x 768 23.7 / 17.7, x 256 22.8 / 11.7)
-    small.cost *= (double)(K + 1024) / (double)(K + 384) * (8192.0 + 384.0) / (8192.0 + 1024.0);
+    if (K < 8192) small.cost *= (double)(K + 1024) / (double)(K + 384) * (8192.0 + 384.0) / (8192.0 + 1024.0);
     const wonly::MidPlan mid = wonly::plan_mid(T, N);
     const bool tiled_ok = reach(half ? 128 : 256), mid_ok = apart && (group <= 0 || group % 128 == 0) && reach(128);
-    if (!tiled_ok || (apart && small.cost <= tiled_cost && (!mid_ok || small.cost <= mid.cost))) {
+    // the de-quantising pass is a launch more, about 0.6 us of such small calls (312 tokens 2532 x 64, groups of 64, 8.3 / 9.6)
+    const double launch_cost = 0.6 * 8192.0 / (double)K;
+    if (!tiled_ok || (apart && small.cost <= tiled_cost + launch_cost && (!mid_ok || small.cost <= mid.cost))) {
         // Its token tiles ride on the grid's y dimension, 65535 of 32 tokens to a launch, and its 32-bit offsets count elements: of
         // pitches beyond their reach (2^27 for a tile of 32 tokens) a launch takes the tokens that they reach.
         const int64_t last = ((1ll << 32) - 1 - K) / ldx, step = last >= 31 ? 65535 * 32 : last + 1;

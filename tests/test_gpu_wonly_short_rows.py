@@ -30,3 +30,10 @@ def test_few_input_channels(orc, bits, T, N, K):
     torch.cuda.synchronize()
     got = out.cpu().numpy().astype(np.float64)
     assert np.all(np.abs(got - ref) <= K * 2.0 ** -24 * mag + 2.0 ** -11 * np.abs(ref) + 2.0 ** -24)
+
+
+@pytest.mark.parametrize("bits", [4, 3])
+@pytest.mark.parametrize("T,N,K", [(312, 2532, 64), (1309, 616, 128), (512, 1024, 8192), (512, 1024, 8256)])
+def test_on_both_sides_of_the_added_launch(orc, bits, T, N, K):
+    """Calls so small that the de-quantising launch decides, and K beyond which the few-token kernel's cost has no offset."""
+    test_few_input_channels(orc, bits, T, N, K)
