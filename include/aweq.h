@@ -64,7 +64,8 @@ typedef enum {
     AWEQ_OP_W8A8_GEMM = 3,
     AWEQ_OP_BIAS_CORRECT = 4,
     AWEQ_OP_WONLY_GEMM = 5,
-    AWEQ_OP_QUANT_ACT = 6
+    AWEQ_OP_QUANT_ACT = 6,
+    AWEQ_OP_CALIBRATE = 7
 } aweq_op;
 
 enum { AWEQ_BIAS_W8A8 = 0, AWEQ_BIAS_WEIGHT_ONLY = 1 };
@@ -287,6 +288,56 @@ int aweq_wonly_gemm(const void* X_hat, int64_t T, int64_t K, int64_t ldx,
                     const float* step_w, const int32_t* zero_w, int64_t N,
                     const float* bias, void* out, aweq_dtype out_dt, int64_t ldo,
                     void* ws, size_t ws_bytes, uint32_t* status, void* stream);
+
+/* ---- Stages 1 - 5 in one call: the calibration of a layer, or of any number of layers that read the same activation (n_weights > 1:
+ * one scale from the merged weight ranges, one activation quantizer, W8A8 per channel).  The outputs are those of the stage entry points
+ * called one after the other; the launches are fewer where the shapes allow (workspace of
+ * aweq_workspace_size(AWEQ_OP_CALIBRATE, T, K, sum of the N); with less, down to what the stages ask for, they run one by one).
+ * Sums in binary64 (xsum, delta) are added in another order than the stages add them; everything else is the same to the bit.
+ * Nullable: count, wcount, p_x, p_w, status; bias_in; rowsum_w and colsum_acc where no stage needs them; xq and rowsum_x without the
+ * forward; out_i32 and out_deq.  W_hat may take the place of W (same pitch).  Output pitch N. */
+typedef struct {
+    const void* X;              /* [T x K], pitch ldx */
+    aweq_dtype dt;              /* of X, every W and W_hat, and out_deq */
+    int64_t T, K, ldx;
+    float *xmin, *xmax;         /* stage 1 */
+    double* xsum;
+    uint64_t* count;
+    float *r_x, *R_x, *p_x;
+    float *wmin, *wmax;
+    uint64_t* wcount;
+    float *r_w, *R_w, *p_w;
+    float *s, *inv_s;           /* stage 2 */
+    float *xhat_range, *mu_xhat, *act_step;
+    int32_t* act_zero;
+    int8_t* xq;                 /* stage 4a */
+    int32_t* rowsum_x;
+    int64_t* colsum_xq;
+    int enable_awe, enable_bc;
+    int bits, group;            /* stage 3 */
+    int w8a8, forward;          /* int8 path (else weight-only); with the GEMM */
+    int fused_weight_pass;      /* where the stages run one by one: aweq_fold_quant_weight (group = 0) */
+    void* ws;
+    size_t ws_bytes;
+    uint32_t* status;
+} aweq_calib_layer;
+
+typedef struct {
+    const void* W;              /* [N x K], pitch ldw */
+    int64_t N, ldw;
+    void* W_hat;                /* pitch ldwh */
+    int64_t ldwh;
+    void* codes;
+    float* step_w;
+    int32_t *zero_w, *rowsum_w;
+    const float* bias_in;
+    float *delta, *bias_out;
+    int32_t* out_i32;
+    void* out_deq;
+    int64_t* colsum_acc;
+} aweq_calib_weight;
+
+int aweq_calibrate(const aweq_calib_layer* layer, const aweq_calib_weight* weights, int n_weights, void* stream);   /* both host structures */
 
 #ifdef __cplusplus
 }

@@ -13,7 +13,7 @@ _LIB_PATH = os.path.join(_HERE, "libaweq.so")
 _lib = None
 
 AWEQ_F32, AWEQ_F16, AWEQ_I8 = 0, 1, 2
-OP_CALIB_STATS, OP_EQUALIZE, OP_QUANT_WEIGHT, OP_W8A8_GEMM, OP_BIAS_CORRECT, OP_WONLY_GEMM, OP_QUANT_ACT = 0, 1, 2, 3, 4, 5, 6
+OP_CALIB_STATS, OP_EQUALIZE, OP_QUANT_WEIGHT, OP_W8A8_GEMM, OP_BIAS_CORRECT, OP_WONLY_GEMM, OP_QUANT_ACT, OP_CALIBRATE = range(8)
 BIAS_W8A8, BIAS_WEIGHT_ONLY = 0, 1
 SCALE_NONE, SCALE_RANGE, SCALE_ABSMAX = 0, 1, 2
 ST_DEGENERATE, ST_NONFINITE, ST_BIGQUOT, ST_SCALEGUARD, ST_ZEROPOINT = 1, 2, 4, 8, 16
@@ -21,10 +21,25 @@ ST_DEGENERATE, ST_NONFINITE, ST_BIGQUOT, ST_SCALEGUARD, ST_ZEROPOINT = 1, 2, 4, 
 EXPORTS = ("aweq_workspace_size", "aweq_status_string", "aweq_calib_stats", "aweq_equalize",
            "aweq_quant_weight", "aweq_quant_act", "aweq_w8a8_gemm", "aweq_bias_correct",
            "aweq_panel_bytes", "aweq_pack_panels_i8", "aweq_unpack_panels_i8", "aweq_wonly_gemm", "aweq_fold_quant_weight", "aweq_w8a8_gemm_fused",
-           "aweq_calib_stats_static")
+           "aweq_calib_stats_static", "aweq_calibrate")
 STATIC_SCRATCH_BYTES = 16 << 20
 
 _vp, _i64, _i32, _u64, _f32, _sz = C.c_void_p, C.c_int64, C.c_int, C.c_uint64, C.c_float, C.c_size_t
+
+
+class CalibLayer(C.Structure):
+    """aweq_calib_layer"""
+    _fields_ = ([("X", _vp), ("dt", _i32), ("T", _i64), ("K", _i64), ("ldx", _i64)] +
+                [(n, _vp) for n in ("xmin", "xmax", "xsum", "count", "r_x", "R_x", "p_x", "wmin", "wmax", "wcount", "r_w", "R_w", "p_w", "s",
+                                    "inv_s", "xhat_range", "mu_xhat", "act_step", "act_zero", "xq", "rowsum_x", "colsum_xq")] +
+                [(n, _i32) for n in ("enable_awe", "enable_bc", "bits", "group", "w8a8", "forward", "fused_weight_pass")] +
+                [("ws", _vp), ("ws_bytes", _sz), ("status", _vp)])
+
+
+class CalibWeight(C.Structure):
+    """aweq_calib_weight"""
+    _fields_ = [("W", _vp), ("N", _i64), ("ldw", _i64), ("W_hat", _vp), ("ldwh", _i64), ("codes", _vp), ("step_w", _vp), ("zero_w", _vp),
+                ("rowsum_w", _vp), ("bias_in", _vp), ("delta", _vp), ("bias_out", _vp), ("out_i32", _vp), ("out_deq", _vp), ("colsum_acc", _vp)]
 
 
 class AweqError(RuntimeError):
@@ -77,6 +92,8 @@ def load_library():
                                     _vp, _vp]
     lib.aweq_fold_quant_weight.restype = _i32
     lib.aweq_fold_quant_weight.argtypes = [_vp, _i32, _i64, _i64, _i64, _vp, _vp, _i64, _i32, _vp, _vp, _vp, _vp, _vp, _vp]
+    lib.aweq_calibrate.restype = _i32
+    lib.aweq_calibrate.argtypes = [_vp, _vp, _i32, _vp]
     lib.aweq_panel_bytes.restype = _sz
     lib.aweq_panel_bytes.argtypes = [_i64, _i64]
     lib.aweq_pack_panels_i8.restype = _i32
@@ -216,3 +233,11 @@ def aweq_wonly_gemm(X_hat, T, K, ldx, codes, bits, group, step_w, zero_w, N, bia
 def aweq_fold_quant_weight(W, dt, N, K, ldw, s, W_hat, ldwh, bits, codes, step, zero, rowsum_w, status=None, stream=None):
     _check(load_library().aweq_fold_quant_weight(_ptr(W), dt, N, K, ldw, _ptr(s), _ptr(W_hat), ldwh, int(bits), _ptr(codes),
                                                  _ptr(step), _ptr(zero), _ptr(rowsum_w), _ptr(status), _stream(stream)))
+
+
+def aweq_calibrate(layer, weights, stream=None):
+    """layer: the fields of CalibLayer in order; weights: a sequence of the fields of CalibWeight in order.  Tensors, addresses, numbers
+    or None."""
+    ws = (CalibWeight * len(weights))(*[tuple(v if v is None or isinstance(v, int) else v.data_ptr() for v in w) for w in weights])
+    lay = CalibLayer(*[v if v is None or isinstance(v, int) else v.data_ptr() for v in layer])
+    _check(load_library().aweq_calibrate(C.addressof(lay), C.addressof(ws), len(weights), _stream(stream)))

@@ -3,7 +3,7 @@
 // By linearity both means contract to K-vectors and integer column sums, so this is a
 // GEMV over W_hat (HBM-bound, one read of the weight): fp64 accumulation because delta is a
 // small difference of two nearly equal means.
-#include "common.hpp"
+#include "code_digits.hpp"
 
 namespace aweq {
 
@@ -95,20 +95,11 @@ __global__ __launch_bounds__(BLOCK) void bias_w8a8_kernel(
                 acc[r] = __builtin_fma((double)w[r][4 + i], (double)m1.f[i], acc[r]);
             }
         if (wq && small) {
-            // digit j of cx[0 .. 3] and of cx[4 .. 7], packed: adding 0x808080 carries into the digit above, and flipping the
-            // lower digits' top bits takes it back out
             uint32_t d[2][4];
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                uint32_t b[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) b[i] = ((uint32_t)(int)cx[4 * h + i] + 0x00808080u) ^ 0x00808080u;
-                const uint32_t l01 = __builtin_amdgcn_perm(b[1], b[0], 0x05010400u), l23 = __builtin_amdgcn_perm(b[3], b[2], 0x05010400u);
-                const uint32_t h01 = __builtin_amdgcn_perm(b[1], b[0], 0x07030602u), h23 = __builtin_amdgcn_perm(b[3], b[2], 0x07030602u);
-                d[h][0] = __builtin_amdgcn_perm(l23, l01, 0x05040100u);
-                d[h][1] = __builtin_amdgcn_perm(l23, l01, 0x07060302u);
-                d[h][2] = __builtin_amdgcn_perm(h23, h01, 0x05040100u);
-                d[h][3] = __builtin_amdgcn_perm(h23, h01, 0x07060302u);
+                const int c4[4] = {(int)cx[4 * h], (int)cx[4 * h + 1], (int)cx[4 * h + 2], (int)cx[4 * h + 3]};
+                pack_digits(c4, d[h]);
             }
 #pragma unroll
             for (int r = 0; r < ROWS; ++r)
@@ -133,8 +124,7 @@ __global__ __launch_bounds__(BLOCK) void bias_w8a8_kernel(
         const double a = wave_allreduce(acc[r], OpAdd());
         if (threadIdx.x % kWave == 0) slot_d[wave][r] = a;
         if (wq) {
-            const long long c = wave_allreduce(ca[r] + cd[r][0] + ((long long)cd[r][1] << 8) + ((long long)cd[r][2] << 16) +
-                                                   ((long long)cd[r][3] << 24), OpAdd());
+            const long long c = wave_allreduce(ca[r] + digits_value(cd[r]), OpAdd());
             if (threadIdx.x % kWave == 0) slot_l[wave][r] = c;
         }
     }
@@ -153,14 +143,8 @@ __global__ __launch_bounds__(BLOCK) void bias_w8a8_kernel(
         if (wq) c_r += slot_l[w][r];
         tot += slot_l[w][ROWS];
     }
-    const long long T = (long long)count;
-    const long long zx = (long long)*act_zero - 128;
-    const double sx = (double)*act_step;
     const int64_t pi = w_per_tensor ? 0 : n;   // one (Step, Z) for the tensor, or one per output channel
-    const long long zw = (long long)zero_w[pi] - 128;
-    const long long a = (wq ? c_r : colsum_acc[n]) - T * zx * (long long)rowsum_w[n] - zw * tot + T * K * zx * zw;
-    const double yq = sx * (double)step_w[pi] * (double)a / (double)T;
-    const double d = a_r - yq;
+    const double d = int8_delta(a_r, wq ? c_r : colsum_acc[n], rowsum_w[n], tot, count, K, *act_step, *act_zero, step_w[pi], zero_w[pi]);
     delta[n] = (float)d;
     bias_out[n] = (float)((bias_in ? (double)bias_in[n] : 0.0) + (enable_bc ? d : 0.0));
 }

@@ -1,5 +1,5 @@
 // Stage 2: equalization factors (Sec. 3.2, Eq. 10) and the fold of Eq. 3 (Sec. 3.1).
-#include "common.hpp"
+#include "equalize.hpp"
 
 namespace aweq {
 
@@ -57,21 +57,7 @@ __global__ __launch_bounds__(kScaleBlock) void equalize_scales(
         for (int i = 0; i < kScaleBatch; ++i) {
             const int64_t k = k0 + i * stride;
             if (k >= K) break;
-            // the per-channel quantity the scale balances: the channel range (Eq. 10), or - the definition the
-            // method replaces (Sec. 1, Sec. 3.2) - the channel's largest magnitude
-            const float r_x = enable_awe == AWEQ_SCALE_ABSMAX ? fmaxf(fabsf(x0[i]), fabsf(x1[i])) : x1[i] - x0[i];
-            const float r_w = enable_awe == AWEQ_SCALE_ABSMAX ? fmaxf(fabsf(w0[i]), fabsf(w1[i])) : w1[i] - w0[i];
-            float sk = 1.0f;
-            if (enable_awe) {
-                if (!(r_x >= 1e-5f) || !(r_w >= 1e-5f)) {
-                    st |= AWEQ_ST_SCALEGUARD;
-                } else {
-                    const double rx = (double)r_x, rw = (double)r_w;
-                    sk = (float)(sqrt(rx * rw) / rw);
-                    if (sk < 1e-4f) { sk = 1e-4f; st |= AWEQ_ST_SCALEGUARD; }
-                    if (sk > 1e4f) { sk = 1e4f; st |= AWEQ_ST_SCALEGUARD; }
-                }
-            }
+            const float sk = channel_scale(x0[i], x1[i], w0[i], w1[i], enable_awe, st);
             const float is = 1.0f / sk;
             s[k] = sk;
             inv_s[k] = is;
@@ -154,6 +140,27 @@ __global__ __launch_bounds__(256) void fold_weight(const void* __restrict__ Wv, 
     }
 }
 
+// W_hat = W s on checked arguments
+void launch_fold(const void* W, void* W_hat, aweq_dtype dt, int64_t N, int64_t K, int64_t ldw, int64_t ldwh, const float* s, hipStream_t st)
+{
+    const int E = dt == AWEQ_F16 ? 8 : 4;
+    const unsigned gx = (unsigned)cdiv(K, 256 * E);
+    int64_t slices = cdiv(4096, gx);
+    if (slices > N) slices = N;
+    const int64_t rpb = cdiv(N, slices);
+    dim3 grid(gx, (unsigned)cdiv(N, rpb));
+    // binary16: W is not read again, the folded weight and its codes are: non-temporal, where rows are whole 128-byte lines (after
+    // the statistics of W, us, plain -> non-temporal: 4096 x 11008 60.3 -> 55.1, 11008 x 4096 61.4 -> 57.5).  A line that two rows
+    // share would be fetched twice (14796 x 2360 58.3 -> 61.4, 8500 x 3224 46.6 -> 49.5)
+    const bool lines = reinterpret_cast<uintptr_t>(W) % 128 == 0 && (ldw * 2) % 128 == 0;
+    if (dt == AWEQ_F16 && lines)
+        fold_weight<true, true><<<grid, 256, 0, st>>>(W, W_hat, N, K, ldw, ldwh, s, rpb);
+    else if (dt == AWEQ_F16)
+        fold_weight<true, false><<<grid, 256, 0, st>>>(W, W_hat, N, K, ldw, ldwh, s, rpb);
+    else
+        fold_weight<false, false><<<grid, 256, 0, st>>>(W, W_hat, N, K, ldw, ldwh, s, rpb);
+}
+
 }  // namespace aweq
 
 using namespace aweq;
@@ -188,23 +195,6 @@ extern "C" int aweq_equalize(const float* xmin, const float* xmax, const double*
         xmin, xmax, xsum, count, wmin, wmax, K, enable_awe, s, inv_s, prev_scale, xhat_range, mu_xhat, act_step, act_zero, status, one);
     if (!one && range)
         equalize_range<<<1, kScaleBlock, 0, st>>>(xmin, xmax, inv_s, K, xhat_range, act_step, act_zero, status);
-    if (W) {
-        const int E = dt == AWEQ_F16 ? 8 : 4;
-        const unsigned gx = (unsigned)cdiv(K, 256 * E);
-        int64_t slices = cdiv(4096, gx);
-        if (slices > N) slices = N;
-        const int64_t rpb = cdiv(N, slices);
-        dim3 grid(gx, (unsigned)cdiv(N, rpb));
-        // binary16: W is not read again, the folded weight and its codes are: non-temporal, where rows are whole 128-byte lines (after
-        // the statistics of W, us, plain -> non-temporal: 4096 x 11008 60.3 -> 55.1, 11008 x 4096 61.4 -> 57.5).  A line that two rows
-        // share would be fetched twice (14796 x 2360 58.3 -> 61.4, 8500 x 3224 46.6 -> 49.5)
-        const bool lines = reinterpret_cast<uintptr_t>(W) % 128 == 0 && (ldw * 2) % 128 == 0;
-        if (dt == AWEQ_F16 && lines)
-            fold_weight<true, true><<<grid, 256, 0, st>>>(W, W_hat, N, K, ldw, ldwh, s, rpb);
-        else if (dt == AWEQ_F16)
-            fold_weight<true, false><<<grid, 256, 0, st>>>(W, W_hat, N, K, ldw, ldwh, s, rpb);
-        else
-            fold_weight<false, false><<<grid, 256, 0, st>>>(W, W_hat, N, K, ldw, ldwh, s, rpb);
-    }
+    if (W) launch_fold(W, W_hat, dt, N, K, ldw, ldwh, s, st);
     return launch_status();
 }

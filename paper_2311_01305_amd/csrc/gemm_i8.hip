@@ -26,6 +26,7 @@
 // Workgroups are numbered so that the ones resident on one XCD (which share an L2) form a
 // compact patch of the output.
 #include "gemm_i8.hpp"
+#include "quant_act.hpp"
 #include <type_traits>
 
 namespace aweq {
@@ -782,13 +783,6 @@ __global__ void zero_fill_u32_gemm(uint32_t* p, int64_t n)
     if (i < n) p[i] = 0u;
 }
 
-// from quant_act.hip
-int launch_quant_act(const void* X, aweq_dtype dt, int64_t T, int64_t K, int64_t ldx, const float* inv_s,
-                     const float* act_step, const int32_t* act_zero, int8_t* xq, int32_t* rowsum_x,
-                     int64_t* colsum_xq, void* ws, uint32_t* status, hipStream_t st);
-int check_quant_act_ws(int64_t T, int64_t K, const int32_t* rowsum_x, const int64_t* colsum_xq, const void* ws, size_t ws_bytes);
-int check_quant_act_args(const void* X, aweq_dtype dt, int64_t T, int64_t K, int64_t ldx, const float* inv_s,
-                         const float* act_step, const int32_t* act_zero, const int8_t* xq, bool xq_optional);
 
 }  // namespace aweq
 

@@ -24,6 +24,8 @@
 // quotient too, where |Z| allows it, and divides the units with a quotient beyond 2^22 (7419 x 4096 tokens x channels:
 // 47.4 us with the division everywhere, 40.1 now; a quotient that underflows on the way rounds to 0 either way).
 #include "act_unit.hpp"
+#include "code_digits.hpp"
+#include "quant_act.hpp"
 #include <type_traits>
 
 namespace aweq {
@@ -60,7 +62,7 @@ __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
     const void* __restrict__ X, int64_t T, int64_t K, int64_t ldx, const float* __restrict__ inv_s,
     const float* __restrict__ act_step, const int32_t* __restrict__ act_zero, int8_t* __restrict__ xq,
     int32_t* __restrict__ rowsum_x, int32_t* __restrict__ colsum_part, int rows_per_block, int chunks,
-    unsigned pairs, uint32_t* status)
+    unsigned pairs, uint32_t* status, RangeParts range)
 {
     const unsigned pair = (blockIdx.x % kQaXcds) * (gridDim.x / kQaXcds) + blockIdx.x / kQaXcds;
     if (pair >= pairs) return;   // (the grid is rounded up to a multiple of 8)
@@ -95,7 +97,25 @@ __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
 #pragma unroll
         for (int j = 0; j < kQaVpt; ++j) request(b, j, 8 * b + rsub);
 
-    const ActParams p = quot_params(*act_step, *act_zero);
+    uint32_t st = 0;
+    float step;
+    int zero;
+    if (range.ext) {   // Step and Z are not there yet: every block finds them, the first one stores them
+        __shared__ float slot[2 * kQaWaves];
+        const float2 r = parts_extremes<kQaBlock>(range.ext, range.blocks, 2, slot);
+        uint32_t range_st = 0;
+        qparams(r.x, r.y, 8, step, zero, range_st);
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            st = range_st;
+            range.xhat_range[0] = r.x; range.xhat_range[1] = r.y;
+            *range.act_step = step;
+            *range.act_zero = zero;
+        }
+    } else {
+        step = *act_step;
+        zero = *act_zero;
+    }
+    const ActParams p = quot_params(step, zero);
     float is[kQaVpt][8];
     bool fast_thread = p.fast;
     float is_max = 0.0f;
@@ -115,7 +135,6 @@ __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
     // one path for the whole block (the choice is uniform unless an inv_s is absurd)
     const bool fast = F16 ? __syncthreads_and(fast_thread ? 1 : 0) != 0 : p.screen;
     const bool screen = F16 ? __syncthreads_and(screen_thread ? 1 : 0) != 0 : p.screen;
-    uint32_t st = 0;
     float big = 0.0f;
     float csf[kQaVpt][8];
     int csi[kQaVpt][8];
@@ -210,10 +229,10 @@ __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
 // Fold the per-slice column sums (fixed order, 64-bit) and the per-chunk row sums.  Blocks
 // [0, col_blocks) own 32 columns each: 32 groups of 32 threads take every 32nd slice (few dependent loads
 // per thread: the kernel is bound by their latency) and meet in LDS; the remaining blocks own 1024 rows each.
-constexpr int kQaMergeCols = 32, kQaMergeParts = 32;
+constexpr int kQaMergeCols = kRangeCols, kQaMergeParts = 32;
 __global__ __launch_bounds__(kQaMergeCols * kQaMergeParts) void quant_act_merge(
     const int32_t* __restrict__ colsum_part, int slices, int64_t K, long long* __restrict__ colsum_xq,
-    const int32_t* __restrict__ rowsum_part, int chunks, int64_t T, int32_t* __restrict__ rowsum_x, int col_blocks)
+    const int32_t* __restrict__ rowsum_part, int chunks, int64_t T, int32_t* __restrict__ rowsum_x, int col_blocks, SumDigits dg)
 {
     if ((int)blockIdx.x < col_blocks) {
         __shared__ long long s_s[kQaMergeParts][kQaMergeCols];
@@ -224,10 +243,21 @@ __global__ __launch_bounds__(kQaMergeCols * kQaMergeParts) void quant_act_merge(
             for (int j = part; j < slices; j += kQaMergeParts) s += colsum_part[(int64_t)j * K + k];
         s_s[part][c] = s;
         __syncthreads();
-        if (part != 0 || k >= K) return;
+        if (part != 0) return;
 #pragma unroll
         for (int q = 1; q < kQaMergeParts; ++q) s += s_s[q][c];
-        colsum_xq[k] = s;
+        if (k < K) colsum_xq[k] = s;
+        if (!dg.digits) return;
+        s_s[0][c] = s;   // (0 past K)
+        wave_lds_fence();
+        const long long tot = group_allreduce<5>(s, OpAdd());
+        if (c == 0) dg.totals[blockIdx.x] = tot;
+        if ((c & 3) == 0 && k < K) {   // K % 8 == 0: all four columns or none
+            const int v[4] = {(int)s_s[0][c], (int)s_s[0][c + 1], (int)s_s[0][c + 2], (int)s_s[0][c + 3]};
+            uint32_t d[4];
+            pack_digits(v, d);
+            dg.digits[k >> 2] = make_uint4(d[0], d[1], d[2], d[3]);
+        }
     } else {
         const int64_t t = ((int64_t)blockIdx.x - col_blocks) * (kQaMergeCols * kQaMergeParts) + threadIdx.x;
         if (t >= T) return;
@@ -340,7 +370,8 @@ size_t quant_act_ws_bytes(int64_t T, int64_t K)
 
 int launch_quant_act(const void* X, aweq_dtype dt, int64_t T, int64_t K, int64_t ldx, const float* inv_s,
                      const float* act_step, const int32_t* act_zero, int8_t* xq, int32_t* rowsum_x,
-                     int64_t* colsum_xq, void* ws, uint32_t* status, hipStream_t st)
+                     int64_t* colsum_xq, void* ws, uint32_t* status, hipStream_t st, const RangeParts* range,
+                     const SumDigits* digits)
 {
     // whole rows per block where nothing is summed over tokens, up to the size where the panel form streams as fast
     // (K = 4096 / 11008, us, panel form -> row form: 1 token 7.1 -> 3.1 / 7.9 -> 4.6, 256: 10.1 -> 3.8 / 13.8 -> 6.5,
@@ -350,7 +381,7 @@ int launch_quant_act(const void* X, aweq_dtype dt, int64_t T, int64_t K, int64_t
     // 2500 tokens 5.6 -> 7.0 / 7.3 -> 7.1, binary32 4096 tokens 5.3 -> 7.6 / 8.4 -> 9.9;
     // without the sums 2758 tokens K = 448 6.3 -> 4.8, 4051 tokens K = 120 5.9 -> 5.2).  Not where an output lies over what other
     // blocks still read: the panel form's merge writes the row sums in a launch of its own, and its blocks have 32 rows or more.
-    if (!colsum_xq && xq && aligned16(inv_s) && T <= (rowsum_x && K <= kQaPanels * kPanel ? 2048 : 4096) &&
+    if (!range && !colsum_xq && xq && aligned16(inv_s) && T <= (rowsum_x && K <= kQaPanels * kPanel ? 2048 : 4096) &&
         !overlap({{rowsum_x, T * 4}, {xq, T * panel_count(K) * kPanel}}, {matrix_span(X, T, K, ldx, dtype_size(dt)), {inv_s, K * 4}, {act_step, 4}, {act_zero, 4}})) {
 #define AWEQ_QR(F, R) quant_act_rows<F, R><<<(unsigned)cdiv(T, R), kQrBlock, 0, st>>>(X, T, K, ldx, inv_s, act_step, act_zero, xq, rowsum_x, status)
         if (dt == AWEQ_F16) { if (T <= 256) AWEQ_QR(true, 1); else if (T <= 1024) AWEQ_QR(true, 2); else AWEQ_QR(true, 4); }
@@ -367,11 +398,12 @@ int launch_quant_act(const void* X, aweq_dtype dt, int64_t T, int64_t K, int64_t
     const unsigned pairs = (unsigned)(p.slices * p.chunks);
     const unsigned grid = (unsigned)(cdiv(pairs, kQaXcds) * kQaXcds);
     const bool sums = !xq && !rowsum_x;
+    const RangeParts parts = range ? *range : RangeParts{};
     // codes that fit the memory-side cache are stored through the caches, where the GEMM finds them; more would only evict each
     // other (int8 forward, us, non-temporal -> cached: 16384 tokens 4096 x 11008 (180 MB) 663 -> 650, 4096 x 16384 (268 MB)
     // 979 -> 967, 12000 tokens 8192 x 16384 1306 -> 1307; the pass alone at 262144 x 8192 (2.1 GB) 1188 -> 1268)
     const bool keep = xq && (int64_t)panel_count(K) * kPanel * T <= kCacheBytes;
-#define AWEQ_QA(F, S, P) quant_act_kernel<F, S, P><<<grid, kQaBlock, 0, st>>>(X, T, K, ldx, inv_s, act_step, act_zero, xq, rs_out, colsum_part, (int)p.rpb, p.chunks, pairs, status)
+#define AWEQ_QA(F, S, P) quant_act_kernel<F, S, P><<<grid, kQaBlock, 0, st>>>(X, T, K, ldx, inv_s, act_step, act_zero, xq, rs_out, colsum_part, (int)p.rpb, p.chunks, pairs, status, parts)
     if (dt == AWEQ_F16) { if (sums) AWEQ_QA(true, true, false); else if (keep) AWEQ_QA(true, false, true); else AWEQ_QA(true, false, false); }
     else { if (sums) AWEQ_QA(false, true, false); else if (keep) AWEQ_QA(false, false, true); else AWEQ_QA(false, false, false); }
 #undef AWEQ_QA
@@ -379,7 +411,8 @@ int launch_quant_act(const void* X, aweq_dtype dt, int64_t T, int64_t K, int64_t
     const int64_t row_blocks = (rowsum_x && multi) ? cdiv(T, kQaMergeCols * kQaMergeParts) : 0;
     if (col_blocks + row_blocks > 0)
         quant_act_merge<<<(unsigned)(col_blocks + row_blocks), kQaMergeCols * kQaMergeParts, 0, st>>>(
-            colsum_part, (int)p.slices, K, reinterpret_cast<long long*>(colsum_xq), rowsum_part, p.chunks, T, rowsum_x, col_blocks);
+            colsum_part, (int)p.slices, K, reinterpret_cast<long long*>(colsum_xq), rowsum_part, p.chunks, T, rowsum_x, col_blocks,
+            digits ? *digits : SumDigits{});
     return launch_status();
 }
 

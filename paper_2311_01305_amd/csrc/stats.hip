@@ -1,226 +1,22 @@
 // Stage 1: per-channel minimum / maximum / sum of a tall row-major matrix
 // (Sec. 3.2: channel range and tensor range; Sec. 3.3: E[x] collected alongside).
 //
-// HBM-bound streaming pass.  Lanes own columns (16 bytes = 8 halves or 4 floats per lane),
-// so a wavefront reads 1 KiB contiguous per row; the four wavefronts of a block take
-// interleaved rows of one row slice and meet in LDS; each block writes one partial row of
-// (min, max, sum) to the workspace, and a second small kernel folds the slices in a fixed
-// order (so the fp64 sums are reproducible) and merges with earlier batches.
-#include "common.hpp"
+// HBM-bound streaming pass (col_stats.hpp): each block leaves one partial row of (min, max, sum) in the workspace, and a second
+// small kernel folds the slices in a fixed order (so the fp64 sums are reproducible) and merges with earlier batches.
+#include "col_stats.hpp"
 #include <atomic>
 
 namespace aweq {
 
-constexpr int kStatsBlock = 256;
-constexpr int kStatsWaves = kStatsBlock / kWave;
-constexpr int kRowBatch = 8;  // rows summed in fp32 before one fp64 add (binary16 input only)
-
-struct StatsPlan {
-    int col_chunks;   // blocks along K
-    int slices;       // row slices
-    int64_t rows_per_slice;
-};
-
-// Same plan on the host for the launch and for the workspace size.
-inline StatsPlan stats_plan(int64_t rows, int64_t K, int elts_per_lane)
-{
-    StatsPlan p;
-    const int64_t cols_per_block = (int64_t)kWave * elts_per_lane;
-    p.col_chunks = (int)cdiv(K, cols_per_block);
-    int64_t want = cdiv(1280, p.col_chunks);           // 5 blocks per compute unit, all resident: fewer partial rows to merge
-    int64_t max_slices = cdiv(rows, kStatsWaves * kRowBatch);  // at least one row batch per wavefront
-    if (want > max_slices) want = max_slices;
-    if (want < 1) want = 1;
-    p.rows_per_slice = cdiv(cdiv(rows, want), kStatsWaves * kRowBatch) * (kStatsWaves * kRowBatch);
-    p.slices = (int)cdiv(rows, p.rows_per_slice);
-    return p;
-}
-
-inline size_t stats_ws_bytes(int64_t rows, int64_t K)
-{
-    // sized for the narrower lane width (more chunks never increases the slice count)
-    StatsPlan a = stats_plan(rows, K, 8), b = stats_plan(rows, K, 4);
-    int s = a.slices > b.slices ? a.slices : b.slices;
-    return (size_t)s * (size_t)K * (sizeof(float) * 2 + sizeof(double)) + 16;   // partial rows, then the merge kernel's ticket
-}
-
-constexpr int64_t kKeepBytes = kCacheBytes * 3 / 8;
-
-// Every byte of the matrix is read exactly once by this pass.  KEEP: through the caches, for the pass that reads the same matrix next
-// (rule and figures at the launch); otherwise non-temporal.
-template <bool KEEP>
-__device__ __forceinline__ Half8 load_once(const _Float16* p)
-{
-    typedef int v4i_ __attribute__((ext_vector_type(4)));
-    const v4i_* const q = reinterpret_cast<const v4i_*>(p);
-    return __builtin_bit_cast(Half8, KEEP ? *q : __builtin_nontemporal_load(q));
-}
-template <bool KEEP>
-__device__ __forceinline__ Float4 load_once(const float* p)
-{
-    typedef float v4f_ __attribute__((ext_vector_type(4)));
-    const v4f_* const q = reinterpret_cast<const v4f_*>(p);
-    return __builtin_bit_cast(Float4, KEEP ? *q : __builtin_nontemporal_load(q));
-}
-
-// ---- binary16: 8 columns per lane
-template <bool KEEP>
-__global__ __launch_bounds__(kStatsBlock) void col_stats_partial_f16(
-    const _Float16* __restrict__ M, int64_t rows, int64_t K, int64_t ld, int64_t rows_per_slice,
+template <bool F16, bool KEEP>
+__global__ __launch_bounds__(kStatsBlock) void col_stats_partial(
+    const void* __restrict__ M, int64_t rows, int64_t K, int64_t ld, int64_t rows_per_slice,
     float* __restrict__ pmin, float* __restrict__ pmax, double* __restrict__ psum, uint32_t* __restrict__ ticket)
 {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = threadIdx.x / kWave;
+    __shared__ StatsLds<SliceStats<F16>::kCols> s;
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *ticket = 0u;   // (for the merge kernel that follows on the stream)
-    const int64_t col = ((int64_t)blockIdx.x * kWave + lane) * 8;
-    const bool active = col < K;
-    const int64_t r_begin = (int64_t)blockIdx.y * rows_per_slice;
-    const int64_t r_end = min(rows, r_begin + rows_per_slice);
-
-    const f16x2 pinf = {(_Float16)INFINITY, (_Float16)INFINITY};
-    const f16x2 ninf = {(_Float16)-INFINITY, (_Float16)-INFINITY};
-    f16x2 mn[4] = {pinf, pinf, pinf, pinf};
-    f16x2 mx[4] = {ninf, ninf, ninf, ninf};
-    double sum[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-
-    if (active) {
-        const _Float16* base = M + col;
-        // wavefront w takes rows r_begin + w, + kStatsWaves, ...; kRowBatch rows in flight
-        int64_t r = r_begin + wave;
-        for (; r + (int64_t)(kRowBatch - 1) * kStatsWaves < r_end; r += (int64_t)kRowBatch * kStatsWaves) {
-            Half8 v[kRowBatch];
-#pragma unroll
-            for (int j = 0; j < kRowBatch; ++j)
-                v[j] = load_once<KEEP>(base + (r + (int64_t)j * kStatsWaves) * ld);
-            float part[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-            for (int j = 0; j < kRowBatch; ++j)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    mn[i] = hmin2(mn[i], v[j].h[i]);
-                    mx[i] = hmax2(mx[i], v[j].h[i]);
-                    float2 f = h2f2(v[j].h[i]);
-                    part[2 * i] += f.x;
-                    part[2 * i + 1] += f.y;
-                }
-#pragma unroll
-            for (int i = 0; i < 8; ++i) sum[i] += (double)part[i];
-        }
-        for (; r < r_end; r += kStatsWaves) {
-            Half8 v = load_once<KEEP>(base + r * ld);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                mn[i] = hmin2(mn[i], v.h[i]);
-                mx[i] = hmax2(mx[i], v.h[i]);
-                float2 f = h2f2(v.h[i]);
-                sum[2 * i] += (double)f.x;
-                sum[2 * i + 1] += (double)f.y;
-            }
-        }
-    }
-
-    // cross-wavefront combine in LDS: [wave][lane][8]
-    __shared__ float s_mn[kStatsWaves][kWave][8];
-    __shared__ float s_mx[kStatsWaves][kWave][8];
-    __shared__ double s_sm[kStatsWaves][kWave][8];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        float2 a = h2f2(mn[i]), b = h2f2(mx[i]);
-        s_mn[wave][lane][2 * i] = a.x; s_mn[wave][lane][2 * i + 1] = a.y;
-        s_mx[wave][lane][2 * i] = b.x; s_mx[wave][lane][2 * i + 1] = b.y;
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) s_sm[wave][lane][i] = sum[i];
-    __syncthreads();
-    // 512 columns per block, 256 threads: two columns each
-    for (int c = threadIdx.x; c < kWave * 8; c += kStatsBlock) {
-        const int l = c >> 3, i = c & 7;
-        float a = s_mn[0][l][i], b = s_mx[0][l][i];
-        double s = s_sm[0][l][i];
-#pragma unroll
-        for (int w = 1; w < kStatsWaves; ++w) {
-            a = fminf(a, s_mn[w][l][i]);
-            b = fmaxf(b, s_mx[w][l][i]);
-            s += s_sm[w][l][i];
-        }
-        const int64_t k = (int64_t)blockIdx.x * kWave * 8 + c;
-        if (k < K) {
-            const int64_t o = (int64_t)blockIdx.y * K + k;
-            pmin[o] = a; pmax[o] = b; psum[o] = s;
-        }
-    }
-}
-
-// ---- binary32: 4 columns per lane, every element added in fp64
-template <bool KEEP>
-__global__ __launch_bounds__(kStatsBlock) void col_stats_partial_f32(
-    const float* __restrict__ M, int64_t rows, int64_t K, int64_t ld, int64_t rows_per_slice,
-    float* __restrict__ pmin, float* __restrict__ pmax, double* __restrict__ psum, uint32_t* __restrict__ ticket)
-{
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = threadIdx.x / kWave;
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *ticket = 0u;   // (for the merge kernel that follows on the stream)
-    const int64_t col = ((int64_t)blockIdx.x * kWave + lane) * 4;
-    const bool active = col < K;
-    const int64_t r_begin = (int64_t)blockIdx.y * rows_per_slice;
-    const int64_t r_end = min(rows, r_begin + rows_per_slice);
-    float mn[4] = {INFINITY, INFINITY, INFINITY, INFINITY};
-    float mx[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-    double sum[4] = {0, 0, 0, 0};
-    if (active) {
-        const float* base = M + col;
-        int64_t r = r_begin + wave;
-        for (; r + (int64_t)(kRowBatch - 1) * kStatsWaves < r_end; r += (int64_t)kRowBatch * kStatsWaves) {
-            Float4 v[kRowBatch];
-#pragma unroll
-            for (int j = 0; j < kRowBatch; ++j)
-                v[j] = load_once<KEEP>(base + (r + (int64_t)j * kStatsWaves) * ld);
-#pragma unroll
-            for (int j = 0; j < kRowBatch; ++j)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    mn[i] = fminf(mn[i], v[j].f[i]);
-                    mx[i] = fmaxf(mx[i], v[j].f[i]);
-                    sum[i] += (double)v[j].f[i];
-                }
-        }
-        for (; r < r_end; r += kStatsWaves) {
-            Float4 v = load_once<KEEP>(base + r * ld);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                mn[i] = fminf(mn[i], v.f[i]);
-                mx[i] = fmaxf(mx[i], v.f[i]);
-                sum[i] += (double)v.f[i];
-            }
-        }
-    }
-    __shared__ float s_mn[kStatsWaves][kWave][4];
-    __shared__ float s_mx[kStatsWaves][kWave][4];
-    __shared__ double s_sm[kStatsWaves][kWave][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        s_mn[wave][lane][i] = mn[i];
-        s_mx[wave][lane][i] = mx[i];
-        s_sm[wave][lane][i] = sum[i];
-    }
-    __syncthreads();
-    {
-        const int c = threadIdx.x;  // 256 columns per block, one per thread
-        const int l = c >> 2, i = c & 3;
-        float a = s_mn[0][l][i], b = s_mx[0][l][i];
-        double s = s_sm[0][l][i];
-#pragma unroll
-        for (int w = 1; w < kStatsWaves; ++w) {
-            a = fminf(a, s_mn[w][l][i]);
-            b = fmaxf(b, s_mx[w][l][i]);
-            s += s_sm[w][l][i];
-        }
-        const int64_t k = (int64_t)blockIdx.x * kWave * 4 + c;
-        if (k < K) {
-            const int64_t o = (int64_t)blockIdx.y * K + k;
-            pmin[o] = a; pmax[o] = b; psum[o] = s;
-        }
-    }
+    const int64_t r0 = (int64_t)blockIdx.y * rows_per_slice, o = (int64_t)blockIdx.y * K;
+    stats_slice<F16>(s, M, K, ld, blockIdx.x, r0, min(rows, r0 + rows_per_slice), KEEP, pmin + o, pmax + o, psum + o);
 }
 
 // Fold the row slices and merge with what the caller already holds.  A block owns 32 columns;
@@ -351,9 +147,9 @@ static int run_calib_stats(const void* M, aweq_dtype dt, int64_t rows, int64_t K
     // neither cache the two kinds of loads take the same up to 90 MB (25.9 / 26.1 us with the merge), beyond it plain ones
     // are slower (134 MB 35.0 -> 36.1, 262 MB 53.1 -> 55.7).
     const bool keep = rows * K * (int64_t)dtype_size(dt) <= kKeepBytes;
-#define AWEQ_CS(F, E, P) col_stats_partial_##F<P><<<grid, kStatsBlock, 0, st>>>(reinterpret_cast<const E*>(M), rows, K, ld, plan.rows_per_slice, pmin, pmax, psum, ticket)
-    if (dt == AWEQ_F16) { if (keep) AWEQ_CS(f16, _Float16, true); else AWEQ_CS(f16, _Float16, false); }
-    else { if (keep) AWEQ_CS(f32, float, true); else AWEQ_CS(f32, float, false); }
+#define AWEQ_CS(F, P) col_stats_partial<F, P><<<grid, kStatsBlock, 0, st>>>(M, rows, K, ld, plan.rows_per_slice, pmin, pmax, psum, ticket)
+    if (dt == AWEQ_F16) { if (keep) AWEQ_CS(true, true); else AWEQ_CS(true, false); }
+    else { if (keep) AWEQ_CS(false, true); else AWEQ_CS(false, false); }
 #undef AWEQ_CS
     const bool one = finalize && K <= kOneMergeK;
     const unsigned blocks = (unsigned)cdiv(K, kMergeCols);

@@ -1,6 +1,6 @@
-"""Convenience driver: allocate the buffers of one linear layer with torch and call the
-five C-ABI stages in the order the method applies them (Sec. 3: statistics, equalization,
-quantization, W8A8 forward, bias correction).  No arithmetic of the method happens here.
+"""Convenience driver: allocate the buffers of one linear layer with torch and run the stages in
+the order the method applies them (Sec. 3: statistics, equalization, quantization, W8A8 forward,
+bias correction) as one call of the C ABI (aweq_calibrate).  No arithmetic of the method happens here.
 """
 from dataclasses import dataclass, field
 from typing import Optional
@@ -18,6 +18,15 @@ def _dt(t: torch.Tensor) -> int:
     if t.dtype == torch.int8:
         return B.AWEQ_I8
     raise TypeError(f"unsupported dtype {t.dtype}")
+
+
+def _layer_args(X, T, K, t, acts, enable_awe, enable_bc, bits, group, w8a8, forward, fused_weight_pass):
+    """The fields of binding.CalibLayer from the buffers `t` (acts: xq, rowsum_x, colsum_xq)."""
+    ws = t["ws"]
+    return (X, _dt(X), T, K, X.stride(0), t["xmin"], t["xmax"], t["xsum"], t["count"], t["r_x"], t["R_x"], t["p_x"], t["wmin"], t["wmax"],
+            t["wcount"], t["r_w"], t["R_w"], t["p_w"], t["s"], t["inv_s"], t["xhat_range"], t["mu_xhat"], t["act_step"], t["act_zero"], *acts,
+            int(enable_awe), int(enable_bc), bits, group, int(w8a8), int(forward), int(fused_weight_pass), ws, ws.numel() * ws.element_size(),
+            t["status"])
 
 
 @dataclass
@@ -59,7 +68,7 @@ class LayerBuffers:
         t["delta"], t["bias_out"] = e(N, dtype=f32), e(N, dtype=f32)
         ws = max(B.aweq_workspace_size(B.OP_CALIB_STATS, T, K, N), B.aweq_workspace_size(B.OP_CALIB_STATS, N, K, N),
                  B.aweq_workspace_size(B.OP_QUANT_WEIGHT, N, K, N),
-                 B.aweq_workspace_size(B.OP_W8A8_GEMM, T, K, N) if self.w8a8 else 0, 16)
+                 B.aweq_workspace_size(B.OP_W8A8_GEMM, T, K, N) if self.w8a8 else 0, B.aweq_workspace_size(B.OP_CALIBRATE, T, K, N), 16)
         t["ws"] = e(ws, dtype=torch.uint8)
         if self.w8a8:
             t["xq"] = e(B.aweq_panel_bytes(T, K), dtype=torch.int8)
@@ -78,49 +87,17 @@ def calibrate_layer(X: torch.Tensor, W: torch.Tensor, bias: Optional[torch.Tenso
     """One pass of the whole hot path for one linear layer.  Everything is enqueued on the
     current (or given) stream; nothing synchronises.  forward = False (W8A8) calibrates without
     running the int8 GEMM: the activation quantizer only forms its sums and the bias correction
-    takes the accumulator's sums over tokens from the weight codes (the same integers)."""
+    takes the accumulator's sums over tokens from the weight codes (the same integers).
+    fused_weight_pass matters only where the stages run one by one (include/aweq.h): it fuses fold and quantizer there."""
     t = buf.t
-    T, K, N = buf.T, buf.K, buf.N
-    dt = _dt(X)
-    st = t["status"]
-    # stage 1: statistics of X and of W
-    B.aweq_calib_stats(X, dt, T, K, X.stride(0), t["xmin"], t["xmax"], t["xsum"], t["count"], 0, 1,
-                       t["r_x"], t["R_x"], t["p_x"], t["ws"], st, stream)
-    B.aweq_calib_stats(W, dt, N, K, W.stride(0), t["wmin"], t["wmax"], None, t["wcount"], 0, 1,
-                       t["r_w"], t["R_w"], t["p_w"], t["ws"], st, stream)
-    fused = fused_weight_pass and buf.group == 0
-    ldw, ldwh = W.stride(0), t["W_hat"].stride(0)   # W may be a pitched view (a row slice of a fused qkv weight)
-    # stage 2: equalization scales, fold into W, equalised activation range / mean / quantizer
-    B.aweq_equalize(t["xmin"], t["xmax"], t["xsum"], T, t["wmin"], t["wmax"], K, enable_awe, t["s"], t["inv_s"],
-                    None if fused else W, t["W_hat"], dt, N, ldw, ldwh, None, t["xhat_range"], t["mu_xhat"],
-                    t["act_step"], t["act_zero"], st, stream)
-    # stage 3: weight quantizer (fused: fold and quantise in one pass over W)
-    if fused:
-        B.aweq_fold_quant_weight(W, dt, N, K, ldw, t["s"], t["W_hat"], ldwh, buf.bits, t["codes"], t["step_w"], t["zero_w"],
-                                 t["rowsum_w"] if buf.bits == 8 else None, st, stream)
-    else:
-        B.aweq_quant_weight(t["W_hat"], dt, N, K, ldwh, buf.bits, buf.group, t["codes"], t["step_w"], t["zero_w"],
-                            t["rowsum_w"] if (buf.bits == 8 and buf.group <= 0) else None, t["ws"], st, stream)
-    wg = -1 if buf.group < 0 else 0   # per-tensor weights (Sec. 3): one (Step, Z), read as such by stages 4 and 5
-    if buf.w8a8 and not forward:
-        B.aweq_quant_act(X, dt, T, K, X.stride(0), t["inv_s"], t["act_step"], t["act_zero"], None, None, t["colsum_xq"],
-                         t["ws"], st, stream)
-        B.aweq_bias_correct(B.BIAS_W8A8, t["W_hat"], dt, N, K, ldwh, t["mu_xhat"], T, None, t["colsum_xq"], t["rowsum_w"],
-                            t["act_step"], t["act_zero"], t["codes"], 8, wg, t["step_w"], t["zero_w"], bias, t["delta"],
-                            t["bias_out"], enable_bc, st, stream)
-    elif buf.w8a8:
-        # stage 4: activation quantizer + int8 GEMM (+ per-channel output sums for stage 5)
-        B.aweq_w8a8_gemm(X, dt, T, K, X.stride(0), t["inv_s"], t["act_step"], t["act_zero"], t["xq"], t["rowsum_x"],
-                         t["colsum_xq"], t["codes"], N, t["step_w"], t["zero_w"], wg, t["rowsum_w"], bias,
-                         t.get("out_i32"), t.get("out_deq"), dt, N, t["colsum_acc"], t["ws"], st, stream)
-        # stage 5: bias correction
-        B.aweq_bias_correct(B.BIAS_W8A8, t["W_hat"], dt, N, K, ldwh, t["mu_xhat"], T, t["colsum_acc"], t["colsum_xq"],
-                            t["rowsum_w"], t["act_step"], t["act_zero"], None, 8, wg, t["step_w"], t["zero_w"], bias,
-                            t["delta"], t["bias_out"], enable_bc, st, stream)
-    else:
-        B.aweq_bias_correct(B.BIAS_WEIGHT_ONLY, t["W_hat"], dt, N, K, ldwh, t["mu_xhat"], T, None, None, None, None, None,
-                            t["codes"], buf.bits, buf.group, t["step_w"], t["zero_w"], bias, t["delta"],
-                            t["bias_out"], enable_bc, st, stream)
+    w8a8, forward = buf.w8a8, buf.w8a8 and forward
+    out_i32, out_deq = (t.get("out_i32"), t.get("out_deq")) if forward else (None, None)
+    B.aweq_calibrate(
+        _layer_args(X, buf.T, buf.K, t, (t["xq"], t["rowsum_x"], t["colsum_xq"]) if forward else (None, None, t["colsum_xq"] if w8a8 else None),
+                    enable_awe, enable_bc, buf.bits, buf.group, w8a8, forward, fused_weight_pass),
+        [(W, buf.N, W.stride(0), t["W_hat"], t["W_hat"].stride(0), t["codes"], t["step_w"], t["zero_w"],
+          t["rowsum_w"], bias, t["delta"], t["bias_out"], out_i32, out_deq,
+          t["colsum_acc"] if forward else None)], stream)   # W may be a pitched view (a row slice of a fused qkv weight)
     return t
 
 
@@ -155,7 +132,8 @@ class GroupBuffers:
         t["xq"] = e(B.aweq_panel_bytes(T, K), dtype=torch.int8)
         t["rowsum_x"] = e(T, dtype=i32)
         t["colsum_xq"] = e(K, dtype=i64)
-        ws = max([B.aweq_workspace_size(B.OP_CALIB_STATS, T, K, 0), B.aweq_workspace_size(B.OP_QUANT_ACT, T, K, 0)] +
+        ws = max([B.aweq_workspace_size(B.OP_CALIB_STATS, T, K, 0), B.aweq_workspace_size(B.OP_QUANT_ACT, T, K, 0),
+                  B.aweq_workspace_size(B.OP_CALIBRATE, T, K, sum(self.Ns))] +
                  [B.aweq_workspace_size(B.OP_CALIB_STATS, N, K, N) for N in self.Ns] + [16])
         t["ws"] = e(ws, dtype=torch.uint8)
         for N in self.Ns:
@@ -173,31 +151,9 @@ def calibrate_group(X: torch.Tensor, Ws, biases, gb: GroupBuffers, enable_awe: b
                     stream=None):
     """W8A8 calibration of linears sharing the input X (Sec. 3.1: equalization sits at the
     entrance of the attention block and of the MLP, so layers with a common input share s)."""
-    t, T, K = gb.t, gb.T, gb.K
-    dt = _dt(X)
-    st = t["status"]
-    B.aweq_calib_stats(X, dt, T, K, X.stride(0), t["xmin"], t["xmax"], t["xsum"], t["count"], 0, 1,
-                       t["r_x"], t["R_x"], t["p_x"], t["ws"], st, stream)
-    # weight ranges of the group: min of mins / max of maxes over all its weights
-    for i, W in enumerate(Ws):
-        last = i == len(Ws) - 1
-        B.aweq_calib_stats(W, dt, W.shape[0], K, W.stride(0), t["wmin"], t["wmax"], None, t["wcount"], int(i > 0),
-                           int(last), t["r_w"], t["R_w"], t["p_w"], t["ws"], st, stream)
-    # the scales (and the activation quantizer) depend on the group's merged ranges only: computed once
-    B.aweq_equalize(t["xmin"], t["xmax"], t["xsum"], T, t["wmin"], t["wmax"], K, enable_awe, t["s"], t["inv_s"],
-                    None, None, dt, 0, K, K, None, t["xhat_range"], t["mu_xhat"], t["act_step"], t["act_zero"], st, stream)
-    for W, p in zip(Ws, gb.per):
-        # fold (Eq. 3) and per-channel quantizer in one pass over each weight
-        B.aweq_fold_quant_weight(W, dt, W.shape[0], K, W.stride(0), t["s"], p["W_hat"], p["W_hat"].stride(0), 8, p["codes"],
-                                 p["step_w"], p["zero_w"], p["rowsum_w"], st, stream)
-    B.aweq_quant_act(X, dt, T, K, X.stride(0), t["inv_s"], t["act_step"], t["act_zero"], t["xq"], t["rowsum_x"],
-                     t["colsum_xq"], t["ws"], st, stream)
-    for W, b, p in zip(Ws, biases, gb.per):
-        N = W.shape[0]
-        B.aweq_w8a8_gemm(t["xq"], B.AWEQ_I8, T, K, K, None, t["act_step"], t["act_zero"], None, t["rowsum_x"], None,
-                         p["codes"], N, p["step_w"], p["zero_w"], 0, p["rowsum_w"], b, p.get("out_i32"),
-                         p.get("out_deq"), dt, N, p["colsum_acc"], None, st, stream)
-        B.aweq_bias_correct(B.BIAS_W8A8, p["W_hat"], dt, N, K, p["W_hat"].stride(0), t["mu_xhat"], T, p["colsum_acc"],
-                            t["colsum_xq"], p["rowsum_w"], t["act_step"], t["act_zero"], None, 8, 0, p["step_w"], p["zero_w"], b,
-                            p["delta"], p["bias_out"], enable_bc, st, stream)
+    t = gb.t
+    B.aweq_calibrate(
+        _layer_args(X, gb.T, gb.K, t, (t["xq"], t["rowsum_x"], t["colsum_xq"]), enable_awe, enable_bc, 8, 0, True, True, True),
+        [(W, W.shape[0], W.stride(0), p["W_hat"], p["W_hat"].stride(0), p["codes"], p["step_w"], p["zero_w"], p["rowsum_w"], b, p["delta"],
+          p["bias_out"], p.get("out_i32"), p.get("out_deq"), p["colsum_acc"]) for W, b, p in zip(Ws, biases, gb.per)], stream)
     return gb
