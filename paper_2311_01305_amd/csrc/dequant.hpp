@@ -60,6 +60,13 @@ __device__ __forceinline__ uint32_t fields3(const RawCodes<3>& rc, int d)
          : d == 2 ? __builtin_amdgcn_alignbit(rc.w[2], rc.w[1], 16) : rc.w[2] >> 8;
 }
 
+template <int BITS>
+__device__ __forceinline__ uint32_t fields_of(const RawCodes<BITS>& rc, int d)   // codes k = 8 d .. 8 d + 7 of the 32
+{
+    if constexpr (BITS == 4) return rc.w[d];
+    else return fields3(rc, d);
+}
+
 // (w & mask) | magic in one operation: the compiler spends two on literals, so they sit in registers it cannot see into
 __device__ __forceinline__ uint32_t field(uint32_t w, uint32_t mask, uint32_t magic)
 {
@@ -113,8 +120,7 @@ __device__ __forceinline__ v4i dequant_word_natural(uint32_t w, const Scale<BITS
 template <int BITS>
 __device__ __forceinline__ void dequant8_pairs(const RawCodes<BITS>& rc, int d, const Scale<BITS>& s, uint32_t o[4])
 {
-    if constexpr (BITS == 4) dequant_word<4>(rc.w[d], s, o);
-    else dequant_word<3>(fields3(rc, d), s, o);
+    dequant_word<BITS>(fields_of<BITS>(rc, d), s, o);
 }
 
 // the same pairs for any zero point, through binary32
@@ -133,8 +139,7 @@ __device__ __forceinline__ void dequant_word_any(uint32_t w, const Scale<BITS>& 
 template <int BITS>
 __device__ __forceinline__ void dequant8_pairs_any(const RawCodes<BITS>& rc, int d, const Scale<BITS>& s, uint32_t o[4])
 {
-    if constexpr (BITS == 4) dequant_word_any<4>(rc.w[d], s, o);
-    else dequant_word_any<3>(fields3(rc, d), s, o);
+    dequant_word_any<BITS>(fields_of<BITS>(rc, d), s, o);
 }
 
 // pairs (k, k + 4) -> natural order (and back: the permutation of a 16-byte chunk of 8 halves is its own kind)

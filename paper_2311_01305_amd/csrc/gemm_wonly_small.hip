@@ -11,6 +11,12 @@
 // v_mfma_f32_16x16x32_f16, whose two operands may enumerate K in any common order: both use the order in which the
 // code fields come out of their packed words.
 //
+// Reads past an edge repeat the last row or the last values of K (their results are not stored, their activations are zero), so that no
+// load sits in a branch of its own; quads of tokens past the edge are left out.  With more token tiles than channel tiles the codes
+// are brought to the activations' natural order instead of the other way round (INT4 / INT3, us on the device with the weight in the
+// caches, before -> now: 17 tokens 4096 x 4096 7.2 -> 6.4 / 7.2 -> 6.5, 4096 x 11008 13.7 -> 11.6 / 14.0 -> 12.1; one token 11008 x 4096
+// 7.9 -> 7.6 / 8.4 -> 8.2; 16 tokens and 64 within 2 %).  Bound by the vector unit there: 85 operations for 32 codes a lane with their scale.
+//
 // Bound by the read of the codes and, for small layers, by the launch and one round trip to memory.  Measured (INT4,
 // groups of 128, us per call on the device; before = de-quantising the whole weight and a 256 x 256-tiled GEMM):
 //   tokens          1            16           32           64           128          256
@@ -28,8 +34,6 @@ namespace wonly {
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
-constexpr int kSmallThreads = 512;
-constexpr int kSmallWaves = kSmallThreads / kWave;
 constexpr int kChunk = 256;   // values of K a wavefront takes at a time
 
 // LDS per wavefront: 128 values of RX tokens (256 for RX = 4), 256 codes of 16 NT channels (16 bytes per 32 codes)
@@ -37,12 +41,15 @@ constexpr int small_wave_lds(int rx, int nt) { return (rx == 4 ? 4 * 512 : rx * 
 
 // FINE: groups that are no multiple of 128 (a lane's 32 codes have one (Step, Z), but the four lanes that share
 // 128 values of a channel may differ)
-template <int BITS, int RX, int NT, bool FINE, bool OUT_F16>
-__global__ __launch_bounds__(kSmallThreads) void gemm_small_kernel(SmallArgs g)
+template <int BITS, int RX, int NT, int WAVES, bool FINE, bool OUT_F16>
+__global__ __launch_bounds__(WAVES * kWave) void gemm_small_kernel(SmallArgs g)
 {
     constexpr int TT = RX < 16 ? 1 : RX / 16;
     constexpr int XH = RX == 4 ? 1 : 2;             // activation loads per chunk: whole, or 128 values at a time
     constexpr int XL = RX == 4 ? 2 : 4 * TT;        // 16-byte loads of activations per lane and time
+    constexpr bool kNatural = TT > NT;              // the operand with fewer tiles is the one that is brought to the other's order
+    constexpr int kWords = BITS == 4 ? 4 : 3;
+    typedef int Words __attribute__((ext_vector_type(kWords)));
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
@@ -62,44 +69,46 @@ __global__ __launch_bounds__(kSmallThreads) void gemm_small_kernel(SmallArgs g)
 #pragma unroll
     for (int j = 0; j < NT; ++j)
 #pragma unroll
-        for (int i = 0; i < 2; ++i) crow[j][i] = (uint32_t)min(16 * j + 8 * i + c_row, rows_left) * code_pitch + c_piece * (4 * BITS);
+        for (int i = 0; i < 2; ++i) crow[j][i] = (uint32_t)min(16 * j + 8 * i + c_row, rows_left) * code_pitch;
     // (Step, Z): lane -> row lane / 4 of 16, {Step, Step, Z, Z} of the chunk's first / second 128 values
     const uint32_t* const sbase = ((lane & 2) ? reinterpret_cast<const uint32_t*>(g.zero) : reinterpret_cast<const uint32_t*>(g.step)) +
                                   n0 * g.scale_pitch;
     uint32_t srow[NT];
 #pragma unroll
     for (int j = 0; j < NT; ++j) srow[j] = (uint32_t)min(16 * j + (FINE ? r : lane >> 2), rows_left) * g.scale_pitch;
-    // activations: lane -> token 4 i + lane / 16, 8 values lane % 16 of 128 (RX = 4: the second load is the second 128)
+    // activations: lane -> token 4 i + lane / 16, 8 values lane % 16 of 128 (RX = 4: the second load is the second 128).  Tokens past the
+    // edge re-read the last one, quads of them are left out; their columns are not stored.
     const _Float16* const xbase = g.X + t0 * g.ldx;
     const int tokens_left = (int)min(g.T - t0, (int64_t)(16 * TT));
-    const uint32_t xoff = (uint32_t)(lane >> 4) * (uint32_t)g.ldx + (lane & 15) * 8, x_pitch4 = 4u * (uint32_t)g.ldx;
+    constexpr int XR = RX == 4 ? 1 : XL;
+    uint32_t xrow[XR];
+#pragma unroll
+    for (int i = 0; i < XR; ++i)
+        xrow[i] = min((uint32_t)(lane >> 4) * (uint32_t)g.ldx + (uint32_t)(4 * i) * (uint32_t)g.ldx, (uint32_t)(tokens_left - 1) * (uint32_t)g.ldx);
 
     RawCodes<BITS> rc[NT][2];
     uint32_t sc[NT];
-    v4i xr[XL];
+    v4i xr[XL] = {};
+    // (past K the last values again: the activations they meet are zero)
     auto load_codes_at = [&](int k) {
+        const uint32_t co = (uint32_t)(min(k + c_piece * 32, K - 32) >> 5) * (4 * BITS);
+        const uint32_t so = FINE ? 0u : __umulhi((uint32_t)min(k + (lane & 1) * 128, K - 32) >> 4, g.group_magic);
 #pragma unroll
         for (int j = 0; j < NT; ++j) {
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-#pragma unroll
-                for (int e = 0; e < (BITS == 4 ? 4 : 3); ++e) rc[j][i].w[e] = 0u;
-                if (k + c_piece * 32 < K) rc[j][i] = load_codes<BITS>(cbase + (crow[j][i] + (uint32_t)(k >> 5) * (4 * BITS)));
-            }
-            sc[j] = 0u;
-            if constexpr (!FINE) {
-                const int ks = k + (lane & 1) * 128;
-                if (ks < K) sc[j] = sbase[srow[j] + __umulhi((uint32_t)ks >> 4, g.group_magic)];
-            }
+            for (int i = 0; i < 2; ++i) rc[j][i] = load_codes<BITS>(cbase + (crow[j][i] + co));
+            sc[j] = FINE ? 0u : sbase[srow[j] + so];
         }
     };
     auto load_x_at = [&](int k) {
+        if constexpr (RX == 4) {
+            if ((lane >> 4) >= tokens_left) return;   // (a quarter of the lines for one token)
+        }
 #pragma unroll
         for (int i = 0; i < XL; ++i) {
-            const int row = RX == 4 ? 0 : 4 * i, kk = RX == 4 ? k + 128 * i : k;
-            xr[i] = v4i{0, 0, 0, 0};
-            if (row + (lane >> 4) < tokens_left && kk + (lane & 15) * 8 < K)
-                xr[i] = *reinterpret_cast<const v4i*>(xbase + (xoff + (uint32_t)(row / 4) * x_pitch4 + (uint32_t)kk));
+            if (RX > 4 && 4 * i >= tokens_left) break;
+            const uint32_t xo = (uint32_t)min((RX == 4 ? k + 128 * i : k) + (lane & 15) * 8, K - 8);
+            xr[i] = *reinterpret_cast<const v4i*>(xbase + (xrow[RX == 4 ? 0 : i] + xo));
         }
     };
 
@@ -110,7 +119,7 @@ __global__ __launch_bounds__(kSmallThreads) void gemm_small_kernel(SmallArgs g)
 #pragma unroll
         for (int j = 0; j < NT; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
 
-    constexpr int kStride = kSmallWaves * kChunk;
+    constexpr int kStride = WAVES * kChunk;
     int kc = wave * kChunk;
     if (kc < K) { load_codes_at(kc); load_x_at(kc); }
     for (; kc < K; kc += kStride) {
@@ -121,9 +130,10 @@ __global__ __launch_bounds__(kSmallThreads) void gemm_small_kernel(SmallArgs g)
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 const int row = 8 * i + c_row;
-                v4i w = {(int)rc[j][i].w[0], (int)rc[j][i].w[1], (int)rc[j][i].w[2], 0};
-                if constexpr (BITS == 4) w[3] = (int)rc[j][i].w[3];
-                *reinterpret_cast<v4i*>(lc + j * 2048 + row * 128 + ((c_piece ^ (row & 7)) * 16)) = w;
+                Words w;   // (INT3: 12 bytes of the 16.  As four registers the compiler waited for the load here, to move it)
+#pragma unroll
+                for (int e = 0; e < kWords; ++e) w[e] = (int)rc[j][i].w[e];
+                *reinterpret_cast<Words*>(lc + j * 2048 + row * 128 + ((c_piece ^ (row & 7)) * 16)) = w;
             }
         }
         wave_lds_fence();
@@ -134,8 +144,10 @@ __global__ __launch_bounds__(kSmallThreads) void gemm_small_kernel(SmallArgs g)
             if (h < XH) {
 #pragma unroll
                 for (int i = 0; i < XL; ++i) {
-                    const int row = (RX == 4 ? 0 : 4 * i) + (lane >> 4);
-                    *reinterpret_cast<v4i*>(lx + (RX == 4 ? i * 1024 : 0) + row * 256 + (((lane & 15) ^ (row & 15)) * 16)) = pair_order(xr[i]);
+                    if (RX > 4 && 4 * i >= tokens_left) break;
+                    const int row = (RX == 4 ? 0 : 4 * i) + (lane >> 4), k = kc + (RX == 4 ? i : h) * 128;
+                    if (k + 128 > K && k + (lane & 15) * 8 >= K) xr[i] = v4i{0, 0, 0, 0};
+                    *reinterpret_cast<v4i*>(lx + (RX == 4 ? i * 1024 : 0) + row * 256 + (((lane & 15) ^ (row & 15)) * 16)) = kNatural ? xr[i] : pair_order(xr[i]);
                 }
                 wave_lds_fence();
                 const int kx = h + 1 < XH ? kc + 128 : kc + kStride;
@@ -146,10 +158,10 @@ __global__ __launch_bounds__(kSmallThreads) void gemm_small_kernel(SmallArgs g)
                 return __builtin_bit_cast(v8h, *reinterpret_cast<const v4i*>(lx + (RX == 4 ? h * 1024 : i * 4096) + fr * 256 + (((4 * q + d) ^ fr) * 16)));
             };
             auto frag_w = [&](int j, uint32_t w[4][4]) {
-                const v4i cw = *reinterpret_cast<const v4i*>(lc + j * 2048 + r * 128 + (((4 * h + q) ^ (r & 7)) * 16));
+                const Words cw = *reinterpret_cast<const Words*>(lc + j * 2048 + r * 128 + (((4 * h + q) ^ (r & 7)) * 16));
                 RawCodes<BITS> c;
 #pragma unroll
-                for (int e = 0; e < (BITS == 4 ? 4 : 3); ++e) c.w[e] = (uint32_t)cw[e];
+                for (int e = 0; e < kWords; ++e) c.w[e] = (uint32_t)cw[e];
                 Scale<BITS> s;
                 if constexpr (FINE) {
                     const int k = kc + h * 128 + q * 32;
@@ -161,10 +173,25 @@ __global__ __launch_bounds__(kSmallThreads) void gemm_small_kernel(SmallArgs g)
                 }
                 if (__all(s.packed)) {
 #pragma unroll
-                    for (int d = 0; d < 4; ++d) dequant8_pairs<BITS>(c, d, s, w[d]);
+                    for (int d = 0; d < 4; ++d) {
+                        if constexpr (kNatural) {
+                            const v4i o = dequant_word_natural<BITS>(fields_of<BITS>(c, d), s);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) w[d][e] = (uint32_t)o[e];
+                        } else {
+                            dequant8_pairs<BITS>(c, d, s, w[d]);
+                        }
+                    }
                 } else {
 #pragma unroll
-                    for (int d = 0; d < 4; ++d) dequant8_pairs_any<BITS>(c, d, s, w[d]);
+                    for (int d = 0; d < 4; ++d) {
+                        dequant8_pairs_any<BITS>(c, d, s, w[d]);
+                        if constexpr (kNatural) {
+                            const v4i o = natural_order(w[d]);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) w[d][e] = (uint32_t)o[e];
+                        }
+                    }
                 }
             };
             auto mul = [&](int i, int j, const uint32_t w[4], v8h x) {
@@ -212,13 +239,13 @@ __global__ __launch_bounds__(kSmallThreads) void gemm_small_kernel(SmallArgs g)
 #pragma unroll
         for (int j = 0; j < NT; ++j) *reinterpret_cast<v4f*>(red + ((wave * kTiles + i * NT + j) * kWave + lane) * 4) = acc[i][j];
     __syncthreads();
-    for (int e = threadIdx.x; e < kTiles * kWave; e += kSmallThreads) {
+    for (int e = threadIdx.x; e < kTiles * kWave; e += WAVES * kWave) {
         const int tile = e / kWave, l = e & (kWave - 1);
         const int64_t t = t0 + 16 * (tile / NT) + (l & 15), n = n0 + 16 * (tile % NT) + 4 * (l >> 4);
         if (t >= g.T || n >= g.N) continue;     // N % 4 == 0: all four channels or none
         v4f o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int w = 0; w < kSmallWaves; ++w) o += *reinterpret_cast<const v4f*>(red + ((w * kTiles + tile) * kWave + l) * 4);
+        for (int w = 0; w < WAVES; ++w) o += *reinterpret_cast<const v4f*>(red + ((w * kTiles + tile) * kWave + l) * 4);
         if (g.bias) o += *reinterpret_cast<const v4f*>(g.bias + n);
         if constexpr (OUT_F16) {
             typedef _Float16 h4 __attribute__((ext_vector_type(4)));
@@ -230,21 +257,21 @@ __global__ __launch_bounds__(kSmallThreads) void gemm_small_kernel(SmallArgs g)
     }
 }
 
-template <int BITS, int RX, int NT>
+template <int BITS, int RX, int NT, int WAVES>
 static int launch_tile(const SmallArgs& g, bool fine, bool out_f16, hipStream_t st)
 {
     constexpr int TT = RX < 16 ? 1 : RX / 16;
     const dim3 grid((unsigned)cdiv(g.N, 16 * NT), (unsigned)cdiv(g.T, RX));
-    constexpr int work = kSmallWaves * small_wave_lds(RX, NT), red = kSmallWaves * TT * NT * kWave * 16;
+    constexpr int work = WAVES * small_wave_lds(RX, NT), red = WAVES * TT * NT * kWave * 16;
     constexpr int lds = work > red ? work : red;
-    const void* fn = fine ? (out_f16 ? reinterpret_cast<const void*>(gemm_small_kernel<BITS, RX, NT, true, true>)
-                                     : reinterpret_cast<const void*>(gemm_small_kernel<BITS, RX, NT, true, false>))
-                          : (out_f16 ? reinterpret_cast<const void*>(gemm_small_kernel<BITS, RX, NT, false, true>)
-                                     : reinterpret_cast<const void*>(gemm_small_kernel<BITS, RX, NT, false, false>));
+    const void* fn = fine ? (out_f16 ? reinterpret_cast<const void*>(gemm_small_kernel<BITS, RX, NT, WAVES, true, true>)
+                                     : reinterpret_cast<const void*>(gemm_small_kernel<BITS, RX, NT, WAVES, true, false>))
+                          : (out_f16 ? reinterpret_cast<const void*>(gemm_small_kernel<BITS, RX, NT, WAVES, false, true>)
+                                     : reinterpret_cast<const void*>(gemm_small_kernel<BITS, RX, NT, WAVES, false, false>));
     int dev = 0, cus = 0;
     if (lds > 65536 && (device_cus(dev, cus) != AWEQ_OK || raise_lds_limit(fn, dev, lds) != AWEQ_OK)) return AWEQ_ERR_LAUNCH;
     void* args[] = {const_cast<SmallArgs*>(&g)};
-    if (hipLaunchKernel(fn, grid, dim3(kSmallThreads), args, lds, st) != hipSuccess) return AWEQ_ERR_LAUNCH;
+    if (hipLaunchKernel(fn, grid, dim3(WAVES * kWave), args, lds, st) != hipSuccess) return AWEQ_ERR_LAUNCH;
     return launch_status();
 }
 
@@ -267,10 +294,20 @@ SmallPlan plan_small(int64_t T, int64_t N)
 template <int BITS>
 static int launch_bits(const SmallArgs& g, bool fine, int nt, bool out_f16, hipStream_t st)
 {
-    if (g.T <= 4) return nt == 2 ? launch_tile<BITS, 4, 2>(g, fine, out_f16, st) : launch_tile<BITS, 4, 1>(g, fine, out_f16, st);
-    if (g.T <= 16) return nt == 2 ? launch_tile<BITS, 16, 2>(g, fine, out_f16, st) : launch_tile<BITS, 16, 1>(g, fine, out_f16, st);
-    return nt == 1 ? launch_tile<BITS, 32, 1>(g, fine, out_f16, st) : nt == 2 ? launch_tile<BITS, 32, 2>(g, fine, out_f16, st)
-                                                                              : launch_tile<BITS, 32, 4>(g, fine, out_f16, st);
+    // Long rows on at most one workgroup per compute unit: K split between 16 wavefronts instead of 8, from two chunks a wavefront on (us, INT4,
+    // 8 -> 16: one token 1024 x 22016 12.0 -> 10.7, 4096 x 11008 7.6 -> 7.1, 2048 x 8192 6.1 -> 5.9, 4096 x 4096 the same; 16 tokens 1024 x 22016
+    // 17.2 -> 14.8, but 2048 x 8192 8.4 -> 8.5; 32 tokens do not fit the registers: 4096 x 11008 13.8 -> 16.1)
+    const bool lone = cdiv(g.N, 16) <= 256;
+    if (g.T <= 4) {
+        if (nt == 2) return launch_tile<BITS, 4, 2, 8>(g, fine, out_f16, st);
+        return lone && g.K >= 8192 ? launch_tile<BITS, 4, 1, 16>(g, fine, out_f16, st) : launch_tile<BITS, 4, 1, 8>(g, fine, out_f16, st);
+    }
+    if (g.T <= 16) {
+        if (nt == 2) return launch_tile<BITS, 16, 2, 8>(g, fine, out_f16, st);
+        return lone && g.K >= 16384 ? launch_tile<BITS, 16, 1, 16>(g, fine, out_f16, st) : launch_tile<BITS, 16, 1, 8>(g, fine, out_f16, st);
+    }
+    return nt == 1 ? launch_tile<BITS, 32, 1, 8>(g, fine, out_f16, st) : nt == 2 ? launch_tile<BITS, 32, 2, 8>(g, fine, out_f16, st)
+                                                                                 : launch_tile<BITS, 32, 4, 8>(g, fine, out_f16, st);
 }
 
 int launch_small(const SmallArgs& g, int bits, int group, const SmallPlan& p, bool out_f16, hipStream_t st)
