@@ -53,10 +53,12 @@ constexpr unsigned kQaXcds = 8;                         // workgroup id % 8 name
 // SUMS: neither codes nor row sums are asked for (a calibration without the forward): 14331 x 11008 binary16 72.3 -> 66.3 us
 // without packing the codes, 7419 x 4096 binary32 29.5.
 // KEEP: the codes are stored through the caches for the GEMM that reads them next (rule and figures at the launch).
-// A thread has kBatch groups of 8 rows in flight; the first are requested ahead of Step, Z and the scales, the next after the
-// last of a group has been consumed (8192 x 4096 36.6 -> 35.4 us, 262144 x 8192 1209 -> 1199).  Two groups: four take
-// binary32 210 registers, two wavefronts to a SIMD instead of three (us, 4 -> 2 groups, codes and sums: 4096 x 11008 63.8 -> 51.2,
-// 8192 x 22016 247 -> 222; sums alone 16000 x 4096 59.3 -> 50.2).
+// Whole groups of 8 rows x 2 whole panels of a wavefront go through a ring of two groups in flight, the first requested ahead of Step, Z and the
+// scales, each refilled as soon as it has been consumed, and no load sits in a branch: with the loads predicated the compiler
+// waited for all of them before every unit (us: sums alone 14331 x 11008 71 -> 60, 65536 x 4096 114 -> 102; codes and sums 8192 x 4096 34.1 -> 30.9,
+// 16384 x 16384 175 -> 164, 5000 x 22016 95 -> 83; binary32 7419 x 4096 41.4 -> 36.5, 2048 x 512 10.5 -> 9.1; 262144 x 8192, at the memory's rate,
+// 1178 -> 1174).  Four groups take 147 registers, three wavefronts to a SIMD: 63.0 / 32.7 / 158.6 in place of 59.7 / 30.8 / 163.4; one group
+// 64 / 32 / 170.
 template <bool F16, bool SUMS, bool KEEP>
 __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
     const void* __restrict__ X, int64_t T, int64_t K, int64_t ldx, const float* __restrict__ inv_s,
@@ -70,7 +72,7 @@ __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
     const int64_t slice = pair / (unsigned)chunks;
     __shared__ int lds_rs[kQaMaxRows][kQaWaves];
     const int lane = threadIdx.x & (kWave - 1);
-    const int wave = threadIdx.x / kWave;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     const int rsub = lane >> 3, c8 = lane & 7;
     const int64_t r0 = slice * rows_per_block;
     const int nrows = (int)min((int64_t)rows_per_block, T - r0);
@@ -87,15 +89,21 @@ __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
         valid[j] = col0 + j * kPanel < K;
         pad[j] = !valid[j] && panel0 + j < np;  // zero fill of the last panel
     }
-    constexpr int kBatch = 2, kRowsPerIter = 8 * kBatch;
-    RawUnit<F16> raw[kBatch][kQaVpt];
-    auto request = [&](int b, int j, int row) {
-        if (row < nrows && valid[j]) raw[b][j].load(src0, (int64_t)row * ldx + j * kPanel);
+    // Whole groups of 8 rows of whole panels go through a ring of kRing groups in flight, without a branch around any load: each
+    // group's registers are refilled as soon as they have been consumed.  (With the loads predicated the compiler waited for all of
+    // them before each unit.)
+    constexpr int kRing = 2;
+    const bool whole = (panel0 + kQaVpt) * kPanel <= K && nrows >= 8 * kRing;   // uniform in the wavefront
+    const int ring_groups = whole ? nrows / (8 * kRing) * kRing : 0;
+    RawUnit<F16> raw[kRing][kQaVpt];
+    auto request = [&](int b, int group) {
+#pragma unroll
+        for (int j = 0; j < kQaVpt; ++j) raw[b][j].load(src0, (int64_t)(8 * group + rsub) * ldx + j * kPanel);
     };
+    if (whole) {
 #pragma unroll
-    for (int b = 0; b < kBatch; ++b)
-#pragma unroll
-        for (int j = 0; j < kQaVpt; ++j) request(b, j, 8 * b + rsub);
+        for (int b = 0; b < kRing; ++b) request(b, b);
+    }
 
     uint32_t st = 0;
     float step;
@@ -121,9 +129,14 @@ __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
     float is_max = 0.0f;
 #pragma unroll
     for (int j = 0; j < kQaVpt; ++j) {
+        // (the last unit again past the edge; 16 bytes at a time, aligned to 4)
+        typedef float v4f_ __attribute__((ext_vector_type(4), aligned(4)));
+        const v4f_* const q = reinterpret_cast<const v4f_*>(inv_s + min((int64_t)col0 + j * kPanel, K - 8));
+        const v4f_ a = q[0], b = q[1];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { is[j][i] = a[i]; is[j][4 + i] = b[i]; }
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            is[j][i] = valid[j] ? inv_s[col0 + j * kPanel + i] : 1.0f;
             // the exactness argument needs a y not to overflow: binary16 |x| < 2^16, Step >= 2^-60
             if (!(fabsf(is[j][i]) < 1.0e12f)) fast_thread = false;
             is_max = fmaxf(is_max, fabsf(is[j][i]));
@@ -144,50 +157,75 @@ __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
         for (int i = 0; i < 8; ++i) { csf[j][i] = 0.0f; csi[j][i] = 0; }
     int my_rows = 0;
 
-    auto rows_loop = [&](auto mode_c) {
+    // one unit: its code bytes to d
+    auto unit = [&](auto mode_c, const RawUnit<F16>& u, int j, int8_t* d, int& rs) {
         constexpr int MODE = decltype(mode_c)::value;
-        for (int rb = 0; rb < nrows; rb += kRowsPerIter) {
+        float x[8];
+        u.get(x);
+        const uint2 w = act_unit<MODE, SUMS>(x, is[j], p, csf[j], csi[j], rs, big, st);
+        if (!SUMS && d) {   // (sums only: no code buffer)
+            if constexpr (KEEP) *reinterpret_cast<v2u*>(d) = v2u{w.x, w.y};
+            else __builtin_nontemporal_store(v2u{w.x, w.y}, reinterpret_cast<v2u*>(d));
+        }
+    };
+    auto row_sum = [&](int rs, int row, bool ok) {
+        if constexpr (!SUMS) {
+            rs = group_allreduce<3>(rs, OpAdd());  // the 8 lanes of one row
+            if (ok && c8 == 0) lds_rs[row][wave] = rs;
+        }
+    };
+    int first = 0;   // rows that the ring has taken
+    auto ring = [&](auto mode_c) {
+        auto take = [&](int b, int group) {
+            const int row = 8 * group + rsub;
+            int rs = 0;
 #pragma unroll
-            for (int b = 0; b < kBatch; ++b) {
-                const int row = rb + 8 * b + rsub;
-                const bool row_ok = row < nrows;
-                int rs = 0;
-                if (row_ok) {
-                    ++my_rows;
+            for (int j = 0; j < kQaVpt; ++j) unit(mode_c, raw[b][j], j, dst0 ? dst0 + j * dst_step + row * kPanel : nullptr, rs);
+            row_sum(rs, row, true);
+        };
+        int g = 0;
+        for (; g + kRing < ring_groups; g += kRing) {
 #pragma unroll
-                    for (int j = 0; j < kQaVpt; ++j) {
-                        int8_t* d = dst0 ? dst0 + j * dst_step + row * kPanel : nullptr;
-                        if (valid[j]) {
-                            float x[8];
-                            raw[b][j].get(x);
-                            const uint2 w = act_unit<MODE, SUMS>(x, is[j], p, csf[j], csi[j], rs, big, st);
-                            if (!SUMS && d) {   // (sums only: no code buffer)
-                                if constexpr (KEEP) *reinterpret_cast<v2u*>(d) = v2u{w.x, w.y};
-                                else __builtin_nontemporal_store(v2u{w.x, w.y}, reinterpret_cast<v2u*>(d));
-                            }
-                        } else if (pad[j] && d) {
-                            *reinterpret_cast<uint2*>(d) = make_uint2(0u, 0u);
-                        }
-                    }
-                }
-                if constexpr (!SUMS) {
-                    rs = group_allreduce<3>(rs, OpAdd());  // the 8 lanes of one row
-                    if (row_ok && c8 == 0) lds_rs[row][wave] = rs;
+            for (int b = 0; b < kRing; ++b) { take(b, g + b); request(b, g + kRing + b); }
+        }
+#pragma unroll
+        for (int b = 0; b < kRing; ++b) take(b, g + b);
+        my_rows += ring_groups;
+        first = 8 * ring_groups;
+    };
+    // any rows and columns, one group of 8 rows at a time
+    auto rest = [&](auto mode_c) {
+        for (int rb = first; rb < nrows; rb += 8) {
+            const int row = rb + rsub;
+            const bool row_ok = row < nrows;
+            int rs = 0;
+            if (row_ok) {
+                ++my_rows;
+                RawUnit<F16> u[kQaVpt];
+#pragma unroll
+                for (int j = 0; j < kQaVpt; ++j)
+                    if (valid[j]) u[j].load(src0, (int64_t)row * ldx + j * kPanel);
+#pragma unroll
+                for (int j = 0; j < kQaVpt; ++j) {
+                    int8_t* const d = dst0 ? dst0 + j * dst_step + row * kPanel : nullptr;
+                    if (valid[j]) unit(mode_c, u[j], j, d, rs);
+                    else if (pad[j] && d) *reinterpret_cast<uint2*>(d) = make_uint2(0u, 0u);
                 }
             }
-#pragma unroll
-            for (int b = 0; b < kBatch; ++b)
-#pragma unroll
-                for (int j = 0; j < kQaVpt; ++j) request(b, j, rb + kRowsPerIter + 8 * b + rsub);
+            row_sum(rs, row, row_ok);
         }
     };
     if constexpr (F16) {
-        if (screen) rows_loop(std::integral_constant<int, 2>{});
-        else if (fast) rows_loop(std::integral_constant<int, 1>{});
-        else rows_loop(std::integral_constant<int, 0>{});
+        if (screen) {
+            if (whole) ring(std::integral_constant<int, 2>{});
+            rest(std::integral_constant<int, 2>{});
+        } else if (fast) rest(std::integral_constant<int, 1>{});
+        else rest(std::integral_constant<int, 0>{});
     } else {
-        if (screen) rows_loop(std::integral_constant<int, 3>{});
-        else rows_loop(std::integral_constant<int, 0>{});
+        if (screen) {
+            if (whole) ring(std::integral_constant<int, 3>{});
+            rest(std::integral_constant<int, 3>{});
+        } else rest(std::integral_constant<int, 0>{});
     }
     if (big >= 16777216.0f) st |= AWEQ_ST_BIGQUOT;
     raise_status(status, st);
@@ -270,7 +308,7 @@ __global__ __launch_bounds__(kQaMergeCols * kQaMergeParts) void quant_act_merge(
 // ---- row form: a block owns ROWS whole rows, so their code sums are complete inside it and no partial buffer or merge
 // is needed.  For calls that do not ask for column sums (a forward with a calibrated scale).  Small calls are bound by
 // the launch and the round trips to memory: one launch instead of two (the figures are at the dispatch below), and a row's
-// next unit is requested while this one is quantised (with the stores that stay in the caches, whole int8 forward, us:
+// next unit is requested while this one is quantised, without a branch around the load (3000 x 4104 14.7 -> 12.6 us, 4096 x 4096 15.2 -> 14.1; with the stores that stay in the caches, whole int8 forward, us:
 // 300 tokens 4096 x 11008 46.4 -> 40.5, 2048 tokens 99.2 -> 95.6, 4096 tokens 11008 x 4096 182.6 -> 178.6).
 constexpr int kQrBlock = 512;
 template <bool F16, int ROWS>
@@ -283,17 +321,15 @@ __global__ __launch_bounds__(kQrBlock) void quant_act_rows(
     const int64_t r0 = (int64_t)blockIdx.x * ROWS;
     const int nrows = (int)min((int64_t)ROWS, T - r0);
     const int64_t units = K / 8, padded = panel_count(K) * (kPanel / 8);
-    // the first unit of every row is requested ahead of Step and Z, the next one as soon as a unit has been consumed
+    // the first unit of every row is requested ahead of Step and Z, the next one as soon as a unit has been consumed (without a branch
+    // around a load: past the end the last unit, the last row again, not stored)
     RawUnit<F16> raw[ROWS];
-    Float4 isa = {}, isb = {};
-    auto request = [&](int i, int64_t u) {
-        if (u < units && i < nrows) raw[i].load(X, (r0 + i) * ldx + u * 8);
-    };
+    Float4 isa, isb;
+    auto request = [&](int i, int64_t u) { raw[i].load(X, (r0 + min(i, nrows - 1)) * ldx + min(u, units - 1) * 8); };
     auto request_is = [&](int64_t u) {
-        if (u < units) {
-            isa = *reinterpret_cast<const Float4*>(inv_s + u * 8);
-            isb = *reinterpret_cast<const Float4*>(inv_s + u * 8 + 4);
-        }
+        const float* const q = inv_s + min(u, units - 1) * 8;
+        isa = *reinterpret_cast<const Float4*>(q);
+        isb = *reinterpret_cast<const Float4*>(q + 4);
     };
 #pragma unroll
     for (int i = 0; i < ROWS; ++i) request(i, threadIdx.x);
@@ -304,25 +340,28 @@ __global__ __launch_bounds__(kQrBlock) void quant_act_rows(
     int rs[ROWS];
 #pragma unroll
     for (int i = 0; i < ROWS; ++i) rs[i] = 0;
-    for (int64_t u = threadIdx.x; u < padded; u += kQrBlock) {
+    auto take = [&](int64_t u, auto more_c) {
         int8_t* const d = xq + ((u >> 3) * T + r0) * kPanel + (u & 7) * 8;
-        if (u >= units) {                      // zero fill of the last panel
-            for (int i = 0; i < nrows; ++i) *reinterpret_cast<uint2*>(d + i * kPanel) = make_uint2(0u, 0u);
-            break;
-        }
         float is[8];
 #pragma unroll
         for (int i = 0; i < 4; ++i) { is[i] = isa.f[i]; is[4 + i] = isb.f[i]; }
-        request_is(u + kQrBlock);
+        if constexpr (decltype(more_c)::value) request_is(u + kQrBlock);
 #pragma unroll
         for (int i = 0; i < ROWS; ++i) {
-            if (i >= nrows) break;
             float x[8];
             raw[i].get(x);
-            request(i, u + kQrBlock);
+            if constexpr (decltype(more_c)::value) request(i, u + kQrBlock);
+            if (i >= nrows) continue;
             const uint2 w = act_unit_any<F16>(x, is, p, rs[i], big, st);
             *reinterpret_cast<v2u*>(d + i * kPanel) = v2u{w.x, w.y};
         }
+    };
+    int64_t u = threadIdx.x, base = 0;
+    for (; base + kQrBlock < units; base += kQrBlock, u += kQrBlock) take(u, std::true_type{});   // (a whole block of units, and more to come)
+    if (u < units) take(u, std::false_type{});
+    else if (u < padded) {                     // zero fill of the last panel (a multiple of 8 units, like the blocks of them)
+        int8_t* const d = xq + ((u >> 3) * T + r0) * kPanel + (u & 7) * 8;
+        for (int i = 0; i < nrows; ++i) *reinterpret_cast<uint2*>(d + i * kPanel) = make_uint2(0u, 0u);
     }
     if (big >= 16777216.0f) st |= AWEQ_ST_BIGQUOT;
     raise_status(status, st);
@@ -373,15 +412,17 @@ int launch_quant_act(const void* X, aweq_dtype dt, int64_t T, int64_t K, int64_t
                      int64_t* colsum_xq, void* ws, uint32_t* status, hipStream_t st, const RangeParts* range,
                      const SumDigits* digits)
 {
-    // whole rows per block where nothing is summed over tokens, up to the size where the panel form streams as fast
-    // (K = 4096 / 11008, us, panel form -> row form: 1 token 7.1 -> 3.1 / 7.9 -> 4.6, 256: 10.1 -> 3.8 / 13.8 -> 6.5,
-    // 2048: 13.0 -> 8.9 / 27.0 -> 18.1, 8192: 30.3 -> 26.7 / 68.2 -> 65.9, but 119 -> 128 at K = 22016); one row per block
+    // Whole rows per block where nothing is summed over tokens, up to the size where the panel form streams as fast (us, panel form -> row
+    // form: K = 4096: 1000 tokens 11.2 -> 6.4, 4096: 17.9 -> 14.1, 16384: 43.3 -> 40.2, but 32768: 74.0 -> 81.5; K = 11008: 2048 tokens 25.3 -> 17.9,
+    // 8192: 58.9 -> 57.2, but 16384: 104.5 -> 105.8; 8192 x 22016 106 -> 109; binary32 16000 x 4096 67.0 -> 64.1, 5000 x 11008 61.7 -> 57.1).  Narrow
+    // rows leave part of a block idle: 4097 x 1032 11.6 -> 9.5, but 8192 x 1032 13.2 -> 15.2.  One row per block
     // up to 256 tokens, two up to 1024 (1024 tokens, 1 / 2 / 4 rows: 6.8 / 5.5 / 6.0).  Rows of up to 512 columns, one chunk of the panel
-    // form, which then needs no merge, leave most of a block idle: up to 2048 tokens where a row's sum is asked for (K = 64 / 512, 2048 tokens 5.5 -> 4.8 / 7.3 -> 4.9,
+    // form, which then needs no merge: up to 2048 tokens where a row's sum is asked for (K = 64 / 512, 2048 tokens 5.5 -> 4.8 / 7.3 -> 4.9,
     // 2500 tokens 5.6 -> 7.0 / 7.3 -> 7.1, binary32 4096 tokens 5.3 -> 7.6 / 8.4 -> 9.9;
     // without the sums 2758 tokens K = 448 6.3 -> 4.8, 4051 tokens K = 120 5.9 -> 5.2).  Not where an output lies over what other
     // blocks still read: the panel form's merge writes the row sums in a launch of its own, and its blocks have 32 rows or more.
-    if (!range && !colsum_xq && xq && aligned16(inv_s) && T <= (rowsum_x && K <= kQaPanels * kPanel ? 2048 : 4096) &&
+    const int64_t rows_most = rowsum_x && K <= kQaPanels * kPanel ? 2048 : K < 2048 ? 4096 : T * K <= (6ll << 24) ? 16384 : 4096;
+    if (!range && !colsum_xq && xq && aligned16(inv_s) && T <= rows_most &&
         !overlap({{rowsum_x, T * 4}, {xq, T * panel_count(K) * kPanel}}, {matrix_span(X, T, K, ldx, dtype_size(dt)), {inv_s, K * 4}, {act_step, 4}, {act_zero, 4}})) {
 #define AWEQ_QR(F, R) quant_act_rows<F, R><<<(unsigned)cdiv(T, R), kQrBlock, 0, st>>>(X, T, K, ldx, inv_s, act_step, act_zero, xq, rowsum_x, status)
         if (dt == AWEQ_F16) { if (T <= 256) AWEQ_QR(true, 1); else if (T <= 1024) AWEQ_QR(true, 2); else AWEQ_QR(true, 4); }
