@@ -173,7 +173,7 @@ size_t calibrate_ws_bytes(int64_t T, int64_t K, int64_t N)
         const size_t b = (size_t)slices * (size_t)K * 16;
         if (b > most) most = b;
     }
-    const size_t qa = quant_act_ws_bytes(T, K);
+    const size_t qa = quant_act_ws_bytes(T, K, true);
     return kept_bytes(K) + (most > qa ? most : qa);
 }
 

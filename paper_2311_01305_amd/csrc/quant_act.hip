@@ -399,11 +399,36 @@ static QaPlan qa_plan(int64_t T, int64_t K)
     return p;
 }
 
+// The launch's slices: as many blocks as are resident at a time, since every block begins with the same round trips (for Step, Z, the scales) before
+// its rows stream; never more slices than qa_plan has, which sizes the workspace.  us, 8192 blocks -> about 1024: sums alone 14331 x 11008
+// 60.3 -> 54.4, 8000 x 11008 47.6 -> 35.1, 20000 x 4096 46.7 -> 32.6, 65536 x 4096 102 -> 89; codes and sums 16384 x 4096 50.6 -> 42.0, 4000 x 11008
+// 40.2 -> 36.4, but beyond 2^27 values 3072 (65536 x 4096: 161 with 8192, 141 with 3072, 149 with 1024); binary32 7419 x 4096 36.4 with 2048 or
+// more, 38.5 with 1024.  fine (a workspace of quant_act_ws_bytes(T, K, true)): calls of few blocks in slices of 16 or 8 rows (codes and sums 512 x 4096
+// 11.2 -> 9.8, 2000 x 1024 10.4 -> 9.8, but 600 x 11008, 418 blocks, 17.1 -> 18.3).
+static QaPlan launch_plan(int64_t T, int64_t K, bool f16, bool sums, bool fine)
+{
+    QaPlan p = qa_plan(T, K);
+    const int64_t blocks = f16 && (sums || T * K <= (1ll << 27)) ? 1024 : 3072;
+    int64_t rpb = cdiv(cdiv(T, cdiv(blocks, p.chunks)), kQaSliceRows) * kQaSliceRows;
+    if (rpb > kQaMaxRows) rpb = kQaMaxRows;
+    if (rpb > p.rpb) p.rpb = rpb;
+    if (fine && p.rpb == kQaSliceRows) {
+        const int64_t few = cdiv(T, kQaSliceRows) * p.chunks;
+        p.rpb = few <= 64 ? 8 : few <= 256 ? 16 : kQaSliceRows;
+    }
+    p.slices = cdiv(T, p.rpb);
+    return p;
+}
+
 // workspace: per-slice column sums [slices][K] int32, then (several column chunks only) per-chunk
 // row sums [chunks][T] int32
-size_t quant_act_ws_bytes(int64_t T, int64_t K)
+size_t quant_act_ws_bytes(int64_t T, int64_t K, bool fine)
 {
-    const QaPlan p = qa_plan(T, K);
+    QaPlan p = qa_plan(T, K);
+    if (fine) {
+        const int64_t slices = launch_plan(T, K, true, false, true).slices;   // (the small slices are the same for every form)
+        if (slices > p.slices) p.slices = slices;
+    }
     return (size_t)p.slices * (size_t)K * 4 + (p.chunks > 1 ? (size_t)p.chunks * (size_t)T * 4 : 0);
 }
 
@@ -413,8 +438,8 @@ int launch_quant_act(const void* X, aweq_dtype dt, int64_t T, int64_t K, int64_t
                      const SumDigits* digits)
 {
     // Whole rows per block where nothing is summed over tokens, up to the size where the panel form streams as fast (us, panel form -> row
-    // form: K = 4096: 1000 tokens 11.2 -> 6.4, 4096: 17.9 -> 14.1, 16384: 43.3 -> 40.2, but 32768: 74.0 -> 81.5; K = 11008: 2048 tokens 25.3 -> 17.9,
-    // 8192: 58.9 -> 57.2, but 16384: 104.5 -> 105.8; 8192 x 22016 106 -> 109; binary32 16000 x 4096 67.0 -> 64.1, 5000 x 11008 61.7 -> 57.1).  Narrow
+    // form: K = 4096: 1000 tokens 11.2 -> 6.4, 4096: 17.9 -> 14.1, 16384: 41.3 -> 40.1, but 32768: 74.0 -> 81.6; K = 11008: 2048 tokens 24.4 -> 17.8,
+    // 8192: 58.6 -> 57.9, but 16384: 100 -> 107; 8192 x 22016 106 -> 109; binary32 16000 x 4096 68.7 -> 64.5, 5000 x 11008 63.7 -> 56.8).  Narrow
     // rows leave part of a block idle: 4097 x 1032 11.6 -> 9.5, but 8192 x 1032 13.2 -> 15.2.  One row per block
     // up to 256 tokens, two up to 1024 (1024 tokens, 1 / 2 / 4 rows: 6.8 / 5.5 / 6.0).  Rows of up to 512 columns, one chunk of the panel
     // form, which then needs no merge: up to 2048 tokens where a row's sum is asked for (K = 64 / 512, 2048 tokens 5.5 -> 4.8 / 7.3 -> 4.9,
@@ -430,7 +455,8 @@ int launch_quant_act(const void* X, aweq_dtype dt, int64_t T, int64_t K, int64_t
 #undef AWEQ_QR
         return launch_status();
     }
-    const QaPlan p = qa_plan(T, K);
+    const bool sums = !xq && !rowsum_x;
+    const QaPlan p = launch_plan(T, K, dt == AWEQ_F16, sums, range != nullptr);
     if (p.slices * p.chunks > 0x7ffffff0ll) return AWEQ_ERR_SHAPE;
     const bool multi = p.chunks > 1;
     int32_t* const colsum_part = colsum_xq ? reinterpret_cast<int32_t*>(ws) : nullptr;
@@ -438,7 +464,6 @@ int launch_quant_act(const void* X, aweq_dtype dt, int64_t T, int64_t K, int64_t
     int32_t* const rs_out = !rowsum_x ? nullptr : (multi ? rowsum_part : rowsum_x);
     const unsigned pairs = (unsigned)(p.slices * p.chunks);
     const unsigned grid = (unsigned)(cdiv(pairs, kQaXcds) * kQaXcds);
-    const bool sums = !xq && !rowsum_x;
     const RangeParts parts = range ? *range : RangeParts{};
     // codes that fit the memory-side cache are stored through the caches, where the GEMM finds them; more would only evict each
     // other (int8 forward, us, non-temporal -> cached: 16384 tokens 4096 x 11008 (180 MB) 663 -> 650, 4096 x 16384 (268 MB)
