@@ -26,7 +26,7 @@ constexpr int kWaves = kThreads / kWave;
 // QX: 0: the tokens' codes are in memory (g.A).  1 / 2: every workgroup quantises the few binary16 / binary32 tokens (QuantIn) for
 // itself while its first weights are on their way, the first workgroup also for the caller: a second launch costs more
 // than the repeated work.
-template <int TT, int NT, int U, int QX>
+template <int TT, int NT, int D, int QX>
 __global__ __launch_bounds__(kThreads) void gemm_i8_few(GemmArgs g, QuantIn in)
 {
     extern __shared__ __attribute__((aligned(16))) int red[];   // [wave][TT NT][lane][4], then (QX) the tokens' codes, K padded to panels
@@ -54,22 +54,30 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_few(GemmArgs g, QuantIn in)
 #pragma unroll
         for (int j = 0; j < NT; ++j) acc[i][j] = v4i{0, 0, 0, 0};
 
-    // panels wave, wave + 8, ...: U of them on their way while U are multiplied
-    v4i w[U][NT], x[U][TT];
-    auto load = [&](int p0) {
+    // Panels wave, wave + 8, ... go through a ring of D slots, each refilled as soon as it has been multiplied; no load sits in a branch but
+    // the last ones.  The depths (at the launch) are the best measured of 1 - 8; more cost wavefronts, and the read of the weight is at the
+    // memory's rate between the launch's 2.7 us and its end (us, batches issued once the last one had arrived -> ring, weight in
+    // the caches: one token 4096 x 4096 5.15 -> 4.9, 16 tokens 4096 x 11008 15.1 -> 14.2, 8192 x 8192 17.7 -> 16.9, 32 tokens 4096 x 4096
+    // 9.0 -> 8.5, 4096 x 11008 16.8 -> 15.6, 64 tokens 8192 x 8192 19.1 -> 18.6; wide layers within 1 %).
+    const int cnt = max((np - wave + kWaves - 1) / kWaves, 0);
+    v4i w[D][NT], x[D][TT];
+    auto load = [&](int d, int i) {
+        const int p = wave + i * kWaves;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int p = p0 + u * kWaves;
-            if (p < np) {
+        for (int j = 0; j < NT; ++j) w[d][j] = *reinterpret_cast<const v4i*>(wbase + p * wp + wo[j]);
+        if constexpr (QX == 0) {
 #pragma unroll
-                for (int j = 0; j < NT; ++j) w[u][j] = *reinterpret_cast<const v4i*>(wbase + p * wp + wo[j]);
-#pragma unroll
-                for (int i = 0; i < TT; ++i)
-                    if constexpr (QX == 0) x[u][i] = *reinterpret_cast<const v4i*>(xbase + p * xp + xo[i]);
-            }
+            for (int t = 0; t < TT; ++t) x[d][t] = *reinterpret_cast<const v4i*>(xbase + p * xp + xo[t]);
         }
     };
-    load(wave);
+    if (cnt >= D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) load(d, d);
+    } else {
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+            if (d < cnt) load(d, d);
+    }
     int8_t* const codes = reinterpret_cast<int8_t*>(red + kWaves * TT * NT * kWave * 4);
     if constexpr (QX != 0) {
         const ActParams ap = quot_params(*g.act_step, *g.act_zero);
@@ -119,26 +127,32 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_few(GemmArgs g, QuantIn in)
         if (blockIdx.x == 0 && in.rowsum_x && (int)threadIdx.x < (int)g.T) in.rowsum_x[threadIdx.x] = s_rs[threadIdx.x];
     }
     const int8_t* const own = codes + min(r, (int)g.T - 1) * np * kPanel + q * 16;   // (QX: one row of 16 tokens)
-    for (int p0 = wave; p0 < np; p0 += U * kWaves) {
-        v4i cw[U][NT], cx[U][TT];
+    auto mul = [&](int d, int i) {
+        if constexpr (QX != 0) x[d][0] = *reinterpret_cast<const v4i*>(own + (wave + i * kWaves) * kPanel);
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
+        for (int j = 0; j < NT; ++j)
 #pragma unroll
-            for (int j = 0; j < NT; ++j) cw[u][j] = w[u][j];
+            for (int t = 0; t < TT; ++t) acc[t][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(w[d][j], x[d][t], acc[t][j], 0, 0, 0);
+    };
+    if (cnt >= D) {
+        int i = 0;
+        for (; i + 2 * D <= cnt; i += D) {
 #pragma unroll
-            for (int i = 0; i < TT; ++i)
-                if constexpr (QX == 0) cx[u][i] = x[u][i];
-                else cx[u][i] = *reinterpret_cast<const v4i*>(own + min(p0 + u * kWaves, np - 1) * kPanel);
+            for (int d = 0; d < D; ++d) { mul(d, i + d); load(d, i + D + d); }
         }
-        load(p0 + U * kWaves);
+        const int rest = cnt - i - D;   // panels not requested yet, fewer than D
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (p0 + u * kWaves < np) {
+        for (int d = 0; d < D; ++d) {
+            mul(d, i + d);
+            if (d < rest) load(d, i + D + d);
+        }
 #pragma unroll
-                for (int j = 0; j < NT; ++j)
+        for (int d = 0; d < D - 1; ++d)
+            if (d < rest) mul(d, i + D + d);
+    } else {
 #pragma unroll
-                    for (int i = 0; i < TT; ++i) acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(cw[u][j], cx[u][i], acc[i][j], 0, 0, 0);
-            }
+        for (int d = 0; d < D - 1; ++d)
+            if (d < cnt) mul(d, d);
     }
 
     // register v of lane l is output channel 4 (l / 16) + v of the 16, token l % 16
@@ -207,13 +221,13 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_few(GemmArgs g, QuantIn in)
 
 // Token tiles ride on the grid's y dimension, at most 65535 to a launch: layers of up to 64 channels come here at any number of tokens
 constexpr int kMaxGridY = 65535;
-template <int TT, int NT, int U, int QX = 0>
+template <int TT, int NT, int D, int QX = 0>
 static int launch_tile(GemmArgs g, hipStream_t st, QuantIn in = {})
 {
     constexpr int kSums = kWaves * TT * NT * kWave * 16;   // partial sums; a launch that quantises has the tokens' codes behind them
     static_assert(QX == 0 || kSums + kQuantFewBytes <= 32768, "a launch that quantises stays below the LDS limit that has to be raised");
     const int lds = kSums + (QX != 0 ? (int)(g.T * panel_count(g.K) * kPanel) : 0);
-    const void* fn = reinterpret_cast<const void*>(gemm_i8_few<TT, NT, U, QX>);
+    const void* fn = reinterpret_cast<const void*>(gemm_i8_few<TT, NT, D, QX>);
     int dev = 0, cus = 0;
     if (lds > 32768 && (device_cus(dev, cus) != AWEQ_OK || raise_lds_limit(fn, dev, lds) != AWEQ_OK)) return AWEQ_ERR_LAUNCH;
     void* args[] = {&g, &in};
@@ -246,18 +260,18 @@ FewPlan plan_few(int64_t T, int64_t N)
 
 int launch_gemm_i8_few_quant(const GemmArgs& g, const FewPlan& p, const QuantIn& in, bool f16, hipStream_t st)
 {
-    if (p.tile == 0) return f16 ? few::launch_tile<1, 1, 4, 1>(g, st, in) : few::launch_tile<1, 1, 4, 2>(g, st, in);
+    if (p.tile == 0) return f16 ? few::launch_tile<1, 1, 6, 1>(g, st, in) : few::launch_tile<1, 1, 6, 2>(g, st, in);
     return f16 ? few::launch_tile<1, 2, 4, 1>(g, st, in) : few::launch_tile<1, 2, 4, 2>(g, st, in);
 }
 
 int launch_gemm_i8_few(const GemmArgs& g, const FewPlan& p, hipStream_t st)
 {
     switch (p.tile) {
-    case 0: return few::launch_tile<1, 1, 4>(g, st);
-    case 1: return few::launch_tile<1, 2, 4>(g, st);
-    case 2: return few::launch_tile<2, 1, 4>(g, st);
+    case 0: return few::launch_tile<1, 1, 2>(g, st);
+    case 1: return few::launch_tile<1, 2, 3>(g, st);
+    case 2: return few::launch_tile<2, 1, 3>(g, st);
     case 3: return few::launch_tile<2, 2, 2>(g, st);
-    case 4: return few::launch_tile<2, 4, 2>(g, st);
+    case 4: return few::launch_tile<2, 4, 1>(g, st);
     default: return few::launch_tile<4, 4, 1>(g, st);
     }
 }
