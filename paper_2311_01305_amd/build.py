@@ -1,4 +1,4 @@
-"""Build libaweq.so (hand-written HIP for gfx950) in-tree with hipcc.
+"""Build libaweq.so (hand-written HIP for gfx950) in-tree with hipcc, and _native.so (its calls from Python) with g++.
 
 hipcc cross-compiles without a GPU.  Flags: no FMA contraction (the quantizer's fp32
 steps are single IEEE operations), no packed-fp32 instructions.
@@ -6,12 +6,14 @@ steps are single IEEE operations), no packed-fp32 instructions.
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libaweq.so")
+NATIVE = os.path.join(HERE, "_native.so")   # the Python side of the calls
 SOURCES = ["api.hip", "stats.hip", "equalize.hip", "quant_weight.hip", "quant_act.hip", "gemm_i8.hip", "gemm_i8_few.hip", "gemm_i8_mid.hip", "gemm_wonly.hip", "gemm_wonly_small.hip", "gemm_wonly_mid.hip", "bias.hip", "weight_pass.hip", "calibrate.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -23,9 +25,9 @@ def _deps():
 
 
 def is_stale() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(NATIVE):
         return True
-    t = os.path.getmtime(LIB)
+    t = min(os.path.getmtime(LIB), os.path.getmtime(NATIVE))
     return any(os.path.getmtime(p) > t for p in _deps())
 
 
@@ -57,6 +59,11 @@ def build(force: bool = True, verbose: bool = False) -> str:
     r = subprocess.run(link, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stderr}")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-I", INCLUDE, "-I", sysconfig.get_paths()["include"],
+           os.path.join(CSRC, "native.cpp"), "-o", NATIVE]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed on native.cpp:\n{r.stderr}")
     return LIB
 
 
