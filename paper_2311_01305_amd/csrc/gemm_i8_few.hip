@@ -78,6 +78,30 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_few(GemmArgs g, QuantIn in)
         for (int d = 0; d < D; ++d)
             if (d < cnt) load(d, d);
     }
+    // What the epilogue needs of a channel (a token) is requested here by one thread each and waits in LDS: at the end, one round trip after the
+    // other, it took 1 - 2 us
+    constexpr int kChannels = 16 * NT, kTokens = 16 * TT;
+    static_assert(kChannels + kTokens <= kThreads, "a thread each");
+    __shared__ double s_scale[kChannels], s_bias[kChannels];
+    __shared__ unsigned s_cn[kChannels], s_zw[kChannels], s_rx[kTokens];
+    float e_step = 0.0f, e_bias = 0.0f, e_sx = 0.0f;
+    int e_zw = 0, e_rw = 0, e_zx = 0;
+    const int e_tok = (int)threadIdx.x - kChannels;
+    auto request_constants = [&]() {
+        if (!g.out_deq) return;
+        e_zx = *g.act_zero;
+        e_sx = *g.act_step;
+        if ((int)threadIdx.x <= rows_left) {
+            const int64_t n = n0 + threadIdx.x, pi = g.w_per_tensor ? 0 : n;
+            e_step = g.step_w[pi];
+            e_zw = g.zero_w[pi];
+            e_rw = g.rowsum_w[n];
+            if (g.bias) e_bias = g.bias[n];
+        } else if (QX == 0 && e_tok >= 0 && e_tok <= tokens_left) {
+            e_rw = g.rowsum_x[t0 + e_tok];
+        }
+    };
+    if constexpr (QX == 0) request_constants();   // (otherwise behind the tokens that are quantised first)
     int8_t* const codes = reinterpret_cast<int8_t*>(red + kWaves * TT * NT * kWave * 4);
     if constexpr (QX != 0) {
         const ActParams ap = quot_params(*g.act_step, *g.act_zero);
@@ -125,6 +149,7 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_few(GemmArgs g, QuantIn in)
         if (blockIdx.x == 0) raise_status(g.status, st);
         __syncthreads();
         if (blockIdx.x == 0 && in.rowsum_x && (int)threadIdx.x < (int)g.T) in.rowsum_x[threadIdx.x] = s_rs[threadIdx.x];
+        request_constants();
     }
     const int8_t* const own = codes + min(r, (int)g.T - 1) * np * kPanel + q * 16;   // (QX: one row of 16 tokens)
     auto mul = [&](int d, int i) {
@@ -162,8 +187,22 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_few(GemmArgs g, QuantIn in)
 #pragma unroll
         for (int j = 0; j < NT; ++j) *reinterpret_cast<v4i*>(red + ((wave * kTiles + i * NT + j) * kWave + lane) * 4) = acc[i][j];
     __shared__ long long s_col[TT][16 * NT];
-    __syncthreads();
     uint32_t est = 0;
+    if (g.out_deq) {
+        // the tiled kernel's arithmetic: the integer part in wrap-around 32 bits, scaled and shifted in fp64
+        const int zx = e_zx - 128, zw = e_zw - 128;
+        if (zx < -128 || zx > 127) est |= AWEQ_ST_ZEROPOINT;
+        if ((int)threadIdx.x <= rows_left) {
+            if (zw < -128 || zw > 127) est |= AWEQ_ST_ZEROPOINT;
+            s_scale[threadIdx.x] = (double)e_sx * (double)e_step;
+            s_bias[threadIdx.x] = (double)e_bias;
+            s_cn[threadIdx.x] = (unsigned)g.K * (unsigned)zx * (unsigned)zw - (unsigned)zx * (unsigned)e_rw;
+            s_zw[threadIdx.x] = (unsigned)zw;
+        } else if (QX == 0 && e_tok >= 0 && e_tok < kTokens) {
+            s_rx[e_tok] = (unsigned)e_rw;
+        }
+    }
+    __syncthreads();
     for (int e = threadIdx.x; e < kTiles * kWave; e += kThreads) {
         const int tile = e / kWave, l = e & (kWave - 1);
         const int64_t t = t0 + 16 * (tile / NT) + (l & 15), n = n0 + 16 * (tile % NT) + 4 * (l >> 4);
@@ -173,21 +212,13 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_few(GemmArgs g, QuantIn in)
         for (int wv = 0; wv < kWaves; ++wv) o += *reinterpret_cast<const v4i*>(red + ((wv * kTiles + tile) * kWave + l) * 4);
         if (ok && g.out_i32) *reinterpret_cast<v4i*>(g.out_i32 + t * g.ldo + n) = o;
         if (ok && g.out_deq) {
-            // the tiled kernel's arithmetic: the integer part in wrap-around 32 bits, scaled and shifted in fp64
-            const int zx = *g.act_zero - 128;
-            const double sx = (double)*g.act_step;
-            if (zx < -128 || zx > 127) est |= AWEQ_ST_ZEROPOINT;
-            const unsigned rs = QX != 0 ? (unsigned)s_rs[t] : (unsigned)g.rowsum_x[t];
+            const int tl = 16 * (tile / NT) + (l & 15), nl = 16 * (tile % NT) + 4 * (l >> 4);
+            const unsigned rs = QX != 0 ? (unsigned)s_rs[t] : s_rx[tl];
             float y[4];
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                const int64_t pi = g.w_per_tensor ? 0 : n + c;
-                const int zw = g.zero_w[pi] - 128;
-                if (zw < -128 || zw > 127) est |= AWEQ_ST_ZEROPOINT;
-                const double scale = sx * (double)g.step_w[pi], bd = g.bias ? (double)g.bias[n + c] : 0.0;
-                const unsigned cn = (unsigned)g.K * (unsigned)zx * (unsigned)zw - (unsigned)zx * (unsigned)g.rowsum_w[n + c];
-                const double div = (double)(int)((unsigned)o[c] + cn - (unsigned)zw * rs);
-                y[c] = g.out_f16 ? (float)__builtin_fma(div, scale, bd) : (float)(div * scale + bd);
+                const double div = (double)(int)((unsigned)o[c] + s_cn[nl + c] - s_zw[nl + c] * rs);
+                y[c] = g.out_f16 ? (float)__builtin_fma(div, s_scale[nl + c], s_bias[nl + c]) : (float)(div * s_scale[nl + c] + s_bias[nl + c]);
             }
             if (g.out_f16) {
                 typedef _Float16 h4 __attribute__((ext_vector_type(4)));
