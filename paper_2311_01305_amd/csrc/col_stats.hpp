@@ -11,6 +11,11 @@ constexpr int kStatsBlock = 256;
 constexpr int kStatsWaves = kStatsBlock / kWave;
 constexpr int kRowBatch = 8;  // rows summed in fp32 before one fp64 add (binary16 input only)
 
+// Heights of slices that blocks walk down side by side: no multiple of 64 rows.  With rows of a power of two of bytes the slices would begin a
+// multiple of a large power of two apart and the blocks would be at the same memory channels all along (us, whole calibration, 512 -> 544 rows a
+// slice: 32768 x 4096 144 -> 127, 61440 x 4096 209 -> 197, 28672 x 16384 423 -> 412).
+inline int64_t spread_rows(int64_t rows) { return rows >= 64 && rows % 64 == 0 ? rows + 32 : rows; }
+
 struct StatsPlan {
     int col_chunks;   // blocks along K
     int slices;       // row slices
@@ -27,7 +32,7 @@ inline StatsPlan stats_plan(int64_t rows, int64_t K, int elts_per_lane)
     int64_t max_slices = cdiv(rows, kStatsWaves * kRowBatch);  // at least one row batch per wavefront
     if (want > max_slices) want = max_slices;
     if (want < 1) want = 1;
-    p.rows_per_slice = cdiv(cdiv(rows, want), kStatsWaves * kRowBatch) * (kStatsWaves * kRowBatch);
+    p.rows_per_slice = spread_rows(cdiv(cdiv(rows, want), kStatsWaves * kRowBatch) * (kStatsWaves * kRowBatch));
     p.slices = (int)cdiv(rows, p.rows_per_slice);
     return p;
 }
