@@ -27,6 +27,7 @@
 // compact patch of the output.
 #include "gemm_i8.hpp"
 #include "quant_act.hpp"
+#include "row_reduce.hpp"
 #include <type_traits>
 
 namespace aweq {
@@ -301,9 +302,12 @@ template <int MI, bool I32, int DEQ, bool COLSUM, int EPI = 0, bool STORE = true
 __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
 {
     using TL = Tile<MI>;
+    // (the statistics epilogue, and the quantising one that also stores 256-token tiles, have the general form only: no registers left)
+    constexpr bool kQuick = EPI == 0 || (EPI == 2 && !(STORE && MI == 4));
+    constexpr int kUnroll = kQuick ? 1 : 8;
     constexpr int kSlot = TL::kSlot, kHalfA = TL::kHalfA, kAhead = TL::kAhead, kLoads = TL::kLoads;
     extern __shared__ __attribute__((aligned(1024))) char lds[];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 2, wn = wave & 3;
     const int stride = gridDim.x;
 
@@ -315,17 +319,7 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
     const int nh = (int)panel_count(g.K);
     const int pre = nh < kAhead ? nh : kAhead;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
-    const uint32_t wave_offA = __builtin_amdgcn_readfirstlane(wave) * (512 * MI), wave_offB = kHalfA + __builtin_amdgcn_readfirstlane(wave) * 2048;
-
-    // fragment of K-step ks of a panel: lane reads row lane % 32 of a 32-row sub-tile, chunk
-    // 2 ks + lane / 32 (sub-tiles start at multiples of 32 rows, so f4(row) = f4(lane % 32))
-    const int fr_row = lane & 31, fr_half = lane >> 5;
-    int offA[2], offB[2];
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-        offA[ks] = (wm * (32 * MI) + fr_row) * kPanel + ((ks * 2 + fr_half) ^ f4(fr_row)) * 16;
-        offB[ks] = kHalfA + (wn * 64 + fr_row) * kPanel + ((ks * 2 + fr_half) ^ f4(fr_row)) * 16;
-    }
+    const uint32_t wave_offA = wave * (512 * MI), wave_offB = kHalfA + wave * 2048;
 
     // global -> LDS: wave w brings tile rows 32 w .. 32 w + 31 of the weight and 8 MI w .. of the activations, 16 rows
     // x 64 B per instruction; lane i sits at row i / 4, chunk slot i % 4 and fetches chunk slot ^ f4(row)
@@ -341,12 +335,15 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
         // (wave-uniform by construction; say so, the panel base addresses live in scalar registers)
         m0 = (int64_t)__builtin_amdgcn_readfirstlane(tm) * TL::kRows;
         n0 = (int64_t)__builtin_amdgcn_readfirstlane(tn) * BN;
+        // rows past the edge re-read the last valid row; their results are never stored
+        int lane_ = lane;
+        asm volatile("" : "+v"(lane_));   // (hidden: formed again for every tile instead of living through the multiplications)
+        const int last_m = (int)min((int64_t)TL::kRows, g.T - m0) - 1, last_n = (int)min((int64_t)BN, g.N - n0) - 1;
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-            const int sub = q * 16 + (lane >> 2), chunk = (lane & 3) ^ f4(sub);   // (wavefronts start at multiples of 16 rows)
-            // rows past the edge re-read the last valid row; their results are never stored
-            if (q < MI / 2) oa[q] = (uint32_t)((min(m0 + wave * (8 * MI) + sub, g.T - 1) - m0) * kPanel + chunk * 16);
-            ob[q] = (uint32_t)((min(n0 + wave * 32 + sub, g.N - 1) - n0) * kPanel + chunk * 16);
+            const int sub = q * 16 + (lane_ >> 2), chunk = (lane_ & 3) ^ f4(sub);   // (wavefronts start at multiples of 16 rows)
+            if (q < MI / 2) oa[q] = (uint32_t)(min(wave * (8 * MI) + sub, last_m) * (int)kPanel + chunk * 16);
+            ob[q] = (uint32_t)(min(wave * 32 + sub, last_n) * (int)kPanel + chunk * 16);
         }
         srcA = g.A + m0 * kPanel;
         srcB = g.B + n0 * kPanel;
@@ -382,6 +379,18 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
             for (int j = 0; j < 2; ++j)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[i][j][v] = 0;
+        // fragment of K-step ks of a panel: lane reads row lane % 32 of a 32-row sub-tile, chunk
+        // 2 ks + lane / 32 (sub-tiles start at multiples of 32 rows, so f4(row) = f4(lane % 32))
+        // (formed again for every tile instead of living through the epilogue)
+        int fl_ = lane;
+        asm volatile("" : "+v"(fl_));
+        const int fr_row = fl_ & 31, fr_half = fl_ >> 5;
+        int offA[2], offB[2];
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            offA[ks] = (wm * (32 * MI) + fr_row) * kPanel + ((ks * 2 + fr_half) ^ f4(fr_row)) * 16;
+            offB[ks] = kHalfA + (wn * 64 + fr_row) * kPanel + ((ks * 2 + fr_half) ^ f4(fr_row)) * 16;
+        }
         v4i a0[MI], b0[2], a1[MI], b1[2];
 
 #define RDA(dst, ks, i) dst[i] = *reinterpret_cast<const v4i*>(st + offA[ks] + (i) * 32 * kPanel)
@@ -491,7 +500,10 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
         // lane then holds 16 bytes of one output row and 16 lanes cover 256 contiguous bytes per store.
         // The slabs live in the last ring slot and behind the ring; the next tile's first kAhead
         // panels are already on their way into the other slots.
-        const int rd_r = lane >> 4, rd_c = lane & 15;
+        // (hidden: what follows from the lane is formed here again for every tile instead of living through the multiplications)
+        int lane_ = lane;
+        asm volatile("" : "+v"(lane_));
+        const int rd_r = lane_ >> 4, rd_c = lane_ & 15;
         const int64_t t_lane = cm0 + wm * (32 * MI) + rd_r;              // + 32 i + 4 p
         const int64_t n = cn0 + wn * 64 + rd_c * 4;                // this lane's four channels
         const bool n_ok = n < g.N;                                 // N % 4 == 0: all four or none
@@ -500,7 +512,7 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
         // so that waiting for it does not wait for them
         int rsx[MI / 2] = {};   // row sums of this wave's 32 MI tokens, one per lane and 64: token 64 h + lane
         Float4 sw = {{0.f, 0.f, 0.f, 0.f}}, bs = {{0.f, 0.f, 0.f, 0.f}};
-        int zwv[4] = {0, 0, 0, 0};          // Z'w = Z_w - 128 of this lane's channels
+        int nzw[4] = {0, 0, 0, 0};          // -Z'w = 128 - Z_w of this lane's channels
         unsigned cn[4] = {0, 0, 0, 0};      // K Z'x Z'w - Z'x rowsum_w, in wrap-around 32-bit arithmetic
         uint32_t est = 0;                   // status bits this lane raises for the tile
         int zx = 0;
@@ -532,9 +544,9 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
                 const v4i rw4 = *reinterpret_cast<const v4i*>(g.rowsum_w + n);
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
-                    zwv[c] = zw4[c] - 128;
+                    nzw[c] = 128 - zw4[c];
                     if (zw4[c] < 0 || zw4[c] > 255) est |= AWEQ_ST_ZEROPOINT;
-                    cn[c] = (unsigned)g.K * (unsigned)zx * (unsigned)zwv[c] - (unsigned)zx * (unsigned)rw4[c];
+                    cn[c] = 0u - (unsigned)g.K * (unsigned)zx * (unsigned)nzw[c] - (unsigned)zx * (unsigned)rw4[c];
                 }
                 if (g.bias) bs = *reinterpret_cast<const Float4*>(g.bias + n);
             }
@@ -546,10 +558,13 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
             for (int c = 0; c < 4; ++c) {
                 asm volatile("" : "+v"(sw.f[c]));
                 asm volatile("" : "+v"(bs.f[c]));
-                asm volatile("" : "+v"(zwv[c]));
+                asm volatile("" : "+v"(nzw[c]));
                 asm volatile("" : "+v"(cn[c]));
             }
         }
+        // Which form this tile's rows take (wave-uniform): kPlain, every row and channel inside; kEdge, rows or channels past the edge;
+        // kGeneral, constants outside what the short arithmetic of the other two covers.
+        bool odd = false;   // this lane's channels have such constants
         Float4 nis = {{1.f, 1.f, 1.f, 1.f}};   // the next layer's 1 / s for this lane's four channels
         float nstep = 1.0f, nrstep = 1.0f, nthr = 0.0f;
         int nzero = 0;
@@ -565,7 +580,10 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
             for (int c = 0; c < 4; ++c) {
                 asm volatile("" : "+v"(nis.f[c]));
                 nscreen = nscreen && 65600.0f * fabsf(nis.f[c]) * nrstep < 16777216.0f;
+                // (finite constants and 1 / s > 0: no quotient is a NaN, which the distance-to-tie test would not see)
+                odd = odd || !(nis.f[c] > 0.0f && nis.f[c] < INFINITY) || !(fabsf(sxf * sw.f[c]) < INFINITY) || !(fabsf(bs.f[c]) < INFINITY);
             }
+            odd = odd || !np_.screen;
             nstep = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(nstep)));
             nrstep = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(nrstep)));
             nthr = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(nthr)));
@@ -580,6 +598,17 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
         __builtin_amdgcn_s_barrier();  // every wave is done reading the ring
         if (more) start_tile(ntm, ntn);
 
+        enum { kPlain, kEdge, kGeneral };
+        int form = kGeneral;
+        if constexpr (kQuick) {
+            if constexpr (DEQ != 0) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) odd = odd || nzw[c] >= (1 << 23) || nzw[c] <= -(1 << 23);
+            }
+            const bool inside = cm0 + TL::kRows <= g.T && cn0 + BN <= g.N;
+            if (__builtin_amdgcn_ballot_w64(odd && n_ok) == 0 && g.ldo < (1 << 28) && (!COLSUM || g.K < 32768)) form = inside ? kPlain : kEdge;
+        }
+
         // per-channel constants of the de-quantisation
         double scale[4] = {0, 0, 0, 0}, bsd[4] = {0, 0, 0, 0};
         if constexpr (DEQ != 0) {
@@ -590,8 +619,6 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
             }
         }
         char* slab = lds + TL::kSlabs + wave * 8192;
-        const int wr_t = lane & 31;
-        const int wr_sw = wr_t & 15, wr_half = lane >> 5;           // chunk (8 j + 2 q + l / 32) ^ (t & 15)
         // The sums over tokens leave a wavefront as one atomic instruction of 64 neighbouring channels (lane 16 r + c: channel 4 c + r):
         // the memory side takes them by the line, and four instructions of every fourth channel cost more (binary16 output with
         // sums, 25003 tokens 768 x 768: 54.1 -> 38.9 us).
@@ -604,9 +631,176 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
         int rsy_kept[MI / 2] = {};               // row sums of the next layer's codes: one per lane and 64 tokens
         float cqf[4] = {0.f, 0.f, 0.f, 0.f};     // column sums of the next layer's unsigned codes over this tile (exact: 32 rows)
         const bool yq_pad = (EPI & 2) != 0 && !n_ok && cn0 + wn * 64 < g.N;   // zero fill of the last panel
-        int8_t* const yq_lane = (EPI & 2) != 0 ? g.yq + (((cn0 >> 6) + wn) * g.T) * kPanel + rd_c * 4 : nullptr;
+        // kPlain / kEdge: wave-uniform row pointers that move on by four tokens, the lane's offset from them, its tokens inside
+        const int64_t wave_t = cm0 + wm * (32 * MI), wave_n = cn0 + wn * 64;
+        char* row_i32 = I32 ? reinterpret_cast<char*>(g.out_i32 + wave_t * g.ldo + wave_n) : nullptr;
+        char* row_deq = DEQ != 0 && STORE ? reinterpret_cast<char*>(g.out_deq) + (wave_t * g.ldo + wave_n) * (DEQ == 1 ? 4 : 2) : nullptr;
+        char* row_yq = (EPI & 2) != 0 ? reinterpret_cast<char*>(g.yq) + ((wave_n >> 6) * g.T + wave_t) * kPanel : nullptr;
+        const uint32_t lane_yq = (uint32_t)(rd_r * (int)kPanel + rd_c * 4);
+        const uint32_t lane_elt = (uint32_t)rd_r * (uint32_t)g.ldo + (uint32_t)rd_c * 4;
+        const int rows_t = (int)max((int64_t)0, min((int64_t)(32 * MI), g.T - t_lane)), lim = n_ok ? rows_t : 0;
+        const _Float16 relu = g.act == 1 ? (_Float16)0.0f : (_Float16)__builtin_nanf("");   // max(y, NaN) = y
+        const bool big_quot = __builtin_amdgcn_ballot_w64(!nscreen) != 0;
+        const float qlim = nscreen ? INFINITY : 8388608.0f;          // (quotients up to 2^23: far outside the clamp, not yet flagged)
+        int rsy_pairs = 0;       // code sums of two tokens (16 bits each): lane 16 r + u has the passes 2 u and 2 u + 1
+        uint32_t cq02 = 0, cq13 = 0;   // column sums of the unsigned codes, two channels (16 bits each: 32 rows)
+        int cpart[4] = {0, 0, 0, 0};
+        // fp64 product and sum of the exact integer, as in the general form; |Z'w| and |row sum| < 2^23: a 24-bit multiply-add
+        auto dequantise = [&](const v4i& o, int rs, float y[4]) {
 #pragma unroll
-        for (int i = 0; i < MI; ++i) {
+            for (int c = 0; c < 4; ++c) {
+                const double div = (double)(int)((unsigned)o[c] + cn[c] + (unsigned)__mul24(nzw[c], rs));
+                if constexpr (DEQ == 1) y[c] = (float)(div * scale[c] + bsd[c]);
+                else y[c] = (float)__builtin_fma(div, scale[c], bsd[c]);
+            }
+        };
+        typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+        typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+        auto rounded = [&](const float y[4], h2 oh[2]) {
+            oh[0] = h2{(_Float16)y[0], (_Float16)y[1]};
+            oh[1] = h2{(_Float16)y[2], (_Float16)y[3]};
+            if constexpr ((EPI & 2) != 0) {
+                const h2 lowest = {relu, relu};
+                oh[0] = __builtin_elementwise_max(oh[0], lowest);
+                oh[1] = __builtin_elementwise_max(oh[1], lowest);
+            }
+        };
+        // the next layer's codes of four outputs by the one-FMA quotient, as unsigned bytes (the conversion clamps); tie: one of them is too
+        // close to a tie for that
+        auto next_codes = [&](const h2 oh[2], bool& tie) {
+            const float zf = (float)nzero;
+            float dmax = 0.0f, q[4];
+            uint32_t w = 0;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                q[c] = __builtin_fmaf(__builtin_fmaf((float)oh[c >> 1][c & 1], nis.f[c], 0.0f), nrstep, zf);
+                const float n_ = rintf(q[c]);
+                dmax = fmaxf(dmax, fabsf(q[c] - n_));
+                w = __builtin_amdgcn_cvt_pk_u8_f32(n_, c, w);
+            }
+            if (big_quot) dmax = fmaxf(fmaxf(fabsf(q[0]), fabsf(q[1])), fmaxf(fabsf(q[2]), fabsf(q[3]))) > qlim ? 1.0f : dmax;
+            tie = dmax > nthr;
+            return w;
+        };
+        auto row_sum_of = [&](int i, int p) { return __builtin_amdgcn_ds_bpermute(((i & 1) * 32 + 4 * p) * 4 + rd_r * 4, rsx[i >> 1]); };
+        auto slab_row = [&](int p) { return *reinterpret_cast<const v4i*>(slab + (4 * p + rd_r) * 256 + ((rd_c ^ (4 * (p & 3) + rd_r)) * 16)); };
+        // The eight passes over sub-tile row i of the plain and the edge form.  A tile's epilogue is vector operations of 4.5 cycles each
+        // with nothing multiplying meanwhile (the two wavefronts of a SIMD arrive together): 6 per output of a binary16 result, 14 with the
+        // next layer's codes and the sums, where the general form takes 12 and 20 and waits for the LDS in every pass.  Shorter by: the
+        // 24-bit multiply without its check, addresses that are a scalar and one offset, sums in 32 bits and in packed bytes, row sums two
+        // tokens to a word, divisions for near ties afterwards.  (us, general form -> these: two layers 4096 -> 16384 -> 4096 of 4096
+        // tokens 466 -> 449, three layers 4096 x 4096 of 8192 tokens inside their calibration 437 -> 418, the 128-token tiles of
+        // 2048 tokens 4096 x 11008 89.3 -> 88.3, 262144 tokens 8192 x 8192 with both outputs and sums 14.55 -> 14.49 ms.)
+        auto short_rows = [&](int i, auto edge_c) {
+            constexpr bool EDGE = decltype(edge_c)::value;
+            uint32_t redo = 0;
+            int rsy_even = 0;
+            // a pass's accumulators and row sum are requested one pass ahead (where there are registers for it)
+            constexpr bool kNext = MI == 2 || !(I32 && DEQ == 1 && COLSUM);
+            v4i next_o = {};
+            int next_rs = 0;
+            if constexpr (kNext) {
+                next_o = slab_row(0);
+                if constexpr (DEQ != 0) next_rs = row_sum_of(i, 0);
+            }
+#pragma unroll 1
+            for (int p4 = 0; p4 < 8; p4 += 4)
+#pragma unroll
+            for (int p_ = 0; p_ < 4; ++p_) {
+                const int p = p4 + p_;
+                const int pn = !kNext ? p : p_ < 3 ? p + 1 : (p4 + 4) & 7;   // (after the last one: the first again, not used)
+                v4i o = next_o;
+                int rs = next_rs;
+                next_o = *reinterpret_cast<const v4i*>(slab + pn * 1024 + (rd_r * 256 + ((rd_c ^ (4 * ((kNext ? p_ + 1 : p_) & 3) + rd_r)) * 16)));
+                if constexpr (DEQ != 0) next_rs = row_sum_of(i, pn);
+                if constexpr (!kNext) { o = next_o; rs = next_rs; }
+                SB();
+                const bool in = !EDGE || i * 32 + 4 * p < lim;
+                if constexpr (I32) {
+                    if (in) __builtin_nontemporal_store(o, reinterpret_cast<v4i*>(row_i32 + (uint64_t)(lane_elt * 4u)));
+                    row_i32 += 16 * g.ldo;
+                }
+                if constexpr (DEQ != 0) {
+                    float y[4];
+                    dequantise(o, rs, y);
+                    if constexpr (DEQ == 1) {
+                        typedef float f4 __attribute__((ext_vector_type(4)));
+                        if (in) __builtin_nontemporal_store(f4{y[0], y[1], y[2], y[3]}, reinterpret_cast<f4*>(row_deq + (uint64_t)(lane_elt * 4u)));
+                        row_deq += 16 * g.ldo;
+                    } else {
+                        h2 oh[2];
+                        rounded(y, oh);
+                        if constexpr (STORE) {
+                            if (in) __builtin_nontemporal_store(h4{oh[0][0], oh[0][1], oh[1][0], oh[1][1]}, reinterpret_cast<h4*>(row_deq + (uint64_t)(lane_elt * 2u)));
+                            row_deq += 8 * g.ldo;
+                        }
+                        if constexpr ((EPI & 2) != 0) {
+                            bool tie;
+                            uint32_t w = next_codes(oh, tie);
+                            if constexpr (EDGE) { w = in ? w : 0u; tie = tie & in; }
+                            redo |= __builtin_amdgcn_ballot_w64(tie) != 0 ? 1u << p : 0u;
+                            cq02 += w & 0x00ff00ffu;
+                            cq13 += (w >> 8) & 0x00ff00ffu;
+                            w ^= 0x80808080u;   // u - 128 as a byte
+                            if constexpr (EDGE) {
+                                w = in ? w : 0u;
+                                if (i * 32 + 4 * p < rows_t && (n_ok || yq_pad)) *reinterpret_cast<uint32_t*>(row_yq + (uint64_t)lane_yq) = w;
+                            } else {
+                                *reinterpret_cast<uint32_t*>(row_yq + (uint64_t)lane_yq) = w;
+                            }
+                            row_yq += 4 * kPanel;
+                            // the 16 lanes of one output row, two passes at a time: 64 codes sum to 14 bits
+                            const int d = __builtin_amdgcn_sdot4((int)w, 0x01010101, 0, false);
+                            if ((p_ & 1) == 0) rsy_even = d;
+                            else {
+                                int both = (int)(((unsigned)d << 16) + (unsigned)rsy_even);
+                                both += dpp_from<kXor1>(both);
+                                both += dpp_from<kXor2>(both);
+                                both += dpp_from<kRor4>(both);
+                                both += dpp_from<kRor8>(both);
+                                rsy_pairs = i * 4 + p / 2 == rd_c ? both : rsy_pairs;
+                            }
+                        }
+                    }
+                }
+                if constexpr (COLSUM) {   // (eight accumulators fit 32 bits while K < 16384, four while K < 32768)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        cpart[c] += in ? o[c] : 0;
+                        if (p_ == 3 && (p4 == 4 || g.K >= 16384)) { csum[c] += cpart[c]; cpart[c] = 0; }
+                        else asm volatile("" : "+v"(cpart[c]));   // (summed here, not out of 32 kept values later)
+                    }
+                }
+                SB();
+            }
+            if constexpr ((EPI & 2) != 0) {
+                while (redo != 0) {   // (a wavefront's pass has such a code about once in 30)
+                    const int p = __builtin_ctz(redo);
+                    redo &= redo - 1;
+                    const v4i o = slab_row(p);
+                    float y[4];
+                    h2 oh[2];
+                    dequantise(o, row_sum_of(i, p), y);
+                    rounded(y, oh);
+                    bool tie;
+                    const uint32_t w = next_codes(oh, tie);
+                    if (tie && i * 32 + 4 * p < lim) {
+                        uint32_t e = 0;
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) e |= (uint32_t)quant_div((float)oh[c >> 1][c & 1] * nis.f[c], nstep, nzero, 255, est) << (8 * c);
+                        cq02 += (e & 0x00ff00ffu) - (w & 0x00ff00ffu);
+                        cq13 += ((e >> 8) & 0x00ff00ffu) - ((w >> 8) & 0x00ff00ffu);
+                        *reinterpret_cast<uint32_t*>(row_yq - (8 - p) * (4 * kPanel) + (uint64_t)lane_yq) = e ^ 0x80808080u;
+                        const int d = (int)__builtin_amdgcn_udot4(e, 0x01010101u, 0, false) - (int)__builtin_amdgcn_udot4(w, 0x01010101u, 0, false);
+                        if (d != 0 && g.rowsum_y) atomicAdd(&g.rowsum_y[wave_t + i * 32 + 4 * p + rd_r], d);
+                    }
+                }
+            }
+        };
+        auto turn = [&](int i) {
+            int l_ = lane_;
+            asm volatile("" : "+v"(l_));   // (eight addresses formed again for each sub-tile row rather than kept)
+            const int wr_t = l_ & 31, wr_sw = wr_t & 15, wr_half = l_ >> 5;   // chunk (8 j + 2 q + l / 32) ^ (t & 15)
 #pragma unroll
             for (int j = 0; j < 2; ++j)
 #pragma unroll
@@ -614,99 +808,110 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
                     v4i o = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
                     *reinterpret_cast<v4i*>(slab + wr_t * 256 + (((8 * j + 2 * q + wr_half) ^ wr_sw) * 16)) = o;
                 }
+        };
+        if (kQuick && form == kPlain) {
 #pragma unroll
-            for (int p = 0; p < 8; ++p) {
-                const int r = 4 * p + rd_r;
-                const v4i o = *reinterpret_cast<const v4i*>(slab + r * 256 + ((rd_c ^ (r & 15)) * 16));
-                const int64_t t = t_lane + i * 32 + 4 * p;
-                unsigned rs = 0;
-                int rsy = 0;   // this lane's share of the token's code sum for the next layer
-                // row sum of token 32 i + 4 p + lane / 16 of the wave: held by lane (that % 64), half
-                // i / 2 (fetched with every lane active: a switched-off source lane would read as 0)
-                if constexpr (DEQ != 0) rs = (unsigned)__builtin_amdgcn_ds_bpermute((((i & 1) * 32 + 4 * p + rd_r) & 63) * 4, rsx[i >> 1]);
-                if (t < g.T && n_ok) {
-                    if constexpr (I32) __builtin_nontemporal_store(o, reinterpret_cast<v4i*>(g.out_i32 + t * g.ldo + n));
-                    if constexpr (DEQ != 0) {
-                        float y[4];
+            for (int i = 0; i < MI; ++i) { turn(i); short_rows(i, std::false_type{}); }
+        } else if (kQuick && form == kEdge) {
 #pragma unroll
-                        for (int c = 0; c < 4; ++c) {
-                            // |row sum| <= 128 K < 2^23 and |Z'w| < 2^23 for any zero point binary16 weights can
-                            // produce: a 24-bit multiply (full rate); wider zero points take the 32-bit one
-                            const int zr = (zwv[c] < (1 << 23) && zwv[c] > -(1 << 23)) ? __mul24(zwv[c], (int)rs) : zwv[c] * (int)rs;
-                            const int iv = (int)((unsigned)o[c] + cn[c] - (unsigned)zr);
-                            const double div = (double)iv;
-                            // the binary32 output is the fp64 product and sum rounded once (two fp64 operations,
-                            // like the definition); for binary16 one fused fp64 operation is far inside the rounding
-                            // (the variant with both fused epilogues is out of registers: it widens the bias here)
-                            const double bd = EPI == 3 ? (double)bs.f[c] : bsd[c];
-                            if constexpr (DEQ == 1) y[c] = (float)(div * scale[c] + bd);
-                            else y[c] = (float)__builtin_fma(div, scale[c], bd);
+            for (int i = 0; i < MI; ++i) { turn(i); short_rows(i, std::true_type{}); }
+        } else {
+            int8_t* const yq_lane = (EPI & 2) != 0 ? g.yq + (((cn0 >> 6) + wn) * g.T) * kPanel + rd_c * 4 : nullptr;
+#pragma unroll
+            for (int i = 0; i < MI; ++i) {
+                turn(i);
+#pragma unroll kUnroll
+                for (int p = 0; p < 8; ++p) {
+                    const v4i o = slab_row(p);
+                    const int64_t t = t_lane + i * 32 + 4 * p;
+                    unsigned rs = 0;
+                    int rsy = 0;   // this lane's share of the token's code sum for the next layer
+                    // row sum of token 32 i + 4 p + lane / 16 of the wave: held by lane (that % 64), half
+                    // i / 2 (fetched with every lane active: a switched-off source lane would read as 0)
+                    if constexpr (DEQ != 0) rs = (unsigned)row_sum_of(i, p);
+                    if (t < g.T && n_ok) {
+                        if constexpr (I32) __builtin_nontemporal_store(o, reinterpret_cast<v4i*>(g.out_i32 + t * g.ldo + n));
+                        if constexpr (DEQ != 0) {
+                            float y[4];
+#pragma unroll
+                            for (int c = 0; c < 4; ++c) {
+                                // |row sum| <= 128 K < 2^23 and |Z'w| < 2^23 for any zero point binary16 weights can
+                                // produce: a 24-bit multiply (full rate); wider zero points take the 32-bit one
+                                const unsigned zr = (nzw[c] < (1 << 23) && nzw[c] > -(1 << 23)) ? (unsigned)__mul24(nzw[c], (int)rs) : (unsigned)nzw[c] * rs;
+                                const int iv = (int)((unsigned)o[c] + cn[c] + zr);
+                                const double div = (double)iv;
+                                // the binary32 output is the fp64 product and sum rounded once (two fp64 operations,
+                                // like the definition); for binary16 one fused fp64 operation is far inside the rounding
+                                // (the variant with both fused epilogues is out of registers: it widens the bias here)
+                                const double bd = EPI == 3 ? (double)bs.f[c] : bsd[c];
+                                if constexpr (DEQ == 1) y[c] = (float)(div * scale[c] + bd);
+                                else y[c] = (float)__builtin_fma(div, scale[c], bd);
+                            }
+                            if constexpr ((EPI & 2) != 0) ++rows_in;
+                            if constexpr (DEQ == 2) {
+                                if constexpr (EPI != 0) {
+                                    if (g.act == 1) {
+#pragma unroll
+                                        for (int c = 0; c < 4; ++c) y[c] = fmaxf(y[c], 0.0f);
+                                    }
+                                }
+                                h4 oh = {(_Float16)y[0], (_Float16)y[1], (_Float16)y[2], (_Float16)y[3]};
+                                if constexpr (STORE)
+                                    __builtin_nontemporal_store(oh, reinterpret_cast<h4*>(reinterpret_cast<_Float16*>(g.out_deq) + t * g.ldo + n));
+                                if constexpr ((EPI & 1) != 0) {
+#pragma unroll
+                                    for (int c = 0; c < 4; ++c) {
+                                        const float yf = (float)oh[c];
+                                        ymn[c] = fminf(ymn[c], yf);
+                                        ymx[c] = fmaxf(ymx[c], yf);
+                                        ysum[c] += (double)yf;
+                                    }
+                                }
+                                if constexpr ((EPI & 2) != 0) {
+                                    uint32_t w = 0;
+                                    const float zf = (float)nzero;
+                                    float cn_[4];
+                                    float dmax = 0.0f;
+#pragma unroll
+                                    for (int c = 0; c < 4; ++c) {
+                                        const float a = __builtin_fmaf((float)oh[c], nis.f[c], 0.0f);
+                                        const float q = __builtin_fmaf(a, nrstep, zf);
+                                        cn_[c] = rintf(q);
+                                        dmax = fmaxf(dmax, fabsf(q - cn_[c]));
+                                    }
+                                    if (!nscreen || dmax > nthr) {
+#pragma unroll
+                                        for (int c = 0; c < 4; ++c)
+                                            cn_[c] = (float)quant_div((float)oh[c] * nis.f[c], nstep, nzero, 255, est);
+                                    }
+#pragma unroll
+                                    for (int c = 0; c < 4; ++c) {
+                                        const float u = __builtin_amdgcn_fmed3f(cn_[c], 0.0f, 255.0f);
+                                        cqf[c] += u;
+                                        w = __builtin_amdgcn_cvt_pk_u8_f32(u, c, w);
+                                    }
+                                    w ^= 0x80808080u;   // u - 128 as a byte
+                                    rsy = __builtin_amdgcn_sdot4((int)w, 0x01010101, 0, false);
+                                    *reinterpret_cast<uint32_t*>(yq_lane + t * kPanel) = w;
+                                }
+                            } else {
+                                typedef float f4 __attribute__((ext_vector_type(4)));
+                                f4 of = {y[0], y[1], y[2], y[3]};
+                                __builtin_nontemporal_store(of, reinterpret_cast<f4*>(reinterpret_cast<float*>(g.out_deq) + t * g.ldo + n));
+                            }
                         }
-                        if constexpr ((EPI & 2) != 0) ++rows_in;
-                        if constexpr (DEQ == 2) {
-                            typedef _Float16 h4 __attribute__((ext_vector_type(4)));
-                            if constexpr (EPI != 0) {
-                                if (g.act == 1) {
+                        if constexpr (COLSUM) {
 #pragma unroll
-                                    for (int c = 0; c < 4; ++c) y[c] = fmaxf(y[c], 0.0f);
-                                }
-                            }
-                            h4 oh = {(_Float16)y[0], (_Float16)y[1], (_Float16)y[2], (_Float16)y[3]};
-                            if constexpr (STORE)
-                                __builtin_nontemporal_store(oh, reinterpret_cast<h4*>(reinterpret_cast<_Float16*>(g.out_deq) + t * g.ldo + n));
-                            if constexpr ((EPI & 1) != 0) {
-#pragma unroll
-                                for (int c = 0; c < 4; ++c) {
-                                    const float yf = (float)oh[c];
-                                    ymn[c] = fminf(ymn[c], yf);
-                                    ymx[c] = fmaxf(ymx[c], yf);
-                                    ysum[c] += (double)yf;
-                                }
-                            }
-                            if constexpr ((EPI & 2) != 0) {
-                                uint32_t w = 0;
-                                const float zf = (float)nzero;
-                                float cn_[4];
-                                float dmax = 0.0f;
-#pragma unroll
-                                for (int c = 0; c < 4; ++c) {
-                                    const float a = __builtin_fmaf((float)oh[c], nis.f[c], 0.0f);
-                                    const float q = __builtin_fmaf(a, nrstep, zf);
-                                    cn_[c] = rintf(q);
-                                    dmax = fmaxf(dmax, fabsf(q - cn_[c]));
-                                }
-                                if (!nscreen || dmax > nthr) {
-#pragma unroll
-                                    for (int c = 0; c < 4; ++c)
-                                        cn_[c] = (float)quant_div((float)oh[c] * nis.f[c], nstep, nzero, 255, est);
-                                }
-#pragma unroll
-                                for (int c = 0; c < 4; ++c) {
-                                    const float u = __builtin_amdgcn_fmed3f(cn_[c], 0.0f, 255.0f);
-                                    cqf[c] += u;
-                                    w = __builtin_amdgcn_cvt_pk_u8_f32(u, c, w);
-                                }
-                                w ^= 0x80808080u;   // u - 128 as a byte
-                                rsy = __builtin_amdgcn_sdot4((int)w, 0x01010101, 0, false);
-                                *reinterpret_cast<uint32_t*>(yq_lane + t * kPanel) = w;
-                            }
-                        } else {
-                            typedef float f4 __attribute__((ext_vector_type(4)));
-                            f4 of = {y[0], y[1], y[2], y[3]};
-                            __builtin_nontemporal_store(of, reinterpret_cast<f4*>(reinterpret_cast<float*>(g.out_deq) + t * g.ldo + n));
+                            for (int c = 0; c < 4; ++c) csum[c] += o[c];
                         }
+                    } else if (yq_pad && t < g.T) {
+                        *reinterpret_cast<uint32_t*>(yq_lane + t * kPanel) = 0u;
                     }
-                    if constexpr (COLSUM) {
-#pragma unroll
-                        for (int c = 0; c < 4; ++c) csum[c] += o[c];
+                    if constexpr ((EPI & 2) != 0) {
+                        // the 16 lanes of one output row (every lane active here); lane 16 r + c keeps the sums of passes c and c + 16
+                        rsy = group_allreduce<4>(rsy, OpAdd());
+                        rsy_kept[i >> 1] = (i & 1) * 8 + p == rd_c ? rsy : rsy_kept[i >> 1];
                     }
-                } else if (yq_pad && t < g.T) {
-                    *reinterpret_cast<uint32_t*>(yq_lane + t * kPanel) = 0u;
-                }
-                if constexpr ((EPI & 2) != 0) {
-                    // the 16 lanes of one output row (every lane active here); lane 16 r + c keeps the sums of passes c and c + 16
-                    rsy = group_allreduce<4>(rsy, OpAdd());
-                    rsy_kept[(i * 8 + p) >> 4] = ((i * 8 + p) & 15) == rd_c ? rsy : rsy_kept[(i * 8 + p) >> 4];
                 }
             }
         }
@@ -733,6 +938,15 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
             }
         }
         if constexpr ((EPI & 2) != 0) {
+            if (form != kGeneral) {
+                rows_in = (lim + 3) >> 2;
+#pragma unroll
+                for (int h = 0; h < MI / 2; ++h) {   // lane 16 r + c: pass 16 h + c
+                    const int both = __builtin_amdgcn_ds_bpermute((rd_r * 16 + h * 8 + (rd_c >> 1)) * 4, rsy_pairs);
+                    const int even = (int)(short)both;
+                    rsy_kept[h] = (rd_c & 1) != 0 ? (both - even) >> 16 : even;
+                }
+            }
             // (one atomic instruction per 64 neighbouring tokens; four tokens at a time, the two layers 4096 -> 16384 -> 4096 took
             // 172 instead of 157 us at 1024 tokens, 110 instead of 100 at 512)
             if (g.rowsum_y) {
@@ -745,7 +959,7 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
             int cq[4];
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                cq[c] = (int)cqf[c] - 128 * rows_in;
+                cq[c] = (form != kGeneral ? (int)((((c & 1) ? cq13 : cq02) >> (8 * (c & 2))) & 0xffffu) : (int)cqf[c]) - 128 * rows_in;
                 cq[c] += partner<4>(cq[c]);
                 cq[c] += partner<5>(cq[c]);
             }
