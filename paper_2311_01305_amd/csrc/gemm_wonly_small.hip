@@ -15,7 +15,7 @@
 // load sits in a branch of its own; quads of tokens past the edge are left out.  With more token tiles than channel tiles the codes
 // are brought to the activations' natural order instead of the other way round (INT4 / INT3, us on the device with the weight in the
 // caches, before -> now: 17 tokens 4096 x 4096 7.2 -> 6.4 / 7.2 -> 6.5, 4096 x 11008 13.7 -> 11.6 / 14.0 -> 12.1; one token 11008 x 4096
-// 7.9 -> 7.6 / 8.4 -> 8.2; 16 tokens and 64 within 2 %).  Bound by the vector unit there: 85 operations for 32 codes a lane with their scale.
+// 7.9 -> 7.6 / 8.4 -> 8.2; 16 tokens and 64 within 2 %).  The vector unit has 73 operations there for 32 codes a lane with their scale.
 //
 // Bound by the read of the codes and, for small layers, by the launch and one round trip to memory.  Measured (INT4,
 // groups of 128, us per call on the device; before = de-quantising the whole weight and a 256 x 256-tiled GEMM):
