@@ -12,7 +12,7 @@
 // code fields come out of their packed words.
 //
 // Reads past an edge repeat the last row or the last values of K (their results are not stored, their activations are zero), so that no
-// load sits in a branch of its own; quads of tokens past the edge are left out.  With more token tiles than channel tiles the codes
+// load sits in a branch of its own; where they are many, quads of tokens past the edge are left out.  With more token tiles than channel tiles the codes
 // are brought to the activations' natural order instead of the other way round (INT4 / INT3, us on the device with the weight in the
 // caches, before -> now: 17 tokens 4096 x 4096 7.2 -> 6.4 / 7.2 -> 6.5, 4096 x 11008 13.7 -> 11.6 / 14.0 -> 12.1; one token 11008 x 4096
 // 7.9 -> 7.6 / 8.4 -> 8.2; 16 tokens and 64 within 2 %).  The vector unit has 73 operations there for 32 codes a lane with their scale.
@@ -39,15 +39,19 @@ constexpr int kChunk = 256;   // values of K a wavefront takes at a time
 // LDS per wavefront: 128 values of RX tokens (256 for RX = 4), 256 codes of 16 NT channels (16 bytes per 32 codes)
 constexpr int small_wave_lds(int rx, int nt) { return (rx == 4 ? 4 * 512 : rx * 256) + nt * 16 * 128; }
 
+// FEWER: quads of tokens past the edge are left out, by a branch around each load and write of four tokens.  Without those branches the
+// activations of the second half of a chunk are requested ahead of the next codes (loads return in order, and they are needed first); with them
+// that was slower (us, INT4: 13 tokens 16384 x 4096 12.2 -> 11.9, 32 tokens 16384 x 4096 15.4 -> 15.05, but 6 tokens 4096 x 16384 11.7 -> 12.1).
 // FINE: groups that are no multiple of 128 (a lane's 32 codes have one (Step, Z), but the four lanes that share
 // 128 values of a channel may differ)
-template <int BITS, int RX, int NT, int WAVES, bool FINE, bool OUT_F16>
+template <int BITS, int RX, int NT, int WAVES, bool FEWER, bool FINE, bool OUT_F16>
 __global__ __launch_bounds__(WAVES * kWave) void gemm_small_kernel(SmallArgs g)
 {
     constexpr int TT = RX < 16 ? 1 : RX / 16;
     constexpr int XH = RX == 4 ? 1 : 2;             // activation loads per chunk: whole, or 128 values at a time
     constexpr int XL = RX == 4 ? 2 : 4 * TT;        // 16-byte loads of activations per lane and time
     constexpr bool kNatural = TT > NT;              // the operand with fewer tiles is the one that is brought to the other's order
+    constexpr bool kCodesLate = RX > 4 && !FEWER;
     constexpr int kWords = BITS == 4 ? 4 : 3;
     typedef int Words __attribute__((ext_vector_type(kWords)));
     extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -106,7 +110,7 @@ __global__ __launch_bounds__(WAVES * kWave) void gemm_small_kernel(SmallArgs g)
         }
 #pragma unroll
         for (int i = 0; i < XL; ++i) {
-            if (RX > 4 && 4 * i >= tokens_left) break;
+            if (FEWER && 4 * i >= tokens_left) break;
             const uint32_t xo = (uint32_t)min((RX == 4 ? k + 128 * i : k) + (lane & 15) * 8, K - 8);
             xr[i] = *reinterpret_cast<const v4i*>(xbase + (xrow[RX == 4 ? 0 : i] + xo));
         }
@@ -131,10 +135,16 @@ __global__ __launch_bounds__(WAVES * kWave) void gemm_small_kernel(SmallArgs g)
     v4f bias = {0.f, 0.f, 0.f, 0.f};
     if (RX == 4 && g.bias && mine()) bias = *reinterpret_cast<const v4f*>(g.bias + channel());
 
-    constexpr int kStride = WAVES * kChunk;
-    int kc = wave * kChunk;
-    if (kc < K) { load_codes_at(kc); load_x_at(kc); }
-    for (; kc < K; kc += kStride) {
+    // This wavefront's chunks: wave, wave + WAVES, ...  Where rows begin a multiple of 4 KiB apart, all of them lie on the same memory channels at
+    // one K, and the workgroups of an XCD begin this round at different places (INT4, us, one / five / 16 tokens: 8192 x 8192 12.05 -> 9.85 /
+    // 14.3 -> 11.6 / 15.8 -> 14.0, 4096 x 16384 10.5 -> 9.75 / 12.05 -> 11.65 / 14.8 -> 14.2; elsewhere no gain, and up to 6 % lost where the
+    // activations are large: 33 tokens 8192 x 22016 51.5 -> 54.9).
+    const int cnt = max(((K + kChunk - 1) / kChunk - wave + WAVES - 1) / WAVES, 0);
+    int at = code_pitch % 4096 == 0 ? (int)((blockIdx.x / kXcdCount % 16) * (unsigned)cnt / 16u) : 0, kc = (wave + at * WAVES) * kChunk;
+    if (cnt > 0) { load_codes_at(kc); load_x_at(kc); }
+    for (int left = cnt; left > 0; --left) {
+        at = at + 1 == cnt ? 0 : at + 1;
+        const int kn = left > 1 ? (wave + at * WAVES) * kChunk : K;   // (K: none)
         uint32_t scc[NT];
 #pragma unroll
         for (int j = 0; j < NT; ++j) {
@@ -149,21 +159,23 @@ __global__ __launch_bounds__(WAVES * kWave) void gemm_small_kernel(SmallArgs g)
             }
         }
         wave_lds_fence();
-        if (kc + kStride < K) load_codes_at(kc + kStride);
+        if (!kCodesLate && kn < K) load_codes_at(kn);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             if (kc + h * 128 >= K) break;
             if (h < XH) {
 #pragma unroll
                 for (int i = 0; i < XL; ++i) {
-                    if (RX > 4 && 4 * i >= tokens_left) break;
+                    if (FEWER && 4 * i >= tokens_left) break;
                     const int row = (RX == 4 ? 0 : 4 * i) + (lane >> 4), k = kc + (RX == 4 ? i : h) * 128;
                     if (k + 128 > K && k + (lane & 15) * 8 >= K) xr[i] = v4i{0, 0, 0, 0};
                     *reinterpret_cast<v4i*>(lx + (RX == 4 ? i * 1024 : 0) + row * 256 + (((lane & 15) ^ (row & 15)) * 16)) = kNatural ? xr[i] : pair_order(xr[i]);
                 }
                 wave_lds_fence();
-                const int kx = h + 1 < XH ? kc + 128 : kc + kStride;
+                const int kx = h + 1 < XH && kc + 128 < K ? kc + 128 : kn;
                 if (kx < K) load_x_at(kx);
+                // (loads return in order: behind the second half's activations, which are needed first)
+                if (kCodesLate && h == 0 && kn < K) load_codes_at(kn);
             }
             // the operand with fewer tiles stays in registers over the loop on the other
             auto frag_x = [&](int i, int d) {
@@ -240,6 +252,7 @@ __global__ __launch_bounds__(WAVES * kWave) void gemm_small_kernel(SmallArgs g)
             }
             wave_lds_fence();   // this chunk's reads stay ahead of the next one's writes
         }
+        kc = kn;
     }
 
     // register v of lane l is output channel 4 (l / 16) + v of the 16, token l % 16
@@ -265,17 +278,17 @@ __global__ __launch_bounds__(WAVES * kWave) void gemm_small_kernel(SmallArgs g)
     }
 }
 
-template <int BITS, int RX, int NT, int WAVES>
+template <int BITS, int RX, int NT, int WAVES, bool FEWER>
 static int launch_tile(const SmallArgs& g, bool fine, bool out_f16, hipStream_t st)
 {
     constexpr int TT = RX < 16 ? 1 : RX / 16;
     const dim3 grid((unsigned)cdiv(g.N, 16 * NT), (unsigned)cdiv(g.T, RX));
     constexpr int work = WAVES * small_wave_lds(RX, NT), red = WAVES * TT * NT * kWave * 16;
     constexpr int lds = work > red ? work : red;
-    const void* fn = fine ? (out_f16 ? reinterpret_cast<const void*>(gemm_small_kernel<BITS, RX, NT, WAVES, true, true>)
-                                     : reinterpret_cast<const void*>(gemm_small_kernel<BITS, RX, NT, WAVES, true, false>))
-                          : (out_f16 ? reinterpret_cast<const void*>(gemm_small_kernel<BITS, RX, NT, WAVES, false, true>)
-                                     : reinterpret_cast<const void*>(gemm_small_kernel<BITS, RX, NT, WAVES, false, false>));
+    const void* fn = fine ? (out_f16 ? reinterpret_cast<const void*>(gemm_small_kernel<BITS, RX, NT, WAVES, FEWER, true, true>)
+                                     : reinterpret_cast<const void*>(gemm_small_kernel<BITS, RX, NT, WAVES, FEWER, true, false>))
+                          : (out_f16 ? reinterpret_cast<const void*>(gemm_small_kernel<BITS, RX, NT, WAVES, FEWER, false, true>)
+                                     : reinterpret_cast<const void*>(gemm_small_kernel<BITS, RX, NT, WAVES, FEWER, false, false>));
     int dev = 0, cus = 0;
     if (lds > 65536 && (device_cus(dev, cus) != AWEQ_OK || raise_lds_limit(fn, dev, lds) != AWEQ_OK)) return AWEQ_ERR_LAUNCH;
     void* args[] = {const_cast<SmallArgs*>(&g)};
@@ -307,15 +320,24 @@ static int launch_bits(const SmallArgs& g, bool fine, int nt, bool out_f16, hipS
     // 17.2 -> 14.8, but 2048 x 8192 8.4 -> 8.5; 32 tokens do not fit the registers: 4096 x 11008 13.8 -> 16.1)
     const bool lone = cdiv(g.N, 16) <= 256;
     if (g.T <= 4) {
-        if (nt == 2) return launch_tile<BITS, 4, 2, 8>(g, fine, out_f16, st);
-        return lone && g.K >= 8192 ? launch_tile<BITS, 4, 1, 16>(g, fine, out_f16, st) : launch_tile<BITS, 4, 1, 8>(g, fine, out_f16, st);
+        if (nt == 2) return launch_tile<BITS, 4, 2, 8, false>(g, fine, out_f16, st);
+        return lone && g.K >= 8192 ? launch_tile<BITS, 4, 1, 16, false>(g, fine, out_f16, st) : launch_tile<BITS, 4, 1, 8, false>(g, fine, out_f16, st);
     }
     if (g.T <= 16) {
-        if (nt == 2) return launch_tile<BITS, 16, 2, 8>(g, fine, out_f16, st);
-        return lone && g.K >= 16384 ? launch_tile<BITS, 16, 1, 16>(g, fine, out_f16, st) : launch_tile<BITS, 16, 1, 8>(g, fine, out_f16, st);
+        if (g.T <= 12) {   // (8 tokens of 16: 11008 x 4096 INT4 10.45 / 10.7 us with / without the branches, 13 tokens 11.6 / 11.05)
+            if (nt == 2) return launch_tile<BITS, 16, 2, 8, true>(g, fine, out_f16, st);
+            return lone && g.K >= 16384 ? launch_tile<BITS, 16, 1, 16, true>(g, fine, out_f16, st) : launch_tile<BITS, 16, 1, 8, true>(g, fine, out_f16, st);
+        }
+        if (nt == 2) return launch_tile<BITS, 16, 2, 8, false>(g, fine, out_f16, st);
+        return lone && g.K >= 16384 ? launch_tile<BITS, 16, 1, 16, false>(g, fine, out_f16, st) : launch_tile<BITS, 16, 1, 8, false>(g, fine, out_f16, st);
     }
-    return nt == 1 ? launch_tile<BITS, 32, 1, 8>(g, fine, out_f16, st) : nt == 2 ? launch_tile<BITS, 32, 2, 8>(g, fine, out_f16, st)
-                                                                                 : launch_tile<BITS, 32, 4, 8>(g, fine, out_f16, st);
+    // Tokens left out or not, us: INT4 20 tokens 4096 x 4096 6.2 / 7.0, 24 tokens 8192 x 8192 15.05 / 15.6, 32 tokens 8192 x 8192 16.3 / 15.95;
+    // 64 channels a workgroup: 24 tokens 16384 x 4096 15.7 / 14.95, INT3 17 tokens 11008 x 4096 13.9 / 14.3
+    const bool fewer = g.T <= 24 && (nt <= 2 || BITS == 3);
+    if (fewer) return nt == 1 ? launch_tile<BITS, 32, 1, 8, true>(g, fine, out_f16, st) : nt == 2 ? launch_tile<BITS, 32, 2, 8, true>(g, fine, out_f16, st)
+                                                                                                 : launch_tile<BITS, 32, 4, 8, true>(g, fine, out_f16, st);
+    return nt == 1 ? launch_tile<BITS, 32, 1, 8, false>(g, fine, out_f16, st) : nt == 2 ? launch_tile<BITS, 32, 2, 8, false>(g, fine, out_f16, st)
+                                                                                        : launch_tile<BITS, 32, 4, 8, false>(g, fine, out_f16, st);
 }
 
 int launch_small(const SmallArgs& g, int bits, int group, const SmallPlan& p, bool out_f16, hipStream_t st)
