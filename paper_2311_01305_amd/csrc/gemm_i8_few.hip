@@ -25,8 +25,11 @@ constexpr int kWaves = kThreads / kWave;
 
 // QX: 0: the tokens' codes are in memory (g.A).  1 / 2: every workgroup quantises the few binary16 / binary32 tokens (QuantIn) for
 // itself while its first weights are on their way, the first workgroup also for the caller: a second launch costs more
-// than the repeated work.
-template <int TT, int NT, int D, int QX>
+// than the repeated work.  TQ: their number, 4 for three too.  Loads return in order, so the tokens, their scales and the epilogue's constants are
+// requested ahead of the weights; behind them the quantizer waited for the weights first (us a call, before -> now, with reads of the tokens that
+// leave them in the caches for the other workgroups: one token 4096 x 4096 6.4 -> 5.15, 8192 x 8192 16.0 -> 13.6, 4096 x 16384 18.0 -> 15.6,
+// 11008 x 4096 10.85 -> 9.3; four tokens 16384 x 4096 15.1 -> 12.95).
+template <int TT, int NT, int D, int QX, int TQ>
 __global__ __launch_bounds__(kThreads) void gemm_i8_few(GemmArgs g, QuantIn in)
 {
     extern __shared__ __attribute__((aligned(16))) int red[];   // [wave][TT NT][lane][4], then (QX) the tokens' codes, K padded to panels
@@ -70,13 +73,23 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_few(GemmArgs g, QuantIn in)
             for (int t = 0; t < TT; ++t) x[d][t] = *reinterpret_cast<const v4i*>(xbase + p * xp + xo[t]);
         }
     };
-    if (cnt >= D) {
+    // (QX) A thread has every kThreads-th unit of 8 values of each token, at most kRounds of them
+    constexpr int kRounds = TQ == 1 ? 4 : 2;
+    static_assert(QX == 0 || TQ * kRounds * kThreads * 8 >= kQuantFewBytes, "every code has a thread");
+    const int units = (int)(g.K / 8), padded = np * (kPanel / 8);
+    RawUnit<QX == 1> raw[QX != 0 ? kRounds : 1][QX != 0 ? TQ : 1];
+    Float4 is[QX != 0 ? kRounds : 1][2];
+    if constexpr (QX != 0) {
 #pragma unroll
-        for (int d = 0; d < D; ++d) load(d, d);
-    } else {
+        for (int i = 0; i < kRounds; ++i) {
+            if (i * kThreads >= padded) break;
+            const int u = min(i * kThreads + (int)threadIdx.x, units - 1);   // (past K the last unit again, whose codes are not kept)
 #pragma unroll
-        for (int d = 0; d < D; ++d)
-            if (d < cnt) load(d, d);
+            for (int t = 0; t < TQ; ++t)
+                if (TQ <= 2 || t < (int)g.T) raw[i][t].load_shared(in.X, t * in.ldx + u * 8);
+            is[i][0] = *reinterpret_cast<const Float4*>(in.inv_s + u * 8);
+            is[i][1] = *reinterpret_cast<const Float4*>(in.inv_s + u * 8 + 4);
+        }
     }
     // What the epilogue needs of a channel (a token) is requested here by one thread each and waits in LDS: at the end, one round trip after the
     // other, it took 1 - 2 us
@@ -101,47 +114,51 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_few(GemmArgs g, QuantIn in)
             e_rw = g.rowsum_x[t0 + e_tok];
         }
     };
-    if constexpr (QX == 0) request_constants();   // (otherwise behind the tokens that are quantised first)
+    if constexpr (QX != 0) request_constants();   // (with the tokens, ahead of the weights)
+    if (cnt >= D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) load(d, d);
+    } else {
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+            if (d < cnt) load(d, d);
+    }
+    if constexpr (QX == 0) request_constants();
     int8_t* const codes = reinterpret_cast<int8_t*>(red + kWaves * TT * NT * kWave * 4);
     if constexpr (QX != 0) {
         const ActParams ap = quot_params(*g.act_step, *g.act_zero);
         uint32_t st = 0;
         float big = 0.0f;
-        const int units = (int)(g.K / 8), padded = np * (kPanel / 8);
         const int T = (int)g.T;
-        int rs[kQuantTokens];
+        int rs[TQ];
 #pragma unroll
-        for (int t = 0; t < kQuantTokens; ++t) rs[t] = 0;
+        for (int t = 0; t < TQ; ++t) rs[t] = 0;
         if (threadIdx.x < kQuantTokens) s_rs[threadIdx.x] = 0;
         __syncthreads();
-        for (int u = threadIdx.x; u < padded; u += kThreads) {
-            const bool real = u < units;   // (past K: the zero fill of the last panel)
-            RawUnit<QX == 1> raw[kQuantTokens];
-            float is[8];
-            if (real) {
 #pragma unroll
-                for (int t = 0; t < kQuantTokens; ++t)
-                    if (t < T) raw[t].load(in.X, t * in.ldx + u * 8);
-                const Float4 a = *reinterpret_cast<const Float4*>(in.inv_s + u * 8), b = *reinterpret_cast<const Float4*>(in.inv_s + u * 8 + 4);
+        for (int i = 0; i < kRounds; ++i) {
+            if (i * kThreads >= padded) break;
+            const int u = i * kThreads + (int)threadIdx.x;
+            float isf[8];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) { is[i] = a.f[i]; is[4 + i] = b.f[i]; }
-            }
+            for (int e = 0; e < 4; ++e) { isf[e] = is[i][0].f[e]; isf[4 + e] = is[i][1].f[e]; }
 #pragma unroll
-            for (int t = 0; t < kQuantTokens; ++t) {
-                if (t >= T) break;
-                uint2 c = make_uint2(0u, 0u);
-                if (real) {
-                    float xf[8];
-                    raw[t].get(xf);
-                    c = act_unit_any<QX == 1>(xf, is, ap, rs[t], big, st);
-                }
+            for (int t = 0; t < TQ; ++t) {
+                if (TQ > 2 && t >= T) break;
+                float xf[8];
+                raw[i][t].get(xf);
+                int r8 = 0;
+                uint2 c = act_unit_any<QX == 1>(xf, isf, ap, r8, big, st);
+                if (u >= units) { c = make_uint2(0u, 0u); r8 = 0; }   // (the zero fill of the last panel)
+                rs[t] += r8;
+                if (u >= padded) continue;
                 *reinterpret_cast<uint2*>(codes + (t * padded + u) * 8) = c;
-                if (blockIdx.x == 0) *reinterpret_cast<uint2*>(in.xq + ((int64_t)(u >> 3) * g.T + t) * kPanel + (u & 7) * 8) = c;
+                if (blockIdx.x == 0) *reinterpret_cast<uint2*>(in.xq + ((int64_t)(u >> 3) * T + t) * kPanel + (u & 7) * 8) = c;
             }
         }
 #pragma unroll
-        for (int t = 0; t < kQuantTokens; ++t) {
-            if (t >= T) break;
+        for (int t = 0; t < TQ; ++t) {
+            if (TQ > 2 && t >= T) break;
             rs[t] = wave_allreduce(rs[t], OpAdd());
             if (lane == 0) atomicAdd(&s_rs[t], rs[t]);
         }
@@ -149,7 +166,6 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_few(GemmArgs g, QuantIn in)
         if (blockIdx.x == 0) raise_status(g.status, st);
         __syncthreads();
         if (blockIdx.x == 0 && in.rowsum_x && (int)threadIdx.x < (int)g.T) in.rowsum_x[threadIdx.x] = s_rs[threadIdx.x];
-        request_constants();
     }
     const int8_t* const own = codes + min(r, (int)g.T - 1) * np * kPanel + q * 16;   // (QX: one row of 16 tokens)
     auto mul = [&](int d, int i) {
@@ -252,13 +268,13 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_few(GemmArgs g, QuantIn in)
 
 // Token tiles ride on the grid's y dimension, at most 65535 to a launch: layers of up to 64 channels come here at any number of tokens
 constexpr int kMaxGridY = 65535;
-template <int TT, int NT, int D, int QX = 0>
+template <int TT, int NT, int D, int QX = 0, int TQ = 1>
 static int launch_tile(GemmArgs g, hipStream_t st, QuantIn in = {})
 {
     constexpr int kSums = kWaves * TT * NT * kWave * 16;   // partial sums; a launch that quantises has the tokens' codes behind them
     static_assert(QX == 0 || kSums + kQuantFewBytes <= 32768, "a launch that quantises stays below the LDS limit that has to be raised");
     const int lds = kSums + (QX != 0 ? (int)(g.T * panel_count(g.K) * kPanel) : 0);
-    const void* fn = reinterpret_cast<const void*>(gemm_i8_few<TT, NT, D, QX>);
+    const void* fn = reinterpret_cast<const void*>(gemm_i8_few<TT, NT, D, QX, TQ>);
     int dev = 0, cus = 0;
     if (lds > 32768 && (device_cus(dev, cus) != AWEQ_OK || raise_lds_limit(fn, dev, lds) != AWEQ_OK)) return AWEQ_ERR_LAUNCH;
     void* args[] = {&g, &in};
@@ -291,8 +307,10 @@ FewPlan plan_few(int64_t T, int64_t N)
 
 int launch_gemm_i8_few_quant(const GemmArgs& g, const FewPlan& p, const QuantIn& in, bool f16, hipStream_t st)
 {
-    if (p.tile == 0) return f16 ? few::launch_tile<1, 1, 6, 1>(g, st, in) : few::launch_tile<1, 1, 6, 2>(g, st, in);
-    return f16 ? few::launch_tile<1, 2, 4, 1>(g, st, in) : few::launch_tile<1, 2, 4, 2>(g, st, in);
+#define AWEQ_FQ(NT, D, Q) (g.T == 1 ? few::launch_tile<1, NT, D, Q, 1>(g, st, in) : g.T == 2 ? few::launch_tile<1, NT, D, Q, 2>(g, st, in) : few::launch_tile<1, NT, D, Q, 4>(g, st, in))
+    if (p.tile == 0) return f16 ? AWEQ_FQ(1, 4, 1) : AWEQ_FQ(1, 4, 2);
+    return f16 ? AWEQ_FQ(2, 3, 1) : AWEQ_FQ(2, 3, 2);
+#undef AWEQ_FQ
 }
 
 int launch_gemm_i8_few(const GemmArgs& g, const FewPlan& p, hipStream_t st)
