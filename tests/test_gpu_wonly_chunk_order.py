@@ -12,7 +12,8 @@ DEV = "cuda:0"
 
 @pytest.mark.parametrize("bits,N,K,tokens", [(4, 2052, 8192, (1, 5, 12, 13, 16, 17, 24, 25, 33)),     # more workgroups than an XCD's round has places
                                              (4, 276, 16384, (2, 12, 13, 32)), (3, 260, 32768, (1, 16, 17, 25)),   # 16 wavefronts; two chunks and more
-                                             (3, 516, 448, (12, 13, 16, 24, 25, 33)), (4, 516, 320, (13, 25))])    # a last chunk of which there is half
+                                             (3, 516, 448, (12, 13, 16, 24, 25, 33)), (4, 516, 320, (13, 25)),    # a last chunk of which there is half
+                                             (4, 8212, 320, (1, 4, 5, 12, 13, 16)), (3, 12288, 1088, (1, 5, 16)), (4, 12292, 64, (4, 5)), (3, 16384, 128, (4,))])   # four wavefronts, and past them
 def test_chunk_order(orc, bits, N, K, tokens):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
