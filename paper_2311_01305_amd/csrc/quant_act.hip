@@ -311,7 +311,7 @@ __global__ __launch_bounds__(kQaMergeCols * kQaMergeParts) void quant_act_merge(
 // next unit is requested while this one is quantised, without a branch around the load (3000 x 4104 14.7 -> 12.6 us, 4096 x 4096 15.2 -> 14.1; with the stores that stay in the caches, whole int8 forward, us:
 // 300 tokens 4096 x 11008 46.4 -> 40.5, 2048 tokens 99.2 -> 95.6, 4096 tokens 11008 x 4096 182.6 -> 178.6).
 constexpr int kQrBlock = 512;
-template <bool F16, int ROWS, bool CACHED>
+template <bool F16, int ROWS>
 __global__ __launch_bounds__(kQrBlock) void quant_act_rows(
     const void* __restrict__ X, int64_t T, int64_t K, int64_t ldx, const float* __restrict__ inv_s,
     const float* __restrict__ act_step, const int32_t* __restrict__ act_zero, int8_t* __restrict__ xq,
@@ -325,11 +325,7 @@ __global__ __launch_bounds__(kQrBlock) void quant_act_rows(
     // around a load: past the end the last unit, the last row again, not stored)
     RawUnit<F16> raw[ROWS];
     Float4 isa, isb;
-    auto request = [&](int i, int64_t u) {
-        const int64_t at = (r0 + min(i, nrows - 1)) * ldx + min(u, units - 1) * 8;
-        if constexpr (CACHED) raw[i].load_shared(X, at);
-        else raw[i].load(X, at);
-    };
+    auto request = [&](int i, int64_t u) { raw[i].load(X, (r0 + min(i, nrows - 1)) * ldx + min(u, units - 1) * 8); };
     auto request_is = [&](int64_t u) {
         const float* const q = inv_s + min(u, units - 1) * 8;
         isa = *reinterpret_cast<const Float4*>(q);
@@ -453,17 +449,9 @@ int launch_quant_act(const void* X, aweq_dtype dt, int64_t T, int64_t K, int64_t
     const int64_t rows_most = rowsum_x && K <= kQaPanels * kPanel ? 2048 : K < 2048 ? 4096 : T * K <= (6ll << 24) ? 16384 : 4096;
     if (!range && !colsum_xq && xq && aligned16(inv_s) && T <= rows_most &&
         !overlap({{rowsum_x, T * 4}, {xq, T * panel_count(K) * kPanel}}, {matrix_span(X, T, K, ldx, dtype_size(dt)), {inv_s, K * 4}, {act_step, 4}, {act_zero, 4}})) {
-        // Binary16 X that leaves room in the 256 MB memory-side cache is read through the caches, which still hold it where the layer before has
-        // just written it; non-temporal reads go to memory (int8 forward, us, non-temporal / cached: 2048 tokens 4096 x 11008 (45 MB) 94.0 / 91.6,
-        // 5000 tokens 4096 x 4096 (41 MB) 106 / 96, 12000 tokens 1000 x 3000 63.3 / 59.1, but 8192 tokens 16384 x 4096 (67 MB) 431 / 440,
-        // 3500 tokens 4096 x 11008 (77 MB) 142.9 / 144.9)
-        const bool cached = dt == AWEQ_F16 && T * K <= (24ll << 20);
-#define AWEQ_QR(F, R, C) quant_act_rows<F, R, C><<<(unsigned)cdiv(T, R), kQrBlock, 0, st>>>(X, T, K, ldx, inv_s, act_step, act_zero, xq, rowsum_x, status)
-#define AWEQ_QRT(F, C) do { if (T <= 256) AWEQ_QR(F, 1, C); else if (T <= 1024) AWEQ_QR(F, 2, C); else AWEQ_QR(F, 4, C); } while (0)
-        if (cached) AWEQ_QRT(true, true);
-        else if (dt == AWEQ_F16) AWEQ_QRT(true, false);
-        else AWEQ_QRT(false, false);
-#undef AWEQ_QRT
+#define AWEQ_QR(F, R) quant_act_rows<F, R><<<(unsigned)cdiv(T, R), kQrBlock, 0, st>>>(X, T, K, ldx, inv_s, act_step, act_zero, xq, rowsum_x, status)
+        if (dt == AWEQ_F16) { if (T <= 256) AWEQ_QR(true, 1); else if (T <= 1024) AWEQ_QR(true, 2); else AWEQ_QR(true, 4); }
+        else { if (T <= 256) AWEQ_QR(false, 1); else if (T <= 1024) AWEQ_QR(false, 2); else AWEQ_QR(false, 4); }
 #undef AWEQ_QR
         return launch_status();
     }
