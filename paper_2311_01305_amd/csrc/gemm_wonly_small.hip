@@ -117,11 +117,29 @@ __global__ __launch_bounds__(WAVES * kWave) void gemm_small_kernel(SmallArgs g)
     };
 
     const int fr = RX == 4 ? r & 3 : r;   // (RX = 4: tokens past the fourth repeat the first four, their columns are not stored)
-    v4f acc[TT][NT];
+    // Four wavefronts keep two sums, of every other chunk each, so that no chain of additions is longer than eight wavefronts' (with one, the error
+    // against 64 bits grew from 1.5e-7 to 2.0e-7 at K = 4096)
+    constexpr int kSets = WAVES < 8 ? 2 : 1;
+    v4f acc[TT][NT], other[kSets == 2 ? TT : 1][kSets == 2 ? NT : 1];
 #pragma unroll
     for (int i = 0; i < TT; ++i)
 #pragma unroll
-        for (int j = 0; j < NT; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < NT; ++j) {
+            acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+            if constexpr (kSets == 2) other[i][j] = acc[i][j];
+        }
+    auto swap_sets = [&]() {
+        if constexpr (kSets == 2) {
+#pragma unroll
+            for (int i = 0; i < TT; ++i)
+#pragma unroll
+                for (int j = 0; j < NT; ++j) {
+                    const v4f a = acc[i][j];
+                    acc[i][j] = other[i][j];
+                    other[i][j] = a;
+                }
+        }
+    };
 
     // the quad of channels of one token that this thread stores
     constexpr int kTiles = TT * NT;
@@ -253,21 +271,25 @@ __global__ __launch_bounds__(WAVES * kWave) void gemm_small_kernel(SmallArgs g)
             wave_lds_fence();   // this chunk's reads stay ahead of the next one's writes
         }
         kc = kn;
+        swap_sets();
     }
 
     // register v of lane l is output channel 4 (l / 16) + v of the 16, token l % 16
-    float* const red = reinterpret_cast<float*>(lds);   // [wave][TT NT][lane][4]
+    float* const red = reinterpret_cast<float*>(lds);   // [set][wave][TT NT][lane][4]
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < TT; ++i)
 #pragma unroll
-        for (int j = 0; j < NT; ++j) *reinterpret_cast<v4f*>(red + ((wave * kTiles + i * NT + j) * kWave + lane) * 4) = acc[i][j];
+        for (int j = 0; j < NT; ++j) {
+            *reinterpret_cast<v4f*>(red + ((wave * kTiles + i * NT + j) * kWave + lane) * 4) = acc[i][j];
+            if constexpr (kSets == 2) *reinterpret_cast<v4f*>(red + (((WAVES + wave) * kTiles + i * NT + j) * kWave + lane) * 4) = other[i][j];
+        }
     __syncthreads();
     if (!mine()) return;
     const int64_t t = token(), n = channel();
     v4f o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int w = 0; w < WAVES; ++w) o += *reinterpret_cast<const v4f*>(red + ((w * kTiles + et) * kWave + lane) * 4);
+    for (int w = 0; w < WAVES * kSets; ++w) o += *reinterpret_cast<const v4f*>(red + ((w * kTiles + et) * kWave + lane) * 4);
     if (g.bias) o += RX == 4 ? bias : *reinterpret_cast<const v4f*>(g.bias + n);
     if constexpr (OUT_F16) {
         typedef _Float16 h4 __attribute__((ext_vector_type(4)));
@@ -283,7 +305,7 @@ static int launch_tile(const SmallArgs& g, bool fine, bool out_f16, hipStream_t 
 {
     constexpr int TT = RX < 16 ? 1 : RX / 16;
     const dim3 grid((unsigned)cdiv(g.N, 16 * NT), (unsigned)cdiv(g.T, RX));
-    constexpr int work = WAVES * small_wave_lds(RX, NT), red = WAVES * TT * NT * kWave * 16;
+    constexpr int work = WAVES * small_wave_lds(RX, NT), red = (WAVES < 8 ? 2 : 1) * WAVES * TT * NT * kWave * 16;
     constexpr int lds = work > red ? work : red;
     const void* fn = fine ? (out_f16 ? reinterpret_cast<const void*>(gemm_small_kernel<BITS, RX, NT, WAVES, FEWER, true, true>)
                                      : reinterpret_cast<const void*>(gemm_small_kernel<BITS, RX, NT, WAVES, FEWER, true, false>))
