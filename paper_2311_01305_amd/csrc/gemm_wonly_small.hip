@@ -342,9 +342,9 @@ static int launch_bits(const SmallArgs& g, bool fine, int nt, bool out_f16, hipS
     // 17.2 -> 14.8, but 2048 x 8192 8.4 -> 8.5; 32 tokens do not fit the registers: 4096 x 11008 13.8 -> 16.1)
     const bool lone = cdiv(g.N, 16) <= 256;
     // 513 to 768 workgroups (to 1024 of up to four tokens) of short rows: four wavefronts, of which all workgroups are resident at a time; eight
-    // take 512 of them, and the rest wait (us, INT4, 8 -> 4: one token 11008 x 4096 8.6 -> 8.2, 12288 x 2048 5.35 -> 4.85, 8704 x 1024 4.45 -> 3.65,
-    // 16384 x 4096 (32 channels a workgroup before) 10.25 -> 9.75; 6 tokens 8704 x 4096 9.95 -> 9.0, 11008 x 8192 15.9 -> 15.4, 16 tokens 11008 x 4096
-    // 11.0 -> 10.7; but one token 11008 x 11008 15.8 -> 16.5, INT3 16 tokens 11008 x 5120 12.6 -> 12.9, 6 tokens 16384 x 4096 11.4 -> 11.7)
+    // take 512 of them, and the rest wait (us, INT4, 8 -> 4: one token 11008 x 4096 8.65 -> 8.4, 12288 x 2048 5.35 -> 4.9, 8704 x 1024 4.45 -> 3.65,
+    // 16384 x 4096 (32 channels a workgroup before) 10.25 -> 10.1; 6 tokens 8704 x 4096 9.95 -> 9.2, 16 tokens 11008 x 4096 11.0 -> 10.8; but one
+    // token 11008 x 11008 15.8 -> 16.5, INT3 16 tokens 11008 x 5120 12.6 -> 12.9, 6 tokens 16384 x 4096 11.4 -> 11.7)
     if (g.T <= 16 && cdiv(g.N, 16) > 512 && g.N <= (g.T <= 4 ? 16384 : 12288) && g.K <= (BITS == 4 ? 8192 : 4096))
         return g.T <= 4 ? launch_tile<BITS, 4, 1, 4, false>(g, fine, out_f16, st) : g.T <= 12 ? launch_tile<BITS, 16, 1, 4, true>(g, fine, out_f16, st)
                                                                                               : launch_tile<BITS, 16, 1, 4, false>(g, fine, out_f16, st);
