@@ -26,7 +26,7 @@ constexpr int kWaves = kThreads / kWave;
 // QX: 0: the tokens' codes are in memory (g.A).  1 / 2: every workgroup quantises the few binary16 / binary32 tokens (QuantIn) for
 // itself while its first weights are on their way, the first workgroup also for the caller: a second launch costs more
 // than the repeated work.  TQ: their number, 4 for three too.  Loads return in order, so the tokens, their scales and the epilogue's constants are
-// requested ahead of the weights; behind them the quantizer waited for the weights first (us a call, before -> now, with reads of the tokens that
+// requested ahead of the weights; behind them the quantizer waited for the weights first (us a call, weights in the caches, before -> now, with reads of the tokens that
 // leave them in the caches for the other workgroups: one token 4096 x 4096 6.4 -> 5.15, 8192 x 8192 16.0 -> 13.6, 4096 x 16384 18.0 -> 15.6,
 // 11008 x 4096 10.85 -> 9.3; four tokens 16384 x 4096 15.1 -> 12.95).
 template <int TT, int NT, int D, int QX, int TQ>
