@@ -290,8 +290,8 @@ int aweq_wonly_gemm(const void* X_hat, int64_t T, int64_t K, int64_t ldx,
                     void* ws, size_t ws_bytes, uint32_t* status, void* stream);
 
 /* ---- Stages 1 - 5 in one call: the calibration of a layer, or of any number of layers that read the same activation (n_weights > 1:
- * one scale from the merged weight ranges, one activation quantizer, W8A8 per channel).  The outputs are those of the stage entry points
- * called one after the other; the launches are fewer where the shapes allow (workspace of
+ * one scale from the merged weight ranges, one activation quantizer; every weight has slices of its own, as `group` says).  The outputs are
+ * those of the stage entry points called one after the other; the launches are fewer where the shapes allow (workspace of
  * aweq_workspace_size(AWEQ_OP_CALIBRATE, T, K, sum of the N); with less, down to what the stages ask for, they run one by one).
  * Sums in binary64 (xsum, delta) are added in another order than the stages add them; everything else is the same to the bit.
  * Nullable: count, wcount, p_x, p_w, status; bias_in; rowsum_w and colsum_acc where no stage needs them; xq and rowsum_x without the

@@ -287,7 +287,8 @@ static int run_calibration(const aweq_calib_layer& l, const aweq_calib_weight* w
     const bool front = fused_front(l, w, n);
     bool pass = front;
     for (int i = 0; pass && i < n; ++i) pass = weight_pass_takes(l.bits, l.group, l.w8a8 != 0, w[i].N, l.K, (uint64_t)l.T);
-    const bool fold = n == 1 && !(l.fused_weight_pass && l.group == 0);   // fold and quantise in calls of their own
+    // fold and quantise in calls of their own: aweq_fold_quant_weight has one scale per output channel only
+    const bool fold = l.group != 0 || (n == 1 && !l.fused_weight_pass);
     int rc;
     FinishArgs fin;
     if (front) {
@@ -325,7 +326,7 @@ static int run_calibration(const aweq_calib_layer& l, const aweq_calib_weight* w
     if (front) {
         rc = launch_finish(fin, l.K, st);
         if (rc != AWEQ_OK) return rc;
-        if (fold) launch_fold(w[0].W, w[0].W_hat, l.dt, w[0].N, l.K, w[0].ldw, w[0].ldwh, l.s, st);
+        for (int i = 0; fold && i < n; ++i) launch_fold(w[i].W, w[i].W_hat, l.dt, w[i].N, l.K, w[i].ldw, w[i].ldwh, l.s, st);
     } else {
         rc = aweq_calib_stats(l.X, l.dt, l.T, l.K, l.ldx, l.xmin, l.xmax, l.xsum, l.count, 0, 1, l.r_x, l.R_x, l.p_x, l.ws, l.ws_bytes, l.status, stream);
         for (int i = 0; rc == AWEQ_OK && i < n; ++i)   // (min of mins, max of maxes over the weights)
@@ -335,6 +336,10 @@ static int run_calibration(const aweq_calib_layer& l, const aweq_calib_weight* w
         rc = aweq_equalize(l.xmin, l.xmax, l.xsum, (uint64_t)l.T, l.wmin, l.wmax, l.K, l.enable_awe, l.s, l.inv_s, fold ? w[0].W : nullptr,
                            fold ? w[0].W_hat : nullptr, l.dt, w[0].N, w[0].ldw, w[0].ldwh, nullptr, l.xhat_range, l.mu_xhat, l.act_step, l.act_zero,
                            l.status, stream);
+        for (int i = 1; rc == AWEQ_OK && fold && i < n; ++i) {
+            rc = check_fold_args(w[i].W, w[i].W_hat, l.dt, w[i].N, l.K, w[i].ldw, w[i].ldwh);
+            if (rc == AWEQ_OK) launch_fold(w[i].W, w[i].W_hat, l.dt, w[i].N, l.K, w[i].ldw, w[i].ldwh, l.s, st);
+        }
         if (rc != AWEQ_OK) return rc;
     }
     for (int i = 0; i < n; ++i) {

@@ -140,6 +140,16 @@ __global__ __launch_bounds__(256) void fold_weight(const void* __restrict__ Wv, 
     }
 }
 
+int check_fold_args(const void* W, const void* W_hat, aweq_dtype dt, int64_t N, int64_t K, int64_t ldw, int64_t ldwh)
+{
+    if (!W || !W_hat) return AWEQ_ERR_NULL;
+    if (dt != AWEQ_F32 && dt != AWEQ_F16) return AWEQ_ERR_DTYPE;
+    if (N <= 0 || ldw < K || ldwh < K) return AWEQ_ERR_SHAPE;
+    if (!aligned16(W) || !aligned16(W_hat) || ((size_t)ldw * dtype_size(dt)) % 16 != 0 || ((size_t)ldwh * dtype_size(dt)) % 16 != 0)
+        return AWEQ_ERR_ALIGN;
+    return AWEQ_OK;
+}
+
 // W_hat = W s on checked arguments
 void launch_fold(const void* W, void* W_hat, aweq_dtype dt, int64_t N, int64_t K, int64_t ldw, int64_t ldwh, const float* s, hipStream_t st)
 {
@@ -180,12 +190,8 @@ extern "C" int aweq_equalize(const float* xmin, const float* xmax, const double*
     if (enable_awe < 0 || enable_awe > AWEQ_SCALE_ABSMAX) return AWEQ_ERR_SHAPE;
     if (mu_xhat && count == 0) return AWEQ_ERR_SHAPE;
     if (W) {
-        if (!W_hat) return AWEQ_ERR_NULL;
-        if (dt != AWEQ_F32 && dt != AWEQ_F16) return AWEQ_ERR_DTYPE;
-        if (N <= 0 || ldw < K || ldwh < K) return AWEQ_ERR_SHAPE;
-        if (!aligned16(W) || !aligned16(W_hat) || ((size_t)ldw * dtype_size(dt)) % 16 != 0 ||
-            ((size_t)ldwh * dtype_size(dt)) % 16 != 0)
-            return AWEQ_ERR_ALIGN;
+        const int rc = check_fold_args(W, W_hat, dt, N, K, ldw, ldwh);
+        if (rc != AWEQ_OK) return rc;
     }
     hipStream_t st = as_stream(stream);
     const bool range = xhat_range || act_step;

@@ -60,7 +60,8 @@ __device__ __forceinline__ float2 parts_extremes(const float* ext, int blocks, i
     return make_float2(lo, hi);
 }
 
-// W_hat = W s on checked arguments (equalize.hip)
+// W_hat = W s (equalize.hip): what the launch asks of its arguments, and the launch
+int check_fold_args(const void* W, const void* W_hat, aweq_dtype dt, int64_t N, int64_t K, int64_t ldw, int64_t ldwh);
 void launch_fold(const void* W, void* W_hat, aweq_dtype dt, int64_t N, int64_t K, int64_t ldw, int64_t ldwh, const float* s, hipStream_t st);
 
 }  // namespace aweq
