@@ -315,7 +315,7 @@ typedef struct {
     int64_t* colsum_xq;
     int enable_awe, enable_bc;
     int bits, group;            /* stage 3 */
-    int w8a8, forward;          /* int8 path (else weight-only); with the GEMM */
+    int w8a8, forward;          /* int8 path (8 bits, group 0 or -1; else weight-only); with the GEMM */
     int fused_weight_pass;      /* where the stages run one by one: aweq_fold_quant_weight (group = 0) */
     void* ws;
     size_t ws_bytes;

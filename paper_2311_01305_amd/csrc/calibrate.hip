@@ -390,5 +390,8 @@ extern "C" int aweq_calibrate(const aweq_calib_layer* layer, const aweq_calib_we
 {
     if (!layer || !weights) return AWEQ_ERR_NULL;
     if (n_weights < 1) return AWEQ_ERR_SHAPE;
+    // the int8 path multiplies 8-bit codes in K-panels, with one scale per output channel or per tensor
+    if (layer->w8a8 && layer->bits != 8) return AWEQ_ERR_BITS;
+    if (layer->w8a8 && layer->group != 0 && layer->group != -1) return AWEQ_ERR_GROUP;
     return aweq::run_calibration(*layer, weights, n_weights, stream);
 }

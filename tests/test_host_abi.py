@@ -275,3 +275,27 @@ def test_fused_gemm_argument_errors(B):
     assert _code(call, ws=None, ws_bytes=0) == "AWEQ_ERR_WORKSPACE"
     assert _code(call, next_inv_s=P + 4) == "AWEQ_ERR_ALIGN"
     assert _code(call, bias=P + 4) == "AWEQ_ERR_ALIGN"
+
+
+def _calibrate_call(B, n=1, **kw):
+    """aweq_calibrate with fake pointers, one field of the layer or of its weights replaced"""
+    layer = dict(X=P, dt=B.AWEQ_F16, T=64, K=64, ldx=64, xmin=P, xmax=P, xsum=P, count=P, r_x=P, R_x=P, p_x=P, wmin=P, wmax=P, wcount=P, r_w=P, R_w=P,
+                 p_w=P, s=P, inv_s=P, xhat_range=P, mu_xhat=P, act_step=P, act_zero=P, xq=P, rowsum_x=P, colsum_xq=P, enable_awe=1, enable_bc=1,
+                 bits=8, group=0, w8a8=1, forward=1, fused_weight_pass=0, ws=P, ws_bytes=16, status=None)
+    weight = dict(W=P, N=8, ldw=64, W_hat=P, ldwh=64, codes=P, step_w=P, zero_w=P, rowsum_w=P, bias_in=None, delta=P, bias_out=P, out_i32=P, out_deq=None,
+                  colsum_acc=P)
+    assert set(kw) <= set(layer) | set(weight)
+    layer.update((k, v) for k, v in kw.items() if k in layer)
+    weight.update((k, v) for k, v in kw.items() if k in weight)
+    return B.aweq_calibrate(tuple(layer.values()), [tuple(weight.values())] * n, 0)
+
+
+@pytest.mark.parametrize("n", [1, 2])
+@pytest.mark.parametrize("ws_bytes", [16, 1 << 24])
+def test_calibrate_int8_path_takes_its_formats_only(B, n, ws_bytes):
+    call = lambda **kw: _calibrate_call(B, n, ws_bytes=ws_bytes, **kw)
+    for forward in (0, 1):
+        assert _code(call, bits=4, forward=forward) == "AWEQ_ERR_BITS"
+        assert _code(call, bits=3, forward=forward) == "AWEQ_ERR_BITS"
+        assert _code(call, group=32, forward=forward) == "AWEQ_ERR_GROUP"
+        assert _code(call, group=-2, forward=forward) == "AWEQ_ERR_GROUP"
