@@ -393,5 +393,8 @@ extern "C" int aweq_calibrate(const aweq_calib_layer* layer, const aweq_calib_we
     // the int8 path multiplies 8-bit codes in K-panels, with one scale per output channel or per tensor
     if (layer->w8a8 && layer->bits != 8) return AWEQ_ERR_BITS;
     if (layer->w8a8 && layer->group != 0 && layer->group != -1) return AWEQ_ERR_GROUP;
+    // what the int8 path's bias correction reads, whichever route the call takes
+    for (int i = 0; layer->w8a8 && i < n_weights; ++i)
+        if (!weights[i].rowsum_w || (layer->forward && !weights[i].colsum_acc)) return AWEQ_ERR_NULL;
     return aweq::run_calibration(*layer, weights, n_weights, stream);
 }

@@ -299,3 +299,12 @@ def test_calibrate_int8_path_takes_its_formats_only(B, n, ws_bytes):
         assert _code(call, bits=3, forward=forward) == "AWEQ_ERR_BITS"
         assert _code(call, group=32, forward=forward) == "AWEQ_ERR_GROUP"
         assert _code(call, group=-2, forward=forward) == "AWEQ_ERR_GROUP"
+
+
+@pytest.mark.parametrize("n", [1, 2])
+@pytest.mark.parametrize("ws_bytes", [16, 1 << 24])
+def test_calibrate_null_arguments_do_not_depend_on_the_workspace(B, n, ws_bytes):
+    call = lambda **kw: _calibrate_call(B, n, ws_bytes=ws_bytes, **kw)
+    assert _code(call, rowsum_w=None) == "AWEQ_ERR_NULL"
+    assert _code(call, rowsum_w=None, forward=0) == "AWEQ_ERR_NULL"
+    assert _code(call, colsum_acc=None) == "AWEQ_ERR_NULL"
