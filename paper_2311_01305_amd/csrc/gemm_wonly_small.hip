@@ -42,12 +42,14 @@ constexpr int small_wave_lds(int rx, int nt) { return (rx == 4 ? 4 * 512 : rx * 
 // FEWER: quads of tokens past the edge are left out, by a branch around each load and write of four tokens.  Without those branches the
 // activations of the second half of a chunk are requested ahead of the next codes (loads return in order, and they are needed first); with them
 // that was slower (us, INT4: 13 tokens 16384 x 4096 12.2 -> 11.9, 32 tokens 16384 x 4096 15.4 -> 15.05, but 6 tokens 4096 x 16384 11.7 -> 12.1).
-// FINE: groups that are no multiple of 128 (a lane's 32 codes have one (Step, Z), but the four lanes that share
-// 128 values of a channel may differ)
-template <int BITS, int RX, int NT, int WAVES, bool FEWER, bool FINE, bool OUT_F16>
+// SCALES: kFine: groups that are no multiple of 128 (a lane's 32 codes have one (Step, Z), but the four lanes that share
+// 128 values of a channel may differ); kRagged: one (Step, Z) for a row or the tensor, and K ends inside such 128 values
+enum { kWhole, kRagged, kFine };
+template <int BITS, int RX, int NT, int WAVES, bool FEWER, int SCALES, bool OUT_F16>
 __global__ __launch_bounds__(WAVES * kWave) void gemm_small_kernel(SmallArgs g)
 {
     constexpr int TT = RX < 16 ? 1 : RX / 16;
+    constexpr bool FINE = SCALES == kFine;
     constexpr int XH = RX == 4 ? 1 : 2;             // activation loads per chunk: whole, or 128 values at a time
     constexpr int XL = RX == 4 ? 2 : 4 * TT;        // 16-byte loads of activations per lane and time
     constexpr bool kNatural = TT > NT;              // the operand with fewer tiles is the one that is brought to the other's order
@@ -213,6 +215,9 @@ __global__ __launch_bounds__(WAVES * kWave) void gemm_small_kernel(SmallArgs g)
                     s.set(__uint_as_float((uint32_t)__builtin_amdgcn_ds_bpermute((4 * r + h) * 4, (int)scc[j])),
                           __builtin_amdgcn_ds_bpermute((4 * r + 2 + h) * 4, (int)scc[j]));
                 }
+                // Past K the weights are zero too: one beyond binary16's range, which stands there again, would make NaN of a zero activation.
+                // (Selected in every launch it cost 1 - 3 %; where K is ragged one token 4096 x 4160 4.35 -> 4.40 us, 8 tokens INT3 11008 x 4160 9.5 -> 9.7)
+                if (SCALES != kWhole && kc + h * 128 + q * 32 >= K) { s.step = f16x2{(_Float16)0.0f, (_Float16)0.0f}; s.step_f = 0.0f; }
                 if (__all(s.packed)) {
 #pragma unroll
                     for (int d = 0; d < 4; ++d) {
@@ -301,16 +306,16 @@ __global__ __launch_bounds__(WAVES * kWave) void gemm_small_kernel(SmallArgs g)
 }
 
 template <int BITS, int RX, int NT, int WAVES, bool FEWER>
-static int launch_tile(const SmallArgs& g, bool fine, bool out_f16, hipStream_t st)
+static int launch_tile(const SmallArgs& g, int scales, bool out_f16, hipStream_t st)
 {
     constexpr int TT = RX < 16 ? 1 : RX / 16;
     const dim3 grid((unsigned)cdiv(g.N, 16 * NT), (unsigned)cdiv(g.T, RX));
     constexpr int work = WAVES * small_wave_lds(RX, NT), red = (WAVES < 8 ? 2 : 1) * WAVES * TT * NT * kWave * 16;
     constexpr int lds = work > red ? work : red;
-    const void* fn = fine ? (out_f16 ? reinterpret_cast<const void*>(gemm_small_kernel<BITS, RX, NT, WAVES, FEWER, true, true>)
-                                     : reinterpret_cast<const void*>(gemm_small_kernel<BITS, RX, NT, WAVES, FEWER, true, false>))
-                          : (out_f16 ? reinterpret_cast<const void*>(gemm_small_kernel<BITS, RX, NT, WAVES, FEWER, false, true>)
-                                     : reinterpret_cast<const void*>(gemm_small_kernel<BITS, RX, NT, WAVES, FEWER, false, false>));
+#define AWEQ_SF(S) (out_f16 ? reinterpret_cast<const void*>(gemm_small_kernel<BITS, RX, NT, WAVES, FEWER, S, true>) \
+                            : reinterpret_cast<const void*>(gemm_small_kernel<BITS, RX, NT, WAVES, FEWER, S, false>))
+    const void* fn = scales == kFine ? AWEQ_SF(kFine) : scales == kRagged ? AWEQ_SF(kRagged) : AWEQ_SF(kWhole);
+#undef AWEQ_SF
     int dev = 0, cus = 0;
     if (lds > 65536 && (device_cus(dev, cus) != AWEQ_OK || raise_lds_limit(fn, dev, lds) != AWEQ_OK)) return AWEQ_ERR_LAUNCH;
     void* args[] = {const_cast<SmallArgs*>(&g)};
@@ -335,7 +340,7 @@ SmallPlan plan_small(int64_t T, int64_t N)
 }
 
 template <int BITS>
-static int launch_bits(const SmallArgs& g, bool fine, int nt, bool out_f16, hipStream_t st)
+static int launch_bits(const SmallArgs& g, int scales, int nt, bool out_f16, hipStream_t st)
 {
     // Long rows on at most one workgroup per compute unit: K split between 16 wavefronts instead of 8, from two chunks a wavefront on (us, INT4,
     // 8 -> 16: one token 1024 x 22016 12.0 -> 10.7, 4096 x 11008 7.6 -> 7.1, 2048 x 8192 6.1 -> 5.9, 4096 x 4096 the same; 16 tokens 1024 x 22016
@@ -346,33 +351,33 @@ static int launch_bits(const SmallArgs& g, bool fine, int nt, bool out_f16, hipS
     // 16384 x 4096 (32 channels a workgroup before) 10.25 -> 10.1; 6 tokens 8704 x 4096 9.95 -> 9.2, 16 tokens 11008 x 4096 11.0 -> 10.8; but one
     // token 11008 x 11008 15.8 -> 16.5, INT3 16 tokens 11008 x 5120 12.6 -> 12.9, 6 tokens 16384 x 4096 11.4 -> 11.7)
     if (g.T <= 16 && cdiv(g.N, 16) > 512 && g.N <= (g.T <= 4 ? 16384 : 12288) && g.K <= (BITS == 4 ? 8192 : 4096))
-        return g.T <= 4 ? launch_tile<BITS, 4, 1, 4, false>(g, fine, out_f16, st) : g.T <= 12 ? launch_tile<BITS, 16, 1, 4, true>(g, fine, out_f16, st)
-                                                                                              : launch_tile<BITS, 16, 1, 4, false>(g, fine, out_f16, st);
+        return g.T <= 4 ? launch_tile<BITS, 4, 1, 4, false>(g, scales, out_f16, st) : g.T <= 12 ? launch_tile<BITS, 16, 1, 4, true>(g, scales, out_f16, st)
+                                                                                              : launch_tile<BITS, 16, 1, 4, false>(g, scales, out_f16, st);
     if (g.T <= 4) {
-        if (nt == 2) return launch_tile<BITS, 4, 2, 8, false>(g, fine, out_f16, st);
-        return lone && g.K >= 8192 ? launch_tile<BITS, 4, 1, 16, false>(g, fine, out_f16, st) : launch_tile<BITS, 4, 1, 8, false>(g, fine, out_f16, st);
+        if (nt == 2) return launch_tile<BITS, 4, 2, 8, false>(g, scales, out_f16, st);
+        return lone && g.K >= 8192 ? launch_tile<BITS, 4, 1, 16, false>(g, scales, out_f16, st) : launch_tile<BITS, 4, 1, 8, false>(g, scales, out_f16, st);
     }
     if (g.T <= 16) {
         if (g.T <= 12) {   // (8 tokens of 16: 11008 x 4096 INT4 10.45 / 10.7 us with / without the branches, 13 tokens 11.6 / 11.05)
-            if (nt == 2) return launch_tile<BITS, 16, 2, 8, true>(g, fine, out_f16, st);
-            return lone && g.K >= 16384 ? launch_tile<BITS, 16, 1, 16, true>(g, fine, out_f16, st) : launch_tile<BITS, 16, 1, 8, true>(g, fine, out_f16, st);
+            if (nt == 2) return launch_tile<BITS, 16, 2, 8, true>(g, scales, out_f16, st);
+            return lone && g.K >= 16384 ? launch_tile<BITS, 16, 1, 16, true>(g, scales, out_f16, st) : launch_tile<BITS, 16, 1, 8, true>(g, scales, out_f16, st);
         }
-        if (nt == 2) return launch_tile<BITS, 16, 2, 8, false>(g, fine, out_f16, st);
-        return lone && g.K >= 16384 ? launch_tile<BITS, 16, 1, 16, false>(g, fine, out_f16, st) : launch_tile<BITS, 16, 1, 8, false>(g, fine, out_f16, st);
+        if (nt == 2) return launch_tile<BITS, 16, 2, 8, false>(g, scales, out_f16, st);
+        return lone && g.K >= 16384 ? launch_tile<BITS, 16, 1, 16, false>(g, scales, out_f16, st) : launch_tile<BITS, 16, 1, 8, false>(g, scales, out_f16, st);
     }
     // Tokens left out or not, us: INT4 20 tokens 4096 x 4096 6.2 / 7.0, 24 tokens 8192 x 8192 15.05 / 15.6, 32 tokens 8192 x 8192 16.3 / 15.95;
     // 64 channels a workgroup: 24 tokens 16384 x 4096 15.7 / 14.95, INT3 17 tokens 11008 x 4096 13.9 / 14.3
     const bool fewer = g.T <= 24 && (nt <= 2 || BITS == 3);
-    if (fewer) return nt == 1 ? launch_tile<BITS, 32, 1, 8, true>(g, fine, out_f16, st) : nt == 2 ? launch_tile<BITS, 32, 2, 8, true>(g, fine, out_f16, st)
-                                                                                                 : launch_tile<BITS, 32, 4, 8, true>(g, fine, out_f16, st);
-    return nt == 1 ? launch_tile<BITS, 32, 1, 8, false>(g, fine, out_f16, st) : nt == 2 ? launch_tile<BITS, 32, 2, 8, false>(g, fine, out_f16, st)
-                                                                                        : launch_tile<BITS, 32, 4, 8, false>(g, fine, out_f16, st);
+    if (fewer) return nt == 1 ? launch_tile<BITS, 32, 1, 8, true>(g, scales, out_f16, st) : nt == 2 ? launch_tile<BITS, 32, 2, 8, true>(g, scales, out_f16, st)
+                                                                                                 : launch_tile<BITS, 32, 4, 8, true>(g, scales, out_f16, st);
+    return nt == 1 ? launch_tile<BITS, 32, 1, 8, false>(g, scales, out_f16, st) : nt == 2 ? launch_tile<BITS, 32, 2, 8, false>(g, scales, out_f16, st)
+                                                                                        : launch_tile<BITS, 32, 4, 8, false>(g, scales, out_f16, st);
 }
 
 int launch_small(const SmallArgs& g, int bits, int group, const SmallPlan& p, bool out_f16, hipStream_t st)
 {
-    const bool fine = group > 0 && group % 128 != 0;
-    return bits == 4 ? launch_bits<4>(g, fine, p.nt, out_f16, st) : launch_bits<3>(g, fine, p.nt, out_f16, st);
+    const int scales = group > 0 && group % 128 != 0 ? kFine : g.K % 128 != 0 ? kRagged : kWhole;
+    return bits == 4 ? launch_bits<4>(g, scales, p.nt, out_f16, st) : launch_bits<3>(g, scales, p.nt, out_f16, st);
 }
 
 }  // namespace wonly

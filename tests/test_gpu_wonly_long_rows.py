@@ -65,3 +65,33 @@ def test_an_infinite_activation_stays_in_its_token(B, orc):
         assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isposinf(got), np.isposinf(ref))
         keep = [t for t in range(T) if t not in (1, 2)]
         assert np.all(np.abs(got[keep] - ref[keep]) <= K * 2.0 ** -24 * (np.abs(X[keep].astype(np.float64)) @ np.abs(Wh).T))
+
+
+@pytest.mark.parametrize("bits", [4, 3])
+@pytest.mark.parametrize("K,group", [(192, 0), (192, 64), (64, 32), (320, 0), (8192 + 64, 0)])
+def test_an_infinite_weight_is_not_met_by_the_zeros_past_k(B, bits, K, group):
+    """A weight beyond binary16's range is infinite as a GEMM operand.  Among the last values of K, which stand in for the ones past it, it
+    is multiplied with its activation only: an infinite output, not the NaN of infinity times zero."""
+    N, top, zero = 20, 2 ** bits - 1, 3
+    rng = np.random.default_rng(K + bits)
+    step = np.float32(65504 // (top - 1 - zero) // 64 * 64)   # (a binary16 value)  the highest code is beyond the range, the others are not
+    u = rng.integers(0, top, (N, K)).astype(np.uint8)
+    u[5, K - 1] = u[9, K - 17] = top
+    packed = np.packbits(np.unpackbits(u[..., None], axis=-1, bitorder="little")[..., :bits].reshape(N, K * bits), axis=-1, bitorder="little").reshape(-1)
+    ng = N * (K // group) if group else N
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+    codes, steps, zeros = dev(packed), torch.full((ng,), float(step), device=DEV), torch.full((ng,), zero, dtype=torch.int32, device=DEV)
+    with np.errstate(over="ignore"):
+        Wh = ((u.astype(np.float32) - zero) * step).astype(np.float16).astype(np.float64)
+    assert np.isinf(Wh).sum() == 2
+    ws = torch.empty(B.aweq_workspace_size(B.OP_WONLY_GEMM, 1, K, N), dtype=torch.uint8, device=DEV)
+    for T in (1, 4, 5, 12, 13, 16, 17, 25, 40, 64):
+        print(f"[gpu-wonly-inf] W{bits} T={T} K={K} g={group}", flush=True)
+        X = (np.abs(rng.standard_normal((T, K))) + 0.01).astype(np.float16)
+        out = torch.empty(T, N, dtype=torch.float32, device=DEV)
+        B.aweq_wonly_gemm(dev(X), T, K, K, codes, bits, group, steps, zeros, N, None, out, B.AWEQ_F32, N, ws)
+        torch.cuda.synchronize()
+        got, ref = out.cpu().numpy(), X.astype(np.float64) @ Wh.T
+        assert np.array_equal(np.isposinf(got), np.isposinf(ref)) and not np.isnan(got).any(), T
+        ok = np.isfinite(ref)
+        assert np.all(np.abs(got[ok] - ref[ok]) <= (K * 2.0 ** -24 * (np.abs(X.astype(np.float64)) @ np.where(np.isinf(Wh), 0, np.abs(Wh)).T))[ok]), T
