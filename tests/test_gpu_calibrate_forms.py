@@ -26,6 +26,11 @@ def _e(*shape, dtype=F32):
     return torch.full(shape, GUARD, dtype=dtype, device=DEV)
 
 
+def _copy(W):
+    out = W.new_empty(W.shape[0], W.stride(0))[:, :W.shape[1]]   # with its pitch
+    return out.copy_(W)
+
+
 class Call:
     """Buffers of one call.  codes, Step and Z are longer than the call needs them: what lies behind has to stay."""
 
@@ -33,7 +38,7 @@ class Call:
         self.__dict__.update(B=B, X=X, biases=biases, bits=bits, group=group, w8a8=w8a8, forward=forward, awe=awe, bc=bc, nulls=nulls)
         T, K = X.shape
         self.T, self.K, self.dt = T, K, B.AWEQ_F16 if X.dtype == F16 else B.AWEQ_F32
-        self.Ws = [W.clone() if in_place else W for W in Ws]
+        self.Ws = [_copy(W) if in_place else W for W in Ws]
         v = {n: _e(K) for n in ("xmin", "xmax", "r_x", "p_x", "wmin", "wmax", "r_w", "p_w", "s", "inv_s", "mu_xhat")}
         v.update(xsum=_e(K, dtype=torch.float64), count=_e(1, dtype=I64), wcount=_e(1, dtype=I64), R_x=_e(1), R_w=_e(1), xhat_range=_e(2),
                  act_step=_e(1), act_zero=_e(1, dtype=I32), status=torch.zeros(1, dtype=I32, device=DEV))
@@ -161,3 +166,88 @@ def _check(B, X, Ws, biases, bits, group, w8a8, forward, **options):
 def test_several_weights(B, dtype, bits, group, w8a8, forward):
     """Weights of one input in slices of every kind: each has scales of its own."""
     _check(B, *_inputs(dtype, 70, (5, 12, 3), 640), bits, group, w8a8, forward)
+
+
+FORMS = [(8, 0, True, True), (8, 0, True, False), (4, 128, False, False), (3, 32, False, False), (8, -1, True, False)]
+SHAPES = [(33, (5,), 640), (70, (9, 3), 1032), (40, (6,), 4224), (50, (7,), 8200)]   # whole 128-byte lines and not; a wavefront to a row and more
+
+
+def _fits(K, bits, group):
+    return group <= 0 or K % group == 0
+
+
+@pytest.mark.parametrize("dtype", [F16, F32])
+@pytest.mark.parametrize("form", FORMS)
+@pytest.mark.parametrize("T,Ns,K", SHAPES)
+def test_folded_weight_in_its_weights_place(B, dtype, form, T, Ns, K):
+    if _fits(K, *form[:2]):
+        for pitched in (False, True):
+            _check(B, *_inputs(dtype, T, Ns, K, pitched), *form, in_place=True)
+
+
+@pytest.mark.parametrize("form", FORMS)
+@pytest.mark.parametrize("options", [dict(awe=0), dict(awe=2), dict(bc=0), dict(nulls=("count", "wcount", "p_x", "p_w", "status"))], ids=str)
+def test_options(B, form, options):
+    X, Ws, biases = _inputs(F16, 45, (5, 9), 1152)
+    for b in (biases, [None, None]):
+        _check(B, X, Ws, b, *form, **options)
+
+
+def _wide_zero_points(X, Ws):
+    Ws[0][1] += 60.0           # a row, a stretch of one far from zero: |Z| beyond what the quotient without a division takes
+    Ws[0][2, 128:384] -= 30.0
+    X += 50.0
+
+
+def _degenerate(X, Ws):
+    Ws[0][0] = 0.0
+    Ws[0][1] = 0.25
+    Ws[0][2, 128:384] = 0.0
+    Ws[0][3, 128:384] = -0.0
+    for W in Ws:
+        W[:, 7] = 0.0
+        W[:, 11] = 3.0
+    X[:, 9] = 0.0
+    X[:, 13] = -2.0
+
+
+def _tiny(X, Ws):
+    Ws[0][1] *= 2.0**-12       # (binary16: below its normal numbers)
+    Ws[0][2] = 0.0
+    Ws[0][2, 40] = 2.0**-24
+
+
+def _huge(X, Ws):
+    Ws[0][1, ::2] = 60000.0
+    Ws[0][1, 1::2] = -60000.0
+    X[3, 5] = 60000.0
+
+
+def _infinite_weight(X, Ws):
+    Ws[0][1, 20] = float("inf")
+    Ws[-1][2, 300] = float("-inf")
+
+
+def _nan_weight(X, Ws):
+    Ws[0][1, 20] = float("nan")
+    Ws[-1][2] = float("nan")
+
+
+def _nonfinite_activation(X, Ws):
+    X[3, 20] = float("inf")
+    X[5, 40] = float("nan")
+    X[:, 41] = float("nan")
+
+
+@pytest.mark.parametrize("dtype", [F16, F32])
+@pytest.mark.parametrize("form", FORMS)
+@pytest.mark.parametrize("values", [_wide_zero_points, _degenerate, _tiny, _huge, _infinite_weight, _nan_weight, _nonfinite_activation])
+@pytest.mark.parametrize("K", [1152, 8320])
+def test_values(B, dtype, form, values, K):
+    """Rows, groups and columns without a range, far from zero, near either end of the type's range, with infinities and NaN: the same
+    codes, scales and status."""
+    print(f"[calibrate forms] {values.__name__}", flush=True)
+    X, Ws, biases = _inputs(dtype, 45, (6, 5), K)
+    values(X, Ws)
+    for awe in (1, 0):
+        _check(B, X, Ws, biases, *form, awe=awe)
