@@ -87,6 +87,12 @@ struct Fields {
         ++at;
         return *this;
     }
+    // every field has been taken (the count is what there is to check a structure's layout by)
+    bool done()
+    {
+        if (ok && at != PySequence_Fast_GET_SIZE(seq)) { PyErr_Format(PyExc_TypeError, "%zd fields instead of %zd", PySequence_Fast_GET_SIZE(seq), at); ok = false; }
+        return ok;
+    }
 };
 
 PyObject* call_aweq_calibrate(PyObject*, PyObject* const* o, Py_ssize_t n)
@@ -98,7 +104,7 @@ PyObject* call_aweq_calibrate(PyObject*, PyObject* const* o, Py_ssize_t n)
     f >> l.X >> l.dt >> l.T >> l.K >> l.ldx >> l.xmin >> l.xmax >> l.xsum >> l.count >> l.r_x >> l.R_x >> l.p_x >> l.wmin >> l.wmax >> l.wcount >> l.r_w >>
         l.R_w >> l.p_w >> l.s >> l.inv_s >> l.xhat_range >> l.mu_xhat >> l.act_step >> l.act_zero >> l.xq >> l.rowsum_x >> l.colsum_xq >>
         l.enable_awe >> l.enable_bc >> l.bits >> l.group >> l.w8a8 >> l.forward >> l.fused_weight_pass >> l.ws >> l.ws_bytes >> l.status;
-    if (!f.ok) return nullptr;
+    if (!f.done()) return nullptr;
     PyObject* const members = PySequence_Fast(o[1], "a sequence of weights");
     if (!members) return nullptr;
     const Py_ssize_t count = PySequence_Fast_GET_SIZE(members);
@@ -112,7 +118,7 @@ PyObject* call_aweq_calibrate(PyObject*, PyObject* const* o, Py_ssize_t n)
         Fields m(PySequence_Fast_GET_ITEM(members, i));
         m >> w[i].W >> w[i].N >> w[i].ldw >> w[i].W_hat >> w[i].ldwh >> w[i].codes >> w[i].step_w >> w[i].zero_w >> w[i].rowsum_w >> w[i].bias_in >>
             w[i].delta >> w[i].bias_out >> w[i].out_i32 >> w[i].out_deq >> w[i].colsum_acc;
-        ok = m.ok;
+        ok = m.done();
     }
     if (ok && convert(o[2], stream)) {
         int rc;

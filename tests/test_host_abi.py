@@ -277,7 +277,7 @@ def test_fused_gemm_argument_errors(B):
     assert _code(call, bias=P + 4) == "AWEQ_ERR_ALIGN"
 
 
-def _calibrate_call(B, n=1, **kw):
+def _calibrate_call(B, n=1, more_layer=(), more_weight=(), **kw):
     """aweq_calibrate with fake pointers, one field of the layer or of its weights replaced"""
     layer = dict(X=P, dt=B.AWEQ_F16, T=64, K=64, ldx=64, xmin=P, xmax=P, xsum=P, count=P, r_x=P, R_x=P, p_x=P, wmin=P, wmax=P, wcount=P, r_w=P, R_w=P,
                  p_w=P, s=P, inv_s=P, xhat_range=P, mu_xhat=P, act_step=P, act_zero=P, xq=P, rowsum_x=P, colsum_xq=P, enable_awe=1, enable_bc=1,
@@ -287,7 +287,7 @@ def _calibrate_call(B, n=1, **kw):
     assert set(kw) <= set(layer) | set(weight)
     layer.update((k, v) for k, v in kw.items() if k in layer)
     weight.update((k, v) for k, v in kw.items() if k in weight)
-    return B.aweq_calibrate(tuple(layer.values()), [tuple(weight.values())] * n, 0)
+    return B.aweq_calibrate(tuple(layer.values()) + more_layer, [tuple(weight.values()) + more_weight] * n, 0)
 
 
 @pytest.mark.parametrize("n", [1, 2])
@@ -308,3 +308,14 @@ def test_calibrate_null_arguments_do_not_depend_on_the_workspace(B, n, ws_bytes)
     assert _code(call, rowsum_w=None) == "AWEQ_ERR_NULL"
     assert _code(call, rowsum_w=None, forward=0) == "AWEQ_ERR_NULL"
     assert _code(call, colsum_acc=None) == "AWEQ_ERR_NULL"
+
+
+def test_calibrate_counts_the_fields(B):
+    """A field too many or too few would shift the pointers behind it."""
+    for more in (dict(more_layer=(0,)), dict(more_weight=(None,))):
+        with pytest.raises(TypeError, match="fields instead of"):
+            _calibrate_call(B, bits=4, **more)
+    with pytest.raises(TypeError, match="a field is missing"):
+        B.aweq_calibrate((P,) * 36, [(P,) * 15], 0)
+    with pytest.raises(TypeError, match="a field is missing"):
+        B.aweq_calibrate((P,) * 37, [(P,) * 14], 0)
