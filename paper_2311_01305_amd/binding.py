@@ -1,7 +1,7 @@
 """Binding of libaweq.so: same names and argument order as include/aweq.h.
 
-Argument marshalling only, by the extension module _native.so (host functions: ctypes).  Tensor arguments are torch tensors living on the GPU (or None
-for a nullable pointer); their data_ptr() is handed to the library, and the current torch
+Argument marshalling only, by the extension module _native (host functions: ctypes).  Tensor arguments are torch tensors
+living on the GPU (or None for a nullable pointer); their data_ptr() is handed to the library, and the current torch
 stream is passed unless `stream` is given.  PyTorch is used for device memory and streams
 only.  Raw integer addresses are accepted in place of tensors (used by host-side tests).
 """
@@ -12,7 +12,7 @@ import os
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libaweq.so")
-_NATIVE_PATH = os.path.join(_HERE, "_native.so")
+_NATIVE_PATH = os.path.join(_HERE, "_native" + importlib.machinery.EXTENSION_SUFFIXES[0])   # (the suffix that names this interpreter)
 _lib = None
 _calls = None    # the extension module, bound to the library
 _torch = None

@@ -1,4 +1,4 @@
-"""Build libaweq.so (hand-written HIP for gfx950) in-tree with hipcc, and _native.so (its calls from Python) with g++.
+"""Build libaweq.so (hand-written HIP for gfx950) in-tree with hipcc, and _native (its calls from Python) with g++.
 
 hipcc cross-compiles without a GPU.  Flags: no FMA contraction (the quantizer's fp32
 steps are single IEEE operations), no packed-fp32 instructions.
@@ -13,7 +13,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libaweq.so")
-NATIVE = os.path.join(HERE, "_native.so")   # the Python side of the calls
+# the Python side of the calls: for one interpreter version, which the name says, so that another one does not take it for its own
+NATIVE = os.path.join(HERE, "_native" + sysconfig.get_config_var("EXT_SUFFIX"))
 SOURCES = ["api.hip", "stats.hip", "equalize.hip", "quant_weight.hip", "quant_act.hip", "gemm_i8.hip", "gemm_i8_few.hip", "gemm_i8_mid.hip", "gemm_wonly.hip", "gemm_wonly_small.hip", "gemm_wonly_mid.hip", "bias.hip", "weight_pass.hip", "calibrate.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

@@ -319,3 +319,14 @@ def test_calibrate_counts_the_fields(B):
         B.aweq_calibrate((P,) * 36, [(P,) * 15], 0)
     with pytest.raises(TypeError, match="a field is missing"):
         B.aweq_calibrate((P,) * 37, [(P,) * 14], 0)
+
+
+def test_extension_module_is_named_for_its_interpreter(B):
+    """Without the interpreter's tag another version would load a module that was built for a different one."""
+    import sysconfig
+
+    from paper_2311_01305_amd import build
+    suffix = sysconfig.get_config_var("EXT_SUFFIX")
+    assert "cpython" in suffix and build.NATIVE == B._NATIVE_PATH == os.path.join(ROOT, "paper_2311_01305_amd", "_native" + suffix)
+    maps = open("/proc/self/maps").read()
+    assert B._NATIVE_PATH in maps and "_native.so" not in maps
