@@ -31,8 +31,8 @@ bool convert(PyObject* o, T& v)
         if (a == (unsigned long long)-1 && PyErr_Occurred()) return false;
         v = reinterpret_cast<T>((uintptr_t)a);
     } else {
-        const long long a = PyLong_AsLongLong(o);
-        if (a == -1 && PyErr_Occurred()) return false;
+        const unsigned long long a = PyLong_AsUnsignedLongLongMask(o);   // (the low bits, whatever the integer's sign and size: as ctypes converts)
+        if (a == (unsigned long long)-1 && PyErr_Occurred()) return false;
         v = (T)a;
     }
     return true;

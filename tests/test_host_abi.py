@@ -330,3 +330,16 @@ def test_extension_module_is_named_for_its_interpreter(B):
     assert "cpython" in suffix and build.NATIVE == B._NATIVE_PATH == os.path.join(ROOT, "paper_2311_01305_amd", "_native" + suffix)
     maps = open("/proc/self/maps").read()
     assert B._NATIVE_PATH in maps and "_native.so" not in maps
+
+
+def test_integers_are_converted_as_ctypes_does(B):
+    """The whole range of a 64-bit count, and the low bits of anything larger; floats and texts are refused."""
+    ok = dict(xmin=P, xmax=P, xsum=P, wmin=P, wmax=P, K=12, enable_awe=1, s=P, inv_s=P, W=None, W_hat=None, dt=B.AWEQ_F16, N=0, ldw=0, ldwh=0,
+              prev_scale=None, xhat_range=P, mu_xhat=P, act_step=P, act_zero=P)
+    for count in (2 ** 63, 2 ** 64 - 1, 2 ** 70, -1):
+        assert _code(B.aweq_equalize, count=count, **ok) == "AWEQ_ERR_SHAPE"     # (K = 12)
+    assert _code(B.aweq_equalize, count=2 ** 64, **{**ok, "K": 64}) == "AWEQ_ERR_SHAPE"   # (a count of 0)
+    with pytest.raises(TypeError):
+        B.aweq_equalize(count=1, **{**ok, "K": 64.0})
+    with pytest.raises(TypeError):
+        B.aweq_equalize(count=1, **{**ok, "K": "64"})
