@@ -215,11 +215,33 @@ __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
             row_sum(rs, row, row_ok);
         }
     };
+    // Whole groups one at a time, the next one on its way, for |Z| beyond the screen: its quotient takes the registers of the second group,
+    // and more would cost a wavefront everywhere (us, Z = 6000, 16384 x 11008, one group requested once the last was done -> this: codes and
+    // sums 134 -> 115, codes 132 -> 114, sums alone 100 -> 80).
+    auto whole_rows = [&](auto mode_c) {
+#pragma unroll 1
+        for (int g = 0; g < ring_groups; ++g) {
+            RawUnit<F16> u[kQaVpt];
+#pragma unroll
+            for (int j = 0; j < kQaVpt; ++j) u[j] = raw[0][j];
+            request(0, min(g + 1, ring_groups - 1));
+            const int row = 8 * g + rsub;
+            int rs = 0;
+#pragma unroll
+            for (int j = 0; j < kQaVpt; ++j) unit(mode_c, u[j], j, dst0 ? dst0 + j * dst_step + row * kPanel : nullptr, rs);
+            row_sum(rs, row, true);
+        }
+        my_rows += ring_groups;
+        first = 8 * ring_groups;
+    };
     if constexpr (F16) {
         if (screen) {
             if (whole) ring(std::integral_constant<int, 2>{});
             rest(std::integral_constant<int, 2>{});
-        } else if (fast) rest(std::integral_constant<int, 1>{});
+        } else if (fast) {
+            if (whole) whole_rows(std::integral_constant<int, 1>{});
+            rest(std::integral_constant<int, 1>{});
+        }
         else rest(std::integral_constant<int, 0>{});
     } else {
         if (screen) {

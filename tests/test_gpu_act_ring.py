@@ -19,13 +19,14 @@ def B():
     return binding
 
 
-def _check(B, orc, dtype, T, K, codes, rowsum, colsum, shift):
+def _check(B, orc, dtype, T, K, codes, rowsum, colsum, shift, step=0.041, zero=117):
     from conftest import from_panels
     print(f"[gpu-act-ring] {dtype.__name__} T={T} K={K} codes={codes} rowsum={rowsum} colsum={colsum}", flush=True)
     rng = np.random.default_rng(T * 31 + K)
-    X = (rng.standard_normal((T, K + 8)) * 2).astype(dtype)     # a pitched view
-    inv_s = rng.uniform(0.4, 1.6, K).astype(np.float32)
-    step, zero = np.float32(0.041), 117
+    wide = abs(zero) > 4096
+    X = (rng.standard_normal((T, K + 8)) * 2 + ((128 - zero) * step if wide else 0.0)).astype(dtype)     # a pitched view
+    inv_s = rng.uniform(*((0.9999, 1.0001) if wide else (0.4, 1.6)), K).astype(np.float32)
+    step = np.float32(step)
     a = orc.quant_act(np.ascontiguousarray(X[:, :K]), inv_s, step, zero)
     dev = lambda v: torch.from_numpy(np.ascontiguousarray(v)).to(DEV)
     inv = torch.zeros(K + 4, dtype=torch.float32, device=DEV)[shift:shift + K]
@@ -57,3 +58,14 @@ def test_panel_form(B, orc, dtype, T, K):
 @pytest.mark.parametrize("T,K", [(1, 8), (3, 4088), (5, 4096), (257, 4104), (1027, 520), (2, 8200), (4097, 2040), (4097, 2048), (6, 12288)])
 def test_row_form(B, orc, dtype, T, K):
     _check(B, orc, dtype, T, K, True, True, False, 0)
+
+
+@pytest.mark.parametrize("zero", [6000, -6000, 1 << 21])
+@pytest.mark.parametrize("T,K", [(3, 4096), (15, 128), (16, 128), (17, 256), (40, 1032), (70, 512), (513, 1152), (4097, 640)])
+def test_zero_points_beyond_the_screen(B, orc, zero, T, K):
+    """Quotients that need the exact form: whole groups of rows one at a time, and what the ring leaves over."""
+    step = 0.041 if abs(zero) < 10000 else 0.0041   # (inputs within binary16)
+    for dtype in (np.float16, np.float32):
+        _check(B, orc, dtype, T, K, True, True, True, 0, step, zero)
+        _check(B, orc, dtype, T, K, False, False, True, 1, step, zero)
+        _check(B, orc, dtype, T, K, True, True, False, 0, step, zero)
