@@ -100,9 +100,17 @@ __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
 #pragma unroll
         for (int j = 0; j < kQaVpt; ++j) raw[b][j].load(src0, (int64_t)(8 * group + rsub) * ldx + j * kPanel);
     };
+    // binary16, any rows and columns (binary32 has no registers for it: 65536 x 64 11.1 -> 11.8 us)
+    auto request_any = [&](int row) {
+#pragma unroll
+        for (int j = 0; j < kQaVpt; ++j)
+            if (row < nrows && valid[j]) raw[0][j].load(src0, (int64_t)row * ldx + j * kPanel);
+    };
     if (whole) {
 #pragma unroll
         for (int b = 0; b < kRing; ++b) request(b, b);
+    } else if (F16) {
+        request_any(rsub);
     }
 
     uint32_t st = 0;
@@ -193,18 +201,21 @@ __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
         my_rows += ring_groups;
         first = 8 * ring_groups;
     };
-    // any rows and columns, one group of 8 rows at a time
+    // any rows and columns, one group of 8 rows at a time, binary16 with the next one on its way (20000 x 120 7.8 -> 6.9 us)
     auto rest = [&](auto mode_c) {
+        if (F16 && first > 0) request_any(first + rsub);
+#pragma unroll 1
         for (int rb = first; rb < nrows; rb += 8) {
             const int row = rb + rsub;
             const bool row_ok = row < nrows;
+            if (!F16) request_any(row);
+            RawUnit<F16> u[kQaVpt];
+#pragma unroll
+            for (int j = 0; j < kQaVpt; ++j) u[j] = raw[0][j];
+            if (F16) request_any(row + 8);
             int rs = 0;
             if (row_ok) {
                 ++my_rows;
-                RawUnit<F16> u[kQaVpt];
-#pragma unroll
-                for (int j = 0; j < kQaVpt; ++j)
-                    if (valid[j]) u[j].load(src0, (int64_t)row * ldx + j * kPanel);
 #pragma unroll
                 for (int j = 0; j < kQaVpt; ++j) {
                     int8_t* const d = dst0 ? dst0 + j * dst_step + row * kPanel : nullptr;
