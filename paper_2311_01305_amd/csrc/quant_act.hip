@@ -364,8 +364,10 @@ __global__ __launch_bounds__(kQrBlock) void quant_act_rows(
         isa = *reinterpret_cast<const Float4*>(q);
         isb = *reinterpret_cast<const Float4*>(q + 4);
     };
+    if ((int64_t)(threadIdx.x & ~(kWave - 1u)) < units) {   // (short rows leave wavefronts without a unit: binary32 2048 x 1032 4.8 -> 4.45 us)
 #pragma unroll
-    for (int i = 0; i < ROWS; ++i) request(i, threadIdx.x);
+        for (int i = 0; i < ROWS; ++i) request(i, threadIdx.x);
+    }
     request_is(threadIdx.x);
     const ActParams p = quot_params(*act_step, *act_zero);
     uint32_t st = 0;
