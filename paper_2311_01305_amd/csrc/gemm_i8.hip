@@ -302,8 +302,11 @@ template <int MI, bool I32, int DEQ, bool COLSUM, int EPI = 0, bool STORE = true
 __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
 {
     using TL = Tile<MI>;
-    // (the statistics epilogue, and the quantising one that also stores 256-token tiles, have the general form only: no registers left)
-    constexpr bool kQuick = EPI == 0 || (EPI == 2 && !(STORE && MI == 4));
+    // The epilogue's short forms.  Not with the accumulators among the outputs, which the general form stores as fast or faster (us, short ->
+    // general: 3515 tokens 4468 x 2008 with sums 50.4 -> 48.5, 5000 x 2500 x 1000 with sums 31.3 -> 30.2, with binary16 output too 46.3 -> 44.2,
+    // 4096 x 4096 x 4096 with sums 68.2 -> 67.6); the statistics epilogue, and the quantising one that also stores 256-token tiles, have no
+    // registers left.
+    constexpr bool kQuick = EPI == 0 ? !I32 : EPI == 2 && !(STORE && MI == 4);
     constexpr int kUnroll = kQuick ? 1 : 8;
     constexpr int kSlot = TL::kSlot, kHalfA = TL::kHalfA, kAhead = TL::kAhead, kLoads = TL::kLoads;
     extern __shared__ __attribute__((aligned(1024))) char lds[];
@@ -606,7 +609,8 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
                 for (int c = 0; c < 4; ++c) odd = odd || nzw[c] >= (1 << 23) || nzw[c] <= -(1 << 23);
             }
             const bool inside = cm0 + TL::kRows <= g.T && cn0 + BN <= g.N;
-            if (__builtin_amdgcn_ballot_w64(odd && n_ok) == 0 && g.ldo < (1 << 28) && (!COLSUM || g.K < 32768)) form = inside ? kPlain : kEdge;
+            if (__builtin_amdgcn_ballot_w64(odd && n_ok) == 0 && g.ldo < (1 << 28) && (!COLSUM || g.K < 32768))
+                form = inside ? kPlain : kEdge;
         }
 
         // per-channel constants of the de-quantisation
@@ -631,9 +635,8 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
         int rsy_kept[MI / 2] = {};               // row sums of the next layer's codes: one per lane and 64 tokens
         float cqf[4] = {0.f, 0.f, 0.f, 0.f};     // column sums of the next layer's unsigned codes over this tile (exact: 32 rows)
         const bool yq_pad = (EPI & 2) != 0 && !n_ok && cn0 + wn * 64 < g.N;   // zero fill of the last panel
-        // kPlain / kEdge: wave-uniform row pointers that move on by four tokens, the lane's offset from them, its tokens inside
+        // the short forms: wave-uniform row pointers that move on by four tokens, the lane's offset from them, its tokens inside
         const int64_t wave_t = cm0 + wm * (32 * MI), wave_n = cn0 + wn * 64;
-        char* row_i32 = I32 ? reinterpret_cast<char*>(g.out_i32 + wave_t * g.ldo + wave_n) : nullptr;
         char* row_deq = DEQ != 0 && STORE ? reinterpret_cast<char*>(g.out_deq) + (wave_t * g.ldo + wave_n) * (DEQ == 1 ? 4 : 2) : nullptr;
         char* row_yq = (EPI & 2) != 0 ? reinterpret_cast<char*>(g.yq) + ((wave_n >> 6) * g.T + wave_t) * kPanel : nullptr;
         const uint32_t lane_yq = (uint32_t)(rd_r * (int)kPanel + rd_c * 4);
@@ -684,42 +687,32 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
         };
         auto row_sum_of = [&](int i, int p) { return __builtin_amdgcn_ds_bpermute(((i & 1) * 32 + 4 * p) * 4 + rd_r * 4, rsx[i >> 1]); };
         auto slab_row = [&](int p) { return *reinterpret_cast<const v4i*>(slab + (4 * p + rd_r) * 256 + ((rd_c ^ (4 * (p & 3) + rd_r)) * 16)); };
-        // The eight passes over sub-tile row i of the plain and the edge form.  A tile's epilogue is vector operations of 4.5 cycles each
+        // The eight passes over sub-tile row i of the short forms.  A tile's epilogue is vector operations of 4.5 cycles each
         // with nothing multiplying meanwhile (the two wavefronts of a SIMD arrive together): 6 per output of a binary16 result, 14 with the
         // next layer's codes and the sums, where the general form takes 12 and 20 and waits for the LDS in every pass.  Shorter by: the
         // 24-bit multiply without its check, addresses that are a scalar and one offset, sums in 32 bits and in packed bytes, row sums two
         // tokens to a word, divisions for near ties afterwards.  (us, general form -> these: two layers 4096 -> 16384 -> 4096 of 4096
         // tokens 466 -> 449, three layers 4096 x 4096 of 8192 tokens inside their calibration 437 -> 418, the 128-token tiles of
-        // 2048 tokens 4096 x 11008 89.3 -> 88.3, 262144 tokens 8192 x 8192 with both outputs and sums 14.55 -> 14.49 ms.)
-        auto short_rows = [&](int i, auto edge_c) {
-            constexpr bool EDGE = decltype(edge_c)::value;
+        // 2048 tokens 4096 x 11008 89.3 -> 88.3.)
+        auto short_rows = [&](int i, auto form_c) {
+            constexpr bool EDGE = decltype(form_c)::value == kEdge;
             uint32_t redo = 0;
             int rsy_even = 0;
-            // a pass's accumulators and row sum are requested one pass ahead (where there are registers for it)
-            constexpr bool kNext = MI == 2 || !(I32 && DEQ == 1 && COLSUM);
-            v4i next_o = {};
-            int next_rs = 0;
-            if constexpr (kNext) {
-                next_o = slab_row(0);
-                if constexpr (DEQ != 0) next_rs = row_sum_of(i, 0);
-            }
+            // a pass's accumulators and row sum are requested one pass ahead
+            v4i next_o = slab_row(0);
+            int next_rs = DEQ != 0 ? row_sum_of(i, 0) : 0;
 #pragma unroll 1
             for (int p4 = 0; p4 < 8; p4 += 4)
 #pragma unroll
             for (int p_ = 0; p_ < 4; ++p_) {
                 const int p = p4 + p_;
-                const int pn = !kNext ? p : p_ < 3 ? p + 1 : (p4 + 4) & 7;   // (after the last one: the first again, not used)
-                v4i o = next_o;
-                int rs = next_rs;
-                next_o = *reinterpret_cast<const v4i*>(slab + pn * 1024 + (rd_r * 256 + ((rd_c ^ (4 * ((kNext ? p_ + 1 : p_) & 3) + rd_r)) * 16)));
+                const int pn = p_ < 3 ? p + 1 : (p4 + 4) & 7;   // (after the last one: the first again, not used)
+                const v4i o = next_o;
+                const int rs = next_rs;
+                next_o = *reinterpret_cast<const v4i*>(slab + pn * 1024 + (rd_r * 256 + ((rd_c ^ (4 * ((p_ + 1) & 3) + rd_r)) * 16)));
                 if constexpr (DEQ != 0) next_rs = row_sum_of(i, pn);
-                if constexpr (!kNext) { o = next_o; rs = next_rs; }
                 SB();
                 const bool in = !EDGE || i * 32 + 4 * p < lim;
-                if constexpr (I32) {
-                    if (in) __builtin_nontemporal_store(o, reinterpret_cast<v4i*>(row_i32 + (uint64_t)(lane_elt * 4u)));
-                    row_i32 += 16 * g.ldo;
-                }
                 if constexpr (DEQ != 0) {
                     float y[4];
                     dequantise(o, rs, y);
@@ -811,10 +804,10 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
         };
         if (kQuick && form == kPlain) {
 #pragma unroll
-            for (int i = 0; i < MI; ++i) { turn(i); short_rows(i, std::false_type{}); }
+            for (int i = 0; i < MI; ++i) { turn(i); short_rows(i, std::integral_constant<int, kPlain>{}); }
         } else if (kQuick && form == kEdge) {
 #pragma unroll
-            for (int i = 0; i < MI; ++i) { turn(i); short_rows(i, std::true_type{}); }
+            for (int i = 0; i < MI; ++i) { turn(i); short_rows(i, std::integral_constant<int, kEdge>{}); }
         } else {
             int8_t* const yq_lane = (EPI & 2) != 0 ? g.yq + (((cn0 >> 6) + wn) * g.T) * kPanel + rd_c * 4 : nullptr;
 #pragma unroll
