@@ -308,6 +308,7 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
     // registers left.
     constexpr bool kQuick = EPI == 0 ? !I32 : EPI == 2 && !(STORE && MI == 4);
     constexpr int kUnroll = kQuick ? 1 : 8;
+    constexpr bool kMayShare = kQuick && DEQ == 2 && EPI == 0 && !COLSUM && MI == 4;   // has the form for rows that share lines (kShared)
     constexpr int kSlot = TL::kSlot, kHalfA = TL::kHalfA, kAhead = TL::kAhead, kLoads = TL::kLoads;
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -565,8 +566,8 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
                 asm volatile("" : "+v"(cn[c]));
             }
         }
-        // Which form this tile's rows take (wave-uniform): kPlain, every row and channel inside; kEdge, rows or channels past the edge;
-        // kGeneral, constants outside what the short arithmetic of the other two covers.
+        // Which form this tile's rows take (wave-uniform): kPlain, every row and channel inside; kShared, the same, with stores that stay in the
+        // caches; kEdge, rows or channels past the edge; kGeneral, constants outside what the short arithmetic of the others covers.
         bool odd = false;   // this lane's channels have such constants
         Float4 nis = {{1.f, 1.f, 1.f, 1.f}};   // the next layer's 1 / s for this lane's four channels
         float nstep = 1.0f, nrstep = 1.0f, nthr = 0.0f;
@@ -601,7 +602,7 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
         __builtin_amdgcn_s_barrier();  // every wave is done reading the ring
         if (more) start_tile(ntm, ntn);
 
-        enum { kPlain, kEdge, kGeneral };
+        enum { kPlain, kShared, kEdge, kGeneral };
         int form = kGeneral;
         if constexpr (kQuick) {
             if constexpr (DEQ != 0) {
@@ -609,8 +610,13 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
                 for (int c = 0; c < 4; ++c) odd = odd || nzw[c] >= (1 << 23) || nzw[c] <= -(1 << 23);
             }
             const bool inside = cm0 + TL::kRows <= g.T && cn0 + BN <= g.N;
+            // Rows that do not begin at multiples of 64 bytes share lines with the next tile's, written by another workgroup a little earlier
+            // or later: non-temporal, halves of lines went to memory (us, binary16, non-temporal -> cached: 3515 tokens 4468 x 2008 38.1 -> 35.7,
+            // 3900 x 4092 x 1024 24.6 -> 23.2, 8192 x 4092 x 1024 49.3 -> 43.8; but whole lines 4096 x 4096 x 1024 21.3 -> 24.3, and with sums
+            // over tokens 3900 x 4092 x 1024 28.3 -> 29.7, 128-token tiles 1800 x 4468 x 4096 43.2 -> 44.8)
+            const bool shared = kMayShare && ((reinterpret_cast<uintptr_t>(g.out_deq) | (uintptr_t)(g.ldo * 2)) & 63) != 0;
             if (__builtin_amdgcn_ballot_w64(odd && n_ok) == 0 && g.ldo < (1 << 28) && (!COLSUM || g.K < 32768))
-                form = inside ? kPlain : kEdge;
+                form = !inside ? kEdge : shared ? kShared : kPlain;
         }
 
         // per-channel constants of the de-quantisation
@@ -695,7 +701,7 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
         // tokens 466 -> 449, three layers 4096 x 4096 of 8192 tokens inside their calibration 437 -> 418, the 128-token tiles of
         // 2048 tokens 4096 x 11008 89.3 -> 88.3.)
         auto short_rows = [&](int i, auto form_c) {
-            constexpr bool EDGE = decltype(form_c)::value == kEdge;
+            constexpr bool EDGE = decltype(form_c)::value == kEdge, CACHED = decltype(form_c)::value == kShared;
             uint32_t redo = 0;
             int rsy_even = 0;
             // a pass's accumulators and row sum are requested one pass ahead
@@ -724,7 +730,10 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
                         h2 oh[2];
                         rounded(y, oh);
                         if constexpr (STORE) {
-                            if (in) __builtin_nontemporal_store(h4{oh[0][0], oh[0][1], oh[1][0], oh[1][1]}, reinterpret_cast<h4*>(row_deq + (uint64_t)(lane_elt * 2u)));
+                            h4* const d = reinterpret_cast<h4*>(row_deq + (uint64_t)(lane_elt * 2u));
+                            const h4 o4 = {oh[0][0], oh[0][1], oh[1][0], oh[1][1]};
+                            if constexpr (CACHED) { if (in) *d = o4; }
+                            else if (in) __builtin_nontemporal_store(o4, d);
                             row_deq += 8 * g.ldo;
                         }
                         if constexpr ((EPI & 2) != 0) {
@@ -805,6 +814,9 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
         if (kQuick && form == kPlain) {
 #pragma unroll
             for (int i = 0; i < MI; ++i) { turn(i); short_rows(i, std::integral_constant<int, kPlain>{}); }
+        } else if (kMayShare && form == kShared) {
+#pragma unroll
+            for (int i = 0; i < MI; ++i) { turn(i); short_rows(i, std::integral_constant<int, kShared>{}); }
         } else if (kQuick && form == kEdge) {
 #pragma unroll
             for (int i = 0; i < MI; ++i) { turn(i); short_rows(i, std::integral_constant<int, kEdge>{}); }
