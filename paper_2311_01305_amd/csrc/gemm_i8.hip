@@ -307,7 +307,9 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
     // 4096 x 4096 x 4096 with sums 68.2 -> 67.6); the statistics epilogue, and the quantising one that also stores 256-token tiles, have no
     // registers left.
     constexpr bool kQuick = EPI == 0 ? !I32 : EPI == 2 && !(STORE && MI == 4);
-    constexpr int kUnroll = kQuick ? 1 : 8;
+    // passes of the general form in one piece: all of them where it is the only form; beside the short ones as many as cost no registers
+    // (the next layer's codes with |Z| beyond 4096, 1 -> 4: 1024 tokens 16384 x 4096 85.3 -> 84.3, 2000 x 4096 x 1024 28.1 -> 27.7; 8 spill)
+    constexpr int kUnroll = !kQuick ? 8 : EPI != 0 ? 4 : 1;
     constexpr bool kMayShare = kQuick && DEQ == 2 && EPI == 0 && !COLSUM && MI == 4;   // has the form for rows that share lines (kShared)
     constexpr int kSlot = TL::kSlot, kHalfA = TL::kHalfA, kAhead = TL::kAhead, kLoads = TL::kLoads;
     extern __shared__ __attribute__((aligned(1024))) char lds[];
