@@ -614,9 +614,12 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
             const bool inside = cm0 + TL::kRows <= g.T && cn0 + BN <= g.N;
             // Rows that do not begin at multiples of 64 bytes share lines with the next tile's, written by another workgroup a little earlier
             // or later: non-temporal, halves of lines went to memory (us, binary16, non-temporal -> cached: 3515 tokens 4468 x 2008 38.1 -> 35.7,
-            // 3900 x 4092 x 1024 24.6 -> 23.2, 8192 x 4092 x 1024 49.3 -> 43.8; but whole lines 4096 x 4096 x 1024 21.3 -> 24.3, and with sums
-            // over tokens 3900 x 4092 x 1024 28.3 -> 29.7, 128-token tiles 1800 x 4468 x 4096 43.2 -> 44.8)
-            const bool shared = kMayShare && ((reinterpret_cast<uintptr_t>(g.out_deq) | (uintptr_t)(g.ldo * 2)) & 63) != 0;
+            // 3900 x 4092 x 1024 24.6 -> 23.2, 8192 x 4092 x 1024 49.3 -> 43.8; but whole lines 4096 x 4096 x 1024 21.3 -> 24.3, with sums
+            // over tokens 3900 x 4092 x 1024 28.3 -> 29.7, and where an eighth of the compute units have no tile less is written at a time:
+            // 240 tiles 3800 x 4092 x 1024 / 4096 26.3 -> 25.4 / 61.9 -> 61.2, 208 tiles 3300 x 4092 23.2 -> 23.75 / 55.7 -> 55.9, 144 tiles
+            // 2300 x 4092 19.1 -> 20.8 / 44.6 -> 46.0)
+            const bool shared = kMayShare && ((reinterpret_cast<uintptr_t>(g.out_deq) | (uintptr_t)(g.ldo * 2)) & 63) != 0 &&
+                                (((int)g.T + TL::kRows - 1) / TL::kRows) * (((int)g.N + BN - 1) / BN) > 224;
             if (__builtin_amdgcn_ballot_w64(odd && n_ok) == 0 && g.ldo < (1 << 28) && (!COLSUM || g.K < 32768))
                 form = !inside ? kEdge : shared ? kShared : kPlain;
         }
