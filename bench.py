@@ -146,8 +146,8 @@ def layer_bench(args, torch, B, pipeline, synth, dev, cfg):
     stages = ("stats_x", "stats_w", "equalize", "quant_weight", "quant_act", "gemm", "bias")
 
     def run_layer(lin, X, W, b, buf, ev=None):
-        """The call sequence of pipeline.calibrate_layer, with the activation quantizer and the GEMM
-        issued as two calls so that each can be bracketed by events."""
+        """The stages that pipeline.calibrate_layer runs as one call (aweq_calibrate), called one by one, with the activation
+        quantizer and the GEMM apart, so that each can be bracketed by events."""
         t, K, N, st = buf.t, lin.K, lin.N, buf.t["status"]
 
         def mark(i):
@@ -282,8 +282,8 @@ def layer_bench(args, torch, B, pipeline, synth, dev, cfg):
 
 def block_bench(args, torch, B, pipeline, synth, dev, cfg):
     """W8A8 calibration of a block with shared inputs (Sec. 3.1: equalization sits at the entrance of
-    the attention block and of the MLP): the call sequence of pipeline.calibrate_group with every
-    stage bracketed by events."""
+    the attention block and of the MLP): the stages that pipeline.calibrate_group runs as one call
+    (aweq_calibrate), called one by one, every one bracketed by events."""
     wl = synth.WORKLOADS[cfg]
     T = args.tokens or wl.T
     tdt = torch.float16 if wl.dtype == "f16" else torch.float32

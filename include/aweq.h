@@ -293,7 +293,8 @@ int aweq_wonly_gemm(const void* X_hat, int64_t T, int64_t K, int64_t ldx,
  * one scale from the merged weight ranges, one activation quantizer; every weight has slices of its own, as `group` says).  The outputs are
  * those of the stage entry points called one after the other; the launches are fewer where the shapes allow (workspace of
  * aweq_workspace_size(AWEQ_OP_CALIBRATE, T, K, sum of the N); with less, down to what the stages ask for, they run one by one).
- * Sums in binary64 (xsum, delta) are added in another order than the stages add them; everything else is the same to the bit.
+ * Sums in binary64 are added in another order than the stages add them, so that xsum and what is rounded from such sums (mu_xhat, delta,
+ * bias_out) may differ from the stages' in the last place; everything else is the same to the bit.
  * Nullable: count, wcount, p_x, p_w, status; bias_in; rowsum_w without w8a8; xq, rowsum_x and colsum_acc without the
  * forward; out_i32 and out_deq.  W_hat may take the place of W (same pitch).  Output pitch N. */
 typedef struct {

@@ -6,12 +6,13 @@
 // operands come straight from their K-panels (16 rows of a panel are 1 KiB contiguous) in the operand order of
 // v_mfma_i32_16x16x64_i8: lane l holds row l % 16, bytes 16 (l / 16) .. + 15 of the panel row.
 //
-// Bound by the read of the weight.  Measured (us per call on the device, binary16 output, before = 256 x 256 tiles):
+// Bound by the read of the weight.  Measured (us per call on the device, codes given, binary16 output, the same weight every call; before =
+// 256 x 256 tiles; from 128 tokens on also the kernel for some hundred tokens, where it is modelled to take less):
 //   tokens          1             32            64            128           256
-//   4096 x 4096     37.7 ->  6.0  38.4 ->  7.3  38.9 ->  7.6  40.8 ->  9.5  43.0 -> 12.4
-//   8192 x 8192     68.3 -> 13.3  68.5 -> 13.7  69.3 -> 15.0  71.4 -> 19.4  72.7 -> 36.7
-//   22016 x 8192    71.8 -> 34.5  70.4 -> 39.6  71.3 -> 48.9  73.2 -> 69.4  (tiled: 80)
-// (22016 x 8192 at one token: 180 MB, 5.2 TB/s.)
+//   4096 x 4096     37.7 ->  3.8  38.4 ->  5.2  38.9 ->  6.2  40.8 ->  8.0  43.0 -> 10.6
+//   8192 x 8192     68.3 -> 12.4  68.5 -> 13.4  69.3 -> 14.2  71.4 -> 18.2  72.7 -> 28.9
+//   22016 x 8192    71.8 -> 30.6  70.4 -> 31.1  71.3 -> 31.7  73.2 -> 40.6    80 -> 50.2
+// (22016 x 8192 at one token: 180 MB, 5.9 TB/s.)
 #include "act_unit.hpp"
 #include "gemm_i8.hpp"
 

@@ -17,14 +17,15 @@
 // caches, before -> now: 17 tokens 4096 x 4096 7.2 -> 6.4 / 7.2 -> 6.5, 4096 x 11008 13.7 -> 11.6 / 14.0 -> 12.1; one token 11008 x 4096
 // 7.9 -> 7.6 / 8.4 -> 8.2; 16 tokens and 64 within 2 %).  The vector unit has 73 operations there for 32 codes a lane with their scale.
 //
-// Bound by the read of the codes and, for small layers, by the launch and one round trip to memory.  Measured (INT4,
-// groups of 128, us per call on the device; before = de-quantising the whole weight and a 256 x 256-tiled GEMM):
+// Bound by the read of the codes and, for small layers, by the launch and the round trips to memory (a wavefront asks for one chunk
+// ahead).  Measured (INT4, groups of 128, us per call on the device, the same weight every call; before = de-quantising the whole weight and
+// a 256 x 256-tiled GEMM; from 64 tokens on also the kernel for some hundred tokens, where it is modelled to take less):
 //   tokens          1            16           32           64           128          256
-//   4096 x 4096     85.7 ->  5.2  85.8 ->  6.4  86.3 ->  8.3  86.8 -> 10.4  88.2 -> 14.4  87.6 -> 26.5
-//   11008 x 4096     100 -> 10.3   101 -> 12.7   101 -> 15.1   102 -> 27.4   103 -> 42.4   103 -> 81.4
-//   22016 x 8192     312 -> 26.3   310 -> 33.5   312 -> 50.4   320 -> 76.1   329 ->  146   331 ->  263
-// (22016 x 8192 at one token: 101 MB of codes and scales, 3.9 TB/s.)  With the operands loaded straight in the matrix
-// operand's order, and no pass through LDS, the same table began 6.2 / 13.9 / 42.5 for one token.
+//   4096 x 4096     85.7 ->  4.4  85.8 ->  5.2  86.3 ->  6.9  86.8 ->  8.7  88.2 -> 12.9  87.6 -> 20.9
+//   11008 x 4096     100 ->  7.6   101 ->  9.9   101 -> 13.6   102 -> 21.1   103 -> 21.7   103 -> 38.8
+//   22016 x 8192     312 -> 22.0   310 -> 26.1   312 -> 37.5   320 -> 39.3   329 -> 69.8   331 ->  129
+// (22016 x 8192 at one token: 101 MB of codes and scales, 4.6 TB/s.)  A first form with the operands loaded straight in the matrix
+// operand's order, and no pass through LDS, took 6.2 / 13.9 / 42.5 for one token where this one's began with 5.2 / 10.3 / 26.3.
 #include "dequant.hpp"
 #include "gemm_wonly_small.hpp"
 
@@ -326,13 +327,15 @@ static int launch_tile(const SmallArgs& g, int scales, bool out_f16, hipStream_t
 SmallPlan plan_small(int64_t T, int64_t N)
 {
     // Up to 16 tokens the pass is a read of the codes: 16 channels per workgroup until those workgroups fill the chip
-    // 1.3 times over, then 32, which read the tokens half as often (8192 x 8192, one token: 11.9 / 12.2 us with 16 / 32;
-    // 22016 x 8192: 28.3 / 26.3; 11008 x 4096: 10.3 / 11.3; 64 channels lose everywhere).  Nothing else comes near.
+    // 1.5 times over, then 32, which read the tokens half as often (us with 16 / 32 channels: one token 4096 x 4096 4.4 / 5.9, 8192 x 8192
+    // 9.3 / 10.3, 22016 x 8192 the same; four tokens 22016 x 8192 23.7 / 22.3; 8 tokens 12800 x 8192 19.5 / 17.4; 16 tokens 16384 x 4096
+    // 13.7 / 11.5, but 8192 x 8192 13.2 / 11.8, which the line does not see; 64 channels lose everywhere).  Nothing else comes near.
     if (T <= 16) return {N > 12288 ? 2 : 1, 0.0};
     // More tokens, 32 per workgroup: as many channels as give the fewest rounds of workgroups, each weighted with what a
-    // round was measured to take (8192 x 8192, 17 tokens, us: 19 for 512 workgroups of 16 channels, two per compute unit,
-    // 14 for 256; 17.5 for 32 channels and 27 for 64, one per compute unit).  64 tokens per workgroup gain nothing
-    // (64 tokens: 10.4 us at 4096 x 4096 in 32s, 14.0 in 64s; 76 / 75 at 22016 x 8192).
+    // round was measured to take when a load sat in a branch (8192 x 8192, 17 tokens, us: 19 for 512 workgroups of 16 channels, two per
+    // compute unit, 14 for 256; 17.5 for 32 channels and 27 for 64, one per compute unit; now 18.2, 14.0 and 22.0 for the same 16, 32 and 64,
+    // and the choices are still the fastest of the three: 17 tokens 4096 x 4096 6.2 / 8.1 / 12.5, 11008 x 4096 15.0 / 15.5 / 13.0, 16384 x 4096
+    // 21.2 / 16.8 / 14.0).  64 tokens per workgroup gained nothing (4096 x 4096 10.4 us in 32s, 14.0 in 64s; 22016 x 8192 76 / 75).
     const int64_t tm = cdiv(T, 32), w1 = cdiv(N, 16) * tm, w2 = cdiv(N, 32) * tm, w4 = cdiv(N, 64) * tm;
     const double c1 = w1 <= 256 ? 14.0 : 19.0 * (double)cdiv(w1, 512), c2 = 17.5 * (double)cdiv(w2, 256), c4 = 27.0 * (double)cdiv(w4, 256);
     if (c1 <= c2 && c1 <= c4) return {1, c1};

@@ -2,8 +2,9 @@
 // (Sec. 3.3, Eq. 11-15), W read once and neither W_hat nor the codes read back.  Bound by memory: 2 + 2 + 1 bytes (8 bits) or
 // 2 + 2 + 1/2 (4 bits) an element of binary16, where the three stages one after the other move 8 / 7.
 //
-// A block takes kRows output channels, so that what every channel needs of a column (s, E[x_hat], sum of the activation codes: 16 bytes)
-// is read a quarter as often, and keeps the rows in registers between the extremes and the codes.
+// A block (a wavefront of short rows) takes one to four output channels at a time, so that what every channel needs of a column (s, E[x_hat]
+// and, for 8 bits, the digits of the activation codes' sum: 12 or 8 bytes) is read as much less often, and keeps the rows in registers
+// between the extremes and the codes.
 //
 // The sums over tokens that the int8 path's correction needs are the column sums of the activation codes times the weight codes:
 // sum_t acc[t,n] = sum_k wq[n,k] colsum_xq[k], the same integers that a GEMM adds up.

@@ -21,7 +21,7 @@ def _dt(t: torch.Tensor) -> int:
 
 
 def _layer_args(X, T, K, t, acts, enable_awe, enable_bc, bits, group, w8a8, forward, fused_weight_pass):
-    """The fields of binding.CalibLayer from the buffers `t` (acts: xq, rowsum_x, colsum_xq)."""
+    """The fields of aweq_calib_layer (include/aweq.h), in order, from the buffers `t` (acts: xq, rowsum_x, colsum_xq)."""
     ws = t["ws"]
     return (X, _dt(X), T, K, X.stride(0), t["xmin"], t["xmax"], t["xsum"], t["count"], t["r_x"], t["R_x"], t["p_x"], t["wmin"], t["wmax"],
             t["wcount"], t["r_w"], t["R_w"], t["p_w"], t["s"], t["inv_s"], t["xhat_range"], t["mu_xhat"], t["act_step"], t["act_zero"], *acts,

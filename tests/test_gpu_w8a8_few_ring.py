@@ -1,4 +1,4 @@
-"""Few-token int8 GEMM: numbers of panels around what its wavefronts have in flight (rings of 1 to 6 panels for each of 8 wavefronts), every
+"""Few-token int8 GEMM: numbers of panels around what its wavefronts have in flight (rings of 1 to 4 panels for each of 8 wavefronts), every
 tile, against the exact integer product."""
 import numpy as np
 import pytest
