@@ -12,7 +12,7 @@
 // code fields come out of their packed words.
 //
 // Reads past an edge repeat the last row or the last values of K (their results are not stored, their activations are zero), so that no
-// load sits in a branch of its own; where they are many, quads of tokens past the edge are left out.  With more token tiles than channel tiles the codes
+// load sits in a branch of its own.  With more token tiles than channel tiles the codes
 // are brought to the activations' natural order instead of the other way round (INT4 / INT3, us on the device with the weight in the
 // caches, before -> now: 17 tokens 4096 x 4096 7.2 -> 6.4 / 7.2 -> 6.5, 4096 x 11008 13.7 -> 11.6 / 14.0 -> 12.1; one token 11008 x 4096
 // 7.9 -> 7.6 / 8.4 -> 8.2; 16 tokens and 64 within 2 %).  The vector unit has 73 operations there for 32 codes a lane with their scale.
@@ -40,21 +40,25 @@ constexpr int kChunk = 256;   // values of K a wavefront takes at a time
 // LDS per wavefront: 128 values of RX tokens (256 for RX = 4), 256 codes of 16 NT channels (16 bytes per 32 codes)
 constexpr int small_wave_lds(int rx, int nt) { return (rx == 4 ? 4 * 512 : rx * 256) + nt * 16 * 128; }
 
-// FEWER: quads of tokens past the edge are left out, by a branch around each load and write of four tokens.  Without those branches the
-// activations of the second half of a chunk are requested ahead of the next codes (loads return in order, and they are needed first); with them
-// that was slower (us, INT4: 13 tokens 16384 x 4096 12.2 -> 11.9, 32 tokens 16384 x 4096 15.4 -> 15.05, but 6 tokens 4096 x 16384 11.7 -> 12.1).
+// RX: tokens of a tile whose activations are loaded: 4, 8, 12, 16, 20, 24 or 32.  What a quad of tokens costs is its load, its way through LDS
+// and, with two MFMA tiles of tokens, its share of the operand; left out by a branch around each load instead, as tiles of 16 and 32 once did, the
+// compiler waited for more than it needed (us, branches -> this: INT4 6 tokens 4096 x 11008 9.6 -> 8.9, 8 tokens 11008 x 4096 9.8 -> 9.3, 12 tokens
+// 8192 x 8192 13.0 -> 12.5, 20 tokens 4096 x 4096 6.5 -> 6.15; INT3 11 tokens 4096 x 4096 5.5 -> 5.2, 17 tokens
+// 4096 x 11008 12.5 -> 11.7; against it 10 tokens 8192 x 22016 33.5 -> 34.4, INT3 22 tokens 4096 x 2048 4.55 -> 4.72).  The activations of the second half of a
+// chunk are requested ahead of the next codes (loads return in order, and they are needed first).  A chunk more of codes and activations in flight
+// gained nothing and its registers cost wavefronts (17 tokens 4096 x 11008 INT3 12.6 -> 13.3, one token 8192 x 8192 9.8 -> 10.9).
 // SCALES: kFine: groups that are no multiple of 128 (a lane's 32 codes have one (Step, Z), but the four lanes that share
 // 128 values of a channel may differ); kRagged: one (Step, Z) for a row or the tensor, and K ends inside such 128 values
 enum { kWhole, kRagged, kFine };
-template <int BITS, int RX, int NT, int WAVES, bool FEWER, int SCALES, bool OUT_F16>
+template <int BITS, int RX, int NT, int WAVES, int SCALES, bool OUT_F16>
 __global__ __launch_bounds__(WAVES * kWave) void gemm_small_kernel(SmallArgs g)
 {
-    constexpr int TT = RX < 16 ? 1 : RX / 16;
+    constexpr int TT = (RX + 15) / 16;
     constexpr bool FINE = SCALES == kFine;
     constexpr int XH = RX == 4 ? 1 : 2;             // activation loads per chunk: whole, or 128 values at a time
-    constexpr int XL = RX == 4 ? 2 : 4 * TT;        // 16-byte loads of activations per lane and time
+    constexpr int XL = RX == 4 ? 2 : RX / 4;        // 16-byte loads of activations per lane and time
     constexpr bool kNatural = TT > NT;              // the operand with fewer tiles is the one that is brought to the other's order
-    constexpr bool kCodesLate = RX > 4 && !FEWER;
+    constexpr bool kCodesLate = RX > 4;
     constexpr int kWords = BITS == 4 ? 4 : 3;
     typedef int Words __attribute__((ext_vector_type(kWords)));
     extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -84,7 +88,7 @@ __global__ __launch_bounds__(WAVES * kWave) void gemm_small_kernel(SmallArgs g)
 #pragma unroll
     for (int j = 0; j < NT; ++j) srow[j] = (uint32_t)min(16 * j + (FINE ? r : lane >> 2), rows_left) * g.scale_pitch;
     // activations: lane -> token 4 i + lane / 16, 8 values lane % 16 of 128 (RX = 4: the second load is the second 128).  Tokens past the
-    // edge re-read the last one, quads of them are left out; their columns are not stored.
+    // edge re-read the last one; their columns are not stored.
     const _Float16* const xbase = g.X + t0 * g.ldx;
     const int tokens_left = (int)min(g.T - t0, (int64_t)(16 * TT));
     constexpr int XR = RX == 4 ? 1 : XL;
@@ -113,13 +117,12 @@ __global__ __launch_bounds__(WAVES * kWave) void gemm_small_kernel(SmallArgs g)
         }
 #pragma unroll
         for (int i = 0; i < XL; ++i) {
-            if (FEWER && 4 * i >= tokens_left) break;
             const uint32_t xo = (uint32_t)min((RX == 4 ? k + 128 * i : k) + (lane & 15) * 8, K - 8);
             xr[i] = *reinterpret_cast<const v4i*>(xbase + (xrow[RX == 4 ? 0 : i] + xo));
         }
     };
 
-    const int fr = RX == 4 ? r & 3 : r;   // (RX = 4: tokens past the fourth repeat the first four, their columns are not stored)
+    auto row_of = [&](int i) { return RX - 16 * i < 16 ? min(r, RX - 16 * i - 1) : r; };   // (lanes past the tile's tokens repeat the last one)
     // Four wavefronts keep two sums, of every other chunk each, so that no chain of additions is longer than eight wavefronts' (with one, the error
     // against 64 bits grew from 1.5e-7 to 2.0e-7 at K = 4096)
     constexpr int kSets = WAVES < 8 ? 2 : 1;
@@ -187,7 +190,6 @@ __global__ __launch_bounds__(WAVES * kWave) void gemm_small_kernel(SmallArgs g)
             if (h < XH) {
 #pragma unroll
                 for (int i = 0; i < XL; ++i) {
-                    if (FEWER && 4 * i >= tokens_left) break;
                     const int row = (RX == 4 ? 0 : 4 * i) + (lane >> 4), k = kc + (RX == 4 ? i : h) * 128;
                     if (k + 128 > K && k + (lane & 15) * 8 >= K) xr[i] = v4i{0, 0, 0, 0};
                     *reinterpret_cast<v4i*>(lx + (RX == 4 ? i * 1024 : 0) + row * 256 + (((lane & 15) ^ (row & 15)) * 16)) = kNatural ? xr[i] : pair_order(xr[i]);
@@ -200,7 +202,7 @@ __global__ __launch_bounds__(WAVES * kWave) void gemm_small_kernel(SmallArgs g)
             }
             // the operand with fewer tiles stays in registers over the loop on the other
             auto frag_x = [&](int i, int d) {
-                return __builtin_bit_cast(v8h, *reinterpret_cast<const v4i*>(lx + (RX == 4 ? h * 1024 : i * 4096) + fr * 256 + (((4 * q + d) ^ fr) * 16)));
+                return __builtin_bit_cast(v8h, *reinterpret_cast<const v4i*>(lx + (RX == 4 ? h * 1024 : i * 4096) + row_of(i) * 256 + (((4 * q + d) ^ row_of(i)) * 16)));
             };
             auto frag_w = [&](int j, uint32_t w[4][4]) {
                 const Words cw = *reinterpret_cast<const Words*>(lc + j * 2048 + r * 128 + (((4 * h + q) ^ (r & 7)) * 16));
@@ -306,15 +308,16 @@ __global__ __launch_bounds__(WAVES * kWave) void gemm_small_kernel(SmallArgs g)
     }
 }
 
-template <int BITS, int RX, int NT, int WAVES, bool FEWER>
+template <int BITS, int RX, int NT, int WAVES>
 static int launch_tile(const SmallArgs& g, int scales, bool out_f16, hipStream_t st)
 {
-    constexpr int TT = RX < 16 ? 1 : RX / 16;
-    const dim3 grid((unsigned)cdiv(g.N, 16 * NT), (unsigned)cdiv(g.T, RX));
+    constexpr int TT = (RX + 15) / 16;
+    static_assert(RX == 4 || RX % 16 == 0 || RX < 32, "a tile that is not whole holds all tokens of the call");
+    const dim3 grid((unsigned)cdiv(g.N, 16 * NT), (unsigned)cdiv(g.T, 16 * TT));
     constexpr int work = WAVES * small_wave_lds(RX, NT), red = (WAVES < 8 ? 2 : 1) * WAVES * TT * NT * kWave * 16;
     constexpr int lds = work > red ? work : red;
-#define AWEQ_SF(S) (out_f16 ? reinterpret_cast<const void*>(gemm_small_kernel<BITS, RX, NT, WAVES, FEWER, S, true>) \
-                            : reinterpret_cast<const void*>(gemm_small_kernel<BITS, RX, NT, WAVES, FEWER, S, false>))
+#define AWEQ_SF(S) (out_f16 ? reinterpret_cast<const void*>(gemm_small_kernel<BITS, RX, NT, WAVES, S, true>) \
+                            : reinterpret_cast<const void*>(gemm_small_kernel<BITS, RX, NT, WAVES, S, false>))
     const void* fn = scales == kFine ? AWEQ_SF(kFine) : scales == kRagged ? AWEQ_SF(kRagged) : AWEQ_SF(kWhole);
 #undef AWEQ_SF
     int dev = 0, cus = 0;
@@ -347,34 +350,37 @@ static int launch_bits(const SmallArgs& g, int scales, int nt, bool out_f16, hip
 {
     // Long rows on at most one workgroup per compute unit: K split between 16 wavefronts instead of 8, from two chunks a wavefront on (us, INT4,
     // 8 -> 16: one token 1024 x 22016 12.0 -> 10.7, 4096 x 11008 7.6 -> 7.1, 2048 x 8192 6.1 -> 5.9, 4096 x 4096 the same; 16 tokens 1024 x 22016
-    // 17.2 -> 14.8, but 2048 x 8192 8.4 -> 8.5; 32 tokens do not fit the registers: 4096 x 11008 13.8 -> 16.1)
+    // 17.2 -> 14.8, but 2048 x 8192 8.4 -> 8.5)
     const bool lone = cdiv(g.N, 16) <= 256;
     // 513 to 768 workgroups (to 1024 of up to four tokens) of short rows: four wavefronts, of which all workgroups are resident at a time; eight
     // take 512 of them, and the rest wait (us, INT4, 8 -> 4: one token 11008 x 4096 8.65 -> 8.4, 12288 x 2048 5.35 -> 4.9, 8704 x 1024 4.45 -> 3.65,
     // 16384 x 4096 (32 channels a workgroup before) 10.25 -> 10.1; 6 tokens 8704 x 4096 9.95 -> 9.2, 16 tokens 11008 x 4096 11.0 -> 10.8; but one
     // token 11008 x 11008 15.8 -> 16.5, INT3 16 tokens 11008 x 5120 12.6 -> 12.9, 6 tokens 16384 x 4096 11.4 -> 11.7)
+#define AWEQ_ST(RX, NT, WAVES) launch_tile<BITS, RX, NT, WAVES>(g, scales, out_f16, st)
+#define AWEQ_ST16(NT, WAVES) (g.T <= 8 ? AWEQ_ST(8, NT, WAVES) : g.T <= 12 ? AWEQ_ST(12, NT, WAVES) : AWEQ_ST(16, NT, WAVES))
     if (g.T <= 16 && cdiv(g.N, 16) > 512 && g.N <= (g.T <= 4 ? 16384 : 12288) && g.K <= (BITS == 4 ? 8192 : 4096))
-        return g.T <= 4 ? launch_tile<BITS, 4, 1, 4, false>(g, scales, out_f16, st) : g.T <= 12 ? launch_tile<BITS, 16, 1, 4, true>(g, scales, out_f16, st)
-                                                                                              : launch_tile<BITS, 16, 1, 4, false>(g, scales, out_f16, st);
+        return g.T <= 4 ? AWEQ_ST(4, 1, 4) : AWEQ_ST16(1, 4);
     if (g.T <= 4) {
-        if (nt == 2) return launch_tile<BITS, 4, 2, 8, false>(g, scales, out_f16, st);
-        return lone && g.K >= 8192 ? launch_tile<BITS, 4, 1, 16, false>(g, scales, out_f16, st) : launch_tile<BITS, 4, 1, 8, false>(g, scales, out_f16, st);
+        if (nt == 2) return AWEQ_ST(4, 2, 8);
+        return lone && g.K >= 8192 ? AWEQ_ST(4, 1, 16) : AWEQ_ST(4, 1, 8);
     }
     if (g.T <= 16) {
-        if (g.T <= 12) {   // (8 tokens of 16: 11008 x 4096 INT4 10.45 / 10.7 us with / without the branches, 13 tokens 11.6 / 11.05)
-            if (nt == 2) return launch_tile<BITS, 16, 2, 8, true>(g, scales, out_f16, st);
-            return lone && g.K >= 16384 ? launch_tile<BITS, 16, 1, 16, true>(g, scales, out_f16, st) : launch_tile<BITS, 16, 1, 8, true>(g, scales, out_f16, st);
-        }
-        if (nt == 2) return launch_tile<BITS, 16, 2, 8, false>(g, scales, out_f16, st);
-        return lone && g.K >= 16384 ? launch_tile<BITS, 16, 1, 16, false>(g, scales, out_f16, st) : launch_tile<BITS, 16, 1, 8, false>(g, scales, out_f16, st);
+        if (nt == 2) return AWEQ_ST16(2, 8);
+        if (lone && g.K >= 16384) return AWEQ_ST16(1, 16);
+        return AWEQ_ST16(1, 8);
     }
-    // Tokens left out or not, us: INT4 20 tokens 4096 x 4096 6.2 / 7.0, 24 tokens 8192 x 8192 15.05 / 15.6, 32 tokens 8192 x 8192 16.3 / 15.95;
-    // 64 channels a workgroup: 24 tokens 16384 x 4096 15.7 / 14.95, INT3 17 tokens 11008 x 4096 13.9 / 14.3
-    const bool fewer = g.T <= 24 && (nt <= 2 || BITS == 3);
-    if (fewer) return nt == 1 ? launch_tile<BITS, 32, 1, 8, true>(g, scales, out_f16, st) : nt == 2 ? launch_tile<BITS, 32, 2, 8, true>(g, scales, out_f16, st)
-                                                                                                 : launch_tile<BITS, 32, 4, 8, true>(g, scales, out_f16, st);
-    return nt == 1 ? launch_tile<BITS, 32, 1, 8, false>(g, scales, out_f16, st) : nt == 2 ? launch_tile<BITS, 32, 2, 8, false>(g, scales, out_f16, st)
-                                                                                        : launch_tile<BITS, 32, 4, 8, false>(g, scales, out_f16, st);
+    // 17 to 24 tokens on at most one workgroup per compute unit: 16 wavefronts from one chunk a wavefront on (us, 8 -> 16: INT3 17 tokens
+    // 4096 x 11008 12.6 -> 11.7, INT4 18 tokens 1024 x 4096 6.0 -> 5.8, 24 tokens 4096 x 11008 12.95 -> 12.6; half a chunk each INT3 22 tokens
+    // 4096 x 2048 4.55 -> 4.75; 32 tokens take all registers: 4096 x 4096 7.6 -> 8.05)
+    const bool many = nt == 1 && lone && g.K >= 16 * kChunk;
+    if (g.T <= 24) {
+        if (many) return g.T <= 20 ? AWEQ_ST(20, 1, 16) : AWEQ_ST(24, 1, 16);
+        if (nt == 1) return g.T <= 20 ? AWEQ_ST(20, 1, 8) : AWEQ_ST(24, 1, 8);
+        return nt == 2 ? AWEQ_ST(24, 2, 8) : AWEQ_ST(24, 4, 8);
+    }
+    return nt == 1 ? AWEQ_ST(32, 1, 8) : nt == 2 ? AWEQ_ST(32, 2, 8) : AWEQ_ST(32, 4, 8);
+#undef AWEQ_ST16
+#undef AWEQ_ST
 }
 
 int launch_small(const SmallArgs& g, int bits, int group, const SmallPlan& p, bool out_f16, hipStream_t st)
