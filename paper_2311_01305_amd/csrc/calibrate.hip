@@ -5,7 +5,7 @@
 // costs 4 - 5 us however little it does.  Here the chain is
 //   1. column statistics of X and of every W, in one launch (their blocks share the compute units and the pipeline drains once);
 //   2. merge of the partial rows, ranges, Eq. 10's scales and the pieces of the ranges over all channels, in one launch;
-//   3. int8 path: the activation quantizer, whose blocks find Step and Z from the pieces, and its merge;
+//   3. int8 path: the activation quantizer, whose blocks find Step and Z from the pieces and add their sums up;
 //   4. one pass over every weight: fold, quantise, correct the bias (weight_pass.hip); blocks beside it finish R and p;
 //   5. forward: the GEMMs, without column sums (the pass has them).
 // Calls that the pass does not take (one scale for the tensor, groups or widths it has no form for) run stages 2b - 5 as they are
@@ -82,6 +82,7 @@ struct MergeArgs {
     double* xsum;
     uint64_t *count, *wcount;
     float* ext;           // [6][gridDim.x]
+    int32_t *colsum, *rowsum;   // nullable: zero for the launch that adds to them, [K] and [T]
     uint32_t* status;
 };
 
@@ -95,6 +96,9 @@ __global__ __launch_bounds__(kMergeCols * kMergeParts) void calib_merge(MergeArg
         if (a.count) *a.count = a.T;
         if (a.wcount) *a.wcount = a.N;
     }
+    if (a.colsum && part == 0 && k < a.K) a.colsum[k] = 0;
+    if (a.rowsum)
+        for (uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; t < a.T; t += (uint64_t)gridDim.x * blockDim.x) a.rowsum[t] = 0;
     float lo = INFINITY, hi = -INFINITY, wlo = INFINITY, whi = -INFINITY;
     double sum = 0.0, wsum = 0.0;
     if (k < a.K) {
@@ -154,11 +158,11 @@ __global__ __launch_bounds__(kMergeCols * kMergeParts) void calib_merge(MergeArg
     }
 }
 
-// ---- workspace: what later launches read (the pieces of the ranges; the code sums' digits and totals), then partial rows (of the
-// statistics, then of the quantizer)
+// ---- workspace: what later launches read (the pieces of the ranges; the code sums), then partial rows (of the statistics; of the
+// stages' quantizer)
 static size_t ext_bytes(int64_t K) { return (size_t)cdiv(6 * cdiv(K, kRangeCols) * 4, 256) * 256; }
-static size_t digit_bytes(int64_t K) { return (size_t)cdiv(K * 4, 256) * 256; }
-static size_t kept_bytes(int64_t K) { return ext_bytes(K) + digit_bytes(K) + (size_t)cdiv(cdiv(K, kRangeCols) * 8, 256) * 256; }
+static size_t sum_bytes(int64_t K) { return (size_t)cdiv(K * 4, 256) * 256; }
+static size_t kept_bytes(int64_t K) { return ext_bytes(K) + sum_bytes(K); }
 static size_t partial_bytes(const CalibPlan& p, int64_t K) { return (size_t)p.slices * (size_t)K * 16; }
 
 // for any division of N rows over up to kMaxMembers weights: a plan has at most max(1280 / chunks, n) slices
@@ -174,7 +178,7 @@ size_t calibrate_ws_bytes(int64_t T, int64_t K, int64_t N)
         const size_t b = (size_t)slices * (size_t)K * 16;
         if (b > most) most = b;
     }
-    const size_t qa = quant_act_ws_bytes(T, K, true);
+    const size_t qa = quant_act_ws_bytes(T, K);
     return kept_bytes(K) + (most > qa ? most : qa);
 }
 
@@ -275,9 +279,11 @@ static int run_front(const aweq_calib_layer& l, const aweq_calib_weight* w, int 
     else calib_stats<false><<<grid, kStatsBlock, 0, st>>>(a);
     const unsigned blocks = (unsigned)cdiv(l.K, kMergeCols);
     const MergeArgs m = {a.pmin, a.pmax, a.psum, p.x_slices, p.slices, l.K, (uint64_t)l.T, (uint64_t)N, l.enable_awe, l.xmin, l.xmax, l.r_x,
-                         l.wmin, l.wmax, l.r_w, l.s, l.inv_s, l.mu_xhat, l.xsum, l.count, l.wcount, reinterpret_cast<float*>(l.ws), l.status};
+                         l.wmin, l.wmax, l.r_w, l.s, l.inv_s, l.mu_xhat, l.xsum, l.count, l.wcount, reinterpret_cast<float*>(l.ws),
+                         l.w8a8 ? reinterpret_cast<int32_t*>(reinterpret_cast<char*>(l.ws) + ext_bytes(l.K)) : nullptr,
+                         l.w8a8 && l.forward ? l.rowsum_x : nullptr, l.status};
     calib_merge<<<blocks, kMergeCols * kMergeParts, 0, st>>>(m);
-    fin = {{m.ext, (int)blocks, l.xhat_range, l.act_step, l.act_zero}, l.r_x, l.r_w, l.R_x, l.R_w, l.p_x, l.p_w, l.status};
+    fin = {{m.ext, (int)blocks, l.xhat_range, l.act_step, l.act_zero}, l.r_x, l.r_w, l.R_x, l.R_w, l.p_x, l.p_w, nullptr, nullptr, l.status};
     return launch_status();
 }
 
@@ -297,15 +303,17 @@ static int run_calibration(const aweq_calib_layer& l, const aweq_calib_weight* w
     }
     if (pass) {
         char* const ws = reinterpret_cast<char*>(l.ws);
-        const SumDigits dg = {reinterpret_cast<uint4*>(ws + ext_bytes(l.K)), reinterpret_cast<long long*>(ws + ext_bytes(l.K) + digit_bytes(l.K))};
+        int32_t* const colsum = reinterpret_cast<int32_t*>(ws + ext_bytes(l.K));
         if (l.w8a8) {
             rc = launch_quant_act(l.X, l.dt, l.T, l.K, l.ldx, l.inv_s, l.act_step, l.act_zero, l.forward ? l.xq : nullptr,
-                                  l.forward ? l.rowsum_x : nullptr, l.colsum_xq, ws + kept_bytes(l.K), l.status, st, &fin.range, &dg);
+                                  l.forward ? l.rowsum_x : nullptr, nullptr, nullptr, l.status, st, &fin.range, colsum);
             if (rc != AWEQ_OK) return rc;
             fin.range.act_step = nullptr;   // (the quantizer has written it)
+            fin.colsum = colsum;
+            fin.colsum_xq = reinterpret_cast<long long*>(l.colsum_xq);
         }
         PassArgs a;
-        a.n = n; a.K = l.K; a.s = l.s; a.mu = l.mu_xhat; a.count = (uint64_t)l.T; a.digits = dg.digits; a.totals = dg.totals;
+        a.n = n; a.K = l.K; a.s = l.s; a.mu = l.mu_xhat; a.count = (uint64_t)l.T; a.colsum = colsum;
         a.act_step = l.act_step; a.act_zero = l.act_zero; a.enable_bc = l.enable_bc; a.status = l.status; a.fin = fin;
         for (int i = 0; i < n; ++i)
             a.m[i] = {w[i].W, w[i].W_hat, reinterpret_cast<uint8_t*>(w[i].codes), w[i].step_w, w[i].zero_w, w[i].rowsum_w, w[i].bias_in, w[i].delta,

@@ -24,7 +24,6 @@
 // quotient too, where |Z| allows it, and divides the units with a quotient beyond 2^22 (7419 x 4096 tokens x channels:
 // 47.4 us with the division everywhere, 40.1 now; a quotient that underflows on the way rounds to 0 either way).
 #include "act_unit.hpp"
-#include "code_digits.hpp"
 #include "quant_act.hpp"
 #include <type_traits>
 
@@ -64,7 +63,7 @@ __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
     const void* __restrict__ X, int64_t T, int64_t K, int64_t ldx, const float* __restrict__ inv_s,
     const float* __restrict__ act_step, const int32_t* __restrict__ act_zero, int8_t* __restrict__ xq,
     int32_t* __restrict__ rowsum_x, int32_t* __restrict__ colsum_part, int rows_per_block, int chunks,
-    unsigned pairs, uint32_t* status, RangeParts range)
+    unsigned pairs, uint32_t* status, RangeParts range, int added)
 {
     const unsigned pair = (blockIdx.x % kQaXcds) * (gridDim.x / kQaXcds) + blockIdx.x / kQaXcds;
     if (pair >= pairs) return;   // (the grid is rounded up to a multiple of 8)
@@ -265,8 +264,8 @@ __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
 
     if (colsum_part) {
         // lanes l, l ^ 8, l ^ 16, l ^ 32 hold the same columns for different rows; this block's sums over
-        // its row slice (at most 512 rows of codes in [-128, 127]) go to row `slice` of the partial buffer
-        int32_t* const part = colsum_part + slice * K;
+        // its row slice (at most 512 rows of codes in [-128, 127]) go to row `slice` of the partial buffer, or are added to the one row
+        int32_t* const part = colsum_part + (added ? 0 : slice * K);
 #pragma unroll
         for (int j = 0; j < kQaVpt; ++j) {
             int v[8];
@@ -277,7 +276,13 @@ __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
                 v[i] += partner<4>(v[i]);
                 v[i] += partner<5>(v[i]);
             }
-            if (lane < 8 && valid[j]) {
+            if (added) {
+                // (a wavefront's 64 neighbouring columns in one instruction: lane l the column l / 8 of the eight that unit l % 8 has)
+                int own = v[0];
+#pragma unroll
+                for (int i = 1; i < 8; ++i) own = rsub == i ? v[i] : own;
+                if (valid[j]) atomicAdd(part + col0 + j * kPanel + rsub, own);
+            } else if (lane < 8 && valid[j]) {
                 typedef int v4i_ __attribute__((ext_vector_type(4)));
                 v4i_* d = reinterpret_cast<v4i_*>(part + col0 + j * kPanel);
                 d[0] = v4i_{v[0], v[1], v[2], v[3]};
@@ -287,23 +292,28 @@ __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
     }
     if constexpr (SUMS) return;
     __syncthreads();
-    // with several column chunks `rowsum_x` is the partial buffer [chunks][T], folded by the merge kernel
+    // with several column chunks `rowsum_x` is the partial buffer [chunks][T], folded by the merge kernel, or is added to
     if (rowsum_x)
         for (int i = threadIdx.x; i < nrows; i += kQaBlock) {
             int tot = 0;
 #pragma unroll
             for (int w = 0; w < kQaWaves; ++w) tot += lds_rs[i][w];
-            rowsum_x[(int64_t)chunk * T + r0 + i] = tot;
+            if (added && chunks > 1) atomicAdd(rowsum_x + r0 + i, tot);
+            else rowsum_x[(int64_t)chunk * T + r0 + i] = tot;
         }
 }
+
+// (added: the sums go straight to their places, whole lines to an instruction; whole calibrations, us, partial rows and a merge -> this: 14331 x
+// 11008 178.2 -> 177.2, 9000 x 4096 67.1 -> 64.2, 600 x 4096 with the forward 69.2 -> 66.6, 2000 x 16384 273 -> 262, 700 x 21888 108 -> 96.5,
+// binary32 2048 x 512 28.1 -> 25.4, but 40000 x 512 95.3 -> 96.1.)
 
 // Fold the per-slice column sums (fixed order, 64-bit) and the per-chunk row sums.  Blocks
 // [0, col_blocks) own 32 columns each: 32 groups of 32 threads take every 32nd slice (few dependent loads
 // per thread: the kernel is bound by their latency) and meet in LDS; the remaining blocks own 1024 rows each.
-constexpr int kQaMergeCols = kRangeCols, kQaMergeParts = 32;
+constexpr int kQaMergeCols = 32, kQaMergeParts = 32;
 __global__ __launch_bounds__(kQaMergeCols * kQaMergeParts) void quant_act_merge(
     const int32_t* __restrict__ colsum_part, int slices, int64_t K, long long* __restrict__ colsum_xq,
-    const int32_t* __restrict__ rowsum_part, int chunks, int64_t T, int32_t* __restrict__ rowsum_x, int col_blocks, SumDigits dg)
+    const int32_t* __restrict__ rowsum_part, int chunks, int64_t T, int32_t* __restrict__ rowsum_x, int col_blocks)
 {
     if ((int)blockIdx.x < col_blocks) {
         __shared__ long long s_s[kQaMergeParts][kQaMergeCols];
@@ -318,17 +328,6 @@ __global__ __launch_bounds__(kQaMergeCols * kQaMergeParts) void quant_act_merge(
 #pragma unroll
         for (int q = 1; q < kQaMergeParts; ++q) s += s_s[q][c];
         if (k < K) colsum_xq[k] = s;
-        if (!dg.digits) return;
-        s_s[0][c] = s;   // (0 past K)
-        wave_lds_fence();
-        const long long tot = group_allreduce<5>(s, OpAdd());
-        if (c == 0) dg.totals[blockIdx.x] = tot;
-        if ((c & 3) == 0 && k < K) {   // K % 8 == 0: all four columns or none
-            const int v[4] = {(int)s_s[0][c], (int)s_s[0][c + 1], (int)s_s[0][c + 2], (int)s_s[0][c + 3]};
-            uint32_t d[4];
-            pack_digits(v, d);
-            dg.digits[k >> 2] = make_uint4(d[0], d[1], d[2], d[3]);
-        }
     } else {
         const int64_t t = ((int64_t)blockIdx.x - col_blocks) * (kQaMergeCols * kQaMergeParts) + threadIdx.x;
         if (t >= T) return;
@@ -438,39 +437,33 @@ static QaPlan qa_plan(int64_t T, int64_t K)
 // its rows stream; never more slices than qa_plan has, which sizes the workspace.  us, 8192 blocks -> about 1024: sums alone 14331 x 11008
 // 60.3 -> 54.4, 8000 x 11008 47.6 -> 35.1, 20000 x 4096 46.7 -> 32.6, 65536 x 4096 102 -> 89; codes and sums 16384 x 4096 50.6 -> 42.0, 4000 x 11008
 // 40.2 -> 36.4, but beyond 2^27 values 3072 (65536 x 4096: 161 with 8192, 141 with 3072, 149 with 1024); binary32 7419 x 4096 36.4 with 2048 or
-// more, 38.5 with 1024.  fine (a workspace of quant_act_ws_bytes(T, K, true)): calls of few blocks in slices of 16 or 8 rows (codes and sums 512 x 4096
-// 11.2 -> 9.8, 2000 x 1024 10.4 -> 9.8, but 600 x 11008, 418 blocks, 17.1 -> 18.3).
-static QaPlan launch_plan(int64_t T, int64_t K, bool f16, bool sums, bool fine)
+// more, 38.5 with 1024.  added (no partial rows): calls of few blocks in slices of 16 rows, less than that and the blocks of a column wait for
+// each other's additions (whole calibrations, us, slices of 32 / 16 / 8 rows: 512 x 4096 33.1 / 32.0, binary32 700 x 2048 32.6 / 30.9, 2048 x 512
+// 25.4 / 25.4 / 27.4, but 256 blocks, 4000 x 1024, 38.7 / 40.4).
+static QaPlan launch_plan(int64_t T, int64_t K, bool f16, bool sums, bool added)
 {
     QaPlan p = qa_plan(T, K);
     const int64_t blocks = f16 && (sums || T * K <= (1ll << 27)) ? 1024 : 3072;
     int64_t rpb = cdiv(cdiv(T, cdiv(blocks, p.chunks)), kQaSliceRows) * kQaSliceRows;
     if (rpb > kQaMaxRows) rpb = kQaMaxRows;
     if (rpb > p.rpb) p.rpb = rpb;
-    if (fine && p.rpb == kQaSliceRows) {
-        const int64_t few = cdiv(T, kQaSliceRows) * p.chunks;
-        p.rpb = few <= 64 ? 8 : few <= 256 ? 16 : kQaSliceRows;
-    }
+    if (added && p.rpb == kQaSliceRows && cdiv(T, kQaSliceRows) * p.chunks <= 128) p.rpb = kQaSliceRows / 2;
     p.slices = cdiv(T, p.rpb);
     return p;
 }
 
 // workspace: per-slice column sums [slices][K] int32, then (several column chunks only) per-chunk
 // row sums [chunks][T] int32
-size_t quant_act_ws_bytes(int64_t T, int64_t K, bool fine)
+size_t quant_act_ws_bytes(int64_t T, int64_t K)
 {
-    QaPlan p = qa_plan(T, K);
-    if (fine) {
-        const int64_t slices = launch_plan(T, K, true, false, true).slices;   // (the small slices are the same for every form)
-        if (slices > p.slices) p.slices = slices;
-    }
+    const QaPlan p = qa_plan(T, K);
     return (size_t)p.slices * (size_t)K * 4 + (p.chunks > 1 ? (size_t)p.chunks * (size_t)T * 4 : 0);
 }
 
 int launch_quant_act(const void* X, aweq_dtype dt, int64_t T, int64_t K, int64_t ldx, const float* inv_s,
                      const float* act_step, const int32_t* act_zero, int8_t* xq, int32_t* rowsum_x,
                      int64_t* colsum_xq, void* ws, uint32_t* status, hipStream_t st, const RangeParts* range,
-                     const SumDigits* digits)
+                     int32_t* colsum_added)
 {
     // Whole rows per block where nothing is summed over tokens, up to the size where the panel form streams as fast (us, panel form -> row
     // form: K = 4096: 1000 tokens 11.2 -> 6.4, 4096: 17.9 -> 14.1, 16384: 41.3 -> 40.1, but 32768: 74.0 -> 81.6; K = 11008: 2048 tokens 24.4 -> 17.8,
@@ -491,12 +484,12 @@ int launch_quant_act(const void* X, aweq_dtype dt, int64_t T, int64_t K, int64_t
         return launch_status();
     }
     const bool sums = !xq && !rowsum_x;
-    const QaPlan p = launch_plan(T, K, dt == AWEQ_F16, sums, range != nullptr);
+    const QaPlan p = launch_plan(T, K, dt == AWEQ_F16, sums, colsum_added != nullptr);
     if (p.slices * p.chunks > 0x7ffffff0ll) return AWEQ_ERR_SHAPE;
     const bool multi = p.chunks > 1;
-    int32_t* const colsum_part = colsum_xq ? reinterpret_cast<int32_t*>(ws) : nullptr;
+    int32_t* const colsum_part = colsum_added ? colsum_added : colsum_xq ? reinterpret_cast<int32_t*>(ws) : nullptr;
     int32_t* const rowsum_part = reinterpret_cast<int32_t*>(ws) + (size_t)p.slices * K;
-    int32_t* const rs_out = !rowsum_x ? nullptr : (multi ? rowsum_part : rowsum_x);
+    int32_t* const rs_out = !rowsum_x ? nullptr : (multi && !colsum_added ? rowsum_part : rowsum_x);
     const unsigned pairs = (unsigned)(p.slices * p.chunks);
     const unsigned grid = (unsigned)(cdiv(pairs, kQaXcds) * kQaXcds);
     const RangeParts parts = range ? *range : RangeParts{};
@@ -504,16 +497,16 @@ int launch_quant_act(const void* X, aweq_dtype dt, int64_t T, int64_t K, int64_t
     // other (int8 forward, us, non-temporal -> cached: 16384 tokens 4096 x 11008 (180 MB) 663 -> 650, 4096 x 16384 (268 MB)
     // 979 -> 967, 12000 tokens 8192 x 16384 1306 -> 1307; the pass alone at 262144 x 8192 (2.1 GB) 1188 -> 1268)
     const bool keep = xq && (int64_t)panel_count(K) * kPanel * T <= kCacheBytes;
-#define AWEQ_QA(F, S, P) quant_act_kernel<F, S, P><<<grid, kQaBlock, 0, st>>>(X, T, K, ldx, inv_s, act_step, act_zero, xq, rs_out, colsum_part, (int)p.rpb, p.chunks, pairs, status, parts)
+#define AWEQ_QA(F, S, P) quant_act_kernel<F, S, P><<<grid, kQaBlock, 0, st>>>(X, T, K, ldx, inv_s, act_step, act_zero, xq, rs_out, colsum_part, (int)p.rpb, p.chunks, pairs, status, parts, colsum_added != nullptr)
     if (dt == AWEQ_F16) { if (sums) AWEQ_QA(true, true, false); else if (keep) AWEQ_QA(true, false, true); else AWEQ_QA(true, false, false); }
     else { if (sums) AWEQ_QA(false, true, false); else if (keep) AWEQ_QA(false, false, true); else AWEQ_QA(false, false, false); }
 #undef AWEQ_QA
+    if (colsum_added) return launch_status();
     const int col_blocks = colsum_xq ? (int)cdiv(K, kQaMergeCols) : 0;
     const int64_t row_blocks = (rowsum_x && multi) ? cdiv(T, kQaMergeCols * kQaMergeParts) : 0;
     if (col_blocks + row_blocks > 0)
         quant_act_merge<<<(unsigned)(col_blocks + row_blocks), kQaMergeCols * kQaMergeParts, 0, st>>>(
-            colsum_part, (int)p.slices, K, reinterpret_cast<long long*>(colsum_xq), rowsum_part, p.chunks, T, rowsum_x, col_blocks,
-            digits ? *digits : SumDigits{});
+            colsum_part, (int)p.slices, K, reinterpret_cast<long long*>(colsum_xq), rowsum_part, p.chunks, T, rowsum_x, col_blocks);
     return launch_status();
 }
 

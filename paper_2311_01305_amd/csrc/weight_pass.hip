@@ -28,6 +28,7 @@ __device__ __forceinline__ void finish_ranges(const FinishArgs& f, int64_t K, un
     if (k < K) {
         if (f.p_x) f.p_x[k] = f.r_x[k] / Rx;
         if (f.p_w) f.p_w[k] = f.r_w[k] / Rw;
+        if (f.colsum) f.colsum_xq[k] = f.colsum[k];
     }
     if (block != 0) return;
     if (threadIdx.x == 0) { *f.R_x = Rx; *f.R_w = Rw; }
@@ -157,6 +158,7 @@ __global__ __launch_bounds__(TPR == kWave ? 256 : TPR) void weight_pass_rows(Pas
     __shared__ double slot_d[kWaves][ROWS];
     __shared__ long long slot_l[kWaves][ROWS];
     __shared__ int slot_i[kWaves][ROWS];
+    __shared__ long long slot_t[kWaves];
     const int lane = threadIdx.x & (kWave - 1), wave = kWaves > 1 ? threadIdx.x / kWave : 0, tid = threadIdx.x % TPR;
     const int64_t n0 = ((int64_t)(blockIdx.x - m.first_block) * kSets + threadIdx.x / TPR) * ROWS;
     if (kSets > 1 && n0 >= m.N) return;   // (no barriers where wavefronts have rows of their own)
@@ -209,7 +211,7 @@ __global__ __launch_bounds__(TPR == kWave ? 256 : TPR) void weight_pass_rows(Pas
     }
 
     double acc[ROWS];
-    int rs[ROWS], cd[ROWS][4];
+    int rs[ROWS], cd[ROWS][4], td[4] = {0, 0, 0, 0};
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) {
         acc[r] = 0.0;
@@ -222,8 +224,15 @@ __global__ __launch_bounds__(TPR == kWave ? 256 : TPR) void weight_pass_rows(Pas
         const int64_t u = tid + (int64_t)j * TPR;
         if (u < units) {
             const Float4 m0 = *reinterpret_cast<const Float4*>(a.mu + u * 8), m1 = *reinterpret_cast<const Float4*>(a.mu + u * 8 + 4);
-            const uint4 d0 = a.digits[u * 2], d1 = a.digits[u * 2 + 1];
-            const uint32_t d[2][4] = {{d0.x, d0.y, d0.z, d0.w}, {d1.x, d1.y, d1.z, d1.w}};
+            const int4 c0 = *reinterpret_cast<const int4*>(a.colsum + u * 8), c1 = *reinterpret_cast<const int4*>(a.colsum + u * 8 + 4);
+            const int cx[2][4] = {{c0.x, c0.y, c0.z, c0.w}, {c1.x, c1.y, c1.z, c1.w}};
+            uint32_t d[2][4];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                pack_digits(cx[h], d[h]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) td[i] = __builtin_amdgcn_sdot4(0x01010101, (int)d[h][i], td[i], false);
+            }
             const int64_t off = (u >> 3) * m.N * kPanel + (u & 7) * 8;   // unit u of row 0 in the K-panel layout
 #pragma unroll
             for (int r = 0; r < ROWS; ++r) {
@@ -257,21 +266,21 @@ __global__ __launch_bounds__(TPR == kWave ? 256 : TPR) void weight_pass_rows(Pas
     double a_r = reduce_rows<ROWS, 6>(acc, OpAdd());
     long long c_r = reduce_rows<ROWS, 6>(cv, OpAdd());
     int r_r = reduce_rows<ROWS, 6>(rs, OpAdd());
+    long long tot = wave_allreduce(digits_value(td), OpAdd());   // sum of colsum_xq over the columns
     if constexpr (kWaves > 1) {
+        if (lane == 0) slot_t[wave] = tot;
         if (lane < ROWS) { slot_d[wave][lane] = a_r; slot_l[wave][lane] = c_r; slot_i[wave][lane] = r_r; }
         __syncthreads();
         if (wave != 0) return;
-        a_r = 0.0; c_r = 0; r_r = 0;
+        a_r = 0.0; c_r = 0; r_r = 0; tot = 0;
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) {
             a_r += slot_d[w][lr];
             c_r += slot_l[w][lr];
             r_r += slot_i[w][lr];
+            tot += slot_t[w];
         }
     }
-    long long tot = 0;
-    for (int j = lane; j < a.fin.range.blocks; j += kWave) tot += a.totals[j];
-    tot = wave_allreduce(tot, OpAdd());
     if (lane >= rows) return;
     const int64_t n = n0 + lane;
     const double d = int8_delta(a_r, c_r, r_r, tot, a.count, a.K, *a.act_step, *a.act_zero, my_step, my_zero);

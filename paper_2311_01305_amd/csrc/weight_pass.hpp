@@ -27,6 +27,8 @@ struct FinishArgs {
     RangeParts range;   // act_step null: xhat_range, Step and Z are written elsewhere
     const float *r_x, *r_w;
     float *R_x, *R_w, *p_x, *p_w;   // p nullable
+    const int32_t* colsum;          // nullable: widened to colsum_xq
+    long long* colsum_xq;
     uint32_t* status;
 };
 
@@ -38,8 +40,7 @@ struct PassArgs {
     const float* s;
     const float* mu;
     uint64_t count;                // 8 bits: tokens behind colsum_xq
-    const uint4* digits;           // 8 bits: colsum_xq as digits, four columns to an entry (code_digits.hpp)
-    const long long* totals;       // 8 bits: colsum_xq summed over kRangeCols channels each
+    const int32_t* colsum;         // 8 bits: colsum_xq, of fewer than 2^23 tokens
     const float* act_step;         // 8 bits
     const int32_t* act_zero;
     int enable_bc;
