@@ -7,10 +7,11 @@
 //   2. merge of the partial rows, ranges, Eq. 10's scales and the pieces of the ranges over all channels, in one launch;
 //   3. int8 path: the activation quantizer, whose blocks find Step and Z from the pieces and add their sums up;
 //   4. one pass over every weight: fold, quantise, correct the bias (weight_pass.hip); blocks beside it finish R and p;
-//   5. forward: the GEMMs, without column sums (the pass has them).
+//   5. forward: the GEMMs, without column sums (the pass has them); in one launch where several layers have one width.
 // Calls that the pass does not take (one scale for the tensor, groups or widths it has no form for) run stages 2b - 5 as they are
 // behind 1 and 2; buffers that overlap, or a workspace of the stages' own size, take the stages one by one.
 #include "col_stats.hpp"
+#include "gemm_i8.hpp"
 #include "quant_act.hpp"
 #include "weight_pass.hpp"
 
@@ -287,6 +288,23 @@ static int run_front(const aweq_calib_layer& l, const aweq_calib_weight* w, int 
     return launch_status();
 }
 
+// The forward of layers of one width with binary16 outputs in one launch.  false: nothing was launched.
+static bool group_forward(const aweq_calib_layer& l, const aweq_calib_weight* w, int n, hipStream_t st)
+{
+    if (n < 2 || l.dt != AWEQ_F16 || (w[0].N % 4) != 0) return false;
+    GroupArgs g = {};
+    g.A = l.xq; g.T = l.T; g.N = w[0].N; g.K = l.K; g.out_f16 = 1; g.ldo = w[0].N;
+    g.act_step = l.act_step; g.act_zero = l.act_zero; g.rowsum_x = l.rowsum_x; g.status = l.status;
+    for (int i = 0; i < n; ++i) {
+        const aweq_calib_weight& v = w[i];
+        if (v.N != g.N || v.out_i32 || !v.out_deq || !aligned16(v.out_deq) || !aligned16(v.step_w) || !aligned16(v.zero_w) || !aligned16(v.rowsum_w) ||
+            (v.bias_in && !aligned16(v.bias_in)))
+            return false;
+        g.m[i] = {reinterpret_cast<const int8_t*>(v.codes), v.out_deq, v.step_w, v.zero_w, v.rowsum_w, v.bias_in};
+    }
+    return launch_gemm_i8_group(g, n, st) == AWEQ_OK;
+}
+
 static int run_calibration(const aweq_calib_layer& l, const aweq_calib_weight* w, int n, void* stream)
 {
     hipStream_t st = as_stream(stream);
@@ -320,6 +338,7 @@ static int run_calibration(const aweq_calib_layer& l, const aweq_calib_weight* w
                       w[i].bias_out, l.forward ? reinterpret_cast<long long*>(w[i].colsum_acc) : nullptr, w[i].N, w[i].ldw, w[i].ldwh, 0u};
         rc = launch_weight_pass(a, l.dt, l.bits, l.group, st);
         if (rc != AWEQ_OK) return rc;
+        if (l.w8a8 && l.forward && group_forward(l, w, n, st)) return launch_status();
         for (int i = 0; l.w8a8 && l.forward && i < n; ++i) {
             if (!w[i].out_i32 && !w[i].out_deq) continue;
             rc = aweq_w8a8_gemm(l.xq, AWEQ_I8, l.T, l.K, l.K, nullptr, l.act_step, l.act_zero, nullptr, l.rowsum_x, nullptr,

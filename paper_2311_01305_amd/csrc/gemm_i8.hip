@@ -298,10 +298,12 @@ __device__ __forceinline__ void wait_vm()
 // fly while the results are stored.
 // EPI (with DEQ == 2): bit 0 collects the column statistics of the binary16 output, bit 1 quantises
 // it for the next layer; STORE = false keeps the output itself from being written.
-template <int MI, bool I32, int DEQ, bool COLSUM, int EPI = 0, bool STORE = true>
-__global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
+// Args: GemmArgs, or GroupArgs for several weights.
+template <int MI, bool I32, int DEQ, bool COLSUM, int EPI = 0, bool STORE = true, class Args = GemmArgs>
+__global__ __launch_bounds__(kThreads) void gemm_i8_fast(Args g)
 {
     using TL = Tile<MI>;
+    constexpr bool kGroup = std::is_same<Args, GroupArgs>::value;
     // The epilogue's short forms.  Not with the accumulators among the outputs, which the general form stores as fast or faster (us, short ->
     // general: 3515 tokens 4468 x 2008 with sums 50.4 -> 48.5, 5000 x 2500 x 1000 with sums 31.3 -> 30.2, with binary16 output too 46.3 -> 44.2,
     // 4096 x 4096 x 4096 with sums 68.2 -> 67.6); the statistics epilogue, and the quantising one that also stores 256-token tiles, have no
@@ -333,6 +335,7 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
     const int8_t* srcA;     // the tile's rows in the panel being fetched
     const int8_t* srcB;
     int64_t m0, n0;
+    int member = 0;         // (kGroup) the weight of that tile
 
 #define DMA_A(q) dma16(srcA, oa[q], dst_slot + wave_offA + (q) * 1024)
 #define DMA_B(q) dma16(srcB, ob[q], dst_slot + wave_offB + (q) * 1024)
@@ -340,6 +343,10 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
     auto start_tile = [&](int tm, int tn) {
         // (wave-uniform by construction; say so, the panel base addresses live in scalar registers)
         m0 = (int64_t)__builtin_amdgcn_readfirstlane(tm) * TL::kRows;
+        if constexpr (kGroup) {
+            member = __builtin_amdgcn_readfirstlane(tn / g.member_tiles);
+            tn -= member * g.member_tiles;
+        }
         n0 = (int64_t)__builtin_amdgcn_readfirstlane(tn) * BN;
         // rows past the edge re-read the last valid row; their results are never stored
         int lane_ = lane;
@@ -352,7 +359,8 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
             ob[q] = (uint32_t)(min(wave * 32 + sub, last_n) * (int)kPanel + chunk * 16);
         }
         srcA = g.A + m0 * kPanel;
-        srcB = g.B + n0 * kPanel;
+        if constexpr (kGroup) srcB = g.m[member].B + n0 * kPanel;
+        else srcB = g.B + n0 * kPanel;
         for (int h = 0; h < pre; ++h) {
             const uint32_t dst_slot = lds0 + h * kSlot;
             DMA_A(0); DMA_B(0);
@@ -378,6 +386,7 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
 
     for (;;) {
         const int64_t cm0 = m0, cn0 = n0;   // the tile being multiplied
+        const int cmember = member;
         v16i acc[MI][2];
 #pragma unroll
         for (int i = 0; i < MI; ++i)
@@ -514,6 +523,16 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
         const int64_t n = cn0 + wn * 64 + rd_c * 4;                // this lane's four channels
         const bool n_ok = n < g.N;                                 // N % 4 == 0: all four or none
 
+        const float* step_w;
+        const int32_t *zero_w, *rowsum_w;
+        const float* bias;
+        void* out_deq;
+        if constexpr (kGroup) {
+            const GroupArgs::Member& o = g.m[cmember];
+            step_w = o.step_w; zero_w = o.zero_w; rowsum_w = o.rowsum_w; bias = o.bias; out_deq = o.out_deq;
+        } else {
+            step_w = g.step_w; zero_w = g.zero_w; rowsum_w = g.rowsum_w; bias = g.bias; out_deq = g.out_deq;
+        }
         // everything the epilogue reads from memory is requested before the next tile's panels,
         // so that waiting for it does not wait for them
         int rsx[MI / 2] = {};   // row sums of this wave's 32 MI tokens, one per lane and 64: token 64 h + lane
@@ -539,22 +558,22 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
             if (n_ok) {
                 v4i zw4;
                 if (g.w_per_tensor) {
-                    const float s0 = g.step_w[0];
-                    const int z0 = g.zero_w[0];
+                    const float s0 = step_w[0];
+                    const int z0 = zero_w[0];
                     sw = Float4{{s0, s0, s0, s0}};
                     zw4 = v4i{z0, z0, z0, z0};
                 } else {
-                    sw = *reinterpret_cast<const Float4*>(g.step_w + n);
-                    zw4 = *reinterpret_cast<const v4i*>(g.zero_w + n);
+                    sw = *reinterpret_cast<const Float4*>(step_w + n);
+                    zw4 = *reinterpret_cast<const v4i*>(zero_w + n);
                 }
-                const v4i rw4 = *reinterpret_cast<const v4i*>(g.rowsum_w + n);
+                const v4i rw4 = *reinterpret_cast<const v4i*>(rowsum_w + n);
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
                     nzw[c] = 128 - zw4[c];
                     if (zw4[c] < 0 || zw4[c] > 255) est |= AWEQ_ST_ZEROPOINT;
                     cn[c] = 0u - (unsigned)g.K * (unsigned)zx * (unsigned)nzw[c] - (unsigned)zx * (unsigned)rw4[c];
                 }
-                if (g.bias) bs = *reinterpret_cast<const Float4*>(g.bias + n);
+                if (bias) bs = *reinterpret_cast<const Float4*>(bias + n);
             }
             // pin the values in registers here: the compiler's wait for them then sits before the
             // panel requests below, which it cannot see, instead of behind them
@@ -618,8 +637,8 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
             // over tokens 3900 x 4092 x 1024 28.3 -> 29.7, and where an eighth of the compute units have no tile less is written at a time:
             // 240 tiles 3800 x 4092 x 1024 / 4096 26.3 -> 25.4 / 61.9 -> 61.2, 208 tiles 3300 x 4092 23.2 -> 23.75 / 55.7 -> 55.9, 144 tiles
             // 2300 x 4092 19.1 -> 20.8 / 44.6 -> 46.0)
-            const bool shared = kMayShare && ((reinterpret_cast<uintptr_t>(g.out_deq) | (uintptr_t)(g.ldo * 2)) & 63) != 0 &&
-                                (((int)g.T + TL::kRows - 1) / TL::kRows) * (((int)g.N + BN - 1) / BN) > 224;
+            const bool shared = kMayShare && ((reinterpret_cast<uintptr_t>(out_deq) | (uintptr_t)(g.ldo * 2)) & 63) != 0 &&
+                                g.tiles_m * g.tiles_n > 224;
             if (__builtin_amdgcn_ballot_w64(odd && n_ok) == 0 && g.ldo < (1 << 28) && (!COLSUM || g.K < 32768))
                 form = !inside ? kEdge : shared ? kShared : kPlain;
         }
@@ -648,7 +667,7 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
         const bool yq_pad = (EPI & 2) != 0 && !n_ok && cn0 + wn * 64 < g.N;   // zero fill of the last panel
         // the short forms: wave-uniform row pointers that move on by four tokens, the lane's offset from them, its tokens inside
         const int64_t wave_t = cm0 + wm * (32 * MI), wave_n = cn0 + wn * 64;
-        char* row_deq = DEQ != 0 && STORE ? reinterpret_cast<char*>(g.out_deq) + (wave_t * g.ldo + wave_n) * (DEQ == 1 ? 4 : 2) : nullptr;
+        char* row_deq = DEQ != 0 && STORE ? reinterpret_cast<char*>(out_deq) + (wave_t * g.ldo + wave_n) * (DEQ == 1 ? 4 : 2) : nullptr;
         char* row_yq = (EPI & 2) != 0 ? reinterpret_cast<char*>(g.yq) + ((wave_n >> 6) * g.T + wave_t) * kPanel : nullptr;
         const uint32_t lane_yq = (uint32_t)(rd_r * (int)kPanel + rd_c * 4);
         const uint32_t lane_elt = (uint32_t)rd_r * (uint32_t)g.ldo + (uint32_t)rd_c * 4;
@@ -867,7 +886,7 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
                                 }
                                 h4 oh = {(_Float16)y[0], (_Float16)y[1], (_Float16)y[2], (_Float16)y[3]};
                                 if constexpr (STORE)
-                                    __builtin_nontemporal_store(oh, reinterpret_cast<h4*>(reinterpret_cast<_Float16*>(g.out_deq) + t * g.ldo + n));
+                                    __builtin_nontemporal_store(oh, reinterpret_cast<h4*>(reinterpret_cast<_Float16*>(out_deq) + t * g.ldo + n));
                                 if constexpr ((EPI & 1) != 0) {
 #pragma unroll
                                     for (int c = 0; c < 4; ++c) {
@@ -907,7 +926,7 @@ __global__ __launch_bounds__(kThreads) void gemm_i8_fast(GemmArgs g)
                             } else {
                                 typedef float f4 __attribute__((ext_vector_type(4)));
                                 f4 of = {y[0], y[1], y[2], y[3]};
-                                __builtin_nontemporal_store(of, reinterpret_cast<f4*>(reinterpret_cast<float*>(g.out_deq) + t * g.ldo + n));
+                                __builtin_nontemporal_store(of, reinterpret_cast<f4*>(reinterpret_cast<float*>(out_deq) + t * g.ldo + n));
                             }
                         }
                         if constexpr (COLSUM) {
@@ -1030,6 +1049,35 @@ static int plan_tiled(GemmArgs& g, bool& half, double& cost, int64_t& blocks)
            cdiv(g.T, BM) * cdiv(g.N, BM) <= 6 * 256;
     if (half) { g = h; cost = kHalfTileCost * (double)rounds_of(h); }
     return AWEQ_OK;
+}
+
+// Launches of their own leave compute units without a tile in each one's last round, and each has its ramp and its last epilogue: kLaunchCost us.
+// (us, whole calibrations, a launch each -> one: three weights 4096 x 4096 of 512 tokens 142 -> 115, 2048 tokens 193 -> 186, 8192 tokens 422 -> 412, 2048 x
+// 2048 of 700 tokens 79.0 -> 58.1, two 1024 x 1024 of 2500 tokens 52.7 -> 37.8, two 8192 x 8192 of 32768 tokens within the spread)
+constexpr double kLaunchCost = 4.0;
+int launch_gemm_i8_group(GroupArgs& g, int n, hipStream_t st)
+{
+    const int64_t N = g.N;
+    g.member_tiles = (int)cdiv(N, BN);
+    bool half = false, half_one = false;
+    double cost = 0.0, one = 0.0;
+    int64_t blocks = 0;
+    GemmArgs a = g;
+    int rc = plan_tiled(a, half_one, one, blocks);
+    if (rc != AWEQ_OK) return rc;
+    g.N = (int64_t)n * g.member_tiles * BN;
+    rc = plan_tiled(g, half, cost, blocks);
+    g.N = N;
+    if (rc != AWEQ_OK) return rc;
+    double each = kTiledRoundCost * one;
+    const FewPlan few = plan_few(g.T, N);
+    const MidPlan mid = plan_mid(g.T, N);
+    if (few.cost < each) each = few.cost;
+    if (mid.cost < each) each = mid.cost;
+    if (kTiledRoundCost * cost > n * each + (n - 1) * kLaunchCost * 8192.0 / (double)g.K) return AWEQ_ERR_SHAPE;
+    const void* fn = half ? reinterpret_cast<const void*>(fast::gemm_i8_fast<2, false, 2, false, 0, true, GroupArgs>)
+                          : reinterpret_cast<const void*>(fast::gemm_i8_fast<4, false, 2, false, 0, true, GroupArgs>);
+    return launch_persistent(fn, fast::kThreads, half ? fast::Tile<2>::kLds : fast::Tile<4>::kLds, &g, g.n_ids, st);
 }
 
 static void clear_fused(GemmArgs& g)

@@ -35,6 +35,25 @@ struct GemmArgs : TileWalk {
     uint32_t* status;
 };
 
+// Several weights of N channels each that multiply the same codes, in one launch of the tiled kernel: the tile columns of one after the other's
+// (TileWalk's), each weight with its own operands and output; B, out_deq, step_w, zero_w, rowsum_w and bias above are not read.
+constexpr int kGroupMost = 4;
+struct GroupArgs : GemmArgs {
+    struct Member {
+        const int8_t* B;
+        void* out_deq;
+        const float* step_w;
+        const int32_t* zero_w;
+        const int32_t* rowsum_w;
+        const float* bias;
+    } m[kGroupMost];
+    int member_tiles;   // tile columns of a weight
+};
+
+// The binary16 outputs of n weights of N channels (g: what they share; K, T and A among it) in one launch, where it is modelled to take less than a
+// launch each; AWEQ_ERR_SHAPE, and nothing launched, where not
+int launch_gemm_i8_group(GroupArgs& g, int n, hipStream_t st);
+
 // The few-token kernel's tile for a shape, and what it is modelled to take in the unit of kTiledRoundCost
 struct FewPlan {
     int tile;      // index of the instantiation
