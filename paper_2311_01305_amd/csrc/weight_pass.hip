@@ -123,9 +123,68 @@ __device__ __forceinline__ void fold_unit(Unit<F16>& u, const Float4& s0, const 
     u.set(x);
 }
 
+// Extremes of a lane's elements of one row.  Binary16: two pairs to an operation, which hands a NaN on; then they are taken again without it.
+// (With a minimum, a maximum and a test for NaN of every pair, and every lane's own elements held against Step, it had two operations an element
+// more, and the pass is bound by its vector operations: us, whole calibrations, before -> this: 1000 tokens 11008 x 4096 79.6 -> 76.2, 2000 tokens
+// 4096 x 16384 259 -> 249, 20000 tokens 8192 x 8192 215 -> 211, INT4 65536 tokens 11008 x 4096 145.9 -> 142.7, INT3 2048 tokens 4096 x 11008
+// 80.6 -> 76.9; the byte conversion that clamps among it.)
+template <bool F16> struct LaneExtremes;
+template <>
+struct LaneExtremes<true> {
+    f16x2 lo = {(_Float16)INFINITY, (_Float16)INFINITY}, hi = {(_Float16)-INFINITY, (_Float16)-INFINITY};
+    __device__ __forceinline__ void add(const Unit<true>& u)
+    {
+#pragma unroll
+        for (int i = 0; i < 4; i += 2) {
+            lo = __builtin_elementwise_minimum(__builtin_elementwise_minimum(lo, u.raw.h[i]), u.raw.h[i + 1]);
+            hi = __builtin_elementwise_maximum(__builtin_elementwise_maximum(hi, u.raw.h[i]), u.raw.h[i + 1]);
+        }
+    }
+    __device__ __forceinline__ void add_numbers(const Unit<true>& u)
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { lo = hmin2(lo, u.raw.h[i]); hi = hmax2(hi, u.raw.h[i]); }
+    }
+};
+template <>
+struct LaneExtremes<false> {
+    float lo = INFINITY, hi = -INFINITY, bad = 0.0f;
+    __device__ __forceinline__ void add(const Unit<false>& u)
+    {
+        float x[8];
+        u.get(x);
+        minmax8(x, lo, hi);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) bad = __builtin_fmaf(x[i], 0.0f, bad);   // 0, or NaN from then on
+    }
+    __device__ __forceinline__ void add_numbers(const Unit<false>&) {}
+};
+// a NaN among this lane's elements of any row (binary32: or an infinity; either way a longer path with the same results)
+template <int ROWS>
+__device__ __forceinline__ bool any_nan(const LaneExtremes<true> (&ex)[ROWS])
+{
+    f16x2 s = ex[0].lo;
+#pragma unroll
+    for (int r = 1; r < ROWS; ++r) s = __builtin_elementwise_minimum(s, ex[r].lo);
+    return s.x != s.x || s.y != s.y;
+}
+template <int ROWS>
+__device__ __forceinline__ bool any_nan(const LaneExtremes<false> (&ex)[ROWS])
+{
+    float s = ex[0].bad;
+#pragma unroll
+    for (int r = 1; r < ROWS; ++r) s += ex[r].bad;
+    return s != s;
+}
+// Whether a row whose elements lie in `range` (numbers; no NaN beside them) may take the screened quotient
+__device__ __forceinline__ bool may_screen(float2 range, const ActParams& p)
+{
+    return p.screen && fmaxf(fabsf(range.x), fabsf(range.y)) * p.rstep < 8388608.0f;
+}
+
 // lowest and highest element of row (lane % ROWS), over groups of 2^LEVELS lanes
 template <int LEVELS, int ROWS>
-__device__ __forceinline__ float2 rows_extremes(const Extremes<true> (&ex)[ROWS])
+__device__ __forceinline__ float2 rows_extremes(const LaneExtremes<true> (&ex)[ROWS])
 {
     f16x2 v[ROWS];   // minimum, and the maximum negated: both in one packed operation
 #pragma unroll
@@ -137,7 +196,7 @@ __device__ __forceinline__ float2 rows_extremes(const Extremes<true> (&ex)[ROWS]
     return make_float2((float)m.x, -(float)m.y);
 }
 template <int LEVELS, int ROWS>
-__device__ __forceinline__ float2 rows_extremes(const Extremes<false> (&ex)[ROWS])
+__device__ __forceinline__ float2 rows_extremes(const LaneExtremes<false> (&ex)[ROWS])
 {
     float lo[ROWS], hi[ROWS];
 #pragma unroll
@@ -175,7 +234,7 @@ __global__ __launch_bounds__(TPR == kWave ? 256 : TPR) void weight_pass_rows(Pas
             for (int r = 0; r < ROWS; ++r) load_unit<LINES>(reg[r][j], row_at<F16>(m.W, n0 + min(r, rows - 1), m.ldw), u);
         }
     }
-    Extremes<F16> ex[ROWS];
+    LaneExtremes<F16> ex[ROWS];
 #pragma unroll
     for (int j = 0; j < UPT; ++j) {
         const int64_t u = tid + (int64_t)j * TPR;
@@ -190,6 +249,16 @@ __global__ __launch_bounds__(TPR == kWave ? 256 : TPR) void weight_pass_rows(Pas
         }
     }
     const int lr = lane % ROWS;
+    const bool nan = __any(any_nan(ex));
+    if (F16 && nan) {
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            ex[r] = LaneExtremes<F16>();
+#pragma unroll
+            for (int j = 0; j < UPT; ++j)
+                if (tid + (int64_t)j * TPR < units) ex[r].add_numbers(reg[r][j]);
+        }
+    }
     float2 range = rows_extremes<6>(ex);
     if constexpr (kWaves > 1) {
         if (lane < ROWS) slot_ex[wave][lane] = range;
@@ -201,14 +270,11 @@ __global__ __launch_bounds__(TPR == kWave ? 256 : TPR) void weight_pass_rows(Pas
     int my_zero;
     qparams(range.x, range.y, 8, my_step, my_zero, st);
     if (wave == 0 && lane < rows) { m.step[n0 + lane] = my_step; m.zero[n0 + lane] = my_zero; }
-    const ActParams mine = quot_params(my_step, my_zero);
+    ActParams mine = quot_params(my_step, my_zero);
+    mine.screen = !nan && may_screen(range, mine);
     ActParams p[ROWS];
-    bool screened[ROWS];
 #pragma unroll
-    for (int r = 0; r < ROWS; ++r) {
-        p[r] = params_of_lane(mine, r);
-        screened[r] = __all(may_screen(ex[r], p[r]));
-    }
+    for (int r = 0; r < ROWS; ++r) p[r] = params_of_lane(mine, r);
 
     double acc[ROWS];
     int rs[ROWS], cd[ROWS][4], td[4] = {0, 0, 0, 0};
@@ -239,7 +305,7 @@ __global__ __launch_bounds__(TPR == kWave ? 256 : TPR) void weight_pass_rows(Pas
                 float x[8];
                 reg[r][j].get(x);
                 uint32_t w0, w1;
-                unit_words<8>(x, p[r], screened[r], w0, w1, st);
+                unit_words<8>(x, p[r], p[r].screen, w0, w1, st);
                 if (r < rows) *reinterpret_cast<uint2*>(m.codes + off + (n0 + r) * kPanel) = make_uint2(w0, w1);
                 rs[r] += unit_sum(w0, w1);
 #pragma unroll
@@ -314,12 +380,17 @@ __global__ __launch_bounds__(BLOCK, BLOCK == kWave ? 3 : 4) void weight_pass_gro
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) load_unit<LINES>(reg[r], row_at<F16>(m.W, n0 + min(r, rows - 1), m.ldw), u);   // (past the edge: the last row again, not stored)
         const Float4 s0 = *reinterpret_cast<const Float4*>(a.s + u * 8), s1 = *reinterpret_cast<const Float4*>(a.s + u * 8 + 4);
-        Extremes<F16> ex[ROWS];
+        LaneExtremes<F16> ex[ROWS];
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) {
             fold_unit<F16>(reg[r], s0, s1);
             if (r < rows) store_unit<LINES>(reg[r], const_cast<void*>(row_at<F16>(m.W_hat, n0 + r, m.ldwh)), u);
             ex[r].add(reg[r]);
+        }
+        const bool nan = __any(any_nan(ex));
+        if (F16 && nan) {
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) { ex[r] = LaneExtremes<F16>(); ex[r].add_numbers(reg[r]); }
         }
         const float2 range = rows_extremes<LEVELS>(ex);   // of row (lane % 4)
         float my_step;
@@ -331,12 +402,13 @@ __global__ __launch_bounds__(BLOCK, BLOCK == kWave ? 3 : 4) void weight_pass_gro
             m.step[gi] = my_step;
             m.zero[gi] = my_zero;
         }
-        const ActParams mine = quot_params(my_step, my_zero);
+        ActParams mine = quot_params(my_step, my_zero);
+        mine.screen = !nan && may_screen(range, mine);
         const ActParams p[ROWS] = {params_of_quad<0>(mine), params_of_quad<1>(mine), params_of_quad<2>(mine), params_of_quad<3>(mine)};
         const Float4 m0 = *reinterpret_cast<const Float4*>(a.mu + u * 8), m1 = *reinterpret_cast<const Float4*>(a.mu + u * 8 + 4);
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) {
-            const bool screened = __all(may_screen(ex[r], p[r]));
+            const bool screened = __all(p[r].screen);
             float x[8], diff[8];
             reg[r].get(x);
             uint32_t w0, w1;

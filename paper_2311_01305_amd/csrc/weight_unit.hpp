@@ -116,7 +116,7 @@ __device__ __forceinline__ bool may_screen(const Extremes<F16>& ex, const ActPar
     return p.screen && ex.finite() && (lo > hi || fmaxf(fabsf(lo), fabsf(hi)) * p.rstep < 8388608.0f);
 }
 
-// the codes of one unit as integral floats, for elements that may_screen accepts
+// the codes of one unit as integral floats (8 bits: not clamped yet), for elements that may_screen accepts
 template <int BITS>
 __device__ __forceinline__ void unit_codes(const float x[8], const ActParams& p, float u[8])
 {
@@ -140,6 +140,7 @@ __device__ __forceinline__ void unit_codes(const float x[8], const ActParams& p,
             u[i] = rintf(q) + zf;
         }
     }
+    if constexpr (BITS == 8) return;   // (the conversion to a byte clamps)
 #pragma unroll
     for (int i = 0; i < 8; ++i) u[i] = __builtin_amdgcn_fmed3f(u[i], 0.0f, qmax);
 }
