@@ -469,7 +469,8 @@ int launch_quant_act(const void* X, aweq_dtype dt, int64_t T, int64_t K, int64_t
     // form: K = 4096: 1000 tokens 11.2 -> 6.4, 4096: 17.9 -> 14.1, 16384: 41.3 -> 40.1, but 32768: 74.0 -> 81.6; K = 11008: 2048 tokens 24.4 -> 17.8,
     // 8192: 58.6 -> 57.9, but 16384: 100 -> 107; 8192 x 22016 106 -> 109; binary32 16000 x 4096 68.7 -> 64.5, 5000 x 11008 63.7 -> 56.8).  Narrow
     // rows leave part of a block idle: 4097 x 1032 11.6 -> 9.5, but 8192 x 1032 13.2 -> 15.2.  One row per block
-    // up to 256 tokens, two up to 1024 (1024 tokens, 1 / 2 / 4 rows: 6.8 / 5.5 / 6.0).  Rows of up to 512 columns, one chunk of the panel
+    // up to 256 tokens, two up to 1536, 768 blocks, three a compute unit, in place of 384 (4 / 2 rows: 1030 x 4096 5.8 / 5.0, 1536 x 4096 6.75 / 5.9,
+    // 1536 x 11008 15.6 / 13.5, binary32 1500 x 4096 7.9 / 7.0, but 1700 x 4096 6.95 / 7.05; 1 / 2 rows: 600 x 4096 4.3 / 4.25).  Rows of up to 512 columns, one chunk of the panel
     // form, which then needs no merge: up to 2048 tokens where a row's sum is asked for (K = 64 / 512, 2048 tokens 5.5 -> 4.8 / 7.3 -> 4.9,
     // 2500 tokens 5.6 -> 7.0 / 7.3 -> 7.1, binary32 4096 tokens 5.3 -> 7.6 / 8.4 -> 9.9;
     // without the sums 2758 tokens K = 448 6.3 -> 4.8, 4051 tokens K = 120 5.9 -> 5.2).  Not where an output lies over what other
@@ -478,8 +479,8 @@ int launch_quant_act(const void* X, aweq_dtype dt, int64_t T, int64_t K, int64_t
     if (!range && !colsum_xq && xq && aligned16(inv_s) && T <= rows_most &&
         !overlap({{rowsum_x, T * 4}, {xq, T * panel_count(K) * kPanel}}, {matrix_span(X, T, K, ldx, dtype_size(dt)), {inv_s, K * 4}, {act_step, 4}, {act_zero, 4}})) {
 #define AWEQ_QR(F, R) quant_act_rows<F, R><<<(unsigned)cdiv(T, R), kQrBlock, 0, st>>>(X, T, K, ldx, inv_s, act_step, act_zero, xq, rowsum_x, status)
-        if (dt == AWEQ_F16) { if (T <= 256) AWEQ_QR(true, 1); else if (T <= 1024) AWEQ_QR(true, 2); else AWEQ_QR(true, 4); }
-        else { if (T <= 256) AWEQ_QR(false, 1); else if (T <= 1024) AWEQ_QR(false, 2); else AWEQ_QR(false, 4); }
+        if (dt == AWEQ_F16) { if (T <= 256) AWEQ_QR(true, 1); else if (T <= 1536) AWEQ_QR(true, 2); else AWEQ_QR(true, 4); }
+        else { if (T <= 256) AWEQ_QR(false, 1); else if (T <= 1536) AWEQ_QR(false, 2); else AWEQ_QR(false, 4); }
 #undef AWEQ_QR
         return launch_status();
     }
