@@ -207,7 +207,7 @@ __device__ __forceinline__ float2 rows_extremes(const LaneExtremes<false> (&ex)[
 // ---- 8 bits, one (Step, Z) per output channel.  TPR threads hold ROWS rows in UPT units a row and thread, all requested before the first
 // is used.  Lane r of each wavefront forms the parameters of row r (three divisions once instead of ROWS times).
 template <bool F16, bool LINES, int TPR, int UPT, int ROWS>
-__global__ __launch_bounds__(TPR == kWave ? 256 : TPR) void weight_pass_rows(PassArgs a)
+__global__ __launch_bounds__(TPR == kWave ? 256 : TPR, TPR == 512 && UPT == 3 ? 4 : 1) void weight_pass_rows(PassArgs a)
 {
     constexpr int kThreads = TPR == kWave ? 256 : TPR, kSets = kThreads / TPR, kWaves = TPR / kWave;
     static_assert(kSets == 1 || kWaves == 1, "rows are reduced over a wavefront or over the block");
@@ -467,16 +467,21 @@ static void launch_rows(PassArgs& a, hipStream_t st)
 
 // Threads x units x rows of a block (us with the launch, W found in the memory-side cache where it fits): few registers, so that several
 // blocks of a compute unit are in different phases, and as many rows as those allow.  Binary16: 12288 x 4096 256 x 2 x 4 52.3, x 2 rows 53.0,
-// x 1 54.9, 64 x 8 x 2 57.6; 4096 x 11008 256 x 6 x 2 50.8, 512 x 3 x 4 53.0, 1024 x 2 x 4 71.6; 8192 x 8192 256 x 4 x 4 77.1, x 2 81.0,
+// x 1 54.9, 64 x 8 x 2 57.6; 4096 x 11008 256 x 6 x 2 50.8, 1024 x 2 x 4 71.6; 8192 x 8192 256 x 4 x 4 77.1, x 2 81.0,
 // 512 x 2 x 4 81.4, 1024 x 2 x 2 108; 8192 x 22016 512 x 6 x 2 215, x 1 236, x 4 251, 256 x 11 x 1 235.  Non-temporal reads and writes of whole
 // lines: 8192 x 8192 77.1 -> 68.5, 8192 x 22016 215 -> 202, 4096 x 11008 and 12288 x 4096 within 2 us; not in a cache 63.5 -> 60.2, 61.8 -> 59.6.
+// Binary16 of up to 12288 columns, with digits that four rows share, held to 128 registers (whole calibrations of 600 tokens, 256 x 6 x 2 -> 512 x 3 x 4:
+// 4096 x 11008 84.8 -> 83.9, 1000 x 10000 40.1 -> 38.6, 8192 x 12000 185 -> 182.5; with 130 registers 4096 x 11008 93.0; binary32 spills).
 template <bool F16, bool LINES>
 static void launch_rows_for(PassArgs& a, hipStream_t st)
 {
     if (a.K <= 1024) launch_rows<F16, LINES, 64, 2, 1>(a, st);
     else if (a.K <= 4096) launch_rows<F16, LINES, 256, 2, 4>(a, st);
     else if (a.K <= 8192) launch_rows<F16, LINES, 256, 4, F16 ? 4 : 2>(a, st);
-    else if (a.K <= 12288) launch_rows<F16, LINES, 256, 6, 2>(a, st);
+    else if (a.K <= 12288) {
+        if constexpr (F16) launch_rows<F16, LINES, 512, 3, 4>(a, st);
+        else launch_rows<F16, LINES, 256, 6, 2>(a, st);
+    }
     else launch_rows<F16, LINES, 512, 6, 2>(a, st);
 }
 
