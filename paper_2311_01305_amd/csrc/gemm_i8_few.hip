@@ -309,6 +309,9 @@ FewPlan plan_few(int64_t T, int64_t N)
 int launch_gemm_i8_few_quant(const GemmArgs& g, const FewPlan& p, const QuantIn& in, bool f16, hipStream_t st)
 {
 #define AWEQ_FQ(NT, D, Q) (g.T == 1 ? few::launch_tile<1, NT, D, Q, 1>(g, st, in) : g.T == 2 ? few::launch_tile<1, NT, D, Q, 2>(g, st, in) : few::launch_tile<1, NT, D, Q, 4>(g, st, in))
+    // Depth of the ring, by whether a compute unit has one workgroup (us, buffers that change from call to call, 3 / 4 / 6: one token 4096 x 4096
+    // 6.1 / 6.2 / 5.95, 4096 x 11008 11.35 / 11.55 / 11.95, three tokens 4096 x 4096 7.1 / 7.3, but 6000 x 6144 8.9 / 8.75)
+    if (p.tile == 0 && g.N <= 16 * 256) return f16 ? AWEQ_FQ(1, 3, 1) : AWEQ_FQ(1, 3, 2);
     if (p.tile == 0) return f16 ? AWEQ_FQ(1, 4, 1) : AWEQ_FQ(1, 4, 2);
     return f16 ? AWEQ_FQ(2, 3, 1) : AWEQ_FQ(2, 3, 2);
 #undef AWEQ_FQ
