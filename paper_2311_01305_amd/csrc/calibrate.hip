@@ -83,7 +83,8 @@ struct MergeArgs {
     double* xsum;
     uint64_t *count, *wcount;
     float* ext;           // [6][gridDim.x]
-    int32_t *colsum, *rowsum;   // nullable: zero for the launch that adds to them, [K] and [T]
+    int32_t *colsum, *rowsum;   // nullable: zero for the launch that adds to them, [copies][K] and [T]
+    int copies;
     uint32_t* status;
 };
 
@@ -97,7 +98,7 @@ __global__ __launch_bounds__(kMergeCols * kMergeParts) void calib_merge(MergeArg
         if (a.count) *a.count = a.T;
         if (a.wcount) *a.wcount = a.N;
     }
-    if (a.colsum && part == 0 && k < a.K) a.colsum[k] = 0;
+    if (a.colsum && part < a.copies && k < a.K) a.colsum[part * a.K + k] = 0;
     if (a.rowsum)
         for (uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; t < a.T; t += (uint64_t)gridDim.x * blockDim.x) a.rowsum[t] = 0;
     float lo = INFINITY, hi = -INFINITY, wlo = INFINITY, whi = -INFINITY;
@@ -162,7 +163,7 @@ __global__ __launch_bounds__(kMergeCols * kMergeParts) void calib_merge(MergeArg
 // ---- workspace: what later launches read (the pieces of the ranges; the code sums), then partial rows (of the statistics; of the
 // stages' quantizer)
 static size_t ext_bytes(int64_t K) { return (size_t)cdiv(6 * cdiv(K, kRangeCols) * 4, 256) * 256; }
-static size_t sum_bytes(int64_t K) { return (size_t)cdiv(K * 4, 256) * 256; }
+static size_t sum_bytes(int64_t K) { return (size_t)cdiv(K * 4 * sum_copies(K), 256) * 256; }
 static size_t kept_bytes(int64_t K) { return ext_bytes(K) + sum_bytes(K); }
 static size_t partial_bytes(const CalibPlan& p, int64_t K) { return (size_t)p.slices * (size_t)K * 16; }
 
@@ -282,7 +283,7 @@ static int run_front(const aweq_calib_layer& l, const aweq_calib_weight* w, int 
     const MergeArgs m = {a.pmin, a.pmax, a.psum, p.x_slices, p.slices, l.K, (uint64_t)l.T, (uint64_t)N, l.enable_awe, l.xmin, l.xmax, l.r_x,
                          l.wmin, l.wmax, l.r_w, l.s, l.inv_s, l.mu_xhat, l.xsum, l.count, l.wcount, reinterpret_cast<float*>(l.ws),
                          l.w8a8 ? reinterpret_cast<int32_t*>(reinterpret_cast<char*>(l.ws) + ext_bytes(l.K)) : nullptr,
-                         l.w8a8 && l.forward ? l.rowsum_x : nullptr, l.status};
+                         l.w8a8 && l.forward ? l.rowsum_x : nullptr, sum_copies(l.K), l.status};
     calib_merge<<<blocks, kMergeCols * kMergeParts, 0, st>>>(m);
     fin = {{m.ext, (int)blocks, l.xhat_range, l.act_step, l.act_zero}, l.r_x, l.r_w, l.R_x, l.R_w, l.p_x, l.p_w, nullptr, nullptr, l.status};
     return launch_status();

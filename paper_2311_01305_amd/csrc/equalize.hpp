@@ -29,6 +29,11 @@ __device__ __forceinline__ float channel_scale(float x0, float x1, float w0, flo
 // The range over all channels that a calibration's merge kernel leaves in pieces, and where the quantities derived from it go.  The
 // pieces are min / max per block of channels: of the activations, of the weights, of the equalised activations ([6][blocks]).
 constexpr int kRangeCols = 32;   // channels behind a piece
+
+// Copies of the activation codes' column sums that the quantizer's blocks add to in turn: many blocks to a column of a narrow matrix wait for each
+// other (us, whole calibrations, one copy -> four: FIGURES)
+constexpr int64_t kCopiesK = 1024;
+inline int sum_copies(int64_t K) { return K <= kCopiesK ? 4 : 1; }
 struct RangeParts {
     const float* ext;
     int blocks;

@@ -1069,6 +1069,7 @@ int launch_gemm_i8_group(GroupArgs& g, int n, hipStream_t st)
     rc = plan_tiled(g, half, cost, blocks);
     g.N = N;
     if (rc != AWEQ_OK) return rc;
+    if (one > 8.0) return AWEQ_ERR_SHAPE;   // (many rounds: 32768 tokens 5952 x 5952 1901 -> 1908, 16384 tokens 8192 x 8192 the same)
     double each = kTiledRoundCost * one;
     const FewPlan few = plan_few(g.T, N);
     const MidPlan mid = plan_mid(g.T, N);

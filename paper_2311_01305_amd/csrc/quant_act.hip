@@ -264,8 +264,8 @@ __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
 
     if (colsum_part) {
         // lanes l, l ^ 8, l ^ 16, l ^ 32 hold the same columns for different rows; this block's sums over
-        // its row slice (at most 512 rows of codes in [-128, 127]) go to row `slice` of the partial buffer, or are added to the one row
-        int32_t* const part = colsum_part + (added ? 0 : slice * K);
+        // its row slice (at most 512 rows of codes in [-128, 127]) go to row `slice` of the partial buffer, or are added to one of `added` rows
+        int32_t* const part = colsum_part + (added ? (int)(slice % added) : slice) * K;
 #pragma unroll
         for (int j = 0; j < kQaVpt; ++j) {
             int v[8];
@@ -498,7 +498,7 @@ int launch_quant_act(const void* X, aweq_dtype dt, int64_t T, int64_t K, int64_t
     // other (int8 forward, us, non-temporal -> cached: 16384 tokens 4096 x 11008 (180 MB) 663 -> 650, 4096 x 16384 (268 MB)
     // 979 -> 967, 12000 tokens 8192 x 16384 1306 -> 1307; the pass alone at 262144 x 8192 (2.1 GB) 1188 -> 1268)
     const bool keep = xq && (int64_t)panel_count(K) * kPanel * T <= kCacheBytes;
-#define AWEQ_QA(F, S, P) quant_act_kernel<F, S, P><<<grid, kQaBlock, 0, st>>>(X, T, K, ldx, inv_s, act_step, act_zero, xq, rs_out, colsum_part, (int)p.rpb, p.chunks, pairs, status, parts, colsum_added != nullptr)
+#define AWEQ_QA(F, S, P) quant_act_kernel<F, S, P><<<grid, kQaBlock, 0, st>>>(X, T, K, ldx, inv_s, act_step, act_zero, xq, rs_out, colsum_part, (int)p.rpb, p.chunks, pairs, status, parts, colsum_added ? sum_copies(K) : 0)
     if (dt == AWEQ_F16) { if (sums) AWEQ_QA(true, true, false); else if (keep) AWEQ_QA(true, false, true); else AWEQ_QA(true, false, false); }
     else { if (sums) AWEQ_QA(false, true, false); else if (keep) AWEQ_QA(false, false, true); else AWEQ_QA(false, false, false); }
 #undef AWEQ_QA

@@ -18,7 +18,7 @@ namespace aweq {
 constexpr int kPassRows = 4;
 
 template <int NT>
-__device__ __forceinline__ void finish_ranges(const FinishArgs& f, int64_t K, unsigned block)
+__device__ __forceinline__ void finish_ranges(const FinishArgs& f, int64_t K, unsigned block, int copies)
 {
     __shared__ float slot[3][2 * (NT / kWave)];
     const float2 x = parts_extremes<NT>(f.range.ext, f.range.blocks, 0, slot[0]);
@@ -28,7 +28,11 @@ __device__ __forceinline__ void finish_ranges(const FinishArgs& f, int64_t K, un
     if (k < K) {
         if (f.p_x) f.p_x[k] = f.r_x[k] / Rx;
         if (f.p_w) f.p_w[k] = f.r_w[k] / Rw;
-        if (f.colsum) f.colsum_xq[k] = f.colsum[k];
+        if (f.colsum) {
+            int c = f.colsum[k];
+            for (int64_t j = K; j < copies * K; j += K) c += f.colsum[j + k];
+            f.colsum_xq[k] = c;
+        }
     }
     if (block != 0) return;
     if (threadIdx.x == 0) { *f.R_x = Rx; *f.R_w = Rw; }
@@ -47,7 +51,7 @@ __device__ __forceinline__ void finish_ranges(const FinishArgs& f, int64_t K, un
 }
 
 constexpr int kFinishThreads = 256;
-__global__ __launch_bounds__(kFinishThreads) void calib_finish(FinishArgs f, int64_t K) { finish_ranges<kFinishThreads>(f, K, blockIdx.x); }
+__global__ __launch_bounds__(kFinishThreads) void calib_finish(FinishArgs f, int64_t K) { finish_ranges<kFinishThreads>(f, K, blockIdx.x, 1); }
 
 __device__ __forceinline__ const PassMember& member_of(const PassArgs& a)
 {
@@ -211,7 +215,7 @@ __global__ __launch_bounds__(TPR == kWave ? 256 : TPR, TPR == 512 && UPT == 3 ? 
 {
     constexpr int kThreads = TPR == kWave ? 256 : TPR, kSets = kThreads / TPR, kWaves = TPR / kWave;
     static_assert(kSets == 1 || kWaves == 1, "rows are reduced over a wavefront or over the block");
-    if (blockIdx.x >= a.weight_blocks) { finish_ranges<kThreads>(a.fin, a.K, blockIdx.x - a.weight_blocks); return; }
+    if (blockIdx.x >= a.weight_blocks) { finish_ranges<kThreads>(a.fin, a.K, blockIdx.x - a.weight_blocks, a.K <= kCopiesK ? 4 : 1); return; }
     const PassMember& m = member_of(a);
     __shared__ float2 slot_ex[kWaves][ROWS];
     __shared__ double slot_d[kWaves][ROWS];
@@ -290,8 +294,14 @@ __global__ __launch_bounds__(TPR == kWave ? 256 : TPR, TPR == 512 && UPT == 3 ? 
         const int64_t u = tid + (int64_t)j * TPR;
         if (u < units) {
             const Float4 m0 = *reinterpret_cast<const Float4*>(a.mu + u * 8), m1 = *reinterpret_cast<const Float4*>(a.mu + u * 8 + 4);
-            const int4 c0 = *reinterpret_cast<const int4*>(a.colsum + u * 8), c1 = *reinterpret_cast<const int4*>(a.colsum + u * 8 + 4);
-            const int cx[2][4] = {{c0.x, c0.y, c0.z, c0.w}, {c1.x, c1.y, c1.z, c1.w}};
+            constexpr int kCopies = TPR == kWave ? 4 : 1;   // (sum_copies(K): the launch has TPR = kWave up to kCopiesK columns)
+            int cx[2][4] = {};
+#pragma unroll
+            for (int q = 0; q < kCopies; ++q) {
+                const int4 c0 = *reinterpret_cast<const int4*>(a.colsum + q * a.K + u * 8), c1 = *reinterpret_cast<const int4*>(a.colsum + q * a.K + u * 8 + 4);
+                cx[0][0] += c0.x; cx[0][1] += c0.y; cx[0][2] += c0.z; cx[0][3] += c0.w;
+                cx[1][0] += c1.x; cx[1][1] += c1.y; cx[1][2] += c1.z; cx[1][3] += c1.w;
+            }
             uint32_t d[2][4];
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
@@ -365,7 +375,7 @@ __global__ __launch_bounds__(BLOCK, BLOCK == kWave ? 3 : 4) void weight_pass_gro
 {
     constexpr int ROWS = kPassRows, kLanes = 1 << LEVELS, kWaves = BLOCK / kWave;
     static_assert(ROWS == 4 && LEVELS >= 2, "a quad lies inside a group");
-    if (blockIdx.x >= a.weight_blocks) { finish_ranges<BLOCK>(a.fin, a.K, blockIdx.x - a.weight_blocks); return; }
+    if (blockIdx.x >= a.weight_blocks) { finish_ranges<BLOCK>(a.fin, a.K, blockIdx.x - a.weight_blocks, 1); return; }
     const PassMember& m = member_of(a);
     __shared__ double slot_d[kWaves][ROWS];
     const int64_t n0 = (int64_t)(blockIdx.x - m.first_block) * ROWS;
@@ -475,7 +485,7 @@ static void launch_rows(PassArgs& a, hipStream_t st)
 template <bool F16, bool LINES>
 static void launch_rows_for(PassArgs& a, hipStream_t st)
 {
-    if (a.K <= 1024) launch_rows<F16, LINES, 64, 2, 1>(a, st);
+    if (a.K <= kCopiesK) launch_rows<F16, LINES, 64, 2, 1>(a, st);
     else if (a.K <= 4096) launch_rows<F16, LINES, 256, 2, 4>(a, st);
     else if (a.K <= 8192) launch_rows<F16, LINES, 256, 4, F16 ? 4 : 2>(a, st);
     else if (a.K <= 12288) {

@@ -27,7 +27,7 @@ struct FinishArgs {
     RangeParts range;   // act_step null: xhat_range, Step and Z are written elsewhere
     const float *r_x, *r_w;
     float *R_x, *R_w, *p_x, *p_w;   // p nullable
-    const int32_t* colsum;          // nullable: widened to colsum_xq
+    const int32_t* colsum;          // nullable: its copies' sum is widened to colsum_xq
     long long* colsum_xq;
     uint32_t* status;
 };
@@ -40,7 +40,7 @@ struct PassArgs {
     const float* s;
     const float* mu;
     uint64_t count;                // 8 bits: tokens behind colsum_xq
-    const int32_t* colsum;         // 8 bits: colsum_xq, of fewer than 2^23 tokens
+    const int32_t* colsum;         // 8 bits: colsum_xq, of fewer than 2^23 tokens, as the sum of sum_copies(K) rows
     const float* act_step;         // 8 bits
     const int32_t* act_zero;
     int enable_bc;
