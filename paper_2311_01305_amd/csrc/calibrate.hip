@@ -163,12 +163,12 @@ __global__ __launch_bounds__(kMergeCols * kMergeParts) void calib_merge(MergeArg
 // ---- workspace: what later launches read (the pieces of the ranges; the code sums), then partial rows (of the statistics; of the
 // stages' quantizer)
 static size_t ext_bytes(int64_t K) { return (size_t)cdiv(6 * cdiv(K, kRangeCols) * 4, 256) * 256; }
-static size_t sum_bytes(int64_t K) { return (size_t)cdiv(K * 4 * sum_copies(K), 256) * 256; }
-static size_t kept_bytes(int64_t K) { return ext_bytes(K) + sum_bytes(K); }
+static size_t sum_bytes(int64_t K, int copies) { return (size_t)cdiv(K * 4 * copies, 256) * 256; }
+static size_t kept_bytes(int64_t K, int copies) { return ext_bytes(K) + sum_bytes(K, copies); }
 static size_t partial_bytes(const CalibPlan& p, int64_t K) { return (size_t)p.slices * (size_t)K * 16; }
 
 // for any division of N rows over up to kMaxMembers weights: a plan has at most max(1280 / chunks, n) slices
-size_t calibrate_ws_bytes(int64_t T, int64_t K, int64_t N)
+static size_t calibrate_ws_bytes(int64_t T, int64_t K, int64_t N, int copies)
 {
     if (N <= 0) return 0;
     size_t most = 0;
@@ -181,7 +181,16 @@ size_t calibrate_ws_bytes(int64_t T, int64_t K, int64_t N)
         if (b > most) most = b;
     }
     const size_t qa = quant_act_ws_bytes(T, K);
-    return kept_bytes(K) + (most > qa ? most : qa);
+    return kept_bytes(K, copies) + (most > qa ? most : qa);
+}
+size_t calibrate_ws_bytes(int64_t T, int64_t K, int64_t N) { return calibrate_ws_bytes(T, K, N, sum_copies(K)); }
+
+// a workspace with room for one copy only does with that
+static int copies_in(const aweq_calib_layer& l, const aweq_calib_weight* w, int n)
+{
+    int64_t N = 0;
+    for (int i = 0; i < n; ++i) N += w[i].N;
+    return l.ws_bytes >= calibrate_ws_bytes(l.T, l.K, N) ? sum_copies(l.K) : 1;
 }
 
 // no buffer that is written shares a byte with another buffer
@@ -253,7 +262,7 @@ static bool fused_front(const aweq_calib_layer& l, const aweq_calib_weight* w, i
         N += v.N;
     }
     if (l.w8a8 && (!l.colsum_xq || (l.forward && (!l.xq || !l.rowsum_x || !aligned16(l.xq) || l.K > 32768)))) return false;
-    return l.ws_bytes >= calibrate_ws_bytes(l.T, l.K, N) && buffers_apart(l, w, n);
+    return l.ws_bytes >= calibrate_ws_bytes(l.T, l.K, N, 1) && buffers_apart(l, w, n);
 }
 
 static int run_front(const aweq_calib_layer& l, const aweq_calib_weight* w, int n, FinishArgs& fin, hipStream_t st)
@@ -261,11 +270,12 @@ static int run_front(const aweq_calib_layer& l, const aweq_calib_weight* w, int 
     int64_t rows[kSources] = {l.T}, N = 0;
     for (int i = 0; i < n; ++i) { rows[1 + i] = w[i].N; N += w[i].N; }
     const bool f16 = l.dt == AWEQ_F16;
+    const int copies = copies_in(l, w, n);
     const CalibPlan p = calib_plan(rows, n + 1, l.K, f16);
     if (p.slices > 65535) return AWEQ_ERR_SHAPE;
     StatsSources a;
     a.n = n + 1; a.K = l.K; a.rows_per_slice = p.rows_per_slice;
-    a.psum = reinterpret_cast<double*>(reinterpret_cast<char*>(l.ws) + kept_bytes(l.K));
+    a.psum = reinterpret_cast<double*>(reinterpret_cast<char*>(l.ws) + kept_bytes(l.K, copies));
     a.pmin = reinterpret_cast<float*>(a.psum + (size_t)p.slices * l.K);
     a.pmax = a.pmin + (size_t)p.slices * l.K;
     for (int i = 0; i <= n; ++i) {
@@ -283,7 +293,7 @@ static int run_front(const aweq_calib_layer& l, const aweq_calib_weight* w, int 
     const MergeArgs m = {a.pmin, a.pmax, a.psum, p.x_slices, p.slices, l.K, (uint64_t)l.T, (uint64_t)N, l.enable_awe, l.xmin, l.xmax, l.r_x,
                          l.wmin, l.wmax, l.r_w, l.s, l.inv_s, l.mu_xhat, l.xsum, l.count, l.wcount, reinterpret_cast<float*>(l.ws),
                          l.w8a8 ? reinterpret_cast<int32_t*>(reinterpret_cast<char*>(l.ws) + ext_bytes(l.K)) : nullptr,
-                         l.w8a8 && l.forward ? l.rowsum_x : nullptr, sum_copies(l.K), l.status};
+                         l.w8a8 && l.forward ? l.rowsum_x : nullptr, copies, l.status};
     calib_merge<<<blocks, kMergeCols * kMergeParts, 0, st>>>(m);
     fin = {{m.ext, (int)blocks, l.xhat_range, l.act_step, l.act_zero}, l.r_x, l.r_w, l.R_x, l.R_w, l.p_x, l.p_w, nullptr, nullptr, l.status};
     return launch_status();
@@ -323,16 +333,17 @@ static int run_calibration(const aweq_calib_layer& l, const aweq_calib_weight* w
     if (pass) {
         char* const ws = reinterpret_cast<char*>(l.ws);
         int32_t* const colsum = reinterpret_cast<int32_t*>(ws + ext_bytes(l.K));
+        const int copies = copies_in(l, w, n);
         if (l.w8a8) {
             rc = launch_quant_act(l.X, l.dt, l.T, l.K, l.ldx, l.inv_s, l.act_step, l.act_zero, l.forward ? l.xq : nullptr,
-                                  l.forward ? l.rowsum_x : nullptr, nullptr, nullptr, l.status, st, &fin.range, colsum);
+                                  l.forward ? l.rowsum_x : nullptr, nullptr, nullptr, l.status, st, &fin.range, colsum, copies);
             if (rc != AWEQ_OK) return rc;
             fin.range.act_step = nullptr;   // (the quantizer has written it)
             fin.colsum = colsum;
             fin.colsum_xq = reinterpret_cast<long long*>(l.colsum_xq);
         }
         PassArgs a;
-        a.n = n; a.K = l.K; a.s = l.s; a.mu = l.mu_xhat; a.count = (uint64_t)l.T; a.colsum = colsum;
+        a.n = n; a.K = l.K; a.s = l.s; a.mu = l.mu_xhat; a.count = (uint64_t)l.T; a.colsum = colsum; a.copies = copies;
         a.act_step = l.act_step; a.act_zero = l.act_zero; a.enable_bc = l.enable_bc; a.status = l.status; a.fin = fin;
         for (int i = 0; i < n; ++i)
             a.m[i] = {w[i].W, w[i].W_hat, reinterpret_cast<uint8_t*>(w[i].codes), w[i].step_w, w[i].zero_w, w[i].rowsum_w, w[i].bias_in, w[i].delta,

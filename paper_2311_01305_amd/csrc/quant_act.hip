@@ -463,7 +463,7 @@ size_t quant_act_ws_bytes(int64_t T, int64_t K)
 int launch_quant_act(const void* X, aweq_dtype dt, int64_t T, int64_t K, int64_t ldx, const float* inv_s,
                      const float* act_step, const int32_t* act_zero, int8_t* xq, int32_t* rowsum_x,
                      int64_t* colsum_xq, void* ws, uint32_t* status, hipStream_t st, const RangeParts* range,
-                     int32_t* colsum_added)
+                     int32_t* colsum_added, int copies)
 {
     // Whole rows per block where nothing is summed over tokens, up to the size where the panel form streams as fast (us, panel form -> row
     // form: K = 4096: 1000 tokens 11.2 -> 6.4, 4096: 17.9 -> 14.1, 16384: 41.3 -> 40.1, but 32768: 74.0 -> 81.6; K = 11008: 2048 tokens 24.4 -> 17.8,
@@ -498,7 +498,7 @@ int launch_quant_act(const void* X, aweq_dtype dt, int64_t T, int64_t K, int64_t
     // other (int8 forward, us, non-temporal -> cached: 16384 tokens 4096 x 11008 (180 MB) 663 -> 650, 4096 x 16384 (268 MB)
     // 979 -> 967, 12000 tokens 8192 x 16384 1306 -> 1307; the pass alone at 262144 x 8192 (2.1 GB) 1188 -> 1268)
     const bool keep = xq && (int64_t)panel_count(K) * kPanel * T <= kCacheBytes;
-#define AWEQ_QA(F, S, P) quant_act_kernel<F, S, P><<<grid, kQaBlock, 0, st>>>(X, T, K, ldx, inv_s, act_step, act_zero, xq, rs_out, colsum_part, (int)p.rpb, p.chunks, pairs, status, parts, colsum_added ? sum_copies(K) : 0)
+#define AWEQ_QA(F, S, P) quant_act_kernel<F, S, P><<<grid, kQaBlock, 0, st>>>(X, T, K, ldx, inv_s, act_step, act_zero, xq, rs_out, colsum_part, (int)p.rpb, p.chunks, pairs, status, parts, colsum_added ? copies : 0)
     if (dt == AWEQ_F16) { if (sums) AWEQ_QA(true, true, false); else if (keep) AWEQ_QA(true, false, true); else AWEQ_QA(true, false, false); }
     else { if (sums) AWEQ_QA(false, true, false); else if (keep) AWEQ_QA(false, false, true); else AWEQ_QA(false, false, false); }
 #undef AWEQ_QA

@@ -215,7 +215,7 @@ __global__ __launch_bounds__(TPR == kWave ? 256 : TPR, TPR == 512 && UPT == 3 ? 
 {
     constexpr int kThreads = TPR == kWave ? 256 : TPR, kSets = kThreads / TPR, kWaves = TPR / kWave;
     static_assert(kSets == 1 || kWaves == 1, "rows are reduced over a wavefront or over the block");
-    if (blockIdx.x >= a.weight_blocks) { finish_ranges<kThreads>(a.fin, a.K, blockIdx.x - a.weight_blocks, a.K <= kCopiesK ? 4 : 1); return; }
+    if (blockIdx.x >= a.weight_blocks) { finish_ranges<kThreads>(a.fin, a.K, blockIdx.x - a.weight_blocks, a.copies); return; }
     const PassMember& m = member_of(a);
     __shared__ float2 slot_ex[kWaves][ROWS];
     __shared__ double slot_d[kWaves][ROWS];
@@ -294,10 +294,10 @@ __global__ __launch_bounds__(TPR == kWave ? 256 : TPR, TPR == 512 && UPT == 3 ? 
         const int64_t u = tid + (int64_t)j * TPR;
         if (u < units) {
             const Float4 m0 = *reinterpret_cast<const Float4*>(a.mu + u * 8), m1 = *reinterpret_cast<const Float4*>(a.mu + u * 8 + 4);
-            constexpr int kCopies = TPR == kWave ? 4 : 1;   // (sum_copies(K): the launch has TPR = kWave up to kCopiesK columns)
             int cx[2][4] = {};
 #pragma unroll
-            for (int q = 0; q < kCopies; ++q) {
+            for (int q = 0; q < (TPR == kWave ? kMostCopies : 1); ++q) {   // (the launch has TPR = kWave up to kCopiesK columns)
+                if (q > 0 && q >= a.copies) break;
                 const int4 c0 = *reinterpret_cast<const int4*>(a.colsum + q * a.K + u * 8), c1 = *reinterpret_cast<const int4*>(a.colsum + q * a.K + u * 8 + 4);
                 cx[0][0] += c0.x; cx[0][1] += c0.y; cx[0][2] += c0.z; cx[0][3] += c0.w;
                 cx[1][0] += c1.x; cx[1][1] += c1.y; cx[1][2] += c1.z; cx[1][3] += c1.w;

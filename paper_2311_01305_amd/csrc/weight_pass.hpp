@@ -40,7 +40,8 @@ struct PassArgs {
     const float* s;
     const float* mu;
     uint64_t count;                // 8 bits: tokens behind colsum_xq
-    const int32_t* colsum;         // 8 bits: colsum_xq, of fewer than 2^23 tokens, as the sum of sum_copies(K) rows
+    const int32_t* colsum;         // 8 bits: colsum_xq, of fewer than 2^23 tokens, as the sum of `copies` rows (beyond kCopiesK columns one)
+    int copies;
     const float* act_step;         // 8 bits
     const int32_t* act_zero;
     int enable_bc;
