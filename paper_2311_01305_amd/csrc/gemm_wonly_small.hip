@@ -164,6 +164,9 @@ __global__ __launch_bounds__(WAVES * kWave) void gemm_small_kernel(SmallArgs g)
     // 14.3 -> 11.6 / 15.8 -> 14.0, 4096 x 16384 10.5 -> 9.75 / 12.05 -> 11.65 / 14.8 -> 14.2; elsewhere no gain, and up to 6 % lost where the
     // activations are large: 33 tokens 8192 x 22016 51.5 -> 54.9).
     const int cnt = max(((K + kChunk - 1) / kChunk - wave + WAVES - 1) / WAVES, 0);
+    // Held here, all arguments come in one round trip; tiles without branches around their loads otherwise had the pointers in a second one, behind the
+    // branch below, 0.15 - 0.25 us of every call (INT4 20 tokens 4096 x 2048 4.60 -> 4.39, 8 tokens 4096 x 4096 5.46 -> 5.31, INT3 17 tokens 1024 x 2048 4.57 -> 4.37)
+    asm volatile("" ::"s"(g.X), "s"(g.codes), "s"(g.step), "s"(g.zero), "s"(g.scale_pitch), "s"(g.group_magic));
     int at = code_pitch % 4096 == 0 ? (int)((blockIdx.x / kXcdCount % 16) * (unsigned)cnt / 16u) : 0, kc = (wave + at * WAVES) * kChunk;
     if (cnt > 0) { load_codes_at(kc); load_x_at(kc); }
     for (int left = cnt; left > 0; --left) {
