@@ -168,7 +168,13 @@ __global__ __launch_bounds__(WAVES * kWave) void gemm_small_kernel(SmallArgs g)
     // branch below, 0.15 - 0.25 us of every call (INT4 20 tokens 4096 x 2048 4.60 -> 4.39, 8 tokens 4096 x 4096 5.46 -> 5.31, INT3 17 tokens 1024 x 2048 4.57 -> 4.37)
     asm volatile("" ::"s"(g.X), "s"(g.codes), "s"(g.step), "s"(g.zero), "s"(g.scale_pitch), "s"(g.group_magic));
     int at = code_pitch % 4096 == 0 ? (int)((blockIdx.x / kXcdCount % 16) * (unsigned)cnt / 16u) : 0, kc = (wave + at * WAVES) * kChunk;
-    if (cnt > 0) { load_codes_at(kc); load_x_at(kc); }
+    if (cnt > 0) {
+        load_codes_at(kc);
+        // Codes first: the compiler otherwise puts them behind the addresses of all activations, and a wavefront with one chunk waits for that. (17 - 32 tokens;
+        // us, INT3 24 tokens 2048 x 2048 4.68 -> 4.45, INT4 28 tokens 512 x 8192 10.7 -> 10.25; with 16 wavefronts 17 tokens 4096 x 11008 11.8 -> 12.1)
+        if constexpr (kNatural && WAVES == 8) __builtin_amdgcn_sched_barrier(0);
+        load_x_at(kc);
+    }
     for (int left = cnt; left > 0; --left) {
         at = at + 1 == cnt ? 0 : at + 1;
         const int kn = left > 1 ? (wave + at * WAVES) * kChunk : K;   // (K: none)
