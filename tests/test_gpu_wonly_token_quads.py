@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-@pytest.mark.parametrize("bits,N,K,group", [(4, 52, 4096, 128), (3, 36, 4096 + 128, 128), (4, 20, 3840, 64), (3, 8228, 256, 128), (4, 12292, 320, 0)])
+@pytest.mark.parametrize("bits,N,K,group", [(4, 52, 4096, 128), (3, 36, 4096 + 128, 128), (4, 20, 3840, 64), (3, 8228, 256, 128), (4, 12292, 320, 0), (3, 8228, 320, 0), (3, 12292, 256, 64)])
 def test_token_quads(orc, bits, N, K, group):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
