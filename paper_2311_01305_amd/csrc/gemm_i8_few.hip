@@ -309,9 +309,11 @@ FewPlan plan_few(int64_t T, int64_t N)
 int launch_gemm_i8_few_quant(const GemmArgs& g, const FewPlan& p, const QuantIn& in, bool f16, hipStream_t st)
 {
 #define AWEQ_FQ(NT, D, Q) (g.T == 1 ? few::launch_tile<1, NT, D, Q, 1>(g, st, in) : g.T == 2 ? few::launch_tile<1, NT, D, Q, 2>(g, st, in) : few::launch_tile<1, NT, D, Q, 4>(g, st, in))
-    // Depth of the ring, by whether a compute unit has one workgroup (us, buffers that change from call to call, 3 / 4 / 6: one token 4096 x 4096
-    // 6.1 / 6.2 / 5.95, 4096 x 11008 11.35 / 11.55 / 11.95, three tokens 4096 x 4096 7.1 / 7.3, but 6000 x 6144 8.9 / 8.75)
-    if (p.tile == 0 && g.N <= 16 * 256) return f16 ? AWEQ_FQ(1, 3, 1) : AWEQ_FQ(1, 3, 2);
+    // Depth of the ring: three panels where nearly every compute unit has its one workgroup and a wavefront eight panels or more, four elsewhere, which
+    // hold all panels of short rows and ask for more at a time where compute units are idle (us, buffers that change from call to call, 4 -> 3: one
+    // token 4096 x 4096 6.17 -> 6.06, 4096 x 12288 12.3 -> 12.0, two tokens 3840 x 4096 6.55 -> 6.35, three tokens 4096 x 4096 7.35 -> 7.15, but one token
+    // 4096 x 2048 4.22 -> 4.38, 2560 x 1536 3.69 -> 3.86, 3328 x 3072 5.1 -> 5.25, 2048 x 8192 6.9 -> 7.05, 1024 x 16384 9.65 -> 9.9, 6000 x 6144 8.75 -> 8.9)
+    if (p.tile == 0 && g.N > 16 * 216 && g.N <= 16 * 256 && g.K >= 4096) return f16 ? AWEQ_FQ(1, 3, 1) : AWEQ_FQ(1, 3, 2);
     if (p.tile == 0) return f16 ? AWEQ_FQ(1, 4, 1) : AWEQ_FQ(1, 4, 2);
     return f16 ? AWEQ_FQ(2, 3, 1) : AWEQ_FQ(2, 3, 2);
 #undef AWEQ_FQ
