@@ -1051,10 +1051,15 @@ static int plan_tiled(GemmArgs& g, bool& half, double& cost, int64_t& blocks)
     return AWEQ_OK;
 }
 
-// Launches of their own leave compute units without a tile in each one's last round, and each has its ramp and its last epilogue: kLaunchCost us.
-// (us, whole calibrations, a launch each -> one: three weights 4096 x 4096 of 512 tokens 142 -> 115, 2048 tokens 193 -> 186, 8192 tokens 422 -> 412, 2048 x
-// 2048 of 700 tokens 79.0 -> 58.1, two 1024 x 1024 of 2500 tokens 52.7 -> 37.8, two 8192 x 8192 of 32768 tokens within the spread)
-constexpr double kLaunchCost = 4.0;
+// Launches of their own leave compute units without a tile in each one's last round, and each has its launch, its ramp and its last epilogue, which do
+// not grow with K: kTiledFixed us (the kernel for some hundred tokens the same; the few-token one kFewFixed, the read of its tokens, and per round of tile
+// FewPlan::tile kFewShare of what it is modelled to take).
+// (us, whole calibrations, a launch each -> one: three weights 4096 x 4096 of 512 tokens 135 -> 112, 2048 tokens 193 -> 186, 4096 tokens 274 -> 265, 2048 x
+// 2048 of 700 tokens 77.8 -> 59.2, two 1024 x 1024 of 2048 tokens 46.8 -> 39.3, four 1024 x 4096 of 1024 tokens 88.8 -> 71.8; against it two
+// 1024 x 1024 of 128 tokens 31.0 -> 35.2, two 512 x 512 of 512 tokens 27.1 -> 30.2, three 3072 x 3072 of 16 tokens 70.9 -> 77.3, four 1024 x 8192 of 16
+// tokens 90.6 -> 106.  Of 855 such calls the rule takes the slower form by more than 1 % in 13, most by 3 %.)
+constexpr double kTiledFixed = 3.0, kFewFixed = 1.7, kFewToken = 0.25e-6;
+constexpr double kFewShare[] = {0.75, 1.0, 0.88, 0.96, 0.92, 0.96};
 int launch_gemm_i8_group(GroupArgs& g, int n, hipStream_t st)
 {
     const int64_t N = g.N;
@@ -1070,12 +1075,19 @@ int launch_gemm_i8_group(GroupArgs& g, int n, hipStream_t st)
     g.N = N;
     if (rc != AWEQ_OK) return rc;
     if (one > 8.0) return AWEQ_ERR_SHAPE;   // (many rounds: 32768 tokens 5952 x 5952 1901 -> 1908, 16384 tokens 8192 x 8192 the same)
-    double each = kTiledRoundCost * one;
+    // what aweq_w8a8_gemm takes for each weight
+    const double us = (double)g.K / 8192.0, tiled = kTiledRoundCost * one;
     const FewPlan few = plan_few(g.T, N);
-    const MidPlan mid = plan_mid(g.T, N);
-    if (few.cost < each) each = few.cost;
-    if (mid.cost < each) each = mid.cost;
-    if (kTiledRoundCost * cost > n * each + (n - 1) * kLaunchCost * 8192.0 / (double)g.K) return AWEQ_ERR_SHAPE;
+    MidPlan mid = plan_mid(g.T, N);
+    if (g.K <= 512 && mid.cost > 43.0) mid.cost *= 1.2;
+    const bool by_few = few.cost <= mid.cost && few.cost < tiled, by_tiles = !by_few && mid.cost >= tiled;
+    const double each = by_few ? kFewFixed + (double)(g.T * g.K) * kFewToken + kFewShare[few.tile] * few.cost * us
+                               : kTiledFixed + (by_tiles ? tiled : mid.cost) * us;
+    if (kTiledFixed + kTiledRoundCost * cost * us > n * each) return AWEQ_ERR_SHAPE;
+    // Long rows in as many rounds as launches of their own take, each of which leaves compute units idle (three weights 2048 x 11008 of 3000 tokens
+    // 347 -> 370, 1024 x 8192 of 6000 tokens 250 -> 266; full rounds 2048 x 2048 of 4096 tokens 110 -> 105)
+    const int64_t tiles = (int64_t)a.tiles_m * a.tiles_n;
+    if (by_tiles && cost > 0.94 * n * one && 10 * tiles < 9 * 256 * cdiv(tiles, 256) && g.K >= 4 * N) return AWEQ_ERR_SHAPE;
     const void* fn = half ? reinterpret_cast<const void*>(fast::gemm_i8_fast<2, false, 2, false, 0, true, GroupArgs>)
                           : reinterpret_cast<const void*>(fast::gemm_i8_fast<4, false, 2, false, 0, true, GroupArgs>);
     return launch_persistent(fn, fast::kThreads, half ? fast::Tile<2>::kLds : fast::Tile<4>::kLds, &g, g.n_ids, st);
