@@ -481,11 +481,17 @@ static void launch_rows(PassArgs& a, hipStream_t st)
 // 512 x 2 x 4 81.4, 1024 x 2 x 2 108; 8192 x 22016 512 x 6 x 2 215, x 1 236, x 4 251, 256 x 11 x 1 235.  Non-temporal reads and writes of whole
 // lines: 8192 x 8192 77.1 -> 68.5, 8192 x 22016 215 -> 202, 4096 x 11008 and 12288 x 4096 within 2 us; not in a cache 63.5 -> 60.2, 61.8 -> 59.6.
 // Binary16 of up to 12288 columns, with digits that four rows share, held to 128 registers (whole calibrations of 600 tokens, 256 x 6 x 2 -> 512 x 3 x 4:
-// 4096 x 11008 84.8 -> 83.9, 1000 x 10000 40.1 -> 38.6, 8192 x 12000 185 -> 182.5; with 130 registers 4096 x 11008 93.0; binary32 spills).
+// 4096 x 11008 84.8 -> 83.9, 1000 x 10000 40.1 -> 38.6, 8192 x 12000 185 -> 182.5; with 130 registers 4096 x 11008 93.0; one register is spilled there, in
+// binary32 many).  Up to 1024 columns a wavefront to a row, to two rows of more than 2048, which share what they read of a column (whole calibrations, one
+// row -> two: 2048 tokens 11008 x 1024 45.1 -> 41.8, 512 tokens 11008 x 512 34.4 -> 32.1, binary32 2048 tokens 4096 x 768 29.9 -> 28.9, 3072 x 256
+// 21.6 -> 21.3, but 6000 tokens 2048 x 1024 28.8 -> 29.5; four rows 600 tokens 22016 x 512 44.5 -> 43.0, binary32 22016 x 1024 79.9 -> 82.6).
 template <bool F16, bool LINES>
 static void launch_rows_for(PassArgs& a, hipStream_t st)
 {
-    if (a.K <= kCopiesK) launch_rows<F16, LINES, 64, 2, 1>(a, st);
+    int64_t N = 0;
+    for (int i = 0; i < a.n; ++i) N += a.m[i].N;
+    if (a.K <= kCopiesK && N <= 2048) launch_rows<F16, LINES, 64, 2, 1>(a, st);
+    else if (a.K <= kCopiesK) launch_rows<F16, LINES, 64, 2, 2>(a, st);
     else if (a.K <= 4096) launch_rows<F16, LINES, 256, 2, 4>(a, st);
     else if (a.K <= 8192) launch_rows<F16, LINES, 256, 4, F16 ? 4 : 2>(a, st);
     else if (a.K <= 12288) {

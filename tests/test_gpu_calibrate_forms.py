@@ -169,7 +169,7 @@ def test_several_weights(B, dtype, bits, group, w8a8, forward):
 
 
 FORMS = [(8, 0, True, True), (8, 0, True, False), (4, 128, False, False), (3, 32, False, False), (8, -1, True, False)]
-SHAPES = [(33, (5,), 640), (70, (9, 3), 1032), (40, (6,), 4224), (50, (7,), 8200)]   # whole 128-byte lines and not; a wavefront to a row and more
+SHAPES = [(33, (5,), 640), (70, (9, 3), 1032), (40, (6,), 4224), (50, (7,), 8200), (40, (1030, 1027), 520)]   # whole 128-byte lines and not; a wavefront to a row, to two rows, and more
 
 
 def _fits(K, bits, group):

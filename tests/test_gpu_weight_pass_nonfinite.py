@@ -1,6 +1,6 @@
 """The pass over the weights of a calibration in one call, where weights hold NaN, infinities, zeros of both signs and rows far from zero: the
 extremes hand a NaN on and are then taken again without it.  Against the stage entry points (a workspace of the stages' size), to the bit: folded
-weights, codes, Step, Z, row sums; a short row for a wavefront and rows for a block, a NaN in the first, middle and last unit and lane."""
+weights, codes, Step, Z, row sums; one and two short rows for a wavefront and rows for a block, a NaN in the first, middle and last unit and lane."""
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -11,7 +11,7 @@ DEV = "cuda:0"
 
 @pytest.mark.parametrize("dtype", [torch.float16, torch.float32])
 @pytest.mark.parametrize("N,K,bits,group", [(9, 512, 8, 0), (13, 1024, 8, 0), (10, 4096, 8, 0), (11, 5000, 8, 0), (7, 11008, 8, 0), (5, 13000, 8, 0),
-                                            (9, 512, 4, 128), (10, 4096, 4, 128), (7, 2048, 3, 32), (6, 1536, 3, 512)])
+                                            (9, 512, 4, 128), (10, 4096, 4, 128), (7, 2048, 3, 32), (6, 1536, 3, 512), (2051, 1024, 8, 0), (2049, 72, 8, 0)])
 def test_nonfinite_weights(N, K, bits, group, dtype):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
