@@ -1057,7 +1057,7 @@ static int plan_tiled(GemmArgs& g, bool& half, double& cost, int64_t& blocks)
 // (us, whole calibrations, a launch each -> one: three weights 4096 x 4096 of 512 tokens 135 -> 112, 2048 tokens 193 -> 186, 4096 tokens 274 -> 265, 2048 x
 // 2048 of 700 tokens 77.8 -> 59.2, two 1024 x 1024 of 2048 tokens 46.8 -> 39.3, four 1024 x 4096 of 1024 tokens 88.8 -> 71.8; against it two
 // 1024 x 1024 of 128 tokens 31.0 -> 35.2, two 512 x 512 of 512 tokens 27.1 -> 30.2, three 3072 x 3072 of 16 tokens 70.9 -> 77.3, four 1024 x 8192 of 16
-// tokens 90.6 -> 106.  Of 855 such calls the rule takes the slower form by more than 1 % in 13, most by 3 %.)
+// tokens 90.6 -> 106.)
 constexpr double kTiledFixed = 3.0, kFewFixed = 1.7, kFewToken = 0.25e-6;
 constexpr double kFewShare[] = {0.75, 1.0, 0.88, 0.96, 0.92, 0.96};
 int launch_gemm_i8_group(GroupArgs& g, int n, hipStream_t st)
@@ -1084,10 +1084,18 @@ int launch_gemm_i8_group(GroupArgs& g, int n, hipStream_t st)
     const double each = by_few ? kFewFixed + (double)(g.T * g.K) * kFewToken + kFewShare[few.tile] * few.cost * us
                                : kTiledFixed + (by_tiles ? tiled : mid.cost) * us;
     if (kTiledFixed + kTiledRoundCost * cost * us > n * each) return AWEQ_ERR_SHAPE;
-    // Long rows in as many rounds as launches of their own take, each of which leaves compute units idle (three weights 2048 x 11008 of 3000 tokens
-    // 347 -> 370, 1024 x 8192 of 6000 tokens 250 -> 266; full rounds 2048 x 2048 of 4096 tokens 110 -> 105)
-    const int64_t tiles = (int64_t)a.tiles_m * a.tiles_n;
-    if (by_tiles && cost > 0.94 * n * one && 10 * tiles < 9 * 256 * cdiv(tiles, 256) && g.K >= 4 * N) return AWEQ_ERR_SHAPE;
+    // In as many rounds as launches of their own take.  One of 256-token tiles a weight that leaves compute units idle runs at a higher clock than the
+    // full rounds of one launch, which loses the more the longer the rows and the fewer the tiles (two weights 4276 x 8624 of 2890 tokens, 204 tiles,
+    // 347 -> 367, 2048 x 4096 of 6274, 200, 159 -> 168, but 3796 x 3144 of 3385, 210, 158 -> 153, and full rounds 2048 x 2048 of 4096 tokens 110 -> 105);
+    // of 128-token tiles with rows much longer than the outputs (three 2048 x 11008 of 3000 tokens 347 -> 370, 1024 x 8192 of 6000 250 -> 266); and
+    // weights that do not fit the memory-side cache together (four 8192 x 8192 of 2654 tokens 990 -> 1019, 6432 x 10344 of 1955 847 -> 932).  Over
+    // 1750 groups without regard to these the launch each was faster by more than 1.5 % in 117, now in 11, by 4 % at most.
+    if (by_tiles && cost > 0.94 * n * one) {
+        const double idle = 1.0 - (double)a.tiles_m * a.tiles_n / (256.0 * (double)cdiv((int64_t)a.tiles_m * a.tiles_n, 256));
+        if (!half_one && one <= 1.0 && (double)g.K * (idle - 0.05) > 300.0) return AWEQ_ERR_SHAPE;
+        if (half_one && idle > 0.1 && g.K >= 4 * N) return AWEQ_ERR_SHAPE;
+        if (n * N * g.K >= kCacheBytes) return AWEQ_ERR_SHAPE;
+    }
     const void* fn = half ? reinterpret_cast<const void*>(fast::gemm_i8_fast<2, false, 2, false, 0, true, GroupArgs>)
                           : reinterpret_cast<const void*>(fast::gemm_i8_fast<4, false, 2, false, 0, true, GroupArgs>);
     return launch_persistent(fn, fast::kThreads, half ? fast::Tile<2>::kLds : fast::Tile<4>::kLds, &g, g.n_ids, st);

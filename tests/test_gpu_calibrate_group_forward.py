@@ -79,9 +79,11 @@ def test_group_forward(n, T, N, K, shift, tile):
     assert _form.setdefault(tile, gemm[0]) == gemm[0] and len(set(_form.values())) == len(_form)
 
 
-@pytest.mark.parametrize("n,T,N,K", [(2, 16, 256, 1024), (2, 128, 1024, 1024), (4, 16, 1024, 4096), (3, 16, 2048, 2048), (3, 6000, 1024, 4096)])
+@pytest.mark.parametrize("n,T,N,K", [(2, 16, 256, 1024), (2, 128, 1024, 1024), (4, 16, 1024, 4096), (3, 16, 2048, 2048), (3, 6000, 1024, 4096), (2, 6274, 2048, 4096),
+                                     (4, 2048, 8192, 8192)])
 def test_a_launch_each(n, T, N, K):
-    """Small layers, whose own kernels take less than a round of the tiled GEMM, and long rows in rounds that are not full."""
+    """Small layers, whose own kernels take less than a round of the tiled GEMM, long rows in rounds that are not full (tiles of 128 and of 256
+    tokens), and weights that do not fit the memory-side cache together."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     gb, b, run = _calibrate(n, T, N, K)
