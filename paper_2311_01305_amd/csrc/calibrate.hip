@@ -185,12 +185,12 @@ static size_t calibrate_ws_bytes(int64_t T, int64_t K, int64_t N, int copies)
 }
 size_t calibrate_ws_bytes(int64_t T, int64_t K, int64_t N) { return calibrate_ws_bytes(T, K, N, sum_copies(K)); }
 
-// a workspace with room for one copy only does with that
+// one copy of the code sums for few tokens, and in a workspace with no room for more
 static int copies_in(const aweq_calib_layer& l, const aweq_calib_weight* w, int n)
 {
     int64_t N = 0;
     for (int i = 0; i < n; ++i) N += w[i].N;
-    return l.ws_bytes >= calibrate_ws_bytes(l.T, l.K, N) ? sum_copies(l.K) : 1;
+    return l.T > copies_tokens(l.K) && l.ws_bytes >= calibrate_ws_bytes(l.T, l.K, N) ? sum_copies(l.K) : 1;
 }
 
 // no buffer that is written shares a byte with another buffer

@@ -37,6 +37,10 @@ constexpr int kRangeCols = 32;   // channels behind a piece
 constexpr int64_t kCopiesK = 1024;
 constexpr int kMostCopies = 4;
 inline int sum_copies(int64_t K) { return K <= kCopiesK ? kMostCopies : 1; }
+// Up to so many tokens one copy: few blocks add to a column, and three copies less have to be zeroed, then read by every wavefront of the pass over the
+// weights (us, whole calibrations of 512 channels, four -> one: 256 tokens K = 512 18.6 -> 17.7, K = 1024 20.6 -> 18.9, 1024 tokens 18.8 -> 18.6 and 22.0 -> 20.8,
+// 1536 tokens 19.4 -> 19.5 and 23.1 -> 22.1, 2048 tokens 19.9 -> 20.6 and 23.2 -> 23.3, 4096 tokens 22.6 -> 25.4 and 25.3 -> 25.6; binary32 within 1 % of the same)
+inline int64_t copies_tokens(int64_t K) { return K <= 512 ? 1280 : 2048; }
 struct RangeParts {
     const float* ext;
     int blocks;
