@@ -265,7 +265,8 @@ static bool fused_front(const aweq_calib_layer& l, const aweq_calib_weight* w, i
     return l.ws_bytes >= calibrate_ws_bytes(l.T, l.K, N, 1) && buffers_apart(l, w, n);
 }
 
-static int run_front(const aweq_calib_layer& l, const aweq_calib_weight* w, int n, FinishArgs& fin, hipStream_t st)
+// pass: the quantizer adds its sums up, to what the merge zeroes
+static int run_front(const aweq_calib_layer& l, const aweq_calib_weight* w, int n, bool pass, FinishArgs& fin, hipStream_t st)
 {
     int64_t rows[kSources] = {l.T}, N = 0;
     for (int i = 0; i < n; ++i) { rows[1 + i] = w[i].N; N += w[i].N; }
@@ -292,8 +293,8 @@ static int run_front(const aweq_calib_layer& l, const aweq_calib_weight* w, int 
     const unsigned blocks = (unsigned)cdiv(l.K, kMergeCols);
     const MergeArgs m = {a.pmin, a.pmax, a.psum, p.x_slices, p.slices, l.K, (uint64_t)l.T, (uint64_t)N, l.enable_awe, l.xmin, l.xmax, l.r_x,
                          l.wmin, l.wmax, l.r_w, l.s, l.inv_s, l.mu_xhat, l.xsum, l.count, l.wcount, reinterpret_cast<float*>(l.ws),
-                         l.w8a8 ? reinterpret_cast<int32_t*>(reinterpret_cast<char*>(l.ws) + ext_bytes(l.K)) : nullptr,
-                         l.w8a8 && l.forward ? l.rowsum_x : nullptr, copies, l.status};
+                         pass && l.w8a8 ? reinterpret_cast<int32_t*>(reinterpret_cast<char*>(l.ws) + ext_bytes(l.K)) : nullptr,
+                         pass && l.w8a8 && l.forward && quant_act_adds_rows(l.K) ? l.rowsum_x : nullptr, copies, l.status};
     calib_merge<<<blocks, kMergeCols * kMergeParts, 0, st>>>(m);
     fin = {{m.ext, (int)blocks, l.xhat_range, l.act_step, l.act_zero}, l.r_x, l.r_w, l.R_x, l.R_w, l.p_x, l.p_w, nullptr, nullptr, l.status};
     return launch_status();
@@ -327,7 +328,7 @@ static int run_calibration(const aweq_calib_layer& l, const aweq_calib_weight* w
     int rc;
     FinishArgs fin;
     if (front) {
-        rc = run_front(l, w, n, fin, st);
+        rc = run_front(l, w, n, pass, fin, st);
         if (rc != AWEQ_OK) return rc;
     }
     if (pass) {

@@ -452,6 +452,8 @@ static QaPlan launch_plan(int64_t T, int64_t K, bool f16, bool sums, bool added)
     return p;
 }
 
+bool quant_act_adds_rows(int64_t K) { return panel_count(K) > kQaPanels; }
+
 // workspace: per-slice column sums [slices][K] int32, then (several column chunks only) per-chunk
 // row sums [chunks][T] int32
 size_t quant_act_ws_bytes(int64_t T, int64_t K)
