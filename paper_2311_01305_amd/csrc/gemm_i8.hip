@@ -1058,7 +1058,9 @@ static int plan_tiled(GemmArgs& g, bool& half, double& cost, int64_t& blocks)
 // 2048 of 700 tokens 77.8 -> 59.2, two 1024 x 1024 of 2048 tokens 46.8 -> 39.3, four 1024 x 4096 of 1024 tokens 88.8 -> 71.8; against it two
 // 1024 x 1024 of 128 tokens 31.0 -> 35.2, two 512 x 512 of 512 tokens 27.1 -> 30.2, three 3072 x 3072 of 16 tokens 70.9 -> 77.3, four 1024 x 8192 of 16
 // tokens 90.6 -> 106.)
-constexpr double kTiledFixed = 3.0, kFewFixed = 1.7, kFewToken = 0.25e-6;
+// One launch of few panels takes kTiledLeast (two weights of up to 104 values a row: 36 x 104 of 408 tokens 25.5 -> 27.4, 976 x 80 of 10 tokens 25.2 -> 27.0,
+// but three 28.0 -> 26.8).
+constexpr double kTiledFixed = 3.0, kTiledLeast = 4.2, kFewFixed = 1.7, kFewToken = 0.25e-6;
 constexpr double kFewShare[] = {0.75, 1.0, 0.88, 0.96, 0.92, 0.96};
 int launch_gemm_i8_group(GroupArgs& g, int n, hipStream_t st)
 {
@@ -1083,7 +1085,8 @@ int launch_gemm_i8_group(GroupArgs& g, int n, hipStream_t st)
     const bool by_few = few.cost <= mid.cost && few.cost < tiled, by_tiles = !by_few && mid.cost >= tiled;
     const double each = by_few ? kFewFixed + (double)(g.T * g.K) * kFewToken + kFewShare[few.tile] * few.cost * us
                                : kTiledFixed + (by_tiles ? tiled : mid.cost) * us;
-    if (kTiledFixed + kTiledRoundCost * cost * us > n * each) return AWEQ_ERR_SHAPE;
+    const double together = kTiledFixed + kTiledRoundCost * cost * us;
+    if ((together > kTiledLeast ? together : kTiledLeast) > n * each) return AWEQ_ERR_SHAPE;
     // In as many rounds as launches of their own take.  One of 256-token tiles a weight that leaves compute units idle runs at a higher clock than the
     // full rounds of one launch, which loses the more the longer the rows and the fewer the tiles (two weights 4276 x 8624 of 2890 tokens, 204 tiles,
     // 347 -> 367, 2048 x 4096 of 6274, 200, 159 -> 168, but 3796 x 3144 of 3385, 210, 158 -> 153, and full rounds 2048 x 2048 of 4096 tokens 110 -> 105);

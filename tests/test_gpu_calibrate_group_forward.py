@@ -55,7 +55,7 @@ _form = {}   # tokens of a tile: the kernel
 
 
 # (tokens of a tile as the plan has it)
-@pytest.mark.parametrize("n,T,N,K,shift,tile", [(2, 700, 256, 64, 0.0, 128), (3, 1000, 260, 512, 0.0, 128), (4, 2100, 508, 136, 0.0, 128),
+@pytest.mark.parametrize("n,T,N,K,shift,tile", [(3, 700, 256, 64, 0.0, 128), (3, 1000, 260, 512, 0.0, 128), (4, 2100, 508, 136, 0.0, 128),
                                                 (3, 2048, 1024, 1024, 0.0, 128), (2, 1537, 2300, 640, 0.0, 128), (3, 8200, 768, 320, 0.0, 128),
                                                 (2, 5000, 4092, 128, 0.0, 128), (2, 1500, 1280, 256, 40.0, 128), (2, 4096, 2048, 64, 0.0, 256),
                                                 (2, 4000, 2044, 64, 0.0, 256), (2, 8192, 4096, 64, 0.0, 256), (3, 4000, 2300, 72, 0.0, 256),
@@ -79,7 +79,7 @@ def test_group_forward(n, T, N, K, shift, tile):
     assert _form.setdefault(tile, gemm[0]) == gemm[0] and len(set(_form.values())) == len(_form)
 
 
-@pytest.mark.parametrize("n,T,N,K", [(2, 16, 256, 1024), (2, 128, 1024, 1024), (4, 16, 1024, 4096), (3, 16, 2048, 2048), (3, 6000, 1024, 4096), (2, 6274, 2048, 4096),
+@pytest.mark.parametrize("n,T,N,K", [(2, 700, 256, 64), (2, 10, 976, 80), (2, 16, 256, 1024), (2, 128, 1024, 1024), (4, 16, 1024, 4096), (3, 16, 2048, 2048), (3, 6000, 1024, 4096), (2, 6274, 2048, 4096),
                                      (4, 2048, 8192, 8192)])
 def test_a_launch_each(n, T, N, K):
     """Small layers, whose own kernels take less than a round of the tiled GEMM, long rows in rounds that are not full (tiles of 128 and of 256
