@@ -58,12 +58,16 @@ constexpr unsigned kQaXcds = 8;                         // workgroup id % 8 name
 // 16384 x 16384 175 -> 164, 5000 x 22016 95 -> 83; binary32 7419 x 4096 41.4 -> 36.5, 2048 x 512 10.5 -> 9.1; 262144 x 8192, at the memory's rate,
 // 1178 -> 1174).  Four groups take 147 registers, three wavefronts to a SIMD: 63.0 / 32.7 / 158.6 in place of 59.7 / 30.8 / 163.4; one group
 // 64 / 32 / 170.
-template <bool F16, bool SUMS, bool KEEP>
+// ADD: Step and Z come from the pieces of the range, and the sums go straight to their places, whole lines to an instruction: over tokens to one of
+// `copies` rows, a row's, where several blocks have it, to rowsum_x (whole calibrations, us, partial rows and a merge -> this: 14331 x
+// 11008 178.2 -> 177.2, 9000 x 4096 67.1 -> 64.2, 600 x 4096 with the forward 69.2 -> 66.6, 2000 x 16384 273 -> 262, 700 x 21888 108 -> 96.5,
+// binary32 2048 x 512 28.1 -> 24.1).  A form of its own: with both in one kernel the other took up to 0.3 us more.
+template <bool F16, bool SUMS, bool KEEP, bool ADD>
 __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
     const void* __restrict__ X, int64_t T, int64_t K, int64_t ldx, const float* __restrict__ inv_s,
     const float* __restrict__ act_step, const int32_t* __restrict__ act_zero, int8_t* __restrict__ xq,
     int32_t* __restrict__ rowsum_x, int32_t* __restrict__ colsum_part, int rows_per_block, int chunks,
-    unsigned pairs, uint32_t* status, RangeParts range, int added)
+    unsigned pairs, uint32_t* status, RangeParts range, int copies)
 {
     const unsigned pair = (blockIdx.x % kQaXcds) * (gridDim.x / kQaXcds) + blockIdx.x / kQaXcds;
     if (pair >= pairs) return;   // (the grid is rounded up to a multiple of 8)
@@ -115,7 +119,7 @@ __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
     uint32_t st = 0;
     float step;
     int zero;
-    if (range.ext) {   // Step and Z are not there yet: every block finds them, the first one stores them
+    if constexpr (ADD) {   // Step and Z are not there yet: every block finds them, the first one stores them
         __shared__ float slot[2 * kQaWaves];
         const float2 r = parts_extremes<kQaBlock>(range.ext, range.blocks, 2, slot);
         uint32_t range_st = 0;
@@ -264,8 +268,8 @@ __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
 
     if (colsum_part) {
         // lanes l, l ^ 8, l ^ 16, l ^ 32 hold the same columns for different rows; this block's sums over
-        // its row slice (at most 512 rows of codes in [-128, 127]) go to row `slice` of the partial buffer, or are added to one of `added` rows
-        int32_t* const part = colsum_part + (added ? (int)(slice % added) : slice) * K;
+        // its row slice (at most 512 rows of codes in [-128, 127]) go to row `slice` of the partial buffer, or are added to one of `copies` rows
+        int32_t* const part = colsum_part + (ADD ? (int)(slice % copies) : slice) * K;
 #pragma unroll
         for (int j = 0; j < kQaVpt; ++j) {
             int v[8];
@@ -276,7 +280,7 @@ __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
                 v[i] += partner<4>(v[i]);
                 v[i] += partner<5>(v[i]);
             }
-            if (added) {
+            if constexpr (ADD) {
                 // (a wavefront's 64 neighbouring columns in one instruction: lane l the column l / 8 of the eight that unit l % 8 has)
                 int own = v[0];
 #pragma unroll
@@ -298,14 +302,10 @@ __global__ __launch_bounds__(kQaBlock) void quant_act_kernel(
             int tot = 0;
 #pragma unroll
             for (int w = 0; w < kQaWaves; ++w) tot += lds_rs[i][w];
-            if (added && chunks > 1) atomicAdd(rowsum_x + r0 + i, tot);
+            if (ADD && chunks > 1) atomicAdd(rowsum_x + r0 + i, tot);
             else rowsum_x[(int64_t)chunk * T + r0 + i] = tot;
         }
 }
-
-// (added: the sums go straight to their places, whole lines to an instruction; whole calibrations, us, partial rows and a merge -> this: 14331 x
-// 11008 178.2 -> 177.2, 9000 x 4096 67.1 -> 64.2, 600 x 4096 with the forward 69.2 -> 66.6, 2000 x 16384 273 -> 262, 700 x 21888 108 -> 96.5,
-// binary32 2048 x 512 28.1 -> 25.4, but 40000 x 512 95.3 -> 96.1.)
 
 // Fold the per-slice column sums (fixed order, 64-bit) and the per-chunk row sums.  Blocks
 // [0, col_blocks) own 32 columns each: 32 groups of 32 threads take every 32nd slice (few dependent loads
@@ -495,14 +495,16 @@ int launch_quant_act(const void* X, aweq_dtype dt, int64_t T, int64_t K, int64_t
     int32_t* const rs_out = !rowsum_x ? nullptr : (multi && !colsum_added ? rowsum_part : rowsum_x);
     const unsigned pairs = (unsigned)(p.slices * p.chunks);
     const unsigned grid = (unsigned)(cdiv(pairs, kQaXcds) * kQaXcds);
-    const RangeParts parts = range ? *range : RangeParts{};
+    const RangeParts parts = range ? *range : RangeParts{};   // (with colsum_added only)
     // codes that fit the memory-side cache are stored through the caches, where the GEMM finds them; more would only evict each
     // other (int8 forward, us, non-temporal -> cached: 16384 tokens 4096 x 11008 (180 MB) 663 -> 650, 4096 x 16384 (268 MB)
     // 979 -> 967, 12000 tokens 8192 x 16384 1306 -> 1307; the pass alone at 262144 x 8192 (2.1 GB) 1188 -> 1268)
     const bool keep = xq && (int64_t)panel_count(K) * kPanel * T <= kCacheBytes;
-#define AWEQ_QA(F, S, P) quant_act_kernel<F, S, P><<<grid, kQaBlock, 0, st>>>(X, T, K, ldx, inv_s, act_step, act_zero, xq, rs_out, colsum_part, (int)p.rpb, p.chunks, pairs, status, parts, colsum_added ? copies : 0)
-    if (dt == AWEQ_F16) { if (sums) AWEQ_QA(true, true, false); else if (keep) AWEQ_QA(true, false, true); else AWEQ_QA(true, false, false); }
-    else { if (sums) AWEQ_QA(false, true, false); else if (keep) AWEQ_QA(false, false, true); else AWEQ_QA(false, false, false); }
+#define AWEQ_QA(F, S, P, A) quant_act_kernel<F, S, P, A><<<grid, kQaBlock, 0, st>>>(X, T, K, ldx, inv_s, act_step, act_zero, xq, rs_out, colsum_part, (int)p.rpb, p.chunks, pairs, status, parts, copies)
+#define AWEQ_QF(F, A) do { if (sums) AWEQ_QA(F, true, false, A); else if (keep) AWEQ_QA(F, false, true, A); else AWEQ_QA(F, false, false, A); } while (0)
+    if (colsum_added) { if (dt == AWEQ_F16) AWEQ_QF(true, true); else AWEQ_QF(false, true); }
+    else { if (dt == AWEQ_F16) AWEQ_QF(true, false); else AWEQ_QF(false, false); }
+#undef AWEQ_QF
 #undef AWEQ_QA
     if (colsum_added) return launch_status();
     const int col_blocks = colsum_xq ? (int)cdiv(K, kQaMergeCols) : 0;

@@ -4,7 +4,7 @@
 
 namespace aweq {
 
-// range: Step and Z are not known yet, the launch derives and stores them (the panel form).  colsum_added [copies][K], asked for with range: the blocks add
+// range: Step and Z are not known yet, the launch derives and stores them (the panel form).  colsum_added [copies][K], asked for with range and only then: the blocks add
 // their sums over tokens to one of its rows and, where quant_act_adds_rows, a row's sums to rowsum_x, both zero before the launch, and nothing merges them; in the place
 // of colsum_xq and ws.  Fewer than 2^23 tokens.
 int launch_quant_act(const void* X, aweq_dtype dt, int64_t T, int64_t K, int64_t ldx, const float* inv_s,
