@@ -303,6 +303,7 @@ static int run_front(const aweq_calib_layer& l, const aweq_calib_weight* w, int 
 // The forward of layers of one width with binary16 outputs in one launch.  false: nothing was launched.
 static bool group_forward(const aweq_calib_layer& l, const aweq_calib_weight* w, int n, hipStream_t st)
 {
+    static_assert(kMaxMembers <= kGroupMost, "every weight has its operands");
     if (n < 2 || l.dt != AWEQ_F16 || (w[0].N % 4) != 0) return false;
     GroupArgs g = {};
     g.A = l.xq; g.T = l.T; g.N = w[0].N; g.K = l.K; g.out_f16 = 1; g.ldo = w[0].N;

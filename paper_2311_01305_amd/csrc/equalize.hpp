@@ -29,18 +29,6 @@ __device__ __forceinline__ float channel_scale(float x0, float x1, float w0, flo
 // The range over all channels that a calibration's merge kernel leaves in pieces, and where the quantities derived from it go.  The
 // pieces are min / max per block of channels: of the activations, of the weights, of the equalised activations ([6][blocks]).
 constexpr int kRangeCols = 32;   // channels behind a piece
-
-// Copies of the activation codes' column sums that the quantizer's blocks add to in turn: many blocks to a column of a narrow matrix wait for each
-// other (us, whole calibrations, one copy -> four: 65536 tokens 512 x 512 58.4 -> 45.4, 30000 tokens with the forward 74.3 -> 61.8, binary32 2048 tokens 25.5 ->
-// 24.1, 262144 tokens 1024 x 1024 193 -> 187; wider matrices have fewer blocks to a column and the pass over their weights no registers: four copies of
-// 4096 columns 63.0 -> 64.1 with 9000 tokens)
-constexpr int64_t kCopiesK = 1024;
-constexpr int kMostCopies = 4;
-inline int sum_copies(int64_t K) { return K <= kCopiesK ? kMostCopies : 1; }
-// Up to so many tokens one copy: few blocks add to a column, and three copies less have to be zeroed, then read by every wavefront of the pass over the
-// weights (us, whole calibrations of 512 channels, four -> one: 256 tokens K = 512 18.6 -> 17.7, K = 1024 20.6 -> 18.9, 1024 tokens 18.8 -> 18.6 and 22.0 -> 20.8,
-// 1536 tokens 19.4 -> 19.5 and 23.1 -> 22.1, 2048 tokens 19.9 -> 20.6 and 23.2 -> 23.3, 4096 tokens 22.6 -> 25.4 and 25.3 -> 25.6; binary32 within 1 % of the same)
-inline int64_t copies_tokens(int64_t K) { return K <= 512 ? 1280 : 2048; }
 struct RangeParts {
     const float* ext;
     int blocks;

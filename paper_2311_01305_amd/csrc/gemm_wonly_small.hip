@@ -44,7 +44,8 @@ constexpr int small_wave_lds(int rx, int nt) { return (rx == 4 ? 4 * 512 : rx * 
 // and, with two MFMA tiles of tokens, its share of the operand; left out by a branch around each load instead, as tiles of 16 and 32 once did, the
 // compiler waited for more than it needed (us, branches -> this: INT4 6 tokens 4096 x 11008 9.6 -> 8.9, 8 tokens 11008 x 4096 9.8 -> 9.3, 12 tokens
 // 8192 x 8192 13.0 -> 12.5, 20 tokens 4096 x 4096 6.5 -> 6.15; INT3 11 tokens 4096 x 4096 5.5 -> 5.2, 17 tokens
-// 4096 x 11008 12.5 -> 11.7; against it 10 tokens 8192 x 22016 33.5 -> 34.4, INT3 22 tokens 4096 x 2048 4.55 -> 4.72).  The activations of the second half of a
+// 4096 x 11008 12.5 -> 11.7, 22 tokens 4096 x 2048 5.45 -> 5.35; long rows of many channels, where the codes come at the memory's rate either way, within the
+// spread of 2 %: INT4 10 tokens 8192 x 22016 37.8 / 38.2, 12288 x 22016 55.6 / 55.5).  The activations of the second half of a
 // chunk are requested ahead of the next codes (loads return in order, and they are needed first).  A chunk more of codes and activations in flight
 // gained nothing and its registers cost wavefronts (17 tokens 4096 x 11008 INT3 12.6 -> 13.3, one token 8192 x 8192 9.8 -> 10.9).
 // SCALES: kFine: groups that are no multiple of 128 (a lane's 32 codes have one (Step, Z), but the four lanes that share
@@ -345,9 +346,12 @@ SmallPlan plan_small(int64_t T, int64_t N)
     if (T <= 16) return {N > 12288 ? 2 : 1, 0.0};
     // More tokens, 32 per workgroup: as many channels as give the fewest rounds of workgroups, each weighted with what a
     // round was measured to take when a load sat in a branch (8192 x 8192, 17 tokens, us: 19 for 512 workgroups of 16 channels, two per
-    // compute unit, 14 for 256; 17.5 for 32 channels and 27 for 64, one per compute unit; now 18.2, 14.0 and 22.0 for the same 16, 32 and 64,
-    // and the choices are still the fastest of the three: 17 tokens 4096 x 4096 6.2 / 8.1 / 12.5, 11008 x 4096 15.0 / 15.5 / 13.0, 16384 x 4096
-    // 21.2 / 16.8 / 14.0).  64 tokens per workgroup gained nothing (4096 x 4096 10.4 us in 32s, 14.0 in 64s; 22016 x 8192 76 / 75).
+    // compute unit, 14 for 256; 17.5 for 32 channels and 27 for 64, one per compute unit).  Now a compute unit's first, second, third and fourth
+    // workgroup of 16 channels take 8.3, 7.6, 6.4 and 6.8, one of 32 channels 13 - 14, of 64 channels 21 and 27 (17 to 20 tokens; 21 to 24 up to a tenth more).
+    // The line stays: over 1742 shapes of 17 to 24 tokens its choice takes 0.5 % more than the fastest form, in 168 more than 3 % (most: INT3 of 8200 to
+    // 12288 and 16400 to 20000 channels, where 16 a workgroup are the faster form, 18 tokens 19396 x 8448 46.0 / 41.6); weights fitted to these times were 0.2 %
+    // better in the mean and in 89 shapes 2 - 13 % slower (22 tokens 12328 x 8320 24.2 -> 27.2).  64 tokens per workgroup gained nothing
+    // (4096 x 4096 10.4 us in 32s, 14.0 in 64s; 22016 x 8192 76 / 75).
     const int64_t tm = cdiv(T, 32), w1 = cdiv(N, 16) * tm, w2 = cdiv(N, 32) * tm, w4 = cdiv(N, 64) * tm;
     const double c1 = w1 <= 256 ? 14.0 : 19.0 * (double)cdiv(w1, 512), c2 = 17.5 * (double)cdiv(w2, 256), c4 = 27.0 * (double)cdiv(w4, 256);
     if (c1 <= c2 && c1 <= c4) return {1, c1};

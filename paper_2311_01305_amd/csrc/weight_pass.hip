@@ -1,10 +1,11 @@
 // Stages 2b, 3 and 5 of a calibration in one pass over each weight: W_hat = W s (Eq. 3), its codes (Eq. 1-2) and the bias correction
-// (Sec. 3.3, Eq. 11-15), W read once and neither W_hat nor the codes read back.  Bound by memory: 2 + 2 + 1 bytes (8 bits) or
-// 2 + 2 + 1/2 (4 bits) an element of binary16, where the three stages one after the other move 8 / 7.
+// (Sec. 3.3, Eq. 11-15), W read once and neither W_hat nor the codes read back: 2 + 2 + 1 bytes (8 bits) or 2 + 2 + 1/2 (4 bits) an element of
+// binary16, where the three stages one after the other move 8 / 7.  Bound by its vector operations: with all its stores left out a calibration of 14331
+// tokens 4096 x 11008 took 166 us instead of 178.
 //
-// A block (a wavefront of short rows) takes one to four output channels at a time, so that what every channel needs of a column (s, E[x_hat]
-// and, for 8 bits, the digits of the activation codes' sum: 12 or 8 bytes) is read as much less often, and keeps the rows in registers
-// between the extremes and the codes.
+// A block (a wavefront of short rows) takes one to four output channels at a time, so that what every channel needs of a column is read and
+// prepared as much less often (s and E[x_hat], 8 bytes; for 8 bits also the sum of the activation codes, 4 bytes a copy, whose digits are formed here: 12
+// bytes, with four copies of a narrow matrix's sums 24), and keeps the rows in registers between the extremes and the codes.
 //
 // The sums over tokens that the int8 path's correction needs are the column sums of the activation codes times the weight codes:
 // sum_t acc[t,n] = sum_k wq[n,k] colsum_xq[k], the same integers that a GEMM adds up.
@@ -483,15 +484,18 @@ static void launch_rows(PassArgs& a, hipStream_t st)
 // Binary16 of up to 12288 columns, with digits that four rows share, held to 128 registers (whole calibrations of 600 tokens, 256 x 6 x 2 -> 512 x 3 x 4:
 // 4096 x 11008 84.8 -> 83.9, 1000 x 10000 40.1 -> 38.6, 8192 x 12000 185 -> 182.5; with 130 registers 4096 x 11008 93.0; one register is spilled there, in
 // binary32 many).  Up to 1024 columns a wavefront to a row, to two rows of more than 2048, which share what they read of a column (whole calibrations, one
-// row -> two: 2048 tokens 11008 x 1024 45.1 -> 41.8, 512 tokens 11008 x 512 34.4 -> 32.1, binary32 2048 tokens 4096 x 768 29.9 -> 28.9, 3072 x 256
-// 21.6 -> 21.3, but 6000 tokens 2048 x 1024 28.8 -> 29.5; four rows 600 tokens 22016 x 512 44.5 -> 43.0, binary32 22016 x 1024 79.9 -> 82.6).
+// row -> two: 64 tokens 22016 x 256 45.5 -> 39.0, 512 tokens 11008 x 512 33.9 -> 31.4, 2048 tokens 11008 x 1024 44.9 -> 42.1, binary32 2048 tokens 4096 x 768
+// 31.2 -> 30.3; 2052 rows within 2 % either way, 6000 tokens 2048 x 1024 28.8 -> 29.5; four rows 600 tokens 22016 x 512 44.5 -> 43.0, binary32 22016 x 1024
+// 79.9 -> 82.6).
 template <bool F16, bool LINES>
 static void launch_rows_for(PassArgs& a, hipStream_t st)
 {
+    constexpr int64_t kShortK = kWave * 2 * 8;   // columns that a wavefront's two units a lane hold
+    static_assert(kCopiesK <= kShortK, "only a wavefront of short rows adds copies up");
     int64_t N = 0;
     for (int i = 0; i < a.n; ++i) N += a.m[i].N;
-    if (a.K <= kCopiesK && N <= 2048) launch_rows<F16, LINES, 64, 2, 1>(a, st);
-    else if (a.K <= kCopiesK) launch_rows<F16, LINES, 64, 2, 2>(a, st);
+    if (a.K <= kShortK && N <= 2048) launch_rows<F16, LINES, 64, 2, 1>(a, st);
+    else if (a.K <= kShortK) launch_rows<F16, LINES, 64, 2, 2>(a, st);
     else if (a.K <= 4096) launch_rows<F16, LINES, 256, 2, 4>(a, st);
     else if (a.K <= 8192) launch_rows<F16, LINES, 256, 4, F16 ? 4 : 2>(a, st);
     else if (a.K <= 12288) {

@@ -7,6 +7,19 @@ namespace aweq {
 
 constexpr int kMaxMembers = 4;   // weights that share one input
 
+// Copies of the activation codes' column sums that the quantizer's blocks add to in turn: many blocks to a column of a narrow matrix wait for each
+// other (us, whole calibrations, one copy -> four: 65536 tokens 512 x 512 58.4 -> 45.4, 30000 tokens with the forward 74.3 -> 61.8, binary32 2048 tokens 25.5 ->
+// 24.1, 262144 tokens 1024 x 1024 193 -> 187).  Beyond 1024 columns, where the pass over the weights has no registers for more, one: four copies of 4096
+// columns 63.0 -> 64.1 with 9000 tokens; with one copy such calls wait too, but less than a merge takes (partial rows and a merge -> one copy: 1032 columns of
+// 32768 / 131072 / 262144 tokens 56.8 -> 52.9 / 152 -> 147 / 270 -> 264, 2048 columns 71.1 -> 66.0 / 201 -> 197 / 362 -> 360).
+constexpr int64_t kCopiesK = 1024;
+constexpr int kMostCopies = 4;
+inline int sum_copies(int64_t K) { return K <= kCopiesK ? kMostCopies : 1; }
+// Up to so many tokens one copy: few blocks add to a column, and three copies less have to be zeroed, then read by every wavefront of the pass over the
+// weights (us, whole calibrations of 512 channels, four -> one: 256 tokens K = 512 18.6 -> 17.7, K = 1024 20.6 -> 18.9, 1024 tokens 18.8 -> 18.6 and 22.0 -> 20.8,
+// 1536 tokens 19.4 -> 19.5 and 23.1 -> 22.1, 2048 tokens 19.9 -> 20.6 and 23.2 -> 23.3, 4096 tokens 22.6 -> 25.4 and 25.3 -> 25.6; binary32 within 1 % of the same)
+inline int64_t copies_tokens(int64_t K) { return K <= 512 ? 1280 : 2048; }
+
 struct PassMember {
     const void* W;
     void* W_hat;

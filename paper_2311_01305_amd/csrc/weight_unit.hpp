@@ -151,6 +151,7 @@ template <int BITS, bool DIFF = false>
 __device__ __forceinline__ void unit_words(const float x[8], const ActParams& p, bool screened, uint32_t& w0, uint32_t& w1,
                                            uint32_t& st, float* diff = nullptr)
 {
+    static_assert(BITS != 8 || !DIFF, "8-bit codes are clamped by their conversion only, after the differences");
     constexpr int qmax = (1 << BITS) - 1;
     w0 = 0;
     w1 = 0;
